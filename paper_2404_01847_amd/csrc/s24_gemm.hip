@@ -8,7 +8,7 @@
 //   dense  NT  Y = X W^T (Eq. 1, first GEMM; the comparison kernel): v_mfma_f32_32x32x16_{bf16,f16}
 //   dense  TN  dW = dY^T X (Eq. 1, third GEMM): both operands copied as they lie in memory, k-contiguous
 //              fragments by ds_read_b64_tr_b16; masked decay (Eq. 10) as an optional epilogue
-//   fp32       one-thread-per-output kernels for the small checking workload (no fp32 sparse instruction exists)
+// fp32 data takes the kernels of s24_gemm_f32.hip.
 //
 // Register layout of the sparse instruction (one 32x32 tile, 32 of k):
 // lane l holds for A row l%32 the eight kept values of k in [16*(l/32),
@@ -19,7 +19,7 @@
 // lane's index half, and the chunk-major storage of the compressed operand
 // (vals[K/64][M][32], meta[K/64][M][4]) makes the 64-byte value run and the
 // four index words of one row and chunk contiguous, rows back to back.
-#include "s24_common.h"
+#include "s24_gemm_f32.h"
 
 namespace {
 
@@ -1391,69 +1391,6 @@ __global__ __launch_bounds__(THREADS) void spmm_tn_big_kernel(const uint16_t *__
 }
 }  // namespace sptn
 
-// one thread per output, fp32 data (no fp32 sparse matrix instruction exists)
-template <bool ACCUM>
-__global__ __launch_bounds__(kThreads) void spmm_tn_f32_kernel(const float *__restrict__ Av, const uint16_t *__restrict__ Am,
-                                                               const float *__restrict__ X, float *__restrict__ dW,
-                                                               int64_t T, int64_t M, int64_t N)
-{
-    const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (idx >= M * N) return;
-    const int64_t m = idx / N, n = idx - m * N;
-    float acc = 0.0f;
-    for (int64_t g = 0; g < T / 4; ++g) {
-        const int64_t cr = (g / 16) * M + m;  // chunk-major storage: (chunk, row)
-        const unsigned nib = (Am[cr * 4 + (g & 15) / 4] >> (4 * (g & 3))) & 0xFu;
-        acc = fmaf(Av[cr * 32 + 2 * (g & 15)], X[(4 * g + (nib & 3u)) * N + n], acc);
-        acc = fmaf(Av[cr * 32 + 2 * (g & 15) + 1], X[(4 * g + (nib >> 2)) * N + n], acc);
-    }
-    dW[idx] = ACCUM ? dW[idx] + acc : acc;
-}
-
-// ------------------------------------------------------------------ fp32 fallbacks (small correctness workload)
-// One thread per output element, plain fp32 FMA; no matrix-core claim.
-template <bool ACCUM>
-__global__ __launch_bounds__(kThreads) void spmm_nt_f32_kernel(const float *__restrict__ B, const float *__restrict__ Av,
-                                                               const uint16_t *__restrict__ Am, float *__restrict__ Out,
-                                                               int64_t N, int64_t K, int64_t M, const float *__restrict__ bias)
-{
-    const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (idx >= N * M) return;
-    const int64_t n = idx / M, m = idx - n * M;
-    float acc = 0.0f;
-    for (int64_t g = 0; g < K / 4; ++g) {
-        const int64_t cr = (g / 16) * M + m;  // chunk-major storage: (chunk, row)
-        const unsigned nib = (Am[cr * 4 + (g & 15) / 4] >> (4 * (g & 3))) & 0xFu;
-        acc = fmaf(Av[cr * 32 + 2 * (g & 15)], B[n * K + 4 * g + (nib & 3u)], acc);
-        acc = fmaf(Av[cr * 32 + 2 * (g & 15) + 1], B[n * K + 4 * g + (nib >> 2)], acc);
-    }
-    if (bias != nullptr) acc += bias[m];
-    Out[idx] = ACCUM ? Out[idx] + acc : acc;
-}
-
-__global__ __launch_bounds__(kThreads) void dense_nt_f32_kernel(const float *__restrict__ X, const float *__restrict__ W,
-                                                                float *__restrict__ Y, int64_t N, int64_t K, int64_t M)
-{
-    const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (idx >= N * M) return;
-    const int64_t n = idx / M, m = idx - n * M;
-    float acc = 0.0f;
-    for (int64_t k = 0; k < K; ++k) acc = fmaf(X[n * K + k], W[m * K + k], acc);
-    Y[idx] = acc;
-}
-
-template <bool ACCUM>
-__global__ __launch_bounds__(kThreads) void dense_tn_f32_kernel(const float *__restrict__ dY, const float *__restrict__ X,
-                                                                float *__restrict__ dW, int64_t T, int64_t M, int64_t N)
-{
-    const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (idx >= M * N) return;
-    const int64_t m = idx / N, n = idx - m * N;
-    float acc = 0.0f;
-    for (int64_t t = 0; t < T; ++t) acc = fmaf(dY[t * M + m], X[t * N + n], acc);
-    dW[idx] = ACCUM ? dW[idx] + acc : acc;
-}
-
 __global__ __launch_bounds__(kThreads) void fill_zero_kernel(float *__restrict__ p, int64_t n)
 {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
@@ -1543,13 +1480,8 @@ int launch_spmm(const void *B, const void *Av, const uint16_t *Am, void *Out, in
     if (N == 0 || M == 0) return S24_OK;
     const bool accum = beta != 0.0f;
     if (dt == S24_F32) {
-        const dim3 grid(ceil_div(N * M, kThreads)), block(kThreads);
-        auto *b = static_cast<const float *>(B), *av = static_cast<const float *>(Av);
-        auto *o = static_cast<float *>(Out);
-        auto *d = static_cast<const float *>(bias);
-        if (accum) hipLaunchKernelGGL(spmm_nt_f32_kernel<true>, grid, block, 0, st, b, av, Am, o, N, K, M, d);
-        else hipLaunchKernelGGL(spmm_nt_f32_kernel<false>, grid, block, 0, st, b, av, Am, o, N, K, M, d);
-        return s24_launch_status();
+        return s24_f32_nt({static_cast<const float *>(B), static_cast<const float *>(Av), Am, static_cast<float *>(Out), nullptr,
+                           static_cast<const float *>(bias), N, K, M, accum, S24_F32_PLAIN, 0}, st);
     }
     auto *b = static_cast<const uint16_t *>(B), *av = static_cast<const uint16_t *>(Av), *d = static_cast<const uint16_t *>(bias);
     auto *o = static_cast<uint16_t *>(Out);
@@ -1653,6 +1585,9 @@ extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t 
 #undef S24_LAUNCH_FWD_GLU
         return s24_launch_status();
     }
+    if (dt == S24_F32)
+        return s24_f32_nt({static_cast<const float *>(X), static_cast<const float *>(vals), meta, static_cast<float *>(GU), static_cast<float *>(H),
+                           static_cast<const float *>(bias), p, q, 2 * f, false, S24_F32_GLU, gate}, st);
     // shapes the fused epilogue does not cover: the GEMM into [p][2f], then the stand-alone activation on its halves
     const int rc2 = launch_spmm(X, vals, meta, GU, p, q, 2 * f, 0.0f, dt, st, bias);
     if (rc2 != S24_OK) return rc2;
@@ -1734,10 +1669,8 @@ extern "C" int s24_spmm_fwd_act(const void *X, const void *vals, const uint16_t 
 #undef S24_LAUNCH_FWD_ACT_MI
         return s24_launch_status();
     }
-    // fp32: the GEMM, then the stand-alone activation
-    const int rc2 = launch_spmm(X, vals, meta, Z, p, q, r, 0.0f, dt, st, bias);
-    if (rc2 != S24_OK) return rc2;
-    return s24_act_fwd(Z, H, p * r, act, dt, st);
+    return s24_f32_nt({static_cast<const float *>(X), static_cast<const float *>(vals), meta, static_cast<float *>(Z), static_cast<float *>(H),
+                       static_cast<const float *>(bias), p, q, r, false, S24_F32_ACT, act}, st);
 }
 
 extern "C" int s24_spmm_bwd_dx_act(const void *dY, const void *valsT, const uint16_t *metaT, const void *Z, void *dZ,
@@ -1784,9 +1717,8 @@ extern "C" int s24_dense_gemm(const void *X, const void *W, void *Y, int64_t p, 
     if (rc != S24_OK || p * r == 0) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (dt == S24_F32) {
-        hipLaunchKernelGGL(dense_nt_f32_kernel, dim3(ceil_div(p * r, kThreads)), dim3(kThreads), 0, st,
-                           static_cast<const float *>(X), static_cast<const float *>(W), static_cast<float *>(Y), p, q, r);
-        return s24_launch_status();
+        return s24_f32_nt({static_cast<const float *>(X), static_cast<const float *>(W), nullptr, static_cast<float *>(Y), nullptr, nullptr, p, q, r,
+                           false, S24_F32_PLAIN, 0}, st);
     }
     auto *x = static_cast<const uint16_t *>(X), *w = static_cast<const uint16_t *>(W);
     auto *y = static_cast<uint16_t *>(Y);
@@ -1908,10 +1840,12 @@ int run_dense_dw(const void *dY, const void *X, float *dW, int64_t p, int64_t q,
         }
         if (fuse) decay_pending = false;
     } else {
-        const dim3 grid(ceil_div(r * q, kThreads)), block(kThreads);
-        auto *a = static_cast<const float *>(dY), *b = static_cast<const float *>(X);
-        if (accum) hipLaunchKernelGGL(dense_tn_f32_kernel<true>, grid, block, 0, st, a, b, dW, p, r, q);
-        else hipLaunchKernelGGL(dense_tn_f32_kernel<false>, grid, block, 0, st, a, b, dW, p, r, q);
+        const bool fuse = decay_pending && wdt == S24_F32;
+        const S24F32TnProblem pr{static_cast<const float *>(dY), static_cast<const float *>(X), static_cast<const float *>(fuse ? W : nullptr),
+                                 nullptr, mask, dW, p, r, q, lambda};
+        const int rc = s24_f32_tn(&pr, 1, accum, st);
+        if (rc != S24_OK) return rc;
+        if (fuse) decay_pending = false;
     }
     const int rc = s24_launch_status();
     if (rc != S24_OK || !decay_pending) return rc;
@@ -1999,9 +1933,23 @@ extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, flo
             launch_dw_batch(batch, 128, accum, decay, dt, st);
             return s24_launch_status();
         }
+        if (dt == S24_F32) {   // one grid for every problem with tokens to contract
+            S24F32TnProblem f[dmatn::kMaxBatch];
+            int n = 0;
+            bool rest = false;
+            for (int i = 0; i < count; ++i) {
+                const s24_dw_problem &pr = problems[i];
+                if (pr.p == 0) rest = true;
+                else if (pr.q * pr.r != 0)
+                    f[n++] = {static_cast<const float *>(pr.dY), static_cast<const float *>(pr.X), static_cast<const float *>(pr.W), nullptr, pr.mask,
+                              pr.dW, pr.p, pr.r, pr.q, pr.lambda};
+            }
+            const int rc = n > 0 ? s24_f32_tn(f, n, accum, st) : S24_OK;
+            if (rc != S24_OK || !rest) return rc;
+        }
         for (int i = 0; i < count; ++i) {
             const s24_dw_problem &pr = problems[i];
-            if (pr.q * pr.r == 0) continue;
+            if (pr.q * pr.r == 0 || (dt == S24_F32 && pr.p != 0)) continue;
             const int rc = run_dense_dw(pr.dY, pr.X, pr.dW, pr.p, pr.q, pr.r, beta, dt, pr.W, dt, pr.mask, pr.lambda, st);
             if (rc != S24_OK) return rc;
         }
@@ -2081,10 +2029,12 @@ extern "C" int s24_spmm_dw(const void *vals, const uint16_t *meta, const void *X
 #undef S24_LAUNCH_SPDW
             if (fuse) decay_pending = false;
         } else {
-            const dim3 grid(ceil_div(r * q, kThreads)), block(kThreads);
-            auto *av = static_cast<const float *>(vals), *x = static_cast<const float *>(X);
-            if (accum) hipLaunchKernelGGL(spmm_tn_f32_kernel<true>, grid, block, 0, st, av, meta, x, dW, p, r, q);
-            else hipLaunchKernelGGL(spmm_tn_f32_kernel<false>, grid, block, 0, st, av, meta, x, dW, p, r, q);
+            const bool fuse = decay_pending && wdt == S24_F32;
+            const S24F32TnProblem pr{static_cast<const float *>(vals), static_cast<const float *>(X), static_cast<const float *>(fuse ? W : nullptr),
+                                     meta, mask, dW, p, r, q, lambda};
+            const int rc1 = s24_f32_tn(&pr, 1, accum, st);
+            if (rc1 != S24_OK) return rc1;
+            if (fuse) decay_pending = false;
         }
     }
     const int rc2 = s24_launch_status();

@@ -1,0 +1,392 @@
+// fp32 GEMMs on the matrix cores: v_mfma_f32_32x32x2_f32 (one lane holds A row l%32 and B column l%32 at k = l/32;
+// accumulator i is row 8*(i/4) + 4*(l/32) + i%4 of column l%32).  There is no fp32 sparse instruction: the compressed
+// operand is expanded to its four columns per group in registers, zeros included.
+//
+// What bounds them is latency, not arithmetic: the fp32 layers are small (512 x 256 x 1024 has 0.27 GFLOP per product,
+// 1.7 us of the unit's 157 TFLOP/s), so the whole product has to be spread over every SIMD of the chip at once.  Each
+// wave therefore owns one 32T x 32T output tile and one SLICE of the contraction axis (KS slices per workgroup, 32 to 64
+// of k each where the grid is small), loads its fragments from global memory straight into registers (a fragment is
+// used by one wave of the workgroup only: LDS staging would buy nothing), and the slices are summed in LDS in a
+// fixed order.  A lane takes its k values as runs of eight of one row (two 16-byte loads), the same runs for both
+// operands; which k an instruction multiplies is free as long as both sides agree.
+#include "s24_gemm_f32.h"
+
+namespace {
+
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+__device__ __forceinline__ f32x16 mma(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+
+// Two kept values and their nibble (i0 | i1 << 2) -> the four values of the group
+__device__ __forceinline__ void expand(float v0, float v1, uint32_t nib, float (&e)[4])
+{
+    const uint32_t i0 = nib & 3u, i1 = nib >> 2;
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) e[i] = i0 == i ? v0 : (i1 == i ? v1 : 0.0f);
+}
+
+// Sum of one float4 over the KS slices' copies of a tile, in slice order.  Slice s of a workgroup's tile w is parked at
+// (w * KS + s) * slice floats.
+template <int KS> __device__ __forceinline__ float4 slice_sum(const float *p, int slice)
+{
+    float4 v = *reinterpret_cast<const float4 *>(p);
+#pragma unroll
+    for (int s = 1; s < KS; ++s) {
+        const float4 o = *reinterpret_cast<const float4 *>(p + s * slice);
+        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+    }
+    return v;
+}
+
+// ------------------------------------------------------------------ NT
+struct NtArgs {
+    const float *B, *Av;
+    const uint16_t *Am;
+    float *Out, *H;
+    const float *bias;
+    int N, K, M, F;   // F: gated features (GLU), else M
+    int tiles_m, tiles;
+};
+
+// SPARSE: A compressed.  EPI / ACT: epilogue.  GLU needs T = 2: a tile takes 32 gate rows and the 32 up rows of the same
+// features.
+template <bool SPARSE, bool ACCUM, int EPI, int ACT, int T, int KS, int WM>
+__global__ __launch_bounds__(64 * KS * WM) void f32_nt_kernel(const NtArgs g)
+{
+    static_assert(EPI != S24_F32_GLU || T == 2, "the gated tile pairs two row blocks");
+    constexpr int TW = 32 * T, PITCH = TW + 4, SLICE = TW * PITCH, THREADS = 64 * KS * WM;
+    __shared__ __attribute__((aligned(16))) float s_red[WM * KS * SLICE];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), ks = wave % KS, wt = wave / KS;
+    const int h = lane >> 5, l = lane & 31;
+    const int t = (int)blockIdx.x * WM + wt;
+    const bool live = t < g.tiles;
+    const int tm = t % g.tiles_m, tn = t / g.tiles_m;
+    constexpr int FM = EPI == S24_F32_GLU ? 32 : TW;   // features of the (gated) output per tile
+    const int m0 = tm * FM, n0 = tn * TW;
+
+    f32x16 acc[T][T];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j) acc[i][j] = f32x16{};
+    if (live) {
+        // rows of this lane (clamped at the edge; such rows are never stored)
+        int arow[T];
+        const float *b[T];
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            arow[i] = EPI == S24_F32_GLU ? i * g.F + min(m0 + l, g.F - 1) : min(m0 + 32 * i + l, g.M - 1);
+            b[i] = g.B + (int64_t)min(n0 + 32 * i + l, g.N - 1) * g.K;
+        }
+        // units of 16 of k: lane half h takes k 8h .. 8h+7 of a unit
+        const int units = g.K / 16, u0 = units * ks / KS, u1 = units * (ks + 1) / KS;
+        struct Frag { float4 a[T][2]; float4 b[T][2]; uint32_t nib[T]; };
+        auto load = [&](int u, Frag &f) {
+            const int k = 16 * u + 8 * h;
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                if constexpr (SPARSE) {   // four kept values of the run's two groups, and their byte of the index words
+                    const int64_t cr = (int64_t)(u >> 2) * g.M + arow[i];
+                    f.a[i][0] = *reinterpret_cast<const float4 *>(g.Av + cr * 32 + 8 * (u & 3) + 4 * h);
+                    f.nib[i] = (uint32_t)g.Am[cr * 4 + (u & 3)] >> (8 * h);
+                } else {
+                    const float *a = g.Av + (int64_t)arow[i] * g.K + k;
+                    f.a[i][0] = *reinterpret_cast<const float4 *>(a);
+                    f.a[i][1] = *reinterpret_cast<const float4 *>(a + 4);
+                }
+                f.b[i][0] = *reinterpret_cast<const float4 *>(b[i] + k);
+                f.b[i][1] = *reinterpret_cast<const float4 *>(b[i] + k + 4);
+            }
+        };
+        auto multiply = [&](const Frag &f) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {   // the run's two groups of four
+                float e[T][4], x[T][4];
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    if constexpr (SPARSE) {
+                        const float4 v = f.a[i][0];
+                        expand(q ? v.z : v.x, q ? v.w : v.y, (f.nib[i] >> (4 * q)) & 0xFu, e[i]);
+                    } else {
+                        const float4 v = f.a[i][q];
+                        e[i][0] = v.x; e[i][1] = v.y; e[i][2] = v.z; e[i][3] = v.w;
+                    }
+                    const float4 w = f.b[i][q];
+                    x[i][0] = w.x; x[i][1] = w.y; x[i][2] = w.z; x[i][3] = w.w;
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int i = 0; i < T; ++i)
+#pragma unroll
+                        for (int j = 0; j < T; ++j) acc[i][j] = mma(e[i][k], x[j][k], acc[i][j]);
+            }
+        };
+        Frag f0, f1;
+        if (u0 < u1) load(u0, f0);
+        int u = u0;
+        for (; u + 1 < u1; u += 2) {   // the next unit's loads go out before the current one is multiplied
+            load(u + 1, f1);
+            multiply(f0);
+            load(min(u + 2, u1 - 1), f0);
+            multiply(f1);
+        }
+        if (u < u1) multiply(f0);
+    }
+    float *part = s_red + wave * SLICE;   // wave = wt * KS + ks
+#pragma unroll
+    for (int j = 0; j < T; ++j)
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4 *>(part + (32 * j + l) * PITCH + 32 * i + 8 * q + 4 * h) =
+                    make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+    __syncthreads();
+    constexpr int QUADS = FM / 4, ITEMS = WM * TW * QUADS;   // four features of one token per item
+#pragma unroll 1
+    for (int it = tid; it < ITEMS; it += THREADS) {
+        const int q = it % QUADS, row = (it / QUADS) % TW, w = it / (QUADS * TW), tt = (int)blockIdx.x * WM + w;
+        const int m = (tt % g.tiles_m) * FM + 4 * q, n = (tt / g.tiles_m) * TW + row;
+        if (tt >= g.tiles || n >= g.N || m >= (EPI == S24_F32_GLU ? g.F : g.M)) continue;   // M, F multiples of 16
+        const float *p = s_red + w * KS * SLICE + row * PITCH + 4 * q;
+        auto finish = [&](const float *src, int feature) {
+            float4 v = slice_sum<KS>(src, SLICE);
+            if (g.bias != nullptr) {
+                const float2 b0 = *reinterpret_cast<const float2 *>(g.bias + feature), b1 = *reinterpret_cast<const float2 *>(g.bias + feature + 2);
+                v.x += b0.x; v.y += b0.y; v.z += b1.x; v.w += b1.y;
+            }
+            float4 *o = reinterpret_cast<float4 *>(g.Out + (int64_t)n * g.M + feature);
+            if (ACCUM) {
+                const float4 old = *o;
+                v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
+            }
+            *o = v;
+            return v;
+        };
+        if constexpr (EPI == S24_F32_GLU) {
+            const float4 z = finish(p, m), u = finish(p + 32, g.F + m);
+            *reinterpret_cast<float4 *>(g.H + (int64_t)n * g.F + m) =
+                make_float4(s24_glu<ACT>(z.x, u.x), s24_glu<ACT>(z.y, u.y), s24_glu<ACT>(z.z, u.z), s24_glu<ACT>(z.w, u.w));
+        } else {
+            const float4 z = finish(p, m);
+            if constexpr (EPI == S24_F32_ACT) {
+                auto act = [](float x) { return ACT == S24_ACT_RELU ? (x > 0.0f ? x : 0.0f) : s24_gelu(x); };
+                *reinterpret_cast<float4 *>(g.H + (int64_t)n * g.M + m) = make_float4(act(z.x), act(z.y), act(z.z), act(z.w));
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------ TN (weight gradients)
+// Both operands are token-major: a lane reads T consecutive columns of one token (the columns of tile block i are
+// T*(l%32) + i), lane half h takes every second token.
+struct TnWindow {
+    const float *A, *X, *Wt;
+    const uint16_t *Am, *mask;
+    float *dW;
+    int T, M, N, tiles_m, first;   // first: the problem's first tile in the grid
+    float lambda;
+};
+constexpr int kMaxTn = 4;
+struct TnArgs {
+    TnWindow w[kMaxTn];
+};
+
+template <int T> struct Run { float v[T]; };
+
+template <bool SPARSE, bool ACCUM, int T, int KS>
+__global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
+{
+    constexpr int TW = 32 * T, PITCH = TW + 4, SLICE = TW * PITCH, THREADS = 64 * KS;
+    __shared__ __attribute__((aligned(16))) float s_red[KS * SLICE];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = lane >> 5, l = lane & 31;
+    int which = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxTn; ++i)
+        if ((int)blockIdx.x >= args.w[i].first) which = i;
+    const TnWindow &g = args.w[which];
+    const int t = (int)blockIdx.x - g.first;
+    const int m0 = (t % g.tiles_m) * TW, n0 = (t / g.tiles_m) * TW;
+    const int M = g.M, N = g.N;
+    f32x16 acc[T][T];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j) acc[i][j] = f32x16{};
+    // columns of this lane, clamped at the edge (M and N are multiples of 16: a run of T is all in or all out)
+    const int mc = min(m0 + T * l, M - T), nc = min(n0 + T * l, N - T);
+    if constexpr (SPARSE) {
+        // A compressed along the tokens: a lane reads one group (two kept values, one nibble) of its T rows and expands it;
+        // lane half h takes every second group of four tokens
+        const int groups = g.T / 4, half = groups / 2, p0 = half * ks / KS, p1 = half * (ks + 1) / KS;   // T is a multiple of 64
+        for (int p = p0; p < p1; ++p) {
+            const int gr = 2 * p + h;
+            float e[T][4];
+            Run<T> x[4];
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                const int64_t cr = (int64_t)(gr >> 4) * M + mc + i;
+                const float2 v = *reinterpret_cast<const float2 *>(g.A + cr * 32 + 2 * (gr & 15));
+                expand(v.x, v.y, ((uint32_t)g.Am[cr * 4 + ((gr & 15) >> 2)] >> (4 * (gr & 3))) & 0xFu, e[i]);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[k] = *reinterpret_cast<const Run<T> *>(g.X + (int64_t)(4 * gr + k) * N + nc);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+#pragma unroll
+                    for (int j = 0; j < T; ++j) acc[i][j] = mma(e[i][k], x[k].v[j], acc[i][j]);
+        }
+    } else {
+        constexpr int U = 8;   // token pairs loaded together
+        const int pairs = (g.T + 1) / 2, p0 = pairs * ks / KS, p1 = pairs * (ks + 1) / KS;
+        const float *a = g.A + mc, *x = g.X + nc;
+        int p = p0;
+        Run<T> av[U], xv[U];
+        for (; p + U <= p1 && 2 * (p + U) <= g.T; p += U) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t tok = 2 * (p + u) + h;
+                av[u] = *reinterpret_cast<const Run<T> *>(a + tok * M);
+                xv[u] = *reinterpret_cast<const Run<T> *>(x + tok * N);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+#pragma unroll
+                    for (int j = 0; j < T; ++j) acc[i][j] = mma(av[u].v[i], xv[u].v[j], acc[i][j]);
+        }
+        for (; p < p1; ++p) {   // rest of the slice; the token past an odd count contributes zero
+            const int tok = 2 * p + h;
+            const int64_t tc = min(tok, g.T - 1);
+            Run<T> av1 = *reinterpret_cast<const Run<T> *>(a + tc * M);
+            const Run<T> xv1 = *reinterpret_cast<const Run<T> *>(x + tc * N);
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+                if (tok >= g.T) av1.v[i] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int j = 0; j < T; ++j) acc[i][j] = mma(av1.v[i], xv1.v[j], acc[i][j]);
+        }
+    }
+    // park: matrix row r of block i is output row T*r + i, column c of block j output column T*c + j
+    float *part = s_red + ks * SLICE;
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int r = 8 * (e / 4) + 4 * h + (e & 3);
+            Run<T> o;
+#pragma unroll
+            for (int j = 0; j < T; ++j) o.v[j] = acc[i][j][e];
+            *reinterpret_cast<Run<T> *>(part + (T * r + i) * PITCH + T * l) = o;
+        }
+    __syncthreads();
+    constexpr int QUADS = TW / 4, ITEMS = TW * QUADS;
+#pragma unroll 1
+    for (int it = tid; it < ITEMS; it += THREADS) {
+        const int q = it % QUADS, row = it / QUADS, m = m0 + row, n = n0 + 4 * q;
+        if (m >= M || n >= N) continue;
+        float4 v = slice_sum<KS>(s_red + row * PITCH + 4 * q, SLICE);
+        float4 *o = reinterpret_cast<float4 *>(g.dW + (int64_t)m * N + n);
+        if (ACCUM) {
+            const float4 old = *o;
+            v.x = old.x + v.x; v.y = old.y + v.y; v.z = old.z + v.z; v.w = old.w + v.w;
+        }
+        if (g.Wt != nullptr) {   // masked decay: the one fused multiply-add of the stand-alone kernel
+            const float4 w = *reinterpret_cast<const float4 *>(g.Wt + (int64_t)m * N + n);
+            const uint32_t keep = (uint32_t)g.mask[(int64_t)(m >> 2) * (N >> 2) + (n >> 2)] >> (4 * (m & 3));
+            if (!(keep & 1u)) v.x = fmaf(g.lambda, w.x, v.x);
+            if (!(keep & 2u)) v.y = fmaf(g.lambda, w.y, v.y);
+            if (!(keep & 4u)) v.z = fmaf(g.lambda, w.z, v.z);
+            if (!(keep & 8u)) v.w = fmaf(g.lambda, w.w, v.w);
+        }
+        *o = v;
+    }
+}
+
+inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+template <bool SPARSE, bool ACCUM, int EPI, int ACT, int T, int KS, int WM>
+int launch_nt(const S24F32Nt &g, hipStream_t st)
+{
+    NtArgs a{g.B, g.Av, g.Am, g.Out, g.H, g.bias, (int)g.N, (int)g.K, (int)g.M, (int)(EPI == S24_F32_GLU ? g.M / 2 : g.M), 0, 0};
+    const int64_t tiles_m = EPI == S24_F32_GLU ? ceil_div(a.F, 32) : ceil_div(a.M, 32 * T), tiles = tiles_m * ceil_div(a.N, 32 * T);
+    S24_REQUIRE(tiles < (1ll << 31), S24_ERR_SHAPE);
+    a.tiles_m = (int)tiles_m;
+    a.tiles = (int)tiles;
+    hipLaunchKernelGGL((f32_nt_kernel<SPARSE, ACCUM, EPI, ACT, T, KS, WM>), dim3((unsigned)ceil_div(tiles, WM)), dim3(64 * KS * WM), 0, st, a);
+    return s24_launch_status();
+}
+
+// Tile and slices by the size of the product (the slices decide the order of the sum, so the rule looks at the whole
+// product only: a fused epilogue gives the bits of the plain product).  Measured in us (N x K x M: 8 slices of a 32-tile
+// / 4 slices of a 32-tile / 4 slices of a 64-tile; one thread per output before):
+//   512 x 256 x 1024: 7.3 / 6.5 / 10.0 (109)      512 x 1024 x 256: 9.2 / 10.1 / 26.3 (114)
+//   333 x 1792 x 448: 13.4 / 15.3 / 45.4 (281)    1024 x 768 x 3072: 66 / 61 / 53 (2480)     2048 x 1024 x 4096: 228 / 199 / 168 (8608)
+// The 64-tile reads half the operand bytes per product, which only counts once its own grid fills the chip.
+template <bool SPARSE, bool ACCUM, int EPI, int ACT> int choose_nt(const S24F32Nt &g, hipStream_t st)
+{
+    const bool deep = g.K >= 512 && ceil_div(g.M, 32) * ceil_div(g.N, 32) <= 256;   // few tiles, long sums: 8 slices
+    if constexpr (EPI == S24_F32_GLU) {
+        if (deep) return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 8, 1>(g, st);
+        return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 4, 1>(g, st);
+    } else {
+        if (deep) return launch_nt<SPARSE, ACCUM, EPI, ACT, 1, 8, 1>(g, st);
+        if (ceil_div(g.M, 64) * ceil_div(g.N, 64) < 512) return launch_nt<SPARSE, ACCUM, EPI, ACT, 1, 4, 1>(g, st);
+        return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 4, 1>(g, st);
+    }
+}
+
+template <bool SPARSE, int T> int launch_tn(TnArgs &a, int64_t tiles, bool accum, hipStream_t st)
+{
+    constexpr int KS = 8;
+    const dim3 grid((unsigned)tiles), block(64 * KS);
+    if (accum) hipLaunchKernelGGL((f32_tn_kernel<SPARSE, true, T, KS>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((f32_tn_kernel<SPARSE, false, T, KS>), grid, block, 0, st, a);
+    return s24_launch_status();
+}
+}  // namespace
+
+int s24_f32_nt(const S24F32Nt &g, hipStream_t st)
+{
+    if (g.Am == nullptr) return choose_nt<false, false, S24_F32_PLAIN, 0>(g, st);   // dense comparison GEMM
+    if (g.accum) return choose_nt<true, true, S24_F32_PLAIN, 0>(g, st);
+    if (g.epilogue == S24_F32_ACT)
+        return g.act == S24_ACT_RELU ? choose_nt<true, false, S24_F32_ACT, S24_ACT_RELU>(g, st) : choose_nt<true, false, S24_F32_ACT, S24_ACT_GELU_ERF>(g, st);
+    if (g.epilogue == S24_F32_GLU)
+        return g.act == S24_GATE_SILU ? choose_nt<true, false, S24_F32_GLU, S24_GATE_SILU>(g, st) : choose_nt<true, false, S24_F32_GLU, S24_GATE_GELU_ERF>(g, st);
+    return choose_nt<true, false, S24_F32_PLAIN, 0>(g, st);
+}
+
+// 32-tiles until the 64-tile's own grid is three workgroups per compute unit: 512 tokens, 1024 x 256 out: 8.1 against 15.1 us
+// (58 with one thread per output); 1024 tokens, 3072 x 768: 78 against 84 (1282); 2048 tokens, 4096 x 1024: 248 against 214.
+int s24_f32_tn(const S24F32TnProblem *pr, int count, bool accum, hipStream_t st)
+{
+    int64_t tiles[2] = {0, 0};
+    TnArgs a{};
+    for (int T = 1; T <= 2; ++T)
+        for (int i = 0; i < count; ++i) tiles[T - 1] += ceil_div(pr[i].M, 32 * T) * ceil_div(pr[i].N, 32 * T);
+    const int T = tiles[1] < 768 ? 1 : 2;
+    S24_REQUIRE(tiles[T - 1] < (1ll << 31), S24_ERR_SHAPE);
+    int64_t first = 0;
+    for (int i = 0; i < kMaxTn; ++i) {
+        if (i < count) {
+            const int64_t tm = ceil_div(pr[i].M, 32 * T);
+            a.w[i] = TnWindow{pr[i].A, pr[i].X, pr[i].Wt, pr[i].Am, pr[i].mask, pr[i].dW, (int)pr[i].T, (int)pr[i].M, (int)pr[i].N, (int)tm, (int)first, pr[i].lambda};
+            first += tm * ceil_div(pr[i].N, 32 * T);
+        } else {
+            a.w[i] = a.w[count - 1];
+            a.w[i].first = 0x7FFFFFFF;   // no tile of the grid
+        }
+    }
+    if (pr[0].Am != nullptr) return T == 1 ? launch_tn<true, 1>(a, first, accum, st) : launch_tn<true, 2>(a, first, accum, st);
+    return T == 1 ? launch_tn<false, 1>(a, first, accum, st) : launch_tn<false, 2>(a, first, accum, st);
+}

@@ -1,0 +1,91 @@
+"""The kernel variants that the library picks by size, each at the edges of its tiles and of the sizes it is picked for,
+against the CPU oracle and with the tolerances of tests/util.py."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import s24_inputs as si
+from util import F32_TOL, assert_close, dev, dev_bf16, host_bits, host_f64, tol_for, torch_dtype
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def s24():
+    import paper_2404_01847_amd as lib
+    lib.lib()
+    return lib
+
+
+def compressed(W):
+    """Oracle's compressed operands of a weight, in the library's storage, on the GPU: (vals, meta), (valsT, metaT)."""
+    c = oracle.compress(W, oracle.transposable_mask(W))
+    (v, m), (vt, mt) = oracle.pack(c[0], c[1]), oracle.pack(c[2], c[3])
+    return c, (dev_bf16(v), dev(m)), (dev_bf16(vt), dev(mt))
+
+
+# ------------------------------------------------------------------ fp32 on the matrix cores
+F32_NT = [
+    # (p, q, r): four slices of a 32-tile; eight slices (deep, few tiles); four slices of a 64-tile; ragged edges of each
+    (33, 64, 48), (31, 128, 2064), (40, 576, 80), (1, 1024, 16), (1040, 64, 2064), (1057, 192, 2000)]
+
+
+@pytest.mark.parametrize("pqr", F32_NT)
+def test_f32_products_and_their_epilogues(s24, pqr):
+    p, q, r = pqr
+    r64 = (r + 63) // 64 * 64                # compress needs multiples of 64; the product takes the first r rows
+    W = si.random_matrix(40 + r, (r64, q), 0.02, "f32")
+    X = si.random_matrix(41 + p, (p, q), 1.0, "f32")
+    bias = si.random_matrix(42 + r, (1, r), 0.5, "f32")[0]
+    mask = oracle.transposable_mask(W)
+    cv, cm = (a[:r] for a in oracle.compress(W, mask)[:2])
+    v, m = oracle.pack(np.ascontiguousarray(cv), np.ascontiguousarray(cm))
+    v, m, x = dev(v), dev(m), dev(X)
+    ref = oracle.spmm_fwd(X, cv, cm)
+    Y, Z, H = (torch.full((p, r), 7.0, device="cuda") for _ in range(3))
+    s24.spmm_fwd(x, v, m, Y)
+    assert_close(host_f64(Y), ref, F32_TOL, f"spmm_fwd {pqr}")
+    s24.spmm_fwd_act(x, v, m, dev(bias), Z, H, s24.ACT_GELU_ERF)
+    assert_close(host_f64(Z), ref + bias.astype(np.float64), F32_TOL, f"spmm_fwd_act {pqr}")
+    two = torch.empty_like(H)
+    s24.act_fwd(Z, two, s24.ACT_GELU_ERF)
+    assert_close(host_f64(H), host_f64(two), F32_TOL, f"act {pqr}")
+    s24.spmm_bwd_dx(x, v, m, Y, beta=1.0)    # the same product on top of itself
+    assert_close(host_f64(Y), 2 * ref, F32_TOL, f"accumulate {pqr}")
+    Wd = np.ascontiguousarray(W[:r])
+    s24.dense_gemm(x, dev(Wd), Y)
+    assert_close(host_f64(Y), X.astype(np.float64) @ Wd.astype(np.float64).T, F32_TOL, f"dense_gemm {pqr}")
+    if r % 32 == 0:                          # the same weight as a stacked [gate; up]
+        f, GU, Hg = r // 2, torch.full((p, r), 7.0, device="cuda"), torch.full((p, r // 2), 7.0, device="cuda")
+        for gate in (s24.GATE_SILU, s24.GATE_GELU_ERF):
+            s24.spmm_fwd_glu(x, v, m, dev(bias), GU, Hg, gate)
+            assert torch.equal(GU.view(torch.int32), Z.view(torch.int32))    # the order of the sum is the plain product's
+            two = torch.empty_like(Hg)
+            s24.glu_fwd(Z, two, gate)
+            assert_close(host_f64(Hg), host_f64(two), F32_TOL, f"glu {pqr} f={f}")
+
+
+@pytest.mark.parametrize("case", [
+    # (p, q, r, beta): 32-tiles; slices of less than one token; an odd token count; 64-tiles with ragged edges
+    (1, 16, 16, 0.0), (7, 48, 80, 1.0), (129, 80, 144, 0.0), (131, 1552, 2064, 1.0), (64, 1552, 2064, 0.0), (192, 48, 80, 1.0)])
+def test_f32_weight_gradients(s24, case):
+    p, q, r, beta = case
+    lam = 2e-4
+    dY, X = si.random_matrix(50 + p, (p, r), 1e-2, "f32"), si.random_matrix(51 + p, (p, q), 1.0, "f32")
+    W, dW0 = si.random_matrix(52 + p, (r, q), 0.02, "f32"), si.random_matrix(53 + p, (r, q), 1e-3, "f32")
+    mask = oracle.transposable_mask(W)
+    decay = oracle.masked_decay(np.zeros((r, q), np.float32), W, mask, lam)
+    dY2, X2 = si.random_matrix(54, (p + 5, 32), 1e-2, "f32"), si.random_matrix(55, (p + 5, 48), 1.0, "f32")
+    a, b = dev(dW0).clone(), torch.zeros((32, 48), device="cuda")
+    s24.dense_dw_batch([(dev(dY), dev(X), a, dev(W), dev(mask), lam), (dev(dY2), dev(X2), b, None, None, 0.0)], beta=beta)
+    ref = dY.astype(np.float64).T @ X.astype(np.float64) + beta * dW0.astype(np.float64) + decay
+    assert_close(host_f64(a), ref, F32_TOL, f"dense_dw_batch {case}")
+    assert_close(host_f64(b), dY2.astype(np.float64).T @ X2.astype(np.float64), F32_TOL, f"second problem {case}")
+    if p % 64 == 0:
+        vz, mz = oracle.mvue24(dY, 99)
+        vp, mp = oracle.pack(vz, mz)
+        c = dev(dW0).clone()
+        s24.spmm_dw(dev(vp), dev(mp), dev(X), c, beta=beta, W=dev(W), mask=dev(mask), lam=lam)
+        ref = oracle.spmm_fwd(np.ascontiguousarray(X.T), vz, mz).T + beta * dW0.astype(np.float64) + decay
+        assert_close(host_f64(c), ref, F32_TOL, f"spmm_dw {case}")
