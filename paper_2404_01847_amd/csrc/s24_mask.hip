@@ -168,67 +168,90 @@ __device__ __forceinline__ unsigned lut_index_of_mask(unsigned m)
 // magnitudes of any exponent.  First maximum in id order wins.
 // ---------------------------------------------------------------------------
 struct Mag16 { uint32_t v[16]; };
+struct Fixed320 { uint32_t limb[10]; };
 
-__device__ __noinline__ unsigned slow_best_pattern(Mag16 mag)
+// Deliberately loop-based with locally indexed arrays: this path is rare, and
+// keeping it small keeps the register budget of the common path.
+__device__ __forceinline__ Fixed320 fixed_score(const Mag16 &mag, unsigned pattern)
 {
-    // Deliberately loop-based with locally indexed arrays: this path is rare, and
-    // keeping it small keeps the register budget of the common path.
-    uint32_t sig[16], limb[16], off[16];
+    uint64_t acc[10];
+#pragma unroll 1
+    for (int L = 0; L < 10; ++L) acc[L] = 0;
 #pragma unroll 1
     for (int t = 0; t < 16; ++t) {
-        const uint32_t e = mag.v[t] >> 23;
-        sig[t] = (mag.v[t] & 0x7FFFFFu) | (e ? 0x800000u : 0u);
-        const uint32_t shift = (e ? e : 1u) - 1u;
-        limb[t] = shift >> 5;
-        off[t] = shift & 31u;
+        if (!((pattern >> t) & 1u)) continue;
+        const uint32_t e = mag.v[t] >> 23, sig = (mag.v[t] & 0x7FFFFFu) | (e ? 0x800000u : 0u), shift = (e ? e : 1u) - 1u;
+        const uint64_t v = (uint64_t)sig << (shift & 31u);
+        acc[shift >> 5] += (uint32_t)v;
+        acc[(shift >> 5) + 1] += (uint32_t)(v >> 32);   // the limb is at most 7, so the next one at most 8
     }
-    uint32_t best[10];
+    Fixed320 s;
+    uint64_t carry = 0;
 #pragma unroll 1
-    for (int L = 0; L < 10; ++L) best[L] = 0;
+    for (int L = 0; L < 10; ++L) {
+        const uint64_t x = acc[L] + carry;
+        s.limb[L] = (uint32_t)x;
+        carry = x >> 32;
+    }
+    return s;
+}
+// a > b: 1, a < b: -1, equal: 0 (lexicographic from the top limb)
+__device__ __forceinline__ int fixed_compare(const Fixed320 &a, const Fixed320 &b)
+{
+    int r = 0;
+#pragma unroll 1
+    for (int L = 9; L >= 0; --L)
+        if (r == 0 && a.limb[L] != b.limb[L]) r = a.limb[L] > b.limb[L] ? 1 : -1;
+    return r;
+}
+__device__ __noinline__ unsigned slow_best_pattern(Mag16 mag)
+{
+    Fixed320 best{};
     unsigned best_id = 0;
 #pragma unroll 1
     for (unsigned k = 0; k < S24_NUM_PATTERNS; ++k) {
-        const unsigned pm = g_patterns.mask[k];
-        uint64_t acc[10];
-#pragma unroll 1
-        for (int L = 0; L < 10; ++L) acc[L] = 0;
-#pragma unroll 1
-        for (int t = 0; t < 16; ++t) {
-            if (!((pm >> t) & 1u)) continue;
-            const uint64_t v = (uint64_t)sig[t] << off[t];
-            acc[limb[t]] += (uint32_t)v;
-            acc[limb[t] + 1] += (uint32_t)(v >> 32);   // limb <= 7, so limb + 1 <= 8
-        }
-        uint32_t s[10];
-        uint64_t carry = 0;
-#pragma unroll 1
-        for (int L = 0; L < 10; ++L) {
-            const uint64_t x = acc[L] + carry;
-            s[L] = (uint32_t)x;
-            carry = x >> 32;
-        }
-        // lexicographic compare from the top limb: greater = strictly larger score
-        bool greater = false, decided = false;
-#pragma unroll 1
-        for (int L = 9; L >= 0; --L) {
-            if (!decided && s[L] != best[L]) {
-                greater = s[L] > best[L];
-                decided = true;
-            }
-        }
-        if (greater) {
-#pragma unroll 1
-            for (int L = 0; L < 10; ++L) best[L] = s[L];
+        const Fixed320 s = fixed_score(mag, g_patterns.mask[k]);
+        if (fixed_compare(s, best) > 0) {
+            best = s;
             best_id = k;
         }
     }
     return (unsigned)g_patterns.mask[best_id] | (best_id << 16);
 }
+// The same for one block scored by the whole wave (`mag` uniform, all 64 lanes active): one or two patterns per lane, then a
+// butterfly.  A large fp32 matrix has a block or two this wide, and one lane's walk over 90 patterns held the launch up by 70 us.
+__device__ __noinline__ unsigned wave_slow_best_pattern(Mag16 mag)
+{
+    unsigned id = threadIdx.x & 63;
+    Fixed320 best = fixed_score(mag, g_patterns.mask[id]);
+    if (id + 64u < S24_NUM_PATTERNS) {
+        const Fixed320 s = fixed_score(mag, g_patterns.mask[id + 64u]);
+        if (fixed_compare(s, best) > 0) {
+            best = s;
+            id += 64u;
+        }
+    }
+#pragma unroll 1
+    for (int off = 32; off > 0; off >>= 1) {
+        Fixed320 o;
+#pragma unroll 1
+        for (int L = 0; L < 10; ++L) o.limb[L] = (uint32_t)__shfl_xor((int)best.limb[L], off, 64);
+        const unsigned oid = (unsigned)__shfl_xor((int)id, off, 64);
+        const int c = fixed_compare(o, best);
+        if (c > 0 || (c == 0 && oid < id)) {
+            best = o;
+            id = oid;
+        }
+    }
+    return (unsigned)g_patterns.mask[id] | (id << 16);
+}
 
 // ---------------------------------------------------------------------------
-// Middle path: the 90 sums one by one in fp64, first maximum in id order.  Exact as long as every sum of
+// Middle path: the 90 sums in fp64, first maximum in id order.  Exact as long as every sum of
 // eight magnitudes fits fp64's 53 bits, i.e. the block spans at most 26 binades of fp32 data (42 of bf16
 // data); used for blocks too wide for the fast path's window, which also has to hold the tie-break bits.
+// Two forms.  16-bit weights hardly ever need it (their window is 26 to 29 binades): one lane walks the patterns in a call
+// that costs the common path no registers.
 // ---------------------------------------------------------------------------
 __device__ __noinline__ unsigned mid_best_pattern(Mag16 mag)
 {
@@ -250,13 +273,47 @@ __device__ __noinline__ unsigned mid_best_pattern(Mag16 mag)
     }
     return (unsigned)g_patterns.mask[best_id] | (best_id << 16);
 }
+// fp32 weights (window 13 binades) need it for one block in 300, so nearly every wave has some: there the wave scores one
+// lane's block together, one or two patterns per lane, and agrees on the winner by a butterfly, about 150 instructions
+// where the one-lane walk takes 4300 with the other 63 lanes waiting.  fp32 search, 1024 x 256: 71 -> 5 us; 22016 x 4096:
+// 439 -> 78; search and compress 79 -> 8 and 633 -> 263.  (In the 16-bit kernels its registers cost 5 to 10 %.)
+// All 64 lanes must be active; every lane returns the answer for the block of lane `src`.
+__device__ __forceinline__ unsigned wave_mid_best_pattern(const uint32_t (&mag)[16], int src)
+{
+    const int lane = threadIdx.x & 63;
+    unsigned id = (unsigned)lane;
+    const unsigned other_id = min(id + 64u, (unsigned)S24_NUM_PATTERNS - 1u);   // lanes 26..63 repeat the last pattern
+    const unsigned pm = g_patterns.mask[id], pm2 = g_patterns.mask[other_id];
+    double best = 0.0, second = 0.0;
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+        const double a = (double)__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)mag[t], src));
+        best += ((pm >> t) & 1u) ? a : 0.0;
+        second += ((pm2 >> t) & 1u) ? a : 0.0;
+    }
+    if (second > best) {
+        best = second;
+        id = other_id;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const double o = __shfl_xor(best, off, 64);
+        const unsigned oid = (unsigned)__shfl_xor((int)id, off, 64);
+        if (o > best || (o == best && oid < id)) {
+            best = o;
+            id = oid;
+        }
+    }
+    return (unsigned)g_patterns.mask[id] | (id << 16);
+}
 
 // ---------------------------------------------------------------------------
-// Fast path.  mag[4*i+j] = |w_ij| as fp32 bit patterns.  Returns mask | id<<16.
+// Fast path.  mag[4*i+j] = |w_ij| as fp32 bit patterns.  Returns mask | id<<16.  COOPERATIVE: all 64
+// lanes of the wave call it together.
 // WINDOW = binades below the block maximum within which every element is a
 // multiple of 2048*eps (29 for bf16 data, 13 for fp32 data).
 // ---------------------------------------------------------------------------
-template <int WINDOW, int WIDE>
+template <int WINDOW, int WIDE, bool COOPERATIVE>
 __device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], const uint16_t *lut_mask, const uint8_t *lut_id)
 {
     uint32_t mx = 0, mn = 0xFFFFFFFFu;
@@ -267,7 +324,24 @@ __device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], cons
     }
     const uint32_t emax = max(mx >> 23, 1u);
     const uint32_t emin = (mn == 0xFFFFFFFFu) ? 255u : max(mn >> 23, 1u);
-    if (emin + WINDOW < emax) {
+    const bool wide = emin + WINDOW < emax;
+    unsigned rare = 0;
+    if constexpr (COOPERATIVE) {
+        const bool very_wide = emin + WIDE < emax;
+        for (unsigned long long todo = __ballot(wide && !very_wide); todo != 0; todo &= todo - 1) {
+            const int src = (int)__builtin_ctzll(todo);
+            const unsigned res = wave_mid_best_pattern(mag, src);
+            if ((int)(threadIdx.x & 63) == src) rare = res;
+        }
+        for (unsigned long long todo = __ballot(very_wide); todo != 0; todo &= todo - 1) {
+            const int src = (int)__builtin_ctzll(todo);
+            Mag16 m16;
+#pragma unroll
+            for (int t = 0; t < 16; ++t) m16.v[t] = (uint32_t)__builtin_amdgcn_readlane((int)mag[t], src);
+            const unsigned res = wave_slow_best_pattern(m16);
+            if ((int)(threadIdx.x & 63) == src) rare = res;
+        }
+    } else if (wide) {
         Mag16 m16;
 #pragma unroll
         for (int t = 0; t < 16; ++t) m16.v[t] = mag[t];
@@ -331,8 +405,8 @@ __device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], cons
             best = __builtin_fmax(best, (dt[x] + db[w]) + cross[pair_of(y, z)]);
         }
     const unsigned bonus = (unsigned)__double2loint(best + big) & 0x7FFu;
-    const unsigned x = min(bonus - (unsigned)kBonusBase, 1295u);
-    return (unsigned)lut_mask[x] | ((unsigned)lut_id[x] << 16);
+    const unsigned x = min(bonus - (unsigned)kBonusBase, 1295u);   // (a wide block's index is clamped and unused)
+    return COOPERATIVE && wide ? rare : (unsigned)lut_mask[x] | ((unsigned)lut_id[x] << 16);
 }
 
 // ---------------------------------------------------------------------------
@@ -471,10 +545,12 @@ template <> struct RowOps<float> {
     static __device__ __forceinline__ Pair pair(uint32_t lo, uint32_t hi) { return make_uint2(lo, hi); }
 };
 
-constexpr int kTile = 32;        // blocks per tile edge
-constexpr int kPitch = kTile + 1;
-
-template <typename T, bool SEARCH, bool COMPRESS>
+// A workgroup's tile is TBW blocks wide and 256 / TBW * S blocks tall, S blocks per lane.
+//   32 x 32 (S = 4): the lookup tables are staged once per 1024 blocks and the next block's rows are requested while the
+//   current one is scored: the better shape once there are several tiles per compute unit.
+//   16 x 16 (S = 1): four times as many workgroups, for matrices whose 32 x 32 tiles do not fill the chip, where a lane
+//   walking four blocks one after the other is what takes the time; 32 x 16 (S = 2) between the two.
+template <typename T, bool SEARCH, bool COMPRESS, int TBW, int S>
 __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict__ W, int64_t ldw, int br, int bq,
                                                             const uint16_t *__restrict__ mask_in,
                                                             uint16_t *__restrict__ mask_out, uint8_t *__restrict__ index_out,
@@ -484,40 +560,30 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
     using Ops = RowOps<T>;
     using Row = typename Ops::Row;
     using Pair = typename Ops::Pair;
+    constexpr int LR = 256 / TBW, TBH = LR * S, PITCH = TBH + 1;   // rows of lanes, tile height, LDS pitch of the transposed pairs
+    static_assert(!COMPRESS || TBH % 16 == 0, "a tile holds whole chunks of the column-wise operand");
     constexpr bool FAST = COMPRESS && sizeof(T) == 2;   // bf16: table-driven compressor
     // bf16 search on its own: integer scoring with the blocks it cannot take queued for the fp64 path.  (In the fused
     // search + compress kernel the four blocks' rows held in registers across the queue cost more than the cheaper
     // scoring saves: measured 4-8 % slower, so it keeps the fp64 scoring inside its loop.)
     constexpr bool DEFER = SEARCH && !COMPRESS && sizeof(T) == 2 && RowOps<T>::kWindow == 29;
     __shared__ int s_nhard;
-    __shared__ uint16_t s_hard[DEFER ? 1024 : 1];
-    __shared__ uint32_t s_fix[DEFER ? 1024 : 1];
+    __shared__ uint16_t s_hard[DEFER ? 256 * S : 1];
+    __shared__ uint32_t s_fix[DEFER ? 256 * S : 1];
     __shared__ uint16_t s_lut_mask[SEARCH ? 1296 : 1];
     __shared__ uint8_t s_lut_id[(SEARCH || FAST) ? 1296 : 1];
     __shared__ uint4 s_clut[FAST ? 3 * S24_NUM_PATTERNS : 1];
-    __shared__ Pair s_valsT[COMPRESS ? 4 * kTile * kPitch : 1];
-    __shared__ uint8_t s_nibT[COMPRESS ? 4 * kTile * kPitch : 1];
+    __shared__ Pair s_valsT[COMPRESS ? 4 * TBW * PITCH : 1];
+    __shared__ uint8_t s_nibT[COMPRESS ? 4 * TBW * PITCH : 1];
 
     const int tid = threadIdx.x;
-    if (DEFER && tid == 0) s_nhard = 0;
-    if constexpr (SEARCH || FAST) {
-        for (int x = tid; x < 1296; x += 256) {
-            if constexpr (SEARCH) s_lut_mask[x] = g_lut.mask[x];
-            s_lut_id[x] = g_lut.id[x];
-        }
-        if constexpr (FAST) {
-            const uint4 *src = reinterpret_cast<const uint4 *>(&g_clut);
-            for (int x = tid; x < 3 * S24_NUM_PATTERNS; x += 256) s_clut[x] = src[x];
-        }
-        __syncthreads();
-    }
-    const int bj0 = blockIdx.x * kTile, bi0 = blockIdx.y * kTile;
-    const int lbj = tid & 31;
+    const int bj0 = blockIdx.x * TBW, bi0 = blockIdx.y * TBH;
+    const int lbj = tid % TBW;
     const int bj = bj0 + lbj;
     const int64_t R = 4 * (int64_t)br, Q = 4 * (int64_t)bq;  // rows of vals / of valsT
 
-    // first weight row of this lane's first block; block s of the lane lies 8 s block rows further down
-    const T *wrow = W + (int64_t)(4 * (bi0 + (tid >> 5))) * ldw + 4 * bj;
+    // first weight row of this lane's first block; block s of the lane lies LR s block rows further down
+    const T *wrow = W + (int64_t)(4 * (bi0 + tid / TBW)) * ldw + 4 * bj;
     auto fetch = [&](Row (&dst)[4], const T *p, bool ok) {
         if (ok) {
 #pragma unroll
@@ -536,7 +602,7 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
     // What follows the search for block s of this lane (rows in registers, mask m and pattern id known):
     // the mask and id stores and, when compressing, both compressed orientations.
     auto emit = [&](const Row (&rows)[4], unsigned m, unsigned id, int s) {
-        const int lbi = (tid >> 5) + 8 * s;
+        const int lbi = tid / TBW + LR * s;
         const int bi = bi0 + lbi;
         const bool valid = (bi < br) && (bj < bq);
         if constexpr (SEARCH) {
@@ -596,7 +662,7 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
                 const uint32_t r2 = (j < 2) ? rows[2].x : rows[2].y, r3 = (j < 2) ? rows[3].x : rows[3].y;
                 const uint32_t col_lo = __builtin_amdgcn_perm(r1, r0, half);  // rows 0,1 of column j
                 const uint32_t col_hi = __builtin_amdgcn_perm(r3, r2, half);  // rows 2,3
-                const int a = (j * kTile + lbj) * kPitch + lbi;
+                const int a = (j * TBW + lbj) * PITCH + lbi;
                 s_valsT[a] = __builtin_amdgcn_perm(col_hi, col_lo, cs[j]);
                 s_nibT[a] = (uint8_t)((mt.z >> (4 * j)) & 0xFu);
             }
@@ -640,25 +706,44 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
                 for (int i = 0; i < 4; ++i) e[i] = Ops::bits(rows[i], j);
                 const uint32_t v0 = i0 == 0 ? e[0] : (i0 == 1 ? e[1] : (i0 == 2 ? e[2] : e[3]));
                 const uint32_t v1 = i1 == 0 ? e[0] : (i1 == 1 ? e[1] : (i1 == 2 ? e[2] : e[3]));
-                const int a = (j * kTile + lbj) * kPitch + lbi;
+                const int a = (j * TBW + lbj) * PITCH + lbi;
                 s_valsT[a] = Ops::pair(v0, v1);
                 s_nibT[a] = (uint8_t)(i0 | (i1 << 2));
             }
         }
     };
 
+    // the lookup tables go to LDS; the weights' first loads are issued ahead of this
+    auto stage_tables = [&]() {
+        if (DEFER && tid == 0) s_nhard = 0;
+        if constexpr (SEARCH || FAST) {
+            for (int x = tid; x < 1296; x += 256) {
+                if constexpr (SEARCH) s_lut_mask[x] = g_lut.mask[x];
+                s_lut_id[x] = g_lut.id[x];
+            }
+            if constexpr (FAST) {
+                const uint4 *src = reinterpret_cast<const uint4 *>(&g_clut);
+                for (int x = tid; x < 3 * S24_NUM_PATTERNS; x += 256) s_clut[x] = src[x];
+            }
+            __syncthreads();
+        }
+    };
+
     if constexpr (DEFER) {
-        // bf16 search: all four blocks of the lane are scored by the integer fast path first; the few blocks it
+        // bf16 search: all S blocks of the lane are scored by the integer fast path first; the few blocks it
         // cannot take (about one in forty for normally distributed weights) are queued in LDS and scored afterwards
         // by the fp64 path, one per lane, so that a rare block costs one lane's time instead of stalling its whole
         // wave in a divergent branch.
-        Row blk[4][4];
-        unsigned res[4];
+        Row blk[S][4];
+        unsigned res[S];
+        // (four blocks' loads ahead of the tables' would make the tables wait for all of them: 51 against 47 us at 22016 x 4096)
+        if (S > 1) stage_tables();
 #pragma unroll
-        for (int s = 0; s < 4; ++s) fetch(blk[s], wrow + (int64_t)(32 * s) * ldw, (bi0 + (tid >> 5) + 8 * s < br) && (bj < bq));
+        for (int s = 0; s < S; ++s) fetch(blk[s], wrow + (int64_t)(4 * LR * s) * ldw, (bi0 + tid / TBW + LR * s < br) && (bj < bq));
+        if (S == 1) stage_tables();
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const bool valid = (bi0 + (tid >> 5) + 8 * s < br) && (bj < bq);
+        for (int s = 0; s < S; ++s) {
+            const bool valid = (bi0 + tid / TBW + LR * s < br) && (bj < bq);
             uint32_t mag[16];
             magnitudes(blk[s], mag);
             res[s] = valid ? int_best_pattern(mag, s_lut_mask, s_lut_id) : 0x33CCu;   // off the edge: pattern 0, never stored
@@ -668,37 +753,40 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
         const int nhard = s_nhard;
         for (int e = tid; e < nhard; e += 256) {
             const int code = s_hard[e], hs = code >> 8, owner = code & 255;
-            const T *p = W + (int64_t)(4 * (bi0 + (owner >> 5) + 8 * hs)) * ldw + 4 * (bj0 + (owner & 31));
+            const T *p = W + (int64_t)(4 * (bi0 + owner / TBW + LR * hs)) * ldw + 4 * (bj0 + owner % TBW);
             Row rows[4];
             fetch(rows, p, true);
             uint32_t mag[16];
             magnitudes(rows, mag);
-            s_fix[code] = best_pattern<Ops::kWindow, Ops::kWide>(mag, s_lut_mask, s_lut_id);
+            s_fix[code] = best_pattern<Ops::kWindow, Ops::kWide, false>(mag, s_lut_mask, s_lut_id);
         }
         __syncthreads();
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < S; ++s) {
             const unsigned r = res[s] == kHardBlock ? s_fix[256 * s + tid] : res[s];
             emit(blk[s], r & 0xFFFFu, r >> 16, s);
         }
     } else {
         // The rows of the next block are requested before the current one is scored.
         Row nxt[4];
-        fetch(nxt, wrow, (bi0 + (tid >> 5) < br) && (bj < bq));
+        fetch(nxt, wrow, (bi0 + tid / TBW < br) && (bj < bq));
+        stage_tables();
 #pragma unroll 1
-        for (int s = 0; s < 4; ++s) {
-            const int bi = bi0 + (tid >> 5) + 8 * s;
+        for (int s = 0; s < S; ++s) {
+            const int bi = bi0 + tid / TBW + LR * s;
             const bool valid = (bi < br) && (bj < bq);
             Row rows[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) rows[i] = nxt[i];
-            wrow += 32 * ldw;
-            if (s < 3) fetch(nxt, wrow, (bi + 8 < br) && (bj < bq));
+            if (s + 1 < S) {
+                wrow += 4 * LR * ldw;
+                fetch(nxt, wrow, (bi + LR < br) && (bj < bq));
+            }
             unsigned m = 0, id = 0;
             if constexpr (SEARCH) {
                 uint32_t mag[16];
                 magnitudes(rows, mag);
-                const unsigned res = best_pattern<Ops::kWindow, Ops::kWide>(mag, s_lut_mask, s_lut_id);
+                const unsigned res = best_pattern<Ops::kWindow, Ops::kWide, sizeof(T) == 4>(mag, s_lut_mask, s_lut_id);
                 m = res & 0xFFFFu;
                 id = res >> 16;
             } else {
@@ -709,18 +797,18 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
     }
     if constexpr (COMPRESS) {
         __syncthreads();
-        // valsT: two chunks (16 pairs each) of 128 columns of W.  One item = four consecutive pairs of
+        // valsT: TBH / 16 chunks (16 pairs each) of the tile's 4 TBW columns of W.  One item = four consecutive pairs of
         // one column; consecutive lanes take consecutive items of a column, then the next column, so a
         // chunk of the tile leaves as one contiguous run.
         Pair *outT = reinterpret_cast<Pair *>(valsT);
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int idx = tid + 256 * it;                    // 1024 items
-            const int quad = idx & 3, col = (idx >> 2) & 127, half = idx >> 9;   // col = 4*lbj + j
+        for (int it = 0; it < S; ++it) {
+            const int idx = tid + 256 * it;                    // TBW * TBH items
+            const int quad = idx & 3, col = (idx >> 2) % (4 * TBW), half = idx / (16 * TBW);   // col = 4*lbj + j
             const int j = col & 3, lb = col >> 2;
             const int lbi = 16 * half + 4 * quad, bi = bi0 + lbi;
             if (bj0 + lb < bq && bi < br) {   // br is a multiple of 16: a quad is all in or all out
-                const Pair *src = &s_valsT[(j * kTile + lb) * kPitch + lbi];
+                const Pair *src = &s_valsT[(j * TBW + lb) * PITCH + lbi];
                 Pair *dst = outT + ((int64_t)(bi >> 4) * Q + 4 * (bj0 + lb) + j) * 16 + (bi & 15);
                 if constexpr (sizeof(Pair) == 4) {
                     *reinterpret_cast<uint4 *>(dst) = make_uint4(src[0], src[1], src[2], src[3]);
@@ -730,12 +818,12 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
                 }
             }
         }
-        // metaT: per column two chunks of four words; one thread packs the 16 nibbles of one (column, chunk)
-        {
-            const int col = tid & 127, half = tid >> 7;
+        // metaT: per column and chunk four words; one thread packs the 16 nibbles of one (column, chunk)
+        if (tid < 4 * TBW * (TBH / 16)) {
+            const int col = tid % (4 * TBW), half = tid / (4 * TBW);
             const int j = col & 3, lb = col >> 2;
             if (bj0 + lb < bq && bi0 + 16 * half < br) {
-                const uint8_t *n = &s_nibT[(j * kTile + lb) * kPitch + 16 * half];
+                const uint8_t *n = &s_nibT[(j * TBW + lb) * PITCH + 16 * half];
                 uint32_t w01 = 0, w23 = 0;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
@@ -749,24 +837,41 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
     }
 }
 
+template <typename T, bool SEARCH, bool COMPRESS, int TBW, int S>
+int launch_tiles(const T *W, int64_t ldw, int br, int bq, const uint16_t *mask_in, uint16_t *mask_out, uint8_t *index_out, T *vals,
+                 uint16_t *meta, T *valsT, uint16_t *metaT, hipStream_t st)
+{
+    constexpr int TBH = 256 / TBW * S;
+    const dim3 grid((bq + TBW - 1) / TBW, (br + TBH - 1) / TBH), block(256);
+    hipLaunchKernelGGL((mask_compress_kernel<T, SEARCH, COMPRESS, TBW, S>), grid, block, 0, st, W, ldw, br, bq, mask_in, mask_out,
+                       index_out, vals, meta, valsT, metaT);
+    return s24_launch_status();
+}
+// Which tile, by the number of 32 x 32 tiles (measured in us; 32 x 32 / 32 x 16 / 16 x 16 blocks):
+//   bf16 search + compress   144 tiles (3072 x 768): 8.2 / 7.4 / 6.5    400 (5120 x 1280): 12.2 / 11.7 / 12.4    5504: 87 / 99 / 115
+//   bf16 given mask          144: 7.7 / 6.2 / 5.4    400: 10.8 / 10.0 / 9.3    1376 (11008 x 2048): 28.1 / 24.8 / 25.5    5504: 82 / 83 / 89
+//   fp32 search + compress   16 (1024 x 256): 18.5 / 11.6 / 7.8    400: 33.9 / 31.3 / 29.4    5504: 258 / 254 / 258
+template <typename T, bool SEARCH, bool COMPRESS, typename... Args>
+int launch_sized(const T *W, int64_t ldw, int br, int bq, Args... args)
+{
+    const int64_t tiles = (int64_t)((bq + 31) / 32) * ((br + 31) / 32);
+    if (tiles < (SEARCH && sizeof(T) == 2 ? 300 : 512)) return launch_tiles<T, SEARCH, COMPRESS, 16, 1>(W, ldw, br, bq, args...);
+    if constexpr (!SEARCH && sizeof(T) == 2)
+        if (tiles < 4096) return launch_tiles<T, SEARCH, COMPRESS, 32, 2>(W, ldw, br, bq, args...);
+    return launch_tiles<T, SEARCH, COMPRESS, 32, 4>(W, ldw, br, bq, args...);
+}
+
 template <typename T>
 int launch(const void *W, int64_t r, int64_t q, int64_t ldw, const uint16_t *mask_in, uint16_t *mask_out,
            uint8_t *index_out, void *vals, uint16_t *meta, void *valsT, uint16_t *metaT, bool compress, hipStream_t st)
 {
     const int br = (int)(r / 4), bq = (int)(q / 4);
     if (br == 0 || bq == 0) return S24_OK;
-    const dim3 grid((bq + kTile - 1) / kTile, (br + kTile - 1) / kTile), block(256);
     const T *w = static_cast<const T *>(W);
-    if (!compress)
-        hipLaunchKernelGGL((mask_compress_kernel<T, true, false>), grid, block, 0, st, w, ldw, br, bq, nullptr, mask_out,
-                           index_out, nullptr, nullptr, nullptr, nullptr);
-    else if (mask_in)
-        hipLaunchKernelGGL((mask_compress_kernel<T, false, true>), grid, block, 0, st, w, ldw, br, bq, mask_in, nullptr,
-                           nullptr, static_cast<T *>(vals), meta, static_cast<T *>(valsT), metaT);
-    else
-        hipLaunchKernelGGL((mask_compress_kernel<T, true, true>), grid, block, 0, st, w, ldw, br, bq, nullptr, mask_out,
-                           nullptr, static_cast<T *>(vals), meta, static_cast<T *>(valsT), metaT);
-    return s24_launch_status();
+    T *v = static_cast<T *>(vals), *vt = static_cast<T *>(valsT);
+    if (!compress) return launch_sized<T, true, false>(w, ldw, br, bq, nullptr, mask_out, index_out, nullptr, nullptr, nullptr, nullptr, st);
+    if (mask_in) return launch_sized<T, false, true>(w, ldw, br, bq, mask_in, nullptr, nullptr, v, meta, vt, metaT, st);
+    return launch_sized<T, true, true>(w, ldw, br, bq, nullptr, mask_out, nullptr, v, meta, vt, metaT, st);
 }
 
 // ------------------------------------------------------------------ monitors

@@ -89,3 +89,47 @@ def test_f32_weight_gradients(s24, case):
         s24.spmm_dw(dev(vp), dev(mp), dev(X), c, beta=beta, W=dev(W), mask=dev(mask), lam=lam)
         ref = oracle.spmm_fwd(np.ascontiguousarray(X.T), vz, mz).T + beta * dW0.astype(np.float64) + decay
         assert_close(host_f64(c), ref, F32_TOL, f"spmm_dw {case}")
+
+
+# ------------------------------------------------------------------ mask search, compress and L1 gap by matrix size
+def _search_and_compress(s24, W):
+    r, q = W.shape
+    Wd, dt = dev_bf16(W), torch_dtype({np.uint16: "bf16", np.float16: "f16", np.float32: "f32"}[W.dtype.type])
+    new = lambda shape, t: torch.zeros(shape, dtype=t, device="cuda")
+    out = [new((q // 64, r, 32), dt), new((q // 64, r, 4), torch.int16), new((r // 64, q, 32), dt), new((r // 64, q, 4), torch.int16)]
+    alone, fused = new((r // 4, q // 4), torch.int16), new((r // 4, q // 4), torch.int16)
+    s24.transposable_mask(Wd, alone)
+    s24.compress(Wd, None, *out, mask_out=fused)
+    given = [torch.zeros_like(o) for o in out]
+    s24.compress(Wd, alone, *given)
+    return alone, fused, out, given
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+# one 16 x 16 tile and its edges; both sides of the lines between the tile shapes (32 x 32 tiles: 18 x 16 = 288 and 19 x 16,
+# 16 x 32 = 512, 64 x 64 = 4096), ragged in both directions
+@pytest.mark.parametrize("rq", [(64, 64), (192, 320), (2240, 2048), (2368, 2048), (1984, 4160), (8128, 8256)])
+def test_mask_and_compress_tile_shapes(s24, dtype, rq):
+    if rq[0] > 4096 and dtype == "f32":
+        rq = (rq[0] // 128 * 64, rq[1])
+    W = si.random_matrix(60 + rq[0], rq, 0.02, dtype)
+    alone, fused, out, given = _search_and_compress(s24, W)
+    mask = oracle.transposable_mask(W)
+    assert np.array_equal(host_bits(alone), mask) and np.array_equal(host_bits(fused), mask)
+    c = oracle.compress(W, mask)
+    for got, again, want in zip(out, given, oracle.pack(c[0], c[1]) + oracle.pack(c[2], c[3])):
+        g, w = host_bits(got), want
+        assert np.array_equal(g.view(np.uint8), w.reshape(g.shape).view(np.uint8))
+        assert torch.equal(got.view(torch.uint8), again.view(torch.uint8))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("kind", ["tiny", "range", "subnormal", "window", "zeros"])
+@pytest.mark.parametrize("rq", [(192, 320), (2432, 2048)])
+def test_wide_blocks_in_both_tile_shapes(s24, dtype, kind, rq):
+    """Blocks too wide for the fast path, many per wave: the wave-cooperative paths of fp32, the queue of bf16."""
+    W = si.tie_matrix(61, *rq, dtype, kind)
+    alone, fused, _, _ = _search_and_compress(s24, W)
+    mask = oracle.transposable_mask(W)
+    assert np.array_equal(host_bits(alone), mask) and np.array_equal(host_bits(fused), mask)
+
