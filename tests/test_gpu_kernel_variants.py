@@ -133,3 +133,20 @@ def test_wide_blocks_in_both_tile_shapes(s24, dtype, kind, rq):
     mask = oracle.transposable_mask(W)
     assert np.array_equal(host_bits(alone), mask) and np.array_equal(host_bits(fused), mask)
 
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("kind", ["few", "equal", "zeros", "tiny", "window", "normal"])
+def test_l1_norm_gap_by_classes(s24, dtype, kind):
+    """Ties for the best and for the second best across and inside the classes, ragged sizes; blocks inside the exact window
+    match the oracle's 90 sums bit for bit."""
+    W = si.random_matrix(62, (204, 260), 0.02, dtype) if kind == "normal" else si.tie_matrix(62, 204, 260, dtype, kind)
+    gap = torch.full((51, 65), -1.0, dtype=torch.float64, device="cuda")
+    s24.l1_norm_gap(dev_bf16(W), gap)
+    a = np.abs(si.to_f32(W)).reshape(51, 4, 65, 4).transpose(0, 2, 1, 3).reshape(51, 65, 16).astype(np.float64)
+    e = np.frexp(np.where(a > 0, a, np.nan))[1]
+    exact = np.nanmax(np.where(np.isnan(e), -1e9, e), -1) - np.nanmin(np.where(np.isnan(e), 1e9, e), -1) <= {"bf16": 42, "f16": 39, "f32": 26}[dtype]
+    got, ref = gap.cpu().numpy(), oracle.l1_norm_gap(W)
+    assert exact.mean() > 0.5 or kind == "tiny"
+    assert np.array_equal(got[exact], ref[exact]), kind
+    # beyond it both carry fp64 rounding: eight additions, each 2^-53 of the block's kept norm, in either sum
+    assert np.all(np.abs(got - ref)[~exact] <= 16 * 2.0 ** -53 * a.sum(-1)[~exact])
