@@ -19,6 +19,8 @@
 // lane's index half, and the chunk-major storage of the compressed operand
 // (vals[K/64][M][32], meta[K/64][M][4]) makes the 64-byte value run and the
 // four index words of one row and chunk contiguous, rows back to back.
+#include <algorithm>
+
 #include "s24_gemm_f32.h"
 
 namespace {
@@ -289,8 +291,8 @@ template <int ACT> __device__ __forceinline__ float act_slope(float z)
 // BIAS compiles the bias add into the plain forward kernel (the gated forward tests the pointer at run time; the
 // plain kernel without a bias keeps its register budget, which the extra loads would push into scratch).
 template <typename T, bool ACCUM, bool SWIGLU = false, bool GATE_BWD = false, int GATE = S24_GATE_SILU, bool BIAS = false,
-          int ACT_MODE = 0, int ACT = S24_ACT_RELU, int MI = 4>
-__global__ __launch_bounds__(128 * MI) void spmm_nt_big_kernel(const uint16_t *__restrict__ B,
+          int ACT_MODE = 0, int ACT = S24_ACT_RELU, int MI = 4, int WN = MI>
+__global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *__restrict__ B,
                                                               const uint16_t *__restrict__ Av,
                                                               const uint16_t *__restrict__ Am,
                                                               uint16_t *__restrict__ Out, int N, int K, int M,
@@ -301,12 +303,15 @@ __global__ __launch_bounds__(128 * MI) void spmm_nt_big_kernel(const uint16_t *_
 {
     static_assert(!(ACCUM && (SWIGLU || GATE_BWD)) && !(SWIGLU && GATE_BWD), "the gated epilogues overwrite");
     static_assert(ACT_MODE == 0 || !(ACCUM || SWIGLU || GATE_BWD), "one epilogue at a time");
-    // MI = accumulator blocks per wave along m.  4: the 256 x 256 tile of eight waves (2 x 4, 128 x 64 each).
-    // 2: a 128 x 128 tile of four waves (2 x 2, 64 x 64 each) on 25 KB stages, two workgroups per compute unit,
-    // for outputs with too few large tiles to fill the chip; every epilogue but the gated ones.  A lane
-    // issues the same seven copies per chunk either way (the stage is half as tall and there are half as many lanes).
-    static_assert(MI == 4 || (MI == 2 && !SWIGLU && !GATE_BWD), "the small tile has no gated epilogue");
-    constexpr int BM = 64 * MI, BN = 64 * MI, WM = 32 * MI;   // workgroup tile, wave tile along m
+    // MI = accumulator blocks per wave along m, WN = waves along n (two along m).  MI 4, WN 4: the 256 x 256 tile of eight
+    // waves (128 x 64 each).  MI 2, WN 2: a 128 x 128 tile of four waves (64 x 64 each) on 25 KB stages, two workgroups
+    // per compute unit; every epilogue but the gated ones.  MI 4, WN 2: a 256 (m) x 128 (n) tile of four waves (128 x 64
+    // each) on 34 KB stages.  The two smaller ones are for outputs with too few large tiles to fill the chip.  What
+    // bounds them is LDS: a chunk of the small tile is 25 KB written and 50 KB read, 600 cycles at 128 bytes each, of
+    // which the matrix cores need 256; the medium one has 34 + 68 KB for twice the work.
+    static_assert((MI == 4 && (WN == 4 || WN == 2)) || (MI == 2 && WN == 2 && !SWIGLU && !GATE_BWD), "the small tile has no gated epilogue");
+    constexpr int BM = 64 * MI, BN = 64 * WN, WM = 32 * MI;   // workgroup tile, wave tile along m
+    constexpr int NA = 2 * MI / WN, NX = MI / WN, NC = 4 + NA + NX;   // copies per lane and chunk: values, index words, all
     constexpr int B_STAGE = BN * 128, A_STAGE = BM * 64, M_STAGE = BM * 8, STAGE = B_STAGE + A_STAGE + M_STAGE;
     const ClockStamp t_start = clock_now();
     // One array per ring stage: the compiler then knows which stage a direct-to-LDS
@@ -340,7 +345,7 @@ __global__ __launch_bounds__(128 * MI) void spmm_nt_big_kernel(const uint16_t *_
     // copies cost seven address registers and no vector arithmetic
     const char *baseB = reinterpret_cast<const char *>(B + (int64_t)n0 * K);
     const char *baseV = reinterpret_cast<const char *>(Av), *baseM = reinterpret_cast<const char *>(Am);
-    uint32_t ob[4], oa[2];
+    uint32_t ob[4], oa[NA], om[NX];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int row = 32 * wave + 8 * i + (lane >> 3);
@@ -348,15 +353,16 @@ __global__ __launch_bounds__(128 * MI) void spmm_nt_big_kernel(const uint16_t *_
         ob[i] = ((uint32_t)(min(n0 + row, N - 1) - n0) * (uint32_t)K + 8u * c) * 2u;   // a tile's rows span < 4 GB (host check)
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int row = 32 * wave + 16 * i + (lane >> 2);
+    for (int i = 0; i < NA; ++i) {
+        const int row = 16 * NA * wave + 16 * i + (lane >> 2);
         const int c = (lane & 3) ^ ((row >> 2) & 3);
         oa[i] = ((uint32_t)a_row(row) * 32u + 8u * c) * 2u;
     }
-    // index words: one 4-byte direct-to-LDS copy per lane and chunk (row 32*wave + lane/2, dword lane%2)
-    const uint32_t om = ((uint32_t)a_row(32 * wave + (lane >> 1)) * 4u + 2u * (lane & 1)) * 2u;
-    // Every call issues exactly seven copies per lane (four of the dense operand, two of the
-    // values, one of the index words), so the wait counts below are constants; past the last
+    // index words: 4-byte direct-to-LDS copies (copy i: row 32 * (NX * wave + i) + lane/2, dword lane%2)
+#pragma unroll
+    for (int i = 0; i < NX; ++i) om[i] = ((uint32_t)a_row(32 * (NX * wave + i) + (lane >> 1)) * 4u + 2u * (lane & 1)) * 2u;
+    // Every call issues exactly NC copies per lane (four of the dense operand, NA of the
+    // values, NX of the index words), so the wait counts below are constants; past the last
     // chunk it re-reads the last one into a stage nobody will read again.
     auto issue = [&](unsigned char *st, int kc) {
         kc = min(kc, nk - 1);
@@ -365,8 +371,9 @@ __global__ __launch_bounds__(128 * MI) void spmm_nt_big_kernel(const uint16_t *_
 #pragma unroll
         for (int i = 0; i < 4; ++i) buffer_to_lds<16>(pb, (lds_ptr)(st + (32 * wave + 8 * i) * 128), ob[i]);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) buffer_to_lds<16>(pv, (lds_ptr)(st + B_STAGE + (32 * wave + 16 * i) * 64), oa[i]);
-        buffer_to_lds<4>(pm, (lds_ptr)(st + B_STAGE + A_STAGE + 32 * wave * 8), om);
+        for (int i = 0; i < NA; ++i) buffer_to_lds<16>(pv, (lds_ptr)(st + B_STAGE + 16 * (NA * wave + i) * 64), oa[i]);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) buffer_to_lds<4>(pm, (lds_ptr)(st + B_STAGE + A_STAGE + 32 * (NX * wave + i) * 8), om[i]);
     };
 
     f32x16 acc[MI][2];
@@ -405,7 +412,7 @@ __global__ __launch_bounds__(128 * MI) void spmm_nt_big_kernel(const uint16_t *_
     __builtin_amdgcn_sched_barrier(0);
     issue(s2, 2);
     __builtin_amdgcn_sched_barrier(0);
-    wait_and_barrier<14>();   // chunk 0 has landed for everybody
+    wait_and_barrier<2 * NC>();   // chunk 0 has landed for everybody
     bf16x16 fb0[2];           // first-half fragments and index words of the chunk about to be multiplied
     bf16x8 fa0[MI];
     uint32_t ix[MI];
@@ -438,9 +445,9 @@ __global__ __launch_bounds__(128 * MI) void spmm_nt_big_kernel(const uint16_t *_
             if (MI == 4 ? i < 4 : i < 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
             else if (MI == 2) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        // all but the seven most recent copies (chunk kc+2) are complete: this lane's part of chunk kc+1 is in LDS,
+        // all but the NC most recent copies (chunk kc+2) are complete: this lane's part of chunk kc+1 is in LDS,
         // and its own LDS reads of chunk kc are done
-        wait_and_barrier<7>();
+        wait_and_barrier<NC>();
         issue(cur, kc + 3);
         uint32_t ixn[MI];
         load_index(nxt, ixn);
@@ -454,7 +461,8 @@ __global__ __launch_bounds__(128 * MI) void spmm_nt_big_kernel(const uint16_t *_
             for (int i = 0; i < 8; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 if (i < 6) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-                if (i < 7) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                if (i < NC - 8) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
+                else if (i < NC) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
             }
         } else {   // four matrix instructions: 4 + 2 + 2 reads and 7 copies between them
 #pragma unroll
@@ -506,9 +514,10 @@ __global__ __launch_bounds__(128 * MI) void spmm_nt_big_kernel(const uint16_t *_
         return;
     }
     // a wave's parking area for its output tile (64 rows of 64 MI bytes) in the drained ring
-    static_assert(MI == 4 ? 3 * EWAVE <= STAGE : 2 * (EWAVE / 2) <= STAGE, "wave tiles must fit the ring stages");
+    static_assert((WN == 4 ? 3 : 2) * (EWAVE * MI / 4) <= STAGE, "wave tiles must fit the ring stages");
     auto region = [&](int w) {
-        if constexpr (MI == 4) return (w < 3 ? s0 : (w < 6 ? s1 : s2)) + (w % 3) * EWAVE;
+        if constexpr (MI == 4 && WN == 2) return (w < 2 ? s0 : s1) + (w & 1) * EWAVE;
+        else if constexpr (MI == 4) return (w < 3 ? s0 : (w < 6 ? s1 : s2)) + (w % 3) * EWAVE;
         else return (w < 2 ? s0 : s1) + (w & 1) * (EWAVE / 2);
     };
     if constexpr (SWIGLU) {
@@ -1443,35 +1452,59 @@ inline int s24_cu_count()
 }
 inline bool fills_chip_256(int64_t m, int64_t n) { return (int64_t)ceil_div(m, 256) * ceil_div(n, 256) >= 3 * s24_cu_count() / 4; }
 
-// Large tile (256 x 256, one workgroup per compute unit) or small tile (128 x 128, two per compute unit)?  The small
-// tile moves twice the bytes per FLOP through L2, so it only pays where the large one leaves compute units idle (few
-// tiles, or a last round that is mostly empty) or where the contraction is so short that a tile is mostly prologue
-// and epilogue, which two co-resident workgroups overlap with each other's main loops.  Cost model in rounds of the
-// large tile: a small-tile round (twice as many workgroups, half the work) takes 0.75 of a large one, 0.6 when the
-// contraction is at most 1024 deep (measured: at K = 768 a large tile spends more time filling and draining than multiplying).
-inline bool small_tile_pays(int64_t M, int64_t N, int64_t K)
+// Which tile a sparse NT product takes.  Costs in full rounds of the large tile at the same depth, measured over 128-16384
+// tokens, 256-4096 x 1024-22016 features (us per 64 of k at K = 5504 to 11008: large 0.75 with every compute unit busy and
+// 0.55 with few; medium 0.52 and 0.37; small 0.62 with two workgroups per compute unit, 0.32 with one, 0.28 with few):
+//   large    256 x 256, one workgroup per compute unit: least LDS and L2 traffic per FLOP, where its tiles fill the chip
+//   medium   256 x 128: between half a round and a round of them, e.g. 4160 tokens x 1600 features, K = 6400: large 68, small
+//            63, medium 54 us; 3001 x 2048, K = 11008: 101, 100, 77 us
+//   small    128 x 128, two per compute unit: at most one round of single ones (1024 x 2048, K = 5504: 53, 36, 29 us), or a
+//            contraction so short that a tile is mostly prologue and epilogue, which two co-resident workgroups overlap
+//            (8192 x 3072, K = 768 with activation: 51, 54, 46 us; 2048 deep: 0.7 of a large round, deeper: 0.82)
+// A grid of large tiles whose last round is mostly empty (320 tiles on 256 compute units) can give its last token-tile rows
+// to a smaller tile: the first `slab` tokens run in whole rounds of large tiles (16384 x 1280, K = 5120: 135 -> 117 us).
+// Tokens are independent rows and every tile sums in the same order: the choice does not change a bit of the result.
+struct NtTile {
+    enum Kind { Large, Medium, Small } kind;
+    int64_t slab;   // tokens of a first launch of its own, or 0
+    int bm() const { return kind == Small ? 128 : 256; }
+    int bn() const { return kind == Large ? 256 : 128; }
+    int threads() const { return kind == Large ? 512 : 256; }
+};
+inline double nt_cost(NtTile::Kind kind, int64_t M, int64_t N, int64_t K)
 {
-    const int cus = s24_cu_count();
-    const int64_t t256 = (int64_t)ceil_div(M, 256) * ceil_div(N, 256), t128 = (int64_t)ceil_div(M, 128) * ceil_div(N, 128);
-    const double round_small = K <= 1024 ? 0.6 : 0.75;
-    return round_small * (double)ceil_div(t128, 2 * cus) < (double)ceil_div(t256, cus);
+    const int64_t cus = s24_cu_count();
+    const NtTile t{kind, 0};
+    const int64_t tiles = (int64_t)ceil_div(M, t.bm()) * ceil_div(N, t.bn()), per = kind == NtTile::Small ? 2 * cus : cus;
+    const double full = (double)(tiles / per), rest = (double)(tiles % per);
+    if (kind == NtTile::Large) return full + (rest > 0 ? 0.73 + 0.27 * rest / per : 0);
+    if (kind == NtTile::Medium) return 0.69 * full + (rest > 0 ? 0.49 + 0.20 * rest / per : 0);
+    const double round = K <= 1024 ? 0.6 : K <= 2048 ? 0.7 : 0.82;
+    return round * full + (rest == 0 ? 0 : rest <= cus ? 0.37 + 0.06 * rest / cus : round);
 }
-
-// A grid of large tiles whose last round is mostly empty (320 tiles on 256 compute units: two rounds for 1.25 rounds
-// of work) can give its last token-tile rows to the small tile instead: the first `slab` tokens run in whole rounds of
-// large tiles, the rest as one resident set of small tiles.  Returns the slab's token count, or 0 where the cost
-// model above does not favour the cut.  Tokens are independent rows of the product, so the result does not change.
-inline int64_t large_tile_slab_tokens(int64_t M, int64_t N, int64_t K)
+inline NtTile nt_tile(int64_t M, int64_t N, int64_t K)
 {
-    const int cus = s24_cu_count();
-    const int64_t tm = ceil_div(M, 256), tiles = tm * ceil_div(N, 256), rounds = (tiles + cus - 1) / cus;
-    if (tiles <= cus || tiles % cus == 0 || tm > cus) return 0;
-    const int64_t rows = ((rounds - 1) * cus) / tm, slab = 256 * rows;   // whole token-tile rows within rounds - 1 rounds
-    const int64_t strip_tiles = (int64_t)ceil_div(M, 128) * ceil_div(N - slab, 128);
-    const double round_small = K <= 1024 ? 0.6 : 0.75;
-    const double cost = (double)ceil_div(rows * tm, cus) + round_small * (double)ceil_div(strip_tiles, 2 * cus);
-    return cost < (double)rounds ? slab : 0;
+    const double l = nt_cost(NtTile::Large, M, N, K), m = nt_cost(NtTile::Medium, M, N, K), s = nt_cost(NtTile::Small, M, N, K);
+    return {l <= m && l <= s ? NtTile::Large : m <= s ? NtTile::Medium : NtTile::Small, 0};
 }
+// The same for a product whose tokens may be cut in two launches
+inline NtTile nt_tile_or_slab(int64_t M, int64_t N, int64_t K)
+{
+    NtTile t = nt_tile(M, N, K);
+    const int64_t cus = s24_cu_count(), tm = ceil_div(M, 256), tiles = tm * ceil_div(N, 256);
+    if (tiles <= cus || tiles % cus == 0 || tm > cus) return t;
+    const int64_t rows = tiles / cus * cus / tm, slab = 256 * rows;   // whole token-tile rows within the whole rounds
+    const NtTile strip = nt_tile(M, N - slab, K);
+    if (nt_cost(NtTile::Large, M, slab, K) + nt_cost(strip.kind, M, N - slab, K) < nt_cost(t.kind, M, N, K)) t.slab = slab;
+    return t;
+}
+// Runs MACRO(..., MI, WN) with the wave layout of a tile
+#define S24_WITH_NT_TILE(tile, MACRO, ...)                              \
+    do {                                                                \
+        if ((tile).kind == NtTile::Large) MACRO(__VA_ARGS__, 4, 4);     \
+        else if ((tile).kind == NtTile::Medium) MACRO(__VA_ARGS__, 4, 2); \
+        else MACRO(__VA_ARGS__, 2, 2);                                  \
+    } while (0)
 
 // Out[N][M] = beta * Out + B[N][K] . A^T (+ bias[M], only with beta = 0)
 int launch_spmm(const void *B, const void *Av, const uint16_t *Am, void *Out, int64_t N, int64_t K, int64_t M, float beta,
@@ -1485,47 +1518,25 @@ int launch_spmm(const void *B, const void *Av, const uint16_t *Am, void *Out, in
     }
     auto *b = static_cast<const uint16_t *>(B), *av = static_cast<const uint16_t *>(Av), *d = static_cast<const uint16_t *>(bias);
     auto *o = static_cast<uint16_t *>(Out);
-    const int tm256 = (int)ceil_div(M, 256), tn256 = (int)ceil_div(N, 256), tm128 = (int)ceil_div(M, 128), tn128 = (int)ceil_div(N, 128);
-    S24_REQUIRE((int64_t)tm128 * tn128 < (1ll << 30), S24_ERR_SHAPE);
-    if (!small_tile_pays(M, N, K)) {
-        if (const int64_t slab = large_tile_slab_tokens(M, N, K)) {
-            const int rc = launch_spmm(B, Av, Am, Out, slab, K, M, beta, dt, st, bias);
-            if (rc != S24_OK) return rc;
-            return launch_spmm(b + slab * K, Av, Am, o + slab * M, N - slab, K, M, beta, dt, st, bias);
-        }
-        const int tiles_m = tm256, tiles_n = tn256;
-        const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-        const dim3 grid(per_xcd * 8), block(big::THREADS);
-        S24_WITH_16BIT_TYPE(dt, {
-            if (accum)
-                hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, true>), grid, block, 0, st, b, av, Am, o, (int)N, (int)K, (int)M,
-                                   tiles_m, tiles_n, g_clock_probe, nullptr, 0, nullptr, nullptr);
-            else if (d != nullptr)
-                hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, false, false, false, S24_GATE_SILU, true>), grid, block, 0, st, b,
-                                   av, Am, o, (int)N, (int)K, (int)M, tiles_m, tiles_n, g_clock_probe, nullptr, 0, nullptr, d);
-            else
-                hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, false>), grid, block, 0, st, b, av, Am, o, (int)N, (int)K, (int)M,
-                                   tiles_m, tiles_n, g_clock_probe, nullptr, 0, nullptr, nullptr);
-        });
-    } else {
-        const int tiles_m = tm128, tiles_n = tn128;
-        const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-        const dim3 grid(per_xcd * 8), block(256);
-        S24_WITH_16BIT_TYPE(dt, {
-            if (accum)
-                hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, true, false, false, S24_GATE_SILU, false, 0, S24_ACT_RELU, 2>), grid,
-                                   block, 0, st, b, av, Am, o, (int)N, (int)K, (int)M, tiles_m, tiles_n, nullptr, nullptr, 0,
-                                   nullptr, nullptr);
-            else if (d != nullptr)
-                hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, false, false, false, S24_GATE_SILU, true, 0, S24_ACT_RELU, 2>), grid,
-                                   block, 0, st, b, av, Am, o, (int)N, (int)K, (int)M, tiles_m, tiles_n, nullptr, nullptr, 0,
-                                   nullptr, d);
-            else
-                hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, false, false, false, S24_GATE_SILU, false, 0, S24_ACT_RELU, 2>), grid,
-                                   block, 0, st, b, av, Am, o, (int)N, (int)K, (int)M, tiles_m, tiles_n, nullptr, nullptr, 0,
-                                   nullptr, nullptr);
-        });
+    S24_REQUIRE((int64_t)ceil_div(M, 128) * ceil_div(N, 128) < (1ll << 30), S24_ERR_SHAPE);
+    const NtTile tile = nt_tile_or_slab(M, N, K);
+    if (tile.slab != 0) {
+        const int rc = launch_spmm(B, Av, Am, Out, tile.slab, K, M, beta, dt, st, bias);
+        if (rc != S24_OK) return rc;
+        return launch_spmm(b + tile.slab * K, Av, Am, o + tile.slab * M, N - tile.slab, K, M, beta, dt, st, bias);
     }
+    const int tiles_m = (int)ceil_div(M, tile.bm()), tiles_n = (int)ceil_div(N, tile.bn());
+    const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(tile.threads());
+#define S24_LAUNCH_NT(ACC, BIASED, MI, WN)                                                                                             \
+    hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, ACC, false, false, S24_GATE_SILU, BIASED, 0, S24_ACT_RELU, MI, WN>), grid, block, 0, \
+                       st, b, av, Am, o, (int)N, (int)K, (int)M, tiles_m, tiles_n, tile.kind == NtTile::Large ? g_clock_probe : nullptr, \
+                       nullptr, 0, nullptr, d)
+    S24_WITH_16BIT_TYPE(dt, {
+        if (accum) S24_WITH_NT_TILE(tile, S24_LAUNCH_NT, true, false);
+        else if (d != nullptr) S24_WITH_NT_TILE(tile, S24_LAUNCH_NT, false, true);
+        else S24_WITH_NT_TILE(tile, S24_LAUNCH_NT, false, false);
+    });
+#undef S24_LAUNCH_NT
     return s24_launch_status();
 }
 
@@ -1570,17 +1581,26 @@ extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t 
     S24_REQUIRE(meta != nullptr && H != nullptr, S24_ERR_NULL);
     S24_REQUIRE(s24_aligned(meta, 4) && s24_aligned(H, 16) && s24_aligned(bias, 8), S24_ERR_ALIGN);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int tiles_m = (int)ceil_div(f, 128), tiles_n = (int)ceil_div(p, big::BN);
-    if (dt != S24_F32 && (int64_t)tiles_m * tiles_n >= 3 * s24_cu_count() / 4) {
-        const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(big::THREADS);
+    NtTile tile = nt_tile(2 * f, p, q);
+    // the small tile has no gated epilogue: it is taken only where it saves more than a launch for the activation
+    if (tile.kind == NtTile::Small) {
+        const double l = nt_cost(NtTile::Large, 2 * f, p, q), m = nt_cost(NtTile::Medium, 2 * f, p, q);
+        if (std::min(l, m) < nt_cost(NtTile::Small, 2 * f, p, q) + 0.1) tile.kind = l <= m ? NtTile::Large : NtTile::Medium;
+    }
+    if (dt != S24_F32 && tile.kind != NtTile::Small) {   // 128 gate and 128 up features per tile
+        const int tiles_m = (int)ceil_div(f, 128), tiles_n = (int)ceil_div(p, tile.bn());
+        const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(tile.threads());
         auto *x = static_cast<const uint16_t *>(X), *av = static_cast<const uint16_t *>(vals), *d = static_cast<const uint16_t *>(bias);
         auto *gu = static_cast<uint16_t *>(GU), *h = static_cast<uint16_t *>(H);
-#define S24_LAUNCH_FWD_GLU(G)                                                                                              \
-    hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, false, true, false, G>), grid, block, 0, st, x, av, meta, gu, (int)p, \
-                       (int)q, (int)(2 * f), tiles_m, tiles_n, g_clock_probe, h, (int)f, nullptr, d)
+#define S24_LAUNCH_FWD_GLU(G, WN)                                                                                                    \
+    hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, false, true, false, G, false, 0, S24_ACT_RELU, 4, WN>), grid, block, 0, st, x, av, meta, \
+                       gu, (int)p, (int)q, (int)(2 * f), tiles_m, tiles_n, tile.kind == NtTile::Large ? g_clock_probe : nullptr, h, (int)f, \
+                       nullptr, d)
         S24_WITH_16BIT_TYPE(dt, {
-            if (gate == S24_GATE_SILU) S24_LAUNCH_FWD_GLU(S24_GATE_SILU);
-            else S24_LAUNCH_FWD_GLU(S24_GATE_GELU_ERF);
+            if (gate == S24_GATE_SILU && tile.kind == NtTile::Large) S24_LAUNCH_FWD_GLU(S24_GATE_SILU, 4);
+            else if (gate == S24_GATE_SILU) S24_LAUNCH_FWD_GLU(S24_GATE_SILU, 2);
+            else if (tile.kind == NtTile::Large) S24_LAUNCH_FWD_GLU(S24_GATE_GELU_ERF, 4);
+            else S24_LAUNCH_FWD_GLU(S24_GATE_GELU_ERF, 2);
         });
 #undef S24_LAUNCH_FWD_GLU
         return s24_launch_status();
@@ -1644,29 +1664,23 @@ extern "C" int s24_spmm_fwd_act(const void *X, const void *vals, const uint16_t 
     S24_REQUIRE(s24_aligned(meta, 4) && s24_aligned(H, 16) && s24_aligned(bias, 8), S24_ERR_ALIGN);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (dt != S24_F32) {
-        const bool small = small_tile_pays(r, p, q);
-        const int tile = small ? 128 : 256;
-        const int tiles_m = (int)ceil_div(r, tile), tiles_n = (int)ceil_div(p, tile);
+        const NtTile tile = nt_tile(r, p, q);
+        const int tiles_m = (int)ceil_div(r, tile.bm()), tiles_n = (int)ceil_div(p, tile.bn());
         S24_REQUIRE((int64_t)tiles_m * tiles_n < (1ll << 30), S24_ERR_SHAPE);
-        const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(small ? 256 : big::THREADS);
+        const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(tile.threads());
         auto *x = static_cast<const uint16_t *>(X), *av = static_cast<const uint16_t *>(vals), *d = static_cast<const uint16_t *>(bias);
         auto *z = static_cast<uint16_t *>(Z), *h = static_cast<uint16_t *>(H);
-#define S24_LAUNCH_FWD_ACT_MI(A, BIASED, MI_)                                                                                       \
-    hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, false, false, false, S24_GATE_SILU, BIASED, 1, A, MI_>), grid, block, 0, st, x, \
-                       av, meta, z, (int)p, (int)q, (int)r, tiles_m, tiles_n, small ? nullptr : g_clock_probe, h, 0, nullptr, d)
-#define S24_LAUNCH_FWD_ACT(A, BIASED)                 \
-    do {                                              \
-        if (small) S24_LAUNCH_FWD_ACT_MI(A, BIASED, 2); \
-        else S24_LAUNCH_FWD_ACT_MI(A, BIASED, 4);     \
-    } while (0)
+#define S24_LAUNCH_FWD_ACT(A, BIASED, MI, WN)                                                                                           \
+    hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, false, false, false, S24_GATE_SILU, BIASED, 1, A, MI, WN>), grid, block, 0, st, x, av, \
+                       meta, z, (int)p, (int)q, (int)r, tiles_m, tiles_n, tile.kind == NtTile::Large ? g_clock_probe : nullptr, h, 0,     \
+                       nullptr, d)
         S24_WITH_16BIT_TYPE(dt, {
-            if (act == S24_ACT_RELU && d != nullptr) S24_LAUNCH_FWD_ACT(S24_ACT_RELU, true);
-            else if (act == S24_ACT_RELU) S24_LAUNCH_FWD_ACT(S24_ACT_RELU, false);
-            else if (d != nullptr) S24_LAUNCH_FWD_ACT(S24_ACT_GELU_ERF, true);
-            else S24_LAUNCH_FWD_ACT(S24_ACT_GELU_ERF, false);
+            if (act == S24_ACT_RELU && d != nullptr) S24_WITH_NT_TILE(tile, S24_LAUNCH_FWD_ACT, S24_ACT_RELU, true);
+            else if (act == S24_ACT_RELU) S24_WITH_NT_TILE(tile, S24_LAUNCH_FWD_ACT, S24_ACT_RELU, false);
+            else if (d != nullptr) S24_WITH_NT_TILE(tile, S24_LAUNCH_FWD_ACT, S24_ACT_GELU_ERF, true);
+            else S24_WITH_NT_TILE(tile, S24_LAUNCH_FWD_ACT, S24_ACT_GELU_ERF, false);
         });
 #undef S24_LAUNCH_FWD_ACT
-#undef S24_LAUNCH_FWD_ACT_MI
         return s24_launch_status();
     }
     return s24_f32_nt({static_cast<const float *>(X), static_cast<const float *>(vals), meta, static_cast<float *>(Z), static_cast<float *>(H),
@@ -1684,28 +1698,22 @@ extern "C" int s24_spmm_bwd_dx_act(const void *dY, const void *valsT, const uint
     S24_REQUIRE(s24_aligned(metaT, 4) && s24_aligned(Z, 16), S24_ERR_ALIGN);
     // the 16-bit kernels carry this epilogue; fp32 takes s24_spmm_bwd_dx + s24_act_bwd
     S24_REQUIRE(dt != S24_F32, S24_ERR_UNSUPPORTED);
-    const bool small = small_tile_pays(f, p, r);
-    const int tile = small ? 128 : 256;
-    const int tiles_m = (int)ceil_div(f, tile), tiles_n = (int)ceil_div(p, tile);
+    const NtTile tile = nt_tile(f, p, r);
+    const int tiles_m = (int)ceil_div(f, tile.bm()), tiles_n = (int)ceil_div(p, tile.bn());
     S24_REQUIRE((int64_t)tiles_m * tiles_n < (1ll << 30), S24_ERR_SHAPE);
-    const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(small ? 256 : big::THREADS);
+    const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(tile.threads());
     hipStream_t st = static_cast<hipStream_t>(stream);
     auto *dy = static_cast<const uint16_t *>(dY), *av = static_cast<const uint16_t *>(valsT), *z = static_cast<const uint16_t *>(Z);
     auto *o = static_cast<uint16_t *>(dZ);
-#define S24_LAUNCH_BWD_ACT_MI(A, MI_)                                                                                                 \
-    hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, false, false, false, S24_GATE_SILU, false, 2, A, MI_>), grid, block, 0, st, dy, av, \
-                       metaT, o, (int)p, (int)r, (int)f, tiles_m, tiles_n, small ? nullptr : g_clock_probe, nullptr, 0, z, nullptr)
-#define S24_LAUNCH_BWD_ACT(A)                   \
-    do {                                        \
-        if (small) S24_LAUNCH_BWD_ACT_MI(A, 2); \
-        else S24_LAUNCH_BWD_ACT_MI(A, 4);       \
-    } while (0)
+#define S24_LAUNCH_BWD_ACT(A, MI, WN)                                                                                                  \
+    hipLaunchKernelGGL((big::spmm_nt_big_kernel<T, false, false, false, S24_GATE_SILU, false, 2, A, MI, WN>), grid, block, 0, st, dy, av, \
+                       metaT, o, (int)p, (int)r, (int)f, tiles_m, tiles_n, tile.kind == NtTile::Large ? g_clock_probe : nullptr, nullptr, \
+                       0, z, nullptr)
     S24_WITH_16BIT_TYPE(dt, {
-        if (act == S24_ACT_RELU) S24_LAUNCH_BWD_ACT(S24_ACT_RELU);
-        else S24_LAUNCH_BWD_ACT(S24_ACT_GELU_ERF);
+        if (act == S24_ACT_RELU) S24_WITH_NT_TILE(tile, S24_LAUNCH_BWD_ACT, S24_ACT_RELU);
+        else S24_WITH_NT_TILE(tile, S24_LAUNCH_BWD_ACT, S24_ACT_GELU_ERF);
     });
 #undef S24_LAUNCH_BWD_ACT
-#undef S24_LAUNCH_BWD_ACT_MI
     return s24_launch_status();
 }
 

@@ -150,3 +150,40 @@ def test_l1_norm_gap_by_classes(s24, dtype, kind):
     assert np.array_equal(got[exact], ref[exact]), kind
     # beyond it both carry fp64 rounding: eight additions, each 2^-53 of the block's kept norm, in either sum
     assert np.all(np.abs(got - ref)[~exact] <= 16 * 2.0 ** -53 * a.sum(-1)[~exact])
+
+
+# ------------------------------------------------------------------ sparse products on the 256 x 128 tile
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+# (p, q, r): one, two, three and four chunks of the ring, ragged in both directions (136 tiles); a strip of such tiles
+# after a slab of large ones (51 rows of tiles, then 26 of half their height)
+@pytest.mark.parametrize("pqr", [(2050, 64, 2016), (2050, 128, 2016), (2049, 192, 2048), (2061, 256, 2016), (16390, 64, 1248)])
+def test_medium_tile_and_its_epilogues(s24, dtype, pqr):
+    p, q, r = pqr
+    r64 = (r + 63) // 64 * 64
+    W, X = si.random_matrix(70 + q, (r64, q), 0.02, dtype), si.random_matrix(71 + p, (p, q), 1.0, dtype)
+    bias, Zin = si.random_matrix(72, (1, r), 0.5, dtype)[0], si.random_matrix(73, (p, r), 1.0, dtype)
+    cv, cm = (np.ascontiguousarray(a[:r]) for a in oracle.compress(W, oracle.transposable_mask(W))[:2])
+    v, m = oracle.pack(cv, cm)
+    v, m, x, b = dev_bf16(v), dev(m), dev_bf16(X), dev_bf16(bias)
+    rows = np.unique(np.concatenate([[0, 1, 127, 128, 255, 256, p - 2, p - 1], np.random.default_rng(p).integers(0, p, 40)]))
+    at = torch.from_numpy(rows).cuda()
+    ref = oracle.spmm_fwd(X, cv, cm, rows=rows)
+    tol, new = tol_for(dtype), lambda n: torch.full((p, n), 7.0, dtype=torch_dtype(dtype), device="cuda")
+    Y, Z, H, dZ = new(r), new(r), new(r), new(r)
+    s24.spmm_fwd(x, v, m, Y)
+    assert_close(host_f64(Y[at]), ref, tol, f"spmm_fwd {pqr}")
+    Y2 = Y.clone()
+    s24.spmm_bwd_dx(x, v, m, Y2, beta=1.0)
+    assert_close(host_f64(Y2[at]), ref + host_f64(Y[at]), tol, f"accumulate {pqr}")
+    s24.spmm_fwd_act(x, v, m, b, Z, H, s24.ACT_GELU_ERF)
+    assert_close(host_f64(Z[at]), ref + host_f64(b), tol, f"spmm_fwd_act {pqr}")
+    two = torch.empty_like(H)
+    s24.act_fwd(Z, two, s24.ACT_GELU_ERF)
+    assert torch.equal(H.view(torch.int16), two.view(torch.int16))
+    s24.spmm_bwd_dx_act(x, v, m, dev_bf16(Zin), dZ, s24.ACT_GELU_ERF)
+    s24.act_bwd(Y, dev_bf16(Zin), two, s24.ACT_GELU_ERF)
+    assert torch.equal(dZ.view(torch.int16), two.view(torch.int16))
+    GU, Hg, two = new(r), new(r // 2), new(r // 2)
+    s24.spmm_fwd_glu(x, v, m, b, GU, Hg, s24.GATE_SILU)
+    s24.glu_fwd(GU, two, s24.GATE_SILU)
+    assert torch.equal(GU.view(torch.int16), Z.view(torch.int16)) and torch.equal(Hg.view(torch.int16), two.view(torch.int16))
