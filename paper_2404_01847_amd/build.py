@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libs24.so")
 OBJ = os.path.join(HERE, "_build")
 
-SOURCES = ["s24_host.hip", "s24_mask.hip", "s24_elementwise.hip", "s24_gemm.hip", "s24_gemm_f32.hip", "s24_mvue.hip", "s24_probe.hip"]
+SOURCES = ["s24_host.hip", "s24_mask.hip", "s24_elementwise.hip", "s24_gemm.hip", "s24_gemm_f32.hip", "s24_gemm_slice.hip", "s24_mvue.hip", "s24_probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]

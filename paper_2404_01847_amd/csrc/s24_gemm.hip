@@ -8,7 +8,7 @@
 //   dense  NT  Y = X W^T (Eq. 1, first GEMM; the comparison kernel): v_mfma_f32_32x32x16_{bf16,f16}
 //   dense  TN  dW = dY^T X (Eq. 1, third GEMM): both operands copied as they lie in memory, k-contiguous
 //              fragments by ds_read_b64_tr_b16; masked decay (Eq. 10) as an optional epilogue
-// fp32 data takes the kernels of s24_gemm_f32.hip.
+// fp32 data takes the kernels of s24_gemm_f32.hip, sparse NT products of few tokens or features those of s24_gemm_slice.hip.
 //
 // Register layout of the sparse instruction (one 32x32 tile, 32 of k):
 // lane l holds for A row l%32 the eight kept values of k in [16*(l/32),
@@ -22,6 +22,7 @@
 #include <algorithm>
 
 #include "s24_gemm_f32.h"
+#include "s24_gemm_slice.h"
 
 namespace {
 
@@ -1519,6 +1520,7 @@ int launch_spmm(const void *B, const void *Av, const uint16_t *Am, void *Out, in
     auto *b = static_cast<const uint16_t *>(B), *av = static_cast<const uint16_t *>(Av), *d = static_cast<const uint16_t *>(bias);
     auto *o = static_cast<uint16_t *>(Out);
     S24_REQUIRE((int64_t)ceil_div(M, 128) * ceil_div(N, 128) < (1ll << 30), S24_ERR_SHAPE);
+    if (s24_slice_pays(N, K, M)) return s24_slice_nt({b, av, Am, o, nullptr, nullptr, d, N, K, M, accum, S24_SLICE_PLAIN, 0}, dt, st);
     const NtTile tile = nt_tile_or_slab(M, N, K);
     if (tile.slab != 0) {
         const int rc = launch_spmm(B, Av, Am, Out, tile.slab, K, M, beta, dt, st, bias);
@@ -1581,6 +1583,9 @@ extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t 
     S24_REQUIRE(meta != nullptr && H != nullptr, S24_ERR_NULL);
     S24_REQUIRE(s24_aligned(meta, 4) && s24_aligned(H, 16) && s24_aligned(bias, 8), S24_ERR_ALIGN);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (dt != S24_F32 && s24_slice_pays(p, q, 2 * f))
+        return s24_slice_nt({static_cast<const uint16_t *>(X), static_cast<const uint16_t *>(vals), meta, static_cast<uint16_t *>(GU),
+                             static_cast<uint16_t *>(H), nullptr, static_cast<const uint16_t *>(bias), p, q, 2 * f, false, S24_SLICE_GLU, gate}, dt, st);
     NtTile tile = nt_tile(2 * f, p, q);
     // the small tile has no gated epilogue: it is taken only where it saves more than a launch for the activation
     if (tile.kind == NtTile::Small) {
@@ -1664,6 +1669,9 @@ extern "C" int s24_spmm_fwd_act(const void *X, const void *vals, const uint16_t 
     S24_REQUIRE(s24_aligned(meta, 4) && s24_aligned(H, 16) && s24_aligned(bias, 8), S24_ERR_ALIGN);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (dt != S24_F32) {
+        if (s24_slice_pays(p, q, r))
+            return s24_slice_nt({static_cast<const uint16_t *>(X), static_cast<const uint16_t *>(vals), meta, static_cast<uint16_t *>(Z),
+                                 static_cast<uint16_t *>(H), nullptr, static_cast<const uint16_t *>(bias), p, q, r, false, S24_SLICE_ACT, act}, dt, st);
         const NtTile tile = nt_tile(r, p, q);
         const int tiles_m = (int)ceil_div(r, tile.bm()), tiles_n = (int)ceil_div(p, tile.bn());
         S24_REQUIRE((int64_t)tiles_m * tiles_n < (1ll << 30), S24_ERR_SHAPE);
@@ -1698,6 +1706,9 @@ extern "C" int s24_spmm_bwd_dx_act(const void *dY, const void *valsT, const uint
     S24_REQUIRE(s24_aligned(metaT, 4) && s24_aligned(Z, 16), S24_ERR_ALIGN);
     // the 16-bit kernels carry this epilogue; fp32 takes s24_spmm_bwd_dx + s24_act_bwd
     S24_REQUIRE(dt != S24_F32, S24_ERR_UNSUPPORTED);
+    if (s24_slice_pays(p, r, f))
+        return s24_slice_nt({static_cast<const uint16_t *>(dY), static_cast<const uint16_t *>(valsT), metaT, static_cast<uint16_t *>(dZ), nullptr,
+                             static_cast<const uint16_t *>(Z), nullptr, p, r, f, false, S24_SLICE_ACT_BWD, act}, dt, static_cast<hipStream_t>(stream));
     const NtTile tile = nt_tile(f, p, r);
     const int tiles_m = (int)ceil_div(f, tile.bm()), tiles_n = (int)ceil_div(p, tile.bn());
     S24_REQUIRE((int64_t)tiles_m * tiles_n < (1ll << 30), S24_ERR_SHAPE);

@@ -1,0 +1,273 @@
+// Sparse NT products of few tokens or few features, bf16 and binary16: out[n][m] = sum_k B[n][k] A[m][k] with A compressed
+// along k, on v_smfmac_f32_16x16x64_{bf16,f16}.
+//
+// What bounds them is latency and then the first-level cache: with one 128 x 128 tile per workgroup, 16 tokens x 4096 features
+// are 32 workgroups that walk K = 11008 in 172 steps of 0.28 us each on an eighth of the chip.  Here a tile is 16 x 16 to
+// 64 x 32, eight waves of a workgroup split its contraction, fragments come from memory straight into registers (each is used
+// by one wave of the workgroup only), and the slices are summed in LDS.  16 tokens, K = 4096 and 11008 (a gated layer of
+// 4096 x 11008, 152 MB of compressed weights): 30 + 60 -> 23 + 16 us, the activation's launch gone; 64 x 2048, K = 5504:
+// 24.5 -> 10.7; 256 x 768, K = 3072: 15.7 -> 9.1; 1024 x 1024, K = 256: 8.8 -> 5.1.
+//
+// Operands of the instruction: lane l holds, of A row l%16, the eight kept values of k in [16*(l/16), 16*(l/16)+16) with
+// their 2-bit positions in the low half of the index register; of B column l%16, element j is k = 32*(j/8) + 8*(l/16) + j%8;
+// accumulator i is row 4*(l/16) + i of column l%16.  In the chunk-major storage (vals[K/64][M][32], meta[K/64][M][4]) 16
+// rows of a chunk are 1024 contiguous bytes, lane by lane in this order, and a lane's index word is the uint16 behind
+// them: a fragment is one fully coalesced 16-byte load, with no LDS in between.
+#include "s24_gemm_slice.h"
+
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(16))) __bf16 bf16x16;
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
+typedef __attribute__((ext_vector_type(16))) _Float16 f16x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+struct Two { uint4 a, b; };
+
+template <typename T> __device__ __forceinline__ f32x4 mma(uint4 a, Two b, f32x4 c, uint32_t idx);
+template <> __device__ __forceinline__ f32x4 mma<uint16_t>(uint4 a, Two b, f32x4 c, uint32_t idx)
+{
+    return __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x16, b), c, (int)idx, 0, 0);
+}
+template <> __device__ __forceinline__ f32x4 mma<s24_half>(uint4 a, Two b, f32x4 c, uint32_t idx)
+{
+    return __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x16, b), c, (int)idx, 0, 0);
+}
+
+struct NtArgs {
+    const uint16_t *B, *Av, *Am;
+    uint16_t *Out, *H;
+    const uint16_t *Z, *bias;
+    int N, K, M, F;   // F: gated features (GLU)
+    int tiles_n, tiles;
+};
+
+template <int ACT> __device__ __forceinline__ float act_value(float z) { return ACT == S24_ACT_RELU ? (z > 0.0f ? z : 0.0f) : s24_gelu(z); }
+template <int ACT> __device__ __forceinline__ float act_slope(float z) { return ACT == S24_ACT_RELU ? (z > 0.0f ? 1.0f : 0.0f) : s24_gelu_slope(z); }
+
+// Slices per workgroup.  One number for all shapes: an output's bits then depend on K alone, so that one stacked weight and
+// its two halves, or a product with and without a fused epilogue, agree to the last bit.
+constexpr int KS = 8;
+
+// A workgroup owns 16*TM features x 16*TN tokens; wave s of its KS waves takes the 64-chunks s, s + KS, ... of the
+// contraction, D of them in flight, and the slices are summed in LDS in wave order, so the result does not depend on
+// scheduling.  GLU: the tile's row blocks are 8*TM gate rows and the 8*TM up rows of the same features.
+template <typename T, bool ACCUM, int EPI, int ACT, int TM, int TN>
+__global__ __launch_bounds__(64 * KS) void spmm_slice_kernel(const NtArgs g)
+{
+    static_assert(EPI != S24_SLICE_GLU || TM % 2 == 0, "the gated tile pairs row blocks");
+    constexpr int THREADS = 64 * KS, D = TM + TN <= 3 ? 4 : 2;
+    constexpr int TWM = 16 * TM, TWN = 16 * TN, PITCH = TWM + 4, SLICE = TWN * PITCH;
+    constexpr int FM = EPI == S24_SLICE_GLU ? TWM / 2 : TWM;   // features of the (gated) output per tile
+    __shared__ __attribute__((aligned(16))) float s_red[KS * SLICE];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // workgroups are dealt round-robin to the eight XCDs: each takes one contiguous eighth of the tile list, the token
+    // tiles of one feature tile next to each other, so that they read its weights through one L2
+    const int per_xcd = (g.tiles + 7) / 8, t = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (t >= g.tiles) return;
+    const int tm = t / g.tiles_n, tn = t - tm * g.tiles_n;
+    const int m0 = tm * FM, n0 = tn * TWN;
+    const int l = lane & 15, q = lane >> 4;
+
+    // byte offsets of this lane from wave-uniform bases (rows clamped at the edge; such rows are never stored)
+    uint32_t oa[TM], ob[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int row = EPI == S24_SLICE_GLU ? (i < TM / 2 ? 0 : g.F) + min(m0 + 16 * (i % (TM / 2 > 0 ? TM / 2 : 1)) + l, g.F - 1)
+                                             : min(m0 + 16 * i + l, g.M - 1);
+        oa[i] = (uint32_t)row * 64u + 16u * q;
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) ob[j] = (uint32_t)(min(n0 + 16 * j + l, g.N - 1) - n0) * (uint32_t)g.K * 2u + 16u * q;
+    const char *baseB = reinterpret_cast<const char *>(g.B + (int64_t)n0 * g.K);
+    const char *baseV = reinterpret_cast<const char *>(g.Av), *baseM = reinterpret_cast<const char *>(g.Am);
+
+    struct Frag { uint4 a[TM]; uint32_t ix[TM]; Two b[TN]; };
+    auto load = [&](Frag &f, int c) {
+        const char *pv = baseV + (int64_t)c * g.M * 64, *pm = baseM + (int64_t)c * g.M * 8, *pb = baseB + (int64_t)c * 128;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) f.a[i] = *reinterpret_cast<const uint4 *>(pv + oa[i]);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) f.ix[i] = *reinterpret_cast<const uint16_t *>(pm + (oa[i] >> 3));
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            f.b[j].a = *reinterpret_cast<const uint4 *>(pb + ob[j]);
+            f.b[j].b = *reinterpret_cast<const uint4 *>(pb + ob[j] + 64);
+        }
+    };
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{};
+    auto multiply = [&](const Frag &f) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = mma<T>(f.a[i], f.b[j], acc[i][j], f.ix[i]);
+    };
+    const int nk = g.K / 64, steps = ks < nk ? (nk - ks + KS - 1) / KS : 0;
+    Frag f[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (d < steps) load(f[d], ks + KS * d);
+    int i = 0;
+    for (; i + 2 * D <= steps; i += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            multiply(f[d]);
+            load(f[d], ks + KS * (i + D + d));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (i + d < steps) {
+            multiply(f[d]);
+            if (i + D + d < steps) load(f[d], ks + KS * (i + D + d));
+        }
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (i + D + d < steps) multiply(f[d]);
+
+    float *part = s_red + ks * SLICE;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int k = 0; k < TM; ++k)
+            *reinterpret_cast<float4 *>(part + (16 * j + l) * PITCH + 16 * k + 4 * q) = make_float4(acc[k][j][0], acc[k][j][1], acc[k][j][2], acc[k][j][3]);
+
+    // four features of one token per item; what the epilogue reads from memory is fetched ahead of the barrier
+    using Num = s24_num<T>;
+    constexpr int QUADS = FM / 4, ITEMS = TWN * QUADS, PER = (ITEMS + THREADS - 1) / THREADS;
+    const int limit = EPI == S24_SLICE_GLU ? g.F : g.M;
+    uint2 old[PER], b0[PER], b1[PER];
+    bool live[PER];
+    int64_t at[PER];
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        const int it = tid + p * THREADS, m = m0 + 4 * (it % QUADS), n = n0 + it / QUADS;
+        live[p] = it < ITEMS && n < g.N && m < limit;   // M and F are multiples of 16
+        at[p] = (int64_t)n * g.M + m;
+        old[p] = b0[p] = b1[p] = make_uint2(0, 0);
+        if (live[p]) {
+            if (ACCUM) old[p] = *reinterpret_cast<const uint2 *>(g.Out + at[p]);
+            if (EPI == S24_SLICE_ACT_BWD) old[p] = *reinterpret_cast<const uint2 *>(g.Z + at[p]);
+            if (!ACCUM && EPI != S24_SLICE_ACT_BWD && g.bias != nullptr) {
+                b0[p] = *reinterpret_cast<const uint2 *>(g.bias + m);
+                if (EPI == S24_SLICE_GLU) b1[p] = *reinterpret_cast<const uint2 *>(g.bias + g.F + m);
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        if (!live[p]) continue;
+        const int it = tid + p * THREADS;
+        const float *src = s_red + (it / QUADS) * PITCH + 4 * (it % QUADS);
+        // sum of the slices, plus two packed addends (bias, or the old output); without them the bits of the sum stay
+        auto total = [&](const float *s, uint2 add, bool has) {
+            float4 v = *reinterpret_cast<const float4 *>(s);
+#pragma unroll
+            for (int k = 1; k < KS; ++k) {
+                const float4 o = *reinterpret_cast<const float4 *>(s + k * SLICE);
+                v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+            }
+            if (has) { v.x += Num::lo(add.x); v.y += Num::hi(add.x); v.z += Num::lo(add.y); v.w += Num::hi(add.y); }
+            return v;
+        };
+        auto packed = [&](float4 v) { return make_uint2(Num::pack2(v.x, v.y), Num::pack2(v.z, v.w)); };
+        const bool biased = !ACCUM && EPI != S24_SLICE_ACT_BWD && g.bias != nullptr;
+        const uint2 z = packed(total(src, ACCUM ? old[p] : b0[p], ACCUM || biased));
+        uint16_t *out = g.Out + at[p];
+        if constexpr (EPI == S24_SLICE_ACT_BWD) {
+            *reinterpret_cast<uint2 *>(out) =
+                make_uint2(Num::pack2(Num::lo(z.x) * act_slope<ACT>(Num::lo(old[p].x)), Num::hi(z.x) * act_slope<ACT>(Num::hi(old[p].x))),
+                           Num::pack2(Num::lo(z.y) * act_slope<ACT>(Num::lo(old[p].y)), Num::hi(z.y) * act_slope<ACT>(Num::hi(old[p].y))));
+        } else {
+            *reinterpret_cast<uint2 *>(out) = z;
+            if constexpr (EPI == S24_SLICE_ACT)
+                *reinterpret_cast<uint2 *>(g.H + at[p]) =
+                    make_uint2(Num::pack2(act_value<ACT>(Num::lo(z.x)), act_value<ACT>(Num::hi(z.x))),
+                               Num::pack2(act_value<ACT>(Num::lo(z.y)), act_value<ACT>(Num::hi(z.y))));
+            if constexpr (EPI == S24_SLICE_GLU) {
+                const uint2 u = packed(total(src + FM, b1[p], biased));
+                *reinterpret_cast<uint2 *>(out + g.F) = u;
+                const int64_t n = n0 + it / QUADS, m = m0 + 4 * (it % QUADS);
+                *reinterpret_cast<uint2 *>(g.H + n * g.F + m) =
+                    make_uint2(Num::pack2(s24_glu<ACT>(Num::lo(z.x), Num::lo(u.x)), s24_glu<ACT>(Num::hi(z.x), Num::hi(u.x))),
+                               Num::pack2(s24_glu<ACT>(Num::lo(z.y), Num::lo(u.y)), s24_glu<ACT>(Num::hi(z.y), Num::hi(u.y))));
+            }
+        }
+    }
+}
+
+template <typename T, bool ACCUM, int EPI, int ACT, int TM, int TN>
+void launch(const S24SliceNt &g, hipStream_t st)
+{
+    constexpr int FM = EPI == S24_SLICE_GLU ? 8 * TM : 16 * TM;
+    const int64_t F = g.M / 2, feats = EPI == S24_SLICE_GLU ? F : g.M;
+    const int tiles_m = (int)((feats + FM - 1) / FM), tiles_n = (int)((g.N + 16 * TN - 1) / (16 * TN)), tiles = tiles_m * tiles_n;
+    const NtArgs a{g.B, g.Av, g.Am, g.Out, g.H, g.Z, g.bias, (int)g.N, (int)g.K, (int)g.M, (int)F, tiles_n, tiles};
+    hipLaunchKernelGGL((spmm_slice_kernel<T, ACCUM, EPI, ACT, TM, TN>), dim3(((tiles + 7) / 8) * 8), dim3(64 * KS), 0, st, a);
+}
+
+template <typename T, int TM, int TN> int launch_epilogue(const S24SliceNt &g, hipStream_t st)
+{
+    if (g.epilogue == S24_SLICE_PLAIN) {
+        if (g.accum) launch<T, true, S24_SLICE_PLAIN, 0, TM, TN>(g, st);
+        else launch<T, false, S24_SLICE_PLAIN, 0, TM, TN>(g, st);
+    } else if (g.epilogue == S24_SLICE_GLU) {
+        constexpr int TG = TM < 2 ? 2 : TM;
+        if (g.act == S24_GATE_SILU) launch<T, false, S24_SLICE_GLU, S24_GATE_SILU, TG, TN>(g, st);
+        else launch<T, false, S24_SLICE_GLU, S24_GATE_GELU_ERF, TG, TN>(g, st);
+    } else if (g.epilogue == S24_SLICE_ACT) {
+        if (g.act == S24_ACT_RELU) launch<T, false, S24_SLICE_ACT, S24_ACT_RELU, TM, TN>(g, st);
+        else launch<T, false, S24_SLICE_ACT, S24_ACT_GELU_ERF, TM, TN>(g, st);
+    } else {
+        if (g.act == S24_ACT_RELU) launch<T, false, S24_SLICE_ACT_BWD, S24_ACT_RELU, TM, TN>(g, st);
+        else launch<T, false, S24_SLICE_ACT_BWD, S24_ACT_GELU_ERF, TM, TN>(g, st);
+    }
+    return s24_launch_status();
+}
+
+// Tile of a product, by the cost of one 64 of k with up to one workgroup per compute unit (us, measured over 1-1024 tokens x
+// 768-22016 features, K = 256-11008); beyond that they share its first-level cache, and the fullest compute unit decides.
+struct Plan { int tm, tn; double us; };
+Plan plan(int64_t N, int64_t K, int64_t M)
+{
+    constexpr Plan tiles[4] = {{1, 1, 0.085}, {2, 1, 0.11}, {4, 1, 0.15}, {4, 2, 0.19}};
+    Plan best{0, 0, 0.0};
+    for (const Plan &t : tiles) {
+        if (N <= 16 && t.tn > 1) continue;
+        const int64_t n = ((M + 16 * t.tm - 1) / (16 * t.tm)) * ((N + 16 * t.tn - 1) / (16 * t.tn));
+        const double us = 3.4 + t.us * (double)((n + 255) / 256) * (double)(K / 64);
+        if (best.tm == 0 || us < best.us) best = {t.tm, t.tn, us};
+    }
+    return best;
+}
+
+}  // namespace
+
+// The alternative is the 128 x 128 tile, 0.22 us per 64 of k on top of 5.5 while each compute unit has at most one (with more,
+// its output fills the chip).  Up to 16 tokens it multiplies seven eighths of nothing; there the slices were never slower.
+bool s24_slice_pays(int64_t N, int64_t K, int64_t M)
+{
+    if (N <= 16) return true;
+    if (((M + 127) / 128) * ((N + 127) / 128) > 256) return false;
+    return plan(N, K, M).us < 0.95 * (5.5 + 0.22 * (double)(K / 64));
+}
+
+int s24_slice_nt(const S24SliceNt &g, int dt, hipStream_t st)
+{
+    const Plan p = plan(g.N, g.K, g.M);
+    auto with = [&](auto t) {
+        using T = decltype(t);
+        if (p.tm == 1) return launch_epilogue<T, 1, 1>(g, st);
+        if (p.tm == 2) return launch_epilogue<T, 2, 1>(g, st);
+        if (p.tn == 1) return launch_epilogue<T, 4, 1>(g, st);
+        return launch_epilogue<T, 4, 2>(g, st);
+    };
+    return dt == S24_BF16 ? with(uint16_t{}) : with(s24_half{});
+}

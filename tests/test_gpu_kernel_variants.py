@@ -187,3 +187,43 @@ def test_medium_tile_and_its_epilogues(s24, dtype, pqr):
     s24.spmm_fwd_glu(x, v, m, b, GU, Hg, s24.GATE_SILU)
     s24.glu_fwd(GU, two, s24.GATE_SILU)
     assert torch.equal(GU.view(torch.int16), Z.view(torch.int16)) and torch.equal(Hg.view(torch.int16), two.view(torch.int16))
+
+
+# ------------------------------------------------------------------ sparse products in slices of the contraction
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+# (p, q, r): one chunk (seven idle slices), one feature block; a slice more or less than the others and the load pipeline's
+# remainders (9, 31, 65 and 68 chunks); each of the four tiles, ragged along both axes
+@pytest.mark.parametrize("pqr", [(1, 64, 16), (16, 576, 48), (15, 1984, 4112), (3, 4160, 272), (33, 4352, 2080), (17, 640, 4128),
+                                 (130, 2112, 1040), (257, 512, 1056), (61, 1088, 4112)])
+def test_sliced_products_and_their_epilogues(s24, dtype, pqr):
+    p, q, r = pqr
+    r64 = (r + 63) // 64 * 64
+    W, X = si.random_matrix(80 + q, (r64, q), 0.02, dtype), si.random_matrix(81 + p, (p, q), 1.0, dtype)
+    bias, Zin = si.random_matrix(82, (1, r), 0.5, dtype)[0], si.random_matrix(83, (p, r), 1.0, dtype)
+    cv, cm = (np.ascontiguousarray(a[:r]) for a in oracle.compress(W, oracle.transposable_mask(W))[:2])
+    v, m = oracle.pack(cv, cm)
+    v, m, x, b = dev_bf16(v), dev(m), dev_bf16(X), dev_bf16(bias)
+    ref, tol = oracle.spmm_fwd(X, cv, cm), tol_for(dtype)
+    new = lambda n: torch.full((p, n), 7.0, dtype=torch_dtype(dtype), device="cuda")
+    bits = lambda t: t.view(torch.int16)
+    Y, Yb, Z, H, dZ, two = (new(r) for _ in range(6))
+    s24.spmm_fwd(x, v, m, Y)
+    assert_close(host_f64(Y), ref, tol, f"spmm_fwd {pqr}")
+    Y2 = Y.clone()
+    s24.spmm_bwd_dx(x, v, m, Y2, beta=1.0)
+    assert_close(host_f64(Y2), ref + host_f64(Y), tol, f"accumulate {pqr}")
+    s24.spmm_fwd_bias(x, v, m, b, Yb)
+    assert_close(host_f64(Yb), ref + host_f64(b), tol, f"bias {pqr}")
+    for act in (s24.ACT_RELU, s24.ACT_GELU_ERF):   # the fused epilogues give the bits of the separate calls
+        s24.spmm_fwd_act(x, v, m, b, Z, H, act)
+        s24.act_fwd(Yb, two, act)
+        assert torch.equal(bits(Z), bits(Yb)) and torch.equal(bits(H), bits(two))
+        s24.spmm_bwd_dx_act(x, v, m, dev_bf16(Zin), dZ, act)
+        s24.act_bwd(Y, dev_bf16(Zin), two, act)
+        assert torch.equal(bits(dZ), bits(two))
+    if r % 32 == 0:
+        GU, Hg, two = new(r), new(r // 2), new(r // 2)
+        for gate in (s24.GATE_SILU, s24.GATE_GELU_ERF):
+            s24.spmm_fwd_glu(x, v, m, b, GU, Hg, gate)
+            s24.glu_fwd(Yb, two, gate)
+            assert torch.equal(bits(GU), bits(Yb)) and torch.equal(bits(Hg), bits(two))
