@@ -234,29 +234,31 @@ template <typename T, int TM, int TN> int launch_epilogue(const S24SliceNt &g, h
 
 // Tile of a product, by the cost of one 64 of k with up to one workgroup per compute unit (us, measured over 1-1024 tokens x
 // 768-22016 features, K = 256-11008); beyond that they share its first-level cache, and the fullest compute unit decides.
-struct Plan { int tm, tn; double us; };
+struct Plan { int tm, tn; double us; int64_t rounds; };
 Plan plan(int64_t N, int64_t K, int64_t M)
 {
-    constexpr Plan tiles[4] = {{1, 1, 0.085}, {2, 1, 0.11}, {4, 1, 0.15}, {4, 2, 0.19}};
-    Plan best{0, 0, 0.0};
+    constexpr Plan tiles[4] = {{1, 1, 0.085, 0}, {2, 1, 0.11, 0}, {4, 1, 0.15, 0}, {4, 2, 0.19, 0}};
+    Plan best{0, 0, 0.0, 0};
     for (const Plan &t : tiles) {
         if (N <= 16 && t.tn > 1) continue;
-        const int64_t n = ((M + 16 * t.tm - 1) / (16 * t.tm)) * ((N + 16 * t.tn - 1) / (16 * t.tn));
-        const double us = 3.4 + t.us * (double)((n + 255) / 256) * (double)(K / 64);
-        if (best.tm == 0 || us < best.us) best = {t.tm, t.tn, us};
+        const int64_t n = ((M + 16 * t.tm - 1) / (16 * t.tm)) * ((N + 16 * t.tn - 1) / (16 * t.tn)), rounds = (n + 255) / 256;
+        const double us = 3.4 + t.us * (double)rounds * (double)(K / 64);
+        if (best.tm == 0 || us < best.us) best = {t.tm, t.tn, us, rounds};
     }
     return best;
 }
 
 }  // namespace
 
-// The alternative is the 128 x 128 tile, 0.22 us per 64 of k on top of 5.5 while each compute unit has at most one (with more,
+// The alternative is the 128 x 128 tile, 0.22 us per 64 of k on top of 6.2 while each compute unit has at most one (with more,
 // its output fills the chip).  Up to 16 tokens it multiplies seven eighths of nothing; there the slices were never slower.
+// More than two rounds of sliced tiles cost more than the model says (4096 tokens x 1024, K = 256: 13.7 against 10.6 us).
 bool s24_slice_pays(int64_t N, int64_t K, int64_t M)
 {
     if (N <= 16) return true;
     if (((M + 127) / 128) * ((N + 127) / 128) > 256) return false;
-    return plan(N, K, M).us < 0.95 * (5.5 + 0.22 * (double)(K / 64));
+    const Plan p = plan(N, K, M);
+    return p.rounds <= 2 && p.us < 0.95 * (6.2 + 0.22 * (double)(K / 64));
 }
 
 int s24_slice_nt(const S24SliceNt &g, int dt, hipStream_t st)
