@@ -227,3 +227,11 @@ def test_sliced_products_and_their_epilogues(s24, dtype, pqr):
             s24.spmm_fwd_glu(x, v, m, b, GU, Hg, gate)
             s24.glu_fwd(Yb, two, gate)
             assert torch.equal(bits(GU), bits(Yb)) and torch.equal(bits(Hg), bits(two))
+
+
+def test_calls_go_to_the_current_stream(s24):
+    from paper_2404_01847_amd import binding
+    side = torch.cuda.Stream()
+    assert binding._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert binding._stream() == side.cuda_stream != torch.cuda.default_stream().cuda_stream
