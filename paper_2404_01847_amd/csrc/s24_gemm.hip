@@ -871,14 +871,15 @@ __global__ __launch_bounds__(THREADS) void dense_nt_big_kernel(const uint16_t *_
 // rather than issued in one burst.
 namespace dmatn {
 constexpr int THREADS = 256;
-// WT = 32 x 32 accumulator blocks per wave and axis: 4 -> 256 x 256 workgroup tiles; 2 -> 128 x 128 tiles for
-// outputs with too few large tiles to fill the chip.  BT = tokens per ring stage: 32 for the large tile (128 KB
+// WTM x WTN = 32 x 32 accumulator blocks per wave: 4 x 4 -> 256 x 256 workgroup tiles; 4 x 2 and 2 x 2 -> 256 x 128 and
+// 128 x 128 tiles for outputs with too few large tiles to fill the chip.  BT = tokens per ring stage: 32 for the large tile (128 KB
 // of LDS); for the small tile 32 (64 KB, two workgroups per CU) when there are more tiles than CUs, else 64 (a
 // small tile has a quarter of the matrix work per token, so the barrier is paid half as often).
-template <int WT, int BT_> struct Cfg {
-    static constexpr int BM = 64 * WT, BN = 64 * WT, BT = BT_;
-    static constexpr int ROWB = BM * 2, OPERAND = BT * ROWB, STAGE = 2 * OPERAND, CPR = ROWB / 16;
-    static constexpr int NIO = OPERAND / 1024 / 4, NI = 2 * NIO;   // copies per wave, chunk and operand / in total
+template <int WTM_, int WTN_, int BT_> struct Cfg {
+    static constexpr int WTM = WTM_, WTN = WTN_, BM = 64 * WTM, BN = 64 * WTN, BT = BT_;
+    static constexpr int ROWA = BM * 2, ROWX = BN * 2;                              // bytes of a token's row in the dY / X tile
+    static constexpr int OPERAND = BT * ROWA, STAGE = OPERAND + BT * ROWX;
+    static constexpr int NIA = BT * ROWA / 4096, NIX = BT * ROWX / 4096, NI = NIA + NIX;   // copies per wave and chunk
 };
 using big::glb_ptr;
 using big::lds_ptr;
@@ -924,12 +925,11 @@ struct DwBatch {
     int first_slot[kMaxBatch + 1];
 };
 
-template <typename ET, int WT, int BT_, bool ACCUM, bool DECAY>
+template <typename ET, typename C, bool ACCUM, bool DECAY>
 __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch batch, unsigned long long *probe)
 {
-    using C = Cfg<WT, BT_>;
-    constexpr int BM = C::BM, BN = C::BN, BT = C::BT, ROWB = C::ROWB, OPERAND = C::OPERAND, STAGE = C::STAGE, CPR = C::CPR;
-    constexpr int NIO = C::NIO, NI = C::NI;
+    constexpr int WTM = C::WTM, WTN = C::WTN, BM = C::BM, BN = C::BN, BT = C::BT, ROWA = C::ROWA, ROWX = C::ROWX;
+    constexpr int OPERAND = C::OPERAND, STAGE = C::STAGE, NIA = C::NIA, NIX = C::NIX, NI = C::NI;
     constexpr int KS = BT / 16, CPS = NI / KS;   // 16-token steps per chunk, copies issued per step
     static_assert(KS % 2 == 0 && CPS * KS == NI, "steps alternate between two fragment sets");
     const big::ClockStamp t_start = big::clock_now();
@@ -962,22 +962,28 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     const int nk = (T + BT - 1) / BT;
 
     // Copies: instruction g of an operand fills the 16-byte slots 64g .. 64g+63 of its stage region, slot ->
-    // (row = slot / CPR, chunk = slot % CPR); the source chunk is chunk ^ (4 * (row & 3)).  Columns past the
+    // (row = slot / slots per row, chunk = the rest); the source chunk is chunk ^ (4 * (row & 3)).  Columns past the
     // matrix edge are clamped to its last 16-byte chunk.  A lane's byte offsets from the first token row of a
     // chunk are fixed for the whole kernel; only the (wave-uniform) row base moves, so a copy costs no vector
     // arithmetic.  A chunk always starts at a row that leaves BT rows below it: the last chunk of a token count
     // that is not a multiple of BT starts at T - BT and overlaps its predecessor (clear_tail drops the overlap);
     // with fewer than BT tokens in all there is one chunk, rows past T - 1 re-read row T - 1.
-    uint32_t voffA[NIO], voffB[NIO];
+    uint32_t voffA[NIA], voffB[NIX];
     const int lastA = (min(M - m0, BM) >> 3) - 1, lastB = (min(N - n0, BN) >> 3) - 1;
 #pragma unroll
-    for (int j = 0; j < NIO; ++j) {
-        const int slot = (wave * NIO + j) * 64 + lane, row = min(slot / CPR, T - 1), c = (slot % CPR) ^ (((slot / CPR) & 3) << 2);
+    for (int j = 0; j < NIA; ++j) {
+        constexpr int CPR = ROWA / 16;
+        const int slot = (wave * NIA + j) * 64 + lane, row = min(slot / CPR, T - 1), c = (slot % CPR) ^ (((slot / CPR) & 3) << 2);
         voffA[j] = (uint32_t)(row * ldy + m0 + 8 * min(c, lastA)) * 2u;
+    }
+#pragma unroll
+    for (int j = 0; j < NIX; ++j) {
+        constexpr int CPR = ROWX / 16;
+        const int slot = (wave * NIX + j) * 64 + lane, row = min(slot / CPR, T - 1), c = (slot % CPR) ^ (((slot / CPR) & 3) << 2);
         voffB[j] = (uint32_t)(row * ldx + n0 + 8 * min(c, lastB)) * 2u;
     }
     auto first_row = [&](int kc) { return max(min(kc * BT, T - BT), 0); };
-    // Copies first .. first+count-1 of a chunk's list (the dY tile's NIO, then the X tile's NIO).
+    // Copies first .. first+count-1 of a chunk's list (the dY tile's NIA, then the X tile's NIX).
     // The copies are buffer loads into LDS: a descriptor (scalar registers) whose base is the chunk's first token
     // row, and the lane's fixed 32-bit offset; nothing of a copy's address is computed on the vector unit.
     auto issue = [&](unsigned char *st, int kc, int first, int count) {
@@ -985,52 +991,50 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
         const big::rsrc_t ya = big::buffer_of(dY + (int64_t)row0 * ldy), xb = big::buffer_of(X + (int64_t)row0 * ldx);
 #pragma unroll
         for (int c = first; c < first + count; ++c) {
-            const int j = c < NIO ? c : c - NIO;
-            if (c < NIO)
-                big::buffer_to_lds<16>(ya, (lds_ptr)(st + (wave * NIO + j) * 1024), voffA[j]);
+            if (c < NIA)
+                big::buffer_to_lds<16>(ya, (lds_ptr)(st + (wave * NIA + c) * 1024), voffA[c]);
             else
-                big::buffer_to_lds<16>(xb, (lds_ptr)(st + OPERAND + (wave * NIO + j) * 1024), voffB[j]);
+                big::buffer_to_lds<16>(xb, (lds_ptr)(st + OPERAND + (wave * NIX + c - NIA) * 1024), voffB[c - NIA]);
         }
     };
-    f32x16 acc[WT][WT];
+    f32x16 acc[WTM][WTN];
 #pragma unroll
-    for (int mi = 0; mi < WT; ++mi)
+    for (int mi = 0; mi < WTM; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < WT; ++ni) acc[mi][ni] = f32x16{};
+        for (int ni = 0; ni < WTN; ++ni) acc[mi][ni] = f32x16{};
 
     // fragment addressing of this lane: group G = lane/16 -> k half G/2, column half G%2
     const int gi = lane & 15, G = lane >> 4;
     const int frow = 8 * (G >> 1) + (gi >> 2), fcol = 16 * (G & 1) + 4 * (gi & 3);
-    int offA[WT], offB[WT];
+    int offA[WTM], offB[WTN];
 #pragma unroll
-    for (int i = 0; i < WT; ++i) {
-        offA[i] = tr_off<ROWB>(frow, 32 * WT * wm + 32 * i + fcol);
-        offB[i] = OPERAND + tr_off<ROWB>(frow, 32 * WT * wn + 32 * i + fcol);
-    }
-    auto load_frags = [&](const unsigned char *st, int ks, bf16x8 (&a)[WT], bf16x8 (&b)[WT]) {
+    for (int i = 0; i < WTM; ++i) offA[i] = tr_off<ROWA>(frow, 32 * WTM * wm + 32 * i + fcol);
 #pragma unroll
-        for (int ni = 0; ni < WT; ++ni) b[ni] = tr_frag<ROWB>(st + offB[ni] + 16 * ks * ROWB);
+    for (int i = 0; i < WTN; ++i) offB[i] = OPERAND + tr_off<ROWX>(frow, 32 * WTN * wn + 32 * i + fcol);
+    auto load_frags = [&](const unsigned char *st, int ks, bf16x8 (&a)[WTM], bf16x8 (&b)[WTN]) {
 #pragma unroll
-        for (int mi = 0; mi < WT; ++mi) a[mi] = tr_frag<ROWB>(st + offA[mi] + 16 * ks * ROWB);
+        for (int ni = 0; ni < WTN; ++ni) b[ni] = tr_frag<ROWX>(st + offB[ni] + 16 * ks * ROWX);
+#pragma unroll
+        for (int mi = 0; mi < WTM; ++mi) a[mi] = tr_frag<ROWA>(st + offA[mi] + 16 * ks * ROWA);
     };
-    auto mma = [&](const bf16x8 (&a)[WT], const bf16x8 (&b)[WT]) {
+    auto mma = [&](const bf16x8 (&a)[WTM], const bf16x8 (&b)[WTN]) {
 #pragma unroll
-        for (int mi = 0; mi < WT; ++mi)
+        for (int mi = 0; mi < WTM; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < WT; ++ni)
+            for (int ni = 0; ni < WTN; ++ni)
                 acc[mi][ni] = Mma<ET>::dense(a[mi], b[ni], acc[mi][ni]);
     };
-    // Issue order of one 16-token step: a matrix instruction, then 4/WT LDS reads of the next step's fragments
-    // (4*WT reads against WT*WT matrix instructions), and after every other matrix instruction one copy.
-    // The reads go out in the first half of the step (two per matrix instruction for the large tile), so that the
-    // last fragment has arrived well before the step ends: with one wave per SIMD nobody else covers a wait.
+    // Issue order of one 16-token step: a matrix instruction, then two LDS reads of the next step's fragments
+    // (2 * (WTM + WTN) reads against WTM * WTN matrix instructions), and after every other matrix instruction one copy.
+    // The reads go out as early in the step as two per matrix instruction allow, so that the last fragment has arrived
+    // well before the step ends: with one wave per SIMD nobody else covers a wait.
     auto interleave = [&]() {
-        constexpr int RPM = 4 / WT, EARLY = WT == 4 ? 2 : 1;
-        static_assert(RPM * WT * WT == 4 * WT && 2 * CPS <= WT * WT, "reads and copies fit between the matrix instructions");
+        constexpr int READS = 2 * (WTM + WTN), MFMAS = WTM * WTN;
+        static_assert(READS <= 2 * MFMAS && 2 * CPS <= MFMAS, "reads and copies fit between the matrix instructions");
 #pragma unroll
-        for (int i = 0; i < WT * WT; ++i) {
+        for (int i = 0; i < MFMAS; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (i < WT * WT / EARLY) __builtin_amdgcn_sched_group_barrier(0x100, RPM * EARLY, 0);
+            if (2 * i < READS) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
             if ((i & 1) && (i >> 1) < CPS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -1040,8 +1044,9 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     // fewer than BT tokens in all, the trailing rows past T.  They are cleared in the dY tile.
     auto clear_tail = [&](unsigned char *st, int kc) {
         const int rem = T - kc * BT, skip = T >= BT ? 0 : rem;
+        constexpr int CPR = ROWA / 16;
         for (int idx = tid; idx < (BT - rem) * CPR; idx += THREADS)
-            *reinterpret_cast<uint4 *>(st + (skip + idx / CPR) * ROWB + ((idx % CPR) << 4)) = make_uint4(0, 0, 0, 0);
+            *reinterpret_cast<uint4 *>(st + (skip + idx / CPR) * ROWA + ((idx % CPR) << 4)) = make_uint4(0, 0, 0, 0);
         __syncthreads();
     };
     const bool partial = (T % BT) != 0;
@@ -1055,7 +1060,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     __builtin_amdgcn_sched_barrier(0);
     big::wait_and_barrier<2 * NI>();
     if (partial && nk == 1) clear_tail(s0, 0);
-    bf16x8 fa[2][WT], fb[2][WT];   // fragments of the current and of the next 16-token step
+    bf16x8 fa[2][WTM], fb[2][WTN];   // fragments of the current and of the next 16-token step
     load_frags(s0, 0, fa[0], fb[0]);
 
     // Iteration kc: all but the NI most recent copies (chunk kc+2) are complete, so chunk kc+1 is in LDS for
@@ -1083,11 +1088,11 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     if (kc < nk) chunk(s0, s1, s3, kc);
     if (kc + 1 < nk) chunk(s1, s2, s0, kc + 1);
     if (kc + 2 < nk) chunk(s2, s3, s1, kc + 2);
-    // Epilogue through LDS, so that global memory sees 16-byte accesses along rows: each wave parks 64 columns
-    // of its tile at a time (32*WT rows of fp32, 256-byte rows) in its own ring stage, then lane l of pass j
+    // Epilogue through LDS, so that global memory sees 16-byte accesses along rows: each wave parks a slice of its tile
+    // at a time (32*RB rows x 64 columns of fp32, 256-byte rows) in its own ring stage, then lane l of pass j
     // owns row (64j + l) / 16, columns 4 * (l % 16) .. +3: one LDS read, one 16-byte store, and for the
     // optional terms one 16-byte load of the old gradient, one 8-byte load of W and one mask word.
-    // The W and mask loads of a whole 64-column slice are issued in one go, well before they are needed: those of
+    // The W and mask loads of a whole slice are issued in one go, well before they are needed: those of
     // the first slice ahead of the wait that drains the ring, those of the second before it is parked in LDS.
     // Loaded pass by pass where they are used, their latency was exposed eight times per tile with only four
     // waves on the compute unit to hide it (c5: 0.45 ms per step).
@@ -1095,46 +1100,49 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     // scalar register), so the 64 loads of a slice share two address registers.  M is a multiple of 16 and a wave's
     // rows start at a multiple of 64: the four rows of a pass are all inside the matrix or all outside, and passes
     // past the edge re-read the last pass inside (a wave with no row inside re-reads the tile's first rows).
-    constexpr int NP = 8 * WT;   // passes per slice
+    constexpr int RB = WTM * 8192 <= STAGE ? WTM : WTM / 2, NR = WTM / RB;   // row blocks per slice, slices down a wave's tile
+    static_assert(RB * 8192 <= STAGE && RB * NR == WTM, "a wave's slice fits one stage");
+    constexpr int NP = 8 * RB;   // passes per slice
     uint2 wv[DECAY ? NP : 1];
     uint32_t keep[DECAY ? NP : 1];
-    const int wave_rows = min(M - m0 - 32 * WT * wm, 32 * WT);   // rows of this wave's sub-tile inside the matrix
-    const int wave_row0 = wave_rows > 0 ? 32 * WT * wm : 0, last_pass = wave_rows > 0 ? (wave_rows >> 2) - 1 : 0;
-    auto decay_loads = [&](int h2) {
+    const int wave_rows = min(M - m0 - 32 * WTM * wm, 32 * WTM);   // rows of this wave's sub-tile inside the matrix
+    const int wave_row0 = wave_rows > 0 ? 32 * WTM * wm : 0, last_pass = wave_rows > 0 ? (wave_rows >> 2) - 1 : 0;
+    auto decay_loads = [&](int h2, int r2) {
         if constexpr (DECAY) {
-            const int nc = min(n0 + 32 * WT * wn + 64 * h2 + 4 * (lane & 15), N - 4);
+            const int nc = min(n0 + 32 * WTN * wn + 64 * h2 + 4 * (lane & 15), N - 4);
             const big::rsrc_t wbuf = big::buffer_of(Wt + (int64_t)(m0 + wave_row0) * ldw);
             const big::rsrc_t mbuf = big::buffer_of(mask + (int64_t)((m0 + wave_row0) >> 2) * (ldw >> 2));
             const uint32_t voff_w = ((uint32_t)(lane >> 4) * (uint32_t)ldw + (uint32_t)nc) * 2u, voff_m = (uint32_t)(nc >> 2) * 2u;
             const uint32_t shift = 4 * (lane >> 4);   // row of the 4 x 4 block: the tile starts at a multiple of four
 #pragma unroll
             for (int j = 0; j < NP; ++j) {
-                const uint32_t jc = (uint32_t)min(j, last_pass);
+                const uint32_t jc = (uint32_t)min(NP * r2 + j, last_pass);
                 wv[j] = big::buffer_load_8(wbuf, voff_w, jc * 8u * (uint32_t)ldw);
                 keep[j] = big::buffer_load_2(mbuf, voff_m, jc * 2u * (uint32_t)(ldw >> 2)) >> shift;
             }
         }
     };
-    decay_loads(0);
+    decay_loads(0, 0);
     big::wait_and_barrier<0>();   // last (redundant) copies drained, nobody reads the ring any more: reuse it
     big::clock_report(probe, t_start);
-    static_assert(32 * WT * 256 <= STAGE, "a wave's 64-column slice fits one stage");
     unsigned char *est = wave == 0 ? s0 : (wave == 1 ? s1 : (wave == 2 ? s2 : s3));
 #pragma unroll
-    for (int h2 = 0; h2 < WT / 2; ++h2) {
-        if (h2 > 0) decay_loads(h2);
+    for (int slice = 0; slice < NR * (WTN / 2); ++slice) {
+        const int h2 = slice / NR, r2 = slice % NR;
+        if (slice > 0) decay_loads(h2, r2);
 #pragma unroll
         for (int nj = 0; nj < 2; ++nj)
 #pragma unroll
-            for (int mi = 0; mi < WT; ++mi)
+            for (int mi = 0; mi < RB; ++mi)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int row = 32 * mi + 8 * (e / 4) + 4 * (lane >> 5) + (e & 3), col = 32 * nj + (lane & 31);
-                    *reinterpret_cast<float *>(est + row * 256 + col * 4) = acc[mi][2 * h2 + nj][e];
+                    *reinterpret_cast<float *>(est + row * 256 + col * 4) = acc[RB * r2 + mi][2 * h2 + nj][e];
                 }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(big::wait_vm_lgkm0(63));   // LDS only: the wave reads back only what it wrote itself
         asm volatile("" ::: "memory");
+        const int ms = m0 + 32 * WTM * wm + 32 * RB * r2, ns = n0 + 32 * WTN * wn + 64 * h2;   // the slice's first row and column
         constexpr int BATCH = 8;
 #pragma unroll
         for (int j0 = 0; j0 < NP; j0 += BATCH) {
@@ -1143,7 +1151,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
 #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
                 const int idx = (j0 + b) * 64 + lane, row = idx >> 4, c4 = idx & 15;
-                const int m = m0 + 32 * WT * wm + row, n = n0 + 32 * WT * wn + 64 * h2 + 4 * c4;
+                const int m = ms + row, n = ns + 4 * c4;
                 live[b] = m < M && n < N;   // N is a multiple of 16: the four columns are all in or all out
                 const int mc = min(m, M - 1), nc = min(n, N - 4);
                 v[b] = *reinterpret_cast<const float4 *>(est + row * 256 + c4 * 16);
@@ -1152,7 +1160,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
 #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
                 const int idx = (j0 + b) * 64 + lane, row = idx >> 4, c4 = idx & 15;
-                const int m = m0 + 32 * WT * wm + row, n = n0 + 32 * WT * wn + 64 * h2 + 4 * c4;
+                const int m = ms + row, n = ns + 4 * c4;
                 float4 o = v[b];
                 if (ACCUM) { o.x = old[b].x + o.x; o.y = old[b].y + o.y; o.z = old[b].z + o.z; o.w = old[b].w + o.w; }
                 if constexpr (DECAY) {
@@ -1763,8 +1771,11 @@ struct DwProblem {
     int64_t p, q, r;
     float lambda;
 };
+enum class DwTile { Large, Medium, Small };   // 256 x 256, 256 x 128, 128 x 128
+int64_t dw_tiles_m(DwTile t, int64_t r) { return ceil_div(r, t == DwTile::Small ? 128 : 256); }
+int64_t dw_tiles_n(DwTile t, int64_t q) { return ceil_div(q, t == DwTile::Large ? 256 : 128); }
 // The window [m_off, m_off + mm) x [n_off, n_off + nn) of a problem's output, in tiles of `tile`
-dmatn::DwWindow dw_window(const DwProblem &pr, int tile, int64_t m_off, int64_t mm, int64_t n_off, int64_t nn)
+dmatn::DwWindow dw_window(const DwProblem &pr, DwTile tile, int64_t m_off, int64_t mm, int64_t n_off, int64_t nn)
 {
     dmatn::DwWindow w{};
     w.dY = pr.dY + m_off;
@@ -1778,29 +1789,52 @@ dmatn::DwWindow dw_window(const DwProblem &pr, int tile, int64_t m_off, int64_t 
     w.ldy = (int)pr.r;
     w.ldx = (int)pr.q;
     w.ldw = (int)pr.q;
-    w.tiles_m = (int)ceil_div(mm, tile);
-    w.tiles_n = (int)ceil_div(nn, tile);
+    w.tiles_m = (int)dw_tiles_m(tile, mm);
+    w.tiles_n = (int)dw_tiles_n(tile, nn);
     w.lambda = pr.lambda;
     return w;
 }
-// tile: 256 (large), or 128 (small; 32 tokens per stage when there are more tiles than compute units, else 64)
-void launch_dw_batch(const dmatn::DwBatch &batch, int tile, bool accum, bool decay, int dt, hipStream_t st)
+// Tile of a grid that the large tile does not fill, by cost in us (measured over 128-16384 tokens and layers of 256 x 1024 to
+// 1280 x 5120; the bits are the same).  Per 32 tokens: small tiles 0.48 with two workgroups per compute unit and 0.22 with
+// one, medium ones 0.42 and 0.32 with few, large ones 0.85 and 0.52; on top of that the filling and draining of a tile.  The
+// small tile reads 32 KB of LDS per 16 KB copied, the medium one 48 per 24 for twice the work: where the small tile needs two
+// workgroups per compute unit and the medium one does not, that is 8192 tokens x 768 x 3072 (both gradients) 106 -> 90 us,
+// 8192 x 1024 x 4096 124 -> 113.
+DwTile dw_few_tile(const DwProblem *pr, int count)
+{
+    const int64_t cus = s24_cu_count();
+    int64_t tiles[3] = {0, 0, 0}, chunks = 0;
+    for (int i = 0; i < count; ++i) {
+        for (int t = 0; t < 3; ++t) tiles[t] += dw_tiles_m((DwTile)t, pr[i].r) * dw_tiles_n((DwTile)t, pr[i].q);
+        chunks = std::max(chunks, (pr[i].p + 31) / 32);
+    }
+    auto rest = [&](DwTile t, int64_t per) { return (double)(tiles[(int)t] % per) / per; };
+    auto full = [&](DwTile t, int64_t per) { return (double)(tiles[(int)t] / per); };
+    const double rl = rest(DwTile::Large, cus), rm = rest(DwTile::Medium, cus), rs = rest(DwTile::Small, 2 * cus);
+    const double l = 15.3 + chunks * (0.85 * full(DwTile::Large, cus) + (rl > 0 ? 0.52 + 0.3 * rl : 0));
+    const double m = 10.8 + chunks * (0.42 * full(DwTile::Medium, cus) + (rm > 0 ? 0.32 + 0.1 * rm : 0));
+    const double s = 9.8 + chunks * (0.48 * full(DwTile::Small, 2 * cus) + (rs > 0.5 ? 0.45 : rs > 0 ? 0.22 : 0));
+    return s <= m && s <= l ? DwTile::Small : m <= l ? DwTile::Medium : DwTile::Large;
+}
+// small tile: 32 tokens per stage when there are more tiles than compute units, else 64
+void launch_dw_batch(const dmatn::DwBatch &batch, DwTile tile, bool accum, bool decay, int dt, hipStream_t st)
 {
     const int slots = batch.first_slot[dmatn::kMaxBatch];   // per XCD
     const dim3 grid(slots * 8), block(dmatn::THREADS);
-#define S24_LAUNCH_DW(WT, BT, ACC, DEC) \
-    hipLaunchKernelGGL((dmatn::dense_tn_dma_kernel<T, WT, BT, ACC, DEC>), grid, block, 0, st, batch, g_clock_probe)
-#define S24_LAUNCH_DW_TILE(WT, BT)                               \
-    do {                                                         \
-        if (accum && decay) S24_LAUNCH_DW(WT, BT, true, true);   \
-        else if (accum) S24_LAUNCH_DW(WT, BT, true, false);      \
-        else if (decay) S24_LAUNCH_DW(WT, BT, false, true);      \
-        else S24_LAUNCH_DW(WT, BT, false, false);                \
+#define S24_LAUNCH_DW(WTM, WTN, BT, ACC, DEC) \
+    hipLaunchKernelGGL((dmatn::dense_tn_dma_kernel<T, dmatn::Cfg<WTM, WTN, BT>, ACC, DEC>), grid, block, 0, st, batch, g_clock_probe)
+#define S24_LAUNCH_DW_TILE(WTM, WTN, BT)                               \
+    do {                                                               \
+        if (accum && decay) S24_LAUNCH_DW(WTM, WTN, BT, true, true);   \
+        else if (accum) S24_LAUNCH_DW(WTM, WTN, BT, true, false);      \
+        else if (decay) S24_LAUNCH_DW(WTM, WTN, BT, false, true);      \
+        else S24_LAUNCH_DW(WTM, WTN, BT, false, false);                \
     } while (0)
     S24_WITH_16BIT_TYPE(dt, {
-        if (tile == 256) S24_LAUNCH_DW_TILE(4, 32);
-        else if (slots * 8 > s24_cu_count()) S24_LAUNCH_DW_TILE(2, 32);
-        else S24_LAUNCH_DW_TILE(2, 64);
+        if (tile == DwTile::Large) S24_LAUNCH_DW_TILE(4, 4, 32);
+        else if (tile == DwTile::Medium) S24_LAUNCH_DW_TILE(4, 2, 32);
+        else if (slots * 8 > s24_cu_count()) S24_LAUNCH_DW_TILE(2, 2, 32);
+        else S24_LAUNCH_DW_TILE(2, 2, 64);
     });
 #undef S24_LAUNCH_DW_TILE
 #undef S24_LAUNCH_DW
@@ -1818,11 +1852,11 @@ int run_dense_dw(const void *dY, const void *X, float *dW, int64_t p, int64_t q,
         auto *a = static_cast<const uint16_t *>(dY), *b = static_cast<const uint16_t *>(X);
         const bool fuse = decay_pending && wdt == dt;   // the epilogue reads W in the operands' own 16-bit type
         auto *w = static_cast<const uint16_t *>(fuse ? W : nullptr);
+        const DwProblem pr0{a, b, dW, w, fuse ? mask : nullptr, p, q, r, lambda};
         // One launch over the window [m_off, m_off + mm) x [n_off, n_off + nn) of the output, in tiles of `tile`
-        auto launch = [&](int tile, int64_t m_off, int64_t mm, int64_t n_off, int64_t nn) {
-            const DwProblem pr{a, b, dW, w, fuse ? mask : nullptr, p, q, r, lambda};
+        auto launch = [&](DwTile tile, int64_t m_off, int64_t mm, int64_t n_off, int64_t nn) {
             dmatn::DwBatch batch{};
-            batch.w[0] = dw_window(pr, tile, m_off, mm, n_off, nn);
+            batch.w[0] = dw_window(pr0, tile, m_off, mm, n_off, nn);
             const int slots = (batch.w[0].tiles_m * batch.w[0].tiles_n + 7) / 8;
             for (int i = 1; i <= dmatn::kMaxBatch; ++i) batch.first_slot[i] = slots;
             launch_dw_batch(batch, tile, accum, fuse, dt, st);
@@ -1837,8 +1871,9 @@ int run_dense_dw(const void *dY, const void *X, float *dW, int64_t p, int64_t q,
         // element belongs to exactly one launch either way, so nothing about the result changes.
         const int tm256 = (int)ceil_div(r, 256), tn256 = (int)ceil_div(q, 256), total = tm256 * tn256;
         const int cus = s24_cu_count();
+        const DwTile few = dw_few_tile(&pr0, 1);
         if (total < 3 * cus / 4) {
-            launch(128, 0, r, 0, q);
+            launch(few, 0, r, 0, q);
         } else {
             int cut_m = 0, cut_n = 0;   // tile rows / columns kept in the large-tile slab (0: no such cut)
             if (total % cus != 0) {
@@ -1848,13 +1883,13 @@ int run_dense_dw(const void *dY, const void *X, float *dW, int64_t p, int64_t q,
                     if ((k * tm256) % cus == 0 && (tn256 - k) * tm256 <= cus / 2) cut_n = k;
             }
             if (cut_m && (!cut_n || cut_m * tn256 >= cut_n * tm256)) {
-                launch(256, 0, 256ll * cut_m, 0, q);
-                launch(128, 256ll * cut_m, r - 256ll * cut_m, 0, q);
+                launch(DwTile::Large, 0, 256ll * cut_m, 0, q);
+                launch(DwTile::Small, 256ll * cut_m, r - 256ll * cut_m, 0, q);
             } else if (cut_n) {
-                launch(256, 0, r, 0, 256ll * cut_n);
-                launch(128, 0, r, 256ll * cut_n, q - 256ll * cut_n);
+                launch(DwTile::Large, 0, r, 0, 256ll * cut_n);
+                launch(DwTile::Small, 0, r, 256ll * cut_n, q - 256ll * cut_n);
             } else {
-                launch(256, 0, r, 0, q);
+                launch(DwTile::Large, 0, r, 0, q);
             }
         }
         if (fuse) decay_pending = false;
@@ -1941,15 +1976,16 @@ extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, flo
                          (int64_t)ceil_div(pr.r, 256) * ceil_div(pr.q, 256) < 3 * cus / 4;
         }
         if (small_grid) {
+            const DwTile few = dw_few_tile(prs, count);
             dmatn::DwBatch batch{};
             int first = 0;
             for (int i = 0; i < count; ++i) {
-                batch.w[i] = dw_window(prs[i], 128, 0, prs[i].r, 0, prs[i].q);
+                batch.w[i] = dw_window(prs[i], few, 0, prs[i].r, 0, prs[i].q);
                 batch.first_slot[i] = first;
                 first += (batch.w[i].tiles_m * batch.w[i].tiles_n + 7) / 8;
             }
             for (int i = count; i <= dmatn::kMaxBatch; ++i) batch.first_slot[i] = first;
-            launch_dw_batch(batch, 128, accum, decay, dt, st);
+            launch_dw_batch(batch, few, accum, decay, dt, st);
             return s24_launch_status();
         }
         if (dt == S24_F32) {   // one grid for every problem with tokens to contract
@@ -1992,19 +2028,19 @@ extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, flo
         // the cut removes the LAST tile rows / columns, the ragged edge included: what stays is a multiple of 256
         const int64_t keep_m = i == cut && cut_rows ? 256ll * ((int64_t)ceil_div(prs[i].r, 256) - cut_rows) : prs[i].r;
         const int64_t keep_n = i == cut && cut_cols ? 256ll * ((int64_t)ceil_div(prs[i].q, 256) - cut_cols) : prs[i].q;
-        batch.w[i] = dw_window(prs[i], 256, 0, keep_m, 0, keep_n);
+        batch.w[i] = dw_window(prs[i], DwTile::Large, 0, keep_m, 0, keep_n);
         batch.first_slot[i] = first;
         first += (batch.w[i].tiles_m * batch.w[i].tiles_n + 7) / 8;
     }
     for (int i = count; i <= dmatn::kMaxBatch; ++i) batch.first_slot[i] = first;
-    launch_dw_batch(batch, 256, accum, decay, dt, st);
+    launch_dw_batch(batch, DwTile::Large, accum, decay, dt, st);
     if (cut >= 0) {
         dmatn::DwBatch strip{};
         const int64_t m_off = cut_rows ? batch.w[cut].M : 0, n_off = cut_cols ? batch.w[cut].N : 0;
-        strip.w[0] = dw_window(prs[cut], 128, m_off, prs[cut].r - m_off, n_off, prs[cut].q - n_off);
+        strip.w[0] = dw_window(prs[cut], DwTile::Small, m_off, prs[cut].r - m_off, n_off, prs[cut].q - n_off);
         const int slots = (strip.w[0].tiles_m * strip.w[0].tiles_n + 7) / 8;
         for (int i = 1; i <= dmatn::kMaxBatch; ++i) strip.first_slot[i] = slots;
-        launch_dw_batch(strip, 128, accum, decay, dt, st);
+        launch_dw_batch(strip, DwTile::Small, accum, decay, dt, st);
     }
     return s24_launch_status();
 }

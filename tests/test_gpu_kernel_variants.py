@@ -235,3 +235,30 @@ def test_calls_go_to_the_current_stream(s24):
     assert binding._stream() == torch.cuda.current_stream().cuda_stream
     with torch.cuda.stream(side):
         assert binding._stream() == side.cuda_stream != torch.cuda.default_stream().cuda_stream
+
+
+# ------------------------------------------------------------------ weight gradients on the 256 x 128 tile
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+# 144 such tiles in all, 288 small ones; whole chunks and a remainder;
+# edges ragged along both axes
+@pytest.mark.parametrize("case", [(2048, 0.0), (2003, 1.0), (1100, 0.0)])
+def test_medium_tile_weight_gradients(s24, dtype, case):
+    p, beta = case
+    lam, d, f = 2e-4, 752, 3056
+    shapes = [(d, f), (f, d)]
+    dY = [si.random_matrix(90 + i, (p, r), 1e-2, dtype) for i, (r, q) in enumerate(shapes)]
+    X = [si.random_matrix(92 + i, (p, q), 1.0, dtype) for i, (r, q) in enumerate(shapes)]
+    W = [si.random_matrix(94 + i, sh, 0.02, dtype) for i, sh in enumerate(shapes)]
+    dW0 = [si.random_matrix(96 + i, sh, 1e-3, "f32") for i, sh in enumerate(shapes)]
+    masks = [oracle.transposable_mask(w) for w in W]
+    got = [dev(w).clone() for w in dW0]
+    s24.dense_dw_batch([(dev_bf16(dY[i]), dev_bf16(X[i]), got[i], dev_bf16(W[i]), dev(masks[i]), lam) for i in range(2)], beta=beta)
+    plain = [dev(w).clone() for w in dW0]
+    s24.dense_dw_batch([(dev_bf16(dY[i]), dev_bf16(X[i]), plain[i], None, None, 0.0) for i in range(2)], beta=beta)
+    for i, (r, q) in enumerate(shapes):
+        rows = np.unique(np.concatenate([[0, 63, 64, 127, 128, 255, 256, r - 1], np.random.default_rng(i).integers(0, r, 40)]))
+        ref = si.to_f32(dY[i])[:, rows].astype(np.float64).T @ si.to_f32(X[i]).astype(np.float64) + beta * dW0[i][rows].astype(np.float64)
+        assert_close(host_f64(plain[i])[rows], ref, tol_for(dtype), f"dense_dw_batch {case} {i}")
+        two = plain[i].clone()
+        s24.masked_decay_grad(two, dev_bf16(W[i]), dev(masks[i]), lam)     # the decay's bits are the separate kernel's
+        assert torch.equal(got[i].view(torch.int32), two.view(torch.int32))
