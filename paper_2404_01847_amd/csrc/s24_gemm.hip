@@ -57,7 +57,6 @@ template <> struct Mma<s24_half> {
     }
 };
 
-constexpr int BM = 128, BN = 128, BK = 64;  // workgroup tile; BK in elements of k
 constexpr int kThreads = 256;
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -65,40 +64,6 @@ __device__ __forceinline__ bf16x16 as_bf16x16(uint4 lo, uint4 hi)
 {
     struct { uint4 a, b; } t{lo, hi};
     return __builtin_bit_cast(bf16x16, t);
-}
-
-// LDS tile of a k-contiguous operand: rows of 64 bf16 (128 bytes = 8 chunks of
-// 16 bytes); chunk c of row r sits at chunk position c ^ ((r ^ r>>3) & 7), which
-// keeps 16-byte accesses to one chunk column free of bank conflicts both over
-// consecutive rows (MFMA operand reads) and over rows 8 apart (transposed stores).
-__device__ __forceinline__ int lds_off(int row, int chunk)
-{
-    return row * 128 + ((chunk ^ ((row ^ (row >> 3)) & 7)) << 4);
-}
-__device__ __forceinline__ uint4 lds_read(const unsigned char *buf, int row, int chunk)
-{
-    return *reinterpret_cast<const uint4 *>(buf + lds_off(row, chunk));
-}
-
-// Copy a [rows x 64] bf16 tile (row stride ld elements) from global memory into
-// registers: 1024 chunks of 16 bytes, four per thread.  Rows >= nrows read as zero.
-struct TileRegs { uint4 v[4]; };
-__device__ __forceinline__ void tile_load(TileRegs &t, const uint16_t *g, int64_t ld, int row0, int nrows, int k0, int tid)
-{
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int id = tid + kThreads * i, row = id >> 3, c = id & 7;
-        if (row0 + row < nrows) t.v[i] = *reinterpret_cast<const uint4 *>(g + (int64_t)(row0 + row) * ld + k0 + 8 * c);
-        else t.v[i] = make_uint4(0, 0, 0, 0);
-    }
-}
-__device__ __forceinline__ void tile_store(const TileRegs &t, unsigned char *buf, int tid)
-{
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int id = tid + kThreads * i, row = id >> 3, c = id & 7;
-        *reinterpret_cast<uint4 *>(buf + lds_off(row, c)) = t.v[i];
-    }
 }
 
 // ------------------------------------------------------------------ sparse NT
@@ -113,8 +78,7 @@ __device__ __forceinline__ void tile_store(const TileRegs &t, unsigned char *buf
 // consecutive lanes of an operand read on distinct 16-byte slots modulo 256
 // bytes, which is what a full-rate 128-bit LDS read needs on this chip.
 namespace big {
-constexpr int BM = 256, BN = 256, THREADS = 512;
-constexpr int B_STAGE = BN * 128, A_STAGE = BM * 64, M_STAGE = BM * 8, STAGE = B_STAGE + A_STAGE + M_STAGE;
+constexpr int BM = 256, BN = 256, THREADS = 512;   // the large tile
 typedef __attribute__((address_space(3))) void *lds_ptr;
 typedef const __attribute__((address_space(1))) void *glb_ptr;
 
@@ -639,104 +603,28 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
 }
 }  // namespace big
 
-// ------------------------------------------------------------------ dense MFMA core
-// Both operands in LDS as k-contiguous swizzled tiles.  MFMA step i of a lane
-// with k-group g = lane/32 uses chunk 4*g + i of its row, i.e. k in
-// [32*g + 8*i, 32*g + 8*i + 8) of the 64-wide chunk, for A and B alike.
-template <typename T>
-__device__ __forceinline__ void dense_chunk(f32x16 (&acc)[2][2], const unsigned char *sa, const unsigned char *sb, int wm,
-                                            int wn, int lane)
-{
-    const int g = lane >> 5;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        bf16x8 a[2], b[2];
-#pragma unroll
-        for (int mi = 0; mi < 2; ++mi) a[mi] = as_bf16x8(lds_read(sa, 64 * wm + 32 * mi + (lane & 31), 4 * g + i));
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni) b[ni] = as_bf16x8(lds_read(sb, 64 * wn + 32 * ni + (lane & 31), 4 * g + i));
-#pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni)
-                acc[mi][ni] = Mma<T>::dense(a[mi], b[ni], acc[mi][ni]);
-    }
-}
-
-// Y[n][m] = sum_k X[n][k] W[m][k]  (n tokens, m out-features)
-template <typename T>
-__global__ __launch_bounds__(kThreads) void dense_nt_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W,
-                                                            uint16_t *__restrict__ Y, int N, int K, int M)
-{
-    __shared__ __attribute__((aligned(16))) unsigned char s_a[2][BM * 128];
-    __shared__ __attribute__((aligned(16))) unsigned char s_b[2][BN * 128];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave & 1, wn = wave >> 1;
-    const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
-    const int nk = K / BK;
-    f32x16 acc[2][2];
-#pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = f32x16{};
-    TileRegs ra, rb;
-    tile_load(ra, W, K, m0, M, 0, tid);
-    tile_load(rb, X, K, n0, N, 0, tid);
-    tile_store(ra, s_a[0], tid);
-    tile_store(rb, s_b[0], tid);
-    __syncthreads();
-    for (int kc = 0; kc < nk; ++kc) {
-        const bool more = kc + 1 < nk;
-        if (more) {
-            tile_load(ra, W, K, m0, M, (kc + 1) * BK, tid);
-            tile_load(rb, X, K, n0, N, (kc + 1) * BK, tid);
-        }
-        dense_chunk<T>(acc, s_a[kc & 1], s_b[kc & 1], wm, wn, lane);
-        if (more) {
-            tile_store(ra, s_a[(kc + 1) & 1], tid);
-            tile_store(rb, s_b[(kc + 1) & 1], tid);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int ni = 0; ni < 2; ++ni) {
-        const int n = n0 + 64 * wn + 32 * ni + (lane & 31);
-        if (n >= N) continue;
-#pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int m = m0 + 64 * wm + 32 * mi + 8 * g + 4 * (lane >> 5);
-                if (m >= M) continue;
-                *reinterpret_cast<uint2 *>(Y + (int64_t)n * M + m) =
-                    make_uint2(s24_num<T>::pack2(acc[mi][ni][4 * g], acc[mi][ni][4 * g + 1]),
-                               s24_num<T>::pack2(acc[mi][ni][4 * g + 2], acc[mi][ni][4 * g + 3]));
-            }
-    }
-}
-
-// ------------------------------------------------------------------ dense NT, large tile
-// The dense comparison GEMM in the same tiling family as the sparse kernel:
-// 256 x 256 x 64 workgroup tiles, eight waves of 128 x 64, both operands copied
-// straight into LDS.  A dense operand tile is twice the compressed one, so the
-// ring has two 64 KB stages: the copies of chunk kc+1 fly during the math of kc.
+// ------------------------------------------------------------------ dense NT
+// The dense GEMM in the same tiling family as the sparse kernel: both operands copied straight into LDS.
 namespace bignt {
 // Dense NT GEMM, 256 x 256 tiles, eight waves of 128 x 64: the comparison kernel beside the sparse one, on the
 // same schedule.  32 of k per ring stage (two 16 KB operand tiles, 64-byte rows), four stages, three chunks in
 // flight; a chunk is two 16-wide steps of eight matrix instructions, the first running from registers while the
 // second's fragments come in, the one barrier of the chunk between them, and after it the next chunk's first-step
-// fragments and the four copies of chunk kc+4 dealt out between the second step's matrix instructions.
-constexpr int BM = 256, BN = 256, THREADS = 512, OPERAND = 256 * 64, STAGE = 2 * OPERAND;
+// fragments and the copies of chunk kc+4 dealt out between the second step's matrix instructions.
+// MI and WN as in the sparse kernel: 256 x 256 tiles of eight waves, and for outputs with too few of them 256 (m) x 128 (n)
+// and, two workgroups per compute unit, 128 x 128 tiles of four waves.
 using big::a_slot;
 using big::glb_ptr;
 using big::lds_ptr;
 using big::wait_vm_lgkm0;
 
-template <typename T>
-__global__ __launch_bounds__(THREADS) void dense_nt_big_kernel(const uint16_t *__restrict__ X,
+template <typename T, int MI, int WN>
+__global__ __launch_bounds__(128 * WN) void dense_nt_big_kernel(const uint16_t *__restrict__ X,
                                                                const uint16_t *__restrict__ W, uint16_t *__restrict__ Y,
                                                                int N, int K, int M, int tiles_m, int tiles_n, unsigned long long *probe)
 {
+    constexpr int BM = 64 * MI, BN = 64 * WN, WM = 32 * MI, OPERAND = BN * 64, STAGE = OPERAND + BM * 64;
+    constexpr int NW = 2 * MI / WN, NC = 2 + NW;   // copies per lane and chunk: of the weights, all
     const big::ClockStamp t_start = big::clock_now();
     __shared__ __attribute__((aligned(16))) unsigned char s0[STAGE];
     __shared__ __attribute__((aligned(16))) unsigned char s1[STAGE];
@@ -755,42 +643,47 @@ __global__ __launch_bounds__(THREADS) void dense_nt_big_kernel(const uint16_t *_
     const int m0 = tm * BM, n0 = tn * BN;
     const int nk = K / 32;
 
-    // copies: two per operand, lane and chunk; copy i of a wave fills rows 128 i + 16 wave .. +15 (four 16-byte
-    // slots each); slot c of row r holds source chunk c ^ ((r >> 2) & 3).  Wave-uniform bases (one per operand,
+    // copies: two of X and NW of the weights per lane and chunk; copy i of a wave's N fills rows 16 (N wave + i) .. +15
+    // (four 16-byte slots each); slot c of row r holds source chunk c ^ ((r >> 2) & 3).  Wave-uniform bases (one per operand,
     // advanced by 64 bytes per chunk) and fixed 32-bit lane offsets: 256 rows of K elements span < 4 GB (host check).
     const char *baseX = reinterpret_cast<const char *>(X + (int64_t)n0 * K), *baseW = reinterpret_cast<const char *>(W + (int64_t)m0 * K);
-    uint32_t ox[2], ow[2];
+    uint32_t ox[2], ow[NW];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int row = 128 * i + 16 * wave + (lane >> 2);
+        const int row = 16 * (2 * wave + i) + (lane >> 2);
         const int c = (lane & 3) ^ ((row >> 2) & 3);
         ox[i] = ((uint32_t)(min(n0 + row, N - 1) - n0) * (uint32_t)K + 8u * c) * 2u;
+    }
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        const int row = 16 * (NW * wave + i) + (lane >> 2);
+        const int c = (lane & 3) ^ ((row >> 2) & 3);
         ow[i] = ((uint32_t)(min(m0 + row, M - 1) - m0) * (uint32_t)K + 8u * c) * 2u;
     }
-    // exactly four copies per lane and call; past the last chunk it re-reads the last one into a stage nobody reads
+    // exactly NC copies per lane and call; past the last chunk it re-reads the last one into a stage nobody reads
     auto issue = [&](unsigned char *st, int kc) {
         kc = min(kc, nk - 1);
         const big::rsrc_t px = big::buffer_of(baseX + (int64_t)kc * 64), pw = big::buffer_of(baseW + (int64_t)kc * 64);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) big::buffer_to_lds<16>(px, (lds_ptr)(st + (128 * i + 16 * wave) * 64), ox[i]);
+        for (int i = 0; i < 2; ++i) big::buffer_to_lds<16>(px, (lds_ptr)(st + 16 * (2 * wave + i) * 64), ox[i]);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) big::buffer_to_lds<16>(pw, (lds_ptr)(st + OPERAND + (128 * i + 16 * wave) * 64), ow[i]);
+        for (int i = 0; i < NW; ++i) big::buffer_to_lds<16>(pw, (lds_ptr)(st + OPERAND + 16 * (NW * wave + i) * 64), ow[i]);
     };
-    f32x16 acc[4][2];
+    f32x16 acc[MI][2];
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
+    for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = f32x16{};
     // fragments of 16-wide step i of a stage: lane group g = lane / 32 takes source chunk 2 g + i of both operands
     const int g = lane >> 5;
-    auto load_frags = [&](const unsigned char *st, int i, bf16x8 (&b)[2], bf16x8 (&a)[4]) {
+    auto load_frags = [&](const unsigned char *st, int i, bf16x8 (&b)[2], bf16x8 (&a)[MI]) {
         const unsigned char *sb = st, *sa = st + OPERAND;
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni)
             b[ni] = as_bf16x8(*reinterpret_cast<const uint4 *>(sb + a_slot(64 * wn + 32 * ni + (lane & 31), 2 * g + i)));
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
-            a[mi] = as_bf16x8(*reinterpret_cast<const uint4 *>(sa + a_slot(128 * wm + 32 * mi + (lane & 31), 2 * g + i)));
+        for (int mi = 0; mi < MI; ++mi)
+            a[mi] = as_bf16x8(*reinterpret_cast<const uint4 *>(sa + a_slot(WM * wm + 32 * mi + (lane & 31), 2 * g + i)));
     };
     // keep the program order of these groups: the constant wait counts rely on it
     issue(s0, 0);
@@ -801,35 +694,35 @@ __global__ __launch_bounds__(THREADS) void dense_nt_big_kernel(const uint16_t *_
     __builtin_amdgcn_sched_barrier(0);
     issue(s3, 3);
     __builtin_amdgcn_sched_barrier(0);
-    big::wait_and_barrier<12>();   // chunk 0 has landed for everybody
-    bf16x8 fb0[2], fa0[4];
+    big::wait_and_barrier<3 * NC>();   // chunk 0 has landed for everybody
+    bf16x8 fb0[2], fa0[MI];
     load_frags(s0, 0, fb0, fa0);
     auto chunk = [&](unsigned char *cur, const unsigned char *nxt, int kc) {
-        bf16x8 fb1[2], fa1[4];
+        bf16x8 fb1[2], fa1[MI];
         load_frags(cur, 1, fb1, fa1);
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
+        for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
             for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = Mma<T>::dense(fa0[mi], fb0[ni], acc[mi][ni]);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {   // six reads, two per matrix instruction
+        for (int i = 0; i < 2 * MI; ++i) {   // MI + 2 reads, two per matrix instruction
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            if (2 * i < MI + 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         }
-        // all but the eight most recent copies (chunks kc+2, kc+3) are complete: this lane's part of chunk kc+1 is
+        // all but the copies of chunks kc+2 and kc+3 are complete: this lane's part of chunk kc+1 is
         // in LDS, and its own reads of chunk kc are done
-        big::wait_and_barrier<8>();
+        big::wait_and_barrier<2 * NC>();
         issue(cur, kc + 4);
         load_frags(nxt, 0, fb0, fa0);
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
+        for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
             for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = Mma<T>::dense(fa1[mi], fb1[ni], acc[mi][ni]);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {   // six reads and four copies
+        for (int i = 0; i < 2 * MI; ++i) {   // MI + 2 reads and NC copies
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            if (i & 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            if (2 * i < MI + 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            if (NC == 2 * MI || (NC == 4 ? i & 1 : i > 1)) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -847,9 +740,11 @@ __global__ __launch_bounds__(THREADS) void dense_nt_big_kernel(const uint16_t *_
     if (kc + 2 < nk) chunk(s2, s3, kc + 2);
     big::wait_and_barrier<0>();   // last (redundant) copies drained, nobody reads the ring any more: reuse it
     big::clock_report(probe, t_start);
-    static_assert(2 * big::EWAVE <= STAGE, "two waves' output tiles per ring stage");
-    unsigned char *est = (wave < 2 ? s0 : (wave < 4 ? s1 : (wave < 6 ? s2 : s3))) + (wave & 1) * big::EWAVE;
-    big::staged_store<T, 4>(acc, est, Y, N, M, n0 + 64 * wn, m0 + 128 * wm, lane);
+    constexpr int PER = WN / 2;   // waves that park their output tile in one ring stage
+    static_assert(PER * (big::EWAVE * MI / 4) <= STAGE, "wave tiles must fit the ring stages");
+    const int home = wave / PER;
+    unsigned char *est = (home == 0 ? s0 : (home == 1 ? s1 : (home == 2 ? s2 : s3))) + (wave % PER) * big::EWAVE;
+    big::staged_store<T, MI>(acc, est, Y, N, M, n0 + 64 * wn, m0 + WM * wm, lane);
 }
 }  // namespace bignt
 
@@ -1459,7 +1354,6 @@ inline int s24_cu_count()
     }();
     return n;
 }
-inline bool fills_chip_256(int64_t m, int64_t n) { return (int64_t)ceil_div(m, 256) * ceil_div(n, 256) >= 3 * s24_cu_count() / 4; }
 
 // Which tile a sparse NT product takes.  Costs in full rounds of the large tile at the same depth, measured over 128-16384
 // tokens, 256-4096 x 1024-22016 features (us per 64 of k at K = 5504 to 11008: large 0.75 with every compute unit busy and
@@ -1480,22 +1374,27 @@ struct NtTile {
     int bn() const { return kind == Large ? 256 : 128; }
     int threads() const { return kind == Large ? 512 : 256; }
 };
-inline double nt_cost(NtTile::Kind kind, int64_t M, int64_t N, int64_t K)
+// Cost of a full round of medium and small tiles, and of a partial round (offset, slope over its fill) of each kind
+struct NtCosts {
+    double large0, large1, medium, medium0, medium1, small, small0, small1;
+};
+inline double nt_cost(NtTile::Kind kind, int64_t M, int64_t N, const NtCosts &c)
 {
     const int64_t cus = s24_cu_count();
     const NtTile t{kind, 0};
     const int64_t tiles = (int64_t)ceil_div(M, t.bm()) * ceil_div(N, t.bn()), per = kind == NtTile::Small ? 2 * cus : cus;
-    const double full = (double)(tiles / per), rest = (double)(tiles % per);
-    if (kind == NtTile::Large) return full + (rest > 0 ? 0.73 + 0.27 * rest / per : 0);
-    if (kind == NtTile::Medium) return 0.69 * full + (rest > 0 ? 0.49 + 0.20 * rest / per : 0);
-    const double round = K <= 1024 ? 0.6 : K <= 2048 ? 0.7 : 0.82;
-    return round * full + (rest == 0 ? 0 : rest <= cus ? 0.37 + 0.06 * rest / cus : round);
+    const double full = (double)(tiles / per), rest = (double)(tiles % per) / cus;
+    if (kind == NtTile::Large) return full + (rest > 0 ? c.large0 + c.large1 * rest : 0);
+    if (kind == NtTile::Medium) return c.medium * full + (rest > 0 ? c.medium0 + c.medium1 * rest : 0);
+    return c.small * full + (rest == 0 ? 0 : rest <= 1 ? c.small0 + c.small1 * rest : c.small);
 }
-inline NtTile nt_tile(int64_t M, int64_t N, int64_t K)
+inline NtTile cheapest_tile(int64_t M, int64_t N, const NtCosts &c)
 {
-    const double l = nt_cost(NtTile::Large, M, N, K), m = nt_cost(NtTile::Medium, M, N, K), s = nt_cost(NtTile::Small, M, N, K);
+    const double l = nt_cost(NtTile::Large, M, N, c), m = nt_cost(NtTile::Medium, M, N, c), s = nt_cost(NtTile::Small, M, N, c);
     return {l <= m && l <= s ? NtTile::Large : m <= s ? NtTile::Medium : NtTile::Small, 0};
 }
+inline NtCosts sparse_costs(int64_t K) { return {0.73, 0.27, 0.69, 0.49, 0.20, K <= 1024 ? 0.6 : K <= 2048 ? 0.7 : 0.82, 0.37, 0.06}; }
+inline NtTile nt_tile(int64_t M, int64_t N, int64_t K) { return cheapest_tile(M, N, sparse_costs(K)); }
 // The same for a product whose tokens may be cut in two launches
 inline NtTile nt_tile_or_slab(int64_t M, int64_t N, int64_t K)
 {
@@ -1503,10 +1402,15 @@ inline NtTile nt_tile_or_slab(int64_t M, int64_t N, int64_t K)
     const int64_t cus = s24_cu_count(), tm = ceil_div(M, 256), tiles = tm * ceil_div(N, 256);
     if (tiles <= cus || tiles % cus == 0 || tm > cus) return t;
     const int64_t rows = tiles / cus * cus / tm, slab = 256 * rows;   // whole token-tile rows within the whole rounds
-    const NtTile strip = nt_tile(M, N - slab, K);
-    if (nt_cost(NtTile::Large, M, slab, K) + nt_cost(strip.kind, M, N - slab, K) < nt_cost(t.kind, M, N, K)) t.slab = slab;
+    const NtCosts c = sparse_costs(K);
+    const NtTile strip = cheapest_tile(M, N - slab, c);
+    if (nt_cost(NtTile::Large, M, slab, c) + nt_cost(strip.kind, M, N - slab, c) < nt_cost(t.kind, M, N, c)) t.slab = slab;
     return t;
 }
+// The dense product: us per 64 of k, large 1.7 and 0.9 (full, few), medium 1.05 and 0.7, small 1.2 with two workgroups per
+// compute unit, 0.5 with one.  The 128 x 128 kernel that staged its operands through registers took 1.5 and 0.8: 8192 x 1024,
+// K = 4096: 96 -> 72 us (medium); 500 x 4096, K = 16384: 204 -> 115; 2048 x 3072, K = 768: 21 -> 17.
+inline NtTile dense_tile(int64_t M, int64_t N) { return cheapest_tile(M, N, {0.53, 0.30, 0.62, 0.40, 0.20, 0.70, 0.26, 0.08}); }
 // Runs MACRO(..., MI, WN) with the wave layout of a tile
 #define S24_WITH_NT_TILE(tile, MACRO, ...)                              \
     do {                                                                \
@@ -1597,8 +1501,9 @@ extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t 
     NtTile tile = nt_tile(2 * f, p, q);
     // the small tile has no gated epilogue: it is taken only where it saves more than a launch for the activation
     if (tile.kind == NtTile::Small) {
-        const double l = nt_cost(NtTile::Large, 2 * f, p, q), m = nt_cost(NtTile::Medium, 2 * f, p, q);
-        if (std::min(l, m) < nt_cost(NtTile::Small, 2 * f, p, q) + 0.1) tile.kind = l <= m ? NtTile::Large : NtTile::Medium;
+        const NtCosts c = sparse_costs(q);
+        const double l = nt_cost(NtTile::Large, 2 * f, p, c), m = nt_cost(NtTile::Medium, 2 * f, p, c);
+        if (std::min(l, m) < nt_cost(NtTile::Small, 2 * f, p, c) + 0.1) tile.kind = l <= m ? NtTile::Large : NtTile::Medium;
     }
     if (dt != S24_F32 && tile.kind != NtTile::Small) {   // 128 gate and 128 up features per tile
         const int tiles_m = (int)ceil_div(f, 128), tiles_n = (int)ceil_div(p, tile.bn());
@@ -1749,16 +1654,19 @@ extern "C" int s24_dense_gemm(const void *X, const void *W, void *Y, int64_t p, 
     }
     auto *x = static_cast<const uint16_t *>(X), *w = static_cast<const uint16_t *>(W);
     auto *y = static_cast<uint16_t *>(Y);
-    if (fills_chip_256(r, p)) {
-        const int tiles_m = (int)ceil_div(r, bignt::BM), tiles_n = (int)ceil_div(p, bignt::BN);
-        S24_WITH_16BIT_TYPE(dt, hipLaunchKernelGGL(bignt::dense_nt_big_kernel<T>, dim3(((tiles_m * tiles_n + 7) / 8) * 8),
-                                                   dim3(bignt::THREADS), 0, st, x, w, y, (int)p, (int)q, (int)r, tiles_m,
-                                                   tiles_n, g_clock_probe));
-    } else {
-        const dim3 grid(ceil_div(r, BM), ceil_div(p, BN)), block(kThreads);
-        S24_REQUIRE(grid.y <= 65535, S24_ERR_SHAPE);
-        S24_WITH_16BIT_TYPE(dt, hipLaunchKernelGGL(dense_nt_kernel<T>, grid, block, 0, st, x, w, y, (int)p, (int)q, (int)r));
-    }
+    S24_REQUIRE((int64_t)ceil_div(r, 128) * ceil_div(p, 128) < (1ll << 30), S24_ERR_SHAPE);
+    const NtTile tile = dense_tile(r, p);
+    const int tiles_m = (int)ceil_div(r, tile.bm()), tiles_n = (int)ceil_div(p, tile.bn());
+    const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(tile.threads());
+#define S24_LAUNCH_DENSE(MI, WN)                                                                                              \
+    hipLaunchKernelGGL((bignt::dense_nt_big_kernel<T, MI, WN>), grid, block, 0, st, x, w, y, (int)p, (int)q, (int)r, tiles_m, \
+                       tiles_n, tile.kind == NtTile::Large ? g_clock_probe : nullptr)
+    S24_WITH_16BIT_TYPE(dt, {
+        if (tile.kind == NtTile::Large) S24_LAUNCH_DENSE(4, 4);
+        else if (tile.kind == NtTile::Medium) S24_LAUNCH_DENSE(4, 2);
+        else S24_LAUNCH_DENSE(2, 2);
+    });
+#undef S24_LAUNCH_DENSE
     return s24_launch_status();
 }
 

@@ -262,3 +262,18 @@ def test_medium_tile_weight_gradients(s24, dtype, case):
         two = plain[i].clone()
         s24.masked_decay_grad(two, dev_bf16(W[i]), dev(masks[i]), lam)     # the decay's bits are the separate kernel's
         assert torch.equal(got[i].view(torch.int32), two.view(torch.int32))
+
+
+# ------------------------------------------------------------------ dense products on the smaller tiles
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+# the 128 x 128 tile and the 256 x 128 one (136 of them), ragged both ways; 2, 4, 6 and 10 chunks of 32 against a ring of four
+@pytest.mark.parametrize("pr", [(1, 16), (130, 144), (2050, 2032)])
+@pytest.mark.parametrize("q", [64, 128, 192, 320])
+def test_dense_product_tiles(s24, dtype, pr, q):
+    p, r = pr
+    X, W = si.random_matrix(100 + p, (p, q), 1.0, dtype), si.random_matrix(101 + r, (r, q), 0.02, dtype)
+    Y = torch.full((p, r), 7.0, dtype=torch_dtype(dtype), device="cuda")
+    s24.dense_gemm(dev_bf16(X), dev_bf16(W), Y)
+    rows = np.unique(np.concatenate([[0, p - 1], np.random.default_rng(p).integers(0, p, 40), np.arange(min(p, 260))]))
+    ref = si.to_f32(X)[rows].astype(np.float64) @ si.to_f32(W).astype(np.float64).T
+    assert_close(host_f64(Y)[rows], ref, tol_for(dtype), f"dense_gemm {pr} {q}")
