@@ -1084,22 +1084,24 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
 // copied as they lie, fragments gathered with the transposing LDS read).  One sparse instruction covers the
 // tokens {16h .. 16h+15} and {32+16h .. 32+16h+15} of a 64-token chunk (h = 0, 1), which is how the index
 // words split over a lane pair; its dense fragment is therefore two 8-token runs 32 tokens apart.
-// 256 x 256 tiles, eight waves of 128 (m) x 64 (n), ring of three 50 KB stages, fp32 output through LDS.
+// MI and WN as in the sparse NT kernel: 256 x 256 tiles of eight waves, 256 (m) x 128 (n) and 128 x 128 ones of four; ring of
+// three stages, fp32 output through LDS.
 namespace sptn {
-constexpr int BM = 256, BN = 256, THREADS = 512, ROWB = BN * 2, CPR = ROWB / 16;
-constexpr int B_STAGE = 64 * ROWB, A_STAGE = BM * 64, M_STAGE = BM * 8, STAGE = B_STAGE + A_STAGE + M_STAGE;
 using big::a_slot;
 using big::glb_ptr;
 using big::lds_ptr;
 
-template <typename ET, bool ACCUM, bool DECAY>
-__global__ __launch_bounds__(THREADS) void spmm_tn_big_kernel(const uint16_t *__restrict__ Av,
+template <typename ET, bool ACCUM, bool DECAY, int MI, int WN>
+__global__ __launch_bounds__(128 * WN) void spmm_tn_big_kernel(const uint16_t *__restrict__ Av,
                                                               const uint16_t *__restrict__ Am,
                                                               const uint16_t *__restrict__ X, float *__restrict__ dW,
                                                               int T, int M, int N, int tiles_m, int tiles_n,
                                                               unsigned long long *probe, const uint16_t *__restrict__ Wt,
                                                               const uint16_t *__restrict__ mask, float lambda)
 {
+    constexpr int BM = 64 * MI, BN = 64 * WN, WM = 32 * MI, ROWB = BN * 2, CPR = ROWB / 16;
+    constexpr int B_STAGE = 64 * ROWB, A_STAGE = BM * 64, M_STAGE = BM * 8, STAGE = B_STAGE + A_STAGE + M_STAGE;
+    constexpr int NA = 2 * MI / WN, NX = MI / WN, NC = 4 + NA + NX;   // copies per lane and chunk: values, index words, all
     const big::ClockStamp t_start = big::clock_now();
     __shared__ __attribute__((aligned(16))) unsigned char s0[STAGE];
     __shared__ __attribute__((aligned(16))) unsigned char s1[STAGE];
@@ -1117,12 +1119,12 @@ __global__ __launch_bounds__(THREADS) void spmm_tn_big_kernel(const uint16_t *__
     const int m0 = tm * BM, n0 = tn * BN;
     const int nk = T / 64;
 
-    // Copies per lane and chunk: four of the X tile (rows 8*wave .. 8*wave+7), two of the values, one index dword;
+    // Copies per lane and chunk: four of the X tile, NA of the values, NX index dwords;
     // buffer loads into LDS with a wave-uniform base per operand and chunk and a fixed 32-bit byte offset per lane
     // (64 token rows of X and one chunk of the compressed operand span less than 4 GB: host check).
     const char *baseX = reinterpret_cast<const char *>(X), *baseV = reinterpret_cast<const char *>(Av);
     const char *baseM = reinterpret_cast<const char *>(Am);
-    uint32_t ob[4], oa[2];
+    uint32_t ob[4], oa[NA], om[NX];
     const int lastB = (min(N - n0, BN) >> 3) - 1;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -1130,13 +1132,14 @@ __global__ __launch_bounds__(THREADS) void spmm_tn_big_kernel(const uint16_t *__
         ob[j] = ((uint32_t)row * (uint32_t)N + (uint32_t)(n0 + 8 * min(c, lastB))) * 2u;
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int row = 32 * wave + 16 * i + (lane >> 2);
+    for (int i = 0; i < NA; ++i) {
+        const int row = 16 * (NA * wave + i) + (lane >> 2);
         const int c = (lane & 3) ^ ((row >> 2) & 3);
         oa[i] = ((uint32_t)min(m0 + row, M - 1) * 32u + 8u * c) * 2u;
     }
-    const uint32_t om = ((uint32_t)min(m0 + 32 * wave + (lane >> 1), M - 1) * 4u + 2u * (lane & 1)) * 2u;
-    // exactly seven copies per lane and call; past the last chunk it re-reads the last one into a stage nobody
+#pragma unroll
+    for (int i = 0; i < NX; ++i) om[i] = ((uint32_t)min(m0 + 32 * (NX * wave + i) + (lane >> 1), M - 1) * 4u + 2u * (lane & 1)) * 2u;
+    // exactly NC copies per lane and call; past the last chunk it re-reads the last one into a stage nobody
     // will read again, so that the wait counts below are constants
     auto issue = [&](unsigned char *st, int kc) {
         kc = min(kc, nk - 1);
@@ -1145,13 +1148,14 @@ __global__ __launch_bounds__(THREADS) void spmm_tn_big_kernel(const uint16_t *__
 #pragma unroll
         for (int j = 0; j < 4; ++j) big::buffer_to_lds<16>(px, (lds_ptr)(st + (wave * 4 + j) * 1024), ob[j]);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) big::buffer_to_lds<16>(pv, (lds_ptr)(st + B_STAGE + (32 * wave + 16 * i) * 64), oa[i]);
-        big::buffer_to_lds<4>(pm, (lds_ptr)(st + B_STAGE + A_STAGE + 32 * wave * 8), om);
+        for (int i = 0; i < NA; ++i) big::buffer_to_lds<16>(pv, (lds_ptr)(st + B_STAGE + 16 * (NA * wave + i) * 64), oa[i]);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) big::buffer_to_lds<4>(pm, (lds_ptr)(st + B_STAGE + A_STAGE + 32 * (NX * wave + i) * 8), om[i]);
     };
 
-    f32x16 acc[4][2];
+    f32x16 acc[MI][2];
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
+    for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = f32x16{};
 
@@ -1163,7 +1167,7 @@ __global__ __launch_bounds__(THREADS) void spmm_tn_big_kernel(const uint16_t *__
     for (int ni = 0; ni < 2; ++ni) offB[ni] = dmatn::tr_off<ROWB>(frow, 64 * wn + 32 * ni + fcol);
     // Fragments of half h of a stage (the tokens {16h..16h+15} and {32+16h..} of the chunk): eight transposing
     // reads of the X tile and four 128-bit reads of the values
-    auto load_frags = [&](const unsigned char *st, int h, bf16x16 (&b)[2], bf16x8 (&a)[4]) {
+    auto load_frags = [&](const unsigned char *st, int h, bf16x16 (&b)[2], bf16x8 (&a)[MI]) {
         const unsigned char *sb = st, *sa = st + B_STAGE;
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni) {
@@ -1172,14 +1176,14 @@ __global__ __launch_bounds__(THREADS) void spmm_tn_big_kernel(const uint16_t *__
             b[ni] = __builtin_bit_cast(bf16x16, pair);
         }
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
-            a[mi] = as_bf16x8(*reinterpret_cast<const uint4 *>(sa + a_slot(128 * wm + 32 * mi + (lane & 31), 2 * g + h)));
+        for (int mi = 0; mi < MI; ++mi)
+            a[mi] = as_bf16x8(*reinterpret_cast<const uint4 *>(sa + a_slot(WM * wm + 32 * mi + (lane & 31), 2 * g + h)));
     };
-    auto load_index = [&](const unsigned char *st, uint32_t (&x)[4]) {
+    auto load_index = [&](const unsigned char *st, uint32_t (&x)[MI]) {
         const unsigned char *sm = st + B_STAGE + A_STAGE;
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
-            x[mi] = *reinterpret_cast<const uint32_t *>(sm + (128 * wm + 32 * mi + (lane & 31)) * 8 + 4 * g);
+        for (int mi = 0; mi < MI; ++mi)
+            x[mi] = *reinterpret_cast<const uint32_t *>(sm + (WM * wm + 32 * mi + (lane & 31)) * 8 + 4 * g);
     };
 
     // keep the program order of these groups: the constant wait counts rely on it
@@ -1189,48 +1193,50 @@ __global__ __launch_bounds__(THREADS) void spmm_tn_big_kernel(const uint16_t *__
     __builtin_amdgcn_sched_barrier(0);
     issue(s2, 2);
     __builtin_amdgcn_sched_barrier(0);
-    big::wait_and_barrier<14>();   // chunk 0 has landed for everybody
+    big::wait_and_barrier<2 * NC>();   // chunk 0 has landed for everybody
     bf16x16 fb0[2];
-    bf16x8 fa0[4];
-    uint32_t ix[4];
+    bf16x8 fa0[MI];
+    uint32_t ix[MI];
     load_index(s0, ix);
     load_frags(s0, 0, fb0, fa0);
 
     // One chunk, pipelined across the workgroup barrier exactly as in the NT kernel: the first half's matrix
     // instructions run from registers while the second half's fragments come in; after the one barrier of the chunk
     // the second half's matrix instructions cover the next chunk's index words and first-half fragments and the
-    // seven copies of chunk kc+3 into the stage just vacated.
+    // copies of chunk kc+3 into the stage just vacated.
     auto chunk = [&](unsigned char *cur, const unsigned char *nxt, int kc) {
         bf16x16 fb1[2];
-        bf16x8 fa1[4];
+        bf16x8 fa1[MI];
         load_frags(cur, 1, fb1, fa1);
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
+        for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
             for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = Mma<ET>::template sparse<0>(fa0[mi], fb0[ni], acc[mi][ni], (int)ix[mi]);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {   // twelve reads, two per matrix instruction
+        for (int i = 0; i < 2 * MI; ++i) {   // 8 + MI reads
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (i < 6) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            if (MI == 2) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+            else if (i < 6) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         }
-        big::wait_and_barrier<7>();   // this lane's part of chunk kc+1 is in LDS, its own reads of chunk kc are done
+        big::wait_and_barrier<NC>();   // this lane's part of chunk kc+1 is in LDS, its own reads of chunk kc are done
         issue(cur, kc + 3);
-        uint32_t ixn[4];
+        uint32_t ixn[MI];
         load_index(nxt, ixn);
         load_frags(nxt, 0, fb0, fa0);
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
+        for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
             for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = Mma<ET>::template sparse<1>(fa1[mi], fb1[ni], acc[mi][ni], (int)ix[mi]);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {   // sixteen reads and seven copies
+        for (int i = 0; i < 2 * MI; ++i) {   // 8 + 2 MI reads and NC copies
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            if (i < 7) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, MI == 2 ? 3 : 2, 0);
+            if (i < NC - 2 * MI) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
+            else if (i < NC) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi) ix[mi] = ixn[mi];
+        for (int mi = 0; mi < MI; ++mi) ix[mi] = ixn[mi];
     };
     // past the last chunk the prefetched fragments come from a stage that holds a re-read of the last chunk (or is
     // being refilled with one); they are never multiplied
@@ -1244,27 +1250,28 @@ __global__ __launch_bounds__(THREADS) void spmm_tn_big_kernel(const uint16_t *__
     if (kc + 1 < nk) chunk(s1, s2, kc + 1);
     big::wait_and_barrier<0>();   // copies drained, nobody reads the ring any more: reuse it
     big::clock_report(probe, t_start);
-    // fp32 output through LDS in 16-byte row segments: a wave parks 64 rows x 64 columns (two of its four row
-    // blocks) at a time in 16 KB of the ring, lane l of pass j owns row (64j + l) / 16, columns 4 * (l % 16) .. +3
-    static_assert(3 * 16384 <= STAGE, "three waves' staging areas per ring stage");
-    unsigned char *est = (wave < 3 ? s0 : (wave < 6 ? s1 : s2)) + (wave % 3) * 16384;
+    // fp32 output through LDS in 16-byte row segments: a wave parks RB row blocks x 64 columns at a time in its part of
+    // the ring, lane l of pass j owns row (64j + l) / 16, columns 4 * (l % 16) .. +3
+    constexpr int RB = MI / 2, PER = WN == 4 ? 3 : 2, REGION = RB * 8192;   // PER waves' staging areas per ring stage
+    static_assert(PER * REGION <= STAGE && 2 * WN <= 3 * PER, "staging areas must fit the ring");
+    unsigned char *est = (wave < PER ? s0 : (wave < 2 * PER ? s1 : s2)) + (wave % PER) * REGION;
 #pragma unroll
-    for (int h2 = 0; h2 < 2; ++h2) {
+    for (int h2 = 0; h2 < MI / RB; ++h2) {
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni)
 #pragma unroll
-            for (int mj = 0; mj < 2; ++mj)
+            for (int mj = 0; mj < RB; ++mj)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int row = 32 * mj + 8 * (e / 4) + 4 * (lane >> 5) + (e & 3), col = 32 * ni + (lane & 31);
-                    *reinterpret_cast<float *>(est + row * 256 + col * 4) = acc[2 * h2 + mj][ni][e];
+                    *reinterpret_cast<float *>(est + row * 256 + col * 4) = acc[RB * h2 + mj][ni][e];
                 }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(big::wait_vm_lgkm0(0));   // the wave reads back only what it wrote itself
         asm volatile("" ::: "memory");
         constexpr int BATCH = 8;
 #pragma unroll 1
-        for (int j0 = 0; j0 < 16; j0 += BATCH) {
+        for (int j0 = 0; j0 < 8 * RB; j0 += BATCH) {
             float4 v[BATCH], old[BATCH];
             uint2 wv[BATCH];
             uint32_t keep[BATCH];
@@ -1272,7 +1279,7 @@ __global__ __launch_bounds__(THREADS) void spmm_tn_big_kernel(const uint16_t *__
 #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
                 const int idx = (j0 + b) * 64 + lane, row = idx >> 4, c4 = idx & 15;
-                const int m = m0 + 128 * wm + 64 * h2 + row, n = n0 + 64 * wn + 4 * c4;
+                const int m = m0 + WM * wm + 32 * RB * h2 + row, n = n0 + 64 * wn + 4 * c4;
                 live[b] = m < M && n < N;   // N is a multiple of 16: the four columns are all in or all out
                 const int mc = min(m, M - 1), nc = min(n, N - 4);
                 v[b] = *reinterpret_cast<const float4 *>(est + row * 256 + c4 * 16);
@@ -1285,7 +1292,7 @@ __global__ __launch_bounds__(THREADS) void spmm_tn_big_kernel(const uint16_t *__
 #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
                 const int idx = (j0 + b) * 64 + lane, row = idx >> 4, c4 = idx & 15;
-                const int m = m0 + 128 * wm + 64 * h2 + row, n = n0 + 64 * wn + 4 * c4;
+                const int m = m0 + WM * wm + 32 * RB * h2 + row, n = n0 + 64 * wn + 4 * c4;
                 float4 o = v[b];
                 if (ACCUM) { o.x = old[b].x + o.x; o.y = old[b].y + o.y; o.z = old[b].z + o.z; o.w = old[b].w + o.w; }
                 if (DECAY) {
@@ -1411,6 +1418,10 @@ inline NtTile nt_tile_or_slab(int64_t M, int64_t N, int64_t K)
 // compute unit, 0.5 with one.  The 128 x 128 kernel that staged its operands through registers took 1.5 and 0.8: 8192 x 1024,
 // K = 4096: 96 -> 72 us (medium); 500 x 4096, K = 16384: 204 -> 115; 2048 x 3072, K = 768: 21 -> 17.
 inline NtTile dense_tile(int64_t M, int64_t N) { return cheapest_tile(M, N, {0.53, 0.30, 0.62, 0.40, 0.20, 0.70, 0.26, 0.08}); }
+// The sparse weight gradient: us per 64 tokens, large 1.15 and 0.6 (full, few), medium 0.5 (one round), small 0.66 with two
+// workgroups per compute unit and 0.34 to 0.43 with one.  Large alone before: 8192 tokens, 768 x 3072: 78 -> 43 us (small);
+// 2048, 512 x 2048: 27 -> 14; 16384, 1280 x 5120: 164 -> 126 (medium); 3008, 1472 x 4032: 42 -> 32.
+inline NtTile sparse_dw_tile(int64_t M, int64_t N) { return cheapest_tile(M, N, {0.50, 0.45, 0.62, 0.36, 0.10, 0.60, 0.29, 0.08}); }
 // Runs MACRO(..., MI, WN) with the wave layout of a tile
 #define S24_WITH_NT_TILE(tile, MACRO, ...)                              \
     do {                                                                \
@@ -1975,19 +1986,21 @@ extern "C" int s24_spmm_dw(const void *vals, const uint16_t *meta, const void *X
         S24_REQUIRE(meta != nullptr, S24_ERR_NULL);
         S24_REQUIRE(s24_aligned(meta, 4), S24_ERR_ALIGN);
         if (dt != S24_F32) {
-            const int tiles_m = (int)ceil_div(r, sptn::BM), tiles_n = (int)ceil_div(q, sptn::BN);
-            const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(sptn::THREADS);
+            const NtTile tile = sparse_dw_tile(r, q);
+            S24_REQUIRE((int64_t)ceil_div(r, 128) * ceil_div(q, 128) < (1ll << 30), S24_ERR_SHAPE);
+            const int tiles_m = (int)ceil_div(r, tile.bm()), tiles_n = (int)ceil_div(q, tile.bn());
+            const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(tile.threads());
             auto *av = static_cast<const uint16_t *>(vals), *x = static_cast<const uint16_t *>(X);
             const bool fuse = decay_pending && wdt == dt;
             auto *w = static_cast<const uint16_t *>(fuse ? W : nullptr);
-#define S24_LAUNCH_SPDW(ACC, DEC)                                                                                           \
-    hipLaunchKernelGGL((sptn::spmm_tn_big_kernel<T, ACC, DEC>), grid, block, 0, st, av, meta, x, dW, (int)p, (int)r, (int)q, \
-                       tiles_m, tiles_n, g_clock_probe, w, mask, lambda)
+#define S24_LAUNCH_SPDW(ACC, DEC, MI, WN)                                                                                           \
+    hipLaunchKernelGGL((sptn::spmm_tn_big_kernel<T, ACC, DEC, MI, WN>), grid, block, 0, st, av, meta, x, dW, (int)p, (int)r, (int)q, \
+                       tiles_m, tiles_n, tile.kind == NtTile::Large ? g_clock_probe : nullptr, w, mask, lambda)
             S24_WITH_16BIT_TYPE(dt, {
-                if (accum && fuse) S24_LAUNCH_SPDW(true, true);
-                else if (accum) S24_LAUNCH_SPDW(true, false);
-                else if (fuse) S24_LAUNCH_SPDW(false, true);
-                else S24_LAUNCH_SPDW(false, false);
+                if (accum && fuse) S24_WITH_NT_TILE(tile, S24_LAUNCH_SPDW, true, true);
+                else if (accum) S24_WITH_NT_TILE(tile, S24_LAUNCH_SPDW, true, false);
+                else if (fuse) S24_WITH_NT_TILE(tile, S24_LAUNCH_SPDW, false, true);
+                else S24_WITH_NT_TILE(tile, S24_LAUNCH_SPDW, false, false);
             });
 #undef S24_LAUNCH_SPDW
             if (fuse) decay_pending = false;

@@ -277,3 +277,27 @@ def test_dense_product_tiles(s24, dtype, pr, q):
     rows = np.unique(np.concatenate([[0, p - 1], np.random.default_rng(p).integers(0, p, 40), np.arange(min(p, 260))]))
     ref = si.to_f32(X)[rows].astype(np.float64) @ si.to_f32(W).astype(np.float64).T
     assert_close(host_f64(Y)[rows], ref, tol_for(dtype), f"dense_gemm {pr} {q}")
+
+
+# ------------------------------------------------------------------ sparse weight gradients by size of the output
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+# 128 x 128, 256 x 128 (136 of them) and 256 x 256 tiles, ragged both ways; one, three and four chunks against a ring of three
+@pytest.mark.parametrize("rq", [(144, 272), (2032, 2064), (4080, 4112)])
+@pytest.mark.parametrize("p,beta", [(64, 0.0), (192, 1.0), (256, 0.0)])
+def test_sparse_weight_gradient_tiles(s24, dtype, rq, p, beta):
+    (r, q), lam = rq, 2e-4
+    dY, X = si.random_matrix(110 + p, (p, r), 1e-2, dtype), si.random_matrix(111 + p, (p, q), 1.0, dtype)
+    W, dW0 = si.random_matrix(112 + r, (r, q), 0.02, dtype), si.random_matrix(113 + r, (r, q), 1e-3, "f32")
+    mask = oracle.transposable_mask(W)
+    vz, mz = oracle.mvue24(dY, 7)
+    v, m = oracle.pack(vz, mz)
+    plain, decayed = dev(dW0).clone(), dev(dW0).clone()
+    s24.spmm_dw(dev_bf16(v), dev(m), dev_bf16(X), plain, beta=beta)
+    s24.spmm_dw(dev_bf16(v), dev(m), dev_bf16(X), decayed, beta=beta, W=dev_bf16(W), mask=dev(mask), lam=lam)
+    rows = np.unique(np.concatenate([[0, r - 1], np.random.default_rng(r).integers(0, r, 40), np.arange(min(r, 130))]))
+    rows = np.resize(rows, (rows.size + 15) // 16 * 16)     # the oracle takes multiples of 16: the first ones again
+    ref = oracle.spmm_fwd(np.ascontiguousarray(X.T), np.ascontiguousarray(vz[rows]), np.ascontiguousarray(mz[rows])).T + beta * dW0[rows].astype(np.float64)
+    assert_close(host_f64(plain)[rows], ref, tol_for(dtype), f"spmm_dw {rq} {p}")
+    two = plain.clone()
+    s24.masked_decay_grad(two, dev_bf16(W), dev(mask), lam)
+    assert torch.equal(decayed.view(torch.int32), two.view(torch.int32))
