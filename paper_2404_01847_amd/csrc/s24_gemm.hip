@@ -1430,9 +1430,12 @@ inline NtTile sparse_dw_tile(int64_t M, int64_t N) { return cheapest_tile(M, N, 
         else MACRO(__VA_ARGS__, 2, 2);                                  \
     } while (0)
 
+// Outputs that the gated backward epilogue serves: three quarters of the compute units have a large tile
+inline bool gated_bwd_fits(int64_t p, int64_t f) { return (int64_t)ceil_div(f, 256) * ceil_div(p, 256) >= 3 * s24_cu_count() / 4; }
+
 // Out[N][M] = beta * Out + B[N][K] . A^T (+ bias[M], only with beta = 0)
 int launch_spmm(const void *B, const void *Av, const uint16_t *Am, void *Out, int64_t N, int64_t K, int64_t M, float beta,
-                int dt, hipStream_t st, const void *bias = nullptr)
+                int dt, hipStream_t st, const void *bias = nullptr, bool may_slice = true)
 {
     if (N == 0 || M == 0) return S24_OK;
     const bool accum = beta != 0.0f;
@@ -1443,12 +1446,12 @@ int launch_spmm(const void *B, const void *Av, const uint16_t *Am, void *Out, in
     auto *b = static_cast<const uint16_t *>(B), *av = static_cast<const uint16_t *>(Av), *d = static_cast<const uint16_t *>(bias);
     auto *o = static_cast<uint16_t *>(Out);
     S24_REQUIRE((int64_t)ceil_div(M, 128) * ceil_div(N, 128) < (1ll << 30), S24_ERR_SHAPE);
-    if (s24_slice_pays(N, K, M)) return s24_slice_nt({b, av, Am, o, nullptr, nullptr, d, N, K, M, accum, S24_SLICE_PLAIN, 0}, dt, st);
+    if (may_slice && s24_slice_pays(N, K, M)) return s24_slice_nt({b, av, Am, o, nullptr, nullptr, d, N, K, M, accum, S24_SLICE_PLAIN, 0}, dt, st);
     const NtTile tile = nt_tile_or_slab(M, N, K);
     if (tile.slab != 0) {
-        const int rc = launch_spmm(B, Av, Am, Out, tile.slab, K, M, beta, dt, st, bias);
+        const int rc = launch_spmm(B, Av, Am, Out, tile.slab, K, M, beta, dt, st, bias, false);
         if (rc != S24_OK) return rc;
-        return launch_spmm(b + tile.slab * K, Av, Am, o + tile.slab * M, N - tile.slab, K, M, beta, dt, st, bias);
+        return launch_spmm(b + tile.slab * K, Av, Am, o + tile.slab * M, N - tile.slab, K, M, beta, dt, st, bias, false);
     }
     const int tiles_m = (int)ceil_div(M, tile.bm()), tiles_n = (int)ceil_div(N, tile.bn());
     const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(tile.threads());
@@ -1493,7 +1496,8 @@ extern "C" int s24_spmm_bwd_dx(const void *dY, const void *valsT, const uint16_t
     if (rc != S24_OK || p * q == 0) return rc;
     S24_REQUIRE(metaT != nullptr, S24_ERR_NULL);
     S24_REQUIRE(s24_aligned(metaT, 4), S24_ERR_ALIGN);
-    return launch_spmm(dY, valsT, metaT, dX, p, r, q, beta, dt, static_cast<hipStream_t>(stream));
+    // where s24_spmm_bwd_dx_glu takes its large tiles, the plain product sums in the same order: same bits
+    return launch_spmm(dY, valsT, metaT, dX, p, r, q, beta, dt, static_cast<hipStream_t>(stream), nullptr, !gated_bwd_fits(p, q));
 }
 
 extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t *meta, const void *bias, void *GU, void *H,
@@ -1560,7 +1564,7 @@ extern "C" int s24_spmm_bwd_dx_glu(const void *dY, const void *valsT, const uint
     S24_REQUIRE(s24_aligned(metaT, 4) && s24_aligned(GU, 16), S24_ERR_ALIGN);
     const int tiles_m = (int)ceil_div(f, big::BM), tiles_n = (int)ceil_div(p, big::BN);
     // only the large-tile 16-bit kernel carries this epilogue; other shapes take s24_spmm_bwd_dx + s24_glu_bwd
-    S24_REQUIRE(dt != S24_F32 && (int64_t)tiles_m * tiles_n >= 3 * s24_cu_count() / 4, S24_ERR_UNSUPPORTED);
+    S24_REQUIRE(dt != S24_F32 && gated_bwd_fits(p, f), S24_ERR_UNSUPPORTED);
     const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(big::THREADS);
     hipStream_t st = static_cast<hipStream_t>(stream);
     auto *dy = static_cast<const uint16_t *>(dY), *av = static_cast<const uint16_t *>(valsT), *gu = static_cast<const uint16_t *>(GU);

@@ -301,3 +301,28 @@ def test_sparse_weight_gradient_tiles(s24, dtype, rq, p, beta):
     two = plain.clone()
     s24.masked_decay_grad(two, dev_bf16(W), dev(mask), lam)
     assert torch.equal(decayed.view(torch.int32), two.view(torch.int32))
+
+
+# one lane, a vector and a remainder, the four-vector pass and what it leaves, more vectors than 256 workgroups take in one pass
+@pytest.mark.parametrize("n", [1, 7, 8, 8193, 32768, 40970, 2097152 + 8 * 300 + 5])
+def test_mask_flips_by_size(s24, n):
+    rng = np.random.default_rng(n)
+    a, b = rng.integers(0, 65536, n).astype(np.uint16), rng.integers(0, 65536, n).astype(np.uint16)
+    flips, per = torch.full((1,), 9, dtype=torch.int64, device="cuda"), torch.ones(n, dtype=torch.int32, device="cuda")
+    s24.mask_flips(dev(a), dev(b), flips, per)
+    want = np.unpackbits((a ^ b).view(np.uint8).reshape(n, 2), axis=1).sum(1)
+    assert flips.item() == want.sum() and np.array_equal(per.cpu().numpy(), 1 + want.astype(np.int32))
+    s24.mask_flips(dev(a), dev(b), flips)
+    assert flips.item() == want.sum()
+
+
+def test_gated_backward_of_few_tokens_and_many_features_keeps_the_plain_products_bits(s24):
+    p, f, r = 13, 49152, 64                  # 192 large tiles of one row: the fused epilogue, and a plain product of few tokens
+    dY, Wd = si.random_matrix(120, (p, r), 1e-2, "bf16"), si.random_matrix(121, (r, f), 0.02, "bf16")
+    vt, mt = oracle.pack(*oracle.compress(Wd, oracle.transposable_mask(Wd))[2:])
+    GU = dev_bf16(si.random_matrix(122, (p, 2 * f), 1.0, "bf16"))
+    dH, dGU, two = torch.empty((p, f), dtype=torch.bfloat16, device="cuda"), torch.empty_like(GU), torch.empty_like(GU)
+    s24.spmm_bwd_dx_glu(dev_bf16(dY), dev_bf16(vt), dev(mt), GU, dGU, s24.GATE_SILU)
+    s24.spmm_bwd_dx(dev_bf16(dY), dev_bf16(vt), dev(mt), dH)
+    s24.glu_bwd(dH, GU, two, s24.GATE_SILU)
+    assert torch.equal(dGU.view(torch.int16), two.view(torch.int16))
