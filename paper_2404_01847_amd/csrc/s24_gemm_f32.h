@@ -1,6 +1,7 @@
 // fp32 matrix products of the library (s24_gemm_f32.hip), called by the GEMM entry points after their checks.
 #pragma once
 #include "s24_common.h"
+#include "s24_split.h"
 
 enum S24F32Epilogue { S24_F32_PLAIN, S24_F32_ACT, S24_F32_GLU };
 

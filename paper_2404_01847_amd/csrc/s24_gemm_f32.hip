@@ -80,7 +80,7 @@ __global__ __launch_bounds__(64 * KS * WM) void f32_nt_kernel(const NtArgs g)
             b[i] = g.B + (int64_t)min(n0 + 32 * i + l, g.N - 1) * g.K;
         }
         // units of 16 of k: lane half h takes k 8h .. 8h+7 of a unit
-        const int units = g.K / 16, u0 = units * ks / KS, u1 = units * (ks + 1) / KS;
+        const int units = g.K / 16, u0 = s24_slice_begin(units, ks, KS), u1 = s24_slice_begin(units, ks + 1, KS);
         struct Frag { float4 a[T][2]; float4 b[T][2]; uint32_t nib[T]; };
         auto load = [&](int u, Frag &f) {
             const int k = 16 * u + 8 * h;
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
     if constexpr (SPARSE) {
         // A compressed along the tokens: a lane reads one group (two kept values, one nibble) of its T rows and expands it;
         // lane half h takes every second group of four tokens
-        const int groups = g.T / 4, half = groups / 2, p0 = half * ks / KS, p1 = half * (ks + 1) / KS;   // T is a multiple of 64
+        const int groups = g.T / 4, half = groups / 2, p0 = s24_slice_begin(half, ks, KS), p1 = s24_slice_begin(half, ks + 1, KS);   // T is a multiple of 64
         for (int p = p0; p < p1; ++p) {
             const int gr = 2 * p + h;
             float e[T][4];
@@ -244,11 +244,11 @@ __global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
         }
     } else {
         constexpr int U = 8;   // token pairs loaded together
-        const int pairs = (g.T + 1) / 2, p0 = pairs * ks / KS, p1 = pairs * (ks + 1) / KS;
+        const int pairs = s24_token_pairs(g.T), p0 = s24_slice_begin(pairs, ks, KS), p1 = s24_slice_begin(pairs, ks + 1, KS);
         const float *a = g.A + mc, *x = g.X + nc;
         int p = p0;
         Run<T> av[U], xv[U];
-        for (; p + U <= p1 && 2 * (p + U) <= g.T; p += U) {
+        for (; p + U <= p1 && p + U <= g.T / 2; p += U) {   // (whole pairs)
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int64_t tok = 2 * (p + u) + h;

@@ -4,6 +4,7 @@ anything is launched.  No kernel runs here."""
 import ctypes as C
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -239,6 +240,31 @@ def test_gated_family_argument_errors(lib):
     assert lib.s24_transposable_mask(P, 2, 6, 8, 8, P, None, None) == SHAPE
     assert lib.s24_spmm_fwd(P, P, P, P, 0, 64, 16, 2, None) == OK
     assert lib.s24_mvue24(P, 2, 0, 16, 16, 1, None, None, None) == OK
+
+
+@pytest.fixture(scope="module")
+def plain_headers(tmp_path_factory):
+    """The headers of csrc/ that hold no HIP, behind C symbols."""
+    d = tmp_path_factory.mktemp("headers")
+    (d / "headers.cpp").write_text("""
+#include "s24_split.h"
+extern "C" int token_pairs(int t) { return s24_token_pairs(t); }
+extern "C" int slice_begin(int n, int s, int slices) { return s24_slice_begin(n, s, slices); }
+""")
+    so = str(d / "headers.so")
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2404_01847_amd", "csrc"), str(d / "headers.cpp"), "-o", so], check=True)
+    return C.CDLL(so)
+
+
+# up to the largest token count that the entry points take; eight slices, as the weight gradients have
+@pytest.mark.parametrize("tokens", [1, 2, 15, 16, 17, 4097, 2 ** 29 - 1, 2 ** 29, 2 ** 29 + 1, 2 ** 30 + 7, 2 ** 31 - 2, 2 ** 31 - 1])
+def test_slices_of_the_tokens_cover_each_pair_once(plain_headers, tokens):
+    pairs = plain_headers.token_pairs(tokens)
+    assert pairs == -(-tokens // 2)
+    bounds = [plain_headers.slice_begin(pairs, s, 8) for s in range(9)]
+    assert bounds == [pairs * s // 8 for s in range(9)]
+    assert bounds[0] == 0 and bounds[8] == pairs and 2 * (pairs - 1) < tokens
 
 
 def test_binding_refuses_to_run_without_library(monkeypatch, tmp_path):
