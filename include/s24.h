@@ -193,9 +193,11 @@ int s24_dense_dw_decay(const void *dY, const void *X, float *dW, const void *W, 
  * whole number of rounds by at most half a round, that excess is cut off as whole tile columns or rows of one
  * problem and run in small tiles.  `problems` is a HOST array of `count` <= 4 entries, read during the call:
  *   dY [p][r], X [p][q] (dtype dt), dW [r][q] fp32, W [r][q] (dtype dt) or NULL, mask [r/4][q/4] (with W), lambda.
- * Problems that are each too small for the large tile share one grid of smaller tiles in the same way.  Problems that
- * fit neither shared grid (fp32, no tokens, an empty output, small and large outputs mixed, decay on some but not
- * all) are run one after the other instead.  All problems are validated before the first launch. */
+ * Problems that are each too small for the large tile share one grid of smaller tiles in the same way, and so do fp32
+ * problems.  Problems that fit no shared grid (no tokens, an empty output, small and large outputs mixed, decay on some
+ * but not all, fp32 gradients that overlap a buffer of another problem, e.g. two that add to one dW) are run one after
+ * the other, in their order, instead.  16-bit problems of a shared grid must not overlap so.  All problems are validated
+ * before the first launch. */
 typedef struct {
     const void *dY;
     const void *X;

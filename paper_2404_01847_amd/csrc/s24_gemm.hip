@@ -23,6 +23,7 @@
 
 #include "s24_gemm_f32.h"
 #include "s24_gemm_slice.h"
+#include "s24_overlap.h"
 
 namespace {
 
@@ -1911,7 +1912,10 @@ extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, flo
             launch_dw_batch(batch, few, accum, decay, dt, st);
             return s24_launch_status();
         }
-        if (dt == S24_F32) {   // one grid for every problem with tokens to contract
+        // fp32: one grid for every problem with tokens to contract, unless the order of the problems counts (two of them
+        // adding to one gradient)
+        const bool together = dt == S24_F32 && !s24_dw_problems_overlap(problems, count, sizeof(float));
+        if (together) {
             S24F32TnProblem f[dmatn::kMaxBatch];
             int n = 0;
             bool rest = false;
@@ -1927,7 +1931,7 @@ extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, flo
         }
         for (int i = 0; i < count; ++i) {
             const s24_dw_problem &pr = problems[i];
-            if (pr.q * pr.r == 0 || (dt == S24_F32 && pr.p != 0)) continue;
+            if (pr.q * pr.r == 0 || (together && pr.p != 0)) continue;
             const int rc = run_dense_dw(pr.dY, pr.X, pr.dW, pr.p, pr.q, pr.r, beta, dt, pr.W, dt, pr.mask, pr.lambda, st);
             if (rc != S24_OK) return rc;
         }

@@ -91,6 +91,24 @@ def test_f32_weight_gradients(s24, case):
         assert_close(host_f64(c), ref, F32_TOL, f"spmm_dw {case}")
 
 
+def test_f32_weight_gradients_that_depend_on_their_order(s24):
+    """Two problems that add to one gradient, and one whose operand is another's gradient, act one after the other."""
+    p, q, r = 130, 48, 80
+    dY = [dev(si.random_matrix(56 + i, (p, r), 1e-2, "f32")) for i in range(2)]
+    X = [dev(si.random_matrix(58 + i, (p, q), 1.0, "f32")) for i in range(2)]
+    dZ, start = dev(si.random_matrix(60, (r, 32), 1.0, "f32")), dev(si.random_matrix(61, (r, q), 1e-3, "f32"))
+    sum_, chain = start.clone(), torch.zeros((32, q), device="cuda")
+    problems = [(dY[0], X[0], sum_, None, None, 0.0), (dY[1], X[1], sum_, None, None, 0.0), (dZ, sum_, chain, None, None, 0.0)]
+    s24.dense_dw_batch(problems, beta=1.0)
+    sum1, chain1 = start.clone(), torch.zeros((32, q), device="cuda")
+    for d, x, w in ((dY[0], X[0], sum1), (dY[1], X[1], sum1), (dZ, sum1, chain1)):
+        s24.dense_dw(d, x, w, beta=1.0)
+    assert torch.equal(sum_.view(torch.int32), sum1.view(torch.int32)) and torch.equal(chain.view(torch.int32), chain1.view(torch.int32))
+    ref = host_f64(start) + sum(host_f64(d).T @ host_f64(x) for d, x in zip(dY, X))
+    assert_close(host_f64(sum_), ref, F32_TOL, "two additions")
+    assert_close(host_f64(chain), host_f64(dZ).T @ ref, F32_TOL, "chained")
+
+
 # ------------------------------------------------------------------ mask search, compress and L1 gap by matrix size
 def _search_and_compress(s24, W):
     r, q = W.shape

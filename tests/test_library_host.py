@@ -247,7 +247,9 @@ def plain_headers(tmp_path_factory):
     """The headers of csrc/ that hold no HIP, behind C symbols."""
     d = tmp_path_factory.mktemp("headers")
     (d / "headers.cpp").write_text("""
+#include "s24_overlap.h"
 #include "s24_split.h"
+extern "C" int dw_overlap(const void *p, int n, int esize) { return s24_dw_problems_overlap((const s24_dw_problem *)p, n, esize); }
 extern "C" int token_pairs(int t) { return s24_token_pairs(t); }
 extern "C" int slice_begin(int n, int s, int slices) { return s24_slice_begin(n, s, slices); }
 """)
@@ -265,6 +267,27 @@ def test_slices_of_the_tokens_cover_each_pair_once(plain_headers, tokens):
     bounds = [plain_headers.slice_begin(pairs, s, 8) for s in range(9)]
     assert bounds == [pairs * s // 8 for s in range(9)]
     assert bounds[0] == 0 and bounds[8] == pairs and 2 * (pairs - 1) < tokens
+
+
+def test_overlapping_weight_gradients_are_found(plain_headers):
+    from paper_2404_01847_amd.binding import _DwProblem
+    step = 0x100000                          # distinct buffers, each larger than any used below
+    def problem(k, p=64, q=32, r=48, **other):
+        d = dict(dY=(8 * k + 1) * step, X=(8 * k + 2) * step, dW=(8 * k + 3) * step, W=(8 * k + 4) * step, mask=(8 * k + 5) * step)
+        d.update(other)
+        return _DwProblem(d["dY"], d["X"], d["dW"], d["W"], d["mask"], p, q, r, 1e-4)
+    def overlap(*problems):
+        return bool(plain_headers.dw_overlap((_DwProblem * len(problems))(*problems), len(problems), 4))
+    a = problem(0)
+    grad, cells = 3 * step, 48 * 32
+    assert not overlap(a) and not overlap(a, problem(1), problem(2), problem(3))
+    for name, size in (("dW", 4 * cells), ("X", 64 * 32 * 4), ("dY", 64 * 48 * 4), ("W", 4 * cells), ("mask", cells // 8)):
+        for at, hit in ((grad, True), (grad + 4 * cells - 16, True), (grad + 4 * cells, False), (grad - size + 16, True), (grad - size, False)):
+            assert overlap(a, problem(1, **{name: at})) == hit, (name, at)
+            assert overlap(problem(1, **{name: at}), problem(2), a) == hit, (name, at)
+    assert not overlap(a, problem(1, W=None, mask=grad))            # no decay: the mask is not read
+    assert not overlap(a, problem(1, r=0, dW=grad, X=grad))         # an empty output
+    assert not overlap(a, problem(1, p=0, X=grad, dY=grad)) and overlap(a, problem(1, p=0, dW=grad))
 
 
 def test_binding_refuses_to_run_without_library(monkeypatch, tmp_path):
