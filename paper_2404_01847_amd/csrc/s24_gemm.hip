@@ -1434,9 +1434,14 @@ inline NtTile sparse_dw_tile(int64_t M, int64_t N) { return cheapest_tile(M, N, 
 // Outputs that the gated backward epilogue serves: three quarters of the compute units have a large tile
 inline bool gated_bwd_fits(int64_t p, int64_t f) { return (int64_t)ceil_div(f, 256) * ceil_div(p, 256) >= 3 * s24_cu_count() / 4; }
 
+// Whether the input gradient of p tokens and q features, contraction r, runs in slices.  One rule for s24_spmm_bwd_dx and
+// s24_spmm_bwd_dx_act, whose bits agree; and neither does where s24_spmm_bwd_dx_glu takes its large tiles (possible at up to
+// 16 tokens from 48897 features on), so that all three sum in one order.
+inline bool bwd_dx_slices(int64_t p, int64_t r, int64_t q) { return !gated_bwd_fits(p, q) && s24_slice_pays(p, r, q); }
+
 // Out[N][M] = beta * Out + B[N][K] . A^T (+ bias[M], only with beta = 0)
 int launch_spmm(const void *B, const void *Av, const uint16_t *Am, void *Out, int64_t N, int64_t K, int64_t M, float beta,
-                int dt, hipStream_t st, const void *bias = nullptr, bool may_slice = true)
+                int dt, hipStream_t st, const void *bias, bool slices)
 {
     if (N == 0 || M == 0) return S24_OK;
     const bool accum = beta != 0.0f;
@@ -1447,7 +1452,7 @@ int launch_spmm(const void *B, const void *Av, const uint16_t *Am, void *Out, in
     auto *b = static_cast<const uint16_t *>(B), *av = static_cast<const uint16_t *>(Av), *d = static_cast<const uint16_t *>(bias);
     auto *o = static_cast<uint16_t *>(Out);
     S24_REQUIRE((int64_t)ceil_div(M, 128) * ceil_div(N, 128) < (1ll << 30), S24_ERR_SHAPE);
-    if (may_slice && s24_slice_pays(N, K, M)) return s24_slice_nt({b, av, Am, o, nullptr, nullptr, d, N, K, M, accum, S24_SLICE_PLAIN, 0}, dt, st);
+    if (slices) return s24_slice_nt({b, av, Am, o, nullptr, nullptr, d, N, K, M, accum, S24_SLICE_PLAIN, 0}, dt, st);
     const NtTile tile = nt_tile_or_slab(M, N, K);
     if (tile.slab != 0) {
         const int rc = launch_spmm(B, Av, Am, Out, tile.slab, K, M, beta, dt, st, bias, false);
@@ -1485,7 +1490,7 @@ extern "C" int s24_spmm_fwd_bias(const void *X, const void *vals, const uint16_t
     if (rc != S24_OK || p * r == 0) return rc;
     S24_REQUIRE(meta != nullptr, S24_ERR_NULL);
     S24_REQUIRE(s24_aligned(meta, 4) && s24_aligned(bias, 8), S24_ERR_ALIGN);
-    return launch_spmm(X, vals, meta, Y, p, q, r, 0.0f, dt, static_cast<hipStream_t>(stream), bias);
+    return launch_spmm(X, vals, meta, Y, p, q, r, 0.0f, dt, static_cast<hipStream_t>(stream), bias, s24_slice_pays(p, q, r));
 }
 
 extern "C" int s24_spmm_bwd_dx(const void *dY, const void *valsT, const uint16_t *metaT, void *dX, int64_t p, int64_t q,
@@ -1497,8 +1502,7 @@ extern "C" int s24_spmm_bwd_dx(const void *dY, const void *valsT, const uint16_t
     if (rc != S24_OK || p * q == 0) return rc;
     S24_REQUIRE(metaT != nullptr, S24_ERR_NULL);
     S24_REQUIRE(s24_aligned(metaT, 4), S24_ERR_ALIGN);
-    // where s24_spmm_bwd_dx_glu takes its large tiles, the plain product sums in the same order: same bits
-    return launch_spmm(dY, valsT, metaT, dX, p, r, q, beta, dt, static_cast<hipStream_t>(stream), nullptr, !gated_bwd_fits(p, q));
+    return launch_spmm(dY, valsT, metaT, dX, p, r, q, beta, dt, static_cast<hipStream_t>(stream), nullptr, bwd_dx_slices(p, r, q));
 }
 
 extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t *meta, const void *bias, void *GU, void *H,
@@ -1543,7 +1547,7 @@ extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t 
         return s24_f32_nt({static_cast<const float *>(X), static_cast<const float *>(vals), meta, static_cast<float *>(GU), static_cast<float *>(H),
                            static_cast<const float *>(bias), p, q, 2 * f, false, S24_F32_GLU, gate}, st);
     // shapes the fused epilogue does not cover: the GEMM into [p][2f], then the stand-alone activation on its halves
-    const int rc2 = launch_spmm(X, vals, meta, GU, p, q, 2 * f, 0.0f, dt, st, bias);
+    const int rc2 = launch_spmm(X, vals, meta, GU, p, q, 2 * f, 0.0f, dt, st, bias, false);
     if (rc2 != S24_OK) return rc2;
     return s24_glu_fwd(GU, S24_ROW_MAJOR, 2 * f, H, S24_ROW_MAJOR, f, p, f, gate, dt, st);
 }
@@ -1635,7 +1639,7 @@ extern "C" int s24_spmm_bwd_dx_act(const void *dY, const void *valsT, const uint
     S24_REQUIRE(s24_aligned(metaT, 4) && s24_aligned(Z, 16), S24_ERR_ALIGN);
     // the 16-bit kernels carry this epilogue; fp32 takes s24_spmm_bwd_dx + s24_act_bwd
     S24_REQUIRE(dt != S24_F32, S24_ERR_UNSUPPORTED);
-    if (s24_slice_pays(p, r, f))
+    if (bwd_dx_slices(p, r, f))
         return s24_slice_nt({static_cast<const uint16_t *>(dY), static_cast<const uint16_t *>(valsT), metaT, static_cast<uint16_t *>(dZ), nullptr,
                              static_cast<const uint16_t *>(Z), nullptr, p, r, f, false, S24_SLICE_ACT_BWD, act}, dt, static_cast<hipStream_t>(stream));
     const NtTile tile = nt_tile(f, p, r);

@@ -344,3 +344,24 @@ def test_gated_backward_of_few_tokens_and_many_features_keeps_the_plain_products
     s24.spmm_bwd_dx(dev_bf16(dY), dev_bf16(vt), dev(mt), dH)
     s24.glu_bwd(dH, GU, two, s24.GATE_SILU)
     assert torch.equal(dGU.view(torch.int16), two.view(torch.int16))
+
+
+def test_backward_of_few_tokens_and_many_features_keeps_the_plain_products_bits(s24):
+    # 192 large tiles of one row: the fused gated epilogue takes them, at a token count that the slices are for; ten chunks,
+    # so that the slices would sum in another order
+    p, f, r = 13, 49152, 640
+    dY, Wd = si.random_matrix(120, (p, r), 1e-2, "bf16"), si.random_matrix(121, (r, f), 0.02, "bf16")
+    vt, mt = oracle.pack(*oracle.compress(Wd, oracle.transposable_mask(Wd))[2:])
+    dY, vt, mt = dev_bf16(dY), dev_bf16(vt), dev(mt)
+    GU = dev_bf16(si.random_matrix(122, (p, 2 * f), 1.0, "bf16"))
+    dH, dGU, two = torch.empty((p, f), dtype=torch.bfloat16, device="cuda"), torch.empty_like(GU), torch.empty_like(GU)
+    s24.spmm_bwd_dx(dY, vt, mt, dH)
+    s24.spmm_bwd_dx_glu(dY, vt, mt, GU, dGU, s24.GATE_SILU)
+    s24.glu_bwd(dH, GU, two, s24.GATE_SILU)
+    assert torch.equal(dGU.view(torch.int16), two.view(torch.int16))
+    Z = GU[:, :f].contiguous()
+    dZ, two = torch.empty_like(Z), torch.empty_like(Z)
+    for act in (s24.ACT_RELU, s24.ACT_GELU_ERF):
+        s24.spmm_bwd_dx_act(dY, vt, mt, Z, dZ, act)
+        s24.act_bwd(dH, Z, two, act)
+        assert torch.equal(dZ.view(torch.int16), two.view(torch.int16))
