@@ -265,11 +265,10 @@ __global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
         for (; p < p1; ++p) {   // rest of the slice; the token past an odd count contributes zero
             const int tok = 2 * p + h;
             const int64_t tc = min(tok, g.T - 1);
-            Run<T> av1 = *reinterpret_cast<const Run<T> *>(a + tc * M);
-            const Run<T> xv1 = *reinterpret_cast<const Run<T> *>(x + tc * N);
+            Run<T> av1 = *reinterpret_cast<const Run<T> *>(a + tc * M), xv1 = *reinterpret_cast<const Run<T> *>(x + tc * N);
 #pragma unroll
-            for (int i = 0; i < T; ++i)
-                if (tok >= g.T) av1.v[i] = 0.0f;
+            for (int i = 0; i < T; ++i)   // both operands: zero times an infinity of the repeated last token would be NaN
+                if (tok >= g.T) av1.v[i] = xv1.v[i] = 0.0f;
 #pragma unroll
             for (int i = 0; i < T; ++i)
 #pragma unroll

@@ -91,6 +91,18 @@ def test_f32_weight_gradients(s24, case):
         assert_close(host_f64(c), ref, F32_TOL, f"spmm_dw {case}")
 
 
+@pytest.mark.parametrize("p,q,r", [(7, 48, 80), (129, 48, 80), (131, 1552, 2064)])
+def test_f32_weight_gradient_of_an_odd_token_count_with_an_infinity_in_the_last_token(s24, p, q, r):
+    dY, X = si.random_matrix(150, (p, r), 1e-2, "f32"), si.random_matrix(151, (p, q), 1.0, "f32")
+    X[p - 1, 5] = np.inf
+    dW = torch.zeros((r, q), device="cuda")
+    s24.dense_dw(dev(dY), dev(X), dW)
+    got = dW.cpu().numpy()
+    assert np.array_equal(got[:, 5], np.copysign(np.float32(np.inf), dY[p - 1]))    # dY has no zero
+    rest = np.arange(q) != 5
+    assert_close(got[:, rest].astype(np.float64), dY.astype(np.float64).T @ X[:, rest].astype(np.float64), F32_TOL)
+
+
 def test_f32_weight_gradients_that_depend_on_their_order(s24):
     """Two problems that add to one gradient, and one whose operand is another's gradient, act one after the other."""
     p, q, r = 130, 48, 80
