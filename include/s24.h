@@ -38,7 +38,9 @@
  *   dtypes       S24_BF16 buffers hold raw bfloat16, S24_F16 buffers IEEE binary16 (the paper trains in fp16
  *                mixed precision, Sec. 6), S24_F32 buffers float.  Both 16-bit types run the same kernels on
  *                the matrix cores (fp32 accumulation, one rounding to the storage type); S24_F32 runs fp32
- *                matrix-core kernels (no fp32 sparse instruction exists: pruned elements are multiplied as zeros).  binary16 results overflow to infinity like any IEEE
+ *                matrix-core kernels (no fp32 sparse instruction exists: the compressed operand is expanded in
+ *                registers).  A pruned element never reaches a result in any type, whatever stands beside it in
+ *                the other operand.  binary16 results overflow to infinity like any IEEE
  *                conversion: scaling the loss is the caller's business.
  *   layouts      a logical [p][n] activation matrix is S24_ROW_MAJOR (element (t, c) at t*ld + c) or
  *                S24_COL_MAJOR (at c*ld + t, the layout the paper's sparse GEMMs emit, App. A.2).  The GEMMs of

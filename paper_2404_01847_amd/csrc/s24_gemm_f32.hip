@@ -1,6 +1,6 @@
 // fp32 GEMMs on the matrix cores: v_mfma_f32_32x32x2_f32 (one lane holds A row l%32 and B column l%32 at k = l/32;
 // accumulator i is row 8*(i/4) + 4*(l/32) + i%4 of column l%32).  There is no fp32 sparse instruction: the compressed
-// operand is expanded to its four columns per group in registers, zeros included.
+// operand is expanded to its four columns per group in registers, zeros included (and see kept_sum).
 //
 // What bounds them is latency, not arithmetic: the fp32 layers are small (512 x 256 x 1024 has 0.27 GFLOP per product,
 // 1.7 us of the unit's 157 TFLOP/s), so the whole product has to be spread over every SIMD of the chip at once.  Each
@@ -23,6 +23,23 @@ __device__ __forceinline__ void expand(float v0, float v1, uint32_t nib, float (
     const uint32_t i0 = nib & 3u, i1 = nib >> 2;
 #pragma unroll
     for (uint32_t i = 0; i < 4; ++i) e[i] = i0 == i ? v0 : (i1 == i ? v1 : 0.0f);
+}
+
+// The sum over the kept elements alone: row m of the compressed operand against x[k * stride].  A pruned element is
+// multiplied as a zero above, which makes NaN of an infinity or a NaN beside it; an output that is NaN is therefore taken
+// again from here, so that, as on the 16-bit sparse instruction, what is pruned never reaches a result.
+__device__ __forceinline__ float kept_sum(const float *Av, const uint16_t *Am, int64_t M, int64_t m, int K, const float *x, int64_t stride)
+{
+    float sum = 0.0f;
+#pragma unroll 1
+    for (int gr = 0; gr < K / 4; ++gr, x += 4 * stride) {
+        const int64_t cr = (int64_t)(gr >> 4) * M + m;
+        const float2 v = *reinterpret_cast<const float2 *>(Av + cr * 32 + 2 * (gr & 15));
+        const uint32_t nib = ((uint32_t)Am[cr * 4 + ((gr & 15) >> 2)] >> (4 * (gr & 3))) & 0xFu;
+        sum = fmaf(v.x, x[(nib & 3u) * stride], sum);
+        sum = fmaf(v.y, x[(nib >> 2) * stride], sum);
+    }
+    return sum;
 }
 
 // Sum of one float4 over the KS slices' copies of a tile, in slice order.  Slice s of a workgroup's tile w is parked at
@@ -153,6 +170,13 @@ __global__ __launch_bounds__(64 * KS * WM) void f32_nt_kernel(const NtArgs g)
         const float *p = s_red + w * KS * SLICE + row * PITCH + 4 * q;
         auto finish = [&](const float *src, int feature) {
             float4 v = slice_sum<KS>(src, SLICE);
+            if constexpr (SPARSE) {
+                const float *x = g.B + (int64_t)n * g.K;
+                if (v.x != v.x) v.x = kept_sum(g.Av, g.Am, g.M, feature, g.K, x, 1);
+                if (v.y != v.y) v.y = kept_sum(g.Av, g.Am, g.M, feature + 1, g.K, x, 1);
+                if (v.z != v.z) v.z = kept_sum(g.Av, g.Am, g.M, feature + 2, g.K, x, 1);
+                if (v.w != v.w) v.w = kept_sum(g.Av, g.Am, g.M, feature + 3, g.K, x, 1);
+            }
             if (g.bias != nullptr) {
                 const float2 b0 = *reinterpret_cast<const float2 *>(g.bias + feature), b1 = *reinterpret_cast<const float2 *>(g.bias + feature + 2);
                 v.x += b0.x; v.y += b0.y; v.z += b1.x; v.w += b1.y;
@@ -294,6 +318,12 @@ __global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
         const int q = it % QUADS, row = it / QUADS, m = m0 + row, n = n0 + 4 * q;
         if (m >= M || n >= N) continue;
         float4 v = slice_sum<KS>(s_red + row * PITCH + 4 * q, SLICE);
+        if constexpr (SPARSE) {
+            if (v.x != v.x) v.x = kept_sum(g.A, g.Am, M, m, g.T, g.X + n, N);
+            if (v.y != v.y) v.y = kept_sum(g.A, g.Am, M, m, g.T, g.X + n + 1, N);
+            if (v.z != v.z) v.z = kept_sum(g.A, g.Am, M, m, g.T, g.X + n + 2, N);
+            if (v.w != v.w) v.w = kept_sum(g.A, g.Am, M, m, g.T, g.X + n + 3, N);
+        }
         float4 *o = reinterpret_cast<float4 *>(g.dW + (int64_t)m * N + n);
         if (ACCUM) {
             const float4 old = *o;

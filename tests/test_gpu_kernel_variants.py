@@ -121,6 +121,63 @@ def test_f32_weight_gradients_that_depend_on_their_order(s24):
     assert_close(host_f64(chain), host_f64(dZ).T @ ref, F32_TOL, "chained")
 
 
+# ------------------------------------------------------------------ infinities and NaNs beside pruned elements
+def _cells(mask, shape):
+    i, j = np.indices(shape)
+    return ((mask[i // 4, j // 4] >> (4 * (i % 4) + j % 4)) & 1).astype(bool)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+# fp32: four slices of a 32-tile, eight, four of a 64-tile; 16-bit: slices and the 256 x 128 tile
+@pytest.mark.parametrize("pqr", [(33, 128, 96), (40, 576, 160), (1057, 192, 2016)])
+def test_pruned_elements_never_reach_a_product(s24, dtype, pqr):
+    p, q, r = pqr
+    r64 = (r + 63) // 64 * 64
+    W, X = si.random_matrix(130 + r, (r64, q), 0.02, dtype), si.random_matrix(131, (p, q), 1.0, dtype)
+    mask = oracle.transposable_mask(W)
+    v, m = oracle.pack(*(np.ascontiguousarray(a[:r]) for a in oracle.compress(W, mask)[:2]))
+    kept = np.where(_cells(mask, W.shape)[:r], si.to_f32(W)[:r], 0).astype(np.float64)
+    x = dev_bf16(X).clone()
+    clean, hit = x.clone(), np.zeros((p, r), bool)
+    for t, k, value in ((3, 17, np.inf), (7, 64, np.nan), (8, 100, -np.inf), (p - 1, q - 1, np.inf)):
+        x[t, k], clean[t, k] = value, 0
+        hit[t] |= kept[:, k] != 0
+    ref, (v, m) = host_f64(clean) @ kept.T, (dev_bf16(v), dev(m))
+    new = lambda n: torch.full((p, n), 1.0, dtype=torch_dtype(dtype), device="cuda")
+    Y, Z, H, GU, Hg, dX = new(r), new(r), new(r), new(r), new(r // 2), new(r)
+    s24.spmm_fwd(x, v, m, Y)
+    s24.spmm_fwd_act(x, v, m, None, Z, H, s24.ACT_RELU)
+    s24.spmm_fwd_glu(x, v, m, None, GU, Hg, s24.GATE_SILU)
+    s24.spmm_bwd_dx(x, v, m, dX, beta=1.0)
+    for got, want, what in ((Y, ref, "fwd"), (Z, ref, "act"), (GU, ref, "glu"), (dX, ref + 1, "accumulate")):
+        got = host_f64(got)
+        assert np.array_equal(~np.isfinite(got), hit), what
+        assert_close(np.where(hit, 0, got), np.where(hit, 0, want), tol_for(dtype), what)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("p,q,r", [(192, 48, 80), (64, 1552, 2064)])
+def test_pruned_tokens_never_reach_a_weight_gradient(s24, dtype, p, q, r):
+    dY, X = si.random_matrix(140, (p, r), 1e-2, dtype), si.random_matrix(141, (p, q), 1.0, dtype)
+    vz, mz = oracle.mvue24(dY, 99)
+    kept = np.zeros((r, p), bool)
+    for g in range(p // 4):
+        nib = (mz[:, g // 4].astype(np.uint32) >> (4 * (g % 4))) & 15
+        kept[np.arange(r), 4 * g + (nib & 3)] = kept[np.arange(r), 4 * g + (nib >> 2)] = True
+    v, m = oracle.pack(vz, mz)
+    x, hit = dev_bf16(X).clone(), np.zeros((r, q), bool)
+    clean = x.clone()
+    for t, n, value in ((3, 17, np.inf), (50, 40, np.nan), (p - 1, q - 1, -np.inf)):
+        x[t, n], clean[t, n] = value, 0
+        hit[:, n] |= kept[:, t]
+    got, want = torch.zeros((r, q), device="cuda"), torch.zeros((r, q), device="cuda")
+    s24.spmm_dw(dev_bf16(v), dev(m), x, got)
+    s24.spmm_dw(dev_bf16(v), dev(m), clean, want)
+    got, want = host_f64(got), host_f64(want)
+    assert np.array_equal(~np.isfinite(got), hit)
+    assert_close(np.where(hit, 0, got), np.where(hit, 0, want), F32_TOL)
+
+
 # ------------------------------------------------------------------ mask search, compress and L1 gap by matrix size
 def _search_and_compress(s24, W):
     r, q = W.shape
