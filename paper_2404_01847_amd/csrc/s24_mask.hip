@@ -936,7 +936,7 @@ __global__ __launch_bounds__(256) void mask_flips_kernel(const uint16_t *__restr
 // by the top rows, column shared by the bottom rows) two crossings in either half (48).  About 260 fp64 operations where
 // the 90 sums one by one took 4300 with their selects (bf16 5120 x 1280: 80 -> 9 us).  Sums are exact in any order as
 // long as the block spans at most WIDE binades; a wider block takes the 90 sums one by one in index order, which is
-// what fixes its rounding.
+// what fixes its rounding, and so does one with an infinity or a NaN, which minima and maxima would drop.
 struct Top2 {
     double first, second;
     __device__ __forceinline__ void merge(double f, double s)   // f >= s
@@ -977,7 +977,7 @@ __global__ __launch_bounds__(256) void l1_gap_kernel(const T *__restrict__ W, in
     for (int t = 0; t < 16; ++t) a[t / 4][t % 4] = (double)__uint_as_float(mag[t]);
     const uint32_t emax = max(mx >> 23, 1u), emin = mn == 0xFFFFFFFFu ? 255u : max(mn >> 23, 1u);
     double first = 0.0, second = 0.0;
-    if (emin + Ops::kWide < emax) {
+    if (emin + Ops::kWide < emax || emax == 255u) {
 #pragma unroll 1
         for (int k = 0; k < S24_NUM_PATTERNS; ++k) {
             const unsigned m = g_patterns.mask[k];

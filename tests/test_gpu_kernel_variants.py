@@ -239,6 +239,38 @@ def test_l1_norm_gap_by_classes(s24, dtype, kind):
     assert np.all(np.abs(got - ref)[~exact] <= 16 * 2.0 ** -53 * a.sum(-1)[~exact])
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+def test_l1_norm_gap_of_infinities_and_nans(s24, dtype, legal_blocks):
+    """The gap is what best and second best of the 90 sums give when they are compared one by one, also where a block holds
+    nothing but NaNs (a weight that has diverged must not look like one whose patterns tie)."""
+    w = dev_bf16(si.random_matrix(160, (32, 512), 0.02, dtype)).clone()
+    nan, inf = float("nan"), float("inf")
+    w[0:4, 0:4], w[0:4, 4:8], w[4, 0] = nan, inf, nan
+    w[8:12, 0:4], w[8:12, 4:8] = 3e4, 3e4
+    w[9, 2], w[9, 5] = nan, inf
+    w[12:16, 8:12], w[13, 9] = nan, 1.0
+    if dtype != "f16":
+        w[16:20, 0:4], w[16:20, 4:8] = 2.0 ** 127, 2.0 ** 127
+        w[17, 1], w[17, 6] = nan, inf
+    gap = torch.full((8, 128), -1.0, dtype=torch.float64, device="cuda")
+    s24.l1_norm_gap(w, gap)
+    a = np.abs(host_f64(w)).reshape(8, 4, 128, 4).transpose(0, 2, 1, 3).reshape(8, 128, 16)
+    want = np.empty((8, 128))
+    with np.errstate(invalid="ignore"):
+        for at in np.ndindex(8, 128):
+            sums = [sum(a[at][t] for t in range(16) if (m >> t) & 1) for m in legal_blocks]
+            first, second = sums[0], 0.0
+            for k, v in enumerate(sums[1:], 1):
+                if v > first:
+                    first, second = v, first
+                elif k == 1 or v > second:
+                    second = v
+            want[at] = first - second
+    got = gap.cpu().numpy()
+    assert np.isnan(want[0, :2]).all() and np.isnan(want).sum() < 10
+    assert np.array_equal(got, want, equal_nan=True)
+
+
 # ------------------------------------------------------------------ sparse products on the 256 x 128 tile
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 # (p, q, r): one, two, three and four chunks of the ring, ragged in both directions (136 tiles); a strip of such tiles
