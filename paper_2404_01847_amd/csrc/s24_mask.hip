@@ -293,6 +293,7 @@ __device__ __forceinline__ unsigned wave_mid_best_pattern(const uint32_t (&mag)[
         best += ((pm >> t) & 1u) ? a : 0.0;
         second += ((pm2 >> t) & 1u) ? a : 0.0;
     }
+    best = __builtin_fmax(best, -1.0);   // a pattern whose sum is NaN never wins, as in the one-lane walk
     if (second > best) {
         best = second;
         id = other_id;

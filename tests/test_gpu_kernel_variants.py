@@ -221,6 +221,21 @@ def test_wide_blocks_in_both_tile_shapes(s24, dtype, kind, rq):
     assert np.array_equal(host_bits(alone), mask) and np.array_equal(host_bits(fused), mask)
 
 
+def test_f32_search_beside_infinities_and_nans(s24, legal_blocks):
+    """Blocks of values above 2^102 with an infinity or a NaN go through the fp64 sums: patterns that hold a NaN never win, and
+    the first of the largest does, wherever in the wave the block lies."""
+    W = si.random_matrix(170, (64, 256), 2.0 ** 110, "f32")
+    W = np.where(np.abs(W) < 2.0 ** 104, 2.0 ** 104, W).astype(np.float32)
+    for n in range(16):
+        W[4 * (n % 4) + n // 4, 8 * n + (5 * n) % 8] = np.nan if n % 3 else np.inf
+    a = np.abs(W).astype(np.float64).reshape(16, 4, 64, 4).transpose(0, 2, 1, 3).reshape(16, 64, 1, 16)
+    legal = np.array([[(m >> t) & 1 for t in range(16)] for m in legal_blocks], bool)
+    sums = np.where(legal, a, 0).sum(-1)
+    want = np.array(legal_blocks, np.uint16)[np.where(np.isnan(sums), -1, sums).argmax(-1)]
+    alone, fused, _, _ = _search_and_compress(s24, W)
+    assert np.array_equal(host_bits(alone), want) and np.array_equal(host_bits(fused), want)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
 @pytest.mark.parametrize("kind", ["few", "equal", "zeros", "tiny", "window", "normal"])
 def test_l1_norm_gap_by_classes(s24, dtype, kind):
