@@ -17,6 +17,20 @@ static inline bool s24_valid_gate(int g) { return g == S24_GATE_SILU || g == S24
 static inline bool s24_valid_layout(int l) { return l == S24_ROW_MAJOR || l == S24_COL_MAJOR; }
 static inline size_t s24_elem_size(int dt) { return dt == S24_F32 ? 4 : 2; }
 
+// Compute units of the current device, read once (256 on MI355X; that figure also stands in where no device
+// answers, so that the host-side checks behave the same without a GPU).
+inline int s24_cu_count()
+{
+    static const int n = [] {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
+            return v;
+        return 256;
+    }();
+    return n;
+}
+
 // Call after a kernel launch: turns a refused launch into S24_ERR_LAUNCH.
 static inline int s24_launch_status() { return hipGetLastError() == hipSuccess ? S24_OK : S24_ERR_LAUNCH; }
 

@@ -1349,20 +1349,6 @@ int check_gemm(const void *a, const void *b, const void *c, int64_t p, int64_t q
         }                                 \
     } while (0)
 
-// Compute units of the current device, read once (256 on MI355X; that figure also stands in where no device
-// answers, so that the host-side checks behave the same without a GPU).
-inline int s24_cu_count()
-{
-    static const int n = [] {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-            return v;
-        return 256;
-    }();
-    return n;
-}
-
 // Which tile a sparse NT product takes.  Costs in full rounds of the large tile at the same depth, measured over 128-16384
 // tokens, 256-4096 x 1024-22016 features (us per 64 of k at K = 5504 to 11008: large 0.75 with every compute unit busy and
 // 0.55 with few; medium 0.52 and 0.37; small 0.62 with two workgroups per compute unit, 0.32 with one, 0.28 with few):

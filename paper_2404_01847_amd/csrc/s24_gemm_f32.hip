@@ -363,13 +363,14 @@ int launch_nt(const S24F32Nt &g, hipStream_t st)
 // The 64-tile reads half the operand bytes per product, which only counts once its own grid fills the chip.
 template <bool SPARSE, bool ACCUM, int EPI, int ACT> int choose_nt(const S24F32Nt &g, hipStream_t st)
 {
-    const bool deep = g.K >= 512 && ceil_div(g.M, 32) * ceil_div(g.N, 32) <= 256;   // few tiles, long sums: 8 slices
+    const int64_t cus = s24_cu_count();
+    const bool deep = g.K >= 512 && ceil_div(g.M, 32) * ceil_div(g.N, 32) <= cus;   // few tiles, long sums: 8 slices
     if constexpr (EPI == S24_F32_GLU) {
         if (deep) return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 8, 1>(g, st);
         return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 4, 1>(g, st);
     } else {
         if (deep) return launch_nt<SPARSE, ACCUM, EPI, ACT, 1, 8, 1>(g, st);
-        if (ceil_div(g.M, 64) * ceil_div(g.N, 64) < 512) return launch_nt<SPARSE, ACCUM, EPI, ACT, 1, 4, 1>(g, st);
+        if (ceil_div(g.M, 64) * ceil_div(g.N, 64) < 2 * cus) return launch_nt<SPARSE, ACCUM, EPI, ACT, 1, 4, 1>(g, st);
         return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 4, 1>(g, st);
     }
 }
@@ -403,7 +404,7 @@ int s24_f32_tn(const S24F32TnProblem *pr, int count, bool accum, hipStream_t st)
     TnArgs a{};
     for (int T = 1; T <= 2; ++T)
         for (int i = 0; i < count; ++i) tiles[T - 1] += ceil_div(pr[i].M, 32 * T) * ceil_div(pr[i].N, 32 * T);
-    const int T = tiles[1] < 768 ? 1 : 2;
+    const int T = tiles[1] < 3 * s24_cu_count() ? 1 : 2;
     S24_REQUIRE(tiles[T - 1] < (1ll << 31), S24_ERR_SHAPE);
     int64_t first = 0;
     for (int i = 0; i < kMaxTn; ++i) {

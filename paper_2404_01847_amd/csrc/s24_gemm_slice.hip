@@ -238,10 +238,11 @@ struct Plan { int tm, tn; double us; int64_t rounds; };
 Plan plan(int64_t N, int64_t K, int64_t M)
 {
     constexpr Plan tiles[4] = {{1, 1, 0.085, 0}, {2, 1, 0.11, 0}, {4, 1, 0.15, 0}, {4, 2, 0.19, 0}};
+    const int64_t cus = s24_cu_count();
     Plan best{0, 0, 0.0, 0};
     for (const Plan &t : tiles) {
         if (N <= 16 && t.tn > 1) continue;
-        const int64_t n = ((M + 16 * t.tm - 1) / (16 * t.tm)) * ((N + 16 * t.tn - 1) / (16 * t.tn)), rounds = (n + 255) / 256;
+        const int64_t n = ((M + 16 * t.tm - 1) / (16 * t.tm)) * ((N + 16 * t.tn - 1) / (16 * t.tn)), rounds = (n + cus - 1) / cus;
         const double us = 3.4 + t.us * (double)rounds * (double)(K / 64);
         if (best.tm == 0 || us < best.us) best = {t.tm, t.tn, us, rounds};
     }
@@ -256,7 +257,7 @@ Plan plan(int64_t N, int64_t K, int64_t M)
 bool s24_slice_pays(int64_t N, int64_t K, int64_t M)
 {
     if (N <= 16) return true;
-    if (((M + 127) / 128) * ((N + 127) / 128) > 256) return false;
+    if (((M + 127) / 128) * ((N + 127) / 128) > s24_cu_count()) return false;
     const Plan p = plan(N, K, M);
     return p.rounds <= 2 && p.us < 0.95 * (6.2 + 0.22 * (double)(K / 64));
 }

@@ -850,7 +850,7 @@ int launch_tiles(const T *W, int64_t ldw, int br, int bq, const uint16_t *mask_i
                        index_out, vals, meta, valsT, metaT);
     return s24_launch_status();
 }
-// Which tile, by the number of 32 x 32 tiles (measured in us; 32 x 32 / 32 x 16 / 16 x 16 blocks):
+// Which tile, by the number of 32 x 32 tiles in compute units (256 of them; measured in us; 32 x 32 / 32 x 16 / 16 x 16 blocks):
 //   bf16 search + compress   144 tiles (3072 x 768): 8.2 / 7.4 / 6.5    400 (5120 x 1280): 12.2 / 11.7 / 12.4    5504: 87 / 99 / 115
 //   bf16 given mask          144: 7.7 / 6.2 / 5.4    400: 10.8 / 10.0 / 9.3    1376 (11008 x 2048): 28.1 / 24.8 / 25.5    5504: 82 / 83 / 89
 //   fp32 search + compress   16 (1024 x 256): 18.5 / 11.6 / 7.8    400: 33.9 / 31.3 / 29.4    5504: 258 / 254 / 258
@@ -858,9 +858,10 @@ template <typename T, bool SEARCH, bool COMPRESS, typename... Args>
 int launch_sized(const T *W, int64_t ldw, int br, int bq, Args... args)
 {
     const int64_t tiles = (int64_t)((bq + 31) / 32) * ((br + 31) / 32);
-    if (tiles < (SEARCH && sizeof(T) == 2 ? 300 : 512)) return launch_tiles<T, SEARCH, COMPRESS, 16, 1>(W, ldw, br, bq, args...);
+    const int64_t cus = s24_cu_count();
+    if (tiles < (SEARCH && sizeof(T) == 2 ? 75 * cus / 64 : 2 * cus)) return launch_tiles<T, SEARCH, COMPRESS, 16, 1>(W, ldw, br, bq, args...);
     if constexpr (!SEARCH && sizeof(T) == 2)
-        if (tiles < 4096) return launch_tiles<T, SEARCH, COMPRESS, 32, 2>(W, ldw, br, bq, args...);
+        if (tiles < 16 * cus) return launch_tiles<T, SEARCH, COMPRESS, 32, 2>(W, ldw, br, bq, args...);
     return launch_tiles<T, SEARCH, COMPRESS, 32, 4>(W, ldw, br, bq, args...);
 }
 
