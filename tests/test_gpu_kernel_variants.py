@@ -437,8 +437,9 @@ def test_sparse_weight_gradient_tiles(s24, dtype, rq, p, beta):
     assert torch.equal(decayed.view(torch.int32), two.view(torch.int32))
 
 
-# one lane, a vector and a remainder, the four-vector pass and what it leaves, more vectors than 256 workgroups take in one pass
-@pytest.mark.parametrize("n", [1, 7, 8, 8193, 32768, 40970, 2097152 + 8 * 300 + 5])
+# one lane, a vector and a remainder, the four-vector pass and what it leaves, more vectors than 256 workgroups take in one
+# pass, and with per-block counts more than they take in eight
+@pytest.mark.parametrize("n", [1, 7, 8, 8193, 32768, 40970, 2097152 + 8 * 300 + 5, 4194304 + 21])
 def test_mask_flips_by_size(s24, n):
     rng = np.random.default_rng(n)
     a, b = rng.integers(0, 65536, n).astype(np.uint16), rng.integers(0, 65536, n).astype(np.uint16)
