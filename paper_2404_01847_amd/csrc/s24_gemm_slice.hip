@@ -252,12 +252,16 @@ Plan plan(int64_t N, int64_t K, int64_t M)
 }  // namespace
 
 // The alternative is the 128 x 128 tile, 0.22 us per 64 of k on top of 6.2 while each compute unit has at most one (with more,
-// its output fills the chip).  Up to 16 tokens it multiplies seven eighths of nothing; there the slices were never slower.
+// its output fills the chip).  Up to 16 tokens it multiplies seven eighths of nothing, and the slices are faster up to 32768
+// features (16 tokens x 16384, K = 4096, cold weights: 28 -> 16 us) and mostly beyond (98304: 86 -> 83).  Not where the tiles
+// are nearly two per compute unit and the contraction is long, so that they too keep the memory busy: 50304 x K = 4096:
+// slices 50, tiles 41; 65536: 62 and 51; 50304 x 2048: 27 and 23, but x 768: 12.3 and 13.1.
 // More than two rounds of sliced tiles cost more than the model says (4096 tokens x 1024, K = 256: 13.7 against 10.6 us).
 bool s24_slice_pays(int64_t N, int64_t K, int64_t M)
 {
-    if (N <= 16) return true;
-    if (((M + 127) / 128) * ((N + 127) / 128) > s24_cu_count()) return false;
+    const int64_t cus = s24_cu_count(), tiles = ((M + 127) / 128) * ((N + 127) / 128);
+    if (N <= 16) return !(K >= 2048 && 2 * tiles >= 3 * cus && tiles <= 2 * cus);
+    if (tiles > cus) return false;
     const Plan p = plan(N, K, M);
     return p.rounds <= 2 && p.us < 0.95 * (6.2 + 0.22 * (double)(K / 64));
 }

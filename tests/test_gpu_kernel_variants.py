@@ -363,6 +363,31 @@ def test_sliced_products_and_their_epilogues(s24, dtype, pqr):
             assert torch.equal(bits(GU), bits(Yb)) and torch.equal(bits(Hg), bits(two))
 
 
+@pytest.mark.parametrize("q", [1984, 2048])     # slices; the tiles' kernel from 384 tiles of 128 x 128 and this contraction on
+def test_few_tokens_of_many_features_on_either_kernel(s24, q):
+    p, r = 13, 49152
+    gen = torch.Generator(device="cuda").manual_seed(q)
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    W, x, b = rnd(r, q) * 0.02, rnd(p, q), rnd(r)
+    new = lambda *shape, t=torch.bfloat16: torch.empty(shape, dtype=t, device="cuda")
+    v, m, vt, mt = new(q // 64, r, 32), new(q // 64, r, 4, t=torch.int16), new(r // 64, q, 32), new(r // 64, q, 4, t=torch.int16)
+    mask = new(r // 4, q // 4, t=torch.int16)
+    s24.compress(W, None, v, m, vt, mt, mask_out=mask)
+    rows = np.unique(np.concatenate([[0, 63, 64, 255, 256, r - 1], np.random.default_rng(q).integers(0, r, 200)]))
+    bits = host_bits(mask)[rows[:, None] // 4, np.arange(q)[None] // 4] >> (4 * (rows[:, None] % 4) + np.arange(q)[None] % 4)
+    kept = np.where(bits & 1, host_f64(W[torch.from_numpy(rows).cuda()]), 0)
+    Y, Z, H, two, GU = new(p, r), new(p, r), new(p, r), new(p, r), new(p, r)
+    s24.spmm_fwd_bias(x, v, m, b, Y)
+    assert_close(host_f64(Y)[:, rows], host_f64(x) @ kept.T + host_f64(b)[rows], tol_for("bf16"), f"spmm_fwd_bias {q}")
+    s24.spmm_fwd_act(x, v, m, b, Z, H, s24.ACT_GELU_ERF)
+    s24.act_fwd(Y, two, s24.ACT_GELU_ERF)
+    assert torch.equal(Z.view(torch.int16), Y.view(torch.int16)) and torch.equal(H.view(torch.int16), two.view(torch.int16))
+    Hg, two = new(p, r // 2), new(p, r // 2)
+    s24.spmm_fwd_glu(x, v, m, b, GU, Hg, s24.GATE_SILU)
+    s24.glu_fwd(Y, two, s24.GATE_SILU)
+    assert torch.equal(GU.view(torch.int16), Y.view(torch.int16)) and torch.equal(Hg.view(torch.int16), two.view(torch.int16))
+
+
 def test_calls_go_to_the_current_stream(s24):
     from paper_2404_01847_amd import binding
     side = torch.cuda.Stream()
