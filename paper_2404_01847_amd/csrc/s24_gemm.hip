@@ -1357,10 +1357,15 @@ int check_gemm(const void *a, const void *b, const void *c, int64_t p, int64_t q
 //            63, medium 54 us; 3001 x 2048, K = 11008: 101, 100, 77 us
 //   small    128 x 128, two per compute unit: at most one round of single ones (1024 x 2048, K = 5504: 53, 36, 29 us), or a
 //            contraction so short that a tile is mostly prologue and epilogue, which two co-resident workgroups overlap
-//            (8192 x 3072, K = 768 with activation: 51, 54, 46 us; 2048 deep: 0.7 of a large round, deeper: 0.82)
+//            (8192 x 3072, K = 768 with activation: 51, 54, 46 us; up to 640 deep two rounds of them cost little more than one
+//            of large ones: 8508 x 2112, K = 384: large 26, medium 25, small 21; 1024 deep: 0.54 of a large round, 2048: 0.7,
+//            deeper: 0.82)
 // A grid of large tiles whose last round is mostly empty (320 tiles on 256 compute units) can give its last token-tile rows
-// to a smaller tile: the first `slab` tokens run in whole rounds of large tiles (16384 x 1280, K = 5120: 135 -> 117 us).
-// Tokens are independent rows and every tile sums in the same order: the choice does not change a bit of the result.
+// to a smaller tile: the first `slab` tokens run in whole rounds of large tiles (16384 x 1280, K = 5120: 135 -> 117 us), where
+// that saves more than the second launch costs, 3 us of a round's 5 + 0.75 per 64 of k (2347 x 20032, K = 384: 56 us so cut,
+// 43 in small tiles).
+// Tokens are independent rows and these tiles sum in the same order: the choice among them does not change a bit of the
+// result.  (The slices of s24_gemm_slice.hip, chosen before them, sum in another.)
 struct NtTile {
     enum Kind { Large, Medium, Small } kind;
     int64_t slab;   // tokens of a first launch of its own, or 0
@@ -1387,7 +1392,8 @@ inline NtTile cheapest_tile(int64_t M, int64_t N, const NtCosts &c)
     const double l = nt_cost(NtTile::Large, M, N, c), m = nt_cost(NtTile::Medium, M, N, c), s = nt_cost(NtTile::Small, M, N, c);
     return {l <= m && l <= s ? NtTile::Large : m <= s ? NtTile::Medium : NtTile::Small, 0};
 }
-inline NtCosts sparse_costs(int64_t K) { return {0.73, 0.27, 0.69, 0.49, 0.20, K <= 1024 ? 0.6 : K <= 2048 ? 0.7 : 0.82, 0.37, 0.06}; }
+inline NtCosts sparse_costs(int64_t K) { return {0.73, 0.27, 0.69, 0.49, 0.20, K <= 640 ? 0.505 : K <= 1024 ? 0.54 : K <= 2048 ? 0.7 : 0.82, 0.37, 0.06}; }
+inline double round_us(int64_t K) { return 5.0 + 0.75 * (double)(K / 64); }   // a round of large tiles
 inline NtTile nt_tile(int64_t M, int64_t N, int64_t K) { return cheapest_tile(M, N, sparse_costs(K)); }
 // The same for a product whose tokens may be cut in two launches
 inline NtTile nt_tile_or_slab(int64_t M, int64_t N, int64_t K)
@@ -1398,7 +1404,8 @@ inline NtTile nt_tile_or_slab(int64_t M, int64_t N, int64_t K)
     const int64_t rows = tiles / cus * cus / tm, slab = 256 * rows;   // whole token-tile rows within the whole rounds
     const NtCosts c = sparse_costs(K);
     const NtTile strip = cheapest_tile(M, N - slab, c);
-    if (nt_cost(NtTile::Large, M, slab, c) + nt_cost(strip.kind, M, N - slab, c) < nt_cost(t.kind, M, N, c)) t.slab = slab;
+    const double cut = nt_cost(NtTile::Large, M, slab, c) + nt_cost(strip.kind, M, N - slab, c) + 3.0 / round_us(K);
+    if (cut < nt_cost(t.kind, M, N, c)) t.slab = slab;
     return t;
 }
 // The dense product: us per 64 of k, large 1.7 and 0.9 (full, few), medium 1.05 and 0.7, small 1.2 with two workgroups per

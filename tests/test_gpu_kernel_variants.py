@@ -288,9 +288,11 @@ def test_l1_norm_gap_of_infinities_and_nans(s24, dtype, legal_blocks):
 
 # ------------------------------------------------------------------ sparse products on the 256 x 128 tile
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-# (p, q, r): one, two, three and four chunks of the ring, ragged in both directions (136 tiles); a strip of such tiles
-# after a slab of large ones (51 rows of tiles, then 26 of half their height)
-@pytest.mark.parametrize("pqr", [(2050, 64, 2016), (2050, 128, 2016), (2049, 192, 2048), (2061, 256, 2016), (16390, 64, 1248)])
+# (p, q, r): one, two, three and four chunks of the ring, ragged in both directions (136 tiles, for the gated epilogue; the
+# others take 128 x 128 tiles at so short a contraction); the same from 17 chunks on, for all of them; a strip of such
+# tiles after a slab of large ones (51 rows of tiles, then 27 of half their height)
+@pytest.mark.parametrize("pqr", [(2050, 64, 2016), (2050, 128, 2016), (2049, 192, 2048), (2061, 256, 2016), (16390, 64, 1248),
+                                 (2050, 1088, 2016), (2049, 1152, 2048), (2061, 1216, 2016), (16390, 1088, 1248)])
 def test_medium_tile_and_its_epilogues(s24, dtype, pqr):
     p, q, r = pqr
     r64 = (r + 63) // 64 * 64
