@@ -1512,11 +1512,14 @@ extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t 
         return s24_slice_nt({static_cast<const uint16_t *>(X), static_cast<const uint16_t *>(vals), meta, static_cast<uint16_t *>(GU),
                              static_cast<uint16_t *>(H), nullptr, static_cast<const uint16_t *>(bias), p, q, 2 * f, false, S24_SLICE_GLU, gate}, dt, st);
     NtTile tile = nt_tile(2 * f, p, q);
-    // the small tile has no gated epilogue: it is taken only where it saves more than a launch for the activation
+    // The small tile has no gated epilogue: it is taken only where it saves more than the pass over Z costs, 2.4 us per million
+    // gated features (6 bytes each) less the 1 us that the fused epilogue costs itself.  10041 tokens, 19072 rows, K = 64: fused
+    // 123 us, in two calls 215; 2655 x 7360, K = 448: 31 and 38; but 527 x 1312, K = 960: 15.9 and 10.6.
     if (tile.kind == NtTile::Small) {
         const NtCosts c = sparse_costs(q);
         const double l = nt_cost(NtTile::Large, 2 * f, p, c), m = nt_cost(NtTile::Medium, 2 * f, p, c);
-        if (std::min(l, m) < nt_cost(NtTile::Small, 2 * f, p, c) + 0.1) tile.kind = l <= m ? NtTile::Large : NtTile::Medium;
+        const double pass = (2.4e-6 * (double)p * (double)f - 1.0) / (2.0 + round_us(q));
+        if (std::min(l, m) < nt_cost(NtTile::Small, 2 * f, p, c) + pass) tile.kind = l <= m ? NtTile::Large : NtTile::Medium;
     }
     if (dt != S24_F32 && tile.kind != NtTile::Small) {   // 128 gate and 128 up features per tile
         const int tiles_m = (int)ceil_div(f, 128), tiles_n = (int)ceil_div(p, tile.bn());
