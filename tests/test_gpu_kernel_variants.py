@@ -28,7 +28,10 @@ def compressed(W):
 # ------------------------------------------------------------------ fp32 on the matrix cores
 F32_NT = [
     # (p, q, r): four slices of a 32-tile; eight slices (deep, few tiles); four slices of a 64-tile; ragged edges of each
-    (33, 64, 48), (31, 128, 2064), (40, 576, 80), (1, 1024, 16), (1040, 64, 2064), (1057, 192, 2000)]
+    (33, 64, 48), (31, 128, 2064), (40, 576, 80), (1, 1024, 16), (1040, 64, 2064), (1057, 192, 2000),
+    # r a multiple of 32, so that the gated forward runs too: its 64-tile in four slices and in eight, the 32 features of a
+    # tile ragged (48, 80, 16, 528, 1008)
+    (33, 64, 96), (40, 576, 160), (1, 1024, 32), (300, 512, 1056), (1057, 192, 2016)]
 
 
 @pytest.mark.parametrize("pqr", F32_NT)
@@ -51,6 +54,7 @@ def test_f32_products_and_their_epilogues(s24, pqr):
     two = torch.empty_like(H)
     s24.act_fwd(Z, two, s24.ACT_GELU_ERF)
     assert_close(host_f64(H), host_f64(two), F32_TOL, f"act {pqr}")
+    assert torch.equal(H.view(torch.int32), two.view(torch.int32))           # the bits of the two calls
     s24.spmm_bwd_dx(x, v, m, Y, beta=1.0)    # the same product on top of itself
     assert_close(host_f64(Y), 2 * ref, F32_TOL, f"accumulate {pqr}")
     Wd = np.ascontiguousarray(W[:r])
@@ -64,6 +68,7 @@ def test_f32_products_and_their_epilogues(s24, pqr):
             two = torch.empty_like(Hg)
             s24.glu_fwd(Z, two, gate)
             assert_close(host_f64(Hg), host_f64(two), F32_TOL, f"glu {pqr} f={f}")
+            assert torch.equal(Hg.view(torch.int32), two.view(torch.int32))
 
 
 @pytest.mark.parametrize("case", [
