@@ -1106,15 +1106,16 @@ extern "C" int s24_mask_flips(const uint16_t *mask_new, const uint16_t *mask_old
     hipLaunchKernelGGL(clear_counter_kernel, dim3(1), dim3(1), 0, st, total);
     if (nblocks > 0) {
         const int64_t vecs = (nblocks + 7) / 8;
-        // One vector per lane at first, four where that makes more than a quarter of a workgroup per compute unit, and then at
-        // most one: the atomics on the one counter take 17 ns each, one after the other (one vector per lane and up to 1024
+        // One vector per lane up to a quarter of a workgroup per compute unit, beyond that four, in at most a workgroup per
+        // compute unit: the atomics on the one counter take 17 ns each, one after the other (one vector per lane and up to 1024
         // workgroups: 409600 blocks 6.1 -> 4.6 us, 2.8 M 17.0 -> 8.4, 14.7 M 22.9 -> 14.8; four vectors per lane from the
         // first: 12288 blocks 4.0 -> 4.4).  With per-block counts a vector is eight counters read and written: one per lane up
         // to a workgroup per compute unit (12288 blocks: 4.6 against 5.9 with four), two from 4 M blocks on (14.7 M: 43 us
         // against 52 with one workgroup and 48 with four per compute unit; 2.8 M: 13.5 with one, 14.3 with two).
         const int64_t cus = s24_cu_count(), full = (vecs + 255) / 256;
         const unsigned grid = (unsigned)(block_flips != nullptr ? std::min(full, vecs < 2048 * cus ? cus : 2 * cus)
-                                                                : std::min(std::max((vecs + 1023) / 1024, std::min(full, cus / 4)), cus));
+                                         : full <= cus / 4      ? full
+                                                                : std::min((vecs + 1023) / 1024, cus));
         hipLaunchKernelGGL(mask_flips_kernel, dim3(grid), dim3(256), 0, st, mask_new, mask_old, nblocks, block_flips, total);
     }
     return s24_launch_status();
