@@ -142,6 +142,18 @@ __device__ __forceinline__ float s24_gelu_slope(float x)
     return fmaf(x, e * 0.3989422804f, cdf);
 }
 
+// Ungated activation and its slope, chosen at compile time (the same arithmetic as the stand-alone kernels)
+template <int ACT> __device__ __forceinline__ float s24_act_value(float z)
+{
+    if (ACT == S24_ACT_RELU) return z > 0.0f ? z : 0.0f;
+    return s24_gelu(z);
+}
+template <int ACT> __device__ __forceinline__ float s24_act_slope(float z)
+{
+    if (ACT == S24_ACT_RELU) return z > 0.0f ? 1.0f : 0.0f;
+    return s24_gelu_slope(z);
+}
+
 // Gated activation h = act(g) * u with act chosen at compile time (GATE: 0 = SiLU, 1 = GELU), and its backward
 template <int GATE> __device__ __forceinline__ float s24_glu(float g, float u)
 {

@@ -230,18 +230,6 @@ __device__ __forceinline__ void staged_store(const f32x16 (&acc)[MI][2], unsigne
     }
 }
 
-// Ungated activation and its slope, chosen at compile time (the same arithmetic as the stand-alone kernels)
-template <int ACT> __device__ __forceinline__ float act_value(float z)
-{
-    if (ACT == S24_ACT_RELU) return z > 0.0f ? z : 0.0f;
-    return s24_gelu(z);
-}
-template <int ACT> __device__ __forceinline__ float act_slope(float z)
-{
-    if (ACT == S24_ACT_RELU) return z > 0.0f ? 1.0f : 0.0f;
-    return s24_gelu_slope(z);
-}
-
 // ACT_MODE 1 (forward of an ungated layer): the rounded tile Z is written to Out and H = act(Z) beside it, as the
 // stand-alone activation kernel would form it from the stored Z.  ACT_MODE 2 (input gradient of the second
 // projection): the rounded tile of dH is not written but multiplied by act'(Z), Z read from `GU`, into Out = dZ.
@@ -549,8 +537,8 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
             uint32_t o[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                o[k] = s24_num<T>::pack2(s24_num<T>::lo(dw[k]) * act_slope<ACT>(s24_num<T>::lo(zw[k])),
-                                         s24_num<T>::hi(dw[k]) * act_slope<ACT>(s24_num<T>::hi(zw[k])));
+                o[k] = s24_num<T>::pack2(s24_num<T>::lo(dw[k]) * s24_act_slope<ACT>(s24_num<T>::lo(zw[k])),
+                                         s24_num<T>::hi(dw[k]) * s24_act_slope<ACT>(s24_num<T>::hi(zw[k])));
             if (n < N && m_base + 8 * c < M)   // M is a multiple of 16: a chunk is all in or all out
                 *reinterpret_cast<uint4 *>(Out + (int64_t)n * M + m) = make_uint4(o[0], o[1], o[2], o[3]);
         }
@@ -572,7 +560,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
             uint32_t h[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                h[k] = s24_num<T>::pack2(act_value<ACT>(s24_num<T>::lo(zw[k])), act_value<ACT>(s24_num<T>::hi(zw[k])));
+                h[k] = s24_num<T>::pack2(s24_act_value<ACT>(s24_num<T>::lo(zw[k])), s24_act_value<ACT>(s24_num<T>::hi(zw[k])));
             *reinterpret_cast<uint4 *>(Out + (int64_t)n * M + m) = zc;
             *reinterpret_cast<uint4 *>(H + (int64_t)n * M + m) = make_uint4(h[0], h[1], h[2], h[3]);
         }
@@ -1695,7 +1683,7 @@ struct DwProblem {
     int64_t p, q, r;
     float lambda;
 };
-enum class DwTile { Large, Medium, Small };   // 256 x 256, 256 x 128, 128 x 128
+using DwTile = NtTile::Kind;   // 256 x 256, 256 x 128, 128 x 128
 int64_t dw_tiles_m(DwTile t, int64_t r) { return ceil_div(r, t == DwTile::Small ? 128 : 256); }
 int64_t dw_tiles_n(DwTile t, int64_t q) { return ceil_div(q, t == DwTile::Large ? 256 : 128); }
 // The window [m_off, m_off + mm) x [n_off, n_off + nn) of a problem's output, in tiles of `tile`
@@ -1785,7 +1773,7 @@ int run_dense_dw(const void *dY, const void *X, float *dW, int64_t p, int64_t q,
             for (int i = 1; i <= dmatn::kMaxBatch; ++i) batch.first_slot[i] = slots;
             launch_dw_batch(batch, tile, accum, fuse, dt, st);
         };
-        // 256 x 256 tiles when they fill the chip, 128 x 128 tiles otherwise.  A grid of large tiles that is not a
+        // 256 x 256 tiles when they fill the chip, otherwise the cheapest of the three (dw_few_tile).  A grid of large tiles that is not a
         // whole number of rounds over the 256 compute units leaves the chip part empty in its last round (c4's
         // 1376 tiles: 5.375 rounds).  Where whole tile rows or columns can be cut off so that the rest is an exact
         // number of rounds and the cut-off strip is at most half a round of large tiles, the slab runs in large
@@ -1795,9 +1783,8 @@ int run_dense_dw(const void *dY, const void *X, float *dW, int64_t p, int64_t q,
         // element belongs to exactly one launch either way, so nothing about the result changes.
         const int tm256 = (int)ceil_div(r, 256), tn256 = (int)ceil_div(q, 256), total = tm256 * tn256;
         const int cus = s24_cu_count();
-        const DwTile few = dw_few_tile(&pr0, 1);
         if (total < 3 * cus / 4) {
-            launch(few, 0, r, 0, q);
+            launch(dw_few_tile(&pr0, 1), 0, r, 0, q);
         } else {
             int cut_m = 0, cut_n = 0;   // tile rows / columns kept in the large-tile slab (0: no such cut)
             if (total % cus != 0) {
@@ -1891,8 +1878,8 @@ extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, flo
     }
     const int cus = s24_cu_count();
     if (!shared_grid || total < 3 * cus / 4 || count == 1) {
-        // Problems that would each run in small tiles anyway (fewer than 192 large ones) share one small-tile grid:
-        // a GPT-2-small layer's two gradients are 144 small tiles each, 0.56 of the chip one after the other.
+        // Problems that would each leave the large tile's grid mostly empty (fewer than 192 tiles) share one grid of the tile
+        // that is cheapest for all of them: a GPT-2-small layer's two gradients are 72 medium tiles each.
         bool small_grid = dt != S24_F32 && count > 1;
         for (int i = 0; i < count; ++i) {
             const s24_dw_problem &pr = problems[i];

@@ -42,8 +42,7 @@ __device__ __forceinline__ float kept_sum(const float *Av, const uint16_t *Am, i
     return sum;
 }
 
-// Sum of one float4 over the KS slices' copies of a tile, in slice order.  Slice s of a workgroup's tile w is parked at
-// (w * KS + s) * slice floats.
+// Sum of one float4 over the KS slices' copies of a tile, in slice order.  Slice s is parked at s * slice floats.
 template <int KS> __device__ __forceinline__ float4 slice_sum(const float *p, int slice)
 {
     float4 v = *reinterpret_cast<const float4 *>(p);
@@ -62,23 +61,21 @@ struct NtArgs {
     float *Out, *H;
     const float *bias;
     int N, K, M, F;   // F: gated features (GLU), else M
-    int tiles_m, tiles;
+    int tiles_m;
 };
 
 // SPARSE: A compressed.  EPI / ACT: epilogue.  GLU needs T = 2: a tile takes 32 gate rows and the 32 up rows of the same
 // features.
-template <bool SPARSE, bool ACCUM, int EPI, int ACT, int T, int KS, int WM>
-__global__ __launch_bounds__(64 * KS * WM) void f32_nt_kernel(const NtArgs g)
+template <bool SPARSE, bool ACCUM, int EPI, int ACT, int T, int KS>
+__global__ __launch_bounds__(64 * KS) void f32_nt_kernel(const NtArgs g)
 {
     static_assert(EPI != S24_F32_GLU || T == 2, "the gated tile pairs two row blocks");
-    constexpr int TW = 32 * T, PITCH = TW + 4, SLICE = TW * PITCH, THREADS = 64 * KS * WM;
-    __shared__ __attribute__((aligned(16))) float s_red[WM * KS * SLICE];
+    constexpr int TW = 32 * T, PITCH = TW + 4, SLICE = TW * PITCH, THREADS = 64 * KS;
+    __shared__ __attribute__((aligned(16))) float s_red[KS * SLICE];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), ks = wave % KS, wt = wave / KS;
+    const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, l = lane & 31;
-    const int t = (int)blockIdx.x * WM + wt;
-    const bool live = t < g.tiles;
-    const int tm = t % g.tiles_m, tn = t / g.tiles_m;
+    const int tm = (int)blockIdx.x % g.tiles_m, tn = (int)blockIdx.x / g.tiles_m;
     constexpr int FM = EPI == S24_F32_GLU ? 32 : TW;   // features of the (gated) output per tile
     const int m0 = tm * FM, n0 = tn * TW;
 
@@ -87,71 +84,69 @@ __global__ __launch_bounds__(64 * KS * WM) void f32_nt_kernel(const NtArgs g)
     for (int i = 0; i < T; ++i)
 #pragma unroll
         for (int j = 0; j < T; ++j) acc[i][j] = f32x16{};
-    if (live) {
-        // rows of this lane (clamped at the edge; such rows are never stored)
-        int arow[T];
-        const float *b[T];
+    // rows of this lane (clamped at the edge; such rows are never stored)
+    int arow[T];
+    const float *b[T];
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+        arow[i] = EPI == S24_F32_GLU ? i * g.F + min(m0 + l, g.F - 1) : min(m0 + 32 * i + l, g.M - 1);
+        b[i] = g.B + (int64_t)min(n0 + 32 * i + l, g.N - 1) * g.K;
+    }
+    // units of 16 of k: lane half h takes k 8h .. 8h+7 of a unit
+    const int units = g.K / 16, u0 = s24_slice_begin(units, ks, KS), u1 = s24_slice_begin(units, ks + 1, KS);
+    struct Frag { float4 a[T][2]; float4 b[T][2]; uint32_t nib[T]; };
+    auto load = [&](int u, Frag &f) {
+        const int k = 16 * u + 8 * h;
 #pragma unroll
         for (int i = 0; i < T; ++i) {
-            arow[i] = EPI == S24_F32_GLU ? i * g.F + min(m0 + l, g.F - 1) : min(m0 + 32 * i + l, g.M - 1);
-            b[i] = g.B + (int64_t)min(n0 + 32 * i + l, g.N - 1) * g.K;
+            if constexpr (SPARSE) {   // four kept values of the run's two groups, and their byte of the index words
+                const int64_t cr = (int64_t)(u >> 2) * g.M + arow[i];
+                f.a[i][0] = *reinterpret_cast<const float4 *>(g.Av + cr * 32 + 8 * (u & 3) + 4 * h);
+                f.nib[i] = (uint32_t)g.Am[cr * 4 + (u & 3)] >> (8 * h);
+            } else {
+                const float *a = g.Av + (int64_t)arow[i] * g.K + k;
+                f.a[i][0] = *reinterpret_cast<const float4 *>(a);
+                f.a[i][1] = *reinterpret_cast<const float4 *>(a + 4);
+            }
+            f.b[i][0] = *reinterpret_cast<const float4 *>(b[i] + k);
+            f.b[i][1] = *reinterpret_cast<const float4 *>(b[i] + k + 4);
         }
-        // units of 16 of k: lane half h takes k 8h .. 8h+7 of a unit
-        const int units = g.K / 16, u0 = s24_slice_begin(units, ks, KS), u1 = s24_slice_begin(units, ks + 1, KS);
-        struct Frag { float4 a[T][2]; float4 b[T][2]; uint32_t nib[T]; };
-        auto load = [&](int u, Frag &f) {
-            const int k = 16 * u + 8 * h;
+    };
+    auto multiply = [&](const Frag &f) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {   // the run's two groups of four
+            float e[T][4], x[T][4];
 #pragma unroll
             for (int i = 0; i < T; ++i) {
-                if constexpr (SPARSE) {   // four kept values of the run's two groups, and their byte of the index words
-                    const int64_t cr = (int64_t)(u >> 2) * g.M + arow[i];
-                    f.a[i][0] = *reinterpret_cast<const float4 *>(g.Av + cr * 32 + 8 * (u & 3) + 4 * h);
-                    f.nib[i] = (uint32_t)g.Am[cr * 4 + (u & 3)] >> (8 * h);
+                if constexpr (SPARSE) {
+                    const float4 v = f.a[i][0];
+                    expand(q ? v.z : v.x, q ? v.w : v.y, (f.nib[i] >> (4 * q)) & 0xFu, e[i]);
                 } else {
-                    const float *a = g.Av + (int64_t)arow[i] * g.K + k;
-                    f.a[i][0] = *reinterpret_cast<const float4 *>(a);
-                    f.a[i][1] = *reinterpret_cast<const float4 *>(a + 4);
+                    const float4 v = f.a[i][q];
+                    e[i][0] = v.x; e[i][1] = v.y; e[i][2] = v.z; e[i][3] = v.w;
                 }
-                f.b[i][0] = *reinterpret_cast<const float4 *>(b[i] + k);
-                f.b[i][1] = *reinterpret_cast<const float4 *>(b[i] + k + 4);
+                const float4 w = f.b[i][q];
+                x[i][0] = w.x; x[i][1] = w.y; x[i][2] = w.z; x[i][3] = w.w;
             }
-        };
-        auto multiply = [&](const Frag &f) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {   // the run's two groups of four
-                float e[T][4], x[T][4];
+            for (int k = 0; k < 4; ++k)
 #pragma unroll
-                for (int i = 0; i < T; ++i) {
-                    if constexpr (SPARSE) {
-                        const float4 v = f.a[i][0];
-                        expand(q ? v.z : v.x, q ? v.w : v.y, (f.nib[i] >> (4 * q)) & 0xFu, e[i]);
-                    } else {
-                        const float4 v = f.a[i][q];
-                        e[i][0] = v.x; e[i][1] = v.y; e[i][2] = v.z; e[i][3] = v.w;
-                    }
-                    const float4 w = f.b[i][q];
-                    x[i][0] = w.x; x[i][1] = w.y; x[i][2] = w.z; x[i][3] = w.w;
-                }
+                for (int i = 0; i < T; ++i)
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
-#pragma unroll
-                    for (int i = 0; i < T; ++i)
-#pragma unroll
-                        for (int j = 0; j < T; ++j) acc[i][j] = mma(e[i][k], x[j][k], acc[i][j]);
-            }
-        };
-        Frag f0, f1;
-        if (u0 < u1) load(u0, f0);
-        int u = u0;
-        for (; u + 1 < u1; u += 2) {   // the next unit's loads go out before the current one is multiplied
-            load(u + 1, f1);
-            multiply(f0);
-            load(min(u + 2, u1 - 1), f0);
-            multiply(f1);
+                    for (int j = 0; j < T; ++j) acc[i][j] = mma(e[i][k], x[j][k], acc[i][j]);
         }
-        if (u < u1) multiply(f0);
+    };
+    Frag f0, f1;
+    if (u0 < u1) load(u0, f0);
+    int u = u0;
+    for (; u + 1 < u1; u += 2) {   // the next unit's loads go out before the current one is multiplied
+        load(u + 1, f1);
+        multiply(f0);
+        load(min(u + 2, u1 - 1), f0);
+        multiply(f1);
     }
-    float *part = s_red + wave * SLICE;   // wave = wt * KS + ks
+    if (u < u1) multiply(f0);
+    float *part = s_red + ks * SLICE;
 #pragma unroll
     for (int j = 0; j < T; ++j)
 #pragma unroll
@@ -161,13 +156,12 @@ __global__ __launch_bounds__(64 * KS * WM) void f32_nt_kernel(const NtArgs g)
                 *reinterpret_cast<float4 *>(part + (32 * j + l) * PITCH + 32 * i + 8 * q + 4 * h) =
                     make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
     __syncthreads();
-    constexpr int QUADS = FM / 4, ITEMS = WM * TW * QUADS;   // four features of one token per item
+    constexpr int QUADS = FM / 4, ITEMS = TW * QUADS;   // four features of one token per item
 #pragma unroll 1
     for (int it = tid; it < ITEMS; it += THREADS) {
-        const int q = it % QUADS, row = (it / QUADS) % TW, w = it / (QUADS * TW), tt = (int)blockIdx.x * WM + w;
-        const int m = (tt % g.tiles_m) * FM + 4 * q, n = (tt / g.tiles_m) * TW + row;
-        if (tt >= g.tiles || n >= g.N || m >= (EPI == S24_F32_GLU ? g.F : g.M)) continue;   // M, F multiples of 16
-        const float *p = s_red + w * KS * SLICE + row * PITCH + 4 * q;
+        const int q = it % QUADS, row = it / QUADS, m = m0 + 4 * q, n = n0 + row;
+        if (n >= g.N || m >= (EPI == S24_F32_GLU ? g.F : g.M)) continue;   // M, F multiples of 16
+        const float *p = s_red + row * PITCH + 4 * q;
         auto finish = [&](const float *src, int feature) {
             float4 v = slice_sum<KS>(src, SLICE);
             if constexpr (SPARSE) {
@@ -196,8 +190,7 @@ __global__ __launch_bounds__(64 * KS * WM) void f32_nt_kernel(const NtArgs g)
         } else {
             const float4 z = finish(p, m);
             if constexpr (EPI == S24_F32_ACT) {
-                auto act = [](float x) { return ACT == S24_ACT_RELU ? (x > 0.0f ? x : 0.0f) : s24_gelu(x); };
-                *reinterpret_cast<float4 *>(g.H + (int64_t)n * g.M + m) = make_float4(act(z.x), act(z.y), act(z.z), act(z.w));
+                *reinterpret_cast<float4 *>(g.H + (int64_t)n * g.M + m) = make_float4(s24_act_value<ACT>(z.x), s24_act_value<ACT>(z.y), s24_act_value<ACT>(z.z), s24_act_value<ACT>(z.w));
             }
         }
     }
@@ -343,15 +336,14 @@ __global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-template <bool SPARSE, bool ACCUM, int EPI, int ACT, int T, int KS, int WM>
+template <bool SPARSE, bool ACCUM, int EPI, int ACT, int T, int KS>
 int launch_nt(const S24F32Nt &g, hipStream_t st)
 {
-    NtArgs a{g.B, g.Av, g.Am, g.Out, g.H, g.bias, (int)g.N, (int)g.K, (int)g.M, (int)(EPI == S24_F32_GLU ? g.M / 2 : g.M), 0, 0};
+    NtArgs a{g.B, g.Av, g.Am, g.Out, g.H, g.bias, (int)g.N, (int)g.K, (int)g.M, (int)(EPI == S24_F32_GLU ? g.M / 2 : g.M), 0};
     const int64_t tiles_m = EPI == S24_F32_GLU ? ceil_div(a.F, 32) : ceil_div(a.M, 32 * T), tiles = tiles_m * ceil_div(a.N, 32 * T);
     S24_REQUIRE(tiles < (1ll << 31), S24_ERR_SHAPE);
     a.tiles_m = (int)tiles_m;
-    a.tiles = (int)tiles;
-    hipLaunchKernelGGL((f32_nt_kernel<SPARSE, ACCUM, EPI, ACT, T, KS, WM>), dim3((unsigned)ceil_div(tiles, WM)), dim3(64 * KS * WM), 0, st, a);
+    hipLaunchKernelGGL((f32_nt_kernel<SPARSE, ACCUM, EPI, ACT, T, KS>), dim3((unsigned)tiles), dim3(64 * KS), 0, st, a);
     return s24_launch_status();
 }
 
@@ -366,12 +358,12 @@ template <bool SPARSE, bool ACCUM, int EPI, int ACT> int choose_nt(const S24F32N
     const int64_t cus = s24_cu_count();
     const bool deep = g.K >= 512 && ceil_div(g.M, 32) * ceil_div(g.N, 32) <= cus;   // few tiles, long sums: 8 slices
     if constexpr (EPI == S24_F32_GLU) {
-        if (deep) return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 8, 1>(g, st);
-        return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 4, 1>(g, st);
+        if (deep) return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 8>(g, st);
+        return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 4>(g, st);
     } else {
-        if (deep) return launch_nt<SPARSE, ACCUM, EPI, ACT, 1, 8, 1>(g, st);
-        if (ceil_div(g.M, 64) * ceil_div(g.N, 64) < 2 * cus) return launch_nt<SPARSE, ACCUM, EPI, ACT, 1, 4, 1>(g, st);
-        return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 4, 1>(g, st);
+        if (deep) return launch_nt<SPARSE, ACCUM, EPI, ACT, 1, 8>(g, st);
+        if (ceil_div(g.M, 64) * ceil_div(g.N, 64) < 2 * cus) return launch_nt<SPARSE, ACCUM, EPI, ACT, 1, 4>(g, st);
+        return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 4>(g, st);
     }
 }
 

@@ -42,11 +42,10 @@ struct NtArgs {
     int tiles_n, tiles;
 };
 
-template <int ACT> __device__ __forceinline__ float act_value(float z) { return ACT == S24_ACT_RELU ? (z > 0.0f ? z : 0.0f) : s24_gelu(z); }
-template <int ACT> __device__ __forceinline__ float act_slope(float z) { return ACT == S24_ACT_RELU ? (z > 0.0f ? 1.0f : 0.0f) : s24_gelu_slope(z); }
-
-// Slices per workgroup.  One number for all shapes: an output's bits then depend on K alone, so that one stacked weight and
-// its two halves, or a product with and without a fused epilogue, agree to the last bit.
+// Slices per workgroup.  One number for all shapes: among the products that come here an output's bits depend on K alone, so
+// that a product with and without a fused epilogue agrees to the last bit.  Which products come here depends on their tokens
+// and features too (s24_slice_pays), and the tiles of s24_gemm.hip sum in another order: a token alone and the same token
+// among thousands, or a stacked weight and its halves, may differ in the last bits.
 constexpr int KS = 8;
 
 // A workgroup owns 16*TM features x 16*TN tokens; wave s of its KS waves takes the 64-chunks s, s + KS, ... of the
@@ -183,14 +182,14 @@ __global__ __launch_bounds__(64 * KS) void spmm_slice_kernel(const NtArgs g)
         uint16_t *out = g.Out + at[p];
         if constexpr (EPI == S24_SLICE_ACT_BWD) {
             *reinterpret_cast<uint2 *>(out) =
-                make_uint2(Num::pack2(Num::lo(z.x) * act_slope<ACT>(Num::lo(old[p].x)), Num::hi(z.x) * act_slope<ACT>(Num::hi(old[p].x))),
-                           Num::pack2(Num::lo(z.y) * act_slope<ACT>(Num::lo(old[p].y)), Num::hi(z.y) * act_slope<ACT>(Num::hi(old[p].y))));
+                make_uint2(Num::pack2(Num::lo(z.x) * s24_act_slope<ACT>(Num::lo(old[p].x)), Num::hi(z.x) * s24_act_slope<ACT>(Num::hi(old[p].x))),
+                           Num::pack2(Num::lo(z.y) * s24_act_slope<ACT>(Num::lo(old[p].y)), Num::hi(z.y) * s24_act_slope<ACT>(Num::hi(old[p].y))));
         } else {
             *reinterpret_cast<uint2 *>(out) = z;
             if constexpr (EPI == S24_SLICE_ACT)
                 *reinterpret_cast<uint2 *>(g.H + at[p]) =
-                    make_uint2(Num::pack2(act_value<ACT>(Num::lo(z.x)), act_value<ACT>(Num::hi(z.x))),
-                               Num::pack2(act_value<ACT>(Num::lo(z.y)), act_value<ACT>(Num::hi(z.y))));
+                    make_uint2(Num::pack2(s24_act_value<ACT>(Num::lo(z.x)), s24_act_value<ACT>(Num::hi(z.x))),
+                               Num::pack2(s24_act_value<ACT>(Num::lo(z.y)), s24_act_value<ACT>(Num::hi(z.y))));
             if constexpr (EPI == S24_SLICE_GLU) {
                 const uint2 u = packed(total(src + FM, b1[p], biased));
                 *reinterpret_cast<uint2 *>(out + g.F) = u;

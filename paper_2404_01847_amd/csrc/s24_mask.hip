@@ -1,10 +1,12 @@
 // Transposable 2:4 mask search and prune/compress (Sec. 5.1 and Sec. 5 item 1).
 //
-// One lane owns one aligned 4x4 block.  A workgroup of 256 lanes walks a tile
-// of 32 x 32 blocks (128 x 128 weights), four blocks per lane.  The compressed
-// operands are stored chunk-major (64 of the contraction axis per chunk, all
-// rows of a chunk together), so a tile covers two chunks of each orientation
-// and the column-wise operand, after an LDS transpose, leaves in 8 KB runs.
+// One lane owns one aligned 4x4 block at a time.  A workgroup of 256 lanes
+// takes a tile of 32 x 32 blocks (128 x 128 weights, four blocks per lane), or
+// of 32 x 16 or 16 x 16 for matrices with fewer of them than fill the chip
+// (launch_sized).  The compressed operands are stored chunk-major (64 of the
+// contraction axis per chunk, all rows of a chunk together), so a tile covers
+// one or two chunks of each orientation and the column-wise operand, after an
+// LDS transpose, leaves in runs of 4 or 8 KB.
 //
 // Scoring.  A legal block is a choice of one of six column pairs per row
 // whose columns each get picked twice.  Rows 0-1 and rows 2-3 are scored
