@@ -207,6 +207,10 @@ struct TnWindow {
     float lambda;
 };
 constexpr int kMaxTn = 4;
+// Up to this many tokens the sum is one chain: split into slices of a pair or less it is rounded more often (distance from
+// fp64 against the chain's: 3 tokens 1.10, 5: 1.07, 7: 1.02, 8: 0.94, 16: 0.87).  A launch of such problems alone has one
+// wave per tile (5 tokens, 768 x 3072: 6.4 us with eight waves, 4.7 with one).
+constexpr int kWholeTokens = 7;
 struct TnArgs {
     TnWindow w[kMaxTn];
 };
@@ -261,7 +265,9 @@ __global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
         }
     } else {
         constexpr int U = 8;   // token pairs loaded together
-        const int pairs = s24_token_pairs(g.T), p0 = s24_slice_begin(pairs, ks, KS), p1 = s24_slice_begin(pairs, ks + 1, KS);
+        const int pairs = s24_token_pairs(g.T);
+        const bool whole = g.T <= kWholeTokens;   // the first slice takes all
+        const int p0 = whole ? (ks == 0 ? 0 : pairs) : s24_slice_begin(pairs, ks, KS), p1 = whole ? pairs : s24_slice_begin(pairs, ks + 1, KS);
         const float *a = g.A + mc, *x = g.X + nc;
         int p = p0;
         Run<T> av[U], xv[U];
@@ -367,9 +373,8 @@ template <bool SPARSE, bool ACCUM, int EPI, int ACT> int choose_nt(const S24F32N
     }
 }
 
-template <bool SPARSE, int T> int launch_tn(TnArgs &a, int64_t tiles, bool accum, hipStream_t st)
+template <bool SPARSE, int T, int KS> int launch_tn(TnArgs &a, int64_t tiles, bool accum, hipStream_t st)
 {
-    constexpr int KS = 8;
     const dim3 grid((unsigned)tiles), block(64 * KS);
     if (accum) hipLaunchKernelGGL((f32_tn_kernel<SPARSE, true, T, KS>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((f32_tn_kernel<SPARSE, false, T, KS>), grid, block, 0, st, a);
@@ -399,8 +404,10 @@ int s24_f32_tn(const S24F32TnProblem *pr, int count, bool accum, hipStream_t st)
     const int T = tiles[1] < 3 * s24_cu_count() ? 1 : 2;
     S24_REQUIRE(tiles[T - 1] < (1ll << 31), S24_ERR_SHAPE);
     int64_t first = 0;
+    bool few = true;
     for (int i = 0; i < kMaxTn; ++i) {
         if (i < count) {
+            few = few && pr[i].T <= kWholeTokens;
             const int64_t tm = ceil_div(pr[i].M, 32 * T);
             a.w[i] = TnWindow{pr[i].A, pr[i].X, pr[i].Wt, pr[i].Am, pr[i].mask, pr[i].dW, (int)pr[i].T, (int)pr[i].M, (int)pr[i].N, (int)tm, (int)first, pr[i].lambda};
             first += tm * ceil_div(pr[i].N, 32 * T);
@@ -409,6 +416,7 @@ int s24_f32_tn(const S24F32TnProblem *pr, int count, bool accum, hipStream_t st)
             a.w[i].first = 0x7FFFFFFF;   // no tile of the grid
         }
     }
-    if (pr[0].Am != nullptr) return T == 1 ? launch_tn<true, 1>(a, first, accum, st) : launch_tn<true, 2>(a, first, accum, st);
-    return T == 1 ? launch_tn<false, 1>(a, first, accum, st) : launch_tn<false, 2>(a, first, accum, st);
+    if (pr[0].Am != nullptr) return T == 1 ? launch_tn<true, 1, 8>(a, first, accum, st) : launch_tn<true, 2, 8>(a, first, accum, st);
+    if (few) return T == 1 ? launch_tn<false, 1, 1>(a, first, accum, st) : launch_tn<false, 2, 1>(a, first, accum, st);
+    return T == 1 ? launch_tn<false, 1, 8>(a, first, accum, st) : launch_tn<false, 2, 8>(a, first, accum, st);
 }

@@ -73,7 +73,8 @@ def test_f32_products_and_their_epilogues(s24, pqr):
 
 @pytest.mark.parametrize("case", [
     # (p, q, r, beta): 32-tiles; slices of less than one token; an odd token count; 64-tiles with ragged edges
-    (1, 16, 16, 0.0), (7, 48, 80, 1.0), (129, 80, 144, 0.0), (131, 1552, 2064, 1.0), (64, 1552, 2064, 0.0), (192, 48, 80, 1.0)])
+    # (up to 7 tokens are one chain, here beside a second problem of 12 or fewer)
+    (1, 16, 16, 0.0), (2, 1552, 2064, 0.0), (5, 80, 144, 0.0), (8, 48, 80, 1.0), (7, 48, 80, 1.0), (129, 80, 144, 0.0), (131, 1552, 2064, 1.0), (64, 1552, 2064, 0.0), (192, 48, 80, 1.0)])
 def test_f32_weight_gradients(s24, case):
     p, q, r, beta = case
     lam = 2e-4
@@ -106,6 +107,22 @@ def test_f32_weight_gradient_of_an_odd_token_count_with_an_infinity_in_the_last_
     assert np.array_equal(got[:, 5], np.copysign(np.float32(np.inf), dY[p - 1]))    # dY has no zero
     rest = np.arange(q) != 5
     assert_close(got[:, rest].astype(np.float64), dY.astype(np.float64).T @ X[:, rest].astype(np.float64), F32_TOL)
+
+
+@pytest.mark.parametrize("q,r", [(16, 16), (48, 80), (1552, 2064)])
+def test_f32_weight_gradients_of_few_tokens_are_chains(s24, q, r):
+    """3 and 7 tokens: the bits of fused multiply-adds in token order, alone and in one grid with a problem in slices."""
+    long_ = (dev(si.random_matrix(62, (64, 32), 1e-2, "f32")), dev(si.random_matrix(63, (64, 48), 1.0, "f32")))
+    for p in (3, 7):
+        dY, X = si.random_matrix(64 + p, (p, r), 1e-2, "f32"), si.random_matrix(65 + p, (p, q), 1.0, "f32")
+        chain = np.zeros((r, q), np.float32)
+        for t in range(p):    # the product of two floats is exact in fp64; one rounding of it plus the sum, but for double rounding
+            chain = (dY[t][:, None].astype(np.float64) * X[t][None, :] + chain).astype(np.float32)
+        alone, shared, other = (torch.zeros(s, device="cuda") for s in ((r, q), (r, q), (32, 48)))
+        s24.dense_dw(dev(dY), dev(X), alone)
+        s24.dense_dw_batch([(dev(dY), dev(X), shared, None, None, 0.0), (*long_, other, None, None, 0.0)])
+        assert torch.equal(alone.view(torch.int32), shared.view(torch.int32))
+        assert (alone.cpu().numpy() != chain).mean() <= 1e-5, p    # a double rounding is rarer than one in 2^20 additions
 
 
 def test_f32_weight_gradients_that_depend_on_their_order(s24):
