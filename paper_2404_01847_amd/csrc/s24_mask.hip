@@ -954,15 +954,9 @@ struct Top2 {
         first = __builtin_fmax(first, v);
     }
 };
-template <typename T>
-__global__ __launch_bounds__(256) void l1_gap_kernel(const T *__restrict__ W, int64_t ldw, int br, int bq,
-                                                     double *__restrict__ gap)
+template <typename T> __device__ __forceinline__ double block_gap(const T *__restrict__ W, int64_t ldw, int bi, int bj)
 {
     using Ops = RowOps<T>;
-    // 64 block columns x 4 block rows per workgroup, one wave per block row
-    const unsigned tiles_q = ((unsigned)bq + 63u) / 64u;
-    const int bj = (int)(blockIdx.x % tiles_q) * 64 + ((int)threadIdx.x & 63), bi = (int)(blockIdx.x / tiles_q) * 4 + ((int)threadIdx.x >> 6);
-    if (bi >= br || bj >= bq) return;
     uint32_t mag[16];
     uint32_t mx = 0, mn = 0xFFFFFFFFu;
 #pragma unroll
@@ -1041,7 +1035,19 @@ __global__ __launch_bounds__(256) void l1_gap_kernel(const T *__restrict__ W, in
         first = best.first;
         second = best.second;
     }
-    gap[(int64_t)bi * bq + bj] = first - second;
+    return first - second;
+}
+// A workgroup's tile is 2^wide block columns (up to a wave's 64, fewer for a narrower matrix) x 256 / 2^wide block rows.
+template <typename T, bool NARROW>
+__global__ __launch_bounds__(256) void l1_gap_kernel(const T *__restrict__ W, int64_t ldw, int br, int bq, int narrow,
+                                                     double *__restrict__ gap)
+{
+    const int wide = NARROW ? narrow : 6;
+    const unsigned tiles_q = ((unsigned)bq + (1u << wide) - 1u) >> wide, tile = blockIdx.x;
+    const int bj = (int)(((tile % tiles_q) << wide) + (threadIdx.x & ((1u << wide) - 1u)));
+    const int bi = (int)((tile / tiles_q) * (256u >> wide) + (threadIdx.x >> wide));
+    if (bi >= br || bj >= bq) return;
+    gap[(int64_t)bi * bq + bj] = block_gap(W, ldw, bi, bj);
 }
 
 // Shape and dtype are checked first; an empty matrix (r or q zero) is accepted
@@ -1130,15 +1136,24 @@ extern "C" int s24_l1_norm_gap(const void *W, s24_dtype dt, int64_t r, int64_t q
     S24_REQUIRE(gap != nullptr, S24_ERR_NULL);
     S24_REQUIRE(s24_aligned(gap, 8), S24_ERR_ALIGN);
     const int br = (int)(r / 4), bq = (int)(q / 4);
-    const int64_t tiles = (int64_t)((bq + 63) / 64) * ((br + 3) / 4);
-    S24_REQUIRE(tiles < (1ll << 31), S24_ERR_SHAPE);
+    int wide = 0;
+    while (wide < 6 && (1 << wide) < bq) ++wide;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const dim3 grid((unsigned)tiles), block(256);
-    if (dt == S24_BF16)
-        hipLaunchKernelGGL(l1_gap_kernel<uint16_t>, grid, block, 0, st, static_cast<const uint16_t *>(W), ldw, br, bq, gap);
-    else if (dt == S24_F16)
-        hipLaunchKernelGGL(l1_gap_kernel<s24_half>, grid, block, 0, st, static_cast<const s24_half *>(W), ldw, br, bq, gap);
-    else
-        hipLaunchKernelGGL(l1_gap_kernel<float>, grid, block, 0, st, static_cast<const float *>(W), ldw, br, bq, gap);
+    // A launch takes as many rows of tiles as make at most 2^23 workgroups: it holds less than 2^32 work items (of more it
+    // silently runs the remainder).
+    const int64_t height = 256 >> wide, tiles_q = ((int64_t)bq + (1 << wide) - 1) >> wide, step = height * std::max<int64_t>(1, (1 << 23) / tiles_q);
+    for (int64_t b0 = 0; b0 < br; b0 += step) {
+        const int rows = (int)std::min<int64_t>(br - b0, step);
+        const dim3 grid((unsigned)(tiles_q * ((rows + height - 1) / height))), block(256);
+        auto launch_gap = [&](auto t) {
+            using T = decltype(t);
+            const T *w = static_cast<const T *>(W) + 4 * b0 * ldw;
+            if (wide < 6) hipLaunchKernelGGL((l1_gap_kernel<T, true>), grid, block, 0, st, w, ldw, rows, bq, wide, gap + b0 * bq);
+            else hipLaunchKernelGGL((l1_gap_kernel<T, false>), grid, block, 0, st, w, ldw, rows, bq, wide, gap + b0 * bq);
+        };
+        if (dt == S24_BF16) launch_gap(uint16_t{});
+        else if (dt == S24_F16) launch_gap(s24_half{});
+        else launch_gap(float{});
+    }
     return s24_launch_status();
 }

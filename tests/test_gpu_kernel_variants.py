@@ -276,6 +276,19 @@ def test_l1_norm_gap_by_classes(s24, dtype, kind):
     assert np.all(np.abs(got - ref)[~exact] <= 16 * 2.0 ** -53 * a.sum(-1)[~exact])
 
 
+# one block column up to more than a wave's 64; as many rows of blocks as a grid of one workgroup per four could not hold
+@pytest.mark.parametrize("r,q", [(1028, 4), (1012, 12), (516, 28), (132, 36), (68, 128), (36, 260), (4, 1028), (2 ** 28 + 1028, 4)])
+def test_l1_norm_gap_by_width(s24, r, q):
+    W = torch.empty((r, q), dtype=torch.bfloat16, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(r))
+    gap = torch.full((r // 4, q // 4), -1.0, dtype=torch.float64, device="cuda")
+    s24.l1_norm_gap(W, gap)
+    for first in sorted({0, r // 8 * 4, max(0, r - 1028)}):      # the oracle on the first, middle and last rows
+        rows = min(r - first, 1028)
+        ref = oracle.l1_norm_gap(host_bits(W[first:first + rows]))
+        assert np.array_equal(gap[first // 4:(first + rows) // 4].cpu().numpy(), ref), first
+    assert (gap >= 0).all()
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
 def test_l1_norm_gap_of_infinities_and_nans(s24, dtype, legal_blocks):
     """The gap is what best and second best of the 90 sums give when they are compared one by one, also where a block holds
