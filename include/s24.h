@@ -42,6 +42,10 @@
  *                registers).  A pruned element never reaches a result in any type, whatever stands beside it in
  *                the other operand.  binary16 results overflow to infinity like any IEEE
  *                conversion: scaling the loss is the caller's business.
+ *   sums         a result depends on the call's arguments alone, not on scheduling.  The order in which a product is
+ *                summed depends on its sizes, the token count among them: a row may differ in its last bits from the
+ *                same row computed among more tokens or features.  Where a call below promises the bits of other
+ *                calls with the same sizes, it keeps them at every size.
  *   layouts      a logical [p][n] activation matrix is S24_ROW_MAJOR (element (t, c) at t*ld + c) or
  *                S24_COL_MAJOR (at c*ld + t, the layout the paper's sparse GEMMs emit, App. A.2).  The GEMMs of
  *                this library read and write row-major; the gated activation and the bias gradient take both.
