@@ -6,8 +6,8 @@
 //              with the activation forward / backward (Sec. 5.2) and the bias as optional epilogues
 //   sparse TN  dW = S_z(dY^T) X (Eq. 4): the same instruction, the dense operand read through transposing LDS reads
 //   dense  NT  Y = X W^T (Eq. 1, first GEMM; the comparison kernel): v_mfma_f32_32x32x16_{bf16,f16}
-//   dense  TN  dW = dY^T X (Eq. 1, third GEMM): both operands copied as they lie in memory, k-contiguous
-//              fragments by ds_read_b64_tr_b16; masked decay (Eq. 10) as an optional epilogue
+//   dense  TN  dW = dY^T X (Eq. 1, third GEMM): v_mfma_f32_16x16x32_{bf16,f16}, both operands copied as they lie in memory,
+//              k-contiguous fragments by ds_read_b64_tr_b16; masked decay (Eq. 10) as an optional epilogue
 // fp32 data takes the kernels of s24_gemm_f32.hip, sparse NT products of few tokens or features those of s24_gemm_slice.hip.
 //
 // Register layout of the sparse instruction (one 32x32 tile, 32 of k):
@@ -20,6 +20,7 @@
 // (vals[K/64][M][32], meta[K/64][M][4]) makes the 64-byte value run and the
 // four index words of one row and chunk contiguous, rows back to back.
 #include <algorithm>
+#include <type_traits>
 
 #include "s24_gemm_f32.h"
 #include "s24_gemm_slice.h"
@@ -30,18 +31,33 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) __bf16 bf16x16;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(16))) _Float16 f16x16;
 
 // The 16-bit kernels move operands as raw bits (fragments are typed bf16x8 / bf16x16 whatever they hold); the
 // element type T (uint16_t = bf16 bits, s24_half = IEEE binary16) only selects the matrix instruction and the
 // conversions of the epilogues.
+// c += a b on v_mfma_f32_16x16x32, the accumulator in place.  Written as an instruction because the compiler's own form does
+// not tie its result to its accumulator operand: with all 256 accumulation registers in use (the 128 x 128 wave tile) it
+// shuffled accumulators between register files, a move per instruction.  The compiler does not pad hazards around it:
+// fragments come from LDS reads, not from vector instructions just before (two wait states; a host test looks for such
+// pairs in the built library), and whoever reads the accumulators waits for the matrix unit first (mma_drain).
+#if defined(__HIP_DEVICE_COMPILE__)
+#define S24_MFMA_16X16X32(TYPE, a, b, c) \
+    asm volatile("v_mfma_f32_16x16x32_" TYPE " %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b))
+__device__ __forceinline__ void mma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+#else
+#define S24_MFMA_16X16X32(TYPE, a, b, c) (void)(a), (void)(b), (void)(c)
+__device__ __forceinline__ void mma_drain() {}
+#endif
 template <typename T> struct Mma;
 template <> struct Mma<uint16_t> {
     static __device__ __forceinline__ f32x16 dense(bf16x8 a, bf16x8 b, f32x16 c)
     {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
     }
+    static __device__ __forceinline__ void dense16(bf16x8 a, bf16x8 b, f32x4 &c) { S24_MFMA_16X16X32("bf16", a, b, c); }
     template <int ABID> static __device__ __forceinline__ f32x16 sparse(bf16x8 a, bf16x16 b, f32x16 c, int idx)
     {
         return __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a, b, c, idx, 0, ABID);
@@ -52,6 +68,7 @@ template <> struct Mma<s24_half> {
     {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
     }
+    static __device__ __forceinline__ void dense16(bf16x8 a, bf16x8 b, f32x4 &c) { S24_MFMA_16X16X32("f16", a, b, c); }
     template <int ABID> static __device__ __forceinline__ f32x16 sparse(bf16x8 a, bf16x16 b, f32x16 c, int idx)
     {
         return __builtin_amdgcn_smfmac_f32_32x32x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x16, b), c, idx, 0, ABID);
@@ -130,12 +147,13 @@ __host__ __device__ constexpr int wait_vm_lgkm0(int n) { return (n & 15) | (7 <<
 // chunks) in flight.  The raw wait and barrier instructions carry no memory semantics for the
 // compiler, so they are fenced on both sides against reordering of LDS accesses, in the
 // optimiser (empty asm with a memory clobber) and in the instruction scheduler.
-template <int VM>
+// LDS_READS: whether the wave's own LDS reads have to be back as well.
+template <int VM, bool LDS_READS = true>
 __device__ __forceinline__ void wait_and_barrier()
 {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(VM));
+    __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(VM) | (LDS_READS ? 0 : 15 << 8));
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
@@ -744,18 +762,21 @@ __global__ __launch_bounds__(128 * WN) void dense_nt_big_kernel(const uint16_t *
 // ds_read_b64_tr_b16: in a group of 16 lanes, lane i points at row i/4, columns 4*(i%4)..+3 of a
 // 4 (t) x 16 (columns) patch and receives, for column i, the four consecutive t (measured on the device
 // with an index-filled tile); two such reads give one lane its eight k values.
-// LDS swizzle: 16-byte chunk c of row t sits at slot c ^ (4*(t&3)), which keeps the eight 32-byte row
-// segments touched by 32 lanes in one cycle on distinct banks.
-// Four waves, one per SIMD, each a 128 x 128 tile of 4 x 4 accumulator blocks (256 accumulator registers):
+// LDS swizzle: 16-byte chunk c of token row t sits at slot c ^ (4 (t&3)) ^ (2 (t>>3 & 1)), which keeps the eight 32-byte row
+// segments (rows 0-3 and 8-11 of 16 columns) touched by 32 lanes in one cycle on distinct banks.
+// Four waves, one per SIMD, each a 128 x 128 tile of 8 x 8 accumulator blocks (256 accumulator registers):
 // against eight waves of 128 x 64 this reads a third less LDS per matrix instruction, which matters
-// because the chip sheds clock under the combined matrix + LDS + copy load.  The token axis moves through
-// a ring of four 32 KB stages.  A chunk is waited for one iteration before it is used, so the first
-// fragments of chunk kc+1 are fetched during the last matrix instructions of chunk kc and the barrier
-// finds the matrix unit busy; the copies of chunk kc+3 are dealt out between the matrix instructions
-// rather than issued in one burst.
+// because the chip sheds clock under the combined matrix + LDS + copy load.
+// 16 x 16 blocks and not 32 x 32: what bounds the kernel is the clock the chip holds, and the 16-wide instruction moves half
+// as many accumulator bits per FLOP: alone, on random operands, it runs at 2.05-2.10 PFLOP/s (2.02 GHz) where the 32-wide one
+// gets 1.81 (1.79 GHz); binary16 1.91 against 1.66.  Here: 8192 tokens, 8192 x 28672: 1.32 -> 1.42 PFLOP/s (2921 -> 2711 us, clock
+// 1.47 -> 1.64 GHz); 16384 tokens, 1280 x 5120: 188 -> 172 us.
+// The token axis moves through a ring of four 32 KB stages.  A chunk is waited for one iteration before it is used, so the
+// fragments of chunk kc+1 are fetched during the matrix instructions of chunk kc and the barrier finds the matrix unit
+// busy; the copies of chunk kc+3 are dealt out between the matrix instructions rather than issued in one burst.
 namespace dmatn {
 constexpr int THREADS = 256;
-// WTM x WTN = 32 x 32 accumulator blocks per wave: 4 x 4 -> 256 x 256 workgroup tiles; 4 x 2 and 2 x 2 -> 256 x 128 and
+// WTM x WTN: wave tile in units of 32: 4 x 4 -> 256 x 256 workgroup tiles; 4 x 2 and 2 x 2 -> 256 x 128 and
 // 128 x 128 tiles for outputs with too few large tiles to fill the chip.  BT = tokens per ring stage: 32 for the large tile (128 KB
 // of LDS); for the small tile 32 (64 KB, two workgroups per CU) when there are more tiles than CUs, else 64 (a
 // small tile has a quarter of the matrix work per token, so the barrier is paid half as often).
@@ -770,20 +791,22 @@ using big::lds_ptr;
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16 *lds_v4i16;
 
+// 16-byte slot of chunk c of token row t: c ^ tr_swizzle(t)
+__device__ __forceinline__ int tr_swizzle(int row) { return ((row & 3) << 2) ^ ((row >> 2) & 2); }
 template <int ROWB>
 __device__ __forceinline__ int tr_off(int row, int col)
 {
-    return row * ROWB + ((((col >> 3) ^ ((row & 3) << 2))) << 4) + ((col & 7) << 1);
+    return row * ROWB + (((col >> 3) ^ tr_swizzle(row)) << 4) + ((col & 7) << 1);
 }
-template <int ROWB>
-__device__ __forceinline__ bf16x8 tr_frag(const unsigned char *p)
+__device__ __forceinline__ v4i16 tr_half(const unsigned char *p) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(p)); }
+__device__ __forceinline__ bf16x8 join(v4i16 lo, v4i16 hi)
 {
-    // token rows t..t+3 and t+4..t+7 of this lane group's patch
-    const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(p));
-    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(p + 4 * ROWB));
     struct { v4i16 a, b; } t{lo, hi};
     return __builtin_bit_cast(bf16x8, t);
 }
+// token rows t..t+3 and t+4..t+7 of this lane group's patch
+template <int ROWB>
+__device__ __forceinline__ bf16x8 tr_frag(const unsigned char *p) { return join(tr_half(p), tr_half(p + 4 * ROWB)); }
 
 // DECAY: the masked decay term is added in the epilogue: dW[m][n] += lambda * Wt[m][n] where bit
 // 4*(m%4) + n%4 of mask[m/4][n/4] is clear, with the same single fused multiply-add the stand-alone
@@ -814,8 +837,9 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
 {
     constexpr int WTM = C::WTM, WTN = C::WTN, BM = C::BM, BN = C::BN, BT = C::BT, ROWA = C::ROWA, ROWX = C::ROWX;
     constexpr int OPERAND = C::OPERAND, STAGE = C::STAGE, NIA = C::NIA, NIX = C::NIX, NI = C::NI;
-    constexpr int KS = BT / 16, CPS = NI / KS;   // 16-token steps per chunk, copies issued per step
-    static_assert(KS % 2 == 0 && CPS * KS == NI, "steps alternate between two fragment sets");
+    constexpr int KS = BT / 32, CPS = NI / KS;   // 32-token steps per chunk, copies issued per step
+    static_assert(CPS * KS == NI, "every step issues the same number of copies");
+    constexpr int MB = 2 * WTM, NB = 2 * WTN;     // 16 x 16 accumulator blocks of a wave
     const big::ClockStamp t_start = big::clock_now();
     __shared__ __attribute__((aligned(16))) unsigned char s0[STAGE];
     __shared__ __attribute__((aligned(16))) unsigned char s1[STAGE];
@@ -857,71 +881,63 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
 #pragma unroll
     for (int j = 0; j < NIA; ++j) {
         constexpr int CPR = ROWA / 16;
-        const int slot = (wave * NIA + j) * 64 + lane, row = min(slot / CPR, T - 1), c = (slot % CPR) ^ (((slot / CPR) & 3) << 2);
+        const int slot = (wave * NIA + j) * 64 + lane, row = min(slot / CPR, T - 1), c = (slot % CPR) ^ tr_swizzle(slot / CPR);
         voffA[j] = (uint32_t)(row * ldy + m0 + 8 * min(c, lastA)) * 2u;
     }
 #pragma unroll
     for (int j = 0; j < NIX; ++j) {
         constexpr int CPR = ROWX / 16;
-        const int slot = (wave * NIX + j) * 64 + lane, row = min(slot / CPR, T - 1), c = (slot % CPR) ^ (((slot / CPR) & 3) << 2);
+        const int slot = (wave * NIX + j) * 64 + lane, row = min(slot / CPR, T - 1), c = (slot % CPR) ^ tr_swizzle(slot / CPR);
         voffB[j] = (uint32_t)(row * ldx + n0 + 8 * min(c, lastB)) * 2u;
     }
     auto first_row = [&](int kc) { return max(min(kc * BT, T - BT), 0); };
-    // Copies first .. first+count-1 of a chunk's list (the dY tile's NIA, then the X tile's NIX).
+    const char *baseA = reinterpret_cast<const char *>(dY), *baseB = reinterpret_cast<const char *>(X);
+    // Copy c of a chunk's list (the dY tile's NIA, then the X tile's NIX), rowsA and rowsB its first token row.
     // The copies are buffer loads into LDS: a descriptor (scalar registers) whose base is the chunk's first token
     // row, and the lane's fixed 32-bit offset; nothing of a copy's address is computed on the vector unit.
-    auto issue = [&](unsigned char *st, int kc, int first, int count) {
-        const int row0 = first_row(kc);
-        const big::rsrc_t ya = big::buffer_of(dY + (int64_t)row0 * ldy), xb = big::buffer_of(X + (int64_t)row0 * ldx);
-#pragma unroll
-        for (int c = first; c < first + count; ++c) {
-            if (c < NIA)
-                big::buffer_to_lds<16>(ya, (lds_ptr)(st + (wave * NIA + c) * 1024), voffA[c]);
-            else
-                big::buffer_to_lds<16>(xb, (lds_ptr)(st + OPERAND + (wave * NIX + c - NIA) * 1024), voffB[c - NIA]);
-        }
+    auto issue = [&](unsigned char *st, const char *rowsA, const char *rowsB, int c) {
+        if (c < NIA) big::buffer_to_lds<16>(big::buffer_of(rowsA), (lds_ptr)(st + (wave * NIA + c) * 1024), voffA[c]);
+        else big::buffer_to_lds<16>(big::buffer_of(rowsB), (lds_ptr)(st + OPERAND + (wave * NIX + c - NIA) * 1024), voffB[c - NIA]);
     };
-    f32x16 acc[WTM][WTN];
+    auto issue_all = [&](unsigned char *st, int kc) {
+        const char *ra = baseA + (int64_t)first_row(kc) * ldy * 2, *rb = baseB + (int64_t)first_row(kc) * ldx * 2;
 #pragma unroll
-    for (int mi = 0; mi < WTM; ++mi)
+        for (int c = 0; c < NI; ++c) issue(st, ra, rb, c);
+    };
+    f32x4 acc[MB][NB];
 #pragma unroll
-        for (int ni = 0; ni < WTN; ++ni) acc[mi][ni] = f32x16{};
+    for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NB; ++ni) acc[mi][ni] = f32x4{};
 
-    // fragment addressing of this lane: group G = lane/16 -> k half G/2, column half G%2
+    // fragment addressing of this lane: group G = lane/16 takes tokens 8G .. 8G+7 of a step, 16 columns per block
     const int gi = lane & 15, G = lane >> 4;
-    const int frow = 8 * (G >> 1) + (gi >> 2), fcol = 16 * (G & 1) + 4 * (gi & 3);
-    int offA[WTM], offB[WTN];
+    const int frow = 8 * G + (gi >> 2), fcol = 4 * (gi & 3);
+    // Byte offsets of a lane's fragments from a stage, and the same plus 64 KB for the upper two stages, whose distance does
+    // not fit an instruction's offset field (kept in registers of their own: added on the spot, they were 16 vector
+    // instructions per chunk).
+    constexpr int FAR = 2 * STAGE;
+    int offA[2][MB], offB[2][NB];
 #pragma unroll
-    for (int i = 0; i < WTM; ++i) offA[i] = tr_off<ROWA>(frow, 32 * WTM * wm + 32 * i + fcol);
+    for (int i = 0; i < MB; ++i) offA[0][i] = tr_off<ROWA>(frow, 32 * WTM * wm + 16 * i + fcol);
 #pragma unroll
-    for (int i = 0; i < WTN; ++i) offB[i] = OPERAND + tr_off<ROWX>(frow, 32 * WTN * wn + 32 * i + fcol);
-    auto load_frags = [&](const unsigned char *st, int ks, bf16x8 (&a)[WTM], bf16x8 (&b)[WTN]) {
+    for (int i = 0; i < NB; ++i) offB[0][i] = OPERAND + tr_off<ROWX>(frow, 32 * WTN * wn + 16 * i + fcol);
 #pragma unroll
-        for (int ni = 0; ni < WTN; ++ni) b[ni] = tr_frag<ROWX>(st + offB[ni] + 16 * ks * ROWX);
+    for (int i = 0; i < MB; ++i) {
+        offA[1][i] = offA[0][i] + FAR;
+        asm volatile("" : "+v"(offA[1][i]));
+    }
 #pragma unroll
-        for (int mi = 0; mi < WTM; ++mi) a[mi] = tr_frag<ROWA>(st + offA[mi] + 16 * ks * ROWA);
+    for (int i = 0; i < NB; ++i) {
+        offB[1][i] = offB[0][i] + FAR;
+        asm volatile("" : "+v"(offB[1][i]));
+    }
+    // Half h (tokens 8G + 4h ..) of fragment i of step ks.  S: number of the stage `st`
+    auto load_a = [&](const unsigned char *st, auto S, int ks, int i, int h) {
+        return tr_half((S < 2 ? st + offA[0][i] : st - FAR + offA[1][i]) + (32 * ks + 4 * h) * ROWA);
     };
-    auto mma = [&](const bf16x8 (&a)[WTM], const bf16x8 (&b)[WTN]) {
-#pragma unroll
-        for (int mi = 0; mi < WTM; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < WTN; ++ni)
-                acc[mi][ni] = Mma<ET>::dense(a[mi], b[ni], acc[mi][ni]);
-    };
-    // Issue order of one 16-token step: a matrix instruction, then two LDS reads of the next step's fragments
-    // (2 * (WTM + WTN) reads against WTM * WTN matrix instructions), and after every other matrix instruction one copy.
-    // The reads go out as early in the step as two per matrix instruction allow, so that the last fragment has arrived
-    // well before the step ends: with one wave per SIMD nobody else covers a wait.
-    auto interleave = [&]() {
-        constexpr int READS = 2 * (WTM + WTN), MFMAS = WTM * WTN;
-        static_assert(READS <= 2 * MFMAS && 2 * CPS <= MFMAS, "reads and copies fit between the matrix instructions");
-#pragma unroll
-        for (int i = 0; i < MFMAS; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (2 * i < READS) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            if ((i & 1) && (i >> 1) < CPS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    auto load_b = [&](const unsigned char *st, auto S, int ks, int i, int h) {
+        return tr_half((S < 2 ? st + offB[0][i] : st - FAR + offB[1][i]) + (32 * ks + 4 * h) * ROWX);
     };
     // The last chunk of a token count that is not a multiple of BT holds BT - rem rows that must not contribute:
     // the leading rows that its predecessor already covered (the chunk starts at T - BT), or, when there are
@@ -936,42 +952,105 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     const bool partial = (T % BT) != 0;
 
     // prologue: chunks 0..2 in flight, chunk 0 landed, its first fragments in registers
-    issue(s0, 0, 0, NI);
+    issue_all(s0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    issue(s1, 1, 0, NI);
+    issue_all(s1, 1);
     __builtin_amdgcn_sched_barrier(0);
-    issue(s2, 2, 0, NI);
+    issue_all(s2, 2);
     __builtin_amdgcn_sched_barrier(0);
     big::wait_and_barrier<2 * NI>();
     if (partial && nk == 1) clear_tail(s0, 0);
-    bf16x8 fa[2][WTM], fb[2][WTN];   // fragments of the current and of the next 16-token step
-    load_frags(s0, 0, fa[0], fb[0]);
-
-    // Iteration kc: all but the NI most recent copies (chunk kc+2) are complete, so chunk kc+1 is in LDS for
-    // every wave after the barrier, and nobody reads the stage of chunk kc-1 any more: it takes chunk kc+3.
-    auto chunk = [&](const unsigned char *cur, unsigned char *nxt, unsigned char *refill, int kc) {
-        big::wait_and_barrier<NI>();
-        if (partial && kc + 2 == nk) clear_tail(nxt, kc + 1);
+    // Fragments: of X those of the current and of the next 32-token step; of dY one set, each replaced by the next step's
+    // as soon as its row of accumulators is done (the last one at the start of that step).
+    const std::integral_constant<int, 0> c0;
+    const std::integral_constant<int, 1> c1;
+    const std::integral_constant<int, 2> c2;
+    const std::integral_constant<int, 3> c3;
+    bf16x8 fa[MB], fb[2][NB];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            issue(refill, kc + 3, ks * CPS, CPS);
-            // past the last chunk the final prefetch reads a stage nobody uses; the result is dropped
-            if (ks + 1 < KS) load_frags(cur, ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
-            else load_frags(nxt, 0, fa[0], fb[0]);
-            mma(fa[ks & 1], fb[ks & 1]);
-            interleave();
+    for (int ni = 0; ni < NB; ++ni) fb[0][ni] = join(load_b(s0, c0, 0, ni, 0), load_b(s0, c0, 0, ni, 1));
+#pragma unroll
+    for (int mi = 0; mi < MB - 1; ++mi) fa[mi] = join(load_a(s0, c0, 0, mi, 0), load_a(s0, c0, 0, mi, 1));
+    const char *rowsA = baseA + (int64_t)first_row(3) * ldy * 2, *rowsB = baseB + (int64_t)first_row(3) * ldx * 2;   // of the next chunk to copy
+
+    // One step: rows of NB matrix instructions.  A wave is alone on its SIMD and issues an instruction every four cycles, a
+    // matrix instruction lasts sixteen: whatever else goes out between two of them beyond three instructions leaves the matrix
+    // unit idle (a wait state before each cost 6 % of the kernel).  So the rest is dealt out evenly: beside row mi the
+    // LDS reads of one dY fragment and of NB / MB X fragments, one read per matrix instruction, one copy, and a part of
+    // the address of the next chunk's rows.  The X fragment is the instruction's row operand: a lane's four accumulators
+    // are then four consecutive columns of one row of dW.  Neighbouring instructions share a fragment, at the turns
+    // of the serpentine the other one: the operand bits that toggle cost clock.
+    // `cs` / `ns`: numbers of the stages cur / nxt; `which`: the X fragment set of this step.
+    auto step = [&](const unsigned char *cur, auto cs, int ks, const unsigned char *nxt, auto ns, int ksn, unsigned char *refill, int copy0, int next_row,
+                    auto which) {
+        constexpr int P = decltype(which)::value, RB = 2 * NB / MB, R = RB + 2;   // reads of X beside a row, all reads
+        static_assert(RB * MB == 2 * NB && R <= NB && CPS <= MB, "one read per matrix instruction, one copy per row");
+        int64_t nextA = 0, nextB = 0;
+        v4i16 lo{}, loA{};
+#pragma unroll
+        for (int mi = 0; mi < MB; ++mi) {
+#pragma unroll
+            for (int nj = 0; nj < NB; ++nj) {
+                const int ni = (mi & 1) ? NB - 1 - nj : nj;
+                Mma<ET>::dense16(fb[P][ni], fa[mi], acc[mi][ni]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    if (r * NB / R != nj) continue;
+                    if (r < RB) {
+                        const int i = RB * mi + r;
+                        if (i % 2 == 0) lo = load_b(nxt, ns, ksn, i / 2, 0);
+                        else fb[1 - P][i / 2] = join(lo, load_b(nxt, ns, ksn, i / 2, 1));
+                    } else if (mi == 0) {
+                        if (r == RB) loA = load_a(cur, cs, ks, MB - 1, 0);
+                        else fa[MB - 1] = join(loA, load_a(cur, cs, ks, MB - 1, 1));
+                    } else {
+                        if (r == RB) loA = load_a(nxt, ns, ksn, mi - 1, 0);
+                        else fa[mi - 1] = join(loA, load_a(nxt, ns, ksn, mi - 1, 1));
+                    }
+                }
+                if (nj == NB - 1 && mi < CPS) issue(refill, rowsA, rowsB, copy0 + mi);
+                if (next_row >= 0 && nj == 1) {   // the address of the next chunk's rows, a product or a sum at a time
+                    if (mi == MB - 4) { nextA = (int64_t)next_row * ldy * 2; asm volatile("" : "+s"(nextA)); }
+                    if (mi == MB - 3) { nextB = (int64_t)next_row * ldx * 2; asm volatile("" : "+s"(nextB)); }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (next_row >= 0) { rowsA = baseA + nextA; rowsB = baseB + nextB; }
+    };
+    // Iteration kc: all but the NI most recent copies (chunk kc+2) are complete, so chunk kc+1 is in LDS for
+    // every wave after the barrier, and nobody reads the stage of chunk kc-1 any more: it takes chunk kc+3.  (The last read
+    // of that stage fed the last row of iteration kc-1; the reads still in flight here are of chunk kc and need no wait.)
+    // Past the last chunk the fragments fetched ahead come from a stage nobody uses and are dropped.
+    auto chunk = [&](const unsigned char *cur, auto cs, unsigned char *nxt, auto ns, unsigned char *refill, int kc, bool tail) {
+        big::wait_and_barrier<NI, false>();
+        if (tail && partial && kc + 2 == nk) clear_tail(nxt, kc + 1);
+        const int next_row = first_row(kc + 4);
+        if constexpr (KS == 1) {
+            step(cur, cs, 0, nxt, ns, 0, refill, 0, next_row, std::integral_constant<int, decltype(cs)::value & 1>());
+        } else {
+            static_assert(KS <= 2, "one or two steps per chunk");
+            step(cur, cs, 0, cur, cs, 1, refill, 0, -1, c0);
+            step(cur, cs, 1, nxt, ns, 0, refill, CPS, next_row, c1);
         }
     };
     int kc = 0;
-    for (; kc + 4 <= nk; kc += 4) {
-        chunk(s0, s1, s3, kc);
-        chunk(s1, s2, s0, kc + 1);
-        chunk(s2, s3, s1, kc + 2);
-        chunk(s3, s0, s2, kc + 3);
+    for (; kc + 6 <= nk; kc += 4) {   // the chunk that needs its overlap cleared is never `nxt` in here
+        chunk(s0, c0, s1, c1, s3, kc, false);
+        chunk(s1, c1, s2, c2, s0, kc + 1, false);
+        chunk(s2, c2, s3, c3, s1, kc + 2, false);
+        chunk(s3, c3, s0, c0, s2, kc + 3, false);
     }
-    if (kc < nk) chunk(s0, s1, s3, kc);
-    if (kc + 1 < nk) chunk(s1, s2, s0, kc + 1);
-    if (kc + 2 < nk) chunk(s2, s3, s1, kc + 2);
+    for (; kc < nk; kc += 4) {
+        chunk(s0, c0, s1, c1, s3, kc, true);
+        if (kc + 1 >= nk) break;
+        chunk(s1, c1, s2, c2, s0, kc + 1, true);
+        if (kc + 2 >= nk) break;
+        chunk(s2, c2, s3, c3, s1, kc + 2, true);
+        if (kc + 3 >= nk) break;
+        chunk(s3, c3, s0, c0, s2, kc + 3, true);
+    }
     // Epilogue through LDS, so that global memory sees 16-byte accesses along rows: each wave parks a slice of its tile
     // at a time (32*RB rows x 64 columns of fp32, 256-byte rows) in its own ring stage, then lane l of pass j
     // owns row (64j + l) / 16, columns 4 * (l % 16) .. +3: one LDS read, one 16-byte store, and for the
@@ -1006,6 +1085,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
             }
         }
     };
+    mma_drain();
     decay_loads(0, 0);
     big::wait_and_barrier<0>();   // last (redundant) copies drained, nobody reads the ring any more: reuse it
     big::clock_report(probe, t_start);
@@ -1015,14 +1095,12 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
         const int h2 = slice / NR, r2 = slice % NR;
         if (slice > 0) decay_loads(h2, r2);
 #pragma unroll
-        for (int nj = 0; nj < 2; ++nj)
+        for (int nj = 0; nj < 4; ++nj)
 #pragma unroll
-            for (int mi = 0; mi < RB; ++mi)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int row = 32 * mi + 8 * (e / 4) + 4 * (lane >> 5) + (e & 3), col = 32 * nj + (lane & 31);
-                    *reinterpret_cast<float *>(est + row * 256 + col * 4) = acc[RB * r2 + mi][2 * h2 + nj][e];
-                }
+            for (int mi = 0; mi < 2 * RB; ++mi) {   // 16-byte piece c of row r sits at slot c ^ (r & 15)
+                const int row = 16 * mi + (lane & 15), c4 = 4 * nj + (lane >> 4);
+                *reinterpret_cast<f32x4 *>(est + row * 256 + ((c4 ^ (row & 15)) << 4)) = acc[2 * RB * r2 + mi][4 * h2 + nj];
+            }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(big::wait_vm_lgkm0(63));   // LDS only: the wave reads back only what it wrote itself
         asm volatile("" ::: "memory");
@@ -1038,7 +1116,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
                 const int m = ms + row, n = ns + 4 * c4;
                 live[b] = m < M && n < N;   // N is a multiple of 16: the four columns are all in or all out
                 const int mc = min(m, M - 1), nc = min(n, N - 4);
-                v[b] = *reinterpret_cast<const float4 *>(est + row * 256 + c4 * 16);
+                v[b] = *reinterpret_cast<const float4 *>(est + row * 256 + ((c4 ^ (row & 15)) << 4));
                 if (ACCUM) old[b] = *reinterpret_cast<const float4 *>(dW + (int64_t)mc * ldw + nc);
             }
 #pragma unroll
@@ -1117,7 +1195,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_tn_big_kernel(const uint16_t *_
     const int lastB = (min(N - n0, BN) >> 3) - 1;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int slot = (wave * 4 + j) * 64 + lane, row = slot / CPR, c = (slot % CPR) ^ ((row & 3) << 2);
+        const int slot = (wave * 4 + j) * 64 + lane, row = slot / CPR, c = (slot % CPR) ^ dmatn::tr_swizzle(row);
         ob[j] = ((uint32_t)row * (uint32_t)N + (uint32_t)(n0 + 8 * min(c, lastB))) * 2u;
     }
 #pragma unroll

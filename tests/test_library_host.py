@@ -296,3 +296,74 @@ def test_binding_refuses_to_run_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(binding, "_LIB_PATH", str(tmp_path / "libs24.so"))
     with pytest.raises(FileNotFoundError):
         binding.lib()
+
+
+def _device_code(path):
+    """The gfx950 code objects of the library's offload bundles (one per source file)."""
+    data, out, at = open(path, "rb").read(), [], 0
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    while (at := data.find(magic, at)) >= 0:
+        count = int.from_bytes(data[at + 24:at + 32], "little")
+        pos = at + 32
+        for _ in range(count):
+            offset, size, idlen = (int.from_bytes(data[pos + 8 * k:pos + 8 * k + 8], "little") for k in range(3))
+            name = data[pos + 24:pos + 24 + idlen]
+            if b"gfx950" in name:
+                out.append(data[at + offset:at + offset + size])
+            pos += 24 + idlen
+        at += 24
+    return out
+
+
+def _registers(operand):
+    m = re.fullmatch(r"([av])(\d+)|([av])\[(\d+):(\d+)\]", operand)
+    if not m:
+        return set()
+    if m.group(1):
+        return {(m.group(1), int(m.group(2)))}
+    return {(m.group(3), k) for k in range(int(m.group(4)), int(m.group(5)) + 1)}
+
+
+def test_matrix_instructions_written_as_asm_keep_their_distances(lib, tmp_path):
+    """The compiler pads no hazards around v_mfma_f32_16x16x32 in inline asm: no vector instruction may write an operand
+    within two wait states before one, and nothing but another matrix instruction may touch an accumulator within 18 after."""
+    import paper_2404_01847_amd as s24
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(objdump):
+        pytest.skip("no llvm-objdump")
+    found = 0
+    for k, code in enumerate(_device_code(s24.lib_path())):
+        if b"dense_tn_dma_kernel" not in code:
+            continue
+        obj = tmp_path / f"{k}.co"
+        obj.write_bytes(code)
+        text = subprocess.run([objdump, "-d", "--mcpu=gfx950", "--no-show-raw-insn", "--no-leading-addr", str(obj)],
+                              capture_output=True, text=True, check=True).stdout
+        written, busy, clock = {}, {}, 0   # register -> wait state of its last vector-unit write / end of matrix write
+        for line in text.splitlines():
+            line = line.split("//")[0].strip()
+            if not line or line.endswith(":"):
+                if line.endswith(":"):
+                    written, busy = {}, {}
+                continue
+            op, _, rest = line.partition(" ")
+            args = [a.strip() for a in rest.split(",")]
+            if op == "s_nop":
+                clock += int(args[0], 0) + 1
+                continue
+            clock += 1
+            regs = [_registers(a.split(" ")[0]) for a in args]
+            if op.startswith("v_mfma_f32_16x16x32"):
+                found += 1
+                for r in set().union(*regs[1:]):
+                    assert clock - written.get(r, -9) > 2, (line, r)
+                for r in regs[0]:
+                    busy[r] = clock + 18
+            elif op.startswith(("v_mfma", "v_smfmac")):
+                continue
+            else:
+                for r in set().union(*regs):
+                    assert busy.get(r, -1) < clock, (line, r)
+                if op.startswith("v_"):
+                    written.update((r, clock) for r in regs[0])
+    assert found > 1000
