@@ -46,29 +46,36 @@ typedef __attribute__((ext_vector_type(16))) _Float16 f16x16;
 #if defined(__HIP_DEVICE_COMPILE__)
 #define S24_MFMA_16X16X32(TYPE, a, b, c) \
     asm volatile("v_mfma_f32_16x16x32_" TYPE " %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b))
+#define S24_SMFMAC_16X16X64(TYPE, HALF, a, b, c, idx) \
+    asm volatile("v_smfmac_f32_16x16x64_" TYPE " %0, %1, %2, %3 abid:" HALF : "+v"(c) : "v"(a), "v"(b), "v"(idx))
+__device__ __forceinline__ void mma_operand_gap() { asm volatile("s_nop 1"); }
 __device__ __forceinline__ void mma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 #else
 #define S24_MFMA_16X16X32(TYPE, a, b, c) (void)(a), (void)(b), (void)(c)
+#define S24_SMFMAC_16X16X64(TYPE, HALF, a, b, c, idx) (void)(a), (void)(b), (void)(c), (void)(idx)
+__device__ __forceinline__ void mma_operand_gap() {}
 __device__ __forceinline__ void mma_drain() {}
 #endif
 template <typename T> struct Mma;
 template <> struct Mma<uint16_t> {
-    static __device__ __forceinline__ f32x16 dense(bf16x8 a, bf16x8 b, f32x16 c)
-    {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-    }
     static __device__ __forceinline__ void dense16(bf16x8 a, bf16x8 b, f32x4 &c) { S24_MFMA_16X16X32("bf16", a, b, c); }
+    template <int ABID> static __device__ __forceinline__ void sparse16(bf16x8 a, bf16x16 b, f32x4 &c, uint32_t idx)
+    {
+        if constexpr (ABID == 0) S24_SMFMAC_16X16X64("bf16", "0", a, b, c, idx);
+        else S24_SMFMAC_16X16X64("bf16", "1", a, b, c, idx);
+    }
     template <int ABID> static __device__ __forceinline__ f32x16 sparse(bf16x8 a, bf16x16 b, f32x16 c, int idx)
     {
         return __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a, b, c, idx, 0, ABID);
     }
 };
 template <> struct Mma<s24_half> {
-    static __device__ __forceinline__ f32x16 dense(bf16x8 a, bf16x8 b, f32x16 c)
-    {
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-    }
     static __device__ __forceinline__ void dense16(bf16x8 a, bf16x8 b, f32x4 &c) { S24_MFMA_16X16X32("f16", a, b, c); }
+    template <int ABID> static __device__ __forceinline__ void sparse16(bf16x8 a, bf16x16 b, f32x4 &c, uint32_t idx)
+    {
+        if constexpr (ABID == 0) S24_SMFMAC_16X16X64("f16", "0", a, b, c, idx);
+        else S24_SMFMAC_16X16X64("f16", "1", a, b, c, idx);
+    }
     template <int ABID> static __device__ __forceinline__ f32x16 sparse(bf16x8 a, bf16x16 b, f32x16 c, int idx)
     {
         return __builtin_amdgcn_smfmac_f32_32x32x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x16, b), c, idx, 0, ABID);
@@ -86,22 +93,27 @@ __device__ __forceinline__ bf16x16 as_bf16x16(uint4 lo, uint4 hi)
 
 // ------------------------------------------------------------------ sparse NT
 // Large tile: workgroup tile 256 (m) x 256 (n) x 64 (k), eight waves as 2 (m) x 4 (n), each
-// wave 128 x 64 = 4 x 2 accumulator tiles.  Both operands are copied from
+// wave 128 x 64 = 8 x 4 accumulator blocks of 16 x 16.  Both operands are copied from
 // global memory straight into LDS (no register staging) through a ring of
-// three 50 KB stages; the copies of chunk kc+3 go out while the second half of chunk kc is
-// multiplied, and the one barrier of a chunk sits between its two halves, where the matrix unit
-// still has the second half's operands in registers (see the main loop).  LDS layouts: dense operand rows of 128 bytes with the
-// 16-byte chunk c of row r at slot c ^ ((r ^ r>>3) & 7); compressed operand
-// rows of 64 bytes with chunk c at slot c ^ ((r>>2) & 3).  Both keep any 16
-// consecutive lanes of an operand read on distinct 16-byte slots modulo 256
-// bytes, which is what a full-rate 128-bit LDS read needs on this chip.
+// three 50 KB stages; the one barrier of a chunk sits between its two halves, where the matrix unit
+// still has the second half's operands in registers, and the copies of chunk kc+3 go out from that barrier to the next
+// (see the main loop).  LDS layouts: dense operand rows of 128 bytes with the
+// 16-byte chunk c of row r at slot c ^ ((r>>1) & 7); compressed operand
+// rows of 64 bytes with chunk c at slot c ^ (-(r>>2) & 3).  A full-rate 128-bit LDS read needs distinct 16-byte slots modulo
+// 256 bytes in each group of 16 lanes it takes at a time, which are lanes 0-3, 12-15 and 20-27 (and 4-11, 16-19, 28-31) of
+// each half wave: rows 0-3 and 12-15 of one k quarter beside rows 4-11 of the next.  Both layouts give that, and for 16
+// consecutive rows of one quarter (c ^ (r>>2) alone does not: 260 conflict cycles per chunk of 1600).
+// The 16-wide sparse instruction alone holds 1.81 GHz where the 32-wide one holds 1.62 (3.65 against 3.31 PFLOP/s
+// dense-equivalent on random operands).  What bounds the kernel is the path of the copies together with that clock:
+// 8192 x 8192 x 28672 1719 -> 1656 us, with M and K exchanged 1626 -> 1566, 16384 x 5120, K = 1280 122 -> 114.
 namespace big {
 constexpr int BM = 256, BN = 256, THREADS = 512;   // the large tile
 typedef __attribute__((address_space(3))) void *lds_ptr;
 typedef const __attribute__((address_space(1))) void *glb_ptr;
 
-__device__ __forceinline__ int b_slot(int row, int c) { return row * 128 + ((c ^ ((row ^ (row >> 3)) & 7)) << 4); }
-__device__ __forceinline__ int a_slot(int row, int c) { return row * 64 + ((c ^ ((row >> 2) & 3)) << 4); }
+__device__ __forceinline__ int b_slot(int row, int c) { return row * 128 + ((c ^ ((row >> 1) & 7)) << 4); }
+__device__ __forceinline__ int a_swizzle(int row) { return -(row >> 2) & 3; }
+__device__ __forceinline__ int a_slot(int row, int c) { return row * 64 + ((c ^ a_swizzle(row)) << 4); }
 
 // Buffer descriptor for direct-to-LDS copies: base address in scalar registers, raw (unstructured) addressing, no
 // bounds clamp that the kernels rely on (every offset they form is inside the operand and below 4 GB, which the host
@@ -176,62 +188,53 @@ __device__ __forceinline__ void clock_report(unsigned long long *probe, const Cl
     }
 }
 
-// Output of one wave's 64 (n) x 128 (m) accumulator tile as bf16.  The wave parks the tile in LDS as
-// 64 rows of 256 bytes and streams it out 16 bytes per lane, 16 lanes covering one 256-byte row
-// segment of the output.  Inside a row the 8-byte unit u is stored at u ^ (row & 31), so the
-// accumulator writes of 32 consecutive rows (same u) fall on distinct banks; a 16-byte read gets
-// units 2c and 2c+1 from one aligned slot, in swapped order on odd rows.
+// Output of one wave's 64 (n) x 32 MI (m) accumulator tile as bf16.  The wave parks the tile in LDS as
+// 64 rows of 64 MI bytes and streams it out 16 bytes per lane, LPR lanes covering one row
+// segment of the output.  Inside a row the 8-byte unit u is stored at u ^ stage_swizzle(row), an even number, so the
+// accumulator writes of 32 lanes (16 rows, two neighbouring units) fall on distinct banks and a 16-byte piece stays whole.
 // `estage` is EWAVE bytes of LDS private to the wave and no longer used for anything else.
-// A wave tile has MI accumulator blocks along m (4: 128 features, rows of 256 bytes; 2: 64 features, rows of 128
-// bytes whose units are swizzled with row & 15).
+// MI = 4: 128 features, rows of 256 bytes; 2: 64 features, rows of 128 bytes, two to a round of the banks.
 constexpr int EWAVE = 64 * 256;
+template <int MI> __device__ __forceinline__ int stage_swizzle(int nl) { return MI == 4 ? 2 * (nl & 15) : 2 * ((nl >> 1) & 7); }
 template <typename T, int MI>
-__device__ __forceinline__ void stage_tile(const f32x16 (&acc)[MI][2], unsigned char *estage, int lane)
+__device__ __forceinline__ void stage_tile(const f32x4 (&acc)[2 * MI][4], unsigned char *estage, int lane)
 {
-    constexpr int RB = 64 * MI, UMASK = 8 * MI - 1;
+    constexpr int RB = 64 * MI;
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni)
+    for (int ni = 0; ni < 4; ++ni)
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-                const int nl = 32 * ni + (lane & 31), u = 8 * mi + 2 * g4 + (lane >> 5);
-                *reinterpret_cast<uint2 *>(estage + nl * RB + ((u ^ (nl & UMASK)) << 3)) =
-                    make_uint2(s24_num<T>::pack2(acc[mi][ni][4 * g4], acc[mi][ni][4 * g4 + 1]),
-                               s24_num<T>::pack2(acc[mi][ni][4 * g4 + 2], acc[mi][ni][4 * g4 + 3]));
-            }
+        for (int mi = 0; mi < 2 * MI; ++mi) {
+            const int nl = 16 * ni + (lane & 15), u = 4 * mi + (lane >> 4);
+            *reinterpret_cast<uint2 *>(estage + nl * RB + ((u ^ stage_swizzle<MI>(nl)) << 3)) =
+                make_uint2(s24_num<T>::pack2(acc[mi][ni][0], acc[mi][ni][1]), s24_num<T>::pack2(acc[mi][ni][2], acc[mi][ni][3]));
+        }
 }
-// Z = X W^T + d (Sec. 5.2 step 2): adds the bias of output feature m to the wave's 128 (m) x 64 (n) accumulator
+// Z = X W^T + d (Sec. 5.2 step 2): adds the bias of output feature m to the wave's 32 MI (m) x 64 (n) accumulator
 // tile before it is rounded.  `bias` points at the entry of the tile's first feature; features at or past `limit`
 // (edge tiles; never stored) read the last four valid entries instead.
 template <typename T, int MI>
-__device__ __forceinline__ void add_bias(f32x16 (&acc)[MI][2], const uint16_t *__restrict__ bias, int limit, int lane)
+__device__ __forceinline__ void add_bias(f32x4 (&acc)[2 * MI][4], const uint16_t *__restrict__ bias, int limit, int lane)
 {
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
+    for (int mi = 0; mi < 2 * MI; ++mi) {
+        const int m = min(16 * mi + 4 * (lane >> 4), limit - 4);
+        const uint2 b = *reinterpret_cast<const uint2 *>(bias + m);
+        const float b4[4] = {s24_num<T>::lo(b.x), s24_num<T>::hi(b.x), s24_num<T>::lo(b.y), s24_num<T>::hi(b.y)};
 #pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-            const int m = min(32 * mi + 8 * g4 + 4 * (lane >> 5), limit - 4);
-            const uint2 b = *reinterpret_cast<const uint2 *>(bias + m);
-            const float b4[4] = {s24_num<T>::lo(b.x), s24_num<T>::hi(b.x), s24_num<T>::lo(b.y), s24_num<T>::hi(b.y)};
+        for (int ni = 0; ni < 4; ++ni)
 #pragma unroll
-            for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[mi][ni][4 * g4 + e] += b4[e];
-        }
-        // four loads in flight at a time: all sixteen at once would not fit beside the 128 accumulators
-        __builtin_amdgcn_sched_barrier(0);
+            for (int e = 0; e < 4; ++e) acc[mi][ni][e] += b4[e];
+        // four loads in flight at a time: all at once would not fit beside the accumulators
+        if (mi % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
 }
 // 16-byte chunk c (eight bf16, columns 8c .. 8c+7) of row nl of a staged tile
 template <int MI = 4> __device__ __forceinline__ uint4 staged_chunk(const unsigned char *estage, int nl, int c)
 {
-    const int x = nl & (8 * MI - 1);
-    const uint4 v = *reinterpret_cast<const uint4 *>(estage + nl * (64 * MI) + ((((2 * c) ^ x) & ~1) << 3));
-    return (x & 1) ? make_uint4(v.z, v.w, v.x, v.y) : v;
+    return *reinterpret_cast<const uint4 *>(estage + nl * (64 * MI) + (((2 * c) ^ stage_swizzle<MI>(nl)) << 3));
 }
 template <typename T, int MI>
-__device__ __forceinline__ void staged_store(const f32x16 (&acc)[MI][2], unsigned char *estage, uint16_t *__restrict__ Out,
+__device__ __forceinline__ void staged_store(const f32x4 (&acc)[2 * MI][4], unsigned char *estage, uint16_t *__restrict__ Out,
                                              int N, int M, int n_base, int m_base, int lane)
 {
     stage_tile<T, MI>(acc, estage, lane);
@@ -321,167 +324,173 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int row = 32 * wave + 8 * i + (lane >> 3);
-        const int c = (lane & 7) ^ ((row ^ (row >> 3)) & 7);
+        const int c = (lane & 7) ^ ((row >> 1) & 7);
         ob[i] = ((uint32_t)(min(n0 + row, N - 1) - n0) * (uint32_t)K + 8u * c) * 2u;   // a tile's rows span < 4 GB (host check)
     }
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
         const int row = 16 * NA * wave + 16 * i + (lane >> 2);
-        const int c = (lane & 3) ^ ((row >> 2) & 3);
+        const int c = (lane & 3) ^ a_swizzle(row);
         oa[i] = ((uint32_t)a_row(row) * 32u + 8u * c) * 2u;
     }
     // index words: 4-byte direct-to-LDS copies (copy i: row 32 * (NX * wave + i) + lane/2, dword lane%2)
 #pragma unroll
     for (int i = 0; i < NX; ++i) om[i] = ((uint32_t)a_row(32 * (NX * wave + i) + (lane >> 1)) * 4u + 2u * (lane & 1)) * 2u;
-    // Every call issues exactly NC copies per lane (four of the dense operand, NA of the
-    // values, NX of the index words), so the wait counts below are constants; past the last
-    // chunk it re-reads the last one into a stage nobody will read again.
-    auto issue = [&](unsigned char *st, int kc) {
-        kc = min(kc, nk - 1);
-        const rsrc_t pb = buffer_of(baseB + (int64_t)kc * 128), pv = buffer_of(baseV + (int64_t)kc * M * 64);
-        const rsrc_t pm = buffer_of(baseM + (int64_t)kc * M * 8);
+    // Copy c of a chunk's NC per lane: four of the dense operand, NA of the values, NX of the index words.  Every chunk
+    // issues all of them, so the wait counts below are constants; past the last chunk the last one is read again into a
+    // stage nobody will read.  pb, pv, pm: the operands at the chunk.
+    const char *pb = baseB, *pv = baseV, *pm = baseM;
+    auto issue = [&](unsigned char *st, int c) {
+        if (c < 4) buffer_to_lds<16>(buffer_of(pb), (lds_ptr)(st + (32 * wave + 8 * c) * 128), ob[c]);
+        else if (c < 4 + NA) buffer_to_lds<16>(buffer_of(pv), (lds_ptr)(st + B_STAGE + 16 * (NA * wave + c - 4) * 64), oa[c - 4]);
+        else buffer_to_lds<4>(buffer_of(pm), (lds_ptr)(st + B_STAGE + A_STAGE + 256 * (NX * wave + c - 4 - NA)), om[c - 4 - NA]);
+    };
+    // Copy c of the chunk after next but one goes out beside the copy_slot(c)-th matrix instruction from the start of phase B
+    // (see the main loop), EARLY of them in that phase and the rest in phase A of the next chunk: spread over all of a
+    // chunk's 8 MI instructions, not its second half, the copies queue less (28672 features, K = 8192: 1627 -> 1575 us, and
+    // with the waves in phase B preferred, whose copies are the next to be waited for, 1566; twice as dense instead: 1740).
+    constexpr auto copy_slot = [](int c) { return c * 8 * MI / NC; };
+    constexpr int EARLY = (NC + 1) / 2;
+    const int64_t step_v = (int64_t)M * 64, step_m = (int64_t)M * 8;
+    auto advance = [&](int kc) {   // to chunk kc, or not past the last one
+        if (kc < nk) { pb += 128; pv += step_v; pm += step_m; }
+    };
+    auto issue_all = [&](unsigned char *st, int kc) {
+        if (kc > 0) advance(kc);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) buffer_to_lds<16>(pb, (lds_ptr)(st + (32 * wave + 8 * i) * 128), ob[i]);
-#pragma unroll
-        for (int i = 0; i < NA; ++i) buffer_to_lds<16>(pv, (lds_ptr)(st + B_STAGE + 16 * (NA * wave + i) * 64), oa[i]);
-#pragma unroll
-        for (int i = 0; i < NX; ++i) buffer_to_lds<4>(pm, (lds_ptr)(st + B_STAGE + A_STAGE + 32 * (NX * wave + i) * 8), om[i]);
+        for (int c = 0; c < NC; ++c) issue(st, c);
     };
 
-    f32x16 acc[MI][2];
+    f32x4 acc[2 * MI][4];
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+    for (int mi = 0; mi < 2 * MI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = f32x16{};
+        for (int ni = 0; ni < 4; ++ni) acc[mi][ni] = f32x4{};
 
-    // Fragments of one half (h = 0, 1: the two sparse instructions per accumulator tile and 64-chunk) of a stage
-    const int g = lane >> 5;
-    auto load_frags = [&](const unsigned char *st, int h, bf16x16 (&b)[2], bf16x8 (&a)[MI]) {
-        const unsigned char *sb = st, *sa = st + B_STAGE;
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni) {
-            const int row = 64 * wn + 32 * ni + (lane & 31);
-            b[ni] = as_bf16x16(*reinterpret_cast<const uint4 *>(sb + b_slot(row, 2 * h + g)),
-                               *reinterpret_cast<const uint4 *>(sb + b_slot(row, 4 + 2 * h + g)));
-        }
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi) {
-            const int row = WM * wm + 32 * mi + (lane & 31);
-            a[mi] = as_bf16x8(*reinterpret_cast<const uint4 *>(sa + a_slot(row, 2 * g + h)));
-        }
+    // Fragments of a stage: tokens 16 ni .. of the wave, whole 64-chunk (two LDS reads); features 16 mi .. (one read)
+    const int l16 = lane & 15, g = lane >> 4;
+    auto load_b = [&](const unsigned char *st, int ni, int h) {
+        return *reinterpret_cast<const uint4 *>(st + 2048 * ni + b_slot(64 * wn + l16, 4 * h + g));
     };
-    auto load_index = [&](const unsigned char *st, uint32_t (&x)[MI]) {
-        const unsigned char *sm = st + B_STAGE + A_STAGE;
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-            x[mi] = *reinterpret_cast<const uint32_t *>(sm + (WM * wm + 32 * mi + (lane & 31)) * 8 + 4 * g);
+    auto load_a = [&](const unsigned char *st, int mi) {
+        return as_bf16x8(*reinterpret_cast<const uint4 *>(st + B_STAGE + 1024 * mi + a_slot(WM * wm + l16, g)));
     };
+    // the index words of feature blocks 2i and 2i + 1: a lane reads a dword of each (32 of k, two words) and packs its half of both
+    const uint32_t half_sel = (g & 1) ? 0x07060302u : 0x05040100u;
+    auto load_index = [&](const unsigned char *st, int i) {
+        const unsigned char *p = st + B_STAGE + A_STAGE + 256 * i + (WM * wm + l16) * 8 + 4 * (g >> 1);
+        return make_uint2(*reinterpret_cast<const uint32_t *>(p), *reinterpret_cast<const uint32_t *>(p + 128));
+    };
+    auto pack_index = [&](uint2 d) { return __builtin_amdgcn_perm(d.y, d.x, half_sel); };
 
     // keep the program order of these groups: the constant wait counts rely on it
-    issue(s0, 0);
+    issue_all(s0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    issue(s1, 1);
+    issue_all(s1, 1);
     __builtin_amdgcn_sched_barrier(0);
-    issue(s2, 2);
+    advance(2);
+#pragma unroll
+    for (int c = 0; c < EARLY; ++c) issue(s2, c);
     __builtin_amdgcn_sched_barrier(0);
-    wait_and_barrier<2 * NC>();   // chunk 0 has landed for everybody
-    bf16x16 fb0[2];           // first-half fragments and index words of the chunk about to be multiplied
+    wait_and_barrier<NC + EARLY>();   // chunk 0 has landed for everybody
+    uint4 fb[4][2];      // token fragments of the chunk about to be multiplied, first-half feature fragments and index words
     bf16x8 fa0[MI];
-    uint32_t ix[MI];
-    load_index(s0, ix);
-    load_frags(s0, 0, fb0, fa0);
+    uint32_t ix[MI];     // of feature blocks 2i and 2i + 1; the first half of them on entry to a chunk
+#pragma unroll
+    for (int i = 0; i < MI / 2; ++i) ix[i] = pack_index(load_index(s0, i));
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) fa0[mi] = load_a(s0, mi);
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) fb[ni][h] = load_b(s0, ni, h);
 
-    // One chunk, software-pipelined across the workgroup barrier.  On entry the first-half fragments of chunk kc
-    // are in registers.  Phase A: their eight matrix instructions, with the eight LDS reads of the second half
-    // dealt out between them.  Then the one barrier of the chunk: every wave has read all it needs of chunk
+    // One chunk, software-pipelined across the workgroup barrier.  On entry the token fragments of chunk kc and the first
+    // half of its feature fragments are in registers.  Phase A: their 4 MI matrix instructions, with the LDS reads of the
+    // second half's features between them.  Then the one barrier of the chunk: every wave has read all it needs of chunk
     // kc's stage, and chunk kc+1 (copied two chunks ago) has landed for everybody.  Phase B: the second half's
-    // eight matrix instructions, whose operands are already in registers -- so the matrix unit has work while
-    // the first-half fragments of chunk kc+1 come in from LDS and the seven copies of chunk kc+3 go out into the
-    // stage chunk kc just vacated (one per matrix instruction: a wave that issues its copies in one burst sits in
-    // the memory pipeline's queue while the matrix unit idles).  A barrier at the top of the chunk instead, with
-    // nothing in registers, exposed the LDS latency of twelve reads per wave once per chunk.
-    auto chunk = [&](unsigned char *cur, const unsigned char *nxt, int kc) {
-        bf16x16 fb1[2];
+    // matrix instructions, whose operands are already in registers -- so the matrix unit has work while
+    // the fragments of chunk kc+1 come in from LDS, the token fragments each into the registers of the one that has just had its
+    // last use, and the copies of chunk kc+3 begin to go out into the stage chunk kc just vacated (one at a time, see copy_slot;
+    // the others in phase A of the next chunk).  A barrier at the
+    // top of the chunk instead, with nothing in registers, exposed the LDS latency of twelve reads per wave once per chunk.
+    auto chunk = [&](unsigned char *cur, const unsigned char *nxt, unsigned char *prv, int kc) {
         bf16x8 fa1[MI];
-        load_frags(cur, 1, fb1, fa1);
+        uint2 raw[MI / 2];
+        auto multiply = [&](const bf16x8 (&a)[MI], int first, int i) {   // the i-th matrix instruction of a phase
+            const int ni = i / MI, j = i % MI, b = (ni & 1) ? MI - 1 - j : j, mi = first + b;
+            if (mi & 1) Mma<T>::template sparse16<1>(a[b], as_bf16x16(fb[ni][0], fb[ni][1]), acc[mi][ni], ix[mi / 2]);
+            else Mma<T>::template sparse16<0>(a[b], as_bf16x16(fb[ni][0], fb[ni][1]), acc[mi][ni], ix[mi / 2]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+        for (int i = 0; i < 4 * MI; ++i) {
+            multiply(fa0, 0, i);
+            if (i < MI) fa1[i] = load_a(cur, MI + i);
+            if (i >= MI && i < MI + MI / 2) raw[i - MI] = load_index(cur, MI / 2 + i - MI);
 #pragma unroll
-            for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = Mma<T>::template sparse<0>(fa0[mi], fb0[ni], acc[mi][ni], (int)ix[mi]);
-        // second-half reads: four of the dense operand and MI of the compressed one
-        // (the large tile issues them two per matrix instruction in the first half of the phase, so that the last one
-        // has returned before the barrier)
-#pragma unroll
-        for (int i = 0; i < 2 * MI; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (MI == 4 ? i < 4 : i < 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            else if (MI == 2) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            for (int c = EARLY; c < NC; ++c)
+                if (copy_slot(c) - 4 * MI == i) issue(prv, c);
+            __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int i = 0; i < MI / 2; ++i) ix[MI / 2 + i] = pack_index(raw[i]);
+        advance(kc + 3);
         // all but the NC most recent copies (chunk kc+2) are complete: this lane's part of chunk kc+1 is in LDS,
         // and its own LDS reads of chunk kc are done
         wait_and_barrier<NC>();
-        issue(cur, kc + 3);
-        uint32_t ixn[MI];
-        load_index(nxt, ixn);
-        load_frags(nxt, 0, fb0, fa0);
+        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = Mma<T>::template sparse<1>(fa1[mi], fb1[ni], acc[mi][ni], (int)ix[mi]);
-        if constexpr (MI == 4) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                if (i < 6) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-                if (i < NC - 8) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
-                else if (i < NC) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        for (int i = 0; i < 4 * MI; ++i) {
+            multiply(fa1, MI, i);
+            if (i < MI) fa0[i] = load_a(nxt, i);
+            if (i >= MI / 2 && i < MI) raw[i - MI / 2] = load_index(nxt, i - MI / 2);
+            if (i % MI == (i + 1 < 4 * MI ? 0 : MI - 1) && i >= MI) {   // a token block is done: its successor's two reads
+                const int ni = i + 1 < 4 * MI ? i / MI - 1 : 3;
+                if (i + 1 == 4 * MI) __builtin_amdgcn_sched_barrier(0);
+                fb[ni][0] = load_b(nxt, ni, 0);
+                fb[ni][1] = load_b(nxt, ni, 1);
             }
-        } else {   // four matrix instructions: 4 + 2 + 2 reads and 7 copies between them
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                if (i == 0) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-                else if (i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-                if (i < 3) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
-                else __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-            }
+            for (int c = 0; c < EARLY; ++c)
+                if (copy_slot(c) == i) issue(cur, c);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi) ix[mi] = ixn[mi];
+        for (int i = 0; i < MI / 2; ++i) ix[i] = pack_index(raw[i]);
+        mma_operand_gap();
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
     };
     // past the last chunk the prefetched fragments come from a stage that holds a re-read of the last chunk (or
     // is being refilled with one); they are never multiplied
     int kc = 0;
     for (; kc + 3 <= nk; kc += 3) {
-        chunk(s0, s1, kc);
-        chunk(s1, s2, kc + 1);
-        chunk(s2, s0, kc + 2);
+        chunk(s0, s1, s2, kc);
+        chunk(s1, s2, s0, kc + 1);
+        chunk(s2, s0, s1, kc + 2);
     }
-    if (kc < nk) chunk(s0, s1, kc);
-    if (kc + 1 < nk) chunk(s1, s2, kc + 1);
+    if (kc < nk) chunk(s0, s1, s2, kc);
+    if (kc + 1 < nk) chunk(s1, s2, s0, kc + 1);
+    mma_drain();
     // drain the copies still in flight, then reuse the ring as a staging area for the output tile
     wait_and_barrier<0>();
     clock_report(probe, t_start);
     if constexpr (ACCUM) {
         // beta = 1: add the old output in fp32 straight from the accumulators (a single rounding)
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni) {
-            const int n = n0 + 64 * wn + 32 * ni + (lane & 31);
+        for (int ni = 0; ni < 4; ++ni) {
+            const int n = n0 + 64 * wn + 16 * ni + l16;
             if (n >= N) continue;
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4) {
-                    const int m = m0 + WM * wm + 32 * mi + 8 * g4 + 4 * (lane >> 5);
-                    if (m >= M) continue;
-                    uint2 *dst = reinterpret_cast<uint2 *>(Out + (int64_t)n * M + m);
-                    const uint2 old = *dst;
-                    *dst = make_uint2(s24_num<T>::pack2(acc[mi][ni][4 * g4] + s24_num<T>::lo(old.x),
-                                                        acc[mi][ni][4 * g4 + 1] + s24_num<T>::hi(old.x)),
-                                      s24_num<T>::pack2(acc[mi][ni][4 * g4 + 2] + s24_num<T>::lo(old.y),
-                                                        acc[mi][ni][4 * g4 + 3] + s24_num<T>::hi(old.y)));
-                }
+            for (int mi = 0; mi < 2 * MI; ++mi) {
+                const int m = m0 + WM * wm + 16 * mi + 4 * g;
+                if (m >= M) continue;
+                uint2 *dst = reinterpret_cast<uint2 *>(Out + (int64_t)n * M + m);
+                const uint2 old = *dst;
+                *dst = make_uint2(s24_num<T>::pack2(acc[mi][ni][0] + s24_num<T>::lo(old.x), acc[mi][ni][1] + s24_num<T>::hi(old.x)),
+                                  s24_num<T>::pack2(acc[mi][ni][2] + s24_num<T>::lo(old.y), acc[mi][ni][3] + s24_num<T>::hi(old.y)));
+            }
         }
         return;
     }
@@ -615,12 +624,15 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
 namespace bignt {
 // Dense NT GEMM, 256 x 256 tiles, eight waves of 128 x 64: the comparison kernel beside the sparse one, on the
 // same schedule.  32 of k per ring stage (two 16 KB operand tiles, 64-byte rows), four stages, three chunks in
-// flight; a chunk is two 16-wide steps of eight matrix instructions, the first running from registers while the
-// second's fragments come in, the one barrier of the chunk between them, and after it the next chunk's first-step
-// fragments and the copies of chunk kc+4 dealt out between the second step's matrix instructions.
+// flight; a chunk is two halves of the wave's feature blocks, the first running from registers while the
+// second's fragments come in, the one barrier of the chunk between them, and after it the next chunk's
+// fragments and the copies of chunk kc+4 dealt out between the second half's matrix instructions.
+// 8192 tokens x 28672 features, K = 8192: 2975 -> 2808 us with the 16-wide instruction (1.29 -> 1.37 PFLOP/s), 16384 x 5120,
+// K = 1280: 197 -> 187; 8192 x 1024, K = 4096 (medium tiles): 70 -> 67.
 // MI and WN as in the sparse kernel: 256 x 256 tiles of eight waves, and for outputs with too few of them 256 (m) x 128 (n)
 // and, two workgroups per compute unit, 128 x 128 tiles of four waves.
 using big::a_slot;
+using big::a_swizzle;
 using big::glb_ptr;
 using big::lds_ptr;
 using big::wait_vm_lgkm0;
@@ -658,93 +670,109 @@ __global__ __launch_bounds__(128 * WN) void dense_nt_big_kernel(const uint16_t *
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int row = 16 * (2 * wave + i) + (lane >> 2);
-        const int c = (lane & 3) ^ ((row >> 2) & 3);
+        const int c = (lane & 3) ^ a_swizzle(row);
         ox[i] = ((uint32_t)(min(n0 + row, N - 1) - n0) * (uint32_t)K + 8u * c) * 2u;
     }
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
         const int row = 16 * (NW * wave + i) + (lane >> 2);
-        const int c = (lane & 3) ^ ((row >> 2) & 3);
+        const int c = (lane & 3) ^ a_swizzle(row);
         ow[i] = ((uint32_t)(min(m0 + row, M - 1) - m0) * (uint32_t)K + 8u * c) * 2u;
     }
-    // exactly NC copies per lane and call; past the last chunk it re-reads the last one into a stage nobody reads
-    auto issue = [&](unsigned char *st, int kc) {
-        kc = min(kc, nk - 1);
-        const big::rsrc_t px = big::buffer_of(baseX + (int64_t)kc * 64), pw = big::buffer_of(baseW + (int64_t)kc * 64);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) big::buffer_to_lds<16>(px, (lds_ptr)(st + 16 * (2 * wave + i) * 64), ox[i]);
-#pragma unroll
-        for (int i = 0; i < NW; ++i) big::buffer_to_lds<16>(pw, (lds_ptr)(st + OPERAND + 16 * (NW * wave + i) * 64), ow[i]);
+    // copies over both phases of the main loop, as in the sparse kernel
+    constexpr auto copy_slot = [](int c) { return c * 8 * MI / NC; };
+    constexpr int EARLY = (NC + 1) / 2;
+    // copy c of a chunk's NC per lane; every chunk issues all of them, past the last one it re-reads that into a stage nobody reads
+    const char *px = baseX, *pw = baseW;
+    auto issue = [&](unsigned char *st, int c) {
+        if (c < 2) big::buffer_to_lds<16>(big::buffer_of(px), (lds_ptr)(st + 16 * (2 * wave + c) * 64), ox[c]);
+        else big::buffer_to_lds<16>(big::buffer_of(pw), (lds_ptr)(st + OPERAND + 16 * (NW * wave + c - 2) * 64), ow[c - 2]);
     };
-    f32x16 acc[MI][2];
+    auto advance = [&](int kc) {   // to chunk kc, or not past the last one
+        if (kc < nk) { px += 64; pw += 64; }
+    };
+    auto issue_all = [&](unsigned char *st, int kc) {
+        if (kc > 0) advance(kc);
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+        for (int c = 0; c < NC; ++c) issue(st, c);
+    };
+    f32x4 acc[2 * MI][4];
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = f32x16{};
-    // fragments of 16-wide step i of a stage: lane group g = lane / 32 takes source chunk 2 g + i of both operands
-    const int g = lane >> 5;
-    auto load_frags = [&](const unsigned char *st, int i, bf16x8 (&b)[2], bf16x8 (&a)[MI]) {
-        const unsigned char *sb = st, *sa = st + OPERAND;
+    for (int mi = 0; mi < 2 * MI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni)
-            b[ni] = as_bf16x8(*reinterpret_cast<const uint4 *>(sb + a_slot(64 * wn + 32 * ni + (lane & 31), 2 * g + i)));
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-            a[mi] = as_bf16x8(*reinterpret_cast<const uint4 *>(sa + a_slot(WM * wm + 32 * mi + (lane & 31), 2 * g + i)));
+        for (int ni = 0; ni < 4; ++ni) acc[mi][ni] = f32x4{};
+    // fragments of a stage: 16 rows x 32 of k, lane group g = lane / 16 takes source chunk g
+    const int l16 = lane & 15, g = lane >> 4;
+    auto load_b = [&](const unsigned char *st, int ni) {
+        return as_bf16x8(*reinterpret_cast<const uint4 *>(st + 1024 * ni + a_slot(64 * wn + l16, g)));
+    };
+    auto load_a = [&](const unsigned char *st, int mi) {
+        return as_bf16x8(*reinterpret_cast<const uint4 *>(st + OPERAND + 1024 * mi + a_slot(WM * wm + l16, g)));
     };
     // keep the program order of these groups: the constant wait counts rely on it
-    issue(s0, 0);
+    issue_all(s0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    issue(s1, 1);
+    issue_all(s1, 1);
     __builtin_amdgcn_sched_barrier(0);
-    issue(s2, 2);
+    issue_all(s2, 2);
     __builtin_amdgcn_sched_barrier(0);
-    issue(s3, 3);
-    __builtin_amdgcn_sched_barrier(0);
-    big::wait_and_barrier<3 * NC>();   // chunk 0 has landed for everybody
-    bf16x8 fb0[2], fa0[MI];
-    load_frags(s0, 0, fb0, fa0);
-    auto chunk = [&](unsigned char *cur, const unsigned char *nxt, int kc) {
-        bf16x8 fb1[2], fa1[MI];
-        load_frags(cur, 1, fb1, fa1);
+    advance(3);
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+    for (int c = 0; c < EARLY; ++c) issue(s3, c);
+    __builtin_amdgcn_sched_barrier(0);
+    big::wait_and_barrier<2 * NC + EARLY>();   // chunk 0 has landed for everybody
+    bf16x8 fb[4], fa0[MI];
 #pragma unroll
-            for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = Mma<T>::dense(fa0[mi], fb0[ni], acc[mi][ni]);
+    for (int mi = 0; mi < MI; ++mi) fa0[mi] = load_a(s0, mi);
 #pragma unroll
-        for (int i = 0; i < 2 * MI; ++i) {   // MI + 2 reads, two per matrix instruction
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (2 * i < MI + 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    for (int ni = 0; ni < 4; ++ni) fb[ni] = load_b(s0, ni);
+    auto chunk = [&](unsigned char *cur, const unsigned char *nxt, unsigned char *prv, int kc) {
+        bf16x8 fa1[MI];
+        auto multiply = [&](const bf16x8 (&a)[MI], int first, int i) {   // the i-th matrix instruction of a phase
+            const int ni = i / MI, j = i % MI, b = (ni & 1) ? MI - 1 - j : j;
+            Mma<T>::dense16(a[b], fb[ni], acc[first + b][ni]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+#pragma unroll
+        for (int i = 0; i < 4 * MI; ++i) {
+            multiply(fa0, 0, i);
+            if (i < MI) fa1[i] = load_a(cur, MI + i);
+#pragma unroll
+            for (int c = EARLY; c < NC; ++c)
+                if (copy_slot(c) - 4 * MI == i) issue(prv, c);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        advance(kc + 4);
         // all but the copies of chunks kc+2 and kc+3 are complete: this lane's part of chunk kc+1 is
         // in LDS, and its own reads of chunk kc are done
         big::wait_and_barrier<2 * NC>();
-        issue(cur, kc + 4);
-        load_frags(nxt, 0, fb0, fa0);
+        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+        for (int i = 0; i < 4 * MI; ++i) {
+            multiply(fa1, MI, i);
+            if (i < MI) fa0[i] = load_a(nxt, i);
+            if (i >= MI && i % MI == 0) fb[i / MI - 1] = load_b(nxt, i / MI - 1);   // each after its last use
+            if (i + 1 == 4 * MI) fb[3] = load_b(nxt, 3);
 #pragma unroll
-            for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = Mma<T>::dense(fa1[mi], fb1[ni], acc[mi][ni]);
-#pragma unroll
-        for (int i = 0; i < 2 * MI; ++i) {   // MI + 2 reads and NC copies
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (2 * i < MI + 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            if (NC == 2 * MI || (NC == 4 ? i & 1 : i > 1)) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            for (int c = 0; c < EARLY; ++c)
+                if (copy_slot(c) == i) issue(cur, c);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(0);
     };
     // past the last chunk the prefetched fragments come from a stage that holds a re-read of the last chunk (or is
     // being refilled with one); they are never multiplied
     int kc = 0;
     for (; kc + 4 <= nk; kc += 4) {
-        chunk(s0, s1, kc);
-        chunk(s1, s2, kc + 1);
-        chunk(s2, s3, kc + 2);
-        chunk(s3, s0, kc + 3);
+        chunk(s0, s1, s3, kc);
+        chunk(s1, s2, s0, kc + 1);
+        chunk(s2, s3, s1, kc + 2);
+        chunk(s3, s0, s2, kc + 3);
     }
-    if (kc < nk) chunk(s0, s1, kc);
-    if (kc + 1 < nk) chunk(s1, s2, kc + 1);
-    if (kc + 2 < nk) chunk(s2, s3, kc + 2);
+    if (kc < nk) chunk(s0, s1, s3, kc);
+    if (kc + 1 < nk) chunk(s1, s2, s0, kc + 1);
+    if (kc + 2 < nk) chunk(s2, s3, s1, kc + 2);
+    mma_drain();
     big::wait_and_barrier<0>();   // last (redundant) copies drained, nobody reads the ring any more: reuse it
     big::clock_report(probe, t_start);
     constexpr int PER = WN / 2;   // waves that park their output tile in one ring stage
@@ -1155,6 +1183,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
 // three stages, fp32 output through LDS.
 namespace sptn {
 using big::a_slot;
+using big::a_swizzle;
 using big::glb_ptr;
 using big::lds_ptr;
 
@@ -1201,7 +1230,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_tn_big_kernel(const uint16_t *_
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
         const int row = 16 * (NA * wave + i) + (lane >> 2);
-        const int c = (lane & 3) ^ ((row >> 2) & 3);
+        const int c = (lane & 3) ^ a_swizzle(row);
         oa[i] = ((uint32_t)min(m0 + row, M - 1) * 32u + 8u * c) * 2u;
     }
 #pragma unroll
