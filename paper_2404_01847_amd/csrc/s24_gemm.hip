@@ -2,22 +2,19 @@
 // accumulation; the element type only selects the instruction and the epilogue conversions).
 //
 //   sparse NT  out[n][m] = sum_k B[n][k] * A[m][k], A 2:4-compressed along k
-//              (Eq. 2 with A = W, Eq. 3 with A = W^T): v_smfmac_f32_32x32x32_{bf16,f16},
+//              (Eq. 2 with A = W, Eq. 3 with A = W^T): v_smfmac_f32_16x16x64_{bf16,f16},
 //              with the activation forward / backward (Sec. 5.2) and the bias as optional epilogues
 //   sparse TN  dW = S_z(dY^T) X (Eq. 4): the same instruction, the dense operand read through transposing LDS reads
-//   dense  NT  Y = X W^T (Eq. 1, first GEMM; the comparison kernel): v_mfma_f32_32x32x16_{bf16,f16}
+//   dense  NT  Y = X W^T (Eq. 1, first GEMM; the comparison kernel): v_mfma_f32_16x16x32_{bf16,f16}
 //   dense  TN  dW = dY^T X (Eq. 1, third GEMM): v_mfma_f32_16x16x32_{bf16,f16}, both operands copied as they lie in memory,
 //              k-contiguous fragments by ds_read_b64_tr_b16; masked decay (Eq. 10) as an optional epilogue
 // fp32 data takes the kernels of s24_gemm_f32.hip, sparse NT products of few tokens or features those of s24_gemm_slice.hip.
 //
-// Register layout of the sparse instruction (one 32x32 tile, 32 of k):
-// lane l holds for A row l%32 the eight kept values of k in [16*(l/32),
-// 16*(l/32)+16) in order, with their 2-bit positions in bits [2j+1:2j] of the
-// index register half chosen by ABID; for B column l%32, element j holds
-// k = 16*(j/8) + 8*(l/32) + j%8; accumulator i holds row 8*(i/4)+4*(l/32)+i%4
-// of column l%32.  One metadata word (a uint16 per 16 of k) is exactly one
-// lane's index half, and the chunk-major storage of the compressed operand
-// (vals[K/64][M][32], meta[K/64][M][4]) makes the 64-byte value run and the
+// Register layout of the sparse instruction (one 16x16 tile, 64 of k): lane l holds for A row l%16 the eight kept values of
+// k in [16*(l/16), 16*(l/16)+16) in order, with their 2-bit positions in bits [2j+1:2j] of the index register half chosen by
+// ABID; for B column l%16, element j holds k = 32*(j/8) + 8*(l/16) + j%8; accumulator i holds row 4*(l/16)+i of column l%16.
+// One metadata word (a uint16 per 16 of k) is exactly one lane's index half, and the chunk-major storage of the compressed
+// operand (vals[K/64][M][32], meta[K/64][M][4]) makes the 64-byte value run and the
 // four index words of one row and chunk contiguous, rows back to back.
 #include <algorithm>
 #include <type_traits>
@@ -30,7 +27,6 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) __bf16 bf16x16;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(16))) _Float16 f16x16;
@@ -64,10 +60,6 @@ template <> struct Mma<uint16_t> {
         if constexpr (ABID == 0) S24_SMFMAC_16X16X64("bf16", "0", a, b, c, idx);
         else S24_SMFMAC_16X16X64("bf16", "1", a, b, c, idx);
     }
-    template <int ABID> static __device__ __forceinline__ f32x16 sparse(bf16x8 a, bf16x16 b, f32x16 c, int idx)
-    {
-        return __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a, b, c, idx, 0, ABID);
-    }
 };
 template <> struct Mma<s24_half> {
     static __device__ __forceinline__ void dense16(bf16x8 a, bf16x8 b, f32x4 &c) { S24_MFMA_16X16X32("f16", a, b, c); }
@@ -75,10 +67,6 @@ template <> struct Mma<s24_half> {
     {
         if constexpr (ABID == 0) S24_SMFMAC_16X16X64("f16", "0", a, b, c, idx);
         else S24_SMFMAC_16X16X64("f16", "1", a, b, c, idx);
-    }
-    template <int ABID> static __device__ __forceinline__ f32x16 sparse(bf16x8 a, bf16x16 b, f32x16 c, int idx)
-    {
-        return __builtin_amdgcn_smfmac_f32_32x32x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x16, b), c, idx, 0, ABID);
     }
 };
 
@@ -832,9 +820,6 @@ __device__ __forceinline__ bf16x8 join(v4i16 lo, v4i16 hi)
     struct { v4i16 a, b; } t{lo, hi};
     return __builtin_bit_cast(bf16x8, t);
 }
-// token rows t..t+3 and t+4..t+7 of this lane group's patch
-template <int ROWB>
-__device__ __forceinline__ bf16x8 tr_frag(const unsigned char *p) { return join(tr_half(p), tr_half(p + 4 * ROWB)); }
 
 // DECAY: the masked decay term is added in the epilogue: dW[m][n] += lambda * Wt[m][n] where bit
 // 4*(m%4) + n%4 of mask[m/4][n/4] is clear, with the same single fused multiply-add the stand-alone
@@ -1176,11 +1161,12 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
 // dW[m][n] = sum_t A[m][t] X[t][n] with A = S_z(dY^T) compressed along the tokens (Eq. 4).  The compressed
 // operand takes the sparse NT kernel's path (chunk-major values and index words copied into the same LDS
 // layout, one 128-bit read per fragment), the token-major X tile takes the dense TN kernel's (rows of 512 bytes
-// copied as they lie, fragments gathered with the transposing LDS read).  One sparse instruction covers the
-// tokens {16h .. 16h+15} and {32+16h .. 32+16h+15} of a 64-token chunk (h = 0, 1), which is how the index
-// words split over a lane pair; its dense fragment is therefore two 8-token runs 32 tokens apart.
+// copied as they lie, fragments gathered with the transposing LDS read).  A lane's dense fragment of a 64-token chunk is two
+// 8-token runs 32 tokens apart: four transposing reads.
 // MI and WN as in the sparse NT kernel: 256 x 256 tiles of eight waves, 256 (m) x 128 (n) and 128 x 128 ones of four; ring of
 // three stages, fp32 output through LDS.
+// On the 16-wide instruction, schedule of the NT kernel: 8192 tokens, 8192 x 28672 2044 -> 2014 us, 16384 tokens, 5120 x 1280
+// 121 -> 115, 4160 tokens, 1600 x 6400 54.1 -> 53.3; smaller ones unchanged.
 namespace sptn {
 using big::a_slot;
 using big::a_swizzle;
@@ -1235,115 +1221,139 @@ __global__ __launch_bounds__(128 * WN) void spmm_tn_big_kernel(const uint16_t *_
     }
 #pragma unroll
     for (int i = 0; i < NX; ++i) om[i] = ((uint32_t)min(m0 + 32 * (NX * wave + i) + (lane >> 1), M - 1) * 4u + 2u * (lane & 1)) * 2u;
-    // exactly NC copies per lane and call; past the last chunk it re-reads the last one into a stage nobody
-    // will read again, so that the wait counts below are constants
-    auto issue = [&](unsigned char *st, int kc) {
-        kc = min(kc, nk - 1);
-        const big::rsrc_t px = big::buffer_of(baseX + (int64_t)kc * 128 * N), pv = big::buffer_of(baseV + (int64_t)kc * M * 64);
-        const big::rsrc_t pm = big::buffer_of(baseM + (int64_t)kc * M * 8);
+    // Copy c of a chunk's NC per lane, spread over both phases of the main loop as in the sparse NT kernel; every chunk issues all
+    // of them, past the last one it re-reads that into a stage nobody will read, so that the wait counts below are constants
+    constexpr auto copy_slot = [](int c) { return c * 8 * MI / NC; };
+    constexpr int EARLY = (NC + 1) / 2;
+    const char *px = baseX, *pv = baseV, *pm = baseM;
+    auto issue = [&](unsigned char *st, int c) {
+        if (c < 4) big::buffer_to_lds<16>(big::buffer_of(px), (lds_ptr)(st + (wave * 4 + c) * 1024), ob[c]);
+        else if (c < 4 + NA) big::buffer_to_lds<16>(big::buffer_of(pv), (lds_ptr)(st + B_STAGE + 16 * (NA * wave + c - 4) * 64), oa[c - 4]);
+        else big::buffer_to_lds<4>(big::buffer_of(pm), (lds_ptr)(st + B_STAGE + A_STAGE + 256 * (NX * wave + c - 4 - NA)), om[c - 4 - NA]);
+    };
+    const int64_t step_x = (int64_t)N * 128, step_v = (int64_t)M * 64, step_m = (int64_t)M * 8;
+    auto advance = [&](int kc) {   // to chunk kc, or not past the last one
+        if (kc < nk) { px += step_x; pv += step_v; pm += step_m; }
+    };
+    auto issue_all = [&](unsigned char *st, int kc) {
+        if (kc > 0) advance(kc);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) big::buffer_to_lds<16>(px, (lds_ptr)(st + (wave * 4 + j) * 1024), ob[j]);
-#pragma unroll
-        for (int i = 0; i < NA; ++i) big::buffer_to_lds<16>(pv, (lds_ptr)(st + B_STAGE + 16 * (NA * wave + i) * 64), oa[i]);
-#pragma unroll
-        for (int i = 0; i < NX; ++i) big::buffer_to_lds<4>(pm, (lds_ptr)(st + B_STAGE + A_STAGE + 32 * (NX * wave + i) * 8), om[i]);
+        for (int c = 0; c < NC; ++c) issue(st, c);
     };
 
-    f32x16 acc[MI][2];
+    f32x4 acc[2 * MI][4];
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+    for (int mi = 0; mi < 2 * MI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = f32x16{};
+        for (int ni = 0; ni < 4; ++ni) acc[mi][ni] = f32x4{};
 
-    // X fragment addressing: lane group G = lane/16 -> 8-token half G/2, column half G%2
-    const int gi = lane & 15, G = lane >> 4, g = lane >> 5;
-    const int frow = 8 * (G >> 1) + (gi >> 2), fcol = 16 * (G & 1) + 4 * (gi & 3);
-    int offB[2];
+    // X fragment addressing: lane group g = lane / 16 takes tokens 8g .. 8g+7 and 32 + 8g .. of a chunk, 16 columns per block
+    const int l16 = lane & 15, g = lane >> 4;
+    int offB[4];
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni) offB[ni] = dmatn::tr_off<ROWB>(frow, 64 * wn + 32 * ni + fcol);
-    // Fragments of half h of a stage (the tokens {16h..16h+15} and {32+16h..} of the chunk): eight transposing
-    // reads of the X tile and four 128-bit reads of the values
-    auto load_frags = [&](const unsigned char *st, int h, bf16x16 (&b)[2], bf16x8 (&a)[MI]) {
-        const unsigned char *sb = st, *sa = st + B_STAGE;
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni) {
-            struct { bf16x8 lo, hi; } pair{dmatn::tr_frag<ROWB>(sb + offB[ni] + 16 * h * ROWB),
-                                           dmatn::tr_frag<ROWB>(sb + offB[ni] + (32 + 16 * h) * ROWB)};
-            b[ni] = __builtin_bit_cast(bf16x16, pair);
-        }
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-            a[mi] = as_bf16x8(*reinterpret_cast<const uint4 *>(sa + a_slot(WM * wm + 32 * mi + (lane & 31), 2 * g + h)));
+    for (int ni = 0; ni < 4; ++ni) offB[ni] = dmatn::tr_off<ROWB>(8 * g + (l16 >> 2), 64 * wn + 16 * ni + 4 * (l16 & 3));
+    // Quarter h of X fragment ni (four tokens a lane), value fragments and index words as in the NT kernel
+    auto load_b = [&](const unsigned char *st, int ni, int h) {
+        return dmatn::tr_half(st + offB[ni] + (32 * (h >> 1) + 4 * (h & 1)) * ROWB);
     };
-    auto load_index = [&](const unsigned char *st, uint32_t (&x)[MI]) {
-        const unsigned char *sm = st + B_STAGE + A_STAGE;
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-            x[mi] = *reinterpret_cast<const uint32_t *>(sm + (WM * wm + 32 * mi + (lane & 31)) * 8 + 4 * g);
+    auto load_a = [&](const unsigned char *st, int mi) {
+        return as_bf16x8(*reinterpret_cast<const uint4 *>(st + B_STAGE + 1024 * mi + a_slot(WM * wm + l16, g)));
     };
+    const uint32_t half_sel = (g & 1) ? 0x07060302u : 0x05040100u;
+    auto load_index = [&](const unsigned char *st, int i) {
+        const unsigned char *p = st + B_STAGE + A_STAGE + 256 * i + (WM * wm + l16) * 8 + 4 * (g >> 1);
+        return make_uint2(*reinterpret_cast<const uint32_t *>(p), *reinterpret_cast<const uint32_t *>(p + 128));
+    };
+    auto pack_index = [&](uint2 d) { return __builtin_amdgcn_perm(d.y, d.x, half_sel); };
 
     // keep the program order of these groups: the constant wait counts rely on it
-    issue(s0, 0);
+    issue_all(s0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    issue(s1, 1);
+    issue_all(s1, 1);
     __builtin_amdgcn_sched_barrier(0);
-    issue(s2, 2);
+    advance(2);
+#pragma unroll
+    for (int c = 0; c < EARLY; ++c) issue(s2, c);
     __builtin_amdgcn_sched_barrier(0);
-    big::wait_and_barrier<2 * NC>();   // chunk 0 has landed for everybody
-    bf16x16 fb0[2];
+    big::wait_and_barrier<NC + EARLY>();   // chunk 0 has landed for everybody
+    struct Quarters { dmatn::v4i16 q[4]; };
+    Quarters fb[4];
     bf16x8 fa0[MI];
     uint32_t ix[MI];
-    load_index(s0, ix);
-    load_frags(s0, 0, fb0, fa0);
+#pragma unroll
+    for (int i = 0; i < MI / 2; ++i) ix[i] = pack_index(load_index(s0, i));
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) fa0[mi] = load_a(s0, mi);
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni)
+#pragma unroll
+        for (int h = 0; h < 4; ++h) fb[ni].q[h] = load_b(s0, ni, h);
 
     // One chunk, pipelined across the workgroup barrier exactly as in the NT kernel: the first half's matrix
-    // instructions run from registers while the second half's fragments come in; after the one barrier of the chunk
-    // the second half's matrix instructions cover the next chunk's index words and first-half fragments and the
-    // copies of chunk kc+3 into the stage just vacated.
-    auto chunk = [&](unsigned char *cur, const unsigned char *nxt, int kc) {
-        bf16x16 fb1[2];
+    // instructions run from registers while the second half's value fragments come in; after the one barrier of the chunk
+    // the second half's matrix instructions cover the next chunk's fragments, each X fragment's four reads into the registers
+    // of the one that has just had its last use, and the first copies of chunk kc+3 into the stage just vacated.
+    auto chunk = [&](unsigned char *cur, const unsigned char *nxt, unsigned char *prv, int kc) {
         bf16x8 fa1[MI];
-        load_frags(cur, 1, fb1, fa1);
+        uint2 raw[MI / 2];
+        auto multiply = [&](const bf16x8 (&a)[MI], int first, int i) {   // the i-th matrix instruction of a phase
+            const int ni = i / MI, j = i % MI, b = (ni & 1) ? MI - 1 - j : j, mi = first + b;
+            const bf16x16 x = __builtin_bit_cast(bf16x16, fb[ni]);
+            if (mi & 1) Mma<ET>::template sparse16<1>(a[b], x, acc[mi][ni], ix[mi / 2]);
+            else Mma<ET>::template sparse16<0>(a[b], x, acc[mi][ni], ix[mi / 2]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+        for (int i = 0; i < 4 * MI; ++i) {
+            multiply(fa0, 0, i);
+            if (i < MI) fa1[i] = load_a(cur, MI + i);
+            if (i >= MI && i < MI + MI / 2) raw[i - MI] = load_index(cur, MI / 2 + i - MI);
 #pragma unroll
-            for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = Mma<ET>::template sparse<0>(fa0[mi], fb0[ni], acc[mi][ni], (int)ix[mi]);
-#pragma unroll
-        for (int i = 0; i < 2 * MI; ++i) {   // 8 + MI reads
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (MI == 2) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-            else if (i < 6) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            for (int c = EARLY; c < NC; ++c)
+                if (copy_slot(c) - 4 * MI == i) issue(prv, c);
+            __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int i = 0; i < MI / 2; ++i) ix[MI / 2 + i] = pack_index(raw[i]);
+        advance(kc + 3);
         big::wait_and_barrier<NC>();   // this lane's part of chunk kc+1 is in LDS, its own reads of chunk kc are done
-        issue(cur, kc + 3);
-        uint32_t ixn[MI];
-        load_index(nxt, ixn);
-        load_frags(nxt, 0, fb0, fa0);
+        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+        for (int i = 0; i < 4 * MI; ++i) {
+            multiply(fa1, MI, i);
+            if (i < MI) fa0[i] = load_a(nxt, i);
+            if (i >= MI / 2 && i < MI) raw[i - MI / 2] = load_index(nxt, i - MI / 2);
+            if (i >= MI) {   // block i / MI - 1 is done: its successor's four reads beside the MI instructions of the next block
 #pragma unroll
-            for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = Mma<ET>::template sparse<1>(fa1[mi], fb1[ni], acc[mi][ni], (int)ix[mi]);
+                for (int h = 4 / MI * (i % MI); h < 4 / MI * (i % MI + 1); ++h) fb[i / MI - 1].q[h] = load_b(nxt, i / MI - 1, h);
+            }
+            if (i + 1 == 4 * MI) {
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < 2 * MI; ++i) {   // 8 + 2 MI reads and NC copies
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, MI == 2 ? 3 : 2, 0);
-            if (i < NC - 2 * MI) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
-            else if (i < NC) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                for (int h = 0; h < 4; ++h) fb[3].q[h] = load_b(nxt, 3, h);
+            }
+#pragma unroll
+            for (int c = 0; c < EARLY; ++c)
+                if (copy_slot(c) == i) issue(cur, c);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi) ix[mi] = ixn[mi];
+        for (int i = 0; i < MI / 2; ++i) ix[i] = pack_index(raw[i]);
+        mma_operand_gap();
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
     };
     // past the last chunk the prefetched fragments come from a stage that holds a re-read of the last chunk (or is
     // being refilled with one); they are never multiplied
     int kc = 0;
     for (; kc + 3 <= nk; kc += 3) {
-        chunk(s0, s1, kc);
-        chunk(s1, s2, kc + 1);
-        chunk(s2, s0, kc + 2);
+        chunk(s0, s1, s2, kc);
+        chunk(s1, s2, s0, kc + 1);
+        chunk(s2, s0, s1, kc + 2);
     }
-    if (kc < nk) chunk(s0, s1, kc);
-    if (kc + 1 < nk) chunk(s1, s2, kc + 1);
+    if (kc < nk) chunk(s0, s1, s2, kc);
+    if (kc + 1 < nk) chunk(s1, s2, s0, kc + 1);
+    mma_drain();
     big::wait_and_barrier<0>();   // copies drained, nobody reads the ring any more: reuse it
     big::clock_report(probe, t_start);
     // fp32 output through LDS in 16-byte row segments: a wave parks RB row blocks x 64 columns at a time in its part of
@@ -1354,13 +1364,13 @@ __global__ __launch_bounds__(128 * WN) void spmm_tn_big_kernel(const uint16_t *_
 #pragma unroll
     for (int h2 = 0; h2 < MI / RB; ++h2) {
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni)
+        for (int ni = 0; ni < 4; ++ni)
 #pragma unroll
-            for (int mj = 0; mj < RB; ++mj)
+            for (int mj = 0; mj < 2 * RB; ++mj)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int row = 32 * mj + 8 * (e / 4) + 4 * (lane >> 5) + (e & 3), col = 32 * ni + (lane & 31);
-                    *reinterpret_cast<float *>(est + row * 256 + col * 4) = acc[RB * h2 + mj][ni][e];
+                for (int e = 0; e < 4; ++e) {   // 16-byte piece c of row r sits at slot c ^ (r & 12)
+                    const int row = 16 * mj + 4 * g + e, c4 = 4 * ni + (l16 >> 2);
+                    *reinterpret_cast<float *>(est + row * 256 + ((c4 ^ (row & 12)) << 4) + (l16 & 3) * 4) = acc[2 * RB * h2 + mj][ni][e];
                 }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(big::wait_vm_lgkm0(0));   // the wave reads back only what it wrote itself
@@ -1378,7 +1388,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_tn_big_kernel(const uint16_t *_
                 const int m = m0 + WM * wm + 32 * RB * h2 + row, n = n0 + 64 * wn + 4 * c4;
                 live[b] = m < M && n < N;   // N is a multiple of 16: the four columns are all in or all out
                 const int mc = min(m, M - 1), nc = min(n, N - 4);
-                v[b] = *reinterpret_cast<const float4 *>(est + row * 256 + c4 * 16);
+                v[b] = *reinterpret_cast<const float4 *>(est + row * 256 + ((c4 ^ (row & 12)) << 4));
                 if (ACCUM) old[b] = *reinterpret_cast<const float4 *>(dW + (int64_t)mc * N + nc);
                 if (DECAY) {
                     wv[b] = *reinterpret_cast<const uint2 *>(Wt + (int64_t)mc * N + nc);
