@@ -1823,12 +1823,13 @@ dmatn::DwWindow dw_window(const DwProblem &pr, DwTile tile, int64_t m_off, int64
     w.lambda = pr.lambda;
     return w;
 }
-// Tile of a grid that the large tile does not fill, by cost in us (measured over 128-16384 tokens and layers of 256 x 1024 to
-// 1280 x 5120; the bits are the same).  Per 32 tokens: small tiles 0.48 with two workgroups per compute unit and 0.22 with
-// one, medium ones 0.42 and 0.32 with few, large ones 0.85 and 0.52; on top of that the filling and draining of a tile.  The
-// small tile reads 32 KB of LDS per 16 KB copied, the medium one 48 per 24 for twice the work: where the small tile needs two
-// workgroups per compute unit and the medium one does not, that is 8192 tokens x 768 x 3072 (both gradients) 106 -> 90 us,
-// 8192 x 1024 x 4096 124 -> 113.
+// Tile of a grid that the large tile does not fill, by cost in us (fitted to every tile's time at 40 pairs of gradients, 128-11000
+// tokens, layers of 256 x 768 to 1408 x 4608; the bits are the same).  Per 32 tokens: small tiles 0.53 with two workgroups per
+// compute unit and 0.18 with one, medium ones 0.45 and 0.24 with few, large ones 0.75 and 0.43; on top of that the filling and
+// draining of a tile.  The small tile reads 32 KB of LDS per 16 KB copied, the medium one 48 per 24 for twice the work: where the
+// small tile needs two workgroups per compute unit and the medium one does not, that is 8192 tokens x 768 x 3072 (both
+// gradients) 106 -> 90 us, 8192 x 1024 x 4096 124 -> 113.  The large tile gained most from the 16-wide instruction and is the
+// cheapest from 0.7 of a round on: 5504 tokens x 1408 x 3776 (both) small 122, medium 125, large 111 us; 8000 tokens 173, 177, 160.
 DwTile dw_few_tile(const DwProblem *pr, int count)
 {
     const int64_t cus = s24_cu_count();
@@ -1840,9 +1841,9 @@ DwTile dw_few_tile(const DwProblem *pr, int count)
     auto rest = [&](DwTile t, int64_t per) { return (double)(tiles[(int)t] % per) / per; };
     auto full = [&](DwTile t, int64_t per) { return (double)(tiles[(int)t] / per); };
     const double rl = rest(DwTile::Large, cus), rm = rest(DwTile::Medium, cus), rs = rest(DwTile::Small, 2 * cus);
-    const double l = 15.3 + chunks * (0.85 * full(DwTile::Large, cus) + (rl > 0 ? 0.52 + 0.3 * rl : 0));
-    const double m = 10.8 + chunks * (0.42 * full(DwTile::Medium, cus) + (rm > 0 ? 0.32 + 0.1 * rm : 0));
-    const double s = 9.8 + chunks * (0.48 * full(DwTile::Small, 2 * cus) + (rs > 0.5 ? 0.45 : rs > 0 ? 0.22 : 0));
+    const double l = 14.6 + chunks * (0.75 * full(DwTile::Large, cus) + (rl > 0 ? 0.43 + 0.22 * rl : 0));
+    const double m = 9.7 + chunks * (0.45 * full(DwTile::Medium, cus) + (rm > 0 ? 0.24 + 0.12 * rm : 0));
+    const double s = 7.0 + chunks * (0.53 * full(DwTile::Small, 2 * cus) + (rs > 0.5 ? 0.38 : rs > 0 ? 0.18 : 0));
     return s <= m && s <= l ? DwTile::Small : m <= l ? DwTile::Medium : DwTile::Large;
 }
 // small tile: 32 tokens per stage when there are more tiles than compute units, else 64
