@@ -954,12 +954,16 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     };
     // The last chunk of a token count that is not a multiple of BT holds BT - rem rows that must not contribute:
     // the leading rows that its predecessor already covered (the chunk starts at T - BT), or, when there are
-    // fewer than BT tokens in all, the trailing rows past T.  They are cleared in the dY tile.
+    // fewer than BT tokens in all, the trailing rows past T.  They are cleared in both tiles: in one alone, an infinity in
+    // the other would make a NaN.
     auto clear_tail = [&](unsigned char *st, int kc) {
         const int rem = T - kc * BT, skip = T >= BT ? 0 : rem;
-        constexpr int CPR = ROWA / 16;
-        for (int idx = tid; idx < (BT - rem) * CPR; idx += THREADS)
-            *reinterpret_cast<uint4 *>(st + (skip + idx / CPR) * ROWA + ((idx % CPR) << 4)) = make_uint4(0, 0, 0, 0);
+        auto clear = [&](unsigned char *rows, int row_bytes) {
+            for (int at = 16 * tid; at < (BT - rem) * row_bytes; at += 16 * THREADS)
+                *reinterpret_cast<uint4 *>(rows + skip * row_bytes + at) = make_uint4(0, 0, 0, 0);
+        };
+        clear(st, ROWA);
+        clear(st + OPERAND, ROWX);
         __syncthreads();
     };
     const bool partial = (T % BT) != 0;

@@ -544,3 +544,24 @@ def test_backward_of_few_tokens_and_many_features_keeps_the_plain_products_bits(
         s24.spmm_bwd_dx_act(dY, vt, mt, Z, dZ, act)
         s24.act_bwd(dH, Z, two, act)
         assert torch.equal(dZ.view(torch.int16), two.view(torch.int16))
+
+
+# ------------------------------------------------------------------ 16-bit weight gradients of ragged token counts
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+# fewer tokens than one 32-token step of the contraction, and two to four steps with a remainder
+@pytest.mark.parametrize("p", [1, 31, 33, 48, 63, 70, 100])
+def test_weight_gradient_of_a_ragged_token_count_keeps_infinities(s24, dtype, p):
+    """Tokens that a ragged chunk holds twice, or holds instead of ones past the last, contribute nothing."""
+    r, q = 768, 3072     # alone 144 small tiles, 64 tokens to a stage; as a pair 288 of them, 32 to a stage
+    dY, X = dev_bf16(si.random_matrix(160 + p, (p, r), 1e-2, dtype)), dev_bf16(si.random_matrix(161 + p, (p, q), 1.0, dtype))
+    dY[dY == 0] = 1.0    # zero times infinity is another case
+    at = {5: p - 1, 6: max(p - 20, 0), 7: max(p - 40, 0), 8: 0}
+    for col, t in at.items():
+        X[t, col] = float("inf")
+    single, pair = torch.zeros((r, q), device="cuda"), [torch.zeros((r, q), device="cuda") for _ in range(2)]
+    s24.dense_dw(dY, X, single)
+    s24.dense_dw_batch([(dY, X, dW, None, None, 0.0) for dW in pair])
+    for dW in (single, *pair):
+        for col, t in at.items():
+            assert torch.equal(dW[:, col], torch.copysign(torch.full((r,), float("inf"), device="cuda"), dY[t].float())), (p, t)
+        assert torch.isfinite(dW[:, 9:]).all()
