@@ -883,31 +883,35 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     const int nk = (T + BT - 1) / BT;
 
     // Copies: instruction g of an operand fills the 16-byte slots 64g .. 64g+63 of its stage region, slot ->
-    // (row = slot / slots per row, chunk = the rest); the source chunk is chunk ^ (4 * (row & 3)).  Columns past the
-    // matrix edge are clamped to its last 16-byte chunk.  A lane's byte offsets from the first token row of a
-    // chunk are fixed for the whole kernel; only the (wave-uniform) row base moves, so a copy costs no vector
-    // arithmetic.  A chunk always starts at a row that leaves BT rows below it: the last chunk of a token count
-    // that is not a multiple of BT starts at T - BT and overlaps its predecessor (clear_tail drops the overlap);
-    // with fewer than BT tokens in all there is one chunk, rows past T - 1 re-read row T - 1.
+    // (row = slot / slots per row, chunk = the rest); the source chunk is chunk ^ tr_swizzle(row).  Columns past the
+    // matrix edge are clamped to its last 16-byte chunk.  A lane's byte offsets from the first token row of its copies
+    // are fixed for the whole kernel; only the (wave-uniform) row base moves, so a copy costs no vector
+    // arithmetic.  The tokens of a 32-token step are contiguous rows, and always 32 of them: the step that would reach past
+    // the last token starts at T - 32 and overlaps its predecessor (clear_tail drops the overlap), and so does one that would
+    // lie past it altogether; with fewer than 32 tokens in all, rows past T - 1 re-read row T - 1.  Which tokens one matrix
+    // instruction sums therefore does not depend on the tile or its BT, nor do the bits of the result.  (A stage of two steps
+    // that started at T - 64 as a whole gave other bits than two stages of one for T % 64 of 33 to 63.)
+    const int part = wave * KS / 4;   // the step of a stage whose rows this wave copies
+    static_assert(KS <= 2 && BT / 4 <= 32, "a wave copies rows of one step");
     uint32_t voffA[NIA], voffB[NIX];
     const int lastA = (min(M - m0, BM) >> 3) - 1, lastB = (min(N - n0, BN) >> 3) - 1;
 #pragma unroll
     for (int j = 0; j < NIA; ++j) {
         constexpr int CPR = ROWA / 16;
-        const int slot = (wave * NIA + j) * 64 + lane, row = min(slot / CPR, T - 1), c = (slot % CPR) ^ tr_swizzle(slot / CPR);
+        const int slot = (wave * NIA + j) * 64 + lane, row = min(slot / CPR - 32 * part, T - 1), c = (slot % CPR) ^ tr_swizzle(slot / CPR);
         voffA[j] = (uint32_t)(row * ldy + m0 + 8 * min(c, lastA)) * 2u;
     }
 #pragma unroll
     for (int j = 0; j < NIX; ++j) {
         constexpr int CPR = ROWX / 16;
-        const int slot = (wave * NIX + j) * 64 + lane, row = min(slot / CPR, T - 1), c = (slot % CPR) ^ tr_swizzle(slot / CPR);
+        const int slot = (wave * NIX + j) * 64 + lane, row = min(slot / CPR - 32 * part, T - 1), c = (slot % CPR) ^ tr_swizzle(slot / CPR);
         voffB[j] = (uint32_t)(row * ldx + n0 + 8 * min(c, lastB)) * 2u;
     }
-    auto first_row = [&](int kc) { return max(min(kc * BT, T - BT), 0); };
+    auto first_row = [&](int kc) { return max(min(kc * BT + 32 * part, T - 32), 0); };   // of this wave's copies
     const char *baseA = reinterpret_cast<const char *>(dY), *baseB = reinterpret_cast<const char *>(X);
     // Copy c of a chunk's list (the dY tile's NIA, then the X tile's NIX), rowsA and rowsB its first token row.
-    // The copies are buffer loads into LDS: a descriptor (scalar registers) whose base is the chunk's first token
-    // row, and the lane's fixed 32-bit offset; nothing of a copy's address is computed on the vector unit.
+    // The copies are buffer loads into LDS: a descriptor (scalar registers) whose base is the first of those token
+    // rows, and the lane's fixed 32-bit offset; nothing of a copy's address is computed on the vector unit.
     auto issue = [&](unsigned char *st, const char *rowsA, const char *rowsB, int c) {
         if (c < NIA) big::buffer_to_lds<16>(big::buffer_of(rowsA), (lds_ptr)(st + (wave * NIA + c) * 1024), voffA[c]);
         else big::buffer_to_lds<16>(big::buffer_of(rowsB), (lds_ptr)(st + OPERAND + (wave * NIX + c - NIA) * 1024), voffB[c - NIA]);
@@ -926,7 +930,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     // fragment addressing of this lane: group G = lane/16 takes tokens 8G .. 8G+7 of a step, 16 columns per block
     const int gi = lane & 15, G = lane >> 4;
     const int frow = 8 * G + (gi >> 2), fcol = 4 * (gi & 3);
-    // Byte offsets of a lane's fragments from a stage, and the same plus 64 KB for the upper two stages, whose distance does
+    // Byte offsets of a lane's fragments from a stage, and the same plus two stages for the upper two, whose distance does
     // not fit an instruction's offset field (kept in registers of their own: added on the spot, they were 16 vector
     // instructions per chunk).
     constexpr int FAR = 2 * STAGE;
@@ -952,18 +956,19 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     auto load_b = [&](const unsigned char *st, auto S, int ks, int i, int h) {
         return tr_half((S < 2 ? st + offB[0][i] : st - FAR + offB[1][i]) + (32 * ks + 4 * h) * ROWX);
     };
-    // The last chunk of a token count that is not a multiple of BT holds BT - rem rows that must not contribute:
-    // the leading rows that its predecessor already covered (the chunk starts at T - BT), or, when there are
-    // fewer than BT tokens in all, the trailing rows past T.  They are cleared in both tiles: in one alone, an infinity in
-    // the other would make a NaN.
+    // The last chunk of a token count that is not a multiple of BT holds rows that must not contribute: of each step the
+    // leading ones that its predecessor already covered, or, when there are fewer than 32 tokens in all, the trailing
+    // ones past T.  They are cleared in both tiles: in one alone, an infinity in the other would make a NaN.
     auto clear_tail = [&](unsigned char *st, int kc) {
-        const int rem = T - kc * BT, skip = T >= BT ? 0 : rem;
-        auto clear = [&](unsigned char *rows, int row_bytes) {
-            for (int at = 16 * tid; at < (BT - rem) * row_bytes; at += 16 * THREADS)
-                *reinterpret_cast<uint4 *>(rows + skip * row_bytes + at) = make_uint4(0, 0, 0, 0);
+        auto clear = [&](unsigned char *rows, int bytes) {
+            for (int at = 16 * tid; at < bytes; at += 16 * THREADS) *reinterpret_cast<uint4 *>(rows + at) = make_uint4(0, 0, 0, 0);
         };
-        clear(st, ROWA);
-        clear(st + OPERAND, ROWX);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int live = max(min(T - kc * BT - 32 * ks, 32), 0), row = 32 * ks + (T < 32 ? live : 0);
+            clear(st + row * ROWA, (32 - live) * ROWA);
+            clear(st + OPERAND + row * ROWX, (32 - live) * ROWX);
+        }
         __syncthreads();
     };
     const bool partial = (T % BT) != 0;
@@ -1047,7 +1052,6 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
         if constexpr (KS == 1) {
             step(cur, cs, 0, nxt, ns, 0, refill, 0, next_row, std::integral_constant<int, decltype(cs)::value & 1>());
         } else {
-            static_assert(KS <= 2, "one or two steps per chunk");
             step(cur, cs, 0, cur, cs, 1, refill, 0, -1, c0);
             step(cur, cs, 1, nxt, ns, 0, refill, CPS, next_row, c1);
         }

@@ -565,3 +565,25 @@ def test_weight_gradient_of_a_ragged_token_count_keeps_infinities(s24, dtype, p)
         for col, t in at.items():
             assert torch.equal(dW[:, col], torch.copysign(torch.full((r,), float("inf"), device="cuda"), dY[t].float())), (p, t)
         assert torch.isfinite(dW[:, 9:]).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+# (p, rq, rq of the problem beside it): small tiles alone (64 tokens to a stage) against small (32) and medium tiles in the
+# pair, with a last stage that holds part of one 32-token step or of both; medium tiles alone and large ones in the pair; and
+# an output whose last columns run in small tiles beside large ones, alone one column of large tiles wide, in the pair two
+@pytest.mark.parametrize("case", [(p, (768, 3072), (3072, 768)) for p in (17, 33, 48, 57, 63, 64, 70, 90, 97, 112, 121, 127, 191, 3001)] +
+                         [(5537, (1408, 3776), (3776, 1408))] +
+                         [(p, (2048, 8448), (2048, 8448)) for p in (97, 112, 3001)])
+def test_weight_gradients_have_the_same_bits_in_every_tile(s24, dtype, case):
+    p, a, b = case
+    gen = torch.Generator(device="cuda").manual_seed(p)
+    rnd = lambda n, std: (torch.randn((p, n), generator=gen, device="cuda") * std).to(torch_dtype(dtype))
+    probs = [(rnd(r, 1e-2), rnd(q, 1.0), torch.zeros((r, q), device="cuda"), None, None, 0.0) for r, q in (a, b)]
+    s24.dense_dw_batch(probs)
+    for dY, X, dW, *_ in probs:
+        alone = torch.zeros_like(dW)
+        s24.dense_dw(dY, X, alone)
+        assert torch.equal(alone.view(torch.int32), dW.view(torch.int32)), case
+        rows = torch.cat([torch.arange(0, dW.shape[0], 61), torch.tensor([dW.shape[0] - 1])])
+        ref = host_f64(dY)[:, rows.numpy()].T @ host_f64(X)
+        assert_close(host_f64(dW)[rows.numpy()], ref, F32_TOL, f"dense_dw_batch {case}")
