@@ -2,6 +2,7 @@
 symbol include/s24.h declares, and rejects bad arguments on the host before
 anything is launched.  No kernel runs here."""
 import ctypes as C
+import functools
 import os
 import re
 import subprocess
@@ -315,21 +316,126 @@ def _device_code(path):
     return out
 
 
+@functools.lru_cache(maxsize=None)
 def _registers(operand):
     m = re.fullmatch(r"([av])(\d+)|([av])\[(\d+):(\d+)\]", operand)
     if not m:
-        return set()
+        return frozenset()
     if m.group(1):
-        return {(m.group(1), int(m.group(2)))}
-    return {(m.group(3), k) for k in range(int(m.group(4)), int(m.group(5)) + 1)}
+        return frozenset({(m.group(1), int(m.group(2)))})
+    return frozenset((m.group(3), k) for k in range(int(m.group(4)), int(m.group(5)) + 1))
+
+
+ASM_MATRIX_OPS = ("v_mfma_f32_16x16x32", "v_smfmac_f32_16x16x64")
+OPERAND_GAP, RESULT_GAP = 2, 18   # wait states from a vector write to a matrix instruction, and from one to its result's use
+
+
+def _functions(listing):
+    """llvm-objdump's listing -> {symbol: [(address, op, operands, branch target or None)]}"""
+    out, base = {}, 0
+    for line in listing.splitlines():
+        head = re.match(r"([0-9a-f]+) <(.*)>:$", line)
+        if head:
+            base, code = int(head.group(1), 16), out.setdefault(head.group(2), [])
+        elif line.startswith("\t") and "//" in line:
+            text, _, note = line.partition("//")
+            op, _, rest = text.strip().partition(" ")
+            target = re.search(r"<[^>]*?(?:\+0x([0-9a-f]+))?>$", note.strip()) if "branch" in op else None
+            code.append((int(note.split(":")[0], 16), op, rest, target and base + int(target.group(1) or "0", 16)))
+    return out
+
+
+def _asm_hazards(code):
+    """Places of one function where an operand of a matrix instruction written as asm may have been written by a vector
+    instruction within OPERAND_GAP wait states, or where anything but a matrix instruction adding to the same accumulator may
+    touch a result within RESULT_GAP, on any path.  An instruction counts as one wait state, s_nop as what it says."""
+    step = []   # (wait states, kind, registers read or written, registers written)
+    for _, op, rest, _ in code:
+        args = [a.strip() for a in rest.split(",")] if rest else []
+        regs = [_registers(a.split(" ")[0]) for a in args]
+        every = set().union(*regs)
+        if op == "s_nop":
+            step.append((int(args[0], 0) + 1, "wait", every, set()))
+        elif op.startswith(ASM_MATRIX_OPS):
+            step.append((1, "asm", set().union(*regs[:4]), regs[0]))
+        elif op.startswith(("v_mfma", "v_smfmac")):
+            step.append((1, "matrix", every, regs[0]))
+        elif op.startswith("v_swap"):
+            step.append((1, "vector", every, every))
+        elif op.startswith("v_"):
+            step.append((1, "vector", every, regs[0] if regs else set()))
+        else:
+            step.append((1, "other", every, set()))
+    at = {c[0]: k for k, c in enumerate(code)}
+    assert not any(c[1].startswith(("s_setpc", "s_swappc", "s_call", "s_cbranch_g")) for c in code)
+    starts = sorted({0} | {at[c[3]] for c in code if c[3] is not None} |
+                    {k + 1 for k, c in enumerate(code) if ("branch" in c[1] or c[1] == "s_endpgm") and k + 1 < len(code)})
+    ends = dict(zip(starts, starts[1:] + [len(code)]))
+    entry, found, todo = {0: ({}, {})}, set(), [0]   # block -> (register -> wait states left until usable as operand, as result)
+    while todo:
+        block = todo.pop()
+        ready, done = (dict(s) for s in entry[block])   # -> wait state at which it is usable
+        clock = 0
+        for k in range(block, ends[block]):
+            wait, kind, regs, wrote = step[k]
+            if kind == "asm":
+                found.update((k, r, "operand") for r in regs if ready.get(r, 0) > clock)
+                found.update((k, r, "result") for r in regs - wrote if done.get(r, 0) > clock)
+            elif kind != "matrix":
+                found.update((k, r, "result") for r in regs if done.get(r, 0) > clock)
+            clock += wait
+            if kind == "asm":
+                done.update((r, clock + RESULT_GAP) for r in wrote)
+            elif kind == "vector":
+                ready.update((r, clock + OPERAND_GAP) for r in wrote)
+        left = tuple({r: t - clock for r, t in s.items() if t > clock} for s in (ready, done))
+        _, op, _, target = code[ends[block] - 1]
+        follow = [] if target is None else [at[target]]
+        if op not in ("s_branch", "s_endpgm") and ends[block] < len(code):
+            follow.append(ends[block])
+        for nxt in follow:   # the worst of the paths that meet
+            old = entry.get(nxt)
+            new = left if old is None else tuple({r: max(o.get(r, 0), n.get(r, 0)) for r in {**o, **n}} for o, n in zip(old, left))
+            if new != old:
+                entry[nxt] = new
+                todo.append(nxt)
+    return sorted((code[k][0], code[k][1], code[k][2], r, what) for k, r, what in found)
+
+
+def _listing(*lines):
+    """Lines "op operands" of a function at address 0, four bytes each; "-> n" is a branch to line n."""
+    out = ["0000000000000000 <f>:"]
+    for k, line in enumerate(lines):
+        line, _, to = line.partition(" -> ")
+        out.append(f"\t{line} // {4 * k:012X}: 00000000" + (f" <f+0x{4 * int(to):x}>" if to else ""))
+    return "\n".join(out)
+
+
+def test_hazard_check_follows_every_path_and_operand():
+    dense, sparse = "v_mfma_f32_16x16x32_bf16 a[0:3], v[0:3], v[4:7], a[0:3]", "v_smfmac_f32_16x16x64_f16 v[8:11], v[0:3], v[16:23], v30 abid:1"
+    hazards = lambda *lines: [(a // 4, r, what) for a, _, _, r, what in _asm_hazards(_functions(_listing(*lines))["f"])]
+    drain = ("s_nop 15", "s_nop 1")
+    assert hazards("v_mov_b32_e32 v0, v50", "s_nop 1", dense, dense, *drain, "v_accvgpr_read_b32 v9, a3", "s_endpgm") == []
+    assert hazards("v_mov_b32_e32 v0, v50", "s_nop 0", dense, "s_endpgm") == [(2, ("v", 0), "operand")]
+    assert hazards("v_perm_b32 v30, v1, v2, v3", "s_nop 0", sparse, "s_endpgm") == [(2, ("v", 30), "operand")]
+    assert hazards("v_mov_b32_e32 v9, 0", "s_nop 0", sparse, "s_endpgm") == [(2, ("v", 9), "operand")]      # the accumulator
+    assert hazards("v_accvgpr_write_b32 a2, v9", dense, "s_endpgm") == [(1, ("a", 2), "operand")]
+    assert hazards(dense, "s_nop 15", "s_nop 0", "ds_write_b32 v9, a1", "s_endpgm") == [(3, ("a", 1), "result")]
+    assert hazards(sparse, dense.replace("v[0:3]", "v[8:11]"), "s_endpgm") == [(1, ("v", k), "result") for k in range(8, 12)]
+    # around a loop: the last instruction of the body is just ahead of the first
+    assert hazards("s_mov_b32 s0, 0", sparse, "s_nop 7", "v_mov_b32_e32 v17, 0", "s_cbranch_scc1 65532 -> 1", "s_endpgm") == [(1, ("v", 17), "operand")]
+    # out of it: the fall-through waits, the jump does not
+    assert hazards("s_cbranch_scc0 5 -> 6", sparse, "s_cbranch_scc1 2 -> 5", *drain, "v_mov_b32_e32 v60, v8", "s_endpgm") == [(5, ("v", 8), "result")]
+    # nothing follows a jump but its target
+    assert hazards(sparse, "s_branch 1 -> 3", "v_mov_b32_e32 v60, v8", *drain, "v_mov_b32_e32 v60, v8", "s_endpgm") == []
 
 
 def test_matrix_instructions_written_as_asm_keep_their_distances(lib, tmp_path):
-    """The compiler pads no hazards around the 16-wide matrix instructions in inline asm: no vector instruction may write an operand
-    within two wait states before one, and nothing but another matrix instruction may touch an accumulator within 18 after."""
+    """The compiler pads no hazards around the 16-wide matrix instructions in inline asm; the built library has none."""
     import paper_2404_01847_amd as s24
     objdump = "/opt/rocm/llvm/bin/llvm-objdump"
     if not os.path.exists(objdump):
+        assert not os.path.exists("/opt/rocm/bin/hipcc"), "a compiler without its disassembler: the hazards go unchecked"
         pytest.skip("no llvm-objdump")
     found = 0
     for k, code in enumerate(_device_code(s24.lib_path())):
@@ -337,36 +443,10 @@ def test_matrix_instructions_written_as_asm_keep_their_distances(lib, tmp_path):
             continue
         obj = tmp_path / f"{k}.co"
         obj.write_bytes(code)
-        text = subprocess.run([objdump, "-d", "--mcpu=gfx950", "--no-show-raw-insn", "--no-leading-addr", str(obj)],
-                              capture_output=True, text=True, check=True).stdout
-        written, busy, clock = {}, {}, 0   # register -> wait state of its last vector-unit write / end of matrix write
-        for line in text.splitlines():
-            line = line.split("//")[0].strip()
-            if not line or line.endswith(":"):
-                if line.endswith(":"):
-                    written, busy = {}, {}
-                continue
-            op, _, rest = line.partition(" ")
-            if op in ("s_branch", "s_endpgm"):   # what follows in the listing does not follow in time
-                written, busy = {}, {}
-                continue
-            args = [a.strip() for a in rest.split(",")]
-            if op == "s_nop":
-                clock += int(args[0], 0) + 1
-                continue
-            clock += 1
-            regs = [_registers(a.split(" ")[0]) for a in args]
-            if op.startswith(("v_mfma_f32_16x16x32", "v_smfmac_f32_16x16x64")):
-                found += 1
-                for r in set().union(*regs[1:4]):
-                    assert clock - written.get(r, -9) > 2, (line, r)
-                for r in regs[0]:
-                    busy[r] = clock + 18
-            elif op.startswith(("v_mfma", "v_smfmac")):
-                continue
-            else:
-                for r in set().union(*regs):
-                    assert busy.get(r, -1) < clock, (line, r)
-                if op.startswith("v_"):
-                    written.update((r, clock) for r in regs[0])
+        text = subprocess.run([objdump, "-d", "--mcpu=gfx950", "--no-show-raw-insn", str(obj)], capture_output=True, text=True, check=True).stdout
+        for name, code in _functions(text).items():
+            matrix = sum(c[1].startswith(ASM_MATRIX_OPS) for c in code)
+            found += matrix
+            if matrix:
+                assert _asm_hazards(code) == [], name
     assert found > 1000
