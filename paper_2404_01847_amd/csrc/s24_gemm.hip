@@ -36,22 +36,49 @@ typedef __attribute__((ext_vector_type(16))) _Float16 f16x16;
 // conversions of the epilogues.
 // c += a b on v_mfma_f32_16x16x32, the accumulator in place.  Written as an instruction because the compiler's own form does
 // not tie its result to its accumulator operand: with all 256 accumulation registers in use (the 128 x 128 wave tile) it
-// shuffled accumulators between register files, a move per instruction.  The compiler does not pad hazards around it:
-// fragments come from LDS reads, not from vector instructions just before (two wait states; a host test looks for such
-// pairs in the built library), and whoever reads the accumulators waits for the matrix unit first (mma_drain).
+// shuffled accumulators between register files, a move per instruction.  The compiler does not pad hazards around it, so
+// the distances are kept here: fragments come from LDS reads; what vector instructions compute for it (the cleared
+// accumulators, the packed index words) is done when mma_operands passes, two wait states ahead of the next instruction;
+// and nobody reads an accumulator until mma_drain has passed, which waits for the matrix unit.  Both name the registers as
+// operands, so that no computation of them moves past.  Copies that the register allocator may add are beyond that: a host
+// test follows the built library's instructions.
 #if defined(__HIP_DEVICE_COMPILE__)
 #define S24_MFMA_16X16X32(TYPE, a, b, c) \
     asm volatile("v_mfma_f32_16x16x32_" TYPE " %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b))
 #define S24_SMFMAC_16X16X64(TYPE, HALF, a, b, c, idx) \
     asm volatile("v_smfmac_f32_16x16x64_" TYPE " %0, %1, %2, %3 abid:" HALF : "+v"(c) : "v"(a), "v"(b), "v"(idx))
-__device__ __forceinline__ void mma_operand_gap() { asm volatile("s_nop 1"); }
-__device__ __forceinline__ void mma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+#define S24_TIE(CLASS, x) asm volatile("" : CLASS(x))
+#define S24_MMA_WAIT(N) asm volatile(N ::: "memory")
 #else
 #define S24_MFMA_16X16X32(TYPE, a, b, c) (void)(a), (void)(b), (void)(c)
 #define S24_SMFMAC_16X16X64(TYPE, HALF, a, b, c, idx) (void)(a), (void)(b), (void)(c), (void)(idx)
-__device__ __forceinline__ void mma_operand_gap() {}
-__device__ __forceinline__ void mma_drain() {}
+#define S24_TIE(CLASS, x) (void)(x)
+#define S24_MMA_WAIT(N) (void)0
 #endif
+// the register class of the accumulators: "a" for the dense instruction, "v" for the sparse one
+enum MmaRegs { ACC_AGPR, ACC_VGPR };
+template <MmaRegs REGS, int R, int C> __device__ __forceinline__ void mma_tie(f32x4 (&acc)[R][C])
+{
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            if constexpr (REGS == ACC_AGPR) S24_TIE("+a", acc[i][j]);
+            else S24_TIE("+v", acc[i][j]);
+        }
+}
+template <int FIRST, int COUNT, int N> __device__ __forceinline__ void mma_tie(uint32_t (&idx)[N])
+{
+#pragma unroll
+    for (int i = FIRST; i < FIRST + COUNT; ++i) S24_TIE("+v", idx[i]);
+}
+// The ties above come before the two wait states and, being volatile as the instructions are, these before any of those.
+__device__ __forceinline__ void mma_operands() { S24_MMA_WAIT("s_nop 1"); }
+template <MmaRegs REGS, int R, int C> __device__ __forceinline__ void mma_drain(f32x4 (&acc)[R][C])
+{
+    S24_MMA_WAIT("s_nop 15\n\ts_nop 15");
+    mma_tie<REGS>(acc);
+}
 template <typename T> struct Mma;
 template <> struct Mma<uint16_t> {
     static __device__ __forceinline__ void dense16(bf16x8 a, bf16x8 b, f32x4 &c) { S24_MFMA_16X16X32("bf16", a, b, c); }
@@ -392,6 +419,9 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
     for (int ni = 0; ni < 4; ++ni)
 #pragma unroll
         for (int h = 0; h < 2; ++h) fb[ni][h] = load_b(s0, ni, h);
+    mma_tie<0, MI / 2>(ix);
+    mma_tie<ACC_VGPR>(acc);
+    mma_operands();
 
     // One chunk, software-pipelined across the workgroup barrier.  On entry the token fragments of chunk kc and the first
     // half of its feature fragments are in registers.  Phase A: their 4 MI matrix instructions, with the LDS reads of the
@@ -423,6 +453,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
         }
 #pragma unroll
         for (int i = 0; i < MI / 2; ++i) ix[MI / 2 + i] = pack_index(raw[i]);
+        mma_tie<MI / 2, MI / 2>(ix);   // the wait and the barrier below are the wait states
         advance(kc + 3);
         // all but the NC most recent copies (chunk kc+2) are complete: this lane's part of chunk kc+1 is in LDS,
         // and its own LDS reads of chunk kc are done
@@ -446,7 +477,8 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
         }
 #pragma unroll
         for (int i = 0; i < MI / 2; ++i) ix[i] = pack_index(raw[i]);
-        mma_operand_gap();
+        mma_tie<0, MI / 2>(ix);
+        mma_operands();
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -460,7 +492,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
     }
     if (kc < nk) chunk(s0, s1, s2, kc);
     if (kc + 1 < nk) chunk(s1, s2, s0, kc + 1);
-    mma_drain();
+    mma_drain<ACC_VGPR>(acc);
     // drain the copies still in flight, then reuse the ring as a staging area for the output tile
     wait_and_barrier<0>();
     clock_report(probe, t_start);
@@ -714,6 +746,8 @@ __global__ __launch_bounds__(128 * WN) void dense_nt_big_kernel(const uint16_t *
     for (int mi = 0; mi < MI; ++mi) fa0[mi] = load_a(s0, mi);
 #pragma unroll
     for (int ni = 0; ni < 4; ++ni) fb[ni] = load_b(s0, ni);
+    mma_tie<ACC_AGPR>(acc);
+    mma_operands();
     auto chunk = [&](unsigned char *cur, const unsigned char *nxt, unsigned char *prv, int kc) {
         bf16x8 fa1[MI];
         auto multiply = [&](const bf16x8 (&a)[MI], int first, int i) {   // the i-th matrix instruction of a phase
@@ -760,7 +794,7 @@ __global__ __launch_bounds__(128 * WN) void dense_nt_big_kernel(const uint16_t *
     if (kc < nk) chunk(s0, s1, s3, kc);
     if (kc + 1 < nk) chunk(s1, s2, s0, kc + 1);
     if (kc + 2 < nk) chunk(s2, s3, s1, kc + 2);
-    mma_drain();
+    mma_drain<ACC_AGPR>(acc);
     big::wait_and_barrier<0>();   // last (redundant) copies drained, nobody reads the ring any more: reuse it
     big::clock_report(probe, t_start);
     constexpr int PER = WN / 2;   // waves that park their output tile in one ring stage
@@ -993,6 +1027,8 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     for (int ni = 0; ni < NB; ++ni) fb[0][ni] = join(load_b(s0, c0, 0, ni, 0), load_b(s0, c0, 0, ni, 1));
 #pragma unroll
     for (int mi = 0; mi < MB - 1; ++mi) fa[mi] = join(load_a(s0, c0, 0, mi, 0), load_a(s0, c0, 0, mi, 1));
+    mma_tie<ACC_AGPR>(acc);
+    mma_operands();
     const char *rowsA = baseA + (int64_t)first_row(3) * ldy * 2, *rowsB = baseB + (int64_t)first_row(3) * ldx * 2;   // of the next chunk to copy
 
     // One step: rows of NB matrix instructions.  A wave is alone on its SIMD and issues an instruction every four cycles, a
@@ -1106,7 +1142,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
             }
         }
     };
-    mma_drain();
+    mma_drain<ACC_AGPR>(acc);
     decay_loads(0, 0);
     big::wait_and_barrier<0>();   // last (redundant) copies drained, nobody reads the ring any more: reuse it
     big::clock_report(probe, t_start);
@@ -1296,6 +1332,9 @@ __global__ __launch_bounds__(128 * WN) void spmm_tn_big_kernel(const uint16_t *_
     for (int ni = 0; ni < 4; ++ni)
 #pragma unroll
         for (int h = 0; h < 4; ++h) fb[ni].q[h] = load_b(s0, ni, h);
+    mma_tie<0, MI / 2>(ix);
+    mma_tie<ACC_VGPR>(acc);
+    mma_operands();
 
     // One chunk, pipelined across the workgroup barrier exactly as in the NT kernel: the first half's matrix
     // instructions run from registers while the second half's value fragments come in; after the one barrier of the chunk
@@ -1323,6 +1362,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_tn_big_kernel(const uint16_t *_
         }
 #pragma unroll
         for (int i = 0; i < MI / 2; ++i) ix[MI / 2 + i] = pack_index(raw[i]);
+        mma_tie<MI / 2, MI / 2>(ix);   // the wait and the barrier below are the wait states
         advance(kc + 3);
         big::wait_and_barrier<NC>();   // this lane's part of chunk kc+1 is in LDS, its own reads of chunk kc are done
         __builtin_amdgcn_s_setprio(1);
@@ -1347,7 +1387,8 @@ __global__ __launch_bounds__(128 * WN) void spmm_tn_big_kernel(const uint16_t *_
         }
 #pragma unroll
         for (int i = 0; i < MI / 2; ++i) ix[i] = pack_index(raw[i]);
-        mma_operand_gap();
+        mma_tie<0, MI / 2>(ix);
+        mma_operands();
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -1361,7 +1402,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_tn_big_kernel(const uint16_t *_
     }
     if (kc < nk) chunk(s0, s1, s2, kc);
     if (kc + 1 < nk) chunk(s1, s2, s0, kc + 1);
-    mma_drain();
+    mma_drain<ACC_VGPR>(acc);
     big::wait_and_barrier<0>();   // copies drained, nobody reads the ring any more: reuse it
     big::clock_report(probe, t_start);
     // fp32 output through LDS in 16-byte row segments: a wave parks RB row blocks x 64 columns at a time in its part of
