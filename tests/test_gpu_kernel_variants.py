@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import s24_inputs as si
-from util import F32_TOL, assert_close, dev, dev_bf16, host_bits, host_f64, tol_for, torch_dtype
+from util import F32_TOL, assert_close, dev, dev_bf16, host_bits, host_f64, tiles_run, tol_for, torch_dtype
 
 pytestmark = pytest.mark.gpu
 
@@ -341,7 +341,8 @@ def test_medium_tile_and_its_epilogues(s24, dtype, pqr):
     ref = oracle.spmm_fwd(X, cv, cm, rows=rows)
     tol, new = tol_for(dtype), lambda n: torch.full((p, n), 7.0, dtype=torch_dtype(dtype), device="cuda")
     Y, Z, H, dZ = new(r), new(r), new(r), new(r)
-    s24.spmm_fwd(x, v, m, Y)
+    plain = [(4, 4), (4, 2)] if q >= 1088 and r == 1248 else [(4, 2)] if q >= 1088 else [(2, 2)]
+    assert tiles_run(lambda: s24.spmm_fwd(x, v, m, Y)) == plain
     assert_close(host_f64(Y[at]), ref, tol, f"spmm_fwd {pqr}")
     Y2 = Y.clone()
     s24.spmm_bwd_dx(x, v, m, Y2, beta=1.0)
@@ -355,7 +356,7 @@ def test_medium_tile_and_its_epilogues(s24, dtype, pqr):
     s24.act_bwd(Y, dev_bf16(Zin), two, s24.ACT_GELU_ERF)
     assert torch.equal(dZ.view(torch.int16), two.view(torch.int16))
     GU, Hg, two = new(r), new(r // 2), new(r // 2)
-    s24.spmm_fwd_glu(x, v, m, b, GU, Hg, s24.GATE_SILU)
+    assert tiles_run(lambda: s24.spmm_fwd_glu(x, v, m, b, GU, Hg, s24.GATE_SILU)) == [(4, 4) if r == 1248 else (4, 2)]
     s24.glu_fwd(GU, two, s24.GATE_SILU)
     assert torch.equal(GU.view(torch.int16), Z.view(torch.int16)) and torch.equal(Hg.view(torch.int16), two.view(torch.int16))
 
@@ -435,9 +436,9 @@ def test_calls_go_to_the_current_stream(s24):
 
 # ------------------------------------------------------------------ weight gradients on the 256 x 128 tile
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-# 144 such tiles in all, 288 small ones; whole chunks and a remainder;
-# edges ragged along both axes
-@pytest.mark.parametrize("case", [(2048, 0.0), (2003, 1.0), (1100, 0.0)])
+# 144 such tiles in all; whole chunks and remainders; edges ragged along both axes; and 288 small ones, the cheaper up to
+# about 1200 tokens
+@pytest.mark.parametrize("case", [(2048, 0.0), (2003, 1.0), (1804, 0.0), (1100, 0.0)])
 def test_medium_tile_weight_gradients(s24, dtype, case):
     p, beta = case
     lam, d, f = 2e-4, 752, 3056
@@ -448,7 +449,8 @@ def test_medium_tile_weight_gradients(s24, dtype, case):
     dW0 = [si.random_matrix(96 + i, sh, 1e-3, "f32") for i, sh in enumerate(shapes)]
     masks = [oracle.transposable_mask(w) for w in W]
     got = [dev(w).clone() for w in dW0]
-    s24.dense_dw_batch([(dev_bf16(dY[i]), dev_bf16(X[i]), got[i], dev_bf16(W[i]), dev(masks[i]), lam) for i in range(2)], beta=beta)
+    probs = [(dev_bf16(dY[i]), dev_bf16(X[i]), got[i], dev_bf16(W[i]), dev(masks[i]), lam) for i in range(2)]
+    assert tiles_run(lambda: s24.dense_dw_batch(probs, beta=beta)) == [(4, 2, 32) if p > 1200 else (2, 2, 32)]
     plain = [dev(w).clone() for w in dW0]
     s24.dense_dw_batch([(dev_bf16(dY[i]), dev_bf16(X[i]), plain[i], None, None, 0.0) for i in range(2)], beta=beta)
     for i, (r, q) in enumerate(shapes):
@@ -469,7 +471,8 @@ def test_dense_product_tiles(s24, dtype, pr, q):
     p, r = pr
     X, W = si.random_matrix(100 + p, (p, q), 1.0, dtype), si.random_matrix(101 + r, (r, q), 0.02, dtype)
     Y = torch.full((p, r), 7.0, dtype=torch_dtype(dtype), device="cuda")
-    s24.dense_gemm(dev_bf16(X), dev_bf16(W), Y)
+    x, w = dev_bf16(X), dev_bf16(W)
+    assert tiles_run(lambda: s24.dense_gemm(x, w, Y)) == [(4, 2) if p == 2050 else (2, 2)]
     rows = np.unique(np.concatenate([[0, p - 1], np.random.default_rng(p).integers(0, p, 40), np.arange(min(p, 260))]))
     ref = si.to_f32(X)[rows].astype(np.float64) @ si.to_f32(W).astype(np.float64).T
     assert_close(host_f64(Y)[rows], ref, tol_for(dtype), f"dense_gemm {pr} {q}")
@@ -477,8 +480,9 @@ def test_dense_product_tiles(s24, dtype, pr, q):
 
 # ------------------------------------------------------------------ sparse weight gradients by size of the output
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-# 128 x 128, 256 x 128 (136 of them) and 256 x 256 tiles, ragged both ways; one, three and four chunks against a ring of three
-@pytest.mark.parametrize("rq", [(144, 272), (2032, 2064), (4080, 4112)])
+# 128 x 128, 256 x 128 (136 of them), 256 x 256 tiles (256 of them) and, a column more, 128 x 128 again; ragged both ways; one,
+# three and four chunks against a ring of three
+@pytest.mark.parametrize("rq", [(144, 272), (2032, 2064), (4080, 4080), (4080, 4112)])
 @pytest.mark.parametrize("p,beta", [(64, 0.0), (192, 1.0), (256, 0.0)])
 def test_sparse_weight_gradient_tiles(s24, dtype, rq, p, beta):
     (r, q), lam = rq, 2e-4
@@ -488,7 +492,8 @@ def test_sparse_weight_gradient_tiles(s24, dtype, rq, p, beta):
     vz, mz = oracle.mvue24(dY, 7)
     v, m = oracle.pack(vz, mz)
     plain, decayed = dev(dW0).clone(), dev(dW0).clone()
-    s24.spmm_dw(dev_bf16(v), dev(m), dev_bf16(X), plain, beta=beta)
+    vd, md, x = dev_bf16(v), dev(m), dev_bf16(X)
+    assert tiles_run(lambda: s24.spmm_dw(vd, md, x, plain, beta=beta)) == [{272: (2, 2), 2064: (4, 2), 4080: (4, 4), 4112: (2, 2)}[q]]
     s24.spmm_dw(dev_bf16(v), dev(m), dev_bf16(X), decayed, beta=beta, W=dev_bf16(W), mask=dev(mask), lam=lam)
     rows = np.unique(np.concatenate([[0, r - 1], np.random.default_rng(r).integers(0, r, 40), np.arange(min(r, 130))]))
     rows = np.resize(rows, (rows.size + 15) // 16 * 16)     # the oracle takes multiples of 16: the first ones again
@@ -568,21 +573,22 @@ def test_weight_gradient_of_a_ragged_token_count_keeps_infinities(s24, dtype, p)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-# (p, rq, rq of the problem beside it): small tiles alone (64 tokens to a stage) against small (32) and medium tiles in the
+# (p, rq, rq of the problem beside it, tiles alone, tiles in the pair): small tiles alone (64 tokens to a stage) against small (32) and medium tiles in the
 # pair, with a last stage that holds part of one 32-token step or of both; medium tiles alone and large ones in the pair; and
 # an output whose last columns run in small tiles beside large ones, alone one column of large tiles wide, in the pair two
-@pytest.mark.parametrize("case", [(p, (768, 3072), (3072, 768)) for p in (17, 33, 48, 57, 63, 64, 70, 90, 97, 112, 121, 127, 191, 3001)] +
-                         [(5537, (1408, 3776), (3776, 1408))] +
-                         [(p, (2048, 8448), (2048, 8448)) for p in (97, 112, 3001)])
+@pytest.mark.parametrize("case", [(p, (768, 3072), (3072, 768), [(2, 2, 64)], [(2, 2, 32)]) for p in (17, 33, 48, 57, 63, 64, 70, 90, 97, 112, 121, 127, 191)] +
+                         [(3001, (768, 3072), (3072, 768), [(2, 2, 64)], [(4, 2, 32)])] +
+                         [(5537, (1408, 3776), (3776, 1408), [(4, 2, 32)], [(4, 4, 32)])] +
+                         [(p, (2048, 8448), (2048, 8448), [(4, 4, 32), (2, 2, 64)], [(4, 4, 32), (2, 2, 64)]) for p in (97, 112, 3001)])
 def test_weight_gradients_have_the_same_bits_in_every_tile(s24, dtype, case):
-    p, a, b = case
+    p, a, b, tiles_alone, tiles_pair = case
     gen = torch.Generator(device="cuda").manual_seed(p)
     rnd = lambda n, std: (torch.randn((p, n), generator=gen, device="cuda") * std).to(torch_dtype(dtype))
     probs = [(rnd(r, 1e-2), rnd(q, 1.0), torch.zeros((r, q), device="cuda"), None, None, 0.0) for r, q in (a, b)]
-    s24.dense_dw_batch(probs)
+    assert tiles_run(lambda: s24.dense_dw_batch(probs)) == tiles_pair
     for dY, X, dW, *_ in probs:
         alone = torch.zeros_like(dW)
-        s24.dense_dw(dY, X, alone)
+        assert tiles_run(lambda: s24.dense_dw(dY, X, alone)) == tiles_alone
         assert torch.equal(alone.view(torch.int32), dW.view(torch.int32)), case
         rows = torch.cat([torch.arange(0, dW.shape[0], 61), torch.tensor([dW.shape[0] - 1])])
         ref = host_f64(dY)[:, rows.numpy()].T @ host_f64(X)

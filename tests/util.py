@@ -1,5 +1,7 @@
 """Helpers shared by the GPU parity tests: host<->device conversion of the
 seeded inputs and the error measures of the parity bar."""
+import re
+
 import numpy as np
 import torch
 
@@ -110,3 +112,24 @@ def absorbed_margin_blocks(legal, dtype: str, big_exp: int, every: int = 7):
     if dtype == "bf16":
         W = si.f32_to_bf16_bits(torch.from_numpy(W))
     return W, want
+
+
+def tiles_run(call):
+    """The tiles of the 16-bit GEMM kernels that `call` launches, in order, by the last template arguments of their names:
+    (4, 4) is 256 x 256, (4, 2) 256 (features) x 128 (tokens), (2, 2) 128 x 128; dense weight gradients add the tokens
+    of a stage, the sliced kernel gives ()."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as prof:
+        call()
+        torch.cuda.synchronize()
+    tiles = []
+    for event in sorted(prof.events(), key=lambda e: e.time_range.start):
+        name = re.sub(r"Li(\d+)E", r"\1, ", event.name)   # binary16 instances come under their mangled names
+        if m := re.search(r"dense_tn_dma_kernel.*Cfg(?:<|I)(\d+), (\d+), (\d+)", name):
+            tiles.append(tuple(map(int, m.groups())))
+        elif m := re.search(r"(?:spmm_nt_big|dense_nt_big|spmm_tn_big)_kernel.*?(\d+), (\d+)(?:>\(|, EEv)", name):
+            tiles.append(tuple(map(int, m.groups())))
+        elif "slice" in name:
+            tiles.append(())
+    return tiles
