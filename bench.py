@@ -489,10 +489,10 @@ def measured_ceilings(torch, s24):
     out = {"label": "measured on this device in this run (the published peaks are 2500 / 5000 TFLOP/s and 8000 GB/s)"}
     wgs, iters = 1024, 8000
     sink = torch.empty(wgs * 512, dtype=torch.float32, device="cuda")
-    for sparse, key, flop in ((0, "dense_mfma_32x32x16_bf16", 32768.0), (1, "sparse_smfmac_32x32x32_bf16_dense_equivalent", 65536.0)):
+    for sparse, key, flop in ((0, "dense_mfma_16x16x32_bf16", 16384.0), (1, "sparse_smfmac_16x16x64_bf16_dense_equivalent", 32768.0)):
         ms = min(_time_ms(torch, lambda: s24.probe_matrix_rate(sparse, wgs, iters, sink), 2) for _ in range(3))
-        out[key + "_TFLOP/s"] = round(wgs * 8 * 4.0 * iters * flop / ms / 1e9, 1)
-    out["matrix_rate_probe"] = f"{wgs} workgroups x 8 waves x {4 * iters} instructions on registers only, 4 independent accumulators per wave"
+        out[key + "_TFLOP/s"] = round(wgs * 8 * 8.0 * iters * flop / ms / 1e9, 1)
+    out["matrix_rate_probe"] = f"{wgs} workgroups x 8 waves x {8 * iters} instructions on registers only, 8 independent accumulators per wave"
     n = 1 << 28
     src = torch.ones(n, dtype=torch.float32, device="cuda")
     dst = torch.empty_like(src)

@@ -1,8 +1,9 @@
 // Instrumentation, not part of the method: the two ceilings a roofline for this library is read against, measured on
 // the device the library runs on instead of taken from a data sheet.
 //   s24_probe_matrix_rate  a register-only loop of matrix-core instructions (no LDS, no memory): the rate at which
-//                          the chip issues v_mfma_f32_32x32x16_bf16 (dense) or v_smfmac_f32_32x32x32_bf16 (2:4
-//                          sparse) when nothing else competes, at the clock it holds under that load
+//                          the chip issues v_mfma_f32_16x16x32_bf16 (dense) or v_smfmac_f32_16x16x64_bf16 (2:4
+//                          sparse), the instructions of the 16-bit GEMMs, when nothing else competes, at the clock it
+//                          holds under that load
 //   s24_probe_copy         a plain device-to-device copy in 16-byte accesses: what HBM delivers to a kernel that
 //                          does nothing but move bytes
 // The caller times the launches (events on the stream) and divides.
@@ -12,10 +13,10 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) __bf16 bf16x16;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kProbeThreads = 512;   // eight waves, two per SIMD, as in the large-tile GEMMs
-constexpr int kChains = 4;           // independent accumulators per wave: covers the instruction's own latency
+constexpr int kChains = 8;           // independent accumulators per wave: covers the instruction's own latency
 
 __device__ __forceinline__ float probe_value(uint32_t x)
 {
@@ -23,13 +24,13 @@ __device__ __forceinline__ float probe_value(uint32_t x)
     return (float)((int)(x & 0xFFFF) - 32768) * (1.0f / 65536.0f);   // in [-0.5, 0.5): operands with every bit in use
 }
 
-// KIND 0: dense 32x32x16, 2*32*32*16 FLOP per instruction; KIND 1: sparse 32x32x32, 2*32*32*32 dense-equivalent FLOP
+// KIND 0: dense 16x16x32, 2*16*16*32 FLOP per instruction; KIND 1: sparse 16x16x64, 2*16*16*64 dense-equivalent FLOP
 template <int KIND> __global__ __launch_bounds__(kProbeThreads) void matrix_rate_kernel(int iters, float *sink)
 {
     const uint32_t id = blockIdx.x * kProbeThreads + threadIdx.x;
     bf16x8 a[kChains];
     bf16x16 b[kChains];
-    f32x16 acc[kChains];
+    f32x4 acc[kChains];
 #pragma unroll
     for (int c = 0; c < kChains; ++c) {
 #pragma unroll
@@ -37,7 +38,7 @@ template <int KIND> __global__ __launch_bounds__(kProbeThreads) void matrix_rate
 #pragma unroll
         for (int j = 0; j < 16; ++j) b[c][j] = (__bf16)probe_value(id * 257u + c * 29u + j + 1000u);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) acc[c][j] = 0.0f;
+        for (int j = 0; j < 4; ++j) acc[c][j] = 0.0f;
     }
     const int idx = 0x4E4E4E4E;   // index nibbles i0 | i1 << 2 of kept positions {2,3} and {0,1} in turn: legal pairs
     for (int it = 0; it < iters; ++it) {
@@ -47,9 +48,9 @@ template <int KIND> __global__ __launch_bounds__(kProbeThreads) void matrix_rate
                 bf16x8 bb;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) bb[j] = b[c][j];
-                acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[c], bb, acc[c], 0, 0, 0);
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], bb, acc[c], 0, 0, 0);
             } else {
-                acc[c] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a[c], b[c], acc[c], idx, 0, 0);
+                acc[c] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a[c], b[c], acc[c], idx, 0, 0);
             }
         }
     }
@@ -57,7 +58,7 @@ template <int KIND> __global__ __launch_bounds__(kProbeThreads) void matrix_rate
 #pragma unroll
     for (int c = 0; c < kChains; ++c)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) s += acc[c][j];
+        for (int j = 0; j < 4; ++j) s += acc[c][j];
     sink[id] = s;
 }
 

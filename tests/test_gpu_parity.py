@@ -846,5 +846,5 @@ def test_probe_copy_copies_and_matrix_rate_probe_runs(s24):
         s24.probe_matrix_rate(sparse, 4, 8, sink)
         torch.cuda.synchronize()
         assert torch.isfinite(sink).all()
-    # four accumulators of 32 x 32 x (16 * 8) products of values below 1/2: a loose bound that a wrong loop breaks
+    # four values of each of eight accumulators, sums of (32 * 8) products of values up to 1/2: a loose bound that a wrong loop breaks
     assert float(sink.abs().max()) < 4 * 16 * 8 * 32 * 0.25 * 64
