@@ -119,8 +119,9 @@ __device__ __forceinline__ bf16x16 as_bf16x16(uint4 lo, uint4 hi)
 // each half wave: rows 0-3 and 12-15 of one k quarter beside rows 4-11 of the next.  Both layouts give that, and for 16
 // consecutive rows of one quarter (c ^ (r>>2) alone does not: 260 conflict cycles per chunk of 1600).
 // The 16-wide sparse instruction alone holds 1.81 GHz where the 32-wide one holds 1.62 (3.65 against 3.31 PFLOP/s
-// dense-equivalent on random operands).  What bounds the kernel is the path of the copies together with that clock:
-// 8192 x 8192 x 28672 1719 -> 1656 us, with M and K exchanged 1626 -> 1566, 16384 x 5120, K = 1280 122 -> 114.
+// dense-equivalent on random operands, in one job).  What bounds the kernel is the path of the copies together with that clock:
+// 8192 x 8192 x 28672 1719 -> 1656 us, with M and K exchanged 1626 -> 1566, 16384 x 5120, K = 1280 122 -> 114 (short runs on a
+// card not yet warm; the second product launched on end takes 1.85-1.92 ms at 1.36-1.41 GHz, on zero operands 1.34 at 2.3).
 namespace big {
 constexpr int BM = 256, BN = 256, THREADS = 512;   // the large tile
 typedef __attribute__((address_space(3))) void *lds_ptr;
@@ -817,10 +818,12 @@ __global__ __launch_bounds__(128 * WN) void dense_nt_big_kernel(const uint16_t *
 // Four waves, one per SIMD, each a 128 x 128 tile of 8 x 8 accumulator blocks (256 accumulator registers):
 // against eight waves of 128 x 64 this reads a third less LDS per matrix instruction, which matters
 // because the chip sheds clock under the combined matrix + LDS + copy load.
-// 16 x 16 blocks and not 32 x 32: what bounds the kernel is the clock the chip holds, and the 16-wide instruction moves half
-// as many accumulator bits per FLOP: alone, on random operands, it runs at 2.05-2.10 PFLOP/s (2.02 GHz) where the 32-wide one
-// gets 1.81 (1.79 GHz); binary16 1.91 against 1.66.  Here: 8192 tokens, 8192 x 28672: 1.32 -> 1.42 PFLOP/s (2921 -> 2711 us, clock
-// 1.47 -> 1.64 GHz); 16384 tokens, 1280 x 5120: 188 -> 172 us.
+// 16 x 16 blocks and not 32 x 32: the clock the chip holds under matrix load was the bound, and the 16-wide instruction moves
+// half as many accumulator bits per FLOP: alone, on random operands, it runs at 2.05-2.10 PFLOP/s (2.02 GHz) where the 32-wide
+// one gets 1.81 (1.79 GHz); binary16 1.91 against 1.66.  Here: 8192 tokens, 8192 x 28672: 1.32 -> 1.42 PFLOP/s (2921 -> 2711 us, clock
+// 1.47 -> 1.64 GHz); 16384 tokens, 1280 x 5120: 188 -> 172 us.  What is left is mostly not the clock: on zero operands, at
+// 2.3 GHz, that gradient takes 2.45-2.47 ms, 6-8 % less than on random ones at 1.7 GHz in the same run and no less than with the
+// 32-wide instruction.  That wall, 1.56 PFLOP/s, is the supply of operands; which part of it has not been measured.
 // The token axis moves through a ring of four 32 KB stages.  A chunk is waited for one iteration before it is used, so the
 // fragments of chunk kc+1 are fetched during the matrix instructions of chunk kc and the barrier finds the matrix unit
 // busy; the copies of chunk kc+3 are dealt out between the matrix instructions rather than issued in one burst.
@@ -1503,21 +1506,23 @@ int check_gemm(const void *a, const void *b, const void *c, int64_t p, int64_t q
         }                                 \
     } while (0)
 
-// Which tile a sparse NT product takes.  Costs in full rounds of the large tile at the same depth, measured over 128-16384
-// tokens, 256-4096 x 1024-22016 features (us per 64 of k at K = 5504 to 11008: large 0.75 with every compute unit busy and
-// 0.55 with few; medium 0.52 and 0.37; small 0.62 with two workgroups per compute unit, 0.32 with one, 0.28 with few):
+// Which tile a sparse NT product takes.  Costs in full rounds of the large tile at the same depth (us per 64 of k at K = 5504 to
+// 11008: large 0.82 with every compute unit busy and 0.53 with few; medium 0.45 and 0.33; small 0.58 with two workgroups per
+// compute unit, 0.29 with one, 0.27 with few):
 //   large    256 x 256, one workgroup per compute unit: least LDS and L2 traffic per FLOP, where its tiles fill the chip
-//   medium   256 x 128: between half a round and a round of them, e.g. 4160 tokens x 1600 features, K = 6400: large 68, small
-//            63, medium 54 us; 3001 x 2048, K = 11008: 101, 100, 77 us
-//   small    128 x 128, two per compute unit: at most one round of single ones (1024 x 2048, K = 5504: 53, 36, 29 us), or a
-//            contraction so short that a tile is mostly prologue and epilogue, which two co-resident workgroups overlap
-//            (8192 x 3072, K = 768 with activation: 51, 54, 46 us; up to 640 deep two rounds of them cost little more than one
-//            of large ones: 8508 x 2112, K = 384: large 26, medium 25, small 21; 1024 deep: 0.54 of a large round, 2048: 0.7,
-//            deeper: 0.82)
+//   medium   256 x 128: between half a round and a round of them, e.g. 4160 tokens x 1600 features, K = 6400: large 65, small
+//            62, medium 48 us; 3001 x 2048, K = 11008: 104, 97, 72 us
+//   small    128 x 128, two per compute unit: at most one round of single ones (1024 x 2048, K = 5504: large 51, medium 34,
+//            small 27 us), or a contraction so short that a tile is mostly prologue and epilogue, which two co-resident
+//            workgroups overlap (8192 x 3072, K = 768 with activation: 50, 56, 49 us; 8508 x 2112, K = 384: 22, 22, 19)
+// The constants are a fit to the kernels on the 32-wide instruction, over 128-16384 tokens, 256-4096 x 1024-22016 features.  On the
+// present ones a round of small tiles measures 0.57, 0.59, 0.61, 0.63 and 0.69 of a large one at K = 384, 640, 1024, 2048 and 5504,
+// flatter than the 0.505 to 0.82 below; with every tile timed at 128 products (128-16384 tokens, widths of 256-17000) the tile
+// chosen takes 0.8 % more than the best one at the mean and 2 % at the ninetieth percentile.
 // A grid of large tiles whose last round is mostly empty (320 tiles on 256 compute units) can give its last token-tile rows
-// to a smaller tile: the first `slab` tokens run in whole rounds of large tiles (16384 x 1280, K = 5120: 135 -> 117 us), where
-// that saves more than the second launch costs, 3 us of a round's 5 + 0.75 per 64 of k (2347 x 20032, K = 384: 56 us so cut,
-// 43 in small tiles).
+// to a smaller tile: the first `slab` tokens run in whole rounds of large tiles (16384 x 1280, K = 5120: 122 -> 112 us), where
+// that saves more than the second launch costs, 3 us of a round's 5 + 0.75 per 64 of k (2347 x 20032, K = 384, is not cut: 47 us in
+// large tiles, 41 in small ones).
 // Tokens are independent rows and these tiles sum in the same order: the choice among them does not change a bit of the
 // result.  (The slices of s24_gemm_slice.hip, chosen before them, sum in another.)
 struct NtTile {
@@ -1562,13 +1567,13 @@ inline NtTile nt_tile_or_slab(int64_t M, int64_t N, int64_t K)
     if (cut < nt_cost(t.kind, M, N, c)) t.slab = slab;
     return t;
 }
-// The dense product: us per 64 of k, large 1.7 and 0.9 (full, few), medium 1.05 and 0.7, small 1.2 with two workgroups per
-// compute unit, 0.5 with one.  The 128 x 128 kernel that staged its operands through registers took 1.5 and 0.8: 8192 x 1024,
-// K = 4096: 96 -> 72 us (medium); 500 x 4096, K = 16384: 204 -> 115; 2048 x 3072, K = 768: 21 -> 17.
+// The dense product: us per 64 of k, large 1.45 and 0.94 (full, few), medium 0.85 and 0.54, small 1.04 with two workgroups per
+// compute unit, 0.44 with one.  8192 x 1024, K = 4096: large 75, medium 65, small 76 us; 500 x 4096, K = 16384: 240, 178, 119;
+// 2048 x 3072, K = 768: 20, 16, 17.  0.5 % above the best tile at the mean of 128 products.
 inline NtTile dense_tile(int64_t M, int64_t N) { return cheapest_tile(M, N, {0.53, 0.30, 0.62, 0.40, 0.20, 0.70, 0.26, 0.08}); }
-// The sparse weight gradient: us per 64 tokens, large 1.15 and 0.6 (full, few), medium 0.5 (one round), small 0.66 with two
-// workgroups per compute unit and 0.34 to 0.43 with one.  Large alone before: 8192 tokens, 768 x 3072: 78 -> 43 us (small);
-// 2048, 512 x 2048: 27 -> 14; 16384, 1280 x 5120: 164 -> 126 (medium); 3008, 1472 x 4032: 42 -> 32.
+// The sparse weight gradient: us per 64 tokens, large 0.83 and 0.53 (full, few), medium 0.46 and 0.35, small 0.63 with two
+// workgroups per compute unit and 0.30 with one.  8192 tokens, 768 x 3072: large 77, medium 54, small 45 us; 2048, 512 x 2048: 24,
+// 16, 14; 16384, 1280 x 5120: 162, 117, 215; 3008, 1472 x 4032: 37, 27, 31.  0.8 % above the best tile at the mean of 128.
 inline NtTile sparse_dw_tile(int64_t M, int64_t N) { return cheapest_tile(M, N, {0.50, 0.45, 0.62, 0.36, 0.10, 0.60, 0.29, 0.08}); }
 // Runs MACRO(..., MI, WN) with the wave layout of a tile
 #define S24_WITH_NT_TILE(tile, MACRO, ...)                              \
@@ -1668,7 +1673,7 @@ extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t 
     NtTile tile = nt_tile(2 * f, p, q);
     // The small tile has no gated epilogue: it is taken only where it saves more than the pass over Z costs, 2.4 us per million
     // gated features (6 bytes each) less the 1 us that the fused epilogue costs itself.  10041 tokens, 19072 rows, K = 64: fused
-    // 123 us, in two calls 215; 2655 x 7360, K = 448: 31 and 38; but 527 x 1312, K = 960: 15.9 and 10.6.
+    // 122 us, in two calls 209; 2655 x 7360, K = 448: 28 and 31; but 527 x 1312, K = 960: 12.9 and 9.2.
     if (tile.kind == NtTile::Small) {
         const NtCosts c = sparse_costs(q);
         const double l = nt_cost(NtTile::Large, 2 * f, p, c), m = nt_cost(NtTile::Medium, 2 * f, p, c);
@@ -1877,8 +1882,9 @@ dmatn::DwWindow dw_window(const DwProblem &pr, DwTile tile, int64_t m_off, int64
 // compute unit and 0.18 with one, medium ones 0.45 and 0.24 with few, large ones 0.75 and 0.43; on top of that the filling and
 // draining of a tile.  The small tile reads 32 KB of LDS per 16 KB copied, the medium one 48 per 24 for twice the work: where the
 // small tile needs two workgroups per compute unit and the medium one does not, that is 8192 tokens x 768 x 3072 (both
-// gradients) 106 -> 90 us, 8192 x 1024 x 4096 124 -> 113.  The large tile gained most from the 16-wide instruction and is the
-// cheapest from 0.7 of a round on: 5504 tokens x 1408 x 3776 (both) small 122, medium 125, large 111 us; 8000 tokens 173, 177, 160.
+// gradients) 101 -> 81 us, 8192 x 1024 x 4096 114 -> 100.  The large tile gained most from the 16-wide instruction and is the
+// cheapest from 0.7 of a round on: 5504 tokens x 1408 x 3776 (both) small 118, medium 121, large 112 us; 8000 tokens 165, 167, 154.
+// 0.2 % above the best tile at the mean of 64 other pairs.
 DwTile dw_few_tile(const DwProblem *pr, int count)
 {
     const int64_t cus = s24_cu_count();
@@ -1945,9 +1951,11 @@ int run_dense_dw(const void *dY, const void *X, float *dW, int64_t p, int64_t q,
         // 1376 tiles: 5.375 rounds).  Where whole tile rows or columns can be cut off so that the rest is an exact
         // number of rounds and the cut-off strip is at most half a round of large tiles, the slab runs in large
         // tiles and the strip in small ones (at most 512 of them: one resident set, two workgroups per compute
-        // unit), which costs 0.56 of a round instead of a whole one; a longer strip (c4's other weight, 0.69 of a
-        // round) measured no better than the idle tail it replaces and stays in the single launch.  Every output
-        // element belongs to exactly one launch either way, so nothing about the result changes.
+        // unit).  8192 tokens: a strip of 32 large tiles costs 0.25 of a round of 188 us where the uncut rest costs 0.64, of 64 tiles
+        // 0.32 and 0.67, of 96 0.57 and 0.72, of 128 0.63 and 0.75; 16384 tokens: of 8 tiles 0.35 and 0.71, of 96 0.63 and 0.77.  After
+        // five whole rounds (c4's 1376 tiles) the two are within 1 % of each other.  A longer strip (c4's other weight, 0.69 of a round) stays in the single launch.  Every output
+        // element belongs to exactly one launch either way and all tiles sum the tokens in the same groups, so nothing about the
+        // result changes.
         const int tm256 = (int)ceil_div(r, 256), tn256 = (int)ceil_div(q, 256), total = tm256 * tn256;
         const int cus = s24_cu_count();
         if (total < 3 * cus / 4) {
