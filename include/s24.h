@@ -33,8 +33,8 @@
  *                Storage is chunk-major, 64 columns per chunk, all rows of a
  *                chunk together:  vals[K/64][R][32]  (value j of chunk c of row
  *                o is the row's kept value 32c+j)  and  meta[K/64][R][4]  (word
- *                4c+j of the row).  One chunk of one row is exactly what one
- *                lane pair feeds to two sparse matrix-core instructions.
+ *                4c+j of the row).  One chunk of one row is exactly what four
+ *                lanes feed to one sparse matrix-core instruction.
  *   dtypes       S24_BF16 buffers hold raw bfloat16, S24_F16 buffers IEEE binary16 (the paper trains in fp16
  *                mixed precision, Sec. 6), S24_F32 buffers float.  Both 16-bit types run the same kernels on
  *                the matrix cores (fp32 accumulation, one rounding to the storage type); S24_F32 runs fp32
