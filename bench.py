@@ -810,7 +810,7 @@ def main():
             torch.cuda.empty_cache()
             if w2.dtype == "f32":
                 others[name]["note"] = ("fp32 correctness workload: gfx950 has no fp32 sparse matrix instruction, the GEMMs run "
-                                        "on the vector unit; fractions of the bf16 peaks are shown for form only")
+                                        "on its dense fp32 one; fractions of the bf16 peaks are shown for form only")
             if name == "c3":
                 others[name]["mask_search_only_72_matrices"] = c3_mask_sweep(torch, s24, w2)
         extras["other_workloads"] = others
