@@ -540,8 +540,8 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int64_t o = (int64_t)min(n_base + 4 * j + (lane >> 4), N - 1) * 2 * M + m;
-            g[j] = *reinterpret_cast<const uint4 *>(GU + o);
-            u[j] = *reinterpret_cast<const uint4 *>(GU + o + M);
+            g[j] = s24_load_stream(GU + o);
+            u[j] = s24_load_stream(GU + o + M);
         }
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
@@ -576,7 +576,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
         uint4 z[LPR];   // the accumulators are dead: all loads of Z go out before anything is computed
 #pragma unroll
         for (int j = 0; j < LPR; ++j)
-            z[j] = *reinterpret_cast<const uint4 *>(GU + (int64_t)min(n_base + RPP * j + lane / LPR, N - 1) * M + m);
+            z[j] = s24_load_stream(GU + (int64_t)min(n_base + RPP * j + lane / LPR, N - 1) * M + m);
 #pragma unroll
         for (int j = 0; j < LPR; ++j) {
             const int nl = RPP * j + lane / LPR, n = n_base + nl;
@@ -609,7 +609,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 h[k] = s24_num<T>::pack2(s24_act_value<ACT>(s24_num<T>::lo(zw[k])), s24_act_value<ACT>(s24_num<T>::hi(zw[k])));
-            *reinterpret_cast<uint4 *>(Out + (int64_t)n * M + m) = zc;
+            s24_store_stream(Out + (int64_t)n * M + m, zc);
             *reinterpret_cast<uint4 *>(H + (int64_t)n * M + m) = make_uint4(h[0], h[1], h[2], h[3]);
         }
     } else if constexpr (!SWIGLU) {
@@ -632,8 +632,8 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
             for (int k = 0; k < 4; ++k)
                 hw[k] = s24_num<T>::pack2(s24_glu<GATE>(s24_num<T>::lo(gw[k]), s24_num<T>::lo(uw[k])),
                                           s24_glu<GATE>(s24_num<T>::hi(gw[k]), s24_num<T>::hi(uw[k])));
-            *reinterpret_cast<uint4 *>(Out + (int64_t)n * M + f) = g;
-            *reinterpret_cast<uint4 *>(Out + (int64_t)n * M + F + f) = u;
+            s24_store_stream(Out + (int64_t)n * M + f, g);
+            s24_store_stream(Out + (int64_t)n * M + F + f, u);
             *reinterpret_cast<uint4 *>(H + (int64_t)n * F + f) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
         }
     }
@@ -1193,7 +1193,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
                     if (!(kp & 4u)) o.z = fmaf(lambda, s24_num<ET>::lo(w2.y), o.z);
                     if (!(kp & 8u)) o.w = fmaf(lambda, s24_num<ET>::hi(w2.y), o.w);
                 }
-                if (live[b]) *reinterpret_cast<float4 *>(dW + (int64_t)m * ldw + n) = o;
+                if (live[b]) s24_store_stream(dW + (int64_t)m * ldw + n, o);
             }
             __builtin_amdgcn_sched_barrier(0);   // one batch at a time: hoisting the next batches' reads costs registers
         }
@@ -1459,7 +1459,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_tn_big_kernel(const uint16_t *_
                     if (!(keep[b] & 4u)) o.z = fmaf(lambda, s24_num<ET>::lo(wv[b].y), o.z);
                     if (!(keep[b] & 8u)) o.w = fmaf(lambda, s24_num<ET>::hi(wv[b].y), o.w);
                 }
-                if (live[b]) *reinterpret_cast<float4 *>(dW + (int64_t)m * N + n) = o;
+                if (live[b]) s24_store_stream(dW + (int64_t)m * N + n, o);
             }
         }
         asm volatile("" ::: "memory");
