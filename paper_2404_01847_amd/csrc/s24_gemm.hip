@@ -267,6 +267,55 @@ __device__ __forceinline__ void staged_store(const f32x4 (&acc)[2 * MI][4], unsi
     }
 }
 
+// GELU, or its slope, of bf16 values from a table in LDS.  A bf16 value between 2^-EXP and 16 is one of 128 per octave and sign, so a
+// workgroup computes each of them once (9 to 20 per lane) instead of 128 or 64 tile elements per lane at 26 to 29 issue slots
+// each, two of the instructions on the quarter-rate unit: on a tile of 20 chunks that arithmetic was a third of the time.  An element then
+// costs four packed 16-bit instructions and an LDS read, and has the bits that the function gives it.  Values outside the table
+// (infinities and NaNs among them) send the wave's eight at a time to the function: one in 1e4 normally distributed values of
+// the usual spread.  Not for binary16, whose octaves have 1024 values.  16384 tokens, K = 1280, 5120 features, alternating on one card:
+// forward 158 -> 138 us, backward 174 -> 155 (with ReLU 134 and 139); 4160, 1600, 6400: 65 -> 59 and 70 -> 63; in the 128 x 128 tile, whose
+// lanes have half as many elements to a table, 8192, 768, 3072: 44.5 -> 43 and as before.
+template <int ACT_MODE, int ACT> struct ActTable {
+    typedef std::conditional_t<ACT_MODE == 1, uint16_t, float> entry;   // H as it is stored; the slope is multiplied before it is rounded
+    static constexpr int EXP = ACT_MODE == 1 ? 16 : 14, FIRST = (127 - EXP) << 7, COUNT = (EXP + 4) << 7;   // of either sign
+    static constexpr int BYTES = 2 * COUNT * (int)sizeof(entry);
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+    static __device__ __forceinline__ entry value(float z)
+    {
+        if constexpr (ACT_MODE == 1) return (uint16_t)s24_f32_to_bf16(s24_act_value<ACT>(z));
+        else return s24_act_slope<ACT>(z);
+    }
+    // by the whole workgroup; readable after a barrier
+    template <int THREADS> static __device__ __forceinline__ void build(entry *tab, int tid)
+    {
+        static_assert(COUNT % 128 == 0, "whole waves");
+        for (int i = tid; i < COUNT; i += THREADS) {   // both signs together: they share most of the arithmetic
+            const float z = s24_num<uint16_t>::widen(FIRST + i);
+            tab[i] = value(z);
+            tab[COUNT + i] = value(-z);
+        }
+    }
+    // of the eight values in z
+    static __device__ __forceinline__ void lookup(const entry *tab, const uint32_t (&z)[4], entry (&out)[8])
+    {
+        u16x2 at[4], far = {0, 0};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const u16x2 b = __builtin_bit_cast(u16x2, z[k]), from_first = (b & (unsigned short)0x7FFF) - (unsigned short)FIRST;
+            far = __builtin_elementwise_max(far, from_first);
+            at[k] = (b >> (unsigned short)15) * (unsigned short)COUNT + from_first;
+        }
+        if (__any(far.x >= COUNT || far.y >= COUNT)) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) out[2 * k] = value(s24_num<uint16_t>::lo(z[k])), out[2 * k + 1] = value(s24_num<uint16_t>::hi(z[k]));
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) out[2 * k] = tab[at[k].x], out[2 * k + 1] = tab[at[k].y];
+        }
+    }
+};
+
 // ACT_MODE 1 (forward of an ungated layer): the rounded tile Z is written to Out and H = act(Z) beside it, as the
 // stand-alone activation kernel would form it from the stored Z.  ACT_MODE 2 (input gradient of the second
 // projection): the rounded tile of dH is not written but multiplied by act'(Z), Z read from `GU`, into Out = dZ.
@@ -399,6 +448,19 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
     };
     auto pack_index = [&](uint2 d) { return __builtin_amdgcn_perm(d.y, d.x, half_sel); };
 
+    // The activation's table, where it serves: H's fits beside the ring of the two larger tiles and is computed under the first copies,
+    // the other ones lie in the part of the drained ring that parks no tile.
+    typedef ActTable<ACT_MODE, ACT> Table;
+    constexpr bool TABLE = ACT_MODE != 0 && ACT == S24_ACT_GELU_ERF && std::is_same_v<T, uint16_t>;
+    constexpr bool EARLY_TABLE = TABLE && ACT_MODE == 1 && MI == 4;
+    constexpr int PARKED = MI == 4 && WN == 4 ? 2 * EWAVE : 0;   // in s2
+    static_assert(!TABLE || EARLY_TABLE || PARKED + Table::BYTES <= STAGE, "the table must fit");
+    typename Table::entry *table = reinterpret_cast<typename Table::entry *>(s2 + PARKED);
+    if constexpr (EARLY_TABLE) {
+        __shared__ typename Table::entry s_table[2 * Table::COUNT];
+        table = s_table;
+    }
+
     // keep the program order of these groups: the constant wait counts rely on it
     issue_all(s0, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -408,6 +470,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
 #pragma unroll
     for (int c = 0; c < EARLY; ++c) issue(s2, c);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (EARLY_TABLE) Table::template build<128 * WN>(table, tid);
     wait_and_barrier<NC + EARLY>();   // chunk 0 has landed for everybody
     uint4 fb[4][2];      // token fragments of the chunk about to be multiplied, first-half feature fragments and index words
     bf16x8 fa0[MI];
@@ -577,22 +640,37 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
 #pragma unroll
         for (int j = 0; j < LPR; ++j)
             z[j] = s24_load_stream(GU + (int64_t)min(n_base + RPP * j + lane / LPR, N - 1) * M + m);
+        if constexpr (TABLE) {   // under the loads of Z
+            Table::template build<128 * WN>(table, tid);
+            wait_and_barrier<63>();
+        }
 #pragma unroll
         for (int j = 0; j < LPR; ++j) {
             const int nl = RPP * j + lane / LPR, n = n_base + nl;
             const uint4 dh = staged_chunk<MI>(est, nl, c);
             const uint32_t dw[4] = {dh.x, dh.y, dh.z, dh.w}, zw[4] = {z[j].x, z[j].y, z[j].z, z[j].w};
             uint32_t o[4];
+            float slope[8];
+            if constexpr (TABLE) {
+                Table::lookup(table, zw, slope);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    slope[2 * k] = s24_act_slope<ACT>(s24_num<T>::lo(zw[k])), slope[2 * k + 1] = s24_act_slope<ACT>(s24_num<T>::hi(zw[k]));
+            }
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                o[k] = s24_num<T>::pack2(s24_num<T>::lo(dw[k]) * s24_act_slope<ACT>(s24_num<T>::lo(zw[k])),
-                                         s24_num<T>::hi(dw[k]) * s24_act_slope<ACT>(s24_num<T>::hi(zw[k])));
+                o[k] = s24_num<T>::pack2(s24_num<T>::lo(dw[k]) * slope[2 * k], s24_num<T>::hi(dw[k]) * slope[2 * k + 1]);
             if (n < N && m_base + 8 * c < M)   // M is a multiple of 16: a chunk is all in or all out
                 *reinterpret_cast<uint4 *>(Out + (int64_t)n * M + m) = make_uint4(o[0], o[1], o[2], o[3]);
         }
     } else if constexpr (ACT_MODE == 1) {
         unsigned char *est = region(wave);
         stage_tile<T, MI>(acc, est, lane);
+        if constexpr (TABLE && !EARLY_TABLE) {
+            Table::template build<128 * WN>(table, tid);
+            wait_and_barrier<0>();
+        }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
         asm volatile("" ::: "memory");
@@ -606,9 +684,16 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
             const uint4 zc = staged_chunk<MI>(est, nl, c);
             const uint32_t zw[4] = {zc.x, zc.y, zc.z, zc.w};
             uint32_t h[4];
+            if constexpr (TABLE) {
+                uint16_t v[8];
+                Table::lookup(table, zw, v);
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                h[k] = s24_num<T>::pack2(s24_act_value<ACT>(s24_num<T>::lo(zw[k])), s24_act_value<ACT>(s24_num<T>::hi(zw[k])));
+                for (int k = 0; k < 4; ++k) h[k] = v[2 * k] | ((uint32_t)v[2 * k + 1] << 16);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    h[k] = s24_num<T>::pack2(s24_act_value<ACT>(s24_num<T>::lo(zw[k])), s24_act_value<ACT>(s24_num<T>::hi(zw[k])));
+            }
             s24_store_stream(Out + (int64_t)n * M + m, zc);
             *reinterpret_cast<uint4 *>(H + (int64_t)n * M + m) = make_uint4(h[0], h[1], h[2], h[3]);
         }

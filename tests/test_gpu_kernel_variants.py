@@ -434,6 +434,43 @@ def test_calls_go_to_the_current_stream(s24):
         assert binding._stream() == side.cuda_stream != torch.cuda.default_stream().cuda_stream
 
 
+# ------------------------------------------------------------------ GELU in the epilogues
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+# the 128 x 128, the 256 x 128 and the 256 x 256 tile, ragged in the tokens
+@pytest.mark.parametrize("p,q,tile", [(8136, 64, (2, 2)), (8136, 2112, (4, 2)), (16390, 2112, (4, 4))])
+def test_gelu_of_every_16_bit_value_in_the_epilogues(s24, dtype, p, q, tile):
+    """H and dZ have the bits of the activation kernels for each of the 65536 values that Z can hold."""
+    td, r = torch_dtype(dtype), 1024
+    new = lambda: torch.empty((p, r), dtype=td, device="cuda")
+    bits = lambda x: x.view(torch.int16)
+    W = torch.zeros((r, q), dtype=td, device="cuda")
+    W[torch.arange(r), torch.arange(r) % 4] = 1.0             # Z[n][m] = X[n][m % 4]
+    v, vt = (torch.empty((a // 64, b, 32), dtype=td, device="cuda") for a, b in ((q, r), (r, q)))
+    m, mt = (torch.empty((a // 64, b, 4), dtype=torch.int16, device="cuda") for a, b in ((q, r), (r, q)))
+    s24.compress(W, None, v, m, vt, mt)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    dY = torch.randn((p, q), generator=g, device="cuda").to(td)
+    seen = torch.zeros(65536, dtype=torch.bool, device="cuda")
+    for first in range(0, 65536, 4 * p):
+        every = (first + torch.arange(4 * p, device="cuda")) % 65536
+        X = torch.zeros((p, q), dtype=td, device="cuda")
+        X[:, :4] = every.to(torch.int16).view(td).view(p, 4)
+        Z, H, two = new(), new(), new()
+        assert tiles_run(lambda: s24.spmm_fwd_act(X, v, m, None, Z, H, s24.ACT_GELU_ERF)) == [tile]
+        s24.act_fwd(Z, two, s24.ACT_GELU_ERF)
+        assert torch.equal(bits(H), bits(two))
+        seen[bits(Z).flatten().long() & 0xFFFF] = True
+        Z = every.to(torch.int16).view(td).view(p, 4).repeat(1, r // 4).contiguous()
+        dH, dZ = new(), new()
+        assert tiles_run(lambda: s24.spmm_bwd_dx_act(dY, v, m, Z, dZ, s24.ACT_GELU_ERF)) == [tile]
+        s24.spmm_bwd_dx(dY, v, m, dH)
+        s24.act_bwd(dH, Z, two, s24.ACT_GELU_ERF)
+        assert torch.equal(bits(dZ), bits(two))
+    value = torch.arange(65536, device="cuda").to(torch.int16).view(td).float()
+    normal = value.abs() >= (2.0 ** -126 if dtype == "bf16" else 2.0 ** -14)
+    assert bool(seen[value.isfinite() & normal].all())        # the forward met every normal value
+
+
 # ------------------------------------------------------------------ weight gradients on the 256 x 128 tile
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 # 144 such tiles in all; whole chunks and remainders; edges ragged along both axes; and 288 small ones, the cheaper up to
