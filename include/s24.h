@@ -111,6 +111,19 @@ int s24_compress(const void *W, s24_dtype dt, int64_t r, int64_t q, int64_t ldw,
                  const uint16_t *mask, void *vals, uint16_t *meta, void *valsT, uint16_t *metaT,
                  uint16_t *mask_out, void *stream);
 
+/* s24_compress of up to four weights of one dtype in one pass, each as the call of its own would leave it: the masks of all of
+ * them are searched (mask NULL) or those of all of them are given.  Every weight is checked before anything is written. */
+typedef struct {
+    const void *W;
+    const uint16_t *mask;
+    void *vals;
+    uint16_t *meta;
+    void *valsT;
+    uint16_t *metaT, *mask_out;
+    int64_t r, q, ldw;
+} s24_compress_problem;
+int s24_compress_batch(const s24_compress_problem *problems, int count, s24_dtype dt, void *stream);
+
 /* Forward sparse GEMM (Eq. 2):  Y[p][r] = X[p][q] . (M.*W)^T, contraction over
  * q against the compressed weight (vals [q/64][r][32], meta [q/64][r][4]).
  * 16-bit in / fp32 accumulate / 16-bit out (f32 throughout for S24_F32).

@@ -28,6 +28,7 @@ _SIGNATURES = {
     "s24_pattern_table": (_int, [_vp]),
     "s24_transposable_mask": (_int, [_vp, _int, _i64, _i64, _i64, _vp, _vp, _vp]),
     "s24_compress": (_int, [_vp, _int, _i64, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _vp, _vp]),
+    "s24_compress_batch": (_int, [_vp, _int, _int, _vp]),
     "s24_spmm_fwd": (_int, [_vp, _vp, _vp, _vp, _i64, _i64, _i64, _int, _vp]),
     "s24_spmm_fwd_bias": (_int, [_vp, _vp, _vp, _vp, _vp, _i64, _i64, _i64, _int, _vp]),
     "s24_spmm_fwd_glu": (_int, [_vp, _vp, _vp, _vp, _vp, _vp, _i64, _i64, _i64, _int, _int, _vp]),
@@ -155,6 +156,26 @@ def compress(W, mask, vals, meta, valsT, metaT, mask_out=None):
     r, q = W.shape
     _check(lib().s24_compress(_ptr(W), _dt(W), r, q, W.stride(0), _ptr(mask), _ptr(vals), _ptr(meta), _ptr(valsT),
                               _ptr(metaT), _ptr(mask_out), _stream()), "s24_compress")
+
+
+class _CompressProblem(C.Structure):
+    _fields_ = [("W", _vp), ("mask", _vp), ("vals", _vp), ("meta", _vp), ("valsT", _vp), ("metaT", _vp), ("mask_out", _vp),
+                ("r", _i64), ("q", _i64), ("ldw", _i64)]
+
+
+def compress_batch(weights):
+    """weights: up to four tuples (W, mask, vals, meta, valsT, metaT, mask_out) of one dtype, mask None in all of them (searched) or
+    in none; compress of each in one pass."""
+    arr = (_CompressProblem * len(weights))()
+    for k, (W, mask, vals, meta, valsT, metaT, mask_out) in enumerate(weights):
+        _rows("s24_compress_batch", W=W)
+        _dense("s24_compress_batch", mask=mask, vals=vals, meta=meta, valsT=valsT, metaT=metaT, mask_out=mask_out)
+        if W.dtype != weights[0][0].dtype:
+            raise ValueError("s24_compress_batch: the weights must share one dtype")
+        r, q = W.shape
+        arr[k] = _CompressProblem(_ptr(W), _ptr(mask), _ptr(vals), _ptr(meta), _ptr(valsT), _ptr(metaT), _ptr(mask_out), r, q,
+                                  W.stride(0))
+    _check(lib().s24_compress_batch(C.cast(arr, C.c_void_p), len(weights), _dt(weights[0][0]), _stream()), "s24_compress_batch")
 
 
 def spmm_fwd(X, vals, meta, Y):

@@ -2,8 +2,7 @@
 //
 // One lane owns one aligned 4x4 block at a time.  A workgroup of 256 lanes
 // takes a tile of 32 x 32 blocks (128 x 128 weights, four blocks per lane), or
-// of 32 x 16 or 16 x 16 for matrices with fewer of them than fill the chip
-// (launch_sized).  The compressed operands are stored chunk-major (64 of the
+// of 32 x 16 or 16 x 16 for matrices with few of them (launch_sized).  The compressed operands are stored chunk-major (64 of the
 // contraction axis per chunk, all rows of a chunk together), so a tile covers
 // one or two chunks of each orientation and the column-wise operand, after an
 // LDS transpose, leaves in runs of 4 or 8 KB.
@@ -35,6 +34,8 @@
 // binades than that window take a slow path that scores all 90 patterns in
 // 320-bit fixed point.
 #include <algorithm>
+#include <cstddef>
+#include <type_traits>
 
 #include "s24_common.h"
 
@@ -57,9 +58,11 @@ constexpr int kRowMult[4] = {216, 36, 6, 1};
 constexpr int kColBonus[4] = {0, 2, 3, 4};
 constexpr int kBonusBase = 2 * (216 + 36 + 6 + 1);  // every row contributes at least 2
 
+// Pattern by bonus: entries past the largest legal index, 5*216 + 5*36 = 1260, stand for every illegal one (mask and id 0).
+constexpr int kLutEntries = 1264;
 struct MaskLut {
-    uint16_t mask[1296];
-    uint8_t id[1296];
+    uint16_t mask[kLutEntries];
+    uint8_t id[kLutEntries];
 };
 
 // Index: sum_i 6^(3-i) * (5 - k_i) for row pair indices k_i.  Walking
@@ -88,8 +91,6 @@ constexpr MaskLut make_lut()
     return t;
 }
 
-__device__ const MaskLut g_lut = make_lut();
-
 struct PatList {
     uint16_t mask[S24_NUM_PATTERNS];
 };
@@ -97,7 +98,7 @@ constexpr PatList make_patlist()
 {
     PatList p{};
     const MaskLut t = make_lut();
-    for (int x = 0; x < 1296; ++x)
+    for (int x = 0; x < kLutEntries; ++x)
         if (t.mask[x] != 0) p.mask[t.id[x]] = t.mask[x];
     return p;
 }
@@ -147,7 +148,14 @@ constexpr CompressLut make_compress_lut()
     }
     return t;
 }
-__device__ const CompressLut g_clut = make_compress_lut();
+// All tables in one piece, so that a workgroup stages what it needs with one or two 16-byte loads per lane (1296 two-byte and 1296
+// one-byte entries one by one were twelve loads and as many LDS writes per lane, ahead of everything else).
+struct alignas(16) MaskTables {
+    MaskLut lut;
+    CompressLut clut;
+};
+static_assert(sizeof(MaskLut) % 16 == 0 && offsetof(MaskLut, id) % 16 == 0 && sizeof(CompressLut) % 16 == 0, "whole vectors");
+__device__ const MaskTables g_tables = {make_lut(), make_compress_lut()};
 
 // Pattern id of a given block mask through the bonus-indexed table: row nibble -> pair index k
 // (0 for anything illegal), then the same mixed-radix index the search produces.
@@ -410,7 +418,7 @@ __device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], cons
             best = __builtin_fmax(best, (dt[x] + db[w]) + cross[pair_of(y, z)]);
         }
     const unsigned bonus = (unsigned)__double2loint(best + big) & 0x7FFu;
-    const unsigned x = min(bonus - (unsigned)kBonusBase, 1295u);   // (a wide block's index is clamped and unused)
+    const unsigned x = min(bonus - (unsigned)kBonusBase, kLutEntries - 1u);   // (a wide block's index is clamped and unused)
     return COOPERATIVE && wide ? rare : (unsigned)lut_mask[x] | ((unsigned)lut_id[x] << 16);
 }
 
@@ -493,7 +501,7 @@ __device__ __forceinline__ unsigned int_best_pattern(const uint32_t (&mag)[16], 
                 if (c != x && c != w) (y < 0 ? y : z) = c;
             best = max(best, dt[x] + db[w] + cross[pair_of(y, z)]);
         }
-    const unsigned xi = min((best & 0x7FFu) - (unsigned)kBonusBase, 1295u);
+    const unsigned xi = min((best & 0x7FFu) - (unsigned)kBonusBase, kLutEntries - 1u);
     return (unsigned)lut_mask[xi] | ((unsigned)lut_id[xi] << 16);
 }
 
@@ -552,15 +560,32 @@ template <> struct RowOps<float> {
 
 // A workgroup's tile is TBW blocks wide and 256 / TBW * S blocks tall, S blocks per lane.
 //   32 x 32 (S = 4): the lookup tables are staged once per 1024 blocks and the next block's rows are requested while the
-//   current one is scored: the better shape once there are several tiles per compute unit.
-//   16 x 16 (S = 1): four times as many workgroups, for matrices whose 32 x 32 tiles do not fill the chip, where a lane
-//   walking four blocks one after the other is what takes the time; 32 x 16 (S = 2) between the two.
+//   current one is scored: the better shape for the largest matrices.
+//   16 x 16 (S = 1): four times as many workgroups of a quarter of the length; 32 x 16 (S = 2) between the two.
+// A launch covers up to kMaxWeights weights: tiles first_tile[i] .. first_tile[i+1]-1 belong to weight i (unused entries repeat the
+// total).  A launch for a weight of a million parameters is mostly its start, one workgroup's way through and its drain.  Both weights of a
+// layer, searched and compressed, in a launch each and (with the tables staged as above) in one: 1024 x 256 fp32 17.3 -> 9.2 us,
+// 3072 x 768 bf16 16.2 -> 10.4, 5120 x 1280 27.9 -> 20.5; with given masks 3072 x 768 11.9 -> 7.9, 5504 x 2048 (two and one) 39.4 -> 34.
+constexpr int kMaxWeights = 4;
+struct MaskWeight {
+    const void *W;
+    int64_t ldw;
+    int br, bq;             // blocks
+    const uint16_t *mask_in;
+    uint16_t *mask_out;
+    uint8_t *index_out;
+    void *vals;
+    uint16_t *meta;
+    void *valsT;
+    uint16_t *metaT;
+};
+struct MaskBatch {
+    MaskWeight w[kMaxWeights];
+    int first_tile[kMaxWeights + 1];
+};
+
 template <typename T, bool SEARCH, bool COMPRESS, int TBW, int S>
-__global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict__ W, int64_t ldw, int br, int bq,
-                                                            const uint16_t *__restrict__ mask_in,
-                                                            uint16_t *__restrict__ mask_out, uint8_t *__restrict__ index_out,
-                                                            T *__restrict__ vals, uint16_t *__restrict__ meta,
-                                                            T *__restrict__ valsT, uint16_t *__restrict__ metaT)
+__global__ __launch_bounds__(256) void mask_compress_kernel(const MaskBatch batch)
 {
     using Ops = RowOps<T>;
     using Row = typename Ops::Row;
@@ -568,21 +593,43 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
     constexpr int LR = 256 / TBW, TBH = LR * S, PITCH = TBH + 1;   // rows of lanes, tile height, LDS pitch of the transposed pairs
     static_assert(!COMPRESS || TBH % 16 == 0, "a tile holds whole chunks of the column-wise operand");
     constexpr bool FAST = COMPRESS && sizeof(T) == 2;   // bf16: table-driven compressor
-    // bf16 search on its own: integer scoring with the blocks it cannot take queued for the fp64 path.  (In the fused
-    // search + compress kernel the four blocks' rows held in registers across the queue cost more than the cheaper
-    // scoring saves: measured 4-8 % slower, so it keeps the fp64 scoring inside its loop.)
-    constexpr bool DEFER = SEARCH && !COMPRESS && sizeof(T) == 2 && RowOps<T>::kWindow == 29;
+    // bf16 search on its own in the large tile: integer scoring, the blocks it cannot take queued for the fp64 path.  The queue is a
+    // second trip through the workgroup: in the smaller tiles, whose launches wait for one workgroup, fp64 scoring inside the loop is the faster
+    // (5120 x 1280: 8.8 -> 6.7 us).  (In the fused search + compress kernel the four blocks' rows held in registers across the queue cost
+    // more than the cheaper scoring saves: measured 4-8 % slower, so it keeps the fp64 scoring too.)
+    constexpr bool DEFER = SEARCH && !COMPRESS && sizeof(T) == 2 && RowOps<T>::kWindow == 29 && S == 4;
     __shared__ int s_nhard;
     __shared__ uint16_t s_hard[DEFER ? 256 * S : 1];
     __shared__ uint32_t s_fix[DEFER ? 256 * S : 1];
-    __shared__ uint16_t s_lut_mask[SEARCH ? 1296 : 1];
-    __shared__ uint8_t s_lut_id[(SEARCH || FAST) ? 1296 : 1];
-    __shared__ uint4 s_clut[FAST ? 3 * S24_NUM_PATTERNS : 1];
+    // the part of the tables that this instance uses: masks for a search, ids, compressor entries
+    constexpr int TAB_FIRST = SEARCH ? 0 : offsetof(MaskLut, id) / 16, TAB_LAST = (FAST ? sizeof(MaskTables) : sizeof(MaskLut)) / 16;
+    constexpr int TAB = SEARCH || FAST ? TAB_LAST - TAB_FIRST : 0, TAB_PER_LANE = (TAB + 255) / 256;
+    __shared__ uint4 s_tables[TAB ? TAB : 1];
+    const uint16_t *s_lut_mask = reinterpret_cast<const uint16_t *>(s_tables);
+    const uint8_t *s_lut_id = reinterpret_cast<const uint8_t *>(s_tables + (SEARCH ? offsetof(MaskLut, id) / 16 : 0));
+    const uint4 *s_clut = s_tables + (sizeof(MaskLut) / 16 - TAB_FIRST);
     __shared__ Pair s_valsT[COMPRESS ? 4 * TBW * PITCH : 1];
     __shared__ uint8_t s_nibT[COMPRESS ? 4 * TBW * PITCH : 1];
 
     const int tid = threadIdx.x;
-    const int bj0 = blockIdx.x * TBW, bi0 = blockIdx.y * TBH;
+    uint4 table[TAB_PER_LANE ? TAB_PER_LANE : 1];   // requested ahead of the weights: it is in the L2 and there first
+#pragma unroll
+    for (int k = 0; k < TAB_PER_LANE; ++k) table[k] = reinterpret_cast<const uint4 *>(&g_tables)[TAB_FIRST + min(tid + 256 * k, TAB - 1)];
+    int which = 0;   // wave-uniform
+#pragma unroll
+    for (int i = 1; i < kMaxWeights; ++i)
+        if ((int)blockIdx.x >= batch.first_tile[i]) which = i;
+    const MaskWeight &weight = batch.w[which];
+    const T *__restrict__ W = static_cast<const T *>(weight.W);
+    const int64_t ldw = weight.ldw;
+    const int br = weight.br, bq = weight.bq;
+    const uint16_t *__restrict__ mask_in = weight.mask_in;
+    uint16_t *__restrict__ mask_out = weight.mask_out;
+    uint8_t *__restrict__ index_out = weight.index_out;
+    T *__restrict__ vals = static_cast<T *>(weight.vals), *__restrict__ valsT = static_cast<T *>(weight.valsT);
+    uint16_t *__restrict__ meta = weight.meta, *__restrict__ metaT = weight.metaT;
+    const unsigned tile = blockIdx.x - (unsigned)batch.first_tile[which], tiles_q = (unsigned)(bq + TBW - 1) / TBW;
+    const int bj0 = (int)(tile % tiles_q) * TBW, bi0 = (int)(tile / tiles_q) * TBH;
     const int lbj = tid % TBW;
     const int bj = bj0 + lbj;
     const int64_t R = 4 * (int64_t)br, Q = 4 * (int64_t)bq;  // rows of vals / of valsT
@@ -604,6 +651,36 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
 #pragma unroll
             for (int j = 0; j < 4; ++j) mag[4 * i + j] = Ops::mag(rows[i], j);
     };
+    // Index words along q.  nib_lo, nib_hi: a block's nibbles of rows 0 and 1, and of 2 and 3, 16 bits apart.  Four lanes' nibbles
+    // form a word, the four words of a chunk's 16 lanes a row's eight bytes, and the block row's four rows are contiguous: the
+    // first of the 16 lanes gathers all of it and stores 32 bytes (2-byte stores from every fourth lane were four of them).
+    auto store_meta = [&](uint32_t nib_lo, uint32_t nib_hi, int bi, bool valid) {
+        auto from = [](uint32_t v, auto lanes) {   // of the lane so many further up in the group of 16 (row_shl)
+            return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x100 + decltype(lanes)::value, 0xF, 0xF, true);
+        };
+        const std::integral_constant<int, 1> l1;
+        const std::integral_constant<int, 2> l2;
+        const std::integral_constant<int, 4> l4;
+        const std::integral_constant<int, 8> l8;
+        nib_lo |= from(nib_lo, l1) << 4;
+        nib_hi |= from(nib_hi, l1) << 4;
+        nib_lo |= from(nib_lo, l2) << 8;
+        nib_hi |= from(nib_hi, l2) << 8;
+        const uint32_t next_lo = from(nib_lo, l4), next_hi = from(nib_hi, l4);
+        uint32_t row[4][2];   // words 0 and 1 of rows 0 .. 3
+        row[0][0] = __builtin_amdgcn_perm(next_lo, nib_lo, 0x05040100u);
+        row[1][0] = __builtin_amdgcn_perm(next_lo, nib_lo, 0x07060302u);
+        row[2][0] = __builtin_amdgcn_perm(next_hi, nib_hi, 0x05040100u);
+        row[3][0] = __builtin_amdgcn_perm(next_hi, nib_hi, 0x07060302u);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) row[i][1] = from(row[i][0], l8);   // words 2 and 3
+        if (valid && (lbj & 15) == 0) {   // br and bq are multiples of 16: the 16 lanes are all inside the matrix or all outside
+            typedef uint32_t two_rows __attribute__((ext_vector_type(4), aligned(8)));
+            two_rows *dst = reinterpret_cast<two_rows *>(meta + ((int64_t)(bj >> 4) * R + 4 * bi) * 4);
+            dst[0] = two_rows{row[0][0], row[0][1], row[1][0], row[1][1]};
+            dst[1] = two_rows{row[2][0], row[2][1], row[3][0], row[3][1]};
+        }
+    };
     // What follows the search for block s of this lane (rows in registers, mask m and pattern id known):
     // the mask and id stores and, when compressing, both compressed orientations.
     auto emit = [&](const Row (&rows)[4], unsigned m, unsigned id, int s) {
@@ -617,7 +694,7 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
             }
         }
         if constexpr (FAST) {
-            if constexpr (!SEARCH) id = s_lut_id[min(lut_index_of_mask(m), 1295u)];
+            if constexpr (!SEARCH) id = s_lut_id[min(lut_index_of_mask(m), kLutEntries - 1u)];
             const uint4 rsel = s_clut[3 * id], csel = s_clut[3 * id + 1], mt = s_clut[3 * id + 2];
             const uint32_t rs[4] = {rsel.x, rsel.y, rsel.z, rsel.w}, cs[4] = {csel.x, csel.y, csel.z, csel.w};
             // along q: one dword (two kept bf16) per block row.  The four lanes of a quad (four neighbouring blocks
@@ -647,18 +724,7 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
                 *reinterpret_cast<uint4 *>(reinterpret_cast<uint32_t *>(vals) + ((int64_t)(bj >> 4) * R + 4 * bi + (lbj & 3)) * 16 + (bj & 12)) =
                     make_uint4(pr[0], pr[1], pr[2], pr[3]);
             uint32_t nib_lo = mt.x, nib_hi = mt.y;
-            nib_lo |= (uint32_t)__shfl_down((int)nib_lo, 1) << 4;
-            nib_hi |= (uint32_t)__shfl_down((int)nib_hi, 1) << 4;
-            nib_lo |= (uint32_t)__shfl_down((int)nib_lo, 2) << 8;
-            nib_hi |= (uint32_t)__shfl_down((int)nib_hi, 2) << 8;
-            if (valid && (lbj & 3) == 0) {
-                const int w = bj >> 2;  // metadata word of the row: chunk w/4, word w%4
-                uint16_t *mrow = meta + ((int64_t)(w >> 2) * R + 4 * bi) * 4 + (w & 3);
-                mrow[0] = (uint16_t)(nib_lo & 0xFFFFu);
-                mrow[4] = (uint16_t)(nib_lo >> 16);
-                mrow[8] = (uint16_t)(nib_hi & 0xFFFFu);
-                mrow[12] = (uint16_t)(nib_hi >> 16);
-            }
+            store_meta(nib_lo, nib_hi, bi, valid);
             // along r: gather each column from the four rows, pick its two kept rows, park in LDS
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -686,19 +752,7 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
                 if (i < 2) nib_lo |= nib << (16 * i);
                 else nib_hi |= nib << (16 * (i - 2));
             }
-            // four neighbouring lanes (same block row) form one metadata word per row
-            nib_lo |= (uint32_t)__shfl_down((int)nib_lo, 1) << 4;
-            nib_hi |= (uint32_t)__shfl_down((int)nib_hi, 1) << 4;
-            nib_lo |= (uint32_t)__shfl_down((int)nib_lo, 2) << 8;
-            nib_hi |= (uint32_t)__shfl_down((int)nib_hi, 2) << 8;
-            if (valid && (lbj & 3) == 0) {
-                const int w = bj >> 2;  // metadata word of the row: chunk w/4, word w%4
-                uint16_t *mrow = meta + ((int64_t)(w >> 2) * R + 4 * bi) * 4 + (w & 3);
-                mrow[0] = (uint16_t)(nib_lo & 0xFFFFu);
-                mrow[4] = (uint16_t)(nib_lo >> 16);
-                mrow[8] = (uint16_t)(nib_hi & 0xFFFFu);
-                mrow[12] = (uint16_t)(nib_hi >> 16);
-            }
+            store_meta(nib_lo, nib_hi, bi, valid);
             // along r: kept rows of each column go through LDS to be written transposed
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -718,18 +772,12 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
         }
     };
 
-    // the lookup tables go to LDS; the weights' first loads are issued ahead of this
     auto stage_tables = [&]() {
         if (DEFER && tid == 0) s_nhard = 0;
-        if constexpr (SEARCH || FAST) {
-            for (int x = tid; x < 1296; x += 256) {
-                if constexpr (SEARCH) s_lut_mask[x] = g_lut.mask[x];
-                s_lut_id[x] = g_lut.id[x];
-            }
-            if constexpr (FAST) {
-                const uint4 *src = reinterpret_cast<const uint4 *>(&g_clut);
-                for (int x = tid; x < 3 * S24_NUM_PATTERNS; x += 256) s_clut[x] = src[x];
-            }
+        if constexpr (TAB > 0) {
+#pragma unroll
+            for (int k = 0; k < TAB_PER_LANE; ++k)
+                if (tid + 256 * k < TAB) s_tables[tid + 256 * k] = table[k];
             __syncthreads();
         }
     };
@@ -741,11 +789,9 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
         // wave in a divergent branch.
         Row blk[S][4];
         unsigned res[S];
-        // (four blocks' loads ahead of the tables' would make the tables wait for all of them: 51 against 47 us at 22016 x 4096)
-        if (S > 1) stage_tables();
 #pragma unroll
         for (int s = 0; s < S; ++s) fetch(blk[s], wrow + (int64_t)(4 * LR * s) * ldw, (bi0 + tid / TBW + LR * s < br) && (bj < bq));
-        if (S == 1) stage_tables();
+        stage_tables();
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const bool valid = (bi0 + tid / TBW + LR * s < br) && (bj < bq);
@@ -774,28 +820,33 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
     } else {
         // The rows of the next block are requested before the current one is scored.
         Row nxt[4];
-        fetch(nxt, wrow, (bi0 + tid / TBW < br) && (bj < bq));
+        unsigned m_nxt = 0x33CCu;
+        const uint16_t *mrow = mask_in + (int64_t)(bi0 + tid / TBW) * bq + bj;
+        auto request = [&](int bi) {
+            const bool ok = (bi < br) && (bj < bq);
+            fetch(nxt, wrow, ok);
+            if constexpr (!SEARCH) m_nxt = ok ? *mrow : 0x33CCu;
+        };
+        request(bi0 + tid / TBW);
         stage_tables();
 #pragma unroll 1
         for (int s = 0; s < S; ++s) {
             const int bi = bi0 + tid / TBW + LR * s;
-            const bool valid = (bi < br) && (bj < bq);
             Row rows[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) rows[i] = nxt[i];
+            unsigned m = m_nxt, id = 0;
             if (s + 1 < S) {
                 wrow += 4 * LR * ldw;
-                fetch(nxt, wrow, (bi + LR < br) && (bj < bq));
+                mrow += (int64_t)LR * bq;
+                request(bi + LR);
             }
-            unsigned m = 0, id = 0;
             if constexpr (SEARCH) {
                 uint32_t mag[16];
                 magnitudes(rows, mag);
                 const unsigned res = best_pattern<Ops::kWindow, Ops::kWide, sizeof(T) == 4>(mag, s_lut_mask, s_lut_id);
                 m = res & 0xFFFFu;
                 id = res >> 16;
-            } else {
-                m = valid ? mask_in[(int64_t)bi * bq + bj] : 0x33CCu;
             }
             emit(rows, m, id, s);
         }
@@ -818,8 +869,9 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
                 if constexpr (sizeof(Pair) == 4) {
                     *reinterpret_cast<uint4 *>(dst) = make_uint4(src[0], src[1], src[2], src[3]);
                 } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) dst[e] = src[e];
+                    uint4 *two = reinterpret_cast<uint4 *>(dst);
+                    two[0] = make_uint4(src[0].x, src[0].y, src[1].x, src[1].y);
+                    two[1] = make_uint4(src[2].x, src[2].y, src[3].x, src[3].y);
                 }
             }
         }
@@ -843,41 +895,53 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const T *__restrict_
 }
 
 template <typename T, bool SEARCH, bool COMPRESS, int TBW, int S>
-int launch_tiles(const T *W, int64_t ldw, int br, int bq, const uint16_t *mask_in, uint16_t *mask_out, uint8_t *index_out, T *vals,
-                 uint16_t *meta, T *valsT, uint16_t *metaT, hipStream_t st)
+int launch_tiles(MaskBatch &batch, int count, hipStream_t st)
 {
     constexpr int TBH = 256 / TBW * S;
-    const dim3 grid((bq + TBW - 1) / TBW, (br + TBH - 1) / TBH), block(256);
-    hipLaunchKernelGGL((mask_compress_kernel<T, SEARCH, COMPRESS, TBW, S>), grid, block, 0, st, W, ldw, br, bq, mask_in, mask_out,
-                       index_out, vals, meta, valsT, metaT);
+    int64_t tiles = 0;
+    for (int i = 0; i <= kMaxWeights; ++i) {
+        batch.first_tile[i] = (int)tiles;
+        if (i < count) tiles += (int64_t)((batch.w[i].bq + TBW - 1) / TBW) * ((batch.w[i].br + TBH - 1) / TBH);
+        S24_REQUIRE(tiles < (1 << 24), S24_ERR_SHAPE);   // a launch holds less than 2^32 work items
+    }
+    if (tiles == 0) return S24_OK;
+    hipLaunchKernelGGL((mask_compress_kernel<T, SEARCH, COMPRESS, TBW, S>), dim3((unsigned)tiles), dim3(256), 0, st, batch);
     return s24_launch_status();
 }
-// Which tile, by the number of 32 x 32 tiles in compute units (256 of them; measured in us; 32 x 32 / 32 x 16 / 16 x 16 blocks):
-//   bf16 search + compress   144 tiles (3072 x 768): 8.2 / 7.4 / 6.5    400 (5120 x 1280): 12.2 / 11.7 / 12.4    5504: 87 / 99 / 115
-//   bf16 given mask          144: 7.7 / 6.2 / 5.4    400: 10.8 / 10.0 / 9.3    1376 (11008 x 2048): 28.1 / 24.8 / 25.5    5504: 82 / 83 / 89
-//   fp32 search + compress   16 (1024 x 256): 18.5 / 11.6 / 7.8    400: 33.9 / 31.3 / 29.4    5504: 258 / 254 / 258
-template <typename T, bool SEARCH, bool COMPRESS, typename... Args>
-int launch_sized(const T *W, int64_t ldw, int br, int bq, Args... args)
+// Which tile, by the number of 32 x 32 tiles of all weights together, in compute units (256 of them); measured in us, 32 x 32 / 32 x 16 /
+// 16 x 16 blocks.  The small tile has the shortest way through a workgroup, which is what a launch of few tiles waits for:
+//   bf16 search            100 tiles: 6.5 / 4.4 / 3.9    400: 9.0 / 7.9 / 6.7    1376: 17.7 / 18.9 / 16.8    2752: 36.0 / 39.3 / 38.0
+//   fp16, fp32 search      400: 9.3 / 8.3 / 7.0, 14.0 / 12.1 / 11.2    2752: 34.5 / 35.4 / 33.5, 48.1 / 47.4 / 44.8
+//   bf16 search, compress  288: 12.4 / 11.0 / 10.4    800: 20.9 / 20.4 / 20.5    1300: 28.3 / 29.0 / 28.7    5504: 93 / 103 / 103
+//   fp32 search, compress  32: 20.1 / 12.8 / 9.2    512: 32.1 / 32.4 / 30.0    2048: 95.9 / 97.3 / 90.5
+//   bf16 given mask        288: 10.0 / 8.9 / 7.9    800: 17.4 / 16.4 / 16.2    1376: 26.4 / 23.7 / 23.9    8192: 115 / 114 / 122
+//   fp32 given mask        128: 16.3 / 11.1 / 9.2    288: 22.0 / 17.6 / 18.7    512: 28.8 / 25.8 / 29.2    2048: 95.2 / 99.9 / 97.6
+template <typename T, bool SEARCH, bool COMPRESS> int launch_sized(MaskBatch &batch, int count, hipStream_t st)
 {
-    const int64_t tiles = (int64_t)((bq + 31) / 32) * ((br + 31) / 32);
+    constexpr bool HALF = sizeof(T) == 2;
+    int64_t tiles = 0;
+    for (int i = 0; i < count; ++i) tiles += (int64_t)((batch.w[i].bq + 31) / 32) * ((batch.w[i].br + 31) / 32);
     const int64_t cus = s24_cu_count();
-    if (tiles < (SEARCH && sizeof(T) == 2 ? 75 * cus / 64 : 2 * cus)) return launch_tiles<T, SEARCH, COMPRESS, 16, 1>(W, ldw, br, bq, args...);
-    if constexpr (!SEARCH && sizeof(T) == 2)
-        if (tiles < 16 * cus) return launch_tiles<T, SEARCH, COMPRESS, 32, 2>(W, ldw, br, bq, args...);
-    return launch_tiles<T, SEARCH, COMPRESS, 32, 4>(W, ldw, br, bq, args...);
+    if constexpr (SEARCH && (HALF ? !COMPRESS && RowOps<T>::kWindow != 29 : true)) {
+        return launch_tiles<T, SEARCH, COMPRESS, 16, 1>(batch, count, st);
+    } else {
+        if (tiles < (!COMPRESS ? 8 : HALF ? 4 : 1) * cus) return launch_tiles<T, SEARCH, COMPRESS, 16, 1>(batch, count, st);
+        if constexpr (!SEARCH)
+            if (HALF || tiles < 4 * cus) return launch_tiles<T, SEARCH, COMPRESS, 32, 2>(batch, count, st);
+        if constexpr (SEARCH || !HALF) return launch_tiles<T, SEARCH, COMPRESS, 32, 4>(batch, count, st);
+    }
 }
 
-template <typename T>
-int launch(const void *W, int64_t r, int64_t q, int64_t ldw, const uint16_t *mask_in, uint16_t *mask_out,
-           uint8_t *index_out, void *vals, uint16_t *meta, void *valsT, uint16_t *metaT, bool compress, hipStream_t st)
+// `count` weights of one dtype; the masks of all of them are searched, or those of all of them are given
+int launch(MaskBatch &batch, int count, s24_dtype dt, bool compress, hipStream_t st)
 {
-    const int br = (int)(r / 4), bq = (int)(q / 4);
-    if (br == 0 || bq == 0) return S24_OK;
-    const T *w = static_cast<const T *>(W);
-    T *v = static_cast<T *>(vals), *vt = static_cast<T *>(valsT);
-    if (!compress) return launch_sized<T, true, false>(w, ldw, br, bq, nullptr, mask_out, index_out, nullptr, nullptr, nullptr, nullptr, st);
-    if (mask_in) return launch_sized<T, false, true>(w, ldw, br, bq, mask_in, nullptr, nullptr, v, meta, vt, metaT, st);
-    return launch_sized<T, true, true>(w, ldw, br, bq, nullptr, mask_out, nullptr, v, meta, vt, metaT, st);
+    const bool search = batch.w[0].mask_in == nullptr;
+    auto run = [&](auto t) {
+        using T = decltype(t);
+        if (!compress) return launch_sized<T, true, false>(batch, count, st);
+        return search ? launch_sized<T, true, true>(batch, count, st) : launch_sized<T, false, true>(batch, count, st);
+    };
+    return dt == S24_BF16 ? run(uint16_t{}) : dt == S24_F16 ? run(s24_half{}) : run(float{});
 }
 
 // ------------------------------------------------------------------ monitors
@@ -1072,31 +1136,44 @@ extern "C" int s24_transposable_mask(const void *W, s24_dtype dt, int64_t r, int
     const int rc = check_weight(W, dt, r, q, ldw, 4);
     if (rc != S24_OK || r == 0 || q == 0) return rc;
     S24_REQUIRE(mask != nullptr, S24_ERR_NULL);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (dt == S24_BF16)
-        return launch<uint16_t>(W, r, q, ldw, nullptr, mask, index, nullptr, nullptr, nullptr, nullptr, false, st);
-    if (dt == S24_F16)
-        return launch<s24_half>(W, r, q, ldw, nullptr, mask, index, nullptr, nullptr, nullptr, nullptr, false, st);
-    return launch<float>(W, r, q, ldw, nullptr, mask, index, nullptr, nullptr, nullptr, nullptr, false, st);
+    MaskBatch batch{};
+    batch.w[0] = MaskWeight{W, ldw, (int)(r / 4), (int)(q / 4), nullptr, mask, index, nullptr, nullptr, nullptr, nullptr};
+    return launch(batch, 1, dt, false, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int s24_compress(const void *W, s24_dtype dt, int64_t r, int64_t q, int64_t ldw, const uint16_t *mask,
                             void *vals, uint16_t *meta, void *valsT, uint16_t *metaT, uint16_t *mask_out, void *stream)
 {
-    const int rc = check_weight(W, dt, r, q, ldw, 64);
-    if (rc != S24_OK || r == 0 || q == 0) return rc;
-    S24_REQUIRE(vals && meta && valsT && metaT, S24_ERR_NULL);
-    // the kernel stores 16 bytes of values and 8 bytes of index words at a time (and the GEMMs that consume the
-    // operands copy them in 16-byte pieces)
-    S24_REQUIRE(s24_aligned(vals, 16) && s24_aligned(valsT, 16) && s24_aligned(meta, 8) && s24_aligned(metaT, 8) &&
-                    s24_aligned(mask, 2) && s24_aligned(mask_out, 2),
-                S24_ERR_ALIGN);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (dt == S24_BF16)
-        return launch<uint16_t>(W, r, q, ldw, mask, mask_out, nullptr, vals, meta, valsT, metaT, true, st);
-    if (dt == S24_F16)
-        return launch<s24_half>(W, r, q, ldw, mask, mask_out, nullptr, vals, meta, valsT, metaT, true, st);
-    return launch<float>(W, r, q, ldw, mask, mask_out, nullptr, vals, meta, valsT, metaT, true, st);
+    const s24_compress_problem problem{W, mask, vals, meta, valsT, metaT, mask_out, r, q, ldw};
+    return s24_compress_batch(&problem, 1, dt, stream);
+}
+
+extern "C" int s24_compress_batch(const s24_compress_problem *problems, int count, s24_dtype dt, void *stream)
+{
+    S24_REQUIRE(s24_valid_dtype(dt), S24_ERR_DTYPE);
+    S24_REQUIRE(count >= 0 && count <= kMaxWeights, S24_ERR_SHAPE);
+    if (count == 0) return S24_OK;
+    S24_REQUIRE(problems != nullptr, S24_ERR_NULL);
+    MaskBatch batch{};
+    int used = 0;
+    for (int i = 0; i < count; ++i) {   // every weight is checked before anything is launched
+        const s24_compress_problem &pr = problems[i];
+        const int rc = check_weight(pr.W, dt, pr.r, pr.q, pr.ldw, 64);
+        if (rc != S24_OK) return rc;
+        if (pr.r == 0 || pr.q == 0) continue;
+        S24_REQUIRE(pr.vals && pr.meta && pr.valsT && pr.metaT, S24_ERR_NULL);
+        // the kernel stores 16 bytes of values and 8 bytes of index words at a time (and the GEMMs that consume the
+        // operands copy them in 16-byte pieces)
+        S24_REQUIRE(s24_aligned(pr.vals, 16) && s24_aligned(pr.valsT, 16) && s24_aligned(pr.meta, 8) && s24_aligned(pr.metaT, 8) &&
+                        s24_aligned(pr.mask, 2) && s24_aligned(pr.mask_out, 2),
+                    S24_ERR_ALIGN);
+        // a given mask is not written back
+        batch.w[used] = MaskWeight{pr.W, pr.ldw, (int)(pr.r / 4), (int)(pr.q / 4), pr.mask, pr.mask ? nullptr : pr.mask_out, nullptr,
+                                   pr.vals, pr.meta, pr.valsT, pr.metaT};
+        S24_REQUIRE((batch.w[used].mask_in == nullptr) == (batch.w[0].mask_in == nullptr), S24_ERR_UNSUPPORTED);
+        ++used;
+    }
+    return used ? launch(batch, used, dt, true, static_cast<hipStream_t>(stream)) : S24_OK;
 }
 
 extern "C" int s24_mask_flips(const uint16_t *mask_new, const uint16_t *mask_old, int64_t nblocks, uint32_t *block_flips,

@@ -115,8 +115,10 @@ class SparseFFN:
         return out
 
     def prune(self, search=True):
-        for w in self.w.values():
-            w.refresh(self._k, search)
+        """Rebuild the compressed operands of all weights in one pass, searching their masks or applying the stored ones."""
+        self._k("mask_compress" if search else "compress", s24.compress_batch,
+                [(w.W, None if search else w.mask, w.vals, w.meta, w.valsT, w.metaT, w.mask if search else None)
+                 for w in self.w.values()])
 
     def _fwd(self, Xw, name, out):
         """out = Xw (M.*W)^T, plus the weight's bias if it has one."""

@@ -471,6 +471,61 @@ def test_gelu_of_every_16_bit_value_in_the_epilogues(s24, dtype, p, q, tile):
     assert bool(seen[value.isfinite() & normal].all())        # the forward met every normal value
 
 
+# ------------------------------------------------------------------ several weights in one mask / compress launch
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+# one tile and part of one; more than a compute unit's worth of the small tile; past it, where the larger ones take over (one weight
+# of whole tiles, one with an edge both ways, one of a single chunk), and past the sixteenfold of that
+@pytest.mark.parametrize("shapes", [[(64, 64), (128, 192)], [(1088, 832), (64, 3072), (832, 1088)], [(4096, 1024), (2112, 3520), (64, 64), (64, 4160)],
+                                    [(8192, 8192), (1088, 64)]])
+def test_several_weights_in_one_compress_pass(s24, dtype, shapes):
+    td = torch_dtype(dtype)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    Ws = [torch.randn((r, 2 * q), generator=g, device="cuda").to(td)[:, :q] if k == 1 else torch.randn((r, q), generator=g, device="cuda").to(td)
+          for k, (r, q) in enumerate(shapes)]                 # the second one is a window of a wider matrix
+
+    def buffers():
+        new = lambda shape, t: torch.full(shape, 3, dtype=t, device="cuda")
+        return [(new((q // 64, r, 32), td), new((q // 64, r, 4), torch.int16), new((r // 64, q, 32), td), new((r // 64, q, 4), torch.int16),
+                 new((r // 4, q // 4), torch.int16)) for r, q in shapes]
+
+    one, all_, given = buffers(), buffers(), buffers()
+    for W, (v, m, vt, mt, mask) in zip(Ws, one):
+        s24.transposable_mask(W, mask)                        # checked against the oracle elsewhere
+        s24.compress(W, mask, v, m, vt, mt)
+    s24.compress_batch([(W, None, *b) for W, b in zip(Ws, all_)])
+    s24.compress_batch([(W, o[4], *b[:4], None) for W, o, b in zip(Ws, one, given)])
+    bits = lambda x: x.view(torch.int32 if x.dtype == torch.float32 else torch.int16)
+    for W, (r, q), a, b, c in zip(Ws, shapes, one, all_, given):
+        assert all(torch.equal(bits(x), bits(y)) for x, y in zip(a, b))
+        assert all(torch.equal(bits(x), bits(y)) for x, y in zip(a[:4], c[:4]))
+        # and the operands hold what the mask keeps, in order: the definition, spelled out
+        keep = torch.stack([(a[4].to(torch.int32) >> t) & 1 for t in range(16)], -1).view(r // 4, q // 4, 4, 4).bool()
+        keep = keep.permute(0, 2, 1, 3).reshape(r, q)
+        for dense, k, v, m in ((W, keep, a[0], a[1]), (W.t(), keep.t(), a[2], a[3])):
+            rows, cols = dense.shape
+            kept = dense.contiguous()[k.contiguous()].view(rows, cols // 64, 32).transpose(0, 1).contiguous()
+            assert torch.equal(bits(v), bits(kept))
+            at = torch.arange(cols, device="cuda").expand(rows, cols)[k.contiguous()].view(rows, cols // 64, 4, 8).to(torch.int64) % 4
+            word = (at << (2 * torch.arange(8, device="cuda"))).sum(-1).transpose(0, 1)
+            assert torch.equal(m.to(torch.int64) & 0xFFFF, word)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("spread", [0, 14])
+def test_search_alone_of_large_weights(s24, dtype, spread):
+    """2070 tiles of 32 x 32 blocks: bf16 scores in integers and queues the blocks that these cannot hold (one in forty, or with
+    a spread of binades nearly all); the masks are those of the fused search, whose scores are fp64."""
+    r, q, td = 5888, 5760, torch_dtype(dtype)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    W = torch.randn((r, q), generator=g, device="cuda") * 2.0 ** (-spread * torch.rand((r, q), generator=g, device="cuda")).floor()
+    W = W.to(td)
+    new = lambda *shape, t=td: torch.empty(shape, dtype=t, device="cuda")
+    alone, fused = new(r // 4, q // 4, t=torch.int16), new(r // 4, q // 4, t=torch.int16)
+    s24.transposable_mask(W, alone)
+    s24.compress(W, None, new(q // 64, r, 32), new(q // 64, r, 4, t=torch.int16), new(r // 64, q, 32), new(r // 64, q, 4, t=torch.int16), mask_out=fused)
+    assert torch.equal(alone, fused)
+
+
 # ------------------------------------------------------------------ weight gradients on the 256 x 128 tile
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 # 144 such tiles in all; whole chunks and remainders; edges ragged along both axes; and 288 small ones, the cheaper up to

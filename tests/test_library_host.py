@@ -67,6 +67,21 @@ def test_mask_argument_errors(lib):
     assert f(P, 1, 0, 8, 8, P, None, None) == OK              # empty: nothing to do
 
 
+def test_compress_batch_argument_errors(lib):
+    from paper_2404_01847_amd.binding import _CompressProblem
+    good = _CompressProblem(P, None, P, P, P, P, None, 64, 64, 64)
+
+    def f(*problems, count=None, dt=1):
+        return lib.s24_compress_batch((_CompressProblem * max(len(problems), 1))(*problems), len(problems) if count is None else count, dt, None)
+
+    changed = lambda **kw: _CompressProblem(*[kw.get(n, getattr(good, n)) for n, _ in _CompressProblem._fields_])
+    assert f(count=0) == OK and lib.s24_compress_batch(None, 1, 1, None) == NULL
+    assert f(good, count=-1) == SHAPE and f(*[good] * 5) == SHAPE and f(good, dt=7) == DTYPE
+    assert f(good, changed(q=72)) == SHAPE and f(good, changed(valsT=None)) == NULL and f(good, changed(vals=P + 8)) == ALIGN
+    assert f(good, changed(mask=P)) == UNSUP                   # searched and given masks do not mix
+    assert f(changed(r=0, W=None), changed(q=0, mask=P)) == OK   # empty weights are skipped
+
+
 def test_compress_argument_errors(lib):
     f = lib.s24_compress
     assert f(P, 1, 64, 64, 64, None, None, P, P, P, None, None) == NULL
