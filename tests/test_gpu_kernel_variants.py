@@ -526,6 +526,31 @@ def test_search_alone_of_large_weights(s24, dtype, spread):
     assert torch.equal(alone, fused)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("spread", [0, 3, 60])
+def test_pruned_gradients_of_any_magnitude(s24, dtype, spread):
+    """Groups whose sums lie on either side of what the short form of the draw takes (2^-100 to 2^100, and zero), subnormals and sums
+    that overflow among them, zeros as ReLU leaves them, elements that the sum absorbs: bit for bit as the oracle."""
+    p, r = 320, 208
+    rng = np.random.default_rng(130 + spread)
+    lo, hi = (-24, 15) if dtype == "f16" else (-149, 127) if dtype == "f32" else (-133, 127)
+    e = np.repeat(rng.integers(lo, hi + 1, (p // 4, r)), 4, axis=0) - rng.integers(0, spread + 1, (p, r))
+    e[:, :8] = np.repeat(np.repeat(rng.integers(-103, -97, (p // 4, 4)), 4, axis=0), 2, axis=1)      # around the limits themselves
+    e[:, 4:8] = -e[:, 4:8]
+    x = np.ldexp(rng.choice([-1.0, 1.0], (p, r)) * (1 + rng.random((p, r)) * (rng.random((p, r)) < 0.8)), np.clip(e, lo, hi))
+    x[rng.random((p, r)) < 0.3] = 0.0
+    x = np.clip(x, -65504.0, 65504.0) if dtype == "f16" else np.clip(x, -3.3e38, 3.3e38)
+    x = x.astype(np.float32)
+    dY = x if dtype == "f32" else x.astype(np.float16) if dtype == "f16" else si.f32_to_bf16_bits(torch.from_numpy(x))
+    vals = torch.zeros((p // 64, r, 32), dtype=torch_dtype(dtype), device="cuda")
+    meta = torch.zeros((p // 64, r, 4), dtype=torch.int16, device="cuda")
+    s24.mvue24(dev_bf16(dY), 41, vals, meta)
+    want_v, want_m = oracle.pack(*oracle.mvue24(dY, 41))
+    assert np.array_equal(host_bits(meta).astype(np.uint16), want_m.astype(np.uint16))
+    word = np.uint32 if dtype == "f32" else np.uint16
+    assert np.array_equal(host_bits(vals).view(word), want_v.view(word))
+
+
 # ------------------------------------------------------------------ weight gradients on the 256 x 128 tile
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 # 144 such tiles in all; whole chunks and remainders; edges ragged along both axes; and 288 small ones, the cheaper up to
