@@ -914,7 +914,7 @@ __global__ __launch_bounds__(128 * WN) void dense_nt_big_kernel(const uint16_t *
 // busy; the copies of chunk kc+3 are dealt out between the matrix instructions rather than issued in one burst.
 namespace dmatn {
 constexpr int THREADS = 256;
-// WTM x WTN: wave tile in units of 32: 4 x 4 -> 256 x 256 workgroup tiles; 4 x 2 and 2 x 2 -> 256 x 128 and
+// WTM x WTN: wave tile in units of 32: 4 x 4 -> 256 x 256 workgroup tiles; 4 x 2, 3 x 2 and 2 x 2 -> 256 x 128, 192 x 128 and
 // 128 x 128 tiles for outputs with too few large tiles to fill the chip.  BT = tokens per ring stage: 32 for the large tile (128 KB
 // of LDS); for the small tile 32 (64 KB, two workgroups per CU) when there are more tiles than CUs, else 64 (a
 // small tile has a quarter of the matrix work per token, so the barrier is paid half as often).
@@ -929,12 +929,17 @@ using big::lds_ptr;
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16 *lds_v4i16;
 
-// 16-byte slot of chunk c of token row t: c ^ tr_swizzle(t)
-__device__ __forceinline__ int tr_swizzle(int row) { return ((row & 3) << 2) ^ ((row >> 2) & 2); }
+// 16-byte slot of chunk c of token row t: c ^ tr_swizzle(t).  Rows of 384 bytes lie half a round of the banks apart, so the lowest bit of
+// the row needs no part in it, and their 24 slots take an exchange within eight only.
+template <int ROWB> __device__ __forceinline__ int tr_swizzle(int row)
+{
+    static_assert(ROWB % 256 == 0 || ROWB % 256 == 128, "rows of whole or half rounds of the banks");
+    return (ROWB % 256 == 0 ? (row & 3) << 2 : (row & 2) << 1) ^ ((row >> 2) & 2);
+}
 template <int ROWB>
 __device__ __forceinline__ int tr_off(int row, int col)
 {
-    return row * ROWB + (((col >> 3) ^ tr_swizzle(row)) << 4) + ((col & 7) << 1);
+    return row * ROWB + (((col >> 3) ^ tr_swizzle<ROWB>(row)) << 4) + ((col & 7) << 1);
 }
 __device__ __forceinline__ v4i16 tr_half(const unsigned char *p) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(p)); }
 __device__ __forceinline__ bf16x8 join(v4i16 lo, v4i16 hi)
@@ -1020,13 +1025,13 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
 #pragma unroll
     for (int j = 0; j < NIA; ++j) {
         constexpr int CPR = ROWA / 16;
-        const int slot = (wave * NIA + j) * 64 + lane, row = min(slot / CPR - 32 * part, T - 1), c = (slot % CPR) ^ tr_swizzle(slot / CPR);
+        const int slot = (wave * NIA + j) * 64 + lane, row = min(slot / CPR - 32 * part, T - 1), c = (slot % CPR) ^ tr_swizzle<ROWA>(slot / CPR);
         voffA[j] = (uint32_t)(row * ldy + m0 + 8 * min(c, lastA)) * 2u;
     }
 #pragma unroll
     for (int j = 0; j < NIX; ++j) {
         constexpr int CPR = ROWX / 16;
-        const int slot = (wave * NIX + j) * 64 + lane, row = min(slot / CPR - 32 * part, T - 1), c = (slot % CPR) ^ tr_swizzle(slot / CPR);
+        const int slot = (wave * NIX + j) * 64 + lane, row = min(slot / CPR - 32 * part, T - 1), c = (slot % CPR) ^ tr_swizzle<ROWX>(slot / CPR);
         voffB[j] = (uint32_t)(row * ldx + n0 + 8 * min(c, lastB)) * 2u;
     }
     auto first_row = [&](int kc) { return max(min(kc * BT + 32 * part, T - 32), 0); };   // of this wave's copies
@@ -1129,12 +1134,13 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     // `cs` / `ns`: numbers of the stages cur / nxt; `which`: the X fragment set of this step.
     auto step = [&](const unsigned char *cur, auto cs, int ks, const unsigned char *nxt, auto ns, int ksn, unsigned char *refill, int copy0, int next_row,
                     auto which) {
-        constexpr int P = decltype(which)::value, RB = 2 * NB / MB, R = RB + 2;   // reads of X beside a row, all reads
-        static_assert(RB * MB == 2 * NB && R <= NB && CPS <= MB, "one read per matrix instruction, one copy per row");
+        constexpr int P = decltype(which)::value;
+        static_assert((2 * NB + MB - 1) / MB + 2 <= NB && CPS <= 2 * MB, "one read per matrix instruction, few copies per row");
         int64_t nextA = 0, nextB = 0;
         v4i16 lo{}, loA{};
 #pragma unroll
         for (int mi = 0; mi < MB; ++mi) {
+            const int x0 = 2 * NB * mi / MB, RB = 2 * NB * (mi + 1) / MB - x0, R = RB + 2;   // reads of X beside this row, all reads
 #pragma unroll
             for (int nj = 0; nj < NB; ++nj) {
                 const int ni = (mi & 1) ? NB - 1 - nj : nj;
@@ -1144,7 +1150,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
                 for (int r = 0; r < R; ++r) {
                     if (r * NB / R != nj) continue;
                     if (r < RB) {
-                        const int i = RB * mi + r;
+                        const int i = x0 + r;
                         if (i % 2 == 0) lo = load_b(nxt, ns, ksn, i / 2, 0);
                         else fb[1 - P][i / 2] = join(lo, load_b(nxt, ns, ksn, i / 2, 1));
                     } else if (mi == 0) {
@@ -1155,7 +1161,11 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
                         else fa[mi - 1] = join(loA, load_a(nxt, ns, ksn, mi - 1, 1));
                     }
                 }
-                if (nj == NB - 1 && mi < CPS) issue(refill, rowsA, rowsB, copy0 + mi);
+                if (nj == NB - 1) {   // copy by copy along the rows; where there are more copies than rows, two beside some
+                    constexpr int ROWS = CPS < MB ? CPS : MB;
+#pragma unroll
+                    for (int c = mi * CPS / ROWS; mi < ROWS && c < (mi + 1) * CPS / ROWS; ++c) issue(refill, rowsA, rowsB, copy0 + c);
+                }
                 if (next_row >= 0 && nj == 1) {   // the address of the next chunk's rows, a product or a sum at a time
                     if (mi == MB - 4) { nextA = (int64_t)next_row * ldy * 2; asm volatile("" : "+s"(nextA)); }
                     if (mi == MB - 3) { nextB = (int64_t)next_row * ldx * 2; asm volatile("" : "+s"(nextB)); }
@@ -1342,7 +1352,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_tn_big_kernel(const uint16_t *_
     const int lastB = (min(N - n0, BN) >> 3) - 1;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int slot = (wave * 4 + j) * 64 + lane, row = slot / CPR, c = (slot % CPR) ^ dmatn::tr_swizzle(row);
+        const int slot = (wave * 4 + j) * 64 + lane, row = slot / CPR, c = (slot % CPR) ^ dmatn::tr_swizzle<16 * CPR>(row);
         ob[j] = ((uint32_t)row * (uint32_t)N + (uint32_t)(n0 + 8 * min(c, lastB))) * 2u;
     }
 #pragma unroll
@@ -1939,8 +1949,8 @@ struct DwProblem {
     int64_t p, q, r;
     float lambda;
 };
-using DwTile = NtTile::Kind;   // 256 x 256, 256 x 128, 128 x 128
-int64_t dw_tiles_m(DwTile t, int64_t r) { return ceil_div(r, t == DwTile::Small ? 128 : 256); }
+enum class DwTile { Large, Medium, Small, Medium192 };   // 256 x 256, 256 x 128, 128 x 128, 192 x 128
+int64_t dw_tiles_m(DwTile t, int64_t r) { return ceil_div(r, t == DwTile::Small ? 128 : t == DwTile::Medium192 ? 192 : 256); }
 int64_t dw_tiles_n(DwTile t, int64_t q) { return ceil_div(q, t == DwTile::Large ? 256 : 128); }
 // The window [m_off, m_off + mm) x [n_off, n_off + nn) of a problem's output, in tiles of `tile`
 dmatn::DwWindow dw_window(const DwProblem &pr, DwTile tile, int64_t m_off, int64_t mm, int64_t n_off, int64_t nn)
@@ -1970,12 +1980,17 @@ dmatn::DwWindow dw_window(const DwProblem &pr, DwTile tile, int64_t m_off, int64
 // gradients) 101 -> 81 us, 8192 x 1024 x 4096 114 -> 100.  The large tile gained most from the 16-wide instruction and is the
 // cheapest from 0.7 of a round on: 5504 tokens x 1408 x 3776 (both) small 118, medium 121, large 112 us; 8000 tokens 165, 167, 154.
 // 0.2 % above the best tile at the mean of 64 other pairs.
+// The tile of 192 x 128, where at most one of them falls to a compute unit, spreads over more of these what the medium tile piles on some: a
+// GPT-2-small layer's gradients are 192 of it against 144.  4096 tokens x 768 x 3072 (both gradients) 47.2 -> 43.5 us, 8192 x 896 x
+// 3136 122 -> 109, 6016 x 832 x 2880 86.7 -> 78.7.  From 100 chunks (3200 tokens) on: below, the gain is of the order of 2 us, and with more than one to a
+// compute unit the other tiles are as good (8192 x 1152 x 3072: 138 against 129).  For several gradients in one grid, as measured; one alone keeps the
+// other three.
 DwTile dw_few_tile(const DwProblem *pr, int count)
 {
     const int64_t cus = s24_cu_count();
-    int64_t tiles[3] = {0, 0, 0}, chunks = 0;
+    int64_t tiles[4] = {0, 0, 0, 0}, chunks = 0;
     for (int i = 0; i < count; ++i) {
-        for (int t = 0; t < 3; ++t) tiles[t] += dw_tiles_m((DwTile)t, pr[i].r) * dw_tiles_n((DwTile)t, pr[i].q);
+        for (int t = 0; t < 4; ++t) tiles[t] += dw_tiles_m((DwTile)t, pr[i].r) * dw_tiles_n((DwTile)t, pr[i].q);
         chunks = std::max(chunks, (pr[i].p + 31) / 32);
     }
     auto rest = [&](DwTile t, int64_t per) { return (double)(tiles[(int)t] % per) / per; };
@@ -1984,6 +1999,8 @@ DwTile dw_few_tile(const DwProblem *pr, int count)
     const double l = 14.6 + chunks * (0.75 * full(DwTile::Large, cus) + (rl > 0 ? 0.43 + 0.22 * rl : 0));
     const double m = 9.7 + chunks * (0.45 * full(DwTile::Medium, cus) + (rm > 0 ? 0.24 + 0.12 * rm : 0));
     const double s = 7.0 + chunks * (0.53 * full(DwTile::Small, 2 * cus) + (rs > 0.5 ? 0.38 : rs > 0 ? 0.18 : 0));
+    const int64_t n192 = tiles[(int)DwTile::Medium192];
+    if (count > 1 && chunks >= 100 && n192 <= cus && 9.0 + chunks * (0.20 + 0.095 * n192 / cus) < std::min(l, std::min(m, s))) return DwTile::Medium192;
     return s <= m && s <= l ? DwTile::Small : m <= l ? DwTile::Medium : DwTile::Large;
 }
 // small tile: 32 tokens per stage when there are more tiles than compute units, else 64
@@ -2003,6 +2020,7 @@ void launch_dw_batch(const dmatn::DwBatch &batch, DwTile tile, bool accum, bool 
     S24_WITH_16BIT_TYPE(dt, {
         if (tile == DwTile::Large) S24_LAUNCH_DW_TILE(4, 4, 32);
         else if (tile == DwTile::Medium) S24_LAUNCH_DW_TILE(4, 2, 32);
+        else if (tile == DwTile::Medium192) S24_LAUNCH_DW_TILE(3, 2, 32);
         else if (slots * 8 > s24_cu_count()) S24_LAUNCH_DW_TILE(2, 2, 32);
         else S24_LAUNCH_DW_TILE(2, 2, 64);
     });

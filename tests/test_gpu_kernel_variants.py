@@ -579,6 +579,29 @@ def test_medium_tile_weight_gradients(s24, dtype, case):
         assert torch.equal(got[i].view(torch.int32), two.view(torch.int32))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+# no more tiles of 192 x 128 than compute units (192 and 248); whole chunks and remainders of one and of 31 tokens; ragged both ways
+@pytest.mark.parametrize("p,d,f,beta", [(3264, 752, 3056, 0.0), (3201, 752, 3056, 1.0), (3231, 960, 3056, 0.0)])
+def test_weight_gradients_on_the_192_row_tile(s24, dtype, p, d, f, beta):
+    td = torch_dtype(dtype)
+    g = torch.Generator(device="cuda").manual_seed(p)
+    rnd = lambda sh, std: (torch.randn(sh, generator=g, device="cuda") * std).to(td)
+    probs = []
+    for r, q in [(d, f), (f, d)]:
+        W, mask = rnd((r, q), 0.02), torch.empty((r // 4, q // 4), dtype=torch.int16, device="cuda")
+        s24.transposable_mask(W, mask)
+        probs.append((rnd((p, r), 1e-2), rnd((p, q), 1.0), torch.full((r, q), 1e-3, device="cuda"), W, mask, 2e-4))
+    assert tiles_run(lambda: s24.dense_dw_batch(probs, beta=beta)) == [(3, 2, 32)]
+    for dY, X, dW, W, mask, lam in probs:
+        alone = torch.full_like(dW, 1e-3)      # other tiles, which are compared with the definition elsewhere: the same bits
+        s24.dense_dw_decay(dY, X, alone, W, mask, lam, beta=beta)
+        assert torch.equal(dW.view(torch.int32), alone.view(torch.int32))
+        ref = dY.double().t() @ X.double() + beta * 1e-3
+        keep = torch.stack([(mask.to(torch.int32) >> t) & 1 for t in range(16)], -1).view(*mask.shape, 4, 4).permute(0, 2, 1, 3).reshape(dW.shape)
+        ref += lam * W.double() * (1 - keep)
+        assert float((dW.double() - ref).norm() / ref.norm()) < 1e-5   # sums of 3200 products in fp32
+
+
 # ------------------------------------------------------------------ dense products on the smaller tiles
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 # the 128 x 128 tile and the 256 x 128 one (136 of them), ragged both ways; 2, 4, 6 and 10 chunks of 32 against a ring of four
