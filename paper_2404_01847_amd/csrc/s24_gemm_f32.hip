@@ -217,7 +217,8 @@ struct TnArgs {
 
 template <int T> struct Run { float v[T]; };
 
-template <bool SPARSE, bool ACCUM, int T, int KS>
+// D: batches of eight token pairs in flight (see s24_f32_tn)
+template <bool SPARSE, bool ACCUM, int T, int KS, int D>
 __global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
 {
     constexpr int TW = 32 * T, PITCH = TW + 4, SLICE = TW * PITCH, THREADS = 64 * KS;
@@ -269,21 +270,56 @@ __global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
         const bool whole = g.T <= kWholeTokens;   // the first slice takes all
         const int p0 = whole ? (ks == 0 ? 0 : pairs) : s24_slice_begin(pairs, ks, KS), p1 = whole ? pairs : s24_slice_begin(pairs, ks + 1, KS);
         const float *a = g.A + mc, *x = g.X + nc;
-        int p = p0;
-        Run<T> av[U], xv[U];
-        for (; p + U <= p1 && p + U <= g.T / 2; p += U) {   // (whole pairs)
+        struct Batch { Run<T> a[U], x[U]; };
+        auto load = [&](Batch &f, int p) {   // the U whole pairs from p on
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int64_t tok = 2 * (p + u) + h;
-                av[u] = *reinterpret_cast<const Run<T> *>(a + tok * M);
-                xv[u] = *reinterpret_cast<const Run<T> *>(x + tok * N);
+                f.a[u] = *reinterpret_cast<const Run<T> *>(a + tok * M);
+                f.x[u] = *reinterpret_cast<const Run<T> *>(x + tok * N);
+            }
+        };
+        auto pair = [&](const Run<T> &av, const Run<T> &xv) {
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int j = 0; j < T; ++j) acc[i][j] = mma(av.v[i], xv.v[j], acc[i][j]);
+        };
+        auto multiply = [&](const Batch &f) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) pair(f.a[u], f.x[u]);
+        };
+        int p = p0;
+        if constexpr (D == 1) {
+            Batch f;
+            for (; p + U <= p1 && p + U <= g.T / 2; p += U) {
+                load(f, p);
+                multiply(f);
+            }
+        } else {
+            const int batches = max(min(p1, g.T / 2) - p0, 0) / U;
+            Batch f[D];
+#pragma unroll
+            for (int d = 0; d < D; ++d)
+                if (d < batches) load(f[d], p0 + U * d);
+            int b = 0;
+            for (; b + 2 * D <= batches; b += D) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    multiply(f[d]);
+                    load(f[d], p0 + U * (b + D + d));
+                }
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int d = 0; d < D; ++d)
+                if (b + d < batches) {
+                    multiply(f[d]);
+                    if (b + D + d < batches) load(f[d], p0 + U * (b + D + d));
+                }
 #pragma unroll
-                for (int i = 0; i < T; ++i)
-#pragma unroll
-                    for (int j = 0; j < T; ++j) acc[i][j] = mma(av[u].v[i], xv[u].v[j], acc[i][j]);
+            for (int d = 0; d < D; ++d)
+                if (b + D + d < batches) multiply(f[d]);
+            p = p0 + U * batches;
         }
         for (; p < p1; ++p) {   // rest of the slice; the token past an odd count contributes zero
             const int tok = 2 * p + h;
@@ -292,10 +328,7 @@ __global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
 #pragma unroll
             for (int i = 0; i < T; ++i)   // both operands: zero times an infinity of the repeated last token would be NaN
                 if (tok >= g.T) av1.v[i] = xv1.v[i] = 0.0f;
-#pragma unroll
-            for (int i = 0; i < T; ++i)
-#pragma unroll
-                for (int j = 0; j < T; ++j) acc[i][j] = mma(av1.v[i], xv1.v[j], acc[i][j]);
+            pair(av1, xv1);
         }
     }
     // park: matrix row r of block i is output row T*r + i, column c of block j output column T*c + j
@@ -373,11 +406,11 @@ template <bool SPARSE, bool ACCUM, int EPI, int ACT> int choose_nt(const S24F32N
     }
 }
 
-template <bool SPARSE, int T, int KS> int launch_tn(TnArgs &a, int64_t tiles, bool accum, hipStream_t st)
+template <bool SPARSE, int T, int KS, int D = 1> int launch_tn(TnArgs &a, int64_t tiles, bool accum, hipStream_t st)
 {
     const dim3 grid((unsigned)tiles), block(64 * KS);
-    if (accum) hipLaunchKernelGGL((f32_tn_kernel<SPARSE, true, T, KS>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((f32_tn_kernel<SPARSE, false, T, KS>), grid, block, 0, st, a);
+    if (accum) hipLaunchKernelGGL((f32_tn_kernel<SPARSE, true, T, KS, D>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((f32_tn_kernel<SPARSE, false, T, KS, D>), grid, block, 0, st, a);
     return s24_launch_status();
 }
 }  // namespace
@@ -395,6 +428,10 @@ int s24_f32_nt(const S24F32Nt &g, hipStream_t st)
 
 // 32-tiles until the 64-tile's own grid is three workgroups per compute unit: 512 tokens, 1024 x 256 out: 8.1 against 15.1 us
 // (58 with one thread per output); 1024 tokens, 3072 x 768: 78 against 84 (1282); 2048 tokens, 4096 x 1024: 248 against 214.
+// Batches in flight: with up to two workgroups of 32-tiles per compute unit a wave's trips to memory are what takes the time, and four
+// batches' registers leave room for both (512 tokens, 1024 x 256: 11.1 -> 7.8 us; 2048, 704 x 256: 34.1 -> 19.0).  Beyond that the waves
+// that those registers would displace hide more (1024, 3072 x 768: 73.7 with one batch, 88.6 with four).  The 64-tile has its two waves per SIMD anyway and
+// takes two (2048, 4096 x 1024: 217 -> 183).
 int s24_f32_tn(const S24F32TnProblem *pr, int count, bool accum, hipStream_t st)
 {
     int64_t tiles[2] = {0, 0};
@@ -418,5 +455,6 @@ int s24_f32_tn(const S24F32TnProblem *pr, int count, bool accum, hipStream_t st)
     }
     if (pr[0].Am != nullptr) return T == 1 ? launch_tn<true, 1, 8>(a, first, accum, st) : launch_tn<true, 2, 8>(a, first, accum, st);
     if (few) return T == 1 ? launch_tn<false, 1, 1>(a, first, accum, st) : launch_tn<false, 2, 1>(a, first, accum, st);
-    return T == 1 ? launch_tn<false, 1, 8>(a, first, accum, st) : launch_tn<false, 2, 8>(a, first, accum, st);
+    if (T == 2) return launch_tn<false, 2, 8, 2>(a, first, accum, st);
+    return first <= 2 * s24_cu_count() ? launch_tn<false, 1, 8, 4>(a, first, accum, st) : launch_tn<false, 1, 8>(a, first, accum, st);
 }

@@ -551,6 +551,21 @@ def test_pruned_gradients_of_any_magnitude(s24, dtype, spread):
     assert np.array_equal(host_bits(vals).view(word), want_v.view(word))
 
 
+# ------------------------------------------------------------------ fp32 weight gradients with several batches in flight
+# 32-tiles with four batches of eight token pairs in flight (192 and 512 tiles), with one (1088 tiles), and 64-tiles with two (768)
+@pytest.mark.parametrize("rq", [(176, 1008), (1024, 512), (1072, 1008), (2048, 1536)])
+# per slice: no batch and a rest, one, three, four (all in flight), five and seven with a rest, eight, and past two rounds of them
+@pytest.mark.parametrize("p", [15, 129, 400, 512, 647, 1031, 1024, 1500])
+def test_f32_weight_gradient_batches(s24, rq, p):
+    (r, q), g = rq, torch.Generator(device="cuda").manual_seed(p)
+    dY, X = (torch.randn((p, n), generator=g, device="cuda") for n in (r, q))
+    dW = torch.full((r, q), 5.0, device="cuda")
+    s24.dense_dw(dY, X, dW)
+    ref = dY.double().t() @ X.double()
+    # eight slices and their sum: an error of sqrt(p) roundings of 2^-24 at most, as a chain of p / 8 has
+    assert float((dW.double() - ref).norm() / ref.norm()) < 2.0 ** -24 * p ** 0.5
+
+
 # ------------------------------------------------------------------ weight gradients on the 256 x 128 tile
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 # 144 such tiles in all; whole chunks and remainders; edges ragged along both axes; and 288 small ones, the cheaper up to
