@@ -582,6 +582,7 @@ struct MaskWeight {
 struct MaskBatch {
     MaskWeight w[kMaxWeights];
     int first_tile[kMaxWeights + 1];
+    int begin;              // first tile of this launch
 };
 
 template <typename T, bool SEARCH, bool COMPRESS, int TBW, int S>
@@ -615,10 +616,11 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const MaskBatch batc
     uint4 table[TAB_PER_LANE ? TAB_PER_LANE : 1];   // requested ahead of the weights: it is in the L2 and there first
 #pragma unroll
     for (int k = 0; k < TAB_PER_LANE; ++k) table[k] = reinterpret_cast<const uint4 *>(&g_tables)[TAB_FIRST + min(tid + 256 * k, TAB - 1)];
+    const int batch_tile = batch.begin + (int)blockIdx.x;
     int which = 0;   // wave-uniform
 #pragma unroll
     for (int i = 1; i < kMaxWeights; ++i)
-        if ((int)blockIdx.x >= batch.first_tile[i]) which = i;
+        if (batch_tile >= batch.first_tile[i]) which = i;
     const MaskWeight &weight = batch.w[which];
     const T *__restrict__ W = static_cast<const T *>(weight.W);
     const int64_t ldw = weight.ldw;
@@ -628,7 +630,7 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const MaskBatch batc
     uint8_t *__restrict__ index_out = weight.index_out;
     T *__restrict__ vals = static_cast<T *>(weight.vals), *__restrict__ valsT = static_cast<T *>(weight.valsT);
     uint16_t *__restrict__ meta = weight.meta, *__restrict__ metaT = weight.metaT;
-    const unsigned tile = blockIdx.x - (unsigned)batch.first_tile[which], tiles_q = (unsigned)(bq + TBW - 1) / TBW;
+    const unsigned tile = (unsigned)(batch_tile - batch.first_tile[which]), tiles_q = (unsigned)(bq + TBW - 1) / TBW;
     const int bj0 = (int)(tile % tiles_q) * TBW, bi0 = (int)(tile / tiles_q) * TBH;
     const int lbj = tid % TBW;
     const int bj = bj0 + lbj;
@@ -898,14 +900,18 @@ template <typename T, bool SEARCH, bool COMPRESS, int TBW, int S>
 int launch_tiles(MaskBatch &batch, int count, hipStream_t st)
 {
     constexpr int TBH = 256 / TBW * S;
+    constexpr int64_t LAUNCH = 1 << 23;   // a launch holds less than 2^32 work items (of more it silently runs the remainder)
     int64_t tiles = 0;
     for (int i = 0; i <= kMaxWeights; ++i) {
         batch.first_tile[i] = (int)tiles;
         if (i < count) tiles += (int64_t)((batch.w[i].bq + TBW - 1) / TBW) * ((batch.w[i].br + TBH - 1) / TBH);
-        S24_REQUIRE(tiles < (1 << 24), S24_ERR_SHAPE);   // a launch holds less than 2^32 work items
+        S24_REQUIRE(tiles <= INT32_MAX - LAUNCH, S24_ERR_SHAPE);   // more weights than any memory holds
     }
-    if (tiles == 0) return S24_OK;
-    hipLaunchKernelGGL((mask_compress_kernel<T, SEARCH, COMPRESS, TBW, S>), dim3((unsigned)tiles), dim3(256), 0, st, batch);
+    for (int64_t begin = 0; begin < tiles; begin += LAUNCH) {
+        batch.begin = (int)begin;
+        hipLaunchKernelGGL((mask_compress_kernel<T, SEARCH, COMPRESS, TBW, S>), dim3((unsigned)std::min(tiles - begin, LAUNCH)), dim3(256), 0, st,
+                           batch);
+    }
     return s24_launch_status();
 }
 // Which tile, by the number of 32 x 32 tiles of all weights together, in compute units (256 of them); measured in us, 32 x 32 / 32 x 16 /

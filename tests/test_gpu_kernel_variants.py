@@ -258,6 +258,29 @@ def test_f32_search_beside_infinities_and_nans(s24, legal_blocks):
     assert np.array_equal(host_bits(alone), want) and np.array_equal(host_bits(fused), want)
 
 
+@pytest.mark.parametrize("dtype,r,q", [("f16", 4, 2 ** 30 + 1028), ("f16", 2 ** 30 + 1028, 4), ("f32", 4, 2 ** 30 + 1028)])
+def test_mask_search_in_more_tiles_than_a_launch_holds(s24, dtype, r, q):
+    """2^24 and some tiles of 16 x 16 blocks: the masks that searches of a part each give."""
+    W = torch.empty((r, q), dtype=torch_dtype(dtype), device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(q))
+    new = lambda: torch.full((r // 4, q // 4), -1, dtype=torch.int16, device="cuda")
+    index = torch.full((r // 4, q // 4), 255, dtype=torch.uint8, device="cuda")
+    whole, parts = new(), new()
+    s24.transposable_mask(W, whole, index)
+    step = 2 ** 28
+    for i in range(0, r, step):
+        for j in range(0, q, step):
+            part = torch.empty((min(step, r - i) // 4, min(step, q - j) // 4), dtype=torch.int16, device="cuda")
+            s24.transposable_mask(W[i:i + step, j:j + step], part)
+            parts[i // 4:(i + step) // 4, j // 4:(j + step) // 4] = part
+    assert torch.equal(whole, parts)
+    assert int(index.max()) == 89
+    rows, cols = min(r, 1028), min(q, 1028)
+    for i, j in ((0, 0), (r - rows, q - cols)):
+        want, ids = oracle.transposable_mask(host_bits(W[i:i + rows, j:j + cols].contiguous()), want_index=True)
+        at = (slice(i // 4, (i + rows) // 4), slice(j // 4, (j + cols) // 4))
+        assert np.array_equal(host_bits(whole[at].contiguous()), want) and np.array_equal(index[at].cpu().numpy(), ids)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
 @pytest.mark.parametrize("kind", ["few", "equal", "zeros", "tiny", "window", "normal"])
 def test_l1_norm_gap_by_classes(s24, dtype, kind):
