@@ -270,15 +270,19 @@ __device__ __forceinline__ void staged_store(const f32x4 (&acc)[2 * MI][4], unsi
 // GELU, or its slope, of bf16 values from a table in LDS.  A bf16 value between 2^-EXP and 16 is one of 128 per octave and sign, so a
 // workgroup computes each of them once (9 to 20 per lane) instead of 128 or 64 tile elements per lane at 26 to 29 issue slots
 // each, two of the instructions on the quarter-rate unit: on a tile of 20 chunks that arithmetic was a third of the time.  An element then
-// costs four packed 16-bit instructions and an LDS read, and has the bits that the function gives it.  Values outside the table
-// (infinities and NaNs among them) send the wave's eight at a time to the function: one in 1e4 normally distributed values of
-// the usual spread.  Not for binary16, whose octaves have 1024 values.  16384 tokens, K = 1280, 5120 features, alternating on one card:
-// forward 158 -> 138 us, backward 174 -> 155 (with ReLU 134 and 139); 4160, 1600, 6400: 65 -> 59 and 70 -> 63; in the 128 x 128 tile, whose
-// lanes have half as many elements to a table, 8192, 768, 3072: 44.5 -> 43 and as before.
+// costs four packed 16-bit instructions and an LDS read, and has the bits that the function gives it.  Zeros (padded tokens) and finite
+// values from 16 on (a feature that is an outlier) send the wave's eight at a time through a longer lookup with the function's limits.
+// Infinities, NaNs and the smallest values send them to the function: one in 1e4 normally distributed values of
+// the usual spread.  Not for binary16, whose octaves have 1024 values.  16384 tokens, K = 1280, 5120 features, alternating on one card,
+// the function alone and now: forward 168 -> 144 us, backward 185 -> 161 (with ReLU, another card, 134 and 139); 4160, 1600, 6400: 69 -> 62 and
+// 74 -> 67; in the 128 x 128 tile, whose lanes have half as many elements to a table, 8192, 768, 3072: 48 -> 44 and 47 -> 45.
+// Every other token zero: 153 -> 144 and 184 -> 169, 64 -> 60 and 73 -> 71, 44 -> 45 and 46 -> 49; one feature in 128 past 16: 173 -> 161 and
+// 184 -> 170, 71 -> 68 and 74 -> 71, 48 -> 48 and 47 -> 47 (with the function for those, 177 and 189, 73 and 78, 52 and 48).
 template <int ACT_MODE, int ACT> struct ActTable {
     typedef std::conditional_t<ACT_MODE == 1, uint16_t, float> entry;   // H as it is stored; the slope is multiplied before it is rounded
     static constexpr int EXP = ACT_MODE == 1 ? 16 : 14, FIRST = (127 - EXP) << 7, COUNT = (EXP + 4) << 7;   // of either sign
     static constexpr int BYTES = 2 * COUNT * (int)sizeof(entry);
+    typedef std::conditional_t<ACT_MODE == 1, uint32_t, float2> pair;   // of two neighbours
     typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
     static __device__ __forceinline__ entry value(float z)
@@ -296,22 +300,51 @@ template <int ACT_MODE, int ACT> struct ActTable {
             tab[COUNT + i] = value(-z);
         }
     }
-    // of the eight values in z
-    static __device__ __forceinline__ void lookup(const entry *tab, const uint32_t (&z)[4], entry (&out)[8])
+    static __device__ __forceinline__ pair join(entry lo, entry hi)
     {
+        if constexpr (ACT_MODE == 1) return lo | ((uint32_t)hi << 16);
+        else return make_float2(lo, hi);
+    }
+    // of the eight values in z
+    static __device__ __forceinline__ void lookup(const entry *tab, const uint32_t (&z)[4], pair (&out)[4])
+    {
+        constexpr unsigned short ABS = 0x7FFF, INF = 0x7F80, N = COUNT;
         u16x2 at[4], far = {0, 0};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const u16x2 b = __builtin_bit_cast(u16x2, z[k]), from_first = (b & (unsigned short)0x7FFF) - (unsigned short)FIRST;
+            const u16x2 b = __builtin_bit_cast(u16x2, z[k]), from_first = (b & ABS) - (unsigned short)FIRST;
             far = __builtin_elementwise_max(far, from_first);
-            at[k] = (b >> (unsigned short)15) * (unsigned short)COUNT + from_first;
+            at[k] = (b >> (unsigned short)15) * N + from_first;
         }
-        if (__any(far.x >= COUNT || far.y >= COUNT)) {
+        if (!__any(far.x >= COUNT || far.y >= COUNT)) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) out[2 * k] = value(s24_num<uint16_t>::lo(z[k])), out[2 * k + 1] = value(s24_num<uint16_t>::hi(z[k]));
-        } else {
+            for (int k = 0; k < 4; ++k) out[k] = join(tab[at[k].x], tab[at[k].y]);
+            return;
+        }
+        u16x2 most = {0, 0}, least = {0xFFFF, 0xFFFF};   // of the magnitudes, and of those that are not zero, less one
 #pragma unroll
-            for (int k = 0; k < 4; ++k) out[2 * k] = tab[at[k].x], out[2 * k + 1] = tab[at[k].y];
+        for (int k = 0; k < 4; ++k) {
+            const u16x2 mag = __builtin_bit_cast(u16x2, z[k]) & ABS;
+            most = __builtin_elementwise_max(most, mag);
+            least = __builtin_elementwise_min(least, mag - (unsigned short)1);
+        }
+        if (__any(most.x >= INF || most.y >= INF || least.x < FIRST - 1 || least.y < FIRST - 1)) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) out[k] = join(value(s24_num<uint16_t>::lo(z[k])), value(s24_num<uint16_t>::hi(z[k])));
+            return;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {   // from 16 on the entry of the largest value below it, which is the limit of either sign but of H itself
+            const u16x2 b = __builtin_bit_cast(u16x2, z[k]), from_first = (b & ABS) - (unsigned short)FIRST, last = {N - 1, N - 1};
+            const u16x2 a = (b >> (unsigned short)15) * N + __builtin_elementwise_min(from_first, last);
+            const entry lo = tab[a.x], hi = tab[a.y];
+            if constexpr (ACT_MODE == 1) {   // beyond the table H is z where that is positive or zero, and else minus zero
+                const u16x2 past = __builtin_elementwise_min(__builtin_elementwise_sub_sat(from_first, last), (u16x2){1, 1}) * (unsigned short)0xFFFF;
+                const uint32_t mask = __builtin_bit_cast(uint32_t, past), h = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(b, (u16x2){0x8000, 0x8000}));
+                out[k] = (h & mask) | (join(lo, hi) & ~mask);
+            } else {
+                out[k] = make_float2((z[k] & 0x7FFFu) == 0 ? value(0.0f) : lo, (z[k] & 0x7FFF0000u) == 0 ? value(0.0f) : hi);
+            }
         }
     }
 };
@@ -650,17 +683,15 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
             const uint4 dh = staged_chunk<MI>(est, nl, c);
             const uint32_t dw[4] = {dh.x, dh.y, dh.z, dh.w}, zw[4] = {z[j].x, z[j].y, z[j].z, z[j].w};
             uint32_t o[4];
-            float slope[8];
+            float2 slope[4];
             if constexpr (TABLE) {
                 Table::lookup(table, zw, slope);
             } else {
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    slope[2 * k] = s24_act_slope<ACT>(s24_num<T>::lo(zw[k])), slope[2 * k + 1] = s24_act_slope<ACT>(s24_num<T>::hi(zw[k]));
+                for (int k = 0; k < 4; ++k) slope[k] = make_float2(s24_act_slope<ACT>(s24_num<T>::lo(zw[k])), s24_act_slope<ACT>(s24_num<T>::hi(zw[k])));
             }
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                o[k] = s24_num<T>::pack2(s24_num<T>::lo(dw[k]) * slope[2 * k], s24_num<T>::hi(dw[k]) * slope[2 * k + 1]);
+            for (int k = 0; k < 4; ++k) o[k] = s24_num<T>::pack2(s24_num<T>::lo(dw[k]) * slope[k].x, s24_num<T>::hi(dw[k]) * slope[k].y);
             if (n < N && m_base + 8 * c < M)   // M is a multiple of 16: a chunk is all in or all out
                 *reinterpret_cast<uint4 *>(Out + (int64_t)n * M + m) = make_uint4(o[0], o[1], o[2], o[3]);
         }
@@ -685,10 +716,7 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
             const uint32_t zw[4] = {zc.x, zc.y, zc.z, zc.w};
             uint32_t h[4];
             if constexpr (TABLE) {
-                uint16_t v[8];
-                Table::lookup(table, zw, v);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) h[k] = v[2 * k] | ((uint32_t)v[2 * k + 1] << 16);
+                Table::lookup(table, zw, h);
             } else {
 #pragma unroll
                 for (int k = 0; k < 4; ++k)

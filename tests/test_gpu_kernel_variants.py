@@ -494,6 +494,41 @@ def test_gelu_of_every_16_bit_value_in_the_epilogues(s24, dtype, p, q, tile):
     assert bool(seen[value.isfinite() & normal].all())        # the forward met every normal value
 
 
+@pytest.mark.parametrize("p,q,tile", [(8136, 64, (2, 2)), (8136, 2112, (4, 2)), (16390, 2112, (4, 4))])
+def test_gelu_of_zeros_and_large_values_in_the_epilogues(s24, p, q, tile):
+    """Zeros and every finite bf16 value from 16 on, of both signs, among values between: the bits of the activation kernels."""
+    r = 1024
+    new = lambda: torch.empty((p, r), dtype=torch.bfloat16, device="cuda")
+    bits = lambda x: x.view(torch.int16)
+    W = torch.zeros((r, q), dtype=torch.bfloat16, device="cuda")
+    W[torch.arange(r), torch.arange(r) % 4] = 1.0             # Z[n][m] = X[n][m % 4]
+    v, vt = (torch.empty((a // 64, b, 32), dtype=torch.bfloat16, device="cuda") for a, b in ((q, r), (r, q)))
+    m, mt = (torch.empty((a // 64, b, 4), dtype=torch.int16, device="cuda") for a, b in ((q, r), (r, q)))
+    s24.compress(W, None, v, m, vt, mt)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    dY = torch.randn((p, q), generator=g, device="cuda").bfloat16()
+    n = torch.arange(4 * p, device="cuda")
+    pick, sign = torch.randint(0, 3, n.shape, generator=g, device="cuda"), n % 2 * 0x8000
+    large = 0x4180 + n // 2 % 0x3E00                          # 16 ... the largest finite value
+    between = torch.randint(0x3880, 0x4180, n.shape, generator=g, device="cuda")    # 2^-14 ... 16
+    every = torch.where(pick == 0, large, torch.where(pick == 1, between, 0)) + sign
+    every[:2 * 0x3E00] = (large + sign)[:2 * 0x3E00]
+    every[-4 * 512:] = (n % 2 * 0x8000)[-4 * 512:]            # and whole tiles of zeros
+    val = every.to(torch.int16).view(torch.bfloat16).view(p, 4)
+    X = torch.zeros((p, q), dtype=torch.bfloat16, device="cuda")
+    X[:, :4] = val
+    Z, H, dH, dZ, two = new(), new(), new(), new(), new()
+    assert tiles_run(lambda: s24.spmm_fwd_act(X, v, m, None, Z, H, s24.ACT_GELU_ERF)) == [tile]
+    assert torch.equal(Z, val.repeat(1, r // 4))
+    s24.act_fwd(Z, two, s24.ACT_GELU_ERF)
+    assert torch.equal(bits(H), bits(two))
+    Z = val.repeat(1, r // 4).contiguous()                    # with the zeros' signs
+    assert tiles_run(lambda: s24.spmm_bwd_dx_act(dY, v, m, Z, dZ, s24.ACT_GELU_ERF)) == [tile]
+    s24.spmm_bwd_dx(dY, v, m, dH)
+    s24.act_bwd(dH, Z, two, s24.ACT_GELU_ERF)
+    assert torch.equal(bits(dZ), bits(two))
+
+
 # ------------------------------------------------------------------ several weights in one mask / compress launch
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
 # one tile and part of one; more than a compute unit's worth of the small tile; past it, where the larger ones take over (one weight
