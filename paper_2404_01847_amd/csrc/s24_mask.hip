@@ -320,14 +320,29 @@ __device__ __forceinline__ unsigned wave_mid_best_pattern(const uint32_t (&mag)[
     return (unsigned)g_patterns.mask[id] | (id << 16);
 }
 
-// ---------------------------------------------------------------------------
-// Fast path.  mag[4*i+j] = |w_ij| as fp32 bit patterns.  Returns mask | id<<16.  COOPERATIVE: all 64
-// lanes of the wave call it together.
-// WINDOW = binades below the block maximum within which every element is a
-// multiple of 2048*eps (29 for bf16 data, 13 for fp32 data).
-// ---------------------------------------------------------------------------
-template <int WINDOW, int WIDE, bool COOPERATIVE>
-__device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], const uint16_t *lut_mask, const uint8_t *lut_id)
+// The blocks of the lanes that set `mid` or `slow`, one after the other by the whole wave.  All 64 lanes must be active; a lane that
+// set neither gets 0.
+__device__ __forceinline__ unsigned wave_wide_blocks(const uint32_t (&mag)[16], bool mid, bool slow)
+{
+    unsigned rare = 0;
+    for (unsigned long long todo = __ballot(mid); todo != 0; todo &= todo - 1) {
+        const int src = (int)__builtin_ctzll(todo);
+        const unsigned res = wave_mid_best_pattern(mag, src);
+        if ((int)(threadIdx.x & 63) == src) rare = res;
+    }
+    for (unsigned long long todo = __ballot(slow); todo != 0; todo &= todo - 1) {
+        const int src = (int)__builtin_ctzll(todo);
+        Mag16 m16;
+#pragma unroll
+        for (int t = 0; t < 16; ++t) m16.v[t] = (uint32_t)__builtin_amdgcn_readlane((int)mag[t], src);
+        const unsigned res = wave_slow_best_pattern(m16);
+        if ((int)(threadIdx.x & 63) == src) rare = res;
+    }
+    return rare;
+}
+
+// Exponents of the block's largest and of its smallest magnitude other than zero (255 if there is none)
+__device__ __forceinline__ void exponents(const uint32_t (&mag)[16], uint32_t &emax, uint32_t &emin)
 {
     uint32_t mx = 0, mn = 0xFFFFFFFFu;
 #pragma unroll
@@ -335,26 +350,28 @@ __device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], cons
         mx = max(mx, mag[t]);
         mn = min(mn, mag[t] - 1u);  // zero wraps to the top and never wins
     }
-    const uint32_t emax = max(mx >> 23, 1u);
-    const uint32_t emin = (mn == 0xFFFFFFFFu) ? 255u : max(mn >> 23, 1u);
+    emax = max(mx >> 23, 1u);
+    emin = (mn == 0xFFFFFFFFu) ? 255u : max(mn >> 23, 1u);
+}
+
+// ---------------------------------------------------------------------------
+// Fast path.  mag[4*i+j] = |w_ij| as fp32 bit patterns.  Returns mask | id<<16.
+// WINDOW = binades below the block maximum within which every element is a
+// multiple of 2048*eps (29 for bf16 data, 13 for fp32 data).  What becomes of wider blocks: each lane walks through its own; the
+// wave takes them together (all 64 lanes must call); or they are left to the caller, as kHardBlock.
+// ---------------------------------------------------------------------------
+constexpr unsigned kHardBlock = 0xFFFFFFFFu;
+enum class Wide { Lane, Wave, Left };
+template <int WINDOW, int WIDE, Wide HOW>
+__device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], const uint16_t *lut_mask, const uint8_t *lut_id)
+{
+    uint32_t emax, emin;
+    exponents(mag, emax, emin);
     const bool wide = emin + WINDOW < emax;
-    unsigned rare = 0;
-    if constexpr (COOPERATIVE) {
-        const bool very_wide = emin + WIDE < emax;
-        for (unsigned long long todo = __ballot(wide && !very_wide); todo != 0; todo &= todo - 1) {
-            const int src = (int)__builtin_ctzll(todo);
-            const unsigned res = wave_mid_best_pattern(mag, src);
-            if ((int)(threadIdx.x & 63) == src) rare = res;
-        }
-        for (unsigned long long todo = __ballot(very_wide); todo != 0; todo &= todo - 1) {
-            const int src = (int)__builtin_ctzll(todo);
-            Mag16 m16;
-#pragma unroll
-            for (int t = 0; t < 16; ++t) m16.v[t] = (uint32_t)__builtin_amdgcn_readlane((int)mag[t], src);
-            const unsigned res = wave_slow_best_pattern(m16);
-            if ((int)(threadIdx.x & 63) == src) rare = res;
-        }
-    } else if (wide) {
+    unsigned rare = kHardBlock;
+    if constexpr (HOW == Wide::Wave) {
+        rare = wave_wide_blocks(mag, wide && emin + WIDE >= emax, emin + WIDE < emax);
+    } else if (HOW == Wide::Lane && wide) {
         Mag16 m16;
 #pragma unroll
         for (int t = 0; t < 16; ++t) m16.v[t] = mag[t];
@@ -419,7 +436,7 @@ __device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], cons
         }
     const unsigned bonus = (unsigned)__double2loint(best + big) & 0x7FFu;
     const unsigned x = min(bonus - (unsigned)kBonusBase, kLutEntries - 1u);   // (a wide block's index is clamped and unused)
-    return COOPERATIVE && wide ? rare : (unsigned)lut_mask[x] | ((unsigned)lut_id[x] << 16);
+    return HOW != Wide::Lane && wide ? rare : (unsigned)lut_mask[x] | ((unsigned)lut_id[x] << 16);
 }
 
 // ---------------------------------------------------------------------------
@@ -431,8 +448,6 @@ __device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], cons
 // conversion to an integer are exact.  Returns kHardBlock for a block that does not fit (an element more than ten
 // binades down, a zero or subnormal element, a block maximum below 2^-99): those take the fp64 path above.
 // ---------------------------------------------------------------------------
-constexpr unsigned kHardBlock = 0xFFFFFFFFu;
-
 __device__ __forceinline__ unsigned int_best_pattern(const uint32_t (&mag)[16], const uint16_t *lut_mask, const uint8_t *lut_id)
 {
     uint32_t mx = mag[0], mn = mag[0];
@@ -599,6 +614,7 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const MaskBatch batc
     // (5120 x 1280: 8.8 -> 6.7 us).  (In the fused search + compress kernel the four blocks' rows held in registers across the queue cost
     // more than the cheaper scoring saves: measured 4-8 % slower, so it keeps the fp64 scoring too.)
     constexpr bool DEFER = SEARCH && !COMPRESS && sizeof(T) == 2 && RowOps<T>::kWindow == 29 && S == 4;
+    constexpr bool BF16_SMALL = SEARCH && !COMPRESS && sizeof(T) == 2 && RowOps<T>::kWindow == 29 && S == 1;
     __shared__ int s_nhard;
     __shared__ uint16_t s_hard[DEFER ? 256 * S : 1];
     __shared__ uint32_t s_fix[DEFER ? 256 * S : 1];
@@ -811,7 +827,7 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const MaskBatch batc
             fetch(rows, p, true);
             uint32_t mag[16];
             magnitudes(rows, mag);
-            s_fix[code] = best_pattern<Ops::kWindow, Ops::kWide, false>(mag, s_lut_mask, s_lut_id);
+            s_fix[code] = best_pattern<Ops::kWindow, Ops::kWide, Wide::Lane>(mag, s_lut_mask, s_lut_id);
         }
         __syncthreads();
 #pragma unroll
@@ -828,6 +844,26 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const MaskBatch batc
             const bool ok = (bi < br) && (bj < bq);
             fetch(nxt, wrow, ok);
             if constexpr (!SEARCH) m_nxt = ok ? *mrow : 0x33CCu;
+        };
+        // Of the blocks that the fast path left, few to a wave are scored by the wave together and many by a lane each: in fp64 either costs
+        // as much at about 28, in fixed point (400 us, 29 a block) at 14.  From memory once more, so that the common path keeps no register for it (bf16 search, one block in a
+        // hundred 40 binades wide: 3072 x 768 1010 us with each lane's walk in the loop, 698 with the integer path's queue, 84 so; 5120 x 1280 1496, 609
+        // and 93; without such blocks 6.1, 8.1 and 6.1).
+        auto wide_blocks = [&](const T *p, bool ok, unsigned res) {
+            const bool left = res == kHardBlock;
+            Row again[4];
+            fetch(again, p, ok);
+            Mag16 mag;
+            magnitudes(again, mag.v);
+            uint32_t emax, emin;
+            exponents(mag.v, emax, emin);
+            const bool slow = left && emin + Ops::kWide < emax, mid = left && !slow;
+            const bool mid_alone = __popcll(__ballot(mid)) > 28, slow_alone = __popcll(__ballot(slow)) > 14;
+            const unsigned rare = wave_wide_blocks(mag.v, mid && !mid_alone, slow && !slow_alone);
+            if (left) res = rare;
+            if (mid && mid_alone) res = mid_best_pattern(mag);
+            if (slow && slow_alone) res = slow_best_pattern(mag);
+            return res;
         };
         request(bi0 + tid / TBW);
         stage_tables();
@@ -846,7 +882,10 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const MaskBatch batc
             if constexpr (SEARCH) {
                 uint32_t mag[16];
                 magnitudes(rows, mag);
-                const unsigned res = best_pattern<Ops::kWindow, Ops::kWide, sizeof(T) == 4>(mag, s_lut_mask, s_lut_id);
+                unsigned res = best_pattern<Ops::kWindow, Ops::kWide, sizeof(T) == 4 ? Wide::Wave : BF16_SMALL ? Wide::Left : Wide::Lane>(mag, s_lut_mask, s_lut_id);
+                if constexpr (BF16_SMALL) {
+                    if (__any(res == kHardBlock)) res = wide_blocks(wrow, (bi < br) && (bj < bq), res);
+                }
                 m = res & 0xFFFFu;
                 id = res >> 16;
             }

@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import s24_inputs as si
-from util import F32_TOL, assert_close, dev, dev_bf16, host_bits, host_f64, tiles_run, tol_for, torch_dtype
+from util import F32_TOL, assert_close, dev, dev_bf16, host_bits, host_f64, mask_tiles_run, tiles_run, tol_for, torch_dtype
 
 pytestmark = pytest.mark.gpu
 
@@ -241,6 +241,25 @@ def test_wide_blocks_in_both_tile_shapes(s24, dtype, kind, rq):
     alone, fused, _, _ = _search_and_compress(s24, W)
     mask = oracle.transposable_mask(W)
     assert np.array_equal(host_bits(alone), mask) and np.array_equal(host_bits(fused), mask)
+
+
+# 35 binades: fp64 sums; 60: fixed point.  Few or many of a wave's 64 blocks, all of them among them
+@pytest.mark.parametrize("spread", [(35, 35), (60, 60), (35, 60)])
+@pytest.mark.parametrize("share", [0.01, 0.2, 0.45, 0.95, 1.0])
+def test_bf16_search_of_some_wide_blocks(s24, spread, share):
+    """The small tile: wide blocks leave the common path and are scored by the wave together or by a lane each."""
+    r, q = 208, 336
+    rng = np.random.default_rng(63)
+    scale = np.ones((r // 4, q // 4, 16))
+    wide, at = rng.random((r // 4, q // 4)) < share, rng.integers(0, 16, (r // 4, q // 4))
+    i, j = np.nonzero(wide)
+    scale[i, j, at[i, j]] = 2.0 ** -np.where(rng.random(i.size) < 0.5, *spread)
+    W = rng.standard_normal((r, q)) * 0.02 * scale.reshape(r // 4, q // 4, 4, 4).transpose(0, 2, 1, 3).reshape(r, q)
+    W = si.f32_to_bf16_bits(torch.from_numpy(W.astype(np.float32)))
+    mask, index = torch.zeros((r // 4, q // 4), dtype=torch.int16, device="cuda"), torch.zeros((r // 4, q // 4), dtype=torch.uint8, device="cuda")
+    assert mask_tiles_run(lambda: s24.transposable_mask(dev_bf16(W), mask, index)) == [(16, 16)]
+    want, ids = oracle.transposable_mask(W, want_index=True)
+    assert np.array_equal(host_bits(mask), want) and np.array_equal(index.cpu().numpy(), ids)
 
 
 def test_f32_search_beside_infinities_and_nans(s24, legal_blocks):

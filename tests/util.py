@@ -114,18 +114,29 @@ def absorbed_margin_blocks(legal, dtype: str, big_exp: int, every: int = 7):
     return W, want
 
 
-def tiles_run(call):
-    """The tiles of the 16-bit GEMM kernels that `call` launches, in order, by the last template arguments of their names:
-    (4, 4) is 256 x 256, (4, 2) 256 (features) x 128 (tokens), (2, 2) 128 x 128; dense weight gradients add the tokens
-    of a stage, the sliced kernel gives ()."""
+def _kernels_run(call):
+    """Names of the kernels that `call` launches, in order; binary16 instances, which come under their mangled names, with their
+    arguments spelled out likewise."""
     from torch.profiler import ProfilerActivity, profile
     torch.cuda.synchronize()
     with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as prof:
         call()
         torch.cuda.synchronize()
+    return [re.sub(r"Li(\d+)E", r"\1, ", e.name) for e in sorted(prof.events(), key=lambda e: e.time_range.start)]
+
+
+def mask_tiles_run(call):
+    """The tiles of the mask search and compress kernel that `call` launches, in order: blocks across and down."""
+    found = [re.search(r"mask_compress_kernel.*?(\d+), (\d+)(?:>\(|, EEv)", name) for name in _kernels_run(call)]
+    return [(int(m[1]), 256 // int(m[1]) * int(m[2])) for m in found if m]
+
+
+def tiles_run(call):
+    """The tiles of the 16-bit GEMM kernels that `call` launches, in order, by the last template arguments of their names:
+    (4, 4) is 256 x 256, (4, 2) 256 (features) x 128 (tokens), (2, 2) 128 x 128; dense weight gradients add the tokens
+    of a stage, the sliced kernel gives ()."""
     tiles = []
-    for event in sorted(prof.events(), key=lambda e: e.time_range.start):
-        name = re.sub(r"Li(\d+)E", r"\1, ", event.name)   # binary16 instances come under their mangled names
+    for name in _kernels_run(call):
         if m := re.search(r"dense_tn_dma_kernel.*Cfg(?:<|I)(\d+), (\d+), (\d+)", name):
             tiles.append(tuple(map(int, m.groups())))
         elif m := re.search(r"(?:spmm_nt_big|dense_nt_big|spmm_tn_big)_kernel.*?(\d+), (\d+)(?:>\(|, EEv)", name):
