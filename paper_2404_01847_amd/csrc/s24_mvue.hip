@@ -167,6 +167,9 @@ __global__ __launch_bounds__(kThreads) void mvue24_kernel(const T *__restrict__ 
         Kept k;
         general |= mvue_group(a, draw(g), k) ? 0u : 1u << g;
         out[g] = pack(k);
+        // formed here: put off to the stores, a group's fp32 values are four registers instead of two, and three waves per SIMD are left of
+        // five (16384 x 4096: 118 us against 103; 4160 x 6400: 43 against 35)
+        if constexpr (sizeof(T) == 4) asm("" : "+v"(out[g].x), "+v"(out[g].y));
         words[g >> 3] |= (uint32_t)(k.i0 | (k.i1 << 2)) << (4 * (g & 7));
     }
     if (f >= r) return;
