@@ -428,13 +428,16 @@ int s24_f32_nt(const S24F32Nt &g, hipStream_t st)
 
 // 32-tiles until the 64-tile's own grid is three workgroups per compute unit: 512 tokens, 1024 x 256 out: 8.1 against 15.1 us
 // (58 with one thread per output); 1024 tokens, 3072 x 768: 78 against 84 (1282); 2048 tokens, 4096 x 1024: 248 against 214.
-// Batches in flight: with up to two workgroups of 32-tiles per compute unit a wave's trips to memory are what takes the time, and four
-// batches' registers leave room for both (512 tokens, 1024 x 256: 11.1 -> 7.8 us; 2048, 704 x 256: 34.1 -> 19.0).  Beyond that the waves
-// that those registers would displace hide more (1024, 3072 x 768: 73.7 with one batch, 88.6 with four).  The 64-tile has its two waves per SIMD anyway and
-// takes two (2048, 4096 x 1024: 217 -> 183).
+// Batches in flight (one, two, four; us): below 128 tokens a slice has none of a whole batch and the code for more only costs (64 tokens, 1024 x
+// 256: 3.72, 3.83, 3.91).  With up to one workgroup of 32-tiles per compute unit a wave's trips to memory are what takes the time:
+// four (512, 1024 x 256: 7.43, 6.84, 6.65; 2048: 35.0, 17.7, 19.1).  Up to two, four batches' registers still leave room for both, and up to 512 tokens
+// they are the fastest (512, 896 x 512: 11.1, 11.4, 10.7); past that the waves' turns are what takes the time while the operands stay in an XCD's 4 MB of L2
+// (1000, 768 x 512: 18.7, 19.6, 20.7), and two are the fastest once they do not (1200: 25.6, 22.3, 25.2; 2048: 43.3, 32.1, 36.9).  Beyond
+// two workgroups the waves that more registers would displace hide more (1000, 1024 x 1024: 32.3, 37.5, 40.8).  The 64-tile has its two
+// waves per SIMD anyway and takes two (64, 4096 x 1024: 16.9, 17.1; 512: 67.1, 52.6).
 int s24_f32_tn(const S24F32TnProblem *pr, int count, bool accum, hipStream_t st)
 {
-    int64_t tiles[2] = {0, 0};
+    int64_t tiles[2] = {0, 0}, tokens = 0, bytes = 0;   // tokens: of the longest problem; bytes: of all operands
     TnArgs a{};
     for (int T = 1; T <= 2; ++T)
         for (int i = 0; i < count; ++i) tiles[T - 1] += ceil_div(pr[i].M, 32 * T) * ceil_div(pr[i].N, 32 * T);
@@ -445,6 +448,8 @@ int s24_f32_tn(const S24F32TnProblem *pr, int count, bool accum, hipStream_t st)
     for (int i = 0; i < kMaxTn; ++i) {
         if (i < count) {
             few = few && pr[i].T <= kWholeTokens;
+            tokens = std::max(tokens, pr[i].T);
+            bytes += pr[i].T * (pr[i].M + pr[i].N) * (int64_t)sizeof(float);
             const int64_t tm = ceil_div(pr[i].M, 32 * T);
             a.w[i] = TnWindow{pr[i].A, pr[i].X, pr[i].Wt, pr[i].Am, pr[i].mask, pr[i].dW, (int)pr[i].T, (int)pr[i].M, (int)pr[i].N, (int)tm, (int)first, pr[i].lambda};
             first += tm * ceil_div(pr[i].N, 32 * T);
@@ -455,6 +460,9 @@ int s24_f32_tn(const S24F32TnProblem *pr, int count, bool accum, hipStream_t st)
     }
     if (pr[0].Am != nullptr) return T == 1 ? launch_tn<true, 1, 8>(a, first, accum, st) : launch_tn<true, 2, 8>(a, first, accum, st);
     if (few) return T == 1 ? launch_tn<false, 1, 1>(a, first, accum, st) : launch_tn<false, 2, 1>(a, first, accum, st);
-    if (T == 2) return launch_tn<false, 2, 8, 2>(a, first, accum, st);
-    return first <= 2 * s24_cu_count() ? launch_tn<false, 1, 8, 4>(a, first, accum, st) : launch_tn<false, 1, 8>(a, first, accum, st);
+    const int64_t cus = s24_cu_count();
+    if (T == 2) return tokens < 128 ? launch_tn<false, 2, 8>(a, first, accum, st) : launch_tn<false, 2, 8, 2>(a, first, accum, st);
+    if (tokens < 128 || first > 2 * cus) return launch_tn<false, 1, 8>(a, first, accum, st);
+    if (first <= cus || tokens <= 512) return launch_tn<false, 1, 8, 4>(a, first, accum, st);
+    return bytes < 11 << 19 ? launch_tn<false, 1, 8>(a, first, accum, st) : launch_tn<false, 1, 8, 2>(a, first, accum, st);
 }

@@ -629,10 +629,11 @@ def test_pruned_gradients_of_any_magnitude(s24, dtype, spread):
 
 
 # ------------------------------------------------------------------ fp32 weight gradients with several batches in flight
-# 32-tiles with four batches of eight token pairs in flight (192 and 512 tiles), with one (1088 tiles), and 64-tiles with two (768)
+# 32-tiles in at most a workgroup per compute unit (192 of them), in one to two (512) and in more (1088), and 64-tiles (768): one, two or four
+# batches of eight token pairs in flight
 @pytest.mark.parametrize("rq", [(176, 1008), (1024, 512), (1072, 1008), (2048, 1536)])
-# per slice: no batch and a rest, one, three, four (all in flight), five and seven with a rest, eight, and past two rounds of them
-@pytest.mark.parametrize("p", [15, 129, 400, 512, 647, 1031, 1024, 1500])
+# per slice: no batch and a rest, one, three, four, five and seven with a rest, eight, nine, ten and eleven with a rest
+@pytest.mark.parametrize("p", [15, 127, 128, 129, 400, 512, 513, 647, 1031, 1024, 1216, 1290, 1500])
 def test_f32_weight_gradient_batches(s24, rq, p):
     (r, q), g = rq, torch.Generator(device="cuda").manual_seed(p)
     dY, X = (torch.randn((p, n), generator=g, device="cuda") for n in (r, q))
