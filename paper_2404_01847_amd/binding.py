@@ -171,6 +171,8 @@ class _CompressProblem(C.Structure):
 def compress_batch(weights):
     """weights: up to four tuples (W, mask, vals, meta, valsT, metaT, mask_out) of one dtype, mask None in all of them (searched) or
     in none; compress of each in one pass."""
+    if not weights:
+        return
     arr = (_CompressProblem * len(weights))()
     for k, (W, mask, vals, meta, valsT, metaT, mask_out) in enumerate(weights):
         _rows("s24_compress_batch", "W", W)

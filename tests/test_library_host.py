@@ -80,6 +80,8 @@ def test_compress_batch_argument_errors(lib):
     assert f(good, changed(q=72)) == SHAPE and f(good, changed(valsT=None)) == NULL and f(good, changed(vals=P + 8)) == ALIGN
     assert f(good, changed(mask=P)) == UNSUP                   # searched and given masks do not mix
     assert f(changed(r=0, W=None), changed(q=0, mask=P)) == OK   # empty weights are skipped
+    import paper_2404_01847_amd as s24
+    assert s24.compress_batch([]) is None                      # no weights: nothing to do, as in the C call
 
 
 def test_compress_argument_errors(lib):
