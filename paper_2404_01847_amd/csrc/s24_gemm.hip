@@ -1155,7 +1155,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     // One step: rows of NB matrix instructions.  A wave is alone on its SIMD and issues an instruction every four cycles, a
     // matrix instruction lasts sixteen: whatever else goes out between two of them beyond three instructions leaves the matrix
     // unit idle (a wait state before each cost 6 % of the kernel).  So the rest is dealt out evenly: beside row mi the
-    // LDS reads of one dY fragment and of NB / MB X fragments, one read per matrix instruction, one copy, and a part of
+    // LDS reads of one dY fragment and its share of the NB X fragments', one read per matrix instruction, one copy, and a part of
     // the address of the next chunk's rows.  The X fragment is the instruction's row operand: a lane's four accumulators
     // are then four consecutive columns of one row of dW.  Neighbouring instructions share a fragment, at the turns
     // of the serpentine the other one: the operand bits that toggle cost clock.
@@ -1163,7 +1163,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     auto step = [&](const unsigned char *cur, auto cs, int ks, const unsigned char *nxt, auto ns, int ksn, unsigned char *refill, int copy0, int next_row,
                     auto which) {
         constexpr int P = decltype(which)::value;
-        static_assert((2 * NB + MB - 1) / MB + 2 <= NB && CPS <= 2 * MB, "one read per matrix instruction, few copies per row");
+        static_assert((2 * NB + MB - 1) / MB + 2 <= NB && CPS <= MB, "one read per matrix instruction, one copy per row");
         int64_t nextA = 0, nextB = 0;
         v4i16 lo{}, loA{};
 #pragma unroll
@@ -1189,11 +1189,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
                         else fa[mi - 1] = join(loA, load_a(nxt, ns, ksn, mi - 1, 1));
                     }
                 }
-                if (nj == NB - 1) {   // copy by copy along the rows; where there are more copies than rows, two beside some
-                    constexpr int ROWS = CPS < MB ? CPS : MB;
-#pragma unroll
-                    for (int c = mi * CPS / ROWS; mi < ROWS && c < (mi + 1) * CPS / ROWS; ++c) issue(refill, rowsA, rowsB, copy0 + c);
-                }
+                if (nj == NB - 1 && mi < CPS) issue(refill, rowsA, rowsB, copy0 + mi);
                 if (next_row >= 0 && nj == 1) {   // the address of the next chunk's rows, a product or a sum at a time
                     if (mi == MB - 4) { nextA = (int64_t)next_row * ldy * 2; asm volatile("" : "+s"(nextA)); }
                     if (mi == MB - 3) { nextB = (int64_t)next_row * ldx * 2; asm volatile("" : "+s"(nextB)); }
@@ -1244,7 +1240,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     // waves on the compute unit to hide it (c5: 0.45 ms per step).
     // They are buffer loads: pass j reads four rows further down than pass j - 1, which is a wave-uniform step (a
     // scalar register), so the 64 loads of a slice share two address registers.  M is a multiple of 16 and a wave's
-    // rows start at a multiple of 64: the four rows of a pass are all inside the matrix or all outside, and passes
+    // rows start at a multiple of 32: the four rows of a pass are all inside the matrix or all outside, and passes
     // past the edge re-read the last pass inside (a wave with no row inside re-reads the tile's first rows).
     constexpr int RB = WTM * 8192 <= STAGE ? WTM : WTM / 2, NR = WTM / RB;   // row blocks per slice, slices down a wave's tile
     static_assert(RB * 8192 <= STAGE && RB * NR == WTM, "a wave's slice fits one stage");
@@ -2077,7 +2073,7 @@ int run_dense_dw(const void *dY, const void *X, float *dW, int64_t p, int64_t q,
             for (int i = 1; i <= dmatn::kMaxBatch; ++i) batch.first_slot[i] = slots;
             launch_dw_batch(batch, tile, accum, fuse, dt, st);
         };
-        // 256 x 256 tiles when they fill the chip, otherwise the cheapest of the three (dw_few_tile).  A grid of large tiles that is not a
+        // 256 x 256 tiles when they fill the chip, otherwise the cheapest of the four (dw_few_tile).  A grid of large tiles that is not a
         // whole number of rounds over the 256 compute units leaves the chip part empty in its last round (c4's
         // 1376 tiles: 5.375 rounds).  Where whole tile rows or columns can be cut off so that the rest is an exact
         // number of rounds and the cut-off strip is at most half a round of large tiles, the slab runs in large

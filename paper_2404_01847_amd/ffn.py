@@ -40,15 +40,15 @@ class SparseWeight:
             self.zmeta = torch.empty((p // 64, r, 4), dtype=torch.int16, device=self.W.device)
         return self.zvals, self.zmeta
 
+    def compress_args(self, search):
+        """This weight's entry of a s24.compress_batch call: with `search` the mask is searched in the same pass over W, otherwise
+        the stored mask is applied as it is (the steps between two mask updates)."""
+        return (self.W, None if search else self.mask, self.vals, self.meta, self.valsT, self.metaT, self.mask if search else None)
+
     def refresh(self, call=None, search=True):
-        """Rebuild both compressed operands in one pass over W; with `search` the mask is searched in the
-        same pass, otherwise the stored mask is applied as it is (the steps between two mask updates)."""
-        call = call or (lambda name, fn, *a, **k: fn(*a, **k))
-        if search:
-            call("mask_compress", s24.compress, self.W, None, self.vals, self.meta, self.valsT, self.metaT,
-                 mask_out=self.mask)
-        else:
-            call("compress", s24.compress, self.W, self.mask, self.vals, self.meta, self.valsT, self.metaT)
+        """Rebuild both compressed operands in one pass over W."""
+        call = call or (lambda name, fn, *a: fn(*a))
+        call("mask_compress" if search else "compress", s24.compress_batch, [self.compress_args(search)])
 
 
 class SparseFFN:
@@ -116,9 +116,7 @@ class SparseFFN:
 
     def prune(self, search=True):
         """Rebuild the compressed operands of all weights in one pass, searching their masks or applying the stored ones."""
-        self._k("mask_compress" if search else "compress", s24.compress_batch,
-                [(w.W, None if search else w.mask, w.vals, w.meta, w.valsT, w.metaT, w.mask if search else None)
-                 for w in self.w.values()])
+        self._k("mask_compress" if search else "compress", s24.compress_batch, [w.compress_args(search) for w in self.w.values()])
 
     def _fwd(self, Xw, name, out):
         """out = Xw (M.*W)^T, plus the weight's bias if it has one."""
