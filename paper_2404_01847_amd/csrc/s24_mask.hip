@@ -290,34 +290,46 @@ __device__ __noinline__ unsigned mid_best_pattern(Mag16 mag)
 // where the one-lane walk takes 4300 with the other 63 lanes waiting.  fp32 search, 1024 x 256: 71 -> 5 us; 22016 x 4096:
 // 439 -> 78; search and compress 79 -> 8 and 633 -> 263.  (In the 16-bit kernels its registers cost 5 to 10 %.)
 // All 64 lanes must be active; every lane returns the answer for the block of lane `src`.
-__device__ __forceinline__ unsigned wave_mid_best_pattern(const uint32_t (&mag)[16], int src)
-{
-    const int lane = threadIdx.x & 63;
-    unsigned id = (unsigned)lane;
-    const unsigned other_id = min(id + 64u, (unsigned)S24_NUM_PATTERNS - 1u);   // lanes 26..63 repeat the last pattern
-    const unsigned pm = g_patterns.mask[id], pm2 = g_patterns.mask[other_id];
-    double best = 0.0, second = 0.0;
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const double a = (double)__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)mag[t], src));
+struct WavePatterns {
+    unsigned id, other_id, pm, pm2;   // of this lane
+    __device__ __forceinline__ WavePatterns()
+    {
+        id = threadIdx.x & 63;
+        other_id = min(id + 64u, (unsigned)S24_NUM_PATTERNS - 1u);   // lanes 26..63 repeat the last pattern
+        pm = g_patterns.mask[id], pm2 = g_patterns.mask[other_id];
+    }
+    __device__ __forceinline__ void add(int t, double a, double &best, double &second) const
+    {
         best += ((pm >> t) & 1u) ? a : 0.0;
         second += ((pm2 >> t) & 1u) ? a : 0.0;
     }
-    best = __builtin_fmax(best, -1.0);   // a pattern whose sum is NaN never wins, as in the one-lane walk
-    if (second > best) {
-        best = second;
-        id = other_id;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double o = __shfl_xor(best, off, 64);
-        const unsigned oid = (unsigned)__shfl_xor((int)id, off, 64);
-        if (o > best || (o == best && oid < id)) {
-            best = o;
-            id = oid;
+    __device__ __forceinline__ unsigned first_of_best(double best, double second) const
+    {
+        unsigned win = id;
+        best = __builtin_fmax(best, -1.0);   // a pattern whose sum is NaN never wins, as in the one-lane walk
+        if (second > best) {
+            best = second;
+            win = other_id;
         }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const double o = __shfl_xor(best, off, 64);
+            const unsigned oid = (unsigned)__shfl_xor((int)win, off, 64);
+            if (o > best || (o == best && oid < win)) {
+                best = o;
+                win = oid;
+            }
+        }
+        return (unsigned)g_patterns.mask[win] | (win << 16);
     }
-    return (unsigned)g_patterns.mask[id] | (id << 16);
+};
+__device__ __forceinline__ unsigned wave_mid_best_pattern(const uint32_t (&mag)[16], int src)
+{
+    const WavePatterns patterns;
+    double best = 0.0, second = 0.0;
+#pragma unroll
+    for (int t = 0; t < 16; ++t) patterns.add(t, (double)__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)mag[t], src)), best, second);
+    return patterns.first_of_best(best, second);
 }
 
 // The blocks of the lanes that set `mid` or `slow`, one after the other by the whole wave.  All 64 lanes must be active; a lane that
@@ -358,17 +370,17 @@ __device__ __forceinline__ void exponents(const uint32_t (&mag)[16], uint32_t &e
 // Fast path.  mag[4*i+j] = |w_ij| as fp32 bit patterns.  Returns mask | id<<16.
 // WINDOW = binades below the block maximum within which every element is a
 // multiple of 2048*eps (29 for bf16 data, 13 for fp32 data).  What becomes of wider blocks: each lane walks through its own; the
-// wave takes them together (all 64 lanes must call); or they are left to the caller, as kHardBlock.
+// wave takes them together (all 64 lanes must call); or the caller has their answer, in `given`.
 // ---------------------------------------------------------------------------
-constexpr unsigned kHardBlock = 0xFFFFFFFFu;
-enum class Wide { Lane, Wave, Left };
+enum class Wide { Lane, Wave, Given };
 template <int WINDOW, int WIDE, Wide HOW>
-__device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], const uint16_t *lut_mask, const uint8_t *lut_id)
+__device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], const uint16_t *lut_mask, const uint8_t *lut_id, unsigned given = 0)
 {
     uint32_t emax, emin;
     exponents(mag, emax, emin);
     const bool wide = emin + WINDOW < emax;
-    unsigned rare = kHardBlock;
+    if (HOW == Wide::Given && wide) return given;
+    unsigned rare = 0;
     if constexpr (HOW == Wide::Wave) {
         rare = wave_wide_blocks(mag, wide && emin + WIDE >= emax, emin + WIDE < emax);
     } else if (HOW == Wide::Lane && wide) {
@@ -436,7 +448,7 @@ __device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], cons
         }
     const unsigned bonus = (unsigned)__double2loint(best + big) & 0x7FFu;
     const unsigned x = min(bonus - (unsigned)kBonusBase, kLutEntries - 1u);   // (a wide block's index is clamped and unused)
-    return HOW != Wide::Lane && wide ? rare : (unsigned)lut_mask[x] | ((unsigned)lut_id[x] << 16);
+    return HOW == Wide::Wave && wide ? rare : (unsigned)lut_mask[x] | ((unsigned)lut_id[x] << 16);
 }
 
 // ---------------------------------------------------------------------------
@@ -448,6 +460,8 @@ __device__ __forceinline__ unsigned best_pattern(const uint32_t (&mag)[16], cons
 // conversion to an integer are exact.  Returns kHardBlock for a block that does not fit (an element more than ten
 // binades down, a zero or subnormal element, a block maximum below 2^-99): those take the fp64 path above.
 // ---------------------------------------------------------------------------
+constexpr unsigned kHardBlock = 0xFFFFFFFFu;
+
 __device__ __forceinline__ unsigned int_best_pattern(const uint32_t (&mag)[16], const uint16_t *lut_mask, const uint8_t *lut_id)
 {
     uint32_t mx = mag[0], mn = mag[0];
@@ -573,6 +587,64 @@ template <> struct RowOps<float> {
     static __device__ __forceinline__ Pair pair(uint32_t lo, uint32_t hi) { return make_uint2(lo, hi); }
 };
 
+// The blocks of the lanes that set `wide` (p: the lane's block), all 64 lanes active.  Few to a wave are scored by the wave together and
+// many by a lane each: in fp64 either costs as much at about 28, in fixed point (400 us, 29 a block) at 14.  In a call, from memory and
+// with a loop over rows, so that the common path keeps the registers of seven waves per SIMD.  bf16 search, one block in a hundred 40 binades
+// wide: 5120 x 1280 110 us (1460 with each lane's walk in the loop, 609 with the integer path's queue), 3072 x 768 92 (974, 698); without
+// such blocks 6.79 and 4.74 (6.78 and 4.66; 7.38 and 4.70 with all of this inlined after the scores, for six waves).
+template <typename T> __device__ __noinline__ unsigned wide_blocks(const T *p, int64_t ldw, bool wide)
+{
+    using Ops = RowOps<T>;
+    auto load = [ldw](const T *at) {
+        Mag16 mag;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const typename Ops::Row row = Ops::load(at + i * ldw);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) mag.v[4 * i + j] = Ops::mag(row, j);
+        }
+        return mag;
+    };
+    auto of_lane = [p](int src) {
+        const uint64_t at = (uint64_t)p;
+        return reinterpret_cast<const T *>((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)at, src) |
+                                           (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(at >> 32), src) << 32);
+    };
+    unsigned res = 0;
+    uint32_t emax = 0, emin = 0;
+    if (wide) exponents(load(p).v, emax, emin);
+    const bool slow = emin + Ops::kWide < emax, mid = wide && !slow;
+    unsigned long long mids = __ballot(mid), slows = __ballot(slow);
+    if (__popcll(mids) > 28) {
+        if (mid) res = mid_best_pattern(load(p));
+        mids = 0;
+    }
+    if (__popcll(slows) > 14) {
+        if (slow) res = slow_best_pattern(load(p));
+        slows = 0;
+    }
+    for (; slows != 0; slows &= slows - 1) {
+        const int src = (int)__builtin_ctzll(slows);
+        const unsigned r = wave_slow_best_pattern(load(of_lane(src)));
+        if ((int)(threadIdx.x & 63) == src) res = r;
+    }
+    for (; mids != 0; mids &= mids - 1) {   // a row at a time, which takes few registers
+        const int src = (int)__builtin_ctzll(mids);
+        const T *at = of_lane(src);
+        const WavePatterns patterns;
+        double best = 0.0, second = 0.0;
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) {
+            const typename Ops::Row row = Ops::load(at + i * ldw);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) patterns.add(4 * i + j, (double)__uint_as_float(Ops::mag(row, j)), best, second);
+        }
+        const unsigned r = patterns.first_of_best(best, second);
+        if ((int)(threadIdx.x & 63) == src) res = r;
+    }
+    return res;
+}
+
 // A workgroup's tile is TBW blocks wide and 256 / TBW * S blocks tall, S blocks per lane.
 //   32 x 32 (S = 4): the lookup tables are staged once per 1024 blocks and the next block's rows are requested while the
 //   current one is scored: the better shape for the largest matrices.
@@ -600,8 +672,11 @@ struct MaskBatch {
     int begin;              // first tile of this launch
 };
 
+// bf16, searched alone in the small tile: see wide_blocks
+template <typename T, bool SEARCH, bool COMPRESS, int S> constexpr bool kBf16Small = SEARCH && !COMPRESS && sizeof(T) == 2 && RowOps<T>::kWindow == 29 && S == 1;
+
 template <typename T, bool SEARCH, bool COMPRESS, int TBW, int S>
-__global__ __launch_bounds__(256) void mask_compress_kernel(const MaskBatch batch)
+__global__ __launch_bounds__(256, (kBf16Small<T, SEARCH, COMPRESS, S> ? 7 : 1)) void mask_compress_kernel(const MaskBatch batch)
 {
     using Ops = RowOps<T>;
     using Row = typename Ops::Row;
@@ -614,7 +689,7 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const MaskBatch batc
     // (5120 x 1280: 8.8 -> 6.7 us).  (In the fused search + compress kernel the four blocks' rows held in registers across the queue cost
     // more than the cheaper scoring saves: measured 4-8 % slower, so it keeps the fp64 scoring too.)
     constexpr bool DEFER = SEARCH && !COMPRESS && sizeof(T) == 2 && RowOps<T>::kWindow == 29 && S == 4;
-    constexpr bool BF16_SMALL = SEARCH && !COMPRESS && sizeof(T) == 2 && RowOps<T>::kWindow == 29 && S == 1;
+    constexpr bool BF16_SMALL = kBf16Small<T, SEARCH, COMPRESS, S>;
     __shared__ int s_nhard;
     __shared__ uint16_t s_hard[DEFER ? 256 * S : 1];
     __shared__ uint32_t s_fix[DEFER ? 256 * S : 1];
@@ -845,26 +920,6 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const MaskBatch batc
             fetch(nxt, wrow, ok);
             if constexpr (!SEARCH) m_nxt = ok ? *mrow : 0x33CCu;
         };
-        // Of the blocks that the fast path left, few to a wave are scored by the wave together and many by a lane each: in fp64 either costs
-        // as much at about 28, in fixed point (400 us, 29 a block) at 14.  From memory once more, so that the common path keeps no register for it (bf16 search, one block in a
-        // hundred 40 binades wide: 3072 x 768 1010 us with each lane's walk in the loop, 698 with the integer path's queue, 84 so; 5120 x 1280 1496, 609
-        // and 93; without such blocks 6.1, 8.1 and 6.1).
-        auto wide_blocks = [&](const T *p, bool ok, unsigned res) {
-            const bool left = res == kHardBlock;
-            Row again[4];
-            fetch(again, p, ok);
-            Mag16 mag;
-            magnitudes(again, mag.v);
-            uint32_t emax, emin;
-            exponents(mag.v, emax, emin);
-            const bool slow = left && emin + Ops::kWide < emax, mid = left && !slow;
-            const bool mid_alone = __popcll(__ballot(mid)) > 28, slow_alone = __popcll(__ballot(slow)) > 14;
-            const unsigned rare = wave_wide_blocks(mag.v, mid && !mid_alone, slow && !slow_alone);
-            if (left) res = rare;
-            if (mid && mid_alone) res = mid_best_pattern(mag);
-            if (slow && slow_alone) res = slow_best_pattern(mag);
-            return res;
-        };
         request(bi0 + tid / TBW);
         stage_tables();
 #pragma unroll 1
@@ -882,10 +937,15 @@ __global__ __launch_bounds__(256) void mask_compress_kernel(const MaskBatch batc
             if constexpr (SEARCH) {
                 uint32_t mag[16];
                 magnitudes(rows, mag);
-                unsigned res = best_pattern<Ops::kWindow, Ops::kWide, sizeof(T) == 4 ? Wide::Wave : BF16_SMALL ? Wide::Left : Wide::Lane>(mag, s_lut_mask, s_lut_id);
+                unsigned rare = 0;
                 if constexpr (BF16_SMALL) {
-                    if (__any(res == kHardBlock)) res = wide_blocks(wrow, (bi < br) && (bj < bq), res);
+                    uint32_t emax, emin;
+                    exponents(mag, emax, emin);
+                    const bool wide = emin + Ops::kWindow < emax;
+                    if (__any(wide)) rare = wide_blocks<T>(wrow, ldw, wide);
                 }
+                constexpr Wide HOW = sizeof(T) == 4 ? Wide::Wave : BF16_SMALL ? Wide::Given : Wide::Lane;
+                const unsigned res = best_pattern<Ops::kWindow, Ops::kWide, HOW>(mag, s_lut_mask, s_lut_id, rare);
                 m = res & 0xFFFFu;
                 id = res >> 16;
             }
