@@ -214,15 +214,30 @@ def _search_and_compress(s24, W):
     return alone, fused, out, given
 
 
+def _mask_tile(dtype, call, shapes):
+    """The tile that a search alone, a search with compression ("fused") or a compression with given masks takes, by the number of
+    tiles of 32 x 32 blocks of all weights."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rounds = sum(-(-r // 128) * -(-q // 128) for r, q in shapes) / cus
+    if call == "alone":
+        return (32, 32) if dtype == "bf16" and rounds >= 8 else (16, 16)
+    if call == "fused":
+        return (32, 32) if dtype != "f32" and rounds >= 4 else (16, 16)
+    return (16, 16) if rounds < (1 if dtype == "f32" else 4) else (32, 32) if dtype == "f32" and rounds >= 4 else (32, 16)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
-# one 16 x 16 tile and its edges; both sides of the lines between the tile shapes (32 x 32 tiles: 18 x 16 = 288 and 19 x 16,
-# 16 x 32 = 512, 64 x 64 = 4096), ragged in both directions
-@pytest.mark.parametrize("rq", [(64, 64), (192, 320), (2240, 2048), (2368, 2048), (1984, 4160), (8128, 8256)])
+# one 16 x 16 tile and its edges; both sides of the lines between the tile shapes (256, 1024 and 2048 tiles of 32 x 32 blocks: 16 x 16 and
+# 15 x 17; 32 x 31 and 32 x 32; 64 x 65, in fp32 32 x 65) and between them, ragged
+@pytest.mark.parametrize("rq", [(64, 64), (192, 320), (1920, 2112), (2048, 1984), (2240, 2048), (2368, 2048), (1984, 4160), (4096, 3904), (4032, 4032),
+                                (8128, 8256)])
 def test_mask_and_compress_tile_shapes(s24, dtype, rq):
     if rq[0] > 4096 and dtype == "f32":
         rq = (rq[0] // 128 * 64, rq[1])
     W = si.random_matrix(60 + rq[0], rq, 0.02, dtype)
-    alone, fused, out, given = _search_and_compress(s24, W)
+    result = []
+    assert mask_tiles_run(lambda: result.extend(_search_and_compress(s24, W))) == [_mask_tile(dtype, c, [rq]) for c in ("alone", "fused", "given")]
+    alone, fused, out, given = result
     mask = oracle.transposable_mask(W)
     assert np.array_equal(host_bits(alone), mask) and np.array_equal(host_bits(fused), mask)
     c = oracle.compress(W, mask)
@@ -232,15 +247,51 @@ def test_mask_and_compress_tile_shapes(s24, dtype, rq):
         assert torch.equal(got.view(torch.uint8), again.view(torch.uint8))
 
 
+def _repeated(a, r, q):
+    """`a` over and over along both axes, cut to r x q: what a block is worth does not depend on where it lies."""
+    return np.ascontiguousarray(np.tile(a, (-(-r // a.shape[0]), -(-q // a.shape[1])))[:r, :q])
+
+
+def _search_in_tiles(s24, W, mask, ids, dtype, compress):
+    """Masks and pattern ids of a search alone, and the masks of the search that compresses, in the tiles that the size asks for."""
+    r, q = W.shape
+    new = lambda *shape, t=torch.int16: torch.full(shape, 7, dtype=t, device="cuda")
+    Wd, alone, index = dev_bf16(W), new(r // 4, q // 4), new(r // 4, q // 4, t=torch.uint8)
+    assert mask_tiles_run(lambda: s24.transposable_mask(Wd, alone, index)) == [_mask_tile(dtype, "alone", [(r, q)])]
+    assert np.array_equal(host_bits(alone), mask) and np.array_equal(index.cpu().numpy(), ids)
+    if compress:
+        fused, td = new(r // 4, q // 4), torch_dtype(dtype)
+        out = [new(q // 64, r, 32, t=td), new(q // 64, r, 4), new(r // 64, q, 32, t=td), new(r // 64, q, 4)]
+        assert mask_tiles_run(lambda: s24.compress(Wd, None, *out, mask_out=fused)) == [_mask_tile(dtype, "fused", [(r, q)])]
+        assert np.array_equal(host_bits(fused), mask)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
-@pytest.mark.parametrize("kind", ["tiny", "range", "subnormal", "window", "zeros"])
-@pytest.mark.parametrize("rq", [(192, 320), (2432, 2048)])
+@pytest.mark.parametrize("kind", ["few", "equal", "tiny", "range", "subnormal", "window", "zeros"])
+# the small tile, and 46 x 46 tiles of 32 x 32 blocks, the last ones half empty (and, of the search alone, a block column and row less)
+@pytest.mark.parametrize("rq", [(192, 320), (2432, 2048), (5824, 5824), (5820, 5820)])
 def test_wide_blocks_in_both_tile_shapes(s24, dtype, kind, rq):
-    """Blocks too wide for the fast path, many per wave: the wave-cooperative paths of fp32, the queue of bf16."""
-    W = si.tie_matrix(61, *rq, dtype, kind)
-    alone, fused, _, _ = _search_and_compress(s24, W)
-    mask = oracle.transposable_mask(W)
-    assert np.array_equal(host_bits(alone), mask) and np.array_equal(host_bits(fused), mask)
+    """Ties, and blocks too wide for the fast paths, many per wave: the wave-cooperative paths of fp32, the integer scores of bf16 in the
+    large tile with their queue and what the small one does instead, the fp64 scores of the fused search in either."""
+    r, q = rq
+    one = si.tie_matrix(61, *((192, 320) if r > 4096 else rq), dtype, kind)      # the large ones are it over and over: one oracle's worth
+    mask, ids = oracle.transposable_mask(one, want_index=True)
+    _search_in_tiles(s24, _repeated(one, r, q), _repeated(mask, r // 4, q // 4), _repeated(ids, r // 4, q // 4), dtype, r % 64 == 0)
+
+
+@pytest.mark.parametrize("big_exp", [9, 10, 11, 12, 26, 40, 47, 60, 100])
+@pytest.mark.parametrize("rq", [(64, 320), (5824, 5824)])
+def test_margins_below_an_fp64_sum_in_both_tile_shapes(s24, legal_blocks, big_exp, rq):
+    """Best patterns that are one unit in the last place of a small element ahead of an earlier one.  In every fourth block elements ten
+    binades below the largest stand for the zeros, so that up to 2^10 the integer scores take it."""
+    from util import absorbed_margin_blocks
+    one, _ = absorbed_margin_blocks(legal_blocks, "bf16", big_exp)
+    f = si.to_f32(one)
+    full = np.where((f == 0) & (np.arange(f.shape[1]) // 4 % 4 == 0)[None, :], np.float32(2.0 ** (big_exp - 10)), f)
+    one = si.f32_to_bf16_bits(torch.from_numpy(np.ascontiguousarray(full)))
+    mask, ids = oracle.transposable_mask(one, want_index=True)
+    r, q = rq
+    _search_in_tiles(s24, _repeated(one, r, q), _repeated(mask, r // 4, q // 4), _repeated(ids, r // 4, q // 4), "bf16", True)
 
 
 # 35 binades: fp64 sums; 60: fixed point.  Few or many of a wave's 64 blocks, all of them among them
@@ -550,10 +601,10 @@ def test_gelu_of_zeros_and_large_values_in_the_epilogues(s24, p, q, tile):
 
 # ------------------------------------------------------------------ several weights in one mask / compress launch
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
-# one tile and part of one; more than a compute unit's worth of the small tile; past it, where the larger ones take over (one weight
-# of whole tiles, one with an edge both ways, one of a single chunk), and past the sixteenfold of that
+# 3, 150, 766, 1628 and 4105 tiles of 32 x 32 blocks: the lines lie at 256 and 1024.  Weights of whole tiles, with an edge both ways and of a
+# single chunk
 @pytest.mark.parametrize("shapes", [[(64, 64), (128, 192)], [(1088, 832), (64, 3072), (832, 1088)], [(4096, 1024), (2112, 3520), (64, 64), (64, 4160)],
-                                    [(8192, 8192), (1088, 64)]])
+                                    [(2112, 3520), (4160, 4032), (64, 4160), (1088, 832)], [(8192, 8192), (1088, 64)]])
 def test_several_weights_in_one_compress_pass(s24, dtype, shapes):
     td = torch_dtype(dtype)
     g = torch.Generator(device="cuda").manual_seed(7)
@@ -569,8 +620,8 @@ def test_several_weights_in_one_compress_pass(s24, dtype, shapes):
     for W, (v, m, vt, mt, mask) in zip(Ws, one):
         s24.transposable_mask(W, mask)                        # checked against the oracle elsewhere
         s24.compress(W, mask, v, m, vt, mt)
-    s24.compress_batch([(W, None, *b) for W, b in zip(Ws, all_)])
-    s24.compress_batch([(W, o[4], *b[:4], None) for W, o, b in zip(Ws, one, given)])
+    assert mask_tiles_run(lambda: s24.compress_batch([(W, None, *b) for W, b in zip(Ws, all_)])) == [_mask_tile(dtype, "fused", shapes)]
+    assert mask_tiles_run(lambda: s24.compress_batch([(W, o[4], *b[:4], None) for W, o, b in zip(Ws, one, given)])) == [_mask_tile(dtype, "given", shapes)]
     bits = lambda x: x.view(torch.int32 if x.dtype == torch.float32 else torch.int16)
     for W, (r, q), a, b, c in zip(Ws, shapes, one, all_, given):
         assert all(torch.equal(bits(x), bits(y)) for x, y in zip(a, b))
