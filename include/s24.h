@@ -330,9 +330,12 @@ int s24_set_clock_probe(void *two_counters);
  * instructions on registers only (no LDS, no memory): v_mfma_f32_16x16x32_bf16 (sparse == 0, 16384 FLOP each) or
  * v_smfmac_f32_16x16x64_bf16 (sparse != 0, 32768 dense-equivalent FLOP each).  sink [workgroups * 512] floats,
  * device, receives one checksum per lane.  s24_probe_copy copies `bytes` (a multiple of 16; src and dst 16-byte
- * aligned, not overlapping) device to device in 16-byte accesses.  The caller times the launches. */
+ * aligned, not overlapping) device to device in 16-byte accesses.  The caller times the launches.
+ * s24_probe_reciprocal adds to *different (device) how many of the `count` floats with the bits first, first + 1, ... have a short
+ * reciprocal (the one of the unbiased pruning, for 2^-100 to 2^100) with other bits than the division's. */
 int s24_probe_matrix_rate(int sparse, int workgroups, int iters, float *sink, void *stream);
 int s24_probe_copy(const void *src, void *dst, int64_t bytes, void *stream);
+int s24_probe_reciprocal(uint32_t first, int64_t count, uint64_t *different, void *stream);
 
 #ifdef __cplusplus
 }

@@ -57,6 +57,7 @@ _SIGNATURES = {
     "s24_set_clock_probe": (_int, [_vp]),
     "s24_probe_matrix_rate": (_int, [_int, _int, _int, _vp, _vp]),
     "s24_probe_copy": (_int, [_vp, _vp, _i64, _vp]),
+    "s24_probe_reciprocal": (_int, [C.c_uint32, _i64, _vp, _vp]),
 }
 EXPORTS = tuple(_SIGNATURES)
 
@@ -447,3 +448,10 @@ def probe_copy(src, dst):
     if nbytes != dst.numel() * dst.element_size():
         raise ValueError("s24_probe_copy: sizes differ")
     _check(lib().s24_probe_copy(_ptr(src), _ptr(dst), nbytes, _stream()), "s24_probe_copy")
+
+
+def probe_reciprocal(first, count, different):
+    """Adds to `different` (int64 tensor of one element) how many of `count` floats from the bits `first` on have a short reciprocal
+    that is not the division's."""
+    _dense("s24_probe_reciprocal", "different", different)
+    _check(lib().s24_probe_reciprocal(first, count, _ptr(different), _stream()), "s24_probe_reciprocal")

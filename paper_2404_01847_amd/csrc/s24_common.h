@@ -67,6 +67,14 @@ __device__ __forceinline__ uint4 s24_load_stream(const void *p)
     return __builtin_bit_cast(uint4, __builtin_nontemporal_load(static_cast<const s24_u32x4 *>(p)));
 }
 
+// 1 / d rounded to nearest for 2^-100 <= d <= 2^100: the hardware's estimate and one Newton step on its exact residual.  Each of these
+// d is compared with the division by the tests, through s24_probe_reciprocal.
+__device__ __forceinline__ float s24_reciprocal(float d)
+{
+    const float y = __builtin_amdgcn_rcpf(d);
+    return __fmaf_rn(__fmaf_rn(-d, y, 1.0f), y, y);
+}
+
 // Storage types of the kernels: uint16_t holds bf16 bits, s24_half is IEEE binary16, float is itself.
 // s24_num<T> converts between 16-bit storage and the fp32 the arithmetic runs in: one value from its 16 bits,
 // the low / high half of a dword, and back (round to nearest even; binary16 overflows to infinity).

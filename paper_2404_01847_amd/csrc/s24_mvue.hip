@@ -58,14 +58,6 @@ __device__ __forceinline__ Kept mvue_group_general(const float (&a)[4], uint32_t
     return {i0, i1, pick(i0), pick(i1)};
 }
 
-// 1 / d rounded to nearest for 2^-100 <= d <= 2^100: the hardware's estimate and one Newton step on its exact residual.  Every d of
-// one binade was compared with the division (the others differ in the exponent alone).
-__device__ __forceinline__ float reciprocal(float d)
-{
-    const float y = __builtin_amdgcn_rcpf(d);
-    return __fmaf_rn(__fmaf_rn(-d, y, 1.0f), y, y);
-}
-
 // mvue_group_general with the same operations on the values that matter, about 100 instructions instead of 150 (the kernel is bound
 // by them; bf16, 4160 tokens: 6400 features 33.6 -> 26.8 us, 1600 16.4 -> 13.3, where the memory would take 13.0 and 3.3).  The
 // factor 2 of an uncapped group doubles the reciprocal, exactly; the largest element of a capped one exceeds the others' sum R, so its
@@ -85,7 +77,7 @@ __device__ __forceinline__ bool mvue_group(const float (&a)[4], uint32_t bits, K
     const float R = __fsub_rn(S, mx), D = capped ? R : S;
     const bool few = D == 0.0f;
     const float size = few ? mx : D, offset = few ? -1.0f : 0.0f;
-    const float factor = __fmul_rn(reciprocal(size == 0.0f ? 1.0f : size), few ? 4.0f : (capped ? 1.0f : 2.0f));
+    const float factor = __fmul_rn(s24_reciprocal(size == 0.0f ? 1.0f : size), few ? 4.0f : (capped ? 1.0f : 2.0f));
     const float common = capped ? R : __fmul_rn(0.5f, S), top = capped ? mx : -1.0f;
     auto pi = [&](int i) { return __builtin_amdgcn_fmed3f(__fmaf_rn(m[i], factor, offset), 0.0f, 1.0f); };
     c[1] = pi(0);

@@ -6,7 +6,10 @@
 //                          holds under that load
 //   s24_probe_copy         a plain device-to-device copy in 16-byte accesses: what HBM delivers to a kernel that
 //                          does nothing but move bytes
+//   s24_probe_reciprocal   the short reciprocal of the unbiased pruning beside the division, over a run of floats
 // The caller times the launches (events on the stream) and divides.
+#include <algorithm>
+
 #include "s24_common.h"
 
 namespace {
@@ -71,6 +74,16 @@ __global__ __launch_bounds__(256) void copy_kernel(const u32x4 *__restrict__ src
     if (i < n16) __builtin_nontemporal_store(__builtin_nontemporal_load(src + i), dst + i);
 }
 
+__global__ __launch_bounds__(256) void reciprocal_kernel(uint32_t first, int64_t count, unsigned long long *different)
+{
+    unsigned long long found = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256) {
+        const float d = __uint_as_float(first + (uint32_t)i);
+        found += __float_as_uint(s24_reciprocal(d)) != __float_as_uint(__fdiv_rn(1.0f, d));
+    }
+    if (found != 0) atomicAdd(different, found);
+}
+
 }  // namespace
 
 extern "C" int s24_probe_matrix_rate(int sparse, int workgroups, int iters, float *sink, void *stream)
@@ -98,5 +111,17 @@ extern "C" int s24_probe_copy(const void *src, void *dst, int64_t bytes, void *s
     S24_REQUIRE(grid < (1ll << 31), S24_ERR_SHAPE);
     hipLaunchKernelGGL(copy_kernel, dim3((unsigned)grid), dim3(256), 0, static_cast<hipStream_t>(stream),
                        static_cast<const u32x4 *>(src), static_cast<u32x4 *>(dst), n16);
+    return s24_launch_status();
+}
+
+extern "C" int s24_probe_reciprocal(uint32_t first, int64_t count, uint64_t *different, void *stream)
+{
+    S24_REQUIRE(count >= 0 && count <= (1ll << 32) - first, S24_ERR_SHAPE);
+    if (count == 0) return S24_OK;
+    S24_REQUIRE(different != nullptr, S24_ERR_NULL);
+    S24_REQUIRE(s24_aligned(different, 8), S24_ERR_ALIGN);
+    const int64_t grid = std::min<int64_t>((count + 255) / 256, 8 * s24_cu_count());
+    hipLaunchKernelGGL(reciprocal_kernel, dim3((unsigned)grid), dim3(256), 0, static_cast<hipStream_t>(stream), first, count,
+                       reinterpret_cast<unsigned long long *>(different));
     return s24_launch_status();
 }

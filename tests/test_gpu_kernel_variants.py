@@ -679,6 +679,16 @@ def test_pruned_gradients_of_any_magnitude(s24, dtype, spread):
     assert np.array_equal(host_bits(vals).view(word), want_v.view(word))
 
 
+def test_short_reciprocal_of_every_float_that_it_takes(s24):
+    """2^-100 to 2^100, both ends among them: the bits of the division."""
+    first, last = ((127 + e) << 23 for e in (-100, 100))
+    different = torch.zeros(1, dtype=torch.int64, device="cuda")
+    s24.probe_reciprocal(first, last - first + 1, different)
+    assert int(different) == 0
+    s24.probe_reciprocal(1, 1 << 23, different)               # subnormals and the smallest normal value are not for it: seen to differ
+    assert int(different) > 0
+
+
 # ------------------------------------------------------------------ fp32 weight gradients with several batches in flight
 # 32-tiles in at most a workgroup per compute unit (192 of them), in one to two (512) and in more (1088), and 64-tiles (768): one, two or four
 # batches of eight token pairs in flight

@@ -141,6 +141,9 @@ def test_probe_argument_errors(lib):
     assert lib.s24_probe_copy(P, None, 32, None) == NULL
     assert lib.s24_probe_copy(P + 4, P, 32, None) == ALIGN
     assert lib.s24_probe_copy(None, None, 0, None) == OK
+    assert lib.s24_probe_reciprocal(1, -1, P, None) == SHAPE and lib.s24_probe_reciprocal(1, 1 << 32, P, None) == SHAPE
+    assert lib.s24_probe_reciprocal(1, 5, None, None) == NULL and lib.s24_probe_reciprocal(1, 5, P + 4, None) == ALIGN
+    assert lib.s24_probe_reciprocal(0, 0, None, None) == OK
 
 
 def test_mvue_argument_errors(lib):
