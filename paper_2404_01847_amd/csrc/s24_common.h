@@ -55,7 +55,8 @@ __device__ __forceinline__ uint32_t s24_f32_to_bf16(float f) { return s24_pack_b
 // the backward pass) and the weight gradients (kept for the optimizer), and for the last read of Z and [G|U].  Plain stores
 // stay in the 256 MB Infinity Cache as modified lines, which push out H and dZ before the next product reads them and then cost that
 // product a write to memory for each line it misses: 128 MB read after 256 MB of plain stores came in at 2.9 TB/s, after non-temporal
-// ones at 6.2.  A layer of 16384 x 1280 x 5120: 1042 -> 1001 us a step; 3001 x 2048 x 5504, gated: 570 -> 540; 4160 x 1600 x 6400: 476 -> 460.
+// ones at 6.2.  Plain stores and loads in their place and as it is, alternating on one card: a layer of 16384 x 1280 x 5120 1002 -> 965 us a
+// step; 3001 x 2048 x 5504, gated, 555 -> 522; 4160 x 1600 x 6400 with pruned gradients 455 -> 430; 16384 x 4096 x 11008, gated, 8224 -> 8179, which is noise.
 typedef unsigned int s24_u32x4 __attribute__((ext_vector_type(4)));
 template <typename V> __device__ __forceinline__ void s24_store_stream(void *p, V v)
 {

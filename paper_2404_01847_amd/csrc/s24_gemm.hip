@@ -2006,9 +2006,11 @@ dmatn::DwWindow dw_window(const DwProblem &pr, DwTile tile, int64_t m_off, int64
 // 0.2 % above the best tile at the mean of 64 other pairs.
 // The tile of 192 x 128, where at most one of them falls to a compute unit, spreads over more of these what the medium tile piles on some: a
 // GPT-2-small layer's gradients are 192 of it against 144.  4096 tokens x 768 x 3072 (both gradients) 47.2 -> 43.5 us, 8192 x 896 x
-// 3136 122 -> 109, 6016 x 832 x 2880 86.7 -> 78.7.  From 100 chunks (3200 tokens) on: below, the gain is of the order of 2 us, and with more than one to a
-// compute unit the other tiles are as good (8192 x 1152 x 3072: 138 against 129).  For several gradients in one grid, as measured; one alone keeps the
-// other three.
+// 3136 122 -> 109, 6016 x 832 x 2880 86.7 -> 78.7.  The cost is fitted from 100 chunks (3200 tokens) on.  Below, the tile would save 0.4 to
+// 2.4 us where there are 192 to 244 of it (2048 x 768 x 3072 30.4 -> 28.2, 128 x 768 x 3072 10.3 -> 9.4, 512 x 896 x 3136 15.1 -> 14.7) and lose 10 to 35 %
+// to the small tile where there are fewer (512 x 640 x 2560, 150: 10.6 and 12.8): it is left to the other three there.  With more than one to a
+// compute unit these are faster (8192 x 1024 x 3072, 272: 90 against 131), and so is the small tile for one gradient alone, measured at
+// 44 to 176 of this one (8192 x 4096 x 1024: 60 against 78; 2048 x 3072 x 768: 20 against 26).
 DwTile dw_few_tile(const DwProblem *pr, int count)
 {
     const int64_t cus = s24_cu_count();
