@@ -276,8 +276,9 @@ __device__ __forceinline__ void staged_store(const f32x4 (&acc)[2 * MI][4], unsi
 // the usual spread.  Not for binary16, whose octaves have 1024 values.  16384 tokens, K = 1280, 5120 features, alternating on one card,
 // the function alone and now: forward 168 -> 144 us, backward 185 -> 161 (with ReLU, another card, 134 and 139); 4160, 1600, 6400: 69 -> 62 and
 // 74 -> 67; in the 128 x 128 tile, whose lanes have half as many elements to a table, 8192, 768, 3072: 48 -> 44 and 47 -> 45.
-// Every other token zero: 153 -> 144 and 184 -> 169, 64 -> 60 and 73 -> 71, 44 -> 45 and 46 -> 49; one feature in 128 past 16: 173 -> 161 and
-// 184 -> 170, 71 -> 68 and 74 -> 71, 48 -> 48 and 47 -> 47 (with the function for those, 177 and 189, 73 and 78, 52 and 48).
+// Every other token zero: 157 -> 145 and 187 -> 169, 66 -> 63 and 74 -> 70, 44.8 -> 45.7 and 46.4 -> 47.3; the last half of them: 158 -> 140 and
+// 185 -> 161, 67 -> 61 and 74 -> 69, 45.1 -> 43.7 and 45.8 -> 46.1; one feature in 128 past 16: 171 -> 161 and 187 -> 170, 71 -> 68 and 74 -> 71, 49.5 -> 48.4
+// and 47.4 -> 47.7 (with the function for those, 177 and 189, 73 and 78, 52 and 48).
 template <int ACT_MODE, int ACT> struct ActTable {
     typedef std::conditional_t<ACT_MODE == 1, uint16_t, float> entry;   // H as it is stored; the slope is multiplied before it is rounded
     static constexpr int EXP = ACT_MODE == 1 ? 16 : 14, FIRST = (127 - EXP) << 7, COUNT = (EXP + 4) << 7;   // of either sign
