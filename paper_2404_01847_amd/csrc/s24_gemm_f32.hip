@@ -55,19 +55,11 @@ template <int KS> __device__ __forceinline__ float4 slice_sum(const float *p, in
 }
 
 // ------------------------------------------------------------------ NT
-struct NtArgs {
-    const float *B, *Av;
-    const uint16_t *Am;
-    float *Out, *H;
-    const float *bias;
-    int N, K, M, F;   // F: gated features (GLU), else M
-    int tiles_m;
-};
-
 // SPARSE: A compressed.  EPI / ACT: epilogue.  GLU needs T = 2: a tile takes 32 gate rows and the 32 up rows of the same
-// features.
+// features, F of either (else F = M).  The arguments are one by one and in the order in which they are needed: see FLAGS in build.py.
 template <bool SPARSE, bool ACCUM, int EPI, int ACT, int T, int KS>
-__global__ __launch_bounds__(64 * KS) void f32_nt_kernel(const NtArgs g)
+__global__ __launch_bounds__(64 * KS) void f32_nt_kernel(const float *B, const float *Av, const uint16_t *Am, int N, int K, int M, int F, int tiles_m,
+                                                         float *Out, float *H, const float *bias)
 {
     static_assert(EPI != S24_F32_GLU || T == 2, "the gated tile pairs two row blocks");
     constexpr int TW = 32 * T, PITCH = TW + 4, SLICE = TW * PITCH, THREADS = 64 * KS;
@@ -75,7 +67,7 @@ __global__ __launch_bounds__(64 * KS) void f32_nt_kernel(const NtArgs g)
     const int tid = threadIdx.x, lane = tid & 63;
     const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, l = lane & 31;
-    const int tm = (int)blockIdx.x % g.tiles_m, tn = (int)blockIdx.x / g.tiles_m;
+    const int tm = (int)blockIdx.x % tiles_m, tn = (int)blockIdx.x / tiles_m;
     constexpr int FM = EPI == S24_F32_GLU ? 32 : TW;   // features of the (gated) output per tile
     const int m0 = tm * FM, n0 = tn * TW;
 
@@ -89,22 +81,22 @@ __global__ __launch_bounds__(64 * KS) void f32_nt_kernel(const NtArgs g)
     const float *b[T];
 #pragma unroll
     for (int i = 0; i < T; ++i) {
-        arow[i] = EPI == S24_F32_GLU ? i * g.F + min(m0 + l, g.F - 1) : min(m0 + 32 * i + l, g.M - 1);
-        b[i] = g.B + (int64_t)min(n0 + 32 * i + l, g.N - 1) * g.K;
+        arow[i] = EPI == S24_F32_GLU ? i * F + min(m0 + l, F - 1) : min(m0 + 32 * i + l, M - 1);
+        b[i] = B + (int64_t)min(n0 + 32 * i + l, N - 1) * K;
     }
     // units of 16 of k: lane half h takes k 8h .. 8h+7 of a unit
-    const int units = g.K / 16, u0 = s24_slice_begin(units, ks, KS), u1 = s24_slice_begin(units, ks + 1, KS);
+    const int units = K / 16, u0 = s24_slice_begin(units, ks, KS), u1 = s24_slice_begin(units, ks + 1, KS);
     struct Frag { float4 a[T][2]; float4 b[T][2]; uint32_t nib[T]; };
     auto load = [&](int u, Frag &f) {
         const int k = 16 * u + 8 * h;
 #pragma unroll
         for (int i = 0; i < T; ++i) {
             if constexpr (SPARSE) {   // four kept values of the run's two groups, and their byte of the index words
-                const int64_t cr = (int64_t)(u >> 2) * g.M + arow[i];
-                f.a[i][0] = *reinterpret_cast<const float4 *>(g.Av + cr * 32 + 8 * (u & 3) + 4 * h);
-                f.nib[i] = (uint32_t)g.Am[cr * 4 + (u & 3)] >> (8 * h);
+                const int64_t cr = (int64_t)(u >> 2) * M + arow[i];
+                f.a[i][0] = *reinterpret_cast<const float4 *>(Av + cr * 32 + 8 * (u & 3) + 4 * h);
+                f.nib[i] = (uint32_t)Am[cr * 4 + (u & 3)] >> (8 * h);
             } else {
-                const float *a = g.Av + (int64_t)arow[i] * g.K + k;
+                const float *a = Av + (int64_t)arow[i] * K + k;
                 f.a[i][0] = *reinterpret_cast<const float4 *>(a);
                 f.a[i][1] = *reinterpret_cast<const float4 *>(a + 4);
             }
@@ -160,22 +152,22 @@ __global__ __launch_bounds__(64 * KS) void f32_nt_kernel(const NtArgs g)
 #pragma unroll 1
     for (int it = tid; it < ITEMS; it += THREADS) {
         const int q = it % QUADS, row = it / QUADS, m = m0 + 4 * q, n = n0 + row;
-        if (n >= g.N || m >= (EPI == S24_F32_GLU ? g.F : g.M)) continue;   // M, F multiples of 16
+        if (n >= N || m >= (EPI == S24_F32_GLU ? F : M)) continue;   // M, F multiples of 16
         const float *p = s_red + row * PITCH + 4 * q;
         auto finish = [&](const float *src, int feature) {
             float4 v = slice_sum<KS>(src, SLICE);
             if constexpr (SPARSE) {
-                const float *x = g.B + (int64_t)n * g.K;
-                if (v.x != v.x) v.x = kept_sum(g.Av, g.Am, g.M, feature, g.K, x, 1);
-                if (v.y != v.y) v.y = kept_sum(g.Av, g.Am, g.M, feature + 1, g.K, x, 1);
-                if (v.z != v.z) v.z = kept_sum(g.Av, g.Am, g.M, feature + 2, g.K, x, 1);
-                if (v.w != v.w) v.w = kept_sum(g.Av, g.Am, g.M, feature + 3, g.K, x, 1);
+                const float *x = B + (int64_t)n * K;
+                if (v.x != v.x) v.x = kept_sum(Av, Am, M, feature, K, x, 1);
+                if (v.y != v.y) v.y = kept_sum(Av, Am, M, feature + 1, K, x, 1);
+                if (v.z != v.z) v.z = kept_sum(Av, Am, M, feature + 2, K, x, 1);
+                if (v.w != v.w) v.w = kept_sum(Av, Am, M, feature + 3, K, x, 1);
             }
-            if (g.bias != nullptr) {
-                const float2 b0 = *reinterpret_cast<const float2 *>(g.bias + feature), b1 = *reinterpret_cast<const float2 *>(g.bias + feature + 2);
+            if (bias != nullptr) {
+                const float2 b0 = *reinterpret_cast<const float2 *>(bias + feature), b1 = *reinterpret_cast<const float2 *>(bias + feature + 2);
                 v.x += b0.x; v.y += b0.y; v.z += b1.x; v.w += b1.y;
             }
-            float4 *o = reinterpret_cast<float4 *>(g.Out + (int64_t)n * g.M + feature);
+            float4 *o = reinterpret_cast<float4 *>(Out + (int64_t)n * M + feature);
             if (ACCUM) {
                 const float4 old = *o;
                 v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
@@ -184,13 +176,13 @@ __global__ __launch_bounds__(64 * KS) void f32_nt_kernel(const NtArgs g)
             return v;
         };
         if constexpr (EPI == S24_F32_GLU) {
-            const float4 z = finish(p, m), u = finish(p + 32, g.F + m);
-            *reinterpret_cast<float4 *>(g.H + (int64_t)n * g.F + m) =
+            const float4 z = finish(p, m), u = finish(p + 32, F + m);
+            *reinterpret_cast<float4 *>(H + (int64_t)n * F + m) =
                 make_float4(s24_glu<ACT>(z.x, u.x), s24_glu<ACT>(z.y, u.y), s24_glu<ACT>(z.z, u.z), s24_glu<ACT>(z.w, u.w));
         } else {
             const float4 z = finish(p, m);
             if constexpr (EPI == S24_F32_ACT) {
-                *reinterpret_cast<float4 *>(g.H + (int64_t)n * g.M + m) = make_float4(s24_act_value<ACT>(z.x), s24_act_value<ACT>(z.y), s24_act_value<ACT>(z.z), s24_act_value<ACT>(z.w));
+                *reinterpret_cast<float4 *>(H + (int64_t)n * M + m) = make_float4(s24_act_value<ACT>(z.x), s24_act_value<ACT>(z.y), s24_act_value<ACT>(z.z), s24_act_value<ACT>(z.w));
             }
         }
     }
@@ -378,11 +370,11 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 template <bool SPARSE, bool ACCUM, int EPI, int ACT, int T, int KS>
 int launch_nt(const S24F32Nt &g, hipStream_t st)
 {
-    NtArgs a{g.B, g.Av, g.Am, g.Out, g.H, g.bias, (int)g.N, (int)g.K, (int)g.M, (int)(EPI == S24_F32_GLU ? g.M / 2 : g.M), 0};
-    const int64_t tiles_m = EPI == S24_F32_GLU ? ceil_div(a.F, 32) : ceil_div(a.M, 32 * T), tiles = tiles_m * ceil_div(a.N, 32 * T);
+    const int64_t F = EPI == S24_F32_GLU ? g.M / 2 : g.M;
+    const int64_t tiles_m = ceil_div(F, EPI == S24_F32_GLU ? 32 : 32 * T), tiles = tiles_m * ceil_div(g.N, 32 * T);
     S24_REQUIRE(tiles < (1ll << 31), S24_ERR_SHAPE);
-    a.tiles_m = (int)tiles_m;
-    hipLaunchKernelGGL((f32_nt_kernel<SPARSE, ACCUM, EPI, ACT, T, KS>), dim3((unsigned)tiles), dim3(64 * KS), 0, st, a);
+    hipLaunchKernelGGL((f32_nt_kernel<SPARSE, ACCUM, EPI, ACT, T, KS>), dim3((unsigned)tiles), dim3(64 * KS), 0, st, g.B, g.Av, g.Am, (int)g.N, (int)g.K,
+                       (int)g.M, (int)F, (int)tiles_m, g.Out, g.H, g.bias);
     return s24_launch_status();
 }
 

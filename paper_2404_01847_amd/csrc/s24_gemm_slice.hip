@@ -34,14 +34,6 @@ template <> __device__ __forceinline__ f32x4 mma<s24_half>(uint4 a, Two b, f32x4
     return __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x16, b), c, (int)idx, 0, 0);
 }
 
-struct NtArgs {
-    const uint16_t *B, *Av, *Am;
-    uint16_t *Out, *H;
-    const uint16_t *Z, *bias;
-    int N, K, M, F;   // F: gated features (GLU)
-    int tiles_n, tiles;
-};
-
 // Slices per workgroup.  One number for all shapes: among the products that come here an output's bits depend on K alone, so
 // that a product with and without a fused epilogue agrees to the last bit.  Which products come here depends on their tokens
 // and features too (s24_slice_pays), and the tiles of s24_gemm.hip sum in another order: a token alone and the same token
@@ -50,9 +42,12 @@ constexpr int KS = 8;
 
 // A workgroup owns 16*TM features x 16*TN tokens; wave s of its KS waves takes the 64-chunks s, s + KS, ... of the
 // contraction, D of them in flight, and the slices are summed in LDS in wave order, so the result does not depend on
-// scheduling.  GLU: the tile's row blocks are 8*TM gate rows and the 8*TM up rows of the same features.
+// scheduling.  GLU: the tile's row blocks are 8*TM gate rows and the 8*TM up rows of the same features (F of either).
+// The arguments are one by one and in the order in which they are needed: see FLAGS in build.py.
 template <typename T, bool ACCUM, int EPI, int ACT, int TM, int TN>
-__global__ __launch_bounds__(64 * KS) void spmm_slice_kernel(const NtArgs g)
+__global__ __launch_bounds__(64 * KS) void spmm_slice_kernel(const uint16_t *__restrict__ B, const uint16_t *__restrict__ Av, const uint16_t *__restrict__ Am,
+                                                             int N, int K, int M, int F, int tiles_n, int tiles, uint16_t *Out, uint16_t *H,
+                                                             const uint16_t *Z, const uint16_t *bias)
 {
     static_assert(EPI != S24_SLICE_GLU || TM % 2 == 0, "the gated tile pairs row blocks");
     constexpr int THREADS = 64 * KS, D = TM + TN <= 3 ? 4 : 2;
@@ -63,9 +58,9 @@ __global__ __launch_bounds__(64 * KS) void spmm_slice_kernel(const NtArgs g)
     const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);
     // workgroups are dealt round-robin to the eight XCDs: each takes one contiguous eighth of the tile list, the token
     // tiles of one feature tile next to each other, so that they read its weights through one L2
-    const int per_xcd = (g.tiles + 7) / 8, t = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-    if (t >= g.tiles) return;
-    const int tm = t / g.tiles_n, tn = t - tm * g.tiles_n;
+    const int per_xcd = (tiles + 7) / 8, t = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (t >= tiles) return;
+    const int tm = t / tiles_n, tn = t - tm * tiles_n;
     const int m0 = tm * FM, n0 = tn * TWN;
     const int l = lane & 15, q = lane >> 4;
 
@@ -73,18 +68,18 @@ __global__ __launch_bounds__(64 * KS) void spmm_slice_kernel(const NtArgs g)
     uint32_t oa[TM], ob[TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-        const int row = EPI == S24_SLICE_GLU ? (i < TM / 2 ? 0 : g.F) + min(m0 + 16 * (i % (TM / 2 > 0 ? TM / 2 : 1)) + l, g.F - 1)
-                                             : min(m0 + 16 * i + l, g.M - 1);
+        const int row = EPI == S24_SLICE_GLU ? (i < TM / 2 ? 0 : F) + min(m0 + 16 * (i % (TM / 2 > 0 ? TM / 2 : 1)) + l, F - 1)
+                                             : min(m0 + 16 * i + l, M - 1);
         oa[i] = (uint32_t)row * 64u + 16u * q;
     }
 #pragma unroll
-    for (int j = 0; j < TN; ++j) ob[j] = (uint32_t)(min(n0 + 16 * j + l, g.N - 1) - n0) * (uint32_t)g.K * 2u + 16u * q;
-    const char *baseB = reinterpret_cast<const char *>(g.B + (int64_t)n0 * g.K);
-    const char *baseV = reinterpret_cast<const char *>(g.Av), *baseM = reinterpret_cast<const char *>(g.Am);
+    for (int j = 0; j < TN; ++j) ob[j] = (uint32_t)(min(n0 + 16 * j + l, N - 1) - n0) * (uint32_t)K * 2u + 16u * q;
+    const char *baseB = reinterpret_cast<const char *>(B + (int64_t)n0 * K);
+    const char *baseV = reinterpret_cast<const char *>(Av), *baseM = reinterpret_cast<const char *>(Am);
 
     struct Frag { uint4 a[TM]; uint32_t ix[TM]; Two b[TN]; };
     auto load = [&](Frag &f, int c) {
-        const char *pv = baseV + (int64_t)c * g.M * 64, *pm = baseM + (int64_t)c * g.M * 8, *pb = baseB + (int64_t)c * 128;
+        const char *pv = baseV + (int64_t)c * M * 64, *pm = baseM + (int64_t)c * M * 8, *pb = baseB + (int64_t)c * 128;
 #pragma unroll
         for (int i = 0; i < TM; ++i) f.a[i] = *reinterpret_cast<const uint4 *>(pv + oa[i]);
 #pragma unroll
@@ -106,7 +101,7 @@ __global__ __launch_bounds__(64 * KS) void spmm_slice_kernel(const NtArgs g)
 #pragma unroll
             for (int j = 0; j < TN; ++j) acc[i][j] = mma<T>(f.a[i], f.b[j], acc[i][j], f.ix[i]);
     };
-    const int nk = g.K / 64, steps = ks < nk ? (nk - ks + KS - 1) / KS : 0;
+    const int nk = K / 64, steps = ks < nk ? (nk - ks + KS - 1) / KS : 0;
     Frag f[D];
 #pragma unroll
     for (int d = 0; d < D; ++d)
@@ -140,22 +135,22 @@ __global__ __launch_bounds__(64 * KS) void spmm_slice_kernel(const NtArgs g)
     // four features of one token per item; what the epilogue reads from memory is fetched ahead of the barrier
     using Num = s24_num<T>;
     constexpr int QUADS = FM / 4, ITEMS = TWN * QUADS, PER = (ITEMS + THREADS - 1) / THREADS;
-    const int limit = EPI == S24_SLICE_GLU ? g.F : g.M;
+    const int limit = EPI == S24_SLICE_GLU ? F : M;
     uint2 old[PER], b0[PER], b1[PER];
     bool live[PER];
     int64_t at[PER];
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
         const int it = tid + p * THREADS, m = m0 + 4 * (it % QUADS), n = n0 + it / QUADS;
-        live[p] = it < ITEMS && n < g.N && m < limit;   // M and F are multiples of 16
-        at[p] = (int64_t)n * g.M + m;
+        live[p] = it < ITEMS && n < N && m < limit;   // M and F are multiples of 16
+        at[p] = (int64_t)n * M + m;
         old[p] = b0[p] = b1[p] = make_uint2(0, 0);
         if (live[p]) {
-            if (ACCUM) old[p] = *reinterpret_cast<const uint2 *>(g.Out + at[p]);
-            if (EPI == S24_SLICE_ACT_BWD) old[p] = *reinterpret_cast<const uint2 *>(g.Z + at[p]);
-            if (!ACCUM && EPI != S24_SLICE_ACT_BWD && g.bias != nullptr) {
-                b0[p] = *reinterpret_cast<const uint2 *>(g.bias + m);
-                if (EPI == S24_SLICE_GLU) b1[p] = *reinterpret_cast<const uint2 *>(g.bias + g.F + m);
+            if (ACCUM) old[p] = *reinterpret_cast<const uint2 *>(Out + at[p]);
+            if (EPI == S24_SLICE_ACT_BWD) old[p] = *reinterpret_cast<const uint2 *>(Z + at[p]);
+            if (!ACCUM && EPI != S24_SLICE_ACT_BWD && bias != nullptr) {
+                b0[p] = *reinterpret_cast<const uint2 *>(bias + m);
+                if (EPI == S24_SLICE_GLU) b1[p] = *reinterpret_cast<const uint2 *>(bias + F + m);
             }
         }
     }
@@ -177,9 +172,9 @@ __global__ __launch_bounds__(64 * KS) void spmm_slice_kernel(const NtArgs g)
             return v;
         };
         auto packed = [&](float4 v) { return make_uint2(Num::pack2(v.x, v.y), Num::pack2(v.z, v.w)); };
-        const bool biased = !ACCUM && EPI != S24_SLICE_ACT_BWD && g.bias != nullptr;
+        const bool biased = !ACCUM && EPI != S24_SLICE_ACT_BWD && bias != nullptr;
         const uint2 z = packed(total(src, ACCUM ? old[p] : b0[p], ACCUM || biased));
-        uint16_t *out = g.Out + at[p];
+        uint16_t *out = Out + at[p];
         if constexpr (EPI == S24_SLICE_ACT_BWD) {
             *reinterpret_cast<uint2 *>(out) =
                 make_uint2(Num::pack2(Num::lo(z.x) * s24_act_slope<ACT>(Num::lo(old[p].x)), Num::hi(z.x) * s24_act_slope<ACT>(Num::hi(old[p].x))),
@@ -187,14 +182,14 @@ __global__ __launch_bounds__(64 * KS) void spmm_slice_kernel(const NtArgs g)
         } else {
             *reinterpret_cast<uint2 *>(out) = z;
             if constexpr (EPI == S24_SLICE_ACT)
-                *reinterpret_cast<uint2 *>(g.H + at[p]) =
+                *reinterpret_cast<uint2 *>(H + at[p]) =
                     make_uint2(Num::pack2(s24_act_value<ACT>(Num::lo(z.x)), s24_act_value<ACT>(Num::hi(z.x))),
                                Num::pack2(s24_act_value<ACT>(Num::lo(z.y)), s24_act_value<ACT>(Num::hi(z.y))));
             if constexpr (EPI == S24_SLICE_GLU) {
                 const uint2 u = packed(total(src + FM, b1[p], biased));
-                *reinterpret_cast<uint2 *>(out + g.F) = u;
+                *reinterpret_cast<uint2 *>(out + F) = u;
                 const int64_t n = n0 + it / QUADS, m = m0 + 4 * (it % QUADS);
-                *reinterpret_cast<uint2 *>(g.H + n * g.F + m) =
+                *reinterpret_cast<uint2 *>(H + n * F + m) =
                     make_uint2(Num::pack2(s24_glu<ACT>(Num::lo(z.x), Num::lo(u.x)), s24_glu<ACT>(Num::hi(z.x), Num::hi(u.x))),
                                Num::pack2(s24_glu<ACT>(Num::lo(z.y), Num::lo(u.y)), s24_glu<ACT>(Num::hi(z.y), Num::hi(u.y))));
             }
@@ -208,8 +203,8 @@ void launch(const S24SliceNt &g, hipStream_t st)
     constexpr int FM = EPI == S24_SLICE_GLU ? 8 * TM : 16 * TM;
     const int64_t F = g.M / 2, feats = EPI == S24_SLICE_GLU ? F : g.M;
     const int tiles_m = (int)((feats + FM - 1) / FM), tiles_n = (int)((g.N + 16 * TN - 1) / (16 * TN)), tiles = tiles_m * tiles_n;
-    const NtArgs a{g.B, g.Av, g.Am, g.Out, g.H, g.Z, g.bias, (int)g.N, (int)g.K, (int)g.M, (int)F, tiles_n, tiles};
-    hipLaunchKernelGGL((spmm_slice_kernel<T, ACCUM, EPI, ACT, TM, TN>), dim3(((tiles + 7) / 8) * 8), dim3(64 * KS), 0, st, a);
+    hipLaunchKernelGGL((spmm_slice_kernel<T, ACCUM, EPI, ACT, TM, TN>), dim3(((tiles + 7) / 8) * 8), dim3(64 * KS), 0, st, g.B, g.Av, g.Am, (int)g.N,
+                       (int)g.K, (int)g.M, (int)F, tiles_n, tiles, g.Out, g.H, g.Z, g.bias);
 }
 
 template <typename T, int TM, int TN> int launch_epilogue(const S24SliceNt &g, hipStream_t st)
