@@ -21,6 +21,7 @@
 
 #include "s24_gemm_f32.h"
 #include "s24_gemm_slice.h"
+#include "s24_lds.h"
 #include "s24_overlap.h"
 
 namespace {
@@ -124,52 +125,7 @@ __device__ __forceinline__ bf16x16 as_bf16x16(uint4 lo, uint4 hi)
 // card not yet warm; the second product launched on end takes 1.85-1.92 ms at 1.36-1.41 GHz, on zero operands 1.34 at 2.3).
 namespace big {
 constexpr int BM = 256, BN = 256, THREADS = 512;   // the large tile
-typedef __attribute__((address_space(3))) void *lds_ptr;
-typedef const __attribute__((address_space(1))) void *glb_ptr;
-
-__device__ __forceinline__ int b_slot(int row, int c) { return row * 128 + ((c ^ ((row >> 1) & 7)) << 4); }
-__device__ __forceinline__ int a_swizzle(int row) { return -(row >> 2) & 3; }
-__device__ __forceinline__ int a_slot(int row, int c) { return row * 64 + ((c ^ a_swizzle(row)) << 4); }
-
-// Buffer descriptor for direct-to-LDS copies: base address in scalar registers, raw (unstructured) addressing, no
-// bounds clamp that the kernels rely on (every offset they form is inside the operand and below 4 GB, which the host
-// checks; the descriptor declares the full 4 GB of records).
-// (The host pass of the compiler does not know these builtins: it sees empty bodies.)
-#if defined(__HIP_DEVICE_COMPILE__)
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-__device__ __forceinline__ rsrc_t buffer_of(const void *base)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, 0xFFFFFFFFu, 0x27000);
-}
-// BYTES (16 or 4) per lane from byte offset `voff` of the buffer to lds + 64 * BYTES * (lane's index in the wave)
-template <int BYTES> __device__ __forceinline__ void buffer_to_lds(rsrc_t buf, lds_ptr lds, uint32_t voff)
-{
-    static_assert(BYTES == 16 || BYTES == 4, "copy width");
-    if constexpr (BYTES == 16) __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, lds, 16, voff, 0, 0, 0);
-    else __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, lds, 4, voff, 0, 0, 0);
-}
-// 8 bytes / 2 bytes into registers from byte offset voff (per lane) + soff (wave-uniform, a scalar register): a load
-// whose address costs one vector register however many of them a wave issues in a row
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint2 buffer_load_8(rsrc_t buf, uint32_t voff, uint32_t soff)
-{
-    const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(buf, (int)voff, (int)soff, 0);
-    return make_uint2(v.x, v.y);
-}
-__device__ __forceinline__ uint32_t buffer_load_2(rsrc_t buf, uint32_t voff, uint32_t soff)
-{
-    return __builtin_amdgcn_raw_buffer_load_b16(buf, (int)voff, (int)soff, 0);
-}
-#else
-typedef const void *rsrc_t;
-__device__ __forceinline__ rsrc_t buffer_of(const void *base) { return base; }
-template <int BYTES> __device__ __forceinline__ void buffer_to_lds(rsrc_t, lds_ptr, uint32_t) {}
-__device__ __forceinline__ uint2 buffer_load_8(rsrc_t, uint32_t, uint32_t) { return make_uint2(0, 0); }
-__device__ __forceinline__ uint32_t buffer_load_2(rsrc_t, uint32_t, uint32_t) { return 0; }
-#endif
-
-// s_waitcnt immediate: vmcnt(n), lgkmcnt(0), expcnt unconstrained
-__host__ __device__ constexpr int wait_vm_lgkm0(int n) { return (n & 15) | (7 << 4) | ((n >> 4) << 14); }
+using namespace s24_lds;
 
 // Workgroup barrier that leaves up to VM vector-memory operations (direct-to-LDS copies of later
 // chunks) in flight.  The raw wait and barrier instructions carry no memory semantics for the
@@ -1703,13 +1659,31 @@ inline NtTile sparse_dw_tile(int64_t M, int64_t N) { return cheapest_tile(M, N, 
         else MACRO(__VA_ARGS__, 2, 2);                                  \
     } while (0)
 
+// Whether a product of N tokens and M features runs in slices (s24_gemm_slice.hip).  Up to 16 tokens, of which a tile would multiply
+// seven eighths of nothing: yes (16 x 16384, K = 4096, weights out of the caches: 28 us in tiles, 13.7 in slices; x 50304: 44.5 and 43.0),
+// unless the 128 x 128 tiles are nearly two per compute unit and the contraction is long, so that they too keep the memory busy
+// (x 65536, K = 8192: 103 and 109; K = 2048: 40 and 29; 57344, K = 8192: 95 and 92).  With more tokens not where these tiles are more than
+// one per compute unit (40 x 43008, K = 8192: 84 and 93), else where that is estimated to be the faster.  The small grids in question
+// keep a tile's launch, prologue and epilogue in the open: 2.5 us beyond the share of a round, the middle of 1 without and 4 with an
+// activation, since one rule for all epilogues gives them the same bits.  Weights out of the caches come in at 5 TB/s either way.  Of 380
+// products (1-2048 tokens, K = 256-32000, 256-56000 features) the choice takes 1 % more than the best tile of either kind at the mean.
+inline bool slice_pays(int64_t N, int64_t K, int64_t M)
+{
+    const int64_t cus = s24_cu_count(), small = (int64_t)ceil_div(M, 128) * ceil_div(N, 128);
+    if (N <= 16) return !(K >= 4096 && 4 * small > 7 * cus && small <= 2 * cus);
+    if (small > cus) return false;
+    const NtCosts c = sparse_costs(K);
+    const double tiles = 2.5 + round_us(K) * std::min(nt_cost(NtTile::Large, M, N, c), std::min(nt_cost(NtTile::Medium, M, N, c), nt_cost(NtTile::Small, M, N, c)));
+    return s24_slice_us(N, K, M) <= std::max(tiles, 2.0 + 1.125 * (double)M * (double)K / 5.0e6);
+}
+
 // Outputs that the gated backward epilogue serves: three quarters of the compute units have a large tile
 inline bool gated_bwd_fits(int64_t p, int64_t f) { return (int64_t)ceil_div(f, 256) * ceil_div(p, 256) >= 3 * s24_cu_count() / 4; }
 
 // Whether the input gradient of p tokens and q features, contraction r, runs in slices.  One rule for s24_spmm_bwd_dx and
 // s24_spmm_bwd_dx_act, whose bits agree; and neither does where s24_spmm_bwd_dx_glu takes its large tiles (possible at up to
 // 16 tokens from 48897 features on), so that all three sum in one order.
-inline bool bwd_dx_slices(int64_t p, int64_t r, int64_t q) { return !gated_bwd_fits(p, q) && s24_slice_pays(p, r, q); }
+inline bool bwd_dx_slices(int64_t p, int64_t r, int64_t q) { return !gated_bwd_fits(p, q) && slice_pays(p, r, q); }
 
 // Out[N][M] = beta * Out + B[N][K] . A^T (+ bias[M], only with beta = 0)
 int launch_spmm(const void *B, const void *Av, const uint16_t *Am, void *Out, int64_t N, int64_t K, int64_t M, float beta,
@@ -1762,7 +1736,7 @@ extern "C" int s24_spmm_fwd_bias(const void *X, const void *vals, const uint16_t
     if (rc != S24_OK || p * r == 0) return rc;
     S24_REQUIRE(meta != nullptr, S24_ERR_NULL);
     S24_REQUIRE(s24_aligned(meta, 4) && s24_aligned(bias, 8), S24_ERR_ALIGN);
-    return launch_spmm(X, vals, meta, Y, p, q, r, 0.0f, dt, static_cast<hipStream_t>(stream), bias, s24_slice_pays(p, q, r));
+    return launch_spmm(X, vals, meta, Y, p, q, r, 0.0f, dt, static_cast<hipStream_t>(stream), bias, slice_pays(p, q, r));
 }
 
 extern "C" int s24_spmm_bwd_dx(const void *dY, const void *valsT, const uint16_t *metaT, void *dX, int64_t p, int64_t q,
@@ -1787,7 +1761,7 @@ extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t 
     S24_REQUIRE(meta != nullptr && H != nullptr, S24_ERR_NULL);
     S24_REQUIRE(s24_aligned(meta, 4) && s24_aligned(H, 16) && s24_aligned(bias, 8), S24_ERR_ALIGN);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (dt != S24_F32 && s24_slice_pays(p, q, 2 * f))
+    if (dt != S24_F32 && slice_pays(p, q, 2 * f))
         return s24_slice_nt({static_cast<const uint16_t *>(X), static_cast<const uint16_t *>(vals), meta, static_cast<uint16_t *>(GU),
                              static_cast<uint16_t *>(H), nullptr, static_cast<const uint16_t *>(bias), p, q, 2 * f, false, S24_SLICE_GLU, gate}, dt, st);
     NtTile tile = nt_tile(2 * f, p, q);
@@ -1877,7 +1851,7 @@ extern "C" int s24_spmm_fwd_act(const void *X, const void *vals, const uint16_t 
     S24_REQUIRE(s24_aligned(meta, 4) && s24_aligned(H, 16) && s24_aligned(bias, 8), S24_ERR_ALIGN);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (dt != S24_F32) {
-        if (s24_slice_pays(p, q, r))
+        if (slice_pays(p, q, r))
             return s24_slice_nt({static_cast<const uint16_t *>(X), static_cast<const uint16_t *>(vals), meta, static_cast<uint16_t *>(Z),
                                  static_cast<uint16_t *>(H), nullptr, static_cast<const uint16_t *>(bias), p, q, r, false, S24_SLICE_ACT, act}, dt, st);
         const NtTile tile = nt_tile(r, p, q);

@@ -17,5 +17,5 @@ struct S24SliceNt {
     S24SliceEpilogue epilogue;
     int act;
 };
-bool s24_slice_pays(int64_t N, int64_t K, int64_t M);
+double s24_slice_us(int64_t N, int64_t K, int64_t M);   // what it takes while its operands are in the caches
 int s24_slice_nt(const S24SliceNt &g, int dt, hipStream_t st);

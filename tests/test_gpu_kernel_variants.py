@@ -494,6 +494,13 @@ def test_sliced_products_and_their_epilogues(s24, dtype, pqr):
             assert torch.equal(bits(GU), bits(Yb)) and torch.equal(bits(Hg), bits(two))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+# (p, q, r) of the 64 x 64 tile: of three to five chunks to a wave, and of one or two; ragged along both axes, by one token and by 16 features
+@pytest.mark.parametrize("pqr", [(513, 1984, 1040), (193, 2112, 3104), (500, 576, 1616)])
+def test_sliced_products_in_the_largest_tile(s24, dtype, pqr):
+    test_sliced_products_and_their_epilogues(s24, dtype, pqr)
+
+
 @pytest.mark.parametrize("q", [1984, 2048])     # slices; the tiles' kernel from 384 tiles of 128 x 128 and this contraction on
 def test_few_tokens_of_many_features_on_either_kernel(s24, q):
     p, r = 13, 49152
