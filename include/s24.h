@@ -228,6 +228,13 @@ typedef struct {
 } s24_dw_problem;
 int s24_dense_dw_batch(const s24_dw_problem *problems, int count, float beta, s24_dtype dt, void *stream);
 
+/* The last input gradient of a layer and its weight gradients: the same result, bit for bit, as s24_spmm_bwd_dx(dY, valsT, metaT, dX,
+ * p, q, r, 0, ...) followed by s24_dense_dw_batch(problems, count, 0, ...), neither of which needs the other's.  Small ones
+ * that leave the chip mostly idle run in one launch, unless one of them writes what another one reads or writes; all others
+ * in turn.  Everything is validated before the first launch. */
+int s24_spmm_bwd_dx_dw(const void *dY, const void *valsT, const uint16_t *metaT, void *dX, int64_t p, int64_t q, int64_t r,
+                       const s24_dw_problem *problems, int count, s24_dtype dt, void *stream);
+
 /* Unbiased 2:4 pruning of the output gradient (Eq. 6: S_z = MVUE) into the compressed operand of the sparse
  * weight-gradient GEMM (Eq. 4).  Of every four consecutive tokens of one feature two are kept, element j with
  * probability pi_j proportional to |dY_j| (capped at one) and stored as dY_j / pi_j; the pair is drawn by

@@ -44,6 +44,7 @@ _SIGNATURES = {
     "s24_dense_dw": (_int, [_vp, _vp, _vp, _i64, _i64, _i64, _f32, _int, _vp]),
     "s24_dense_dw_decay": (_int, [_vp, _vp, _vp, _vp, _int, _vp, _f32, _i64, _i64, _i64, _f32, _int, _vp]),
     "s24_dense_dw_batch": (_int, [_vp, _int, _f32, _int, _vp]),
+    "s24_spmm_bwd_dx_dw": (_int, [_vp, _vp, _vp, _vp, _i64, _i64, _i64, _vp, _int, _int, _vp]),
     "s24_mvue24": (_int, [_vp, _int, _i64, _i64, _i64, C.c_uint32, _vp, _vp, _vp]),
     "s24_spmm_dw": (_int, [_vp, _vp, _vp, _vp, _vp, _int, _vp, _f32, _i64, _i64, _i64, _f32, _int, _vp]),
     "s24_dense_gemm": (_int, [_vp, _vp, _vp, _i64, _i64, _i64, _int, _vp]),
@@ -332,16 +333,31 @@ class _DwProblem(C.Structure):
                 ("lam", _f32)]
 
 
-def dense_dw_batch(problems, beta=0.0):
-    """problems: up to four tuples (dY, X, dW, W, mask, lam) with W and mask None for no decay term; the weight
-    gradients of all of them in one pass (same bits as dense_dw_decay / dense_dw on each)."""
+def _dw_problems(where, problems):
     arr = (_DwProblem * len(problems))()
     for k, (dY, X, dW, W, mask, lam) in enumerate(problems):
         p, r = dY.shape
-        _dense("s24_dense_dw_batch", "dY X dW W mask", dY, X, dW, W, mask)
+        _dense(where, "dY X dW W mask", dY, X, dW, W, mask)
         arr[k] = _DwProblem(_ptr(dY), _ptr(X), _ptr(dW), _ptr(W), _ptr(mask), p, X.shape[1], r, lam)
+    return arr
+
+
+def dense_dw_batch(problems, beta=0.0):
+    """problems: up to four tuples (dY, X, dW, W, mask, lam) with W and mask None for no decay term; the weight
+    gradients of all of them in one pass (same bits as dense_dw_decay / dense_dw on each)."""
+    arr = _dw_problems("s24_dense_dw_batch", problems)
     _check(lib().s24_dense_dw_batch(C.cast(arr, C.c_void_p), len(problems), beta, _dt(problems[0][0]), _stream()),
            "s24_dense_dw_batch")
+
+
+def spmm_bwd_dx_dw(dY, valsT, metaT, dX, problems):
+    """spmm_bwd_dx(dY, valsT, metaT, dX) and dense_dw_batch(problems), which do not depend on each other: one launch where both are small."""
+    _dense("s24_spmm_bwd_dx_dw", "dY valsT metaT dX", dY, valsT, metaT, dX)
+    p, r = dY.shape
+    arr = _dw_problems("s24_spmm_bwd_dx_dw", problems)
+    _check(lib().s24_spmm_bwd_dx_dw(_ptr(dY), _ptr(valsT), _ptr(metaT), _ptr(dX), p, valsT.shape[1], r, C.cast(arr, C.c_void_p), len(problems), _dt(dY),
+                                    _stream()), "s24_spmm_bwd_dx_dw")
+    return dX
 
 
 def mvue24(dY, seed, vals, meta):

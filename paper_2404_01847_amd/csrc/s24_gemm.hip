@@ -2122,17 +2122,13 @@ extern "C" int s24_dense_dw_decay(const void *dY, const void *X, float *dW, cons
     return run_dense_dw(dY, X, dW, p, q, r, beta, dt, W, wdt, mask, lambda, static_cast<hipStream_t>(stream));
 }
 
-extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, float beta, s24_dtype dt, void *stream)
+namespace {
+int check_dw_batch(const s24_dw_problem *problems, int count, s24_dtype dt)
 {
     S24_REQUIRE(s24_valid_dtype(dt), S24_ERR_DTYPE);
     S24_REQUIRE(count >= 0 && count <= dmatn::kMaxBatch, S24_ERR_SHAPE);
-    S24_REQUIRE(beta == 0.0f || beta == 1.0f, S24_ERR_UNSUPPORTED);
     if (count == 0) return S24_OK;
     S24_REQUIRE(problems != nullptr, S24_ERR_NULL);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    // every problem is checked before anything is launched
-    bool shared_grid = dt != S24_F32;
-    int64_t total = 0;
     for (int i = 0; i < count; ++i) {
         const s24_dw_problem &pr = problems[i];
         S24_REQUIRE(pr.q % 16 == 0 && pr.r % 16 == 0, S24_ERR_SHAPE);
@@ -2142,6 +2138,23 @@ extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, flo
             S24_REQUIRE(pr.mask != nullptr, S24_ERR_NULL);
             S24_REQUIRE(s24_aligned(pr.W, 16) && s24_aligned(pr.mask, 4), S24_ERR_ALIGN);
         }
+    }
+    return S24_OK;
+}
+}  // namespace
+
+extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, float beta, s24_dtype dt, void *stream)
+{
+    S24_REQUIRE(s24_valid_dtype(dt), S24_ERR_DTYPE);
+    S24_REQUIRE(count >= 0 && count <= dmatn::kMaxBatch, S24_ERR_SHAPE);
+    S24_REQUIRE(beta == 0.0f || beta == 1.0f, S24_ERR_UNSUPPORTED);
+    const int checked = check_dw_batch(problems, count, dt);   // every problem is checked before anything is launched
+    if (checked != S24_OK || count == 0) return checked;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    bool shared_grid = dt != S24_F32;
+    int64_t total = 0;
+    for (int i = 0; i < count; ++i) {
+        const s24_dw_problem &pr = problems[i];
         const int64_t tiles = (int64_t)ceil_div(pr.r, 256) * ceil_div(pr.q, 256);
         // one grid for all of them: 16-bit data, tokens to contract, every problem large enough for the large tile,
         // and the decay term on all of them or on none
@@ -2236,6 +2249,38 @@ extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, flo
         launch_dw_batch(strip, DwTile::Small, accum, decay, dt, st);
     }
     return s24_launch_status();
+}
+
+extern "C" int s24_spmm_bwd_dx_dw(const void *dY, const void *valsT, const uint16_t *metaT, void *dX, int64_t p, int64_t q, int64_t r,
+                                  const s24_dw_problem *problems, int count, s24_dtype dt, void *stream)
+{
+    S24_REQUIRE(r % 64 == 0 && q % 16 == 0 && r > 0, S24_ERR_SHAPE);
+    int rc = check_gemm(dY, valsT, dX, p, q, r, dt, p * q);
+    if (rc != S24_OK) return rc;
+    if (p * q != 0) {
+        S24_REQUIRE(metaT != nullptr, S24_ERR_NULL);
+        S24_REQUIRE(s24_aligned(metaT, 4), S24_ERR_ALIGN);
+    }
+    rc = check_dw_batch(problems, count, dt);
+    if (rc != S24_OK) return rc;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    bool together = p * q != 0 && count > 0;
+    for (int i = 0; i < count; ++i)
+        together = together && problems[i].p > 0 && problems[i].q * problems[i].r != 0 && (problems[i].W != nullptr) == (problems[0].W != nullptr);
+    const int64_t esize = (int64_t)s24_elem_size(dt);
+    together = together && !s24_dw_problems_overlap(problems, count, esize) && !s24_dx_meets_dw(dY, valsT, metaT, dX, p, q, r, problems, count, esize);
+    if (together && dt == S24_F32) {
+        S24F32TnProblem f[dmatn::kMaxBatch];
+        for (int i = 0; i < count; ++i) {
+            const s24_dw_problem &pr = problems[i];
+            f[i] = {static_cast<const float *>(pr.dY), static_cast<const float *>(pr.X), static_cast<const float *>(pr.W), nullptr, pr.mask, pr.dW, pr.p, pr.r, pr.q, pr.lambda};
+        }
+        if (s24_f32_nt_tn({static_cast<const float *>(dY), static_cast<const float *>(valsT), metaT, static_cast<float *>(dX), nullptr, nullptr, p, r, q, false,
+                           S24_F32_PLAIN, 0}, f, count, st, rc))
+            return rc;
+    }
+    rc = s24_spmm_bwd_dx(dY, valsT, metaT, dX, p, q, r, 0.0f, dt, stream);
+    return rc != S24_OK ? rc : s24_dense_dw_batch(problems, count, 0.0f, dt, stream);
 }
 
 extern "C" int s24_spmm_dw(const void *vals, const uint16_t *meta, const void *X, float *dW, const void *W, s24_dtype wdt,

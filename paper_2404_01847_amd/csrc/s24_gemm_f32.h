@@ -30,3 +30,7 @@ struct S24F32TnProblem {
     float lambda;
 };
 int s24_f32_tn(const S24F32TnProblem *pr, int count, bool accum, hipStream_t st);
+
+// Input gradient (sparse, overwritten, no epilogue) and weight gradients (dense dY, overwritten) in one launch, where that pays: false if it does
+// not, and nothing was launched.  None of them may read or write what another one writes.
+bool s24_f32_nt_tn(const S24F32Nt &g, const S24F32TnProblem *pr, int count, hipStream_t st, int &status);

@@ -9,6 +9,8 @@
 // used by one wave of the workgroup only: LDS staging would buy nothing), and the slices are summed in LDS in a
 // fixed order.  A lane takes its k values as runs of eight of one row (two 16-byte loads), the same runs for both
 // operands; which k an instruction multiplies is free as long as both sides agree.
+#include <type_traits>
+
 #include "s24_gemm_f32.h"
 
 namespace {
@@ -56,18 +58,18 @@ template <int KS> __device__ __forceinline__ float4 slice_sum(const float *p, in
 
 // ------------------------------------------------------------------ NT
 // SPARSE: A compressed.  EPI / ACT: epilogue.  GLU needs T = 2: a tile takes 32 gate rows and the 32 up rows of the same
-// features, F of either (else F = M).  The arguments are one by one and in the order in which they are needed: see FLAGS in build.py.
+// features, F of either (else F = M).  s_red: lds_floats(T, KS) of LDS.
+constexpr int lds_floats(int T, int KS) { return KS * 32 * T * (32 * T + 4); }
 template <bool SPARSE, bool ACCUM, int EPI, int ACT, int T, int KS>
-__global__ __launch_bounds__(64 * KS) void f32_nt_kernel(const float *B, const float *Av, const uint16_t *Am, int N, int K, int M, int F, int tiles_m,
-                                                         float *Out, float *H, const float *bias)
+__device__ __forceinline__ void f32_nt_tile(float *s_red, int tile, const float *B, const float *Av, const uint16_t *Am, int N, int K, int M, int F,
+                                            int tiles_m, float *Out, float *H, const float *bias)
 {
     static_assert(EPI != S24_F32_GLU || T == 2, "the gated tile pairs two row blocks");
     constexpr int TW = 32 * T, PITCH = TW + 4, SLICE = TW * PITCH, THREADS = 64 * KS;
-    __shared__ __attribute__((aligned(16))) float s_red[KS * SLICE];
     const int tid = threadIdx.x, lane = tid & 63;
     const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, l = lane & 31;
-    const int tm = (int)blockIdx.x % tiles_m, tn = (int)blockIdx.x / tiles_m;
+    const int tm = tile % tiles_m, tn = tile / tiles_m;
     constexpr int FM = EPI == S24_F32_GLU ? 32 : TW;   // features of the (gated) output per tile
     const int m0 = tm * FM, n0 = tn * TW;
 
@@ -188,6 +190,15 @@ __global__ __launch_bounds__(64 * KS) void f32_nt_kernel(const float *B, const f
     }
 }
 
+// The arguments are one by one and in the order in which they are needed: see FLAGS in build.py.
+template <bool SPARSE, bool ACCUM, int EPI, int ACT, int T, int KS>
+__global__ __launch_bounds__(64 * KS) void f32_nt_kernel(const float *B, const float *Av, const uint16_t *Am, int N, int K, int M, int F, int tiles_m,
+                                                         float *Out, float *H, const float *bias)
+{
+    __shared__ __attribute__((aligned(16))) float s_red[lds_floats(T, KS)];
+    f32_nt_tile<SPARSE, ACCUM, EPI, ACT, T, KS>(s_red, (int)blockIdx.x, B, Av, Am, N, K, M, F, tiles_m, Out, H, bias);
+}
+
 // ------------------------------------------------------------------ TN (weight gradients)
 // Both operands are token-major: a lane reads T consecutive columns of one token (the columns of tile block i are
 // T*(l%32) + i), lane half h takes every second token.
@@ -211,19 +222,18 @@ template <int T> struct Run { float v[T]; };
 
 // D: batches of eight token pairs in flight (see s24_f32_tn)
 template <bool SPARSE, bool ACCUM, int T, int KS, int D>
-__global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
+__device__ __forceinline__ void f32_tn_tile(float *s_red, int tile, const TnArgs &args)
 {
     constexpr int TW = 32 * T, PITCH = TW + 4, SLICE = TW * PITCH, THREADS = 64 * KS;
-    __shared__ __attribute__((aligned(16))) float s_red[KS * SLICE];
     const int tid = threadIdx.x, lane = tid & 63;
     const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, l = lane & 31;
     int which = 0;
 #pragma unroll
     for (int i = 1; i < kMaxTn; ++i)
-        if ((int)blockIdx.x >= args.w[i].first) which = i;
+        if (tile >= args.w[i].first) which = i;
     const TnWindow &g = args.w[which];
-    const int t = (int)blockIdx.x - g.first;
+    const int t = tile - g.first;
     const int m0 = (t % g.tiles_m) * TW, n0 = (t / g.tiles_m) * TW;
     const int M = g.M, N = g.N;
     f32x16 acc[T][T];
@@ -365,6 +375,25 @@ __global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
     }
 }
 
+template <bool SPARSE, bool ACCUM, int T, int KS, int D>
+__global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
+{
+    __shared__ __attribute__((aligned(16))) float s_red[lds_floats(T, KS)];
+    f32_tn_tile<SPARSE, ACCUM, T, KS, D>(s_red, (int)blockIdx.x, args);
+}
+
+// An input gradient in eight slices and weight gradients that do not depend on it in one launch: neither fills the chip, and each is a
+// launch and a few trips to memory that the other one can hide.  The input gradient's tiles walk the longer sums and go first.
+// 512 tokens, 256 x 1024 (10.2 and 12.5 us under the tracer): 54.6 -> 47.2 us a step.
+template <int D>
+__global__ __launch_bounds__(512) void f32_nt_tn_kernel(const float *B, const float *Av, const uint16_t *Am, int nt_tiles, int N, int K, int M, int tiles_m,
+                                                        float *Out, const TnArgs args)
+{
+    __shared__ __attribute__((aligned(16))) float s_red[lds_floats(1, 8)];
+    if ((int)blockIdx.x < nt_tiles) f32_nt_tile<true, false, S24_F32_PLAIN, 0, 1, 8>(s_red, (int)blockIdx.x, B, Av, Am, N, K, M, M, tiles_m, Out, nullptr, nullptr);
+    else f32_tn_tile<false, false, 1, 8, D>(s_red, (int)blockIdx.x - nt_tiles, args);
+}
+
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 template <bool SPARSE, bool ACCUM, int EPI, int ACT, int T, int KS>
@@ -384,16 +413,16 @@ int launch_nt(const S24F32Nt &g, hipStream_t st)
 //   512 x 256 x 1024: 7.3 / 6.5 / 10.0 (109)      512 x 1024 x 256: 9.2 / 10.1 / 26.3 (114)
 //   333 x 1792 x 448: 13.4 / 15.3 / 45.4 (281)    1024 x 768 x 3072: 66 / 61 / 53 (2480)     2048 x 1024 x 4096: 228 / 199 / 168 (8608)
 // The 64-tile reads half the operand bytes per product, which only counts once its own grid fills the chip.
+inline bool nt_deep(int64_t N, int64_t K, int64_t M) { return K >= 512 && ceil_div(M, 32) * ceil_div(N, 32) <= s24_cu_count(); }   // few tiles, long sums: 8 slices
 template <bool SPARSE, bool ACCUM, int EPI, int ACT> int choose_nt(const S24F32Nt &g, hipStream_t st)
 {
-    const int64_t cus = s24_cu_count();
-    const bool deep = g.K >= 512 && ceil_div(g.M, 32) * ceil_div(g.N, 32) <= cus;   // few tiles, long sums: 8 slices
+    const bool deep = nt_deep(g.N, g.K, g.M);
     if constexpr (EPI == S24_F32_GLU) {
         if (deep) return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 8>(g, st);
         return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 4>(g, st);
     } else {
         if (deep) return launch_nt<SPARSE, ACCUM, EPI, ACT, 1, 8>(g, st);
-        if (ceil_div(g.M, 64) * ceil_div(g.N, 64) < 2 * cus) return launch_nt<SPARSE, ACCUM, EPI, ACT, 1, 4>(g, st);
+        if (ceil_div(g.M, 64) * ceil_div(g.N, 64) < 2 * s24_cu_count()) return launch_nt<SPARSE, ACCUM, EPI, ACT, 1, 4>(g, st);
         return launch_nt<SPARSE, ACCUM, EPI, ACT, 2, 4>(g, st);
     }
 }
@@ -427,34 +456,68 @@ int s24_f32_nt(const S24F32Nt &g, hipStream_t st)
 // (1000, 768 x 512: 18.7, 19.6, 20.7), and two are the fastest once they do not (1200: 25.6, 22.3, 25.2; 2048: 43.3, 32.1, 36.9).  Beyond
 // two workgroups the waves that more registers would displace hide more (1000, 1024 x 1024: 32.3, 37.5, 40.8).  The 64-tile has its two
 // waves per SIMD anyway and takes two (64, 4096 x 1024: 16.9, 17.1; 512: 67.1, 52.6).
-int s24_f32_tn(const S24F32TnProblem *pr, int count, bool accum, hipStream_t st)
+namespace {
+struct TnPlan {
+    TnArgs a;
+    int T, D;        // tile of 32 T; batches in flight
+    int64_t tiles;
+    bool whole;      // one wave per tile
+};
+TnPlan plan_tn(const S24F32TnProblem *pr, int count)
 {
     int64_t tiles[2] = {0, 0}, tokens = 0, bytes = 0;   // tokens: of the longest problem; bytes: of all operands
-    TnArgs a{};
+    TnPlan plan{};
     for (int T = 1; T <= 2; ++T)
         for (int i = 0; i < count; ++i) tiles[T - 1] += ceil_div(pr[i].M, 32 * T) * ceil_div(pr[i].N, 32 * T);
-    const int T = tiles[1] < 3 * s24_cu_count() ? 1 : 2;
-    S24_REQUIRE(tiles[T - 1] < (1ll << 31), S24_ERR_SHAPE);
-    int64_t first = 0;
-    bool few = true;
+    const int64_t cus = s24_cu_count();
+    const int T = plan.T = tiles[1] < 3 * cus ? 1 : 2;
+    plan.whole = true;
     for (int i = 0; i < kMaxTn; ++i) {
         if (i < count) {
-            few = few && pr[i].T <= kWholeTokens;
+            plan.whole = plan.whole && pr[i].T <= kWholeTokens;
             tokens = std::max(tokens, pr[i].T);
             bytes += pr[i].T * (pr[i].M + pr[i].N) * (int64_t)sizeof(float);
             const int64_t tm = ceil_div(pr[i].M, 32 * T);
-            a.w[i] = TnWindow{pr[i].A, pr[i].X, pr[i].Wt, pr[i].Am, pr[i].mask, pr[i].dW, (int)pr[i].T, (int)pr[i].M, (int)pr[i].N, (int)tm, (int)first, pr[i].lambda};
-            first += tm * ceil_div(pr[i].N, 32 * T);
+            plan.a.w[i] = TnWindow{pr[i].A, pr[i].X, pr[i].Wt, pr[i].Am, pr[i].mask, pr[i].dW, (int)pr[i].T, (int)pr[i].M, (int)pr[i].N, (int)tm, (int)plan.tiles, pr[i].lambda};
+            plan.tiles += tm * ceil_div(pr[i].N, 32 * T);
         } else {
-            a.w[i] = a.w[count - 1];
-            a.w[i].first = 0x7FFFFFFF;   // no tile of the grid
+            plan.a.w[i] = plan.a.w[count - 1];
+            plan.a.w[i].first = 0x7FFFFFFF;   // no tile of the grid
         }
     }
-    if (pr[0].Am != nullptr) return T == 1 ? launch_tn<true, 1, 8>(a, first, accum, st) : launch_tn<true, 2, 8>(a, first, accum, st);
-    if (few) return T == 1 ? launch_tn<false, 1, 1>(a, first, accum, st) : launch_tn<false, 2, 1>(a, first, accum, st);
-    const int64_t cus = s24_cu_count();
-    if (T == 2) return tokens < 128 ? launch_tn<false, 2, 8>(a, first, accum, st) : launch_tn<false, 2, 8, 2>(a, first, accum, st);
-    if (tokens < 128 || first > 2 * cus) return launch_tn<false, 1, 8>(a, first, accum, st);
-    if (first <= cus || tokens <= 512) return launch_tn<false, 1, 8, 4>(a, first, accum, st);
-    return bytes < 11 << 19 ? launch_tn<false, 1, 8>(a, first, accum, st) : launch_tn<false, 1, 8, 2>(a, first, accum, st);
+    if (T == 2) plan.D = tokens < 128 ? 1 : 2;
+    else if (tokens < 128 || plan.tiles > 2 * cus) plan.D = 1;
+    else if (plan.tiles <= cus || tokens <= 512) plan.D = 4;
+    else plan.D = bytes < 11 << 19 ? 1 : 2;
+    return plan;
+}
+}  // namespace
+
+int s24_f32_tn(const S24F32TnProblem *pr, int count, bool accum, hipStream_t st)
+{
+    TnPlan p = plan_tn(pr, count);
+    S24_REQUIRE(p.tiles < (1ll << 31), S24_ERR_SHAPE);
+    if (pr[0].Am != nullptr) return p.T == 1 ? launch_tn<true, 1, 8>(p.a, p.tiles, accum, st) : launch_tn<true, 2, 8>(p.a, p.tiles, accum, st);
+    if (p.whole) return p.T == 1 ? launch_tn<false, 1, 1>(p.a, p.tiles, accum, st) : launch_tn<false, 2, 1>(p.a, p.tiles, accum, st);
+    if (p.T == 2) return p.D == 1 ? launch_tn<false, 2, 8>(p.a, p.tiles, accum, st) : launch_tn<false, 2, 8, 2>(p.a, p.tiles, accum, st);
+    if (p.D == 1) return launch_tn<false, 1, 8>(p.a, p.tiles, accum, st);
+    return p.D == 2 ? launch_tn<false, 1, 8, 2>(p.a, p.tiles, accum, st) : launch_tn<false, 1, 8, 4>(p.a, p.tiles, accum, st);
+}
+
+// Together where the input gradient has a tile for at most every compute unit and the weight gradients take the 32-tile in eight slices
+bool s24_f32_nt_tn(const S24F32Nt &g, const S24F32TnProblem *pr, int count, hipStream_t st, int &status)
+{
+    if (!nt_deep(g.N, g.K, g.M)) return false;
+    const TnPlan p = plan_tn(pr, count);
+    if (p.whole || p.T != 1 || p.tiles >= 1ll << 30) return false;
+    const int64_t tiles_m = ceil_div(g.M, 32), tiles = tiles_m * ceil_div(g.N, 32);
+    auto launch = [&](auto d) {
+        hipLaunchKernelGGL((f32_nt_tn_kernel<decltype(d)::value>), dim3((unsigned)(tiles + p.tiles)), dim3(512), 0, st, g.B, g.Av, g.Am, (int)tiles, (int)g.N, (int)g.K,
+                           (int)g.M, (int)tiles_m, g.Out, p.a);
+    };
+    if (p.D == 1) launch(std::integral_constant<int, 1>());
+    else if (p.D == 2) launch(std::integral_constant<int, 2>());
+    else launch(std::integral_constant<int, 4>());
+    status = s24_launch_status();
+    return true;
 }

@@ -175,6 +175,18 @@ class SparseFFN:
         else:
             self._k('dense_dw', s24.dense_dw, dYw, Xw, weight.grad)
 
+    def _dx_and_dw(self, dYw, name, Xw):
+        """self.dX = dYw (M.*W), and the gradient of that weight with all that are still to be computed: in one call, unless each
+        kernel is to be timed or the gradients come one by one."""
+        weight = self.w[name]
+        if self.batch_dw and not self.mvue and self.timings is None:
+            self._dw(dYw, Xw, weight)
+            s24.spmm_bwd_dx_dw(dYw, weight.valsT, weight.metaT, self.dX, self._pending_dw)
+            self._pending_dw = []
+        else:
+            self._k('spmm_bwd_dx', s24.spmm_bwd_dx, dYw, weight.valsT, weight.metaT, self.dX)
+            self._dw(dYw, Xw, weight)
+
     def _flush_dw(self):
         if self._pending_dw:
             self._k('dense_dw', s24.dense_dw_batch, self._pending_dw)
@@ -202,8 +214,7 @@ class SparseFFN:
                 self._k('spmm_bwd_dx', s24.spmm_bwd_dx, dY, w["Wd"].valsT, w["Wd"].metaT, self.dH)
                 self._k('swiglu_bwd', s24.glu_bwd, self.dH, self.GU, self.dGU, self.gate)
             self._dw(dY, self.H, w["Wd"])
-            self._k('spmm_bwd_dx', s24.spmm_bwd_dx, self.dGU, w["Wgu"].valsT, w["Wgu"].metaT, self.dX)
-            self._dw(self.dGU, X, w["Wgu"])
+            self._dx_and_dw(self.dGU, "Wgu", X)
         elif self.gated:
             self._k('spmm_bwd_dx', s24.spmm_bwd_dx, dY, w["Wd"].valsT, w["Wd"].metaT, self.dH)
             self._dw(dY, self.H, w["Wd"])
@@ -227,8 +238,7 @@ class SparseFFN:
                 self._k('spmm_bwd_dx', s24.spmm_bwd_dx, dY, w["W2"].valsT, w["W2"].metaT, self.dH)
                 self._k('act_bwd', s24.act_bwd, self.dH, self.Z, self.dZ, _ACT[self.act])
             self._dw(dY, self.H, w["W2"])
-            self._k('spmm_bwd_dx', s24.spmm_bwd_dx, self.dZ, w["W1"].valsT, w["W1"].metaT, self.dX)
-            self._dw(self.dZ, X, w["W1"])
+            self._dx_and_dw(self.dZ, "W1", X)
         return self.dX
 
     def decay(self):

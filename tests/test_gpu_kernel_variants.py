@@ -894,3 +894,58 @@ def test_weight_gradients_have_the_same_bits_in_every_tile(s24, dtype, case):
         rows = torch.cat([torch.arange(0, dW.shape[0], 61), torch.tensor([dW.shape[0] - 1])])
         ref = host_f64(dY)[:, rows.numpy()].T @ host_f64(X)
         assert_close(host_f64(dW)[rows.numpy()], ref, F32_TOL, f"dense_dw_batch {case}")
+
+
+# ------------------------------------------------------------------ the last input gradient and the weight gradients in one call
+def backward_operands(s24, p, q, r, dtype, seed):
+    """Of a layer q -> r -> q on p tokens: the compressed transpose of its first weight, the gradient there, and the two weight gradients."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    dt = torch_dtype(dtype)
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(dt)
+    new = lambda *shape, t=dt: torch.full(shape, 7, dtype=t, device="cuda")
+    W1, W2, X, H, dY, dZ = rnd(r, q), rnd(q, r), rnd(p, q), rnd(p, r), rnd(p, q), rnd(p, r)
+    masks, ops = [], []
+    for W in (W1, W2):
+        a, b = W.shape
+        o = new(b // 64, a, 32), new(b // 64, a, 4, t=torch.int16), new(a // 64, b, 32), new(a // 64, b, 4, t=torch.int16)
+        masks.append(new(a // 4, b // 4, t=torch.int16))
+        s24.compress(W, None, *o, mask_out=masks[-1])
+        ops.append(o)
+    grads = [new(q, r, t=torch.float32), new(r, q, t=torch.float32)]
+    problems = lambda decay: [(dY, H, grads[0], W2 if decay else None, masks[1] if decay else None, 1e-3),
+                              (dZ, X, grads[1], W1 if decay else None, masks[0] if decay else None, 1e-3)]
+    return dZ, ops[0][2], ops[0][3], new(p, q), grads, problems, X
+
+
+# fp32 (p, q, r): 32-tiles in eight slices with four, one and two batches of tokens in flight; a chain of a few tokens and a contraction of four slices, which
+# run in turn; ragged in every direction
+BACKWARD = [("f32", s) for s in [(512, 256, 1024), (100, 128, 512), (1200, 192, 576), (7, 64, 512), (130, 64, 448), (515, 320, 1088)]]
+
+
+@pytest.mark.parametrize("decay", [True, False])
+@pytest.mark.parametrize("dtype, pqr", BACKWARD)
+def test_input_and_weight_gradients_in_one_call_have_the_bits_of_two(s24, dtype, pqr, decay):
+    p, q, r = pqr
+    dZ, vT, mT, dX, grads, problems, _ = backward_operands(s24, p, q, r, dtype, p + r)
+    s24.spmm_bwd_dx_dw(dZ, vT, mT, dX, problems(decay))
+    got = [t.clone() for t in (dX, *grads)]
+    for t in (dX, *grads):
+        t.fill_(7)
+    s24.spmm_bwd_dx(dZ, vT, mT, dX)
+    s24.dense_dw_batch(problems(decay))
+    for a, b in zip(got, (dX, *grads)):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("dtype, pqr", [("f32", (512, 256, 1024))])
+def test_an_input_gradient_over_an_operand_of_a_weight_gradient_comes_first(s24, dtype, pqr):
+    """In place of X, which a weight gradient reads: as the two calls in their order."""
+    dZ, vT, mT, dX, grads, problems, X = backward_operands(s24, *pqr, dtype, 5)
+    kept = X.clone()
+    s24.spmm_bwd_dx(dZ, vT, mT, X)
+    s24.dense_dw_batch(problems(True))
+    want = [t.clone() for t in (X, *grads)]
+    X.copy_(kept)
+    s24.spmm_bwd_dx_dw(dZ, vT, mT, X, problems(True))
+    for a, b in zip(want, (X, *grads)):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))

@@ -271,6 +271,10 @@ def plain_headers(tmp_path_factory):
 #include "s24_overlap.h"
 #include "s24_split.h"
 extern "C" int dw_overlap(const void *p, int n, int esize) { return s24_dw_problems_overlap((const s24_dw_problem *)p, n, esize); }
+extern "C" int dx_meets(const void *dY, const void *vT, const void *mT, const void *dX, int p, int q, int r, const void *pr, int n, int esize)
+{
+    return s24_dx_meets_dw(dY, vT, mT, dX, p, q, r, (const s24_dw_problem *)pr, n, esize);
+}
 extern "C" int token_pairs(int t) { return s24_token_pairs(t); }
 extern "C" int slice_begin(int n, int s, int slices) { return s24_slice_begin(n, s, slices); }
 """)
@@ -309,6 +313,25 @@ def test_overlapping_weight_gradients_are_found(plain_headers):
     assert not overlap(a, problem(1, W=None, mask=grad))            # no decay: the mask is not read
     assert not overlap(a, problem(1, r=0, dW=grad, X=grad))         # an empty output
     assert not overlap(a, problem(1, p=0, X=grad, dY=grad)) and overlap(a, problem(1, p=0, dW=grad))
+
+
+def test_input_gradient_that_meets_a_weight_gradient_is_found(plain_headers):
+    from paper_2404_01847_amd.binding import _DwProblem
+    step = 0x100000
+    p, q, r, es = 64, 32, 64, 2
+    at = dict(dY=1, vT=2, mT=3, dX=4, X=5, dW=6, W=7, mask=8)
+    size = dict(dY=p * r * es, vT=r * q // 2 * es, mT=r * q // 8, dX=p * q * es, X=p * q * es, dW=r * q * 4, W=r * q * es, mask=r * q // 8)
+    def meets(decay=True, r_dw=r, **moved):
+        b = {k: C.c_void_p(moved.get(k, v * step)) for k, v in at.items()}
+        pr = (_DwProblem * 1)(_DwProblem(b["dY"], b["X"], b["dW"], b["W"] if decay else None, b["mask"], p, q, r_dw, 1e-4))
+        return bool(plain_headers.dx_meets(b["dY"], b["vT"], b["mT"], b["dX"], p, q, r, pr, 1, es))
+    assert not meets()                           # dY is read by both
+    for written, others in (("dX", ("dY", "X", "dW", "W", "mask")), ("dW", ("dY", "vT", "mT", "dX"))):
+        for o in others:
+            for to, hit in ((at[o] * step, True), (at[o] * step + size[o] - 16, True), (at[o] * step + size[o], False), (at[o] * step - size[written] + 16, True),
+                            (at[o] * step - size[written], False)):
+                assert meets(**{written: to}) == hit, (written, o)
+    assert not meets(decay=False, dX=at["W"] * step) and not meets(r_dw=0, dX=at["dW"] * step)
 
 
 def test_binding_refuses_to_run_without_library(monkeypatch, tmp_path):
