@@ -19,7 +19,9 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "s24_dw.h"
 #include "s24_gemm_f32.h"
+#include "s24_gemm_joint.h"
 #include "s24_gemm_slice.h"
 #include "s24_lds.h"
 #include "s24_overlap.h"
@@ -126,22 +128,6 @@ __device__ __forceinline__ bf16x16 as_bf16x16(uint4 lo, uint4 hi)
 namespace big {
 constexpr int BM = 256, BN = 256, THREADS = 512;   // the large tile
 using namespace s24_lds;
-
-// Workgroup barrier that leaves up to VM vector-memory operations (direct-to-LDS copies of later
-// chunks) in flight.  The raw wait and barrier instructions carry no memory semantics for the
-// compiler, so they are fenced on both sides against reordering of LDS accesses, in the
-// optimiser (empty asm with a memory clobber) and in the instruction scheduler.
-// LDS_READS: whether the wave's own LDS reads have to be back as well.
-template <int VM, bool LDS_READS = true>
-__device__ __forceinline__ void wait_and_barrier()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(VM) | (LDS_READS ? 0 : 15 << 8));
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("" ::: "memory");
-}
 
 // Clock probe (instrumentation, off unless a buffer is registered): workgroup 0 of a large-tile kernel
 // reports how many core-clock cycles and how many ticks of the fixed 100 MHz reference passed between its
@@ -898,6 +884,8 @@ __global__ __launch_bounds__(128 * WN) void dense_nt_big_kernel(const uint16_t *
 // fragments of chunk kc+1 are fetched during the matrix instructions of chunk kc and the barrier finds the matrix unit
 // busy; the copies of chunk kc+3 are dealt out between the matrix instructions rather than issued in one burst.
 namespace dmatn {
+using namespace s24_lds;
+using namespace s24_dw;
 constexpr int THREADS = 256;
 // WTM x WTN: wave tile in units of 32: 4 x 4 -> 256 x 256 workgroup tiles; 4 x 2, 3 x 2 and 2 x 2 -> 256 x 128, 192 x 128 and
 // 128 x 128 tiles for outputs with too few large tiles to fill the chip.  BT = tokens per ring stage: 32 for the large tile (128 KB
@@ -909,54 +897,9 @@ template <int WTM_, int WTN_, int BT_> struct Cfg {
     static constexpr int OPERAND = BT * ROWA, STAGE = OPERAND + BT * ROWX;
     static constexpr int NIA = BT * ROWA / 4096, NIX = BT * ROWX / 4096, NI = NIA + NIX;   // copies per wave and chunk
 };
-using big::glb_ptr;
-using big::lds_ptr;
-typedef short v4i16 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) v4i16 *lds_v4i16;
-
-// 16-byte slot of chunk c of token row t: c ^ tr_swizzle(t).  Rows of 384 bytes lie half a round of the banks apart, so the lowest bit of
-// the row needs no part in it, and their 24 slots take an exchange within eight only.
-template <int ROWB> __device__ __forceinline__ int tr_swizzle(int row)
-{
-    static_assert(ROWB % 256 == 0 || ROWB % 256 == 128, "rows of whole or half rounds of the banks");
-    return (ROWB % 256 == 0 ? (row & 3) << 2 : (row & 2) << 1) ^ ((row >> 2) & 2);
-}
-template <int ROWB>
-__device__ __forceinline__ int tr_off(int row, int col)
-{
-    return row * ROWB + (((col >> 3) ^ tr_swizzle<ROWB>(row)) << 4) + ((col & 7) << 1);
-}
-__device__ __forceinline__ v4i16 tr_half(const unsigned char *p) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(p)); }
-__device__ __forceinline__ bf16x8 join(v4i16 lo, v4i16 hi)
-{
-    struct { v4i16 a, b; } t{lo, hi};
-    return __builtin_bit_cast(bf16x8, t);
-}
-
 // DECAY: the masked decay term is added in the epilogue: dW[m][n] += lambda * Wt[m][n] where bit
 // 4*(m%4) + n%4 of mask[m/4][n/4] is clear, with the same single fused multiply-add the stand-alone
 // decay kernel applies to the stored gradient, so both routes give the same bits.
-// One launch covers up to four weight gradients (DwBatch): their tiles share one grid, so that the compute units
-// left idle by the last, partial round of one problem take tiles of the next.  The operands of a problem may be
-// windows of larger matrices: M and N are the extents of the window's output, ldy, ldx and ldw the row strides
-// (elements) of dY, of X and of dW / Wt (the mask's row stride is ldw / 4; a window starts at a multiple of four
-// rows and columns).
-struct DwWindow {
-    const uint16_t *dY, *X, *Wt, *mask;
-    float *dW;
-    int T, M, N, ldy, ldx, ldw, tiles_m, tiles_n;
-    float lambda;
-};
-constexpr int kMaxBatch = 4;
-// Workgroups are dealt round-robin to the eight XCDs.  Each XCD takes, of every problem in turn, one contiguous
-// eighth of its tile list: first_slot[i] .. first_slot[i+1]-1 are the positions in an XCD's own list that belong to
-// problem i (unused entries repeat the total), so every problem is spread over all XCDs exactly as a launch of its
-// own would spread it, and the workgroups resident on one XCD share operand rows in its L2.
-struct DwBatch {
-    DwWindow w[kMaxBatch];
-    int first_slot[kMaxBatch + 1];
-};
-
 template <typename ET, typename C, bool ACCUM, bool DECAY>
 __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch batch, unsigned long long *probe)
 {
@@ -2141,6 +2084,24 @@ int check_dw_batch(const s24_dw_problem *problems, int count, s24_dtype dt)
     }
     return S24_OK;
 }
+DwProblem dw_problem(const s24_dw_problem &pr)
+{
+    return DwProblem{static_cast<const uint16_t *>(pr.dY), static_cast<const uint16_t *>(pr.X), pr.dW, static_cast<const uint16_t *>(pr.W), pr.mask, pr.p, pr.q, pr.r, pr.lambda};
+}
+// One grid of `tile` for all of several problems
+dmatn::DwBatch shared_batch(const DwProblem *prs, int count, DwTile tile)
+{
+    dmatn::DwBatch batch{};
+    int first = 0;
+    for (int i = 0; i < count; ++i) {
+        batch.w[i] = dw_window(prs[i], tile, 0, prs[i].r, 0, prs[i].q);
+        batch.first_slot[i] = first;
+        first += (batch.w[i].tiles_m * batch.w[i].tiles_n + 7) / 8;
+    }
+    for (int i = count; i <= dmatn::kMaxBatch; ++i) batch.first_slot[i] = first;
+    return batch;
+}
+inline bool dw_is_small(const s24_dw_problem &pr) { return (int64_t)ceil_div(pr.r, 256) * ceil_div(pr.q, 256) < 3 * s24_cu_count() / 4; }
 }  // namespace
 
 extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, float beta, s24_dtype dt, void *stream)
@@ -2163,11 +2124,7 @@ extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, flo
     }
     const bool accum = beta != 0.0f, decay = problems[0].W != nullptr;
     DwProblem prs[dmatn::kMaxBatch];
-    for (int i = 0; i < count; ++i) {
-        const s24_dw_problem &pr = problems[i];
-        prs[i] = DwProblem{static_cast<const uint16_t *>(pr.dY), static_cast<const uint16_t *>(pr.X), pr.dW,
-                           static_cast<const uint16_t *>(pr.W), pr.mask, pr.p, pr.q, pr.r, pr.lambda};
-    }
+    for (int i = 0; i < count; ++i) prs[i] = dw_problem(problems[i]);
     const int cus = s24_cu_count();
     if (!shared_grid || total < 3 * cus / 4 || count == 1) {
         // Problems that would each leave the large tile's grid mostly empty (fewer than 192 tiles) share one grid of the tile
@@ -2175,20 +2132,11 @@ extern "C" int s24_dense_dw_batch(const s24_dw_problem *problems, int count, flo
         bool small_grid = dt != S24_F32 && count > 1;
         for (int i = 0; i < count; ++i) {
             const s24_dw_problem &pr = problems[i];
-            small_grid = small_grid && pr.p > 0 && pr.q * pr.r != 0 && (pr.W != nullptr) == decay &&
-                         (int64_t)ceil_div(pr.r, 256) * ceil_div(pr.q, 256) < 3 * cus / 4;
+            small_grid = small_grid && pr.p > 0 && pr.q * pr.r != 0 && (pr.W != nullptr) == decay && dw_is_small(pr);
         }
         if (small_grid) {
             const DwTile few = dw_few_tile(prs, count);
-            dmatn::DwBatch batch{};
-            int first = 0;
-            for (int i = 0; i < count; ++i) {
-                batch.w[i] = dw_window(prs[i], few, 0, prs[i].r, 0, prs[i].q);
-                batch.first_slot[i] = first;
-                first += (batch.w[i].tiles_m * batch.w[i].tiles_n + 7) / 8;
-            }
-            for (int i = count; i <= dmatn::kMaxBatch; ++i) batch.first_slot[i] = first;
-            launch_dw_batch(batch, few, accum, decay, dt, st);
+            launch_dw_batch(shared_batch(prs, count, few), few, accum, decay, dt, st);
             return s24_launch_status();
         }
         // fp32: one grid for every problem with tokens to contract, unless the order of the problems counts (two of them
@@ -2278,6 +2226,20 @@ extern "C" int s24_spmm_bwd_dx_dw(const void *dY, const void *valsT, const uint1
         if (s24_f32_nt_tn({static_cast<const float *>(dY), static_cast<const float *>(valsT), metaT, static_cast<float *>(dX), nullptr, nullptr, p, r, q, false,
                            S24_F32_PLAIN, 0}, f, count, st, rc))
             return rc;
+    }
+    // 16-bit: where the input gradient runs in slices, one token block to a tile, and the weight gradients in the small tile by eight waves or by
+    // four at no more tokens than make these equal
+    for (int i = 0; i < count; ++i) together = together && dw_is_small(problems[i]) && problems[i].p <= 1024;
+    int tm = 0;
+    if (together && dt != S24_F32 && bwd_dx_slices(p, r, q) && s24_slice_narrow_tile(p, r, q, tm)) {
+        DwProblem prs[dmatn::kMaxBatch];
+        for (int i = 0; i < count; ++i) prs[i] = dw_problem(problems[i]);
+        if (dw_few_tile(prs, count) == DwTile::Small) {
+            const dmatn::DwBatch batch = shared_batch(prs, count, DwTile::Small);
+            s24_dx_dw({static_cast<const uint16_t *>(dY), static_cast<const uint16_t *>(valsT), metaT, static_cast<uint16_t *>(dX), nullptr, nullptr, nullptr, p, r, q,
+                       false, S24_SLICE_PLAIN, 0}, tm, batch, problems[0].W != nullptr, dt, st);
+            return s24_launch_status();
+        }
     }
     rc = s24_spmm_bwd_dx(dY, valsT, metaT, dX, p, q, r, 0.0f, dt, stream);
     return rc != S24_OK ? rc : s24_dense_dw_batch(problems, count, 0.0f, dt, stream);

@@ -18,4 +18,6 @@ struct S24SliceNt {
     int act;
 };
 double s24_slice_us(int64_t N, int64_t K, int64_t M);   // what it takes while its operands are in the caches
+// Row blocks of the best tile with one token block, if it costs no more than 1.3 of the best of all
+bool s24_slice_narrow_tile(int64_t N, int64_t K, int64_t M, int &tm);
 int s24_slice_nt(const S24SliceNt &g, int dt, hipStream_t st);

@@ -5,6 +5,15 @@
 namespace s24_lds {
 typedef __attribute__((address_space(3))) void *lds_ptr;
 typedef const __attribute__((address_space(1))) void *glb_ptr;
+// LDS handed to a device function: with the address space in its type the compiler keeps 32-bit addresses and LDS instructions
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+typedef __attribute__((address_space(3))) s24_u32x4 lds_u32x4;
+__device__ __forceinline__ uint4 lds_load(const lds_byte *p) { return __builtin_bit_cast(uint4, *(const lds_u32x4 *)p); }
+template <typename V> __device__ __forceinline__ void lds_store(lds_byte *p, V v)
+{
+    static_assert(sizeof(V) == 16, "sixteen bytes");
+    *(lds_u32x4 *)p = __builtin_bit_cast(s24_u32x4, v);
+}
 
 __device__ __forceinline__ int b_slot(int row, int c) { return row * 128 + ((c ^ ((row >> 1) & 7)) << 4); }
 __device__ __forceinline__ int a_swizzle(int row) { return -(row >> 2) & 3; }
@@ -55,4 +64,20 @@ template <bool STREAM> __device__ __forceinline__ uint4 buffer_load_16(rsrc_t, u
 
 // s_waitcnt immediate: vmcnt(n), lgkmcnt(0), expcnt unconstrained
 __host__ __device__ constexpr int wait_vm_lgkm0(int n) { return (n & 15) | (7 << 4) | ((n >> 4) << 14); }
+
+// Workgroup barrier that leaves up to VM vector-memory operations (direct-to-LDS copies of later
+// chunks) in flight.  The raw wait and barrier instructions carry no memory semantics for the
+// compiler, so they are fenced on both sides against reordering of LDS accesses, in the
+// optimiser (empty asm with a memory clobber) and in the instruction scheduler.
+// LDS_READS: whether the wave's own LDS reads have to be back as well.
+template <int VM, bool LDS_READS = true>
+__device__ __forceinline__ void wait_and_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(VM) | (LDS_READS ? 0 : 15 << 8));
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+}
 }  // namespace s24_lds

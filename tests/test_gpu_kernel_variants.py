@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import s24_inputs as si
-from util import F32_TOL, assert_close, dev, dev_bf16, host_bits, host_f64, mask_tiles_run, tiles_run, tol_for, torch_dtype
+from util import F32_TOL, assert_close, dev, dev_bf16, host_bits, host_f64, mask_tiles_run, tiles_run, together_run, tol_for, torch_dtype
 
 pytestmark = pytest.mark.gpu
 
@@ -919,7 +919,11 @@ def backward_operands(s24, p, q, r, dtype, seed):
 
 # fp32 (p, q, r): 32-tiles in eight slices with four, one and two batches of tokens in flight; a chain of a few tokens and a contraction of four slices, which
 # run in turn; ragged in every direction
-BACKWARD = [("f32", s) for s in [(512, 256, 1024), (100, 128, 512), (1200, 192, 576), (7, 64, 512), (130, 64, 448), (515, 320, 1088)]]
+BACKWARD = [("f32", s) for s in [(512, 256, 1024), (100, 128, 512), (1200, 192, 576), (1200, 192, 1344), (7, 64, 512), (130, 64, 448), (515, 320, 1088)]]
+# 16-bit: slices of four, one and two row blocks; one token, less than a step of 32, a step and a rest, a ring of whole steps, many whole steps and a
+# rest of one token
+BACKWARD += [("bf16", s) for s in [(256, 768, 3072), (200, 512, 1344), (1, 64, 128), (128, 128, 448), (704, 128, 448), (705, 128, 448)]]
+BACKWARD += [("f16", s) for s in [(100, 512, 1408), (31, 256, 1024), (257, 320, 1088)]]
 
 
 @pytest.mark.parametrize("decay", [True, False])
@@ -927,7 +931,8 @@ BACKWARD = [("f32", s) for s in [(512, 256, 1024), (100, 128, 512), (1200, 192, 
 def test_input_and_weight_gradients_in_one_call_have_the_bits_of_two(s24, dtype, pqr, decay):
     p, q, r = pqr
     dZ, vT, mT, dX, grads, problems, _ = backward_operands(s24, p, q, r, dtype, p + r)
-    s24.spmm_bwd_dx_dw(dZ, vT, mT, dX, problems(decay))
+    in_turn = dtype == "f32" and pqr in ((7, 64, 512), (130, 64, 448))
+    assert together_run(lambda: s24.spmm_bwd_dx_dw(dZ, vT, mT, dX, problems(decay))) == (not in_turn)
     got = [t.clone() for t in (dX, *grads)]
     for t in (dX, *grads):
         t.fill_(7)
@@ -937,7 +942,7 @@ def test_input_and_weight_gradients_in_one_call_have_the_bits_of_two(s24, dtype,
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
-@pytest.mark.parametrize("dtype, pqr", [("f32", (512, 256, 1024))])
+@pytest.mark.parametrize("dtype, pqr", [("f32", (512, 256, 1024)), ("bf16", (256, 768, 3072))])
 def test_an_input_gradient_over_an_operand_of_a_weight_gradient_comes_first(s24, dtype, pqr):
     """In place of X, which a weight gradient reads: as the two calls in their order."""
     dZ, vT, mT, dX, grads, problems, X = backward_operands(s24, *pqr, dtype, 5)
