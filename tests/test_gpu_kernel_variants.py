@@ -897,13 +897,15 @@ def test_weight_gradients_have_the_same_bits_in_every_tile(s24, dtype, case):
 
 
 # ------------------------------------------------------------------ the last input gradient and the weight gradients in one call
-def backward_operands(s24, p, q, r, dtype, seed):
-    """Of a layer q -> r -> q on p tokens: the compressed transpose of its first weight, the gradient there, and the two weight gradients."""
+def backward_operands(s24, p, q, r, dtype, seed, f=None):
+    """Of a layer q -> r -> q on p tokens (gated: r -> f between): the compressed transpose of its first weight, the gradient there, and the two
+    weight gradients."""
+    f = f or r
     gen = torch.Generator(device="cuda").manual_seed(seed)
     dt = torch_dtype(dtype)
     rnd = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(dt)
     new = lambda *shape, t=dt: torch.full(shape, 7, dtype=t, device="cuda")
-    W1, W2, X, H, dY, dZ = rnd(r, q), rnd(q, r), rnd(p, q), rnd(p, r), rnd(p, q), rnd(p, r)
+    W1, W2, X, H, dY, dZ = rnd(r, q), rnd(q, f), rnd(p, q), rnd(p, f), rnd(p, q), rnd(p, r)
     masks, ops = [], []
     for W in (W1, W2):
         a, b = W.shape
@@ -911,7 +913,7 @@ def backward_operands(s24, p, q, r, dtype, seed):
         masks.append(new(a // 4, b // 4, t=torch.int16))
         s24.compress(W, None, *o, mask_out=masks[-1])
         ops.append(o)
-    grads = [new(q, r, t=torch.float32), new(r, q, t=torch.float32)]
+    grads = [new(q, f, t=torch.float32), new(r, q, t=torch.float32)]
     problems = lambda decay: [(dY, H, grads[0], W2 if decay else None, masks[1] if decay else None, 1e-3),
                               (dZ, X, grads[1], W1 if decay else None, masks[0] if decay else None, 1e-3)]
     return dZ, ops[0][2], ops[0][3], new(p, q), grads, problems, X
@@ -925,12 +927,16 @@ BACKWARD = [("f32", s) for s in [(512, 256, 1024), (100, 128, 512), (1200, 192, 
 BACKWARD += [("bf16", s) for s in [(256, 768, 3072), (200, 512, 1344), (1, 64, 128), (128, 128, 448), (704, 128, 448), (705, 128, 448)]]
 BACKWARD += [("f16", s) for s in [(100, 512, 1408), (31, 256, 1024), (257, 320, 1088)]]
 
+# 16-bit, whole grids (p, q, r, f): tiles of 192 x 128, of 256 x 256 in a part of a round and in two and a strip, of 256 x 128; ragged in every direction
+BACKWARD += [("bf16", s) for s in [(8192, 768, 3072), (2475, 1408, 3776), (3001, 2048, 11008, 5504), (3083, 576, 4608, 2304)]]
+BACKWARD += [("f16", s) for s in [(5939, 896, 2368), (1795, 640, 4480, 2240)]]
+
 
 @pytest.mark.parametrize("decay", [True, False])
 @pytest.mark.parametrize("dtype, pqr", BACKWARD)
 def test_input_and_weight_gradients_in_one_call_have_the_bits_of_two(s24, dtype, pqr, decay):
-    p, q, r = pqr
-    dZ, vT, mT, dX, grads, problems, _ = backward_operands(s24, p, q, r, dtype, p + r)
+    p, q, r, *f = pqr
+    dZ, vT, mT, dX, grads, problems, _ = backward_operands(s24, p, q, r, dtype, p + r, *f)
     in_turn = dtype == "f32" and pqr in ((7, 64, 512), (130, 64, 448))
     assert together_run(lambda: s24.spmm_bwd_dx_dw(dZ, vT, mT, dX, problems(decay))) == (not in_turn)
     got = [t.clone() for t in (dX, *grads)]

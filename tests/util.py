@@ -148,4 +148,4 @@ def tiles_run(call):
 
 def together_run(call):
     """Whether the input gradient and the weight gradients that `call` computes share a launch."""
-    return any(re.search(r"dx_dw_kernel|f32_nt_tn_kernel", name) for name in _kernels_run(call))
+    return any(re.search(r"dx_dw_kernel|dw_dx_kernel|f32_nt_tn_kernel", name) for name in _kernels_run(call))
