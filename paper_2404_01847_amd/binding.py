@@ -347,11 +347,13 @@ class _DwProblem(C.Structure):
 _pack_dw = _packer(_DwProblem)
 
 
-def _dw_problems(where, problems):
+def _dw_problems(where, problems, dtype):
     packed = []
     for dY, X, dW, W, mask, lam in problems:
         p, r = dY.shape
         _dense(where, "dY X dW W mask", dY, X, dW, W, mask)
+        if dY.dtype != dtype or X.dtype != dtype or (W is not None and W.dtype != dtype):
+            raise ValueError(f"{where}: the operands and weights of all problems must share one dtype")
         packed.append(_pack_dw(_ptr(dY), _ptr(X), _ptr(dW) or 0, _ptr(W) or 0, _ptr(mask) or 0, p, X.shape[1], r, _f32(lam).value))
     return b"".join(packed)
 
@@ -359,7 +361,7 @@ def _dw_problems(where, problems):
 def dense_dw_batch(problems, beta=0.0):
     """problems: up to four tuples (dY, X, dW, W, mask, lam) with W and mask None for no decay term; the weight
     gradients of all of them in one pass (same bits as dense_dw_decay / dense_dw on each)."""
-    arr = _dw_problems("s24_dense_dw_batch", problems)
+    arr = _dw_problems("s24_dense_dw_batch", problems, problems[0][0].dtype)
     _check(lib().s24_dense_dw_batch(arr, len(problems), beta, _dt(problems[0][0]), _stream()),
            "s24_dense_dw_batch")
 
@@ -368,7 +370,7 @@ def spmm_bwd_dx_dw(dY, valsT, metaT, dX, problems):
     """spmm_bwd_dx(dY, valsT, metaT, dX) and dense_dw_batch(problems), which do not depend on each other: one launch where both are small."""
     _dense("s24_spmm_bwd_dx_dw", "dY valsT metaT dX", dY, valsT, metaT, dX)
     p, r = dY.shape
-    arr = _dw_problems("s24_spmm_bwd_dx_dw", problems)
+    arr = _dw_problems("s24_spmm_bwd_dx_dw", problems, dY.dtype)
     _check(lib().s24_spmm_bwd_dx_dw(_ptr(dY), _ptr(valsT), _ptr(metaT), _ptr(dX), p, valsT.shape[1], r, arr, len(problems), _dt(dY),
                                     _stream()), "s24_spmm_bwd_dx_dw")
     return dX

@@ -334,6 +334,27 @@ def test_input_gradient_that_meets_a_weight_gradient_is_found(plain_headers):
     assert not meets(decay=False, dX=at["W"] * step) and not meets(r_dw=0, dX=at["dW"] * step)
 
 
+@pytest.mark.parametrize("call, odd", [("dense_dw_batch", k) for k in ((1, 0), (0, 1), (1, 1), (0, 3), (1, 3))] +
+                         [("spmm_bwd_dx_dw", k) for k in ((0, 0), (1, 0), (0, 1), (1, 3))])
+@pytest.mark.parametrize("dt, other", [("float32", "bfloat16"), ("bfloat16", "float16"), ("float16", "float32")])
+def test_batched_weight_gradients_refuse_mixed_dtypes(monkeypatch, call, odd, dt, other):
+    """One dtype speaks for all operands of a call: with another one among them the kernels would read past its end."""
+    import torch
+    from paper_2404_01847_amd import binding
+    monkeypatch.setattr(binding, "lib", lambda: pytest.fail("the library was called"))
+    dt, other = getattr(torch, dt), getattr(torch, other)
+    p, q, r = 4, 16, 64
+    new = lambda *shape, t=dt: torch.zeros(shape, dtype=t)
+    problems = [[new(p, r), new(p, q), new(r, q, t=torch.float32), new(r, q), new(r // 4, q // 4, t=torch.int16), 0.5] for _ in range(2)]
+    which, operand = odd
+    problems[which][operand] = problems[which][operand].to(other)
+    with pytest.raises(ValueError, match="share one dtype"):
+        if call == "dense_dw_batch":
+            binding.dense_dw_batch(problems)
+        else:
+            binding.spmm_bwd_dx_dw(new(p, r), new(1, q, 32), new(1, q, 4, t=torch.int16), new(p, q), problems)
+
+
 def test_binding_refuses_to_run_without_library(monkeypatch, tmp_path):
     from paper_2404_01847_amd import binding
     monkeypatch.setattr(binding, "_lib", None)
