@@ -181,18 +181,19 @@ class SparseFFN:
         weight = self.w[name]
         if self.batch_dw and not self.mvue and self.timings is None:
             self._dw(dYw, Xw, weight)
-            s24.spmm_bwd_dx_dw(dYw, weight.valsT, weight.metaT, self.dX, self._pending_dw)
-            self._pending_dw = []
+            problems, self._pending_dw = self._pending_dw, []
+            s24.spmm_bwd_dx_dw(dYw, weight.valsT, weight.metaT, self.dX, problems)
         else:
             self._k('spmm_bwd_dx', s24.spmm_bwd_dx, dYw, weight.valsT, weight.metaT, self.dX)
             self._dw(dYw, Xw, weight)
 
     def _flush_dw(self):
         if self._pending_dw:
-            self._k('dense_dw', s24.dense_dw_batch, self._pending_dw)
-            self._pending_dw = []
+            problems, self._pending_dw = self._pending_dw, []
+            self._k('dense_dw', s24.dense_dw_batch, problems)
 
     def backward(self, X, dY):
+        self._pending_dw = []   # of a pass that failed on its way: its gradients beside this pass's would be written twice in one launch
         out = self._backward(X, dY)
         self._flush_dw()
         return out
