@@ -156,7 +156,7 @@ class SparseFFN:
 
     def _dw(self, dYw, Xw, weight):
         for name in self.bias_grad:   # the bias gradient of this weight: column sums of its output gradient
-            if self.w[name] is weight:
+            if self.w[name] is weight and self.bias[name] is not None:
                 self._k('bias_grad', s24.bias_grad, dYw, self.bias_grad[name])
         if self.batch_dw and not self.mvue:   # collected; backward() runs them all in one pass at its end
             self._pending_dw.append((dYw, Xw, weight.grad, weight.W if self.fuse_decay else None,

@@ -55,3 +55,10 @@ def test_a_backward_pass_that_fails_leaves_nothing_to_the_next(calls, act, kw, f
     ffn.backward(X, dY)
     got = submitted(calls)
     assert len(got) == len(ffn.w) and {id(g) for g in got} == {id(w.grad) for w in ffn.w.values()}
+
+
+def test_a_bias_taken_away_has_no_gradient(calls):
+    ffn, X, dY = make("gelu", biases=("W1", "W2"))
+    ffn.bias["W1"] = None
+    ffn.backward(X, dY)
+    assert [args[1] is ffn.bias_grad["W2"] for name, args in calls if name == "bias_grad"] == [True]
