@@ -257,6 +257,22 @@ def test_gated_family_argument_errors(lib):
     arr[0] = _DwProblem(P, P, P, None, None, 4, 16, 0, 0.0)
     arr[1] = _DwProblem(None, None, None, None, None, 4, 0, 16, 0.0)
     assert lib.s24_dense_dw_batch(ptr, 2, 0.0, 1, None) == OK                        # empty outputs: nothing to do
+    # s24_spmm_bwd_dx_dw(dY, valsT, metaT, dX, p, q, r, problems, count, dt, stream): all of both parts before the first launch
+    def both(pr=(good, good), dY=P, vT=P, mT=P, dX=P, p=4, q=16, r=64, count=None, dt=1):
+        host = (_DwProblem * max(len(pr), 1))(*pr)
+        return lib.s24_spmm_bwd_dx_dw(dY, vT, mT, dX, p, q, r, ctypes.cast(host, ctypes.c_void_p) if pr else None, len(pr) if count is None else count, dt, None)
+    assert both(r=96) == SHAPE and both(r=0) == SHAPE and both(q=24) == SHAPE and both(p=-1) == SHAPE
+    assert both(dt=9) == DTYPE and both(dY=None) == NULL and both(vT=None) == NULL and both(dX=None) == NULL and both(dX=P + 8) == ALIGN
+    assert both(mT=None) == NULL and both(mT=P + 2) == ALIGN
+    assert both(count=5) == SHAPE and both(count=-1) == SHAPE and both(pr=(), count=2) == NULL
+    for pr, status in (((P, P, P, None, None, 4, 24, 16, 0.0), SHAPE), ((P, None, P, None, None, 4, 16, 16, 0.0), NULL), ((P, P, P + 4, None, None, 4, 16, 16, 0.0), ALIGN),
+                       ((P, P, P, P, None, 4, 16, 16, 1e-4), NULL), ((P, P, P, P, P + 2, 4, 16, 16, 1e-4), ALIGN)):
+        bad = _DwProblem(*pr)
+        assert both((bad,)) == status and both((good, bad)) == status and both((good, good, good, bad)) == status
+        assert both((bad,), p=0) == status and both((bad,), q=0) == status      # nothing to do for the other part
+    empty = _DwProblem(None, None, None, None, None, 4, 0, 16, 0.0)
+    for nothing in (dict(p=0), dict(q=0)):
+        assert both((), **nothing) == OK and both((empty, empty), **nothing) == OK and both((empty,), dY=None, vT=None, mT=None, dX=None, **nothing) == OK
     # binary16 is a valid dtype everywhere a dtype is taken
     assert lib.s24_transposable_mask(P, 2, 6, 8, 8, P, None, None) == SHAPE
     assert lib.s24_spmm_fwd(P, P, P, P, 0, 64, 16, 2, None) == OK
