@@ -65,6 +65,19 @@ template <bool STREAM> __device__ __forceinline__ uint4 buffer_load_16(rsrc_t, u
 // s_waitcnt immediate: vmcnt(n), lgkmcnt(0), expcnt unconstrained
 __host__ __device__ constexpr int wait_vm_lgkm0(int n) { return (n & 15) | (7 << 4) | ((n >> 4) << 14); }
 
+// Until at most VM of the wave's vector-memory operations are in flight: ahead of reads of what older ones copied into LDS.  (Left to
+// itself the compiler waits for the copies that it believes to alias a read.  Where two ways through a kernel meet, it knows those of one way
+// only and waits too little: never rely on it.)
+template <int VM> __device__ __forceinline__ void wait_copies()
+{
+    static_assert(VM < 64, "the counter's range");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(VM) | 15 << 8);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+}
+
 // Workgroup barrier that leaves up to VM vector-memory operations (direct-to-LDS copies of later
 // chunks) in flight.  The raw wait and barrier instructions carry no memory semantics for the
 // compiler, so they are fenced on both sides against reordering of LDS accesses, in the

@@ -40,7 +40,7 @@ constexpr int KS = 8;
 // contraction, D of them in flight, and the slices are summed in LDS in wave order, so the result does not depend on
 // scheduling.  GLU: the tile's row blocks are 8*TM gate rows and the 8*TM up rows of the same features (F of either).
 // Tokens go through LDS, in a ring that belongs to the wave alone (no barrier): eight lanes copy the 128 bytes that a token has in a chunk,
-// and the fragments come from there.
+// and the fragments come from there.  A wave waits for its own copies by their number: OPS operations to a chunk, in the order of `load`.
 // s0 .. s3: stage_bytes(TN) of LDS each, of the last two only where TN = 1.  (One array per ring stage: the compiler then knows which stage
 // a copy writes and does not make reads of the other ones wait for it.)
 constexpr int stage_bytes(int TN) { return KS * 2048 * TN; }
@@ -87,6 +87,7 @@ __device__ __forceinline__ void slice_tile(lds_byte *s0, lds_byte *s1, lds_byte 
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < 2 * TN; ++j) buffer_to_lds<16>(buffer_of(pb), (lds_ptr)(stage(d) + 1024 * j), ob[j]);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < TM; ++i) f.a[i] = buffer_load_16<STREAM>(buffer_of(pv), oa[i]);
 #pragma unroll
@@ -98,7 +99,13 @@ __device__ __forceinline__ void slice_tile(lds_byte *s0, lds_byte *s1, lds_byte 
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{};
-    auto multiply = [&](const Frag &f, int d) {
+    // `behind`: chunks that are certain to have been requested after this one.  Its own values and index words need no wait here: they are in registers.
+    constexpr int OPS = 2 * TN + 2 * TM;
+    auto multiply = [&](const Frag &f, int d, int behind) {
+        if (behind == 0) wait_copies<2 * TM>();
+        else if (behind == 1) wait_copies<OPS + 2 * TM>();
+        else if (behind == 2) wait_copies<2 * OPS + 2 * TM>();
+        else wait_copies<3 * OPS + 2 * TM>();
         Two b[TN];
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
@@ -111,7 +118,7 @@ __device__ __forceinline__ void slice_tile(lds_byte *s0, lds_byte *s1, lds_byte 
             for (int j = 0; j < TN; ++j) acc[i][j] = mma<T>(f.a[i], b[j], acc[i][j], f.ix[i]);
     };
     const int nk = K / 64, steps = ks < nk ? (nk - ks + KS - 1) / KS : 0;
-    // (Two ways through, so that on the longer one the compiler knows how many copies are in flight behind the one it waits for.)
+    // (Two ways through, so that on the longer one it is known how many copies are in flight behind the one to wait for.)
     Frag f[D];
     int i = 0;
     if (steps >= D) {
@@ -120,14 +127,14 @@ __device__ __forceinline__ void slice_tile(lds_byte *s0, lds_byte *s1, lds_byte 
         for (; i + 2 * D <= steps; i += D) {
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-                multiply(f[d], d);
+                multiply(f[d], d, D - 1);
                 load(f[d], d, ks + KS * (i + D + d));
             }
         }
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            multiply(f[d], d);
-            if (i + D + d < steps) load(f[d], d, ks + KS * (i + D + d));
+            multiply(f[d], d, D - 1 - d);
+            if (d < D - 1 && i + D + d < steps) load(f[d], d, ks + KS * (i + D + d));
         }
         i += D;
     } else {
@@ -137,7 +144,7 @@ __device__ __forceinline__ void slice_tile(lds_byte *s0, lds_byte *s1, lds_byte 
     }
 #pragma unroll
     for (int d = 0; d < D - 1; ++d)
-        if (i + d < steps) multiply(f[d], d);
+        if (i + d < steps) multiply(f[d], d, 0);
 
     // A wave parks its sums in the first two stages of its own ring, rows of 64 TM bytes (a token), quad c of row r at slot c ^ (its swizzle)
     constexpr int ROW = 64 * TM, RPS = WAVE / ROW;   // tokens that a wave's part of a stage holds
