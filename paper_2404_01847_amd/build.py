@@ -18,7 +18,7 @@ OBJ = os.path.join(HERE, "_build")
 SOURCES = ["s24_host.hip", "s24_mask.hip", "s24_elementwise.hip", "s24_gemm.hip", "s24_gemm_f32.hip", "s24_gemm_slice.hip", "s24_gemm_joint.hip", "s24_mvue.hip", "s24_probe.hip"]
 # The command processor puts the first 14 dwords of a kernel's arguments into scalar registers before a wave starts.  Without that a wave
 # begins with a trip to memory for them, which is half a microsecond of a kernel of eight (256 tokens x 768 x 3072, four sliced products:
-# 51.4 -> 49.5 us a step; two of 16 tokens: 41.7 -> 40.4).  It works on arguments passed one by one (not on structures), those that
+# 51.4 -> 49.5 us a step; two of 16 tokens: 41.7 -> 40.4).  It works on numbers, pointers and vectors (not on structures), those that
 # the first address needs first.
 PRELOAD_ARGUMENTS = ["-mllvm", "-amdgpu-kernarg-preload-count=14"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",

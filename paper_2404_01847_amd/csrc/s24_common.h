@@ -31,6 +31,18 @@ inline int s24_cu_count()
     return n;
 }
 
+// Two 64-bit words of a kernel's arguments: two addresses, an address and two numbers, or four numbers.  What a wave needs first has to be in
+// scalar registers when it starts (build.py, PRELOAD_ARGUMENTS), which a structure's members are not; but the launch pays on the host for
+// each argument (3.57 us with thirteen of them, 2.86 with one structure), so they travel in vectors, and what is needed last in one
+// structure.  Two sliced products through ctypes: 9.5 -> 8.1 us of host time, 8.05 as two structures that were not preloaded.
+typedef uint64_t s24_words __attribute__((ext_vector_type(2)));
+inline s24_words s24_pack(const void *a, const void *b) { return s24_words{reinterpret_cast<uintptr_t>(a), reinterpret_cast<uintptr_t>(b)}; }
+inline s24_words s24_pack(const void *a, int lo, int hi) { return s24_words{reinterpret_cast<uintptr_t>(a), (uint64_t)(uint32_t)hi << 32 | (uint32_t)lo}; }
+inline s24_words s24_pack(int a, int b, int c, int d) { return s24_words{(uint64_t)(uint32_t)b << 32 | (uint32_t)a, (uint64_t)(uint32_t)d << 32 | (uint32_t)c}; }
+template <typename P> __device__ __forceinline__ P *s24_global(uint64_t word) { return (P *)(__attribute__((address_space(1))) P *)word; }
+__device__ __forceinline__ int s24_low(uint64_t word) { return (int)(uint32_t)word; }
+__device__ __forceinline__ int s24_high(uint64_t word) { return (int)(uint32_t)(word >> 32); }
+
 // Call after a kernel launch: turns a refused launch into S24_ERR_LAUNCH.
 static inline int s24_launch_status() { return hipGetLastError() == hipSuccess ? S24_OK : S24_ERR_LAUNCH; }
 

@@ -963,7 +963,7 @@ inline NtTile sparse_dw_tile(int64_t M, int64_t N) { return cheapest_tile(M, N, 
         else MACRO(__VA_ARGS__, 2, 2);                                  \
     } while (0)
 
-// Whether a product of N tokens and M features runs in slices (s24_gemm_slice.hip).  Up to 16 tokens, of which a tile would multiply
+// Whether a product of N tokens and M features runs in slices (s24_gemm_slice.hip), and in which.  Up to 16 tokens, of which a tile would multiply
 // seven eighths of nothing: yes (16 x 16384, K = 4096, weights out of the caches: 28 us in tiles, 13.7 in slices; x 50304: 44.5 and 43.0),
 // unless the 128 x 128 tiles are nearly two per compute unit and the contraction is long, so that they too keep the memory busy
 // (x 65536, K = 8192: 103 and 109; K = 2048: 40 and 29; 57344, K = 8192: 95 and 92).  With more tokens not where these tiles are more than
@@ -971,14 +971,15 @@ inline NtTile sparse_dw_tile(int64_t M, int64_t N) { return cheapest_tile(M, N, 
 // keep a tile's launch, prologue and epilogue in the open: 2.5 us beyond the share of a round, the middle of 1 without and 4 with an
 // activation, since one rule for all epilogues gives them the same bits.  Weights out of the caches come in at 5 TB/s either way.  Of 380
 // products (1-2048 tokens, K = 256-32000, 256-56000 features) the choice takes 1 % more than the best tile of either kind at the mean.
-inline bool slice_pays(int64_t N, int64_t K, int64_t M)
+inline S24SlicePlan slices_if_faster(int64_t N, int64_t K, int64_t M)
 {
     const int64_t cus = s24_cu_count(), small = (int64_t)ceil_div(M, 128) * ceil_div(N, 128);
-    if (N <= 16) return !(K >= 4096 && 4 * small > 7 * cus && small <= 2 * cus);
-    if (small > cus) return false;
+    if (N <= 16) return K >= 4096 && 4 * small > 7 * cus && small <= 2 * cus ? S24SlicePlan{} : s24_slice_plan(N, K, M);
+    if (small > cus) return {};
     const NtCosts c = sparse_costs(K);
     const double tiles = 2.5 + round_us(K) * std::min(nt_cost(NtTile::Large, M, N, c), std::min(nt_cost(NtTile::Medium, M, N, c), nt_cost(NtTile::Small, M, N, c)));
-    return s24_slice_us(N, K, M) <= std::max(tiles, 2.0 + 1.125 * (double)M * (double)K / 5.0e6);
+    const S24SlicePlan p = s24_slice_plan(N, K, M);
+    return p.us <= std::max(tiles, 2.0 + 1.125 * (double)M * (double)K / 5.0e6) ? p : S24SlicePlan{};
 }
 
 // Outputs that the gated backward epilogue serves: three quarters of the compute units have a large tile
@@ -987,11 +988,11 @@ inline bool gated_bwd_fits(int64_t p, int64_t f) { return (int64_t)ceil_div(f, 2
 // Whether the input gradient of p tokens and q features, contraction r, runs in slices.  One rule for s24_spmm_bwd_dx and
 // s24_spmm_bwd_dx_act, whose bits agree; and neither does where s24_spmm_bwd_dx_glu takes its large tiles (possible at up to
 // 16 tokens from 48897 features on), so that all three sum in one order.
-inline bool bwd_dx_slices(int64_t p, int64_t r, int64_t q) { return !gated_bwd_fits(p, q) && slice_pays(p, r, q); }
+inline S24SlicePlan bwd_dx_slices(int64_t p, int64_t r, int64_t q) { return gated_bwd_fits(p, q) ? S24SlicePlan{} : slices_if_faster(p, r, q); }
 
 // Out[N][M] = beta * Out + B[N][K] . A^T (+ bias[M], only with beta = 0)
 int launch_spmm(const void *B, const void *Av, const uint16_t *Am, void *Out, int64_t N, int64_t K, int64_t M, float beta,
-                int dt, hipStream_t st, const void *bias, bool slices)
+                int dt, hipStream_t st, const void *bias, const S24SlicePlan &slices)
 {
     if (N == 0 || M == 0) return S24_OK;
     const bool accum = beta != 0.0f;
@@ -1002,12 +1003,12 @@ int launch_spmm(const void *B, const void *Av, const uint16_t *Am, void *Out, in
     auto *b = static_cast<const uint16_t *>(B), *av = static_cast<const uint16_t *>(Av), *d = static_cast<const uint16_t *>(bias);
     auto *o = static_cast<uint16_t *>(Out);
     S24_REQUIRE((int64_t)ceil_div(M, 128) * ceil_div(N, 128) < (1ll << 30), S24_ERR_SHAPE);
-    if (slices) return s24_slice_nt({b, av, Am, o, nullptr, nullptr, d, N, K, M, accum, S24_SLICE_PLAIN, 0}, dt, st);
+    if (slices) return s24_slice_nt({b, av, Am, o, nullptr, nullptr, d, N, K, M, accum, S24_SLICE_PLAIN, 0}, slices, dt, st);
     const NtTile tile = nt_tile_or_slab(M, N, K);
     if (tile.slab != 0) {
-        const int rc = launch_spmm(B, Av, Am, Out, tile.slab, K, M, beta, dt, st, bias, false);
+        const int rc = launch_spmm(B, Av, Am, Out, tile.slab, K, M, beta, dt, st, bias, {});
         if (rc != S24_OK) return rc;
-        return launch_spmm(b + tile.slab * K, Av, Am, o + tile.slab * M, N - tile.slab, K, M, beta, dt, st, bias, false);
+        return launch_spmm(b + tile.slab * K, Av, Am, o + tile.slab * M, N - tile.slab, K, M, beta, dt, st, bias, {});
     }
     const int tiles_m = (int)ceil_div(M, tile.bm()), tiles_n = (int)ceil_div(N, tile.bn());
     const dim3 grid(((tiles_m * tiles_n + 7) / 8) * 8), block(tile.threads());
@@ -1040,7 +1041,7 @@ extern "C" int s24_spmm_fwd_bias(const void *X, const void *vals, const uint16_t
     if (rc != S24_OK || p * r == 0) return rc;
     S24_REQUIRE(meta != nullptr, S24_ERR_NULL);
     S24_REQUIRE(s24_aligned(meta, 4) && s24_aligned(bias, 8), S24_ERR_ALIGN);
-    return launch_spmm(X, vals, meta, Y, p, q, r, 0.0f, dt, static_cast<hipStream_t>(stream), bias, slice_pays(p, q, r));
+    return launch_spmm(X, vals, meta, Y, p, q, r, 0.0f, dt, static_cast<hipStream_t>(stream), bias, dt == S24_F32 ? S24SlicePlan{} : slices_if_faster(p, q, r));
 }
 
 extern "C" int s24_spmm_bwd_dx(const void *dY, const void *valsT, const uint16_t *metaT, void *dX, int64_t p, int64_t q,
@@ -1052,7 +1053,7 @@ extern "C" int s24_spmm_bwd_dx(const void *dY, const void *valsT, const uint16_t
     if (rc != S24_OK || p * q == 0) return rc;
     S24_REQUIRE(metaT != nullptr, S24_ERR_NULL);
     S24_REQUIRE(s24_aligned(metaT, 4), S24_ERR_ALIGN);
-    return launch_spmm(dY, valsT, metaT, dX, p, r, q, beta, dt, static_cast<hipStream_t>(stream), nullptr, bwd_dx_slices(p, r, q));
+    return launch_spmm(dY, valsT, metaT, dX, p, r, q, beta, dt, static_cast<hipStream_t>(stream), nullptr, dt == S24_F32 ? S24SlicePlan{} : bwd_dx_slices(p, r, q));
 }
 
 extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t *meta, const void *bias, void *GU, void *H,
@@ -1065,9 +1066,9 @@ extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t 
     S24_REQUIRE(meta != nullptr && H != nullptr, S24_ERR_NULL);
     S24_REQUIRE(s24_aligned(meta, 4) && s24_aligned(H, 16) && s24_aligned(bias, 8), S24_ERR_ALIGN);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (dt != S24_F32 && slice_pays(p, q, 2 * f))
+    if (const S24SlicePlan slices = dt == S24_F32 ? S24SlicePlan{} : slices_if_faster(p, q, 2 * f))
         return s24_slice_nt({static_cast<const uint16_t *>(X), static_cast<const uint16_t *>(vals), meta, static_cast<uint16_t *>(GU),
-                             static_cast<uint16_t *>(H), nullptr, static_cast<const uint16_t *>(bias), p, q, 2 * f, false, S24_SLICE_GLU, gate}, dt, st);
+                             static_cast<uint16_t *>(H), nullptr, static_cast<const uint16_t *>(bias), p, q, 2 * f, false, S24_SLICE_GLU, gate}, slices, dt, st);
     NtTile tile = nt_tile(2 * f, p, q);
     // The small tile has no gated epilogue: it is taken only where it saves more than the pass over Z costs, 2.4 us per million
     // gated features (6 bytes each) less the 1 us that the fused epilogue costs itself.  10041 tokens, 19072 rows, K = 64: fused
@@ -1100,7 +1101,7 @@ extern "C" int s24_spmm_fwd_glu(const void *X, const void *vals, const uint16_t 
         return s24_f32_nt({static_cast<const float *>(X), static_cast<const float *>(vals), meta, static_cast<float *>(GU), static_cast<float *>(H),
                            static_cast<const float *>(bias), p, q, 2 * f, false, S24_F32_GLU, gate}, st);
     // shapes the fused epilogue does not cover: the GEMM into [p][2f], then the stand-alone activation on its halves
-    const int rc2 = launch_spmm(X, vals, meta, GU, p, q, 2 * f, 0.0f, dt, st, bias, false);
+    const int rc2 = launch_spmm(X, vals, meta, GU, p, q, 2 * f, 0.0f, dt, st, bias, {});
     if (rc2 != S24_OK) return rc2;
     return s24_glu_fwd(GU, S24_ROW_MAJOR, 2 * f, H, S24_ROW_MAJOR, f, p, f, gate, dt, st);
 }
@@ -1155,9 +1156,9 @@ extern "C" int s24_spmm_fwd_act(const void *X, const void *vals, const uint16_t 
     S24_REQUIRE(s24_aligned(meta, 4) && s24_aligned(H, 16) && s24_aligned(bias, 8), S24_ERR_ALIGN);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (dt != S24_F32) {
-        if (slice_pays(p, q, r))
+        if (const S24SlicePlan slices = slices_if_faster(p, q, r))
             return s24_slice_nt({static_cast<const uint16_t *>(X), static_cast<const uint16_t *>(vals), meta, static_cast<uint16_t *>(Z),
-                                 static_cast<uint16_t *>(H), nullptr, static_cast<const uint16_t *>(bias), p, q, r, false, S24_SLICE_ACT, act}, dt, st);
+                                 static_cast<uint16_t *>(H), nullptr, static_cast<const uint16_t *>(bias), p, q, r, false, S24_SLICE_ACT, act}, slices, dt, st);
         const NtTile tile = nt_tile(r, p, q);
         const int tiles_m = (int)ceil_div(r, tile.bm()), tiles_n = (int)ceil_div(p, tile.bn());
         S24_REQUIRE((int64_t)tiles_m * tiles_n < (1ll << 30), S24_ERR_SHAPE);
@@ -1192,9 +1193,9 @@ extern "C" int s24_spmm_bwd_dx_act(const void *dY, const void *valsT, const uint
     S24_REQUIRE(s24_aligned(metaT, 4) && s24_aligned(Z, 16), S24_ERR_ALIGN);
     // the 16-bit kernels carry this epilogue; fp32 takes s24_spmm_bwd_dx + s24_act_bwd
     S24_REQUIRE(dt != S24_F32, S24_ERR_UNSUPPORTED);
-    if (bwd_dx_slices(p, r, f))
+    if (const S24SlicePlan slices = bwd_dx_slices(p, r, f))
         return s24_slice_nt({static_cast<const uint16_t *>(dY), static_cast<const uint16_t *>(valsT), metaT, static_cast<uint16_t *>(dZ), nullptr,
-                             static_cast<const uint16_t *>(Z), nullptr, p, r, f, false, S24_SLICE_ACT_BWD, act}, dt, static_cast<hipStream_t>(stream));
+                             static_cast<const uint16_t *>(Z), nullptr, p, r, f, false, S24_SLICE_ACT_BWD, act}, slices, dt, static_cast<hipStream_t>(stream));
     const NtTile tile = nt_tile(f, p, r);
     const int tiles_m = (int)ceil_div(f, tile.bm()), tiles_n = (int)ceil_div(p, tile.bn());
     S24_REQUIRE((int64_t)tiles_m * tiles_n < (1ll << 30), S24_ERR_SHAPE);
@@ -1682,24 +1683,25 @@ extern "C" int s24_spmm_bwd_dx_dw(const void *dY, const void *valsT, const uint1
                            S24_F32_PLAIN, 0}, f, count, st, rc))
             return rc;
     }
-    if (together && dt != S24_F32 && !bwd_dx_slices(p, r, q) && launch_dw_dx(static_cast<const uint16_t *>(dY), static_cast<const uint16_t *>(valsT), metaT,
-                                                                              static_cast<uint16_t *>(dX), p, q, r, problems, count, dt, st))
+    const S24SlicePlan slices = p * q == 0 || dt == S24_F32 ? S24SlicePlan{} : bwd_dx_slices(p, r, q);
+    if (together && dt != S24_F32 && !slices && launch_dw_dx(static_cast<const uint16_t *>(dY), static_cast<const uint16_t *>(valsT), metaT,
+                                                             static_cast<uint16_t *>(dX), p, q, r, problems, count, dt, st))
         return s24_launch_status();
     // 16-bit: where the input gradient runs in slices, one token block to a tile, and the weight gradients in the small tile by eight waves or by
     // four at no more tokens than make these equal
     for (int i = 0; i < count; ++i) together = together && dw_is_small(problems[i]) && problems[i].p <= 1024;
-    int tm = 0;
-    if (together && dt != S24_F32 && bwd_dx_slices(p, r, q) && s24_slice_narrow_tile(p, r, q, tm)) {
+    const S24SlicePlan narrow = together && slices ? s24_slice_plan(p, r, q, 1) : S24SlicePlan{};
+    if (narrow && narrow.us <= 1.3 * slices.us) {
         DwProblem prs[dmatn::kMaxBatch];
         for (int i = 0; i < count; ++i) prs[i] = dw_problem(problems[i]);
         if (dw_few_tile(prs, count) == DwTile::Small) {
             const dmatn::DwBatch batch = shared_batch(prs, count, DwTile::Small);
             s24_dx_dw({static_cast<const uint16_t *>(dY), static_cast<const uint16_t *>(valsT), metaT, static_cast<uint16_t *>(dX), nullptr, nullptr, nullptr, p, r, q,
-                       false, S24_SLICE_PLAIN, 0}, tm, batch, problems[0].W != nullptr, dt, st);
+                       false, S24_SLICE_PLAIN, 0}, narrow.tm, batch, problems[0].W != nullptr, dt, st);
             return s24_launch_status();
         }
     }
-    rc = s24_spmm_bwd_dx(dY, valsT, metaT, dX, p, q, r, 0.0f, dt, stream);
+    rc = launch_spmm(dY, valsT, metaT, dX, p, r, q, 0.0f, dt, st, nullptr, slices);
     return rc != S24_OK ? rc : s24_dense_dw_batch(problems, count, 0.0f, dt, stream);
 }
 

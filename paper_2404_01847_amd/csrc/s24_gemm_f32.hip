@@ -190,13 +190,14 @@ __device__ __forceinline__ void f32_nt_tile(float *s_red, int tile, const float 
     }
 }
 
-// The arguments are one by one and in the order in which they are needed: see FLAGS in build.py.
+// first: B, Av; second: Am, N, K; third: M, F, tiles of features, nothing
+struct NtEnds { float *Out, *H; const float *bias; };
 template <bool SPARSE, bool ACCUM, int EPI, int ACT, int T, int KS>
-__global__ __launch_bounds__(64 * KS) void f32_nt_kernel(const float *B, const float *Av, const uint16_t *Am, int N, int K, int M, int F, int tiles_m,
-                                                         float *Out, float *H, const float *bias)
+__global__ __launch_bounds__(64 * KS) void f32_nt_kernel(const s24_words first, const s24_words second, const s24_words third, const NtEnds e)
 {
     __shared__ __attribute__((aligned(16))) float s_red[lds_floats(T, KS)];
-    f32_nt_tile<SPARSE, ACCUM, EPI, ACT, T, KS>(s_red, (int)blockIdx.x, B, Av, Am, N, K, M, F, tiles_m, Out, H, bias);
+    f32_nt_tile<SPARSE, ACCUM, EPI, ACT, T, KS>(s_red, (int)blockIdx.x, s24_global<const float>(first.x), s24_global<const float>(first.y), s24_global<const uint16_t>(second.x),
+                                                s24_low(second.y), s24_high(second.y), s24_low(third.x), s24_high(third.x), s24_low(third.y), e.Out, e.H, e.bias);
 }
 
 // ------------------------------------------------------------------ TN (weight gradients)
@@ -402,8 +403,8 @@ int launch_nt(const S24F32Nt &g, hipStream_t st)
     const int64_t F = EPI == S24_F32_GLU ? g.M / 2 : g.M;
     const int64_t tiles_m = ceil_div(F, EPI == S24_F32_GLU ? 32 : 32 * T), tiles = tiles_m * ceil_div(g.N, 32 * T);
     S24_REQUIRE(tiles < (1ll << 31), S24_ERR_SHAPE);
-    hipLaunchKernelGGL((f32_nt_kernel<SPARSE, ACCUM, EPI, ACT, T, KS>), dim3((unsigned)tiles), dim3(64 * KS), 0, st, g.B, g.Av, g.Am, (int)g.N, (int)g.K,
-                       (int)g.M, (int)F, (int)tiles_m, g.Out, g.H, g.bias);
+    hipLaunchKernelGGL((f32_nt_kernel<SPARSE, ACCUM, EPI, ACT, T, KS>), dim3((unsigned)tiles), dim3(64 * KS), 0, st, s24_pack(g.B, g.Av), s24_pack(g.Am, (int)g.N, (int)g.K),
+                       s24_pack((int)g.M, (int)F, (int)tiles_m, 0), (NtEnds{g.Out, g.H, g.bias}));
     return s24_launch_status();
 }
 

@@ -17,7 +17,11 @@ struct S24SliceNt {
     S24SliceEpilogue epilogue;
     int act;
 };
-double s24_slice_us(int64_t N, int64_t K, int64_t M);   // what it takes while its operands are in the caches
-// Row blocks of the best tile with one token block, if it costs no more than 1.3 of the best of all
-bool s24_slice_narrow_tile(int64_t N, int64_t K, int64_t M, int &tm);
-int s24_slice_nt(const S24SliceNt &g, int dt, hipStream_t st);
+// Tile of a product, 16 tm features x 16 tn tokens, and what it takes in us while its operands are in the caches; tm = 0: not in slices
+struct S24SlicePlan {
+    int tm, tn;
+    double us;
+    explicit operator bool() const { return tm != 0; }
+};
+S24SlicePlan s24_slice_plan(int64_t N, int64_t K, int64_t M, int max_tn = 4);
+int s24_slice_nt(const S24SliceNt &g, const S24SlicePlan &p, int dt, hipStream_t st);

@@ -18,18 +18,20 @@ namespace {
 
 using s24_slice::KS;
 
-// The arguments are one by one and in the order in which they are needed: see FLAGS in build.py.
+// first: B, Av; second: Am, N, K; third: M, F, tiles of tokens, all tiles
+struct SliceEnds { uint16_t *Out, *H; const uint16_t *Z, *bias; };
 template <typename T, bool ACCUM, int EPI, int ACT, int TM, int TN, bool STREAM>
-__global__ __launch_bounds__(64 * KS, TN == 4 ? 2 : 4) void spmm_slice_kernel(const uint16_t *__restrict__ B, const uint16_t *__restrict__ Av,
-                                                                             const uint16_t *__restrict__ Am, int N, int K, int M, int F, int tiles_n, int tiles,
-                                                                             uint16_t *Out, uint16_t *H, const uint16_t *Z, const uint16_t *bias)
+__global__ __launch_bounds__(64 * KS, TN == 4 ? 2 : 4) void spmm_slice_kernel(const s24_words first, const s24_words second, const s24_words third, const SliceEnds e)
 {
     constexpr int STAGE = s24_slice::stage_bytes(TN);
     __shared__ __attribute__((aligned(16))) unsigned char s0[STAGE];
     __shared__ __attribute__((aligned(16))) unsigned char s1[STAGE];
     __shared__ __attribute__((aligned(16))) unsigned char s2[TN == 1 ? STAGE : 16];
     __shared__ __attribute__((aligned(16))) unsigned char s3[TN == 1 ? STAGE : 16];
-    s24_slice::slice_tile<T, ACCUM, EPI, ACT, TM, TN, STREAM>((s24_lds::lds_byte *)s0, (s24_lds::lds_byte *)s1, (s24_lds::lds_byte *)s2, (s24_lds::lds_byte *)s3, (int)blockIdx.x, B, Av, Am, N, K, M, F, tiles_n, tiles, Out, H, Z, bias);
+    s24_slice::slice_tile<T, ACCUM, EPI, ACT, TM, TN, STREAM>((s24_lds::lds_byte *)s0, (s24_lds::lds_byte *)s1, (s24_lds::lds_byte *)s2, (s24_lds::lds_byte *)s3, (int)blockIdx.x,
+                                                              s24_global<const uint16_t>(first.x), s24_global<const uint16_t>(first.y), s24_global<const uint16_t>(second.x),
+                                                              s24_low(second.y), s24_high(second.y), s24_low(third.x), s24_high(third.x), s24_low(third.y), s24_high(third.y),
+                                                              e.Out, e.H, e.Z, e.bias);
 }
 
 template <typename T, bool ACCUM, int EPI, int ACT, int TM, int TN>
@@ -40,8 +42,8 @@ void launch(const S24SliceNt &g, hipStream_t st)
     const int tiles_m = (int)((feats + FM - 1) / FM), tiles_n = (int)((g.N + 16 * TN - 1) / (16 * TN)), tiles = tiles_m * tiles_n;
     const dim3 grid(((tiles + 7) / 8) * 8), block(64 * KS);
 #define S24_LAUNCH_SLICE(STREAM)                                                                                                            \
-    hipLaunchKernelGGL((spmm_slice_kernel<T, ACCUM, EPI, ACT, TM, TN, STREAM>), grid, block, 0, st, g.B, g.Av, g.Am, (int)g.N, (int)g.K, (int)g.M, \
-                       (int)F, tiles_n, tiles, g.Out, g.H, g.Z, g.bias)
+    hipLaunchKernelGGL((spmm_slice_kernel<T, ACCUM, EPI, ACT, TM, TN, STREAM>), grid, block, 0, st, s24_pack(g.B, g.Av), s24_pack(g.Am, (int)g.N, (int)g.K), \
+                       s24_pack((int)g.M, (int)F, tiles_n, tiles), (SliceEnds{g.Out, g.H, g.Z, g.bias}))
     if constexpr (TN == 1) {
         if (tiles_n == 1) {   // every weight is read once
             S24_LAUNCH_SLICE(true);
@@ -71,38 +73,28 @@ template <typename T, int TM, int TN> int launch_epilogue(const S24SliceNt &g, h
     return s24_launch_status();
 }
 
+}  // namespace
+
 // Tile of a product by its cost in us: a launch, and per round of workgroups over the compute units a filling and draining and so
 // much for each 64 of k (fitted to 380 products, 1-2048 tokens, K = 256-32000, 256-56000 features; half of them within 7 %).
 // Two workgroups to a compute unit count as two rounds: they share its first-level cache, which is what bounds them.
-struct Plan { int tm, tn; double launch, round, chunk, us; };
-Plan plan(int64_t N, int64_t K, int64_t M, int max_tn = 4)
+S24SlicePlan s24_slice_plan(int64_t N, int64_t K, int64_t M, int max_tn)
 {
-    constexpr Plan tiles[5] = {{1, 1, 2.2, 0.25, 0.037, 0}, {2, 1, 2.2, 0.25, 0.060, 0}, {4, 1, 2.3, 0.25, 0.105, 0}, {4, 2, 2.1, 0.48, 0.122, 0}, {4, 4, 1.6, 1.2, 0.170, 0}};
+    struct Tile { int tm, tn; double launch, round, chunk; };
+    constexpr Tile tiles[5] = {{1, 1, 2.2, 0.25, 0.037}, {2, 1, 2.2, 0.25, 0.060}, {4, 1, 2.3, 0.25, 0.105}, {4, 2, 2.1, 0.48, 0.122}, {4, 4, 1.6, 1.2, 0.170}};
     const int64_t cus = s24_cu_count();
-    Plan best{};
-    for (Plan t : tiles) {
+    S24SlicePlan best{};
+    for (const Tile &t : tiles) {
         if (t.tn > max_tn || N <= 16 * (t.tn / 2)) continue;   // half of the tile or more would be empty
         const int64_t n = ((M + 16 * t.tm - 1) / (16 * t.tm)) * ((N + 16 * t.tn - 1) / (16 * t.tn)), rounds = (n + cus - 1) / cus;
-        t.us = t.launch + (double)rounds * (t.round + t.chunk * (double)(K / 64));
-        if (best.tm == 0 || t.us < best.us) best = t;
+        const double us = t.launch + (double)rounds * (t.round + t.chunk * (double)(K / 64));
+        if (!best || us < best.us) best = {t.tm, t.tn, us};
     }
     return best;
 }
 
-}  // namespace
-
-double s24_slice_us(int64_t N, int64_t K, int64_t M) { return plan(N, K, M).us; }
-
-bool s24_slice_narrow_tile(int64_t N, int64_t K, int64_t M, int &tm)
+int s24_slice_nt(const S24SliceNt &g, const S24SlicePlan &p, int dt, hipStream_t st)
 {
-    const Plan p = plan(N, K, M, 1);
-    tm = p.tm;
-    return p.us <= 1.3 * plan(N, K, M).us;
-}
-
-int s24_slice_nt(const S24SliceNt &g, int dt, hipStream_t st)
-{
-    const Plan p = plan(g.N, g.K, g.M);
     auto with = [&](auto t) {
         using T = decltype(t);
         if (p.tm == 1) return launch_epilogue<T, 1, 1>(g, st);

@@ -32,7 +32,7 @@ template <> __device__ __forceinline__ f32x4 mma<s24_half>(uint4 a, Two b, f32x4
 
 // Slices per workgroup.  One number for all shapes: among the products that come here an output's bits depend on K alone, so
 // that a product with and without a fused epilogue agrees to the last bit.  Which products come here depends on their tokens
-// and features too (slice_pays there), and the tiles of s24_gemm.hip sum in another order: a token alone and the same token
+// and features too (slices_if_faster there), and the tiles of s24_gemm.hip sum in another order: a token alone and the same token
 // among thousands, or a stacked weight and its halves, may differ in the last bits.
 constexpr int KS = 8;
 

@@ -530,3 +530,24 @@ def test_matrix_instructions_written_as_asm_keep_their_distances(lib, tmp_path):
             if matrix:
                 assert _asm_hazards(code) == [], name
     assert found > 1000
+
+
+def test_short_kernels_take_few_arguments(lib, tmp_path):
+    """A launch pays on the host for each argument, and a step of a few hundred tokens waits for the host."""
+    import paper_2404_01847_amd as s24
+    readelf = "/opt/rocm/llvm/bin/llvm-readelf"
+    if not os.path.exists(readelf):
+        assert not os.path.exists("/opt/rocm/bin/hipcc"), "a compiler without its readelf: the arguments go uncounted"
+        pytest.skip("no llvm-readelf")
+    counted = {"spmm_slice_kernel": 0, "f32_nt_kernel": 0}
+    for k, code in enumerate(_device_code(s24.lib_path())):
+        obj = tmp_path / f"{k}.co"
+        obj.write_bytes(code)
+        notes = subprocess.run([readelf, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout
+        for kernel in re.split(r"^  - ", notes, flags=re.M):   # one entry of amdhsa.kernels each
+            name = re.search(r"^    \.name: +(\S+)", kernel, flags=re.M)
+            for short in counted:
+                if name and short in name[1]:
+                    counted[short] += 1
+                    assert len(re.findall(r"\.value_kind: +(?!hidden)", kernel)) <= 4, name[1]
+    assert all(counted.values()), counted
