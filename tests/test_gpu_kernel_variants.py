@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import s24_inputs as si
-from util import F32_TOL, assert_close, dev, dev_bf16, host_bits, host_f64, mask_tiles_run, tiles_run, together_run, tol_for, torch_dtype
+from util import F32_TOL, assert_close, dev, dev_bf16, host_bits, host_f64, mask_tiles_run, slices_run, tiles_run, together_run, tol_for, torch_dtype
 
 pytestmark = pytest.mark.gpu
 
@@ -503,7 +503,17 @@ def test_sliced_products_in_the_largest_tile(s24, dtype, pqr):
 
 @pytest.mark.parametrize("q", [1984, 2048])     # slices; the tiles' kernel from 384 tiles of 128 x 128 and this contraction on
 def test_few_tokens_of_many_features_on_either_kernel(s24, q):
-    p, r = 13, 49152
+    few_tokens(s24, 13, q, 49152)
+
+
+# below 64 MB of values and index words, from there on, and 101 MB in the lowest tile
+@pytest.mark.parametrize("q, r, variant", [(4096, 14528, (4, 1, False)), (4096, 14592, (4, 1, True)), (22016, 4096, (1, 1, False))])
+def test_weights_of_few_tokens_past_the_caches_and_through_them(s24, q, r, variant):
+    assert few_tokens(s24, 13, q, r) == [variant]
+
+
+def few_tokens(s24, p, q, r):
+    """The forward products of p tokens against a reference and each other; the variants of the sliced kernel that the plain one ran in."""
     gen = torch.Generator(device="cuda").manual_seed(q)
     rnd = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
     W, x, b = rnd(r, q) * 0.02, rnd(p, q), rnd(r)
@@ -515,7 +525,7 @@ def test_few_tokens_of_many_features_on_either_kernel(s24, q):
     bits = host_bits(mask)[rows[:, None] // 4, np.arange(q)[None] // 4] >> (4 * (rows[:, None] % 4) + np.arange(q)[None] % 4)
     kept = np.where(bits & 1, host_f64(W[torch.from_numpy(rows).cuda()]), 0)
     Y, Z, H, two, GU = new(p, r), new(p, r), new(p, r), new(p, r), new(p, r)
-    s24.spmm_fwd_bias(x, v, m, b, Y)
+    variants = slices_run(lambda: s24.spmm_fwd_bias(x, v, m, b, Y))
     assert_close(host_f64(Y)[:, rows], host_f64(x) @ kept.T + host_f64(b)[rows], tol_for("bf16"), f"spmm_fwd_bias {q}")
     s24.spmm_fwd_act(x, v, m, b, Z, H, s24.ACT_GELU_ERF)
     s24.act_fwd(Y, two, s24.ACT_GELU_ERF)
@@ -524,6 +534,7 @@ def test_few_tokens_of_many_features_on_either_kernel(s24, q):
     s24.spmm_fwd_glu(x, v, m, b, GU, Hg, s24.GATE_SILU)
     s24.glu_fwd(Y, two, s24.GATE_SILU)
     assert torch.equal(GU.view(torch.int16), Y.view(torch.int16)) and torch.equal(Hg.view(torch.int16), two.view(torch.int16))
+    return variants
 
 
 def test_calls_go_to_the_current_stream(s24):

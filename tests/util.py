@@ -146,6 +146,13 @@ def tiles_run(call):
     return tiles
 
 
+def slices_run(call):
+    """The variants of the sliced kernel that `call` launches, in order: row blocks and token blocks of 16 to a tile, and whether the weights go
+    past the caches."""
+    found = [re.search(r"spmm_slice_kernel.*?(\d+), (\d+), (?:(true|false)>\(|Lb([01])EEv)", name) for name in _kernels_run(call)]
+    return [(int(m[1]), int(m[2]), m[3] == "true" or m[4] == "1") for m in found if m]
+
+
 def together_run(call):
     """Whether the input gradient and the weight gradients that `call` computes share a launch."""
     return any(re.search(r"dx_dw_kernel|dw_dx_kernel|f32_nt_tn_kernel", name) for name in _kernels_run(call))
