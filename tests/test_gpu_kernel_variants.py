@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import s24_inputs as si
-from util import F32_TOL, assert_close, dev, dev_bf16, host_bits, host_f64, mask_tiles_run, slices_run, tiles_run, together_run, tol_for, torch_dtype
+from util import F32_TOL, assert_close, dev, dev_bf16, host_bits, host_f64, joint_run, mask_tiles_run, slices_run, tiles_run, tol_for, torch_dtype
 
 pytestmark = pytest.mark.gpu
 
@@ -456,11 +456,15 @@ def test_medium_tile_and_its_epilogues(s24, dtype, pqr):
 
 # ------------------------------------------------------------------ sparse products in slices of the contraction
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-# (p, q, r): one chunk (seven idle slices), one feature block; a slice more or less than the others and the load pipeline's
-# remainders (9, 31, 65 and 68 chunks); each of the four tiles, ragged along both axes
-@pytest.mark.parametrize("pqr", [(1, 64, 16), (16, 576, 48), (15, 1984, 4112), (3, 4160, 272), (33, 4352, 2080), (17, 640, 4128),
-                                 (130, 2112, 1040), (257, 512, 1056), (61, 1088, 4112)])
-def test_sliced_products_and_their_epilogues(s24, dtype, pqr):
+# (p, q, r) and the tile: one chunk (seven idle slices), one feature block; a slice more or less than the others and the load pipeline's
+# remainders (9, 31, 65 and 68 chunks); each of the smaller four tiles, ragged along both axes
+@pytest.mark.parametrize("pqr, tile", [((1, 64, 16), (1, 1)), ((16, 576, 48), (1, 1)), ((15, 1984, 4112), (2, 1)), ((3, 4160, 272), (1, 1)), ((33, 4352, 2080), (2, 1)), ((17, 640, 4128), (4, 1)),
+                                       ((130, 2112, 1040), (4, 1)), ((257, 512, 1056), (4, 2)), ((61, 1088, 4112), (4, 2))])
+def test_sliced_products_and_their_epilogues(s24, dtype, pqr, tile):
+    sliced_products_and_their_epilogues(s24, dtype, pqr, tile)
+
+
+def sliced_products_and_their_epilogues(s24, dtype, pqr, tile):
     p, q, r = pqr
     r64 = (r + 63) // 64 * 64
     W, X = si.random_matrix(80 + q, (r64, q), 0.02, dtype), si.random_matrix(81 + p, (p, q), 1.0, dtype)
@@ -472,7 +476,7 @@ def test_sliced_products_and_their_epilogues(s24, dtype, pqr):
     new = lambda n: torch.full((p, n), 7.0, dtype=torch_dtype(dtype), device="cuda")
     bits = lambda t: t.view(torch.int16)
     Y, Yb, Z, H, dZ, two = (new(r) for _ in range(6))
-    s24.spmm_fwd(x, v, m, Y)
+    assert slices_run(lambda: s24.spmm_fwd(x, v, m, Y)) == [(*tile, False)]
     assert_close(host_f64(Y), ref, tol, f"spmm_fwd {pqr}")
     Y2 = Y.clone()
     s24.spmm_bwd_dx(x, v, m, Y2, beta=1.0)
@@ -498,7 +502,7 @@ def test_sliced_products_and_their_epilogues(s24, dtype, pqr):
 # (p, q, r) of the 64 x 64 tile: of three to five chunks to a wave, and of one or two; ragged along both axes, by one token and by 16 features
 @pytest.mark.parametrize("pqr", [(513, 1984, 1040), (193, 2112, 3104), (500, 576, 1616)])
 def test_sliced_products_in_the_largest_tile(s24, dtype, pqr):
-    test_sliced_products_and_their_epilogues(s24, dtype, pqr)
+    sliced_products_and_their_epilogues(s24, dtype, pqr, (4, 4))
 
 
 @pytest.mark.parametrize("q", [1984, 2048])     # slices; the tiles' kernel from 384 tiles of 128 x 128 and this contraction on
@@ -932,42 +936,77 @@ def backward_operands(s24, p, q, r, dtype, seed, f=None):
 
 # fp32 (p, q, r): 32-tiles in eight slices with four, one and two batches of tokens in flight; a chain of a few tokens and a contraction of four slices, which
 # run in turn; ragged in every direction
-BACKWARD = [("f32", s) for s in [(512, 256, 1024), (100, 128, 512), (1200, 192, 576), (1200, 192, 1344), (7, 64, 512), (130, 64, 448), (515, 320, 1088)]]
-# 16-bit: slices of four, one and two row blocks; one token, less than a step of 32, a step and a rest, a ring of whole steps, many whole steps and a
+BACKWARD = [("f32", s, k and ("f32", k)) for s, k in [((512, 256, 1024), 4), ((100, 128, 512), 1), ((1200, 192, 576), 4), ((1200, 192, 1344), 2), ((7, 64, 512), None),
+                                                      ((130, 64, 448), None), ((515, 320, 1088), 1)]]
+# 16-bit: slices of four, two and one row blocks; one token, less than a step of 32, a step and a rest, a ring of whole steps, many whole steps and a
 # rest of one token
-BACKWARD += [("bf16", s) for s in [(256, 768, 3072), (200, 512, 1344), (1, 64, 128), (128, 128, 448), (704, 128, 448), (705, 128, 448)]]
-BACKWARD += [("f16", s) for s in [(100, 512, 1408), (31, 256, 1024), (257, 320, 1088)]]
+BACKWARD += [("bf16", s, ("slices", k)) for s, k in [((256, 768, 3072), 4), ((200, 512, 1344), 2), ((1, 64, 128), 1), ((128, 128, 448), 1), ((704, 128, 448), 2), ((705, 128, 448), 2)]]
+BACKWARD += [("f16", s, ("slices", k)) for s, k in [((100, 512, 1408), 1), ((31, 256, 1024), 1), ((257, 320, 1088), 2)]]
 
 # 16-bit, whole grids (p, q, r, f): tiles of 192 x 128, of 256 x 256 in a part of a round and in two and a strip, of 256 x 128; ragged in every direction
-BACKWARD += [("bf16", s) for s in [(8192, 768, 3072), (2475, 1408, 3776), (3001, 2048, 11008, 5504), (3083, 576, 4608, 2304)]]
-BACKWARD += [("f16", s) for s in [(5939, 896, 2368), (1795, 640, 4480, 2240)]]
+BACKWARD += [("bf16", s, ("grid", *k, 32)) for s, k in [((8192, 768, 3072), (3, 2)), ((2475, 1408, 3776), (4, 4)), ((3001, 2048, 11008, 5504), (4, 4)), ((3083, 576, 4608, 2304), (4, 2))]]
+BACKWARD += [("f16", s, ("grid", *k, 32)) for s, k in [((5939, 896, 2368), (3, 2)), ((1795, 640, 4480, 2240), (4, 2))]]
+
+
+def compare_with_two_calls(s24, dZ, vT, mT, dX, problems, variant):
+    """One call in the expected variant against the two that it stands for: the same bits."""
+    outputs = [dX, *(pr[2] for pr in problems)]
+    kept = [t.clone() for t in outputs]
+    assert joint_run(lambda: s24.spmm_bwd_dx_dw(dZ, vT, mT, dX, problems)) == variant
+    got = [t.clone() for t in outputs]
+    for t, k in zip(outputs, kept):
+        t.copy_(k)
+    s24.spmm_bwd_dx(dZ, vT, mT, dX)
+    tiles = tiles_run(lambda: s24.dense_dw_batch(problems))
+    for a, b in zip(got, outputs):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    if variant and variant[0] == "grid":   # priced as the tile that the gradients take by themselves (their strip, if they have one, comes second)
+        assert variant[1:] == tiles[0]
 
 
 @pytest.mark.parametrize("decay", [True, False])
-@pytest.mark.parametrize("dtype, pqr", BACKWARD)
-def test_input_and_weight_gradients_in_one_call_have_the_bits_of_two(s24, dtype, pqr, decay):
+@pytest.mark.parametrize("dtype, pqr, variant", BACKWARD)
+def test_input_and_weight_gradients_in_one_call_have_the_bits_of_two(s24, dtype, pqr, variant, decay):
     p, q, r, *f = pqr
     dZ, vT, mT, dX, grads, problems, _ = backward_operands(s24, p, q, r, dtype, p + r, *f)
-    in_turn = dtype == "f32" and pqr in ((7, 64, 512), (130, 64, 448))
-    assert together_run(lambda: s24.spmm_bwd_dx_dw(dZ, vT, mT, dX, problems(decay))) == (not in_turn)
-    got = [t.clone() for t in (dX, *grads)]
-    for t in (dX, *grads):
-        t.fill_(7)
-    s24.spmm_bwd_dx(dZ, vT, mT, dX)
-    s24.dense_dw_batch(problems(decay))
-    for a, b in zip(got, (dX, *grads)):
-        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    compare_with_two_calls(s24, dZ, vT, mT, dX, problems(decay), variant)
 
 
-@pytest.mark.parametrize("dtype, pqr", [("f32", (512, 256, 1024)), ("bf16", (256, 768, 3072))])
-def test_an_input_gradient_over_an_operand_of_a_weight_gradient_comes_first(s24, dtype, pqr):
-    """In place of X, which a weight gradient reads: as the two calls in their order."""
+# a gradient alone, three and four of them
+@pytest.mark.parametrize("dtype, pqr, count, variant", [("f32", (512, 256, 1024), 1, ("f32", 4)), ("f32", (512, 256, 1024), 3, ("f32", 1)), ("f32", (100, 128, 512), 4, ("f32", 1)),
+                                                        ("bf16", (256, 768, 3072), 1, ("slices", 4)), ("bf16", (200, 512, 1344), 3, ("slices", 2)), ("f16", (100, 512, 1408), 4, ("slices", 1)),
+                                                        ("bf16", (8192, 768, 3072), 1, None), ("bf16", (4097, 768, 2048), 3, ("grid", 3, 2, 32)), ("f16", (4097, 768, 2048), 4, ("grid", 4, 2, 32))])
+def test_one_to_four_weight_gradients_beside_an_input_gradient(s24, dtype, pqr, count, variant):
+    dZ, vT, mT, dX, grads, problems, _ = backward_operands(s24, *pqr, dtype, 7)
+    more = [(*pr[:2], torch.empty_like(pr[2]), *pr[3:]) for pr in problems(True)]
+    compare_with_two_calls(s24, dZ, vT, mT, dX, (problems(True) + more)[:count], variant)
+
+
+@pytest.mark.parametrize("dtype, pqr, odd", [(*c, o) for c in (("f32", (512, 256, 1024)), ("bf16", (256, 768, 3072)), ("bf16", (8192, 768, 3072))) for o in ("decay on one", "an empty one")] +
+                         [("f32", (512, 256, 1024), "one gradient twice")])   # 16-bit problems of one grid must not overlap
+def test_gradients_that_share_no_grid_run_in_turn(s24, dtype, pqr, odd):
+    dZ, vT, mT, dX, grads, problems, X = backward_operands(s24, *pqr, dtype, 9)
+    first, second = problems(True)
+    if odd == "decay on one":
+        second = (*second[:3], None, None, 0.0)
+    elif odd == "an empty one":
+        second = (dZ, X[:, :0].contiguous(), second[2][:, :0].contiguous(), *second[3:])
+    else:
+        second = (2 * first[0], *first[1:])
+    compare_with_two_calls(s24, dZ, vT, mT, dX, [first, second], None)
+
+
+@pytest.mark.parametrize("dtype, pqr", [("f32", (512, 256, 1024)), ("bf16", (256, 768, 3072)), ("bf16", (8192, 768, 3072))])
+@pytest.mark.parametrize("over", ["X", "H", "dY"])
+def test_an_input_gradient_over_an_operand_of_a_weight_gradient_comes_first(s24, dtype, pqr, over):
+    """In place of what a weight gradient reads: as the two calls in their order."""
     dZ, vT, mT, dX, grads, problems, X = backward_operands(s24, *pqr, dtype, 5)
-    kept = X.clone()
-    s24.spmm_bwd_dx(dZ, vT, mT, X)
+    target = {"X": X, "H": problems(True)[0][1].view(-1)[:X.numel()].view(X.shape), "dY": problems(True)[0][0]}[over]
+    kept = target.clone()
+    s24.spmm_bwd_dx(dZ, vT, mT, target)
     s24.dense_dw_batch(problems(True))
-    want = [t.clone() for t in (X, *grads)]
-    X.copy_(kept)
-    s24.spmm_bwd_dx_dw(dZ, vT, mT, X, problems(True))
-    for a, b in zip(want, (X, *grads)):
+    want = [t.clone() for t in (target, *grads)]
+    target.copy_(kept)
+    assert joint_run(lambda: s24.spmm_bwd_dx_dw(dZ, vT, mT, target, problems(True))) is None
+    for a, b in zip(want, (target, *grads)):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))

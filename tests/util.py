@@ -149,10 +149,21 @@ def tiles_run(call):
 def slices_run(call):
     """The variants of the sliced kernel that `call` launches, in order: row blocks and token blocks of 16 to a tile, and whether the weights go
     past the caches."""
-    found = [re.search(r"spmm_slice_kernel.*?(\d+), (\d+), (?:(true|false)>\(|Lb([01])EEv)", name) for name in _kernels_run(call)]
+    found = [re.search(r"spmm_slice_kernel.*?(\d+), (\d+), (?:(true|false)>\(|Lb([01])EEEv)", name) for name in _kernels_run(call)]
     return [(int(m[1]), int(m[2]), m[3] == "true" or m[4] == "1") for m in found if m]
 
 
-def together_run(call):
-    """Whether the input gradient and the weight gradients that `call` computes share a launch."""
-    return any(re.search(r"dx_dw_kernel|dw_dx_kernel|f32_nt_tn_kernel", name) for name in _kernels_run(call))
+def joint_run(call):
+    """The variant of the kernel in which `call` computes an input gradient and weight gradients together, or None if it computes them in turn:
+    fp32 with the batches of tokens in flight, slices with the row blocks of the input gradient's tile, grid with the weight gradients' tile (see
+    tiles_run)."""
+    found = []
+    for name in _kernels_run(call):
+        if m := re.search(r"f32_nt_tn_kernel<(\d+)>", name):
+            found.append(("f32", int(m[1])))
+        elif m := re.search(r"dx_dw_kernel.*?(\d+)(?:>\(|, EEv)", name):
+            found.append(("slices", int(m[1])))
+        elif m := re.search(r"dw_dx_kernel.*?Cfg(?:<|I)(\d+), (\d+), (\d+)", name):
+            found.append(("grid", *map(int, m.groups())))
+    assert len(found) <= 1, found
+    return found[0] if found else None
