@@ -308,6 +308,387 @@ constexpr int spmm_stage(int MI, int WN) { return 64 * WN * 128 + 64 * MI * (64 
 // T is the storage type of every 16-bit buffer (bf16 bits or binary16).
 // BIAS compiles the bias add into the plain forward kernel (the gated forward tests the pointer at run time; the
 // plain kernel without a bias keeps its register budget, which the extra loads would push into scratch).
+// The tile of workgroup `block`; s0 .. s2: spmm_stage(MI, WN) bytes of LDS each.  (One array per ring stage, and this in line: the compiler then knows which
+// stage a direct-to-LDS copy writes and does not make reads of the other stages wait for it.)
+template <typename T, bool ACCUM, bool SWIGLU, bool GATE_BWD, int GATE, bool BIAS, int ACT_MODE, int ACT, int MI, int WN>
+__device__ __forceinline__ void spmm_nt_tile(unsigned char *s0, unsigned char *s1, unsigned char *s2, unsigned block, const uint16_t *__restrict__ B,
+                                             const uint16_t *__restrict__ Av, const uint16_t *__restrict__ Am, uint16_t *__restrict__ Out, int N, int K,
+                                             int M, int tiles_m, int tiles_n, unsigned long long *probe, uint16_t *__restrict__ H, int F,
+                                             const uint16_t *__restrict__ GU, const uint16_t *__restrict__ bias)
+{
+    static_assert(!(ACCUM && (SWIGLU || GATE_BWD)) && !(SWIGLU && GATE_BWD), "the gated epilogues overwrite");
+    static_assert(ACT_MODE == 0 || !(ACCUM || SWIGLU || GATE_BWD), "one epilogue at a time");
+    // MI = accumulator blocks per wave along m, WN = waves along n (two along m).  MI 4, WN 4: the 256 x 256 tile of eight
+    // waves (128 x 64 each).  MI 2, WN 2: a 128 x 128 tile of four waves (64 x 64 each) on 25 KB stages, two workgroups
+    // per compute unit; every epilogue but the gated ones.  MI 4, WN 2: a 256 (m) x 128 (n) tile of four waves (128 x 64
+    // each) on 34 KB stages.  The two smaller ones are for outputs with too few large tiles to fill the chip.  What
+    // bounds them is LDS: a chunk of the small tile is 25 KB written and 50 KB read, 600 cycles at 128 bytes each, of
+    // which the matrix cores need 256; the medium one has 34 + 68 KB for twice the work.
+    static_assert((MI == 4 && (WN == 4 || WN == 2)) || (MI == 2 && WN == 2 && !SWIGLU && !GATE_BWD), "the small tile has no gated epilogue");
+    constexpr int BM = 64 * MI, BN = 64 * WN, WM = 32 * MI;   // workgroup tile, wave tile along m
+    constexpr int NA = 2 * MI / WN, NX = MI / WN, NC = 4 + NA + NX;   // copies per lane and chunk: values, index words, all
+    constexpr int B_STAGE = BN * 128, A_STAGE = BM * 64, M_STAGE = BM * 8, STAGE = B_STAGE + A_STAGE + M_STAGE;
+    const ClockStamp t_start = clock_now();
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
+    const int wm = wave & 1, wn = wave >> 1;
+    // Workgroups are dealt round-robin to the eight XCDs; give each XCD one contiguous
+    // slab of the tile grid and walk it in groups of eight n-tiles so that the
+    // workgroups resident on one XCD share operand rows in its L2.
+    const int total = tiles_m * tiles_n, per_xcd = (total + 7) / 8;
+    const int t = (int)(block & 7) * per_xcd + (int)(block >> 3);
+    if (t >= total) return;
+    constexpr int GROUP = 4;   // 4 token tiles x 8 feature tiles resident per XCD: least unique bytes per round
+    const int group_sz = GROUP * tiles_m, grp = t / group_sz, in_grp = t - grp * group_sz;
+    const int gw = min(GROUP, tiles_n - grp * GROUP);
+    const int tm = in_grp / gw, tn = grp * GROUP + in_grp % gw;
+    const int m0 = SWIGLU ? tm * 128 : tm * BM, n0 = tn * BN;   // SWIGLU: m0 = first feature of the tile
+    const int nk = K / 64;
+    // row of the compressed operand behind tile row i (clamped at the edge; such rows are never stored)
+    auto a_row = [&](int i) {
+        if (SWIGLU) return (i < 128 ? 0 : F) + min(m0 + (i & 127), F - 1);
+        return min(m0 + i, M - 1);
+    };
+
+    // Sources of the direct-to-LDS copies: a wave-uniform base per operand (advanced by one chunk per stage, in
+    // scalar registers: the base of a buffer descriptor) plus a fixed 32-bit byte offset per lane, so that seven
+    // copies cost seven address registers and no vector arithmetic
+    const char *baseB = reinterpret_cast<const char *>(B + (int64_t)n0 * K);
+    const char *baseV = reinterpret_cast<const char *>(Av), *baseM = reinterpret_cast<const char *>(Am);
+    uint32_t ob[4], oa[NA], om[NX];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row = 32 * wave + 8 * i + (lane >> 3);
+        const int c = (lane & 7) ^ ((row >> 1) & 7);
+        ob[i] = ((uint32_t)(min(n0 + row, N - 1) - n0) * (uint32_t)K + 8u * c) * 2u;   // a tile's rows span < 4 GB (host check)
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int row = 16 * NA * wave + 16 * i + (lane >> 2);
+        const int c = (lane & 3) ^ a_swizzle(row);
+        oa[i] = ((uint32_t)a_row(row) * 32u + 8u * c) * 2u;
+    }
+    // index words: 4-byte direct-to-LDS copies (copy i: row 32 * (NX * wave + i) + lane/2, dword lane%2)
+#pragma unroll
+    for (int i = 0; i < NX; ++i) om[i] = ((uint32_t)a_row(32 * (NX * wave + i) + (lane >> 1)) * 4u + 2u * (lane & 1)) * 2u;
+    // Copy c of a chunk's NC per lane: four of the dense operand, NA of the values, NX of the index words.  Every chunk
+    // issues all of them, so the wait counts below are constants; past the last chunk the last one is read again into a
+    // stage nobody will read.  pb, pv, pm: the operands at the chunk.
+    const char *pb = baseB, *pv = baseV, *pm = baseM;
+    auto issue = [&](unsigned char *st, int c) {
+        if (c < 4) buffer_to_lds<16>(buffer_of(pb), (lds_ptr)(st + (32 * wave + 8 * c) * 128), ob[c]);
+        else if (c < 4 + NA) buffer_to_lds<16>(buffer_of(pv), (lds_ptr)(st + B_STAGE + 16 * (NA * wave + c - 4) * 64), oa[c - 4]);
+        else buffer_to_lds<4>(buffer_of(pm), (lds_ptr)(st + B_STAGE + A_STAGE + 256 * (NX * wave + c - 4 - NA)), om[c - 4 - NA]);
+    };
+    // Copy c of the chunk after next but one goes out beside the copy_slot(c)-th matrix instruction from the start of phase B
+    // (see the main loop), EARLY of them in that phase and the rest in phase A of the next chunk: spread over all of a
+    // chunk's 8 MI instructions, not its second half, the copies queue less (28672 features, K = 8192: 1627 -> 1575 us, and
+    // with the waves in phase B preferred, whose copies are the next to be waited for, 1566; twice as dense instead: 1740).
+    constexpr auto copy_slot = [](int c) { return c * 8 * MI / NC; };
+    constexpr int EARLY = (NC + 1) / 2;
+    const int64_t step_v = (int64_t)M * 64, step_m = (int64_t)M * 8;
+    auto advance = [&](int kc) {   // to chunk kc, or not past the last one
+        if (kc < nk) { pb += 128; pv += step_v; pm += step_m; }
+    };
+    auto issue_all = [&](unsigned char *st, int kc) {
+        if (kc > 0) advance(kc);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) issue(st, c);
+    };
+
+    f32x4 acc[2 * MI][4];
+#pragma unroll
+    for (int mi = 0; mi < 2 * MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < 4; ++ni) acc[mi][ni] = f32x4{};
+
+    // Fragments of a stage: tokens 16 ni .. of the wave, whole 64-chunk (two LDS reads); features 16 mi .. (one read)
+    const int l16 = lane & 15, g = lane >> 4;
+    auto load_b = [&](const unsigned char *st, int ni, int h) {
+        return *reinterpret_cast<const uint4 *>(st + 2048 * ni + b_slot(64 * wn + l16, 4 * h + g));
+    };
+    auto load_a = [&](const unsigned char *st, int mi) {
+        return as_bf16x8(*reinterpret_cast<const uint4 *>(st + B_STAGE + 1024 * mi + a_slot(WM * wm + l16, g)));
+    };
+    // the index words of feature blocks 2i and 2i + 1: a lane reads a dword of each (32 of k, two words) and packs its half of both
+    const uint32_t half_sel = (g & 1) ? 0x07060302u : 0x05040100u;
+    auto load_index = [&](const unsigned char *st, int i) {
+        const unsigned char *p = st + B_STAGE + A_STAGE + 256 * i + (WM * wm + l16) * 8 + 4 * (g >> 1);
+        return make_uint2(*reinterpret_cast<const uint32_t *>(p), *reinterpret_cast<const uint32_t *>(p + 128));
+    };
+    auto pack_index = [&](uint2 d) { return __builtin_amdgcn_perm(d.y, d.x, half_sel); };
+
+    // The activation's table, where it serves: H's fits beside the ring of the two larger tiles and is computed under the first copies,
+    // the other ones lie in the part of the drained ring that parks no tile.
+    typedef ActTable<ACT_MODE, ACT> Table;
+    constexpr bool TABLE = ACT_MODE != 0 && ACT == S24_ACT_GELU_ERF && std::is_same_v<T, uint16_t>;
+    constexpr bool EARLY_TABLE = TABLE && ACT_MODE == 1 && MI == 4;
+    constexpr int PARKED = MI == 4 && WN == 4 ? 2 * EWAVE : 0;   // in s2
+    static_assert(!TABLE || EARLY_TABLE || PARKED + Table::BYTES <= STAGE, "the table must fit");
+    typename Table::entry *table = reinterpret_cast<typename Table::entry *>(s2 + PARKED);
+    if constexpr (EARLY_TABLE) {
+        __shared__ typename Table::entry s_table[2 * Table::COUNT];
+        table = s_table;
+    }
+
+    // keep the program order of these groups: the constant wait counts rely on it
+    issue_all(s0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    issue_all(s1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    advance(2);
+#pragma unroll
+    for (int c = 0; c < EARLY; ++c) issue(s2, c);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (EARLY_TABLE) Table::template build<128 * WN>(table, tid);
+    wait_and_barrier<NC + EARLY>();   // chunk 0 has landed for everybody
+    uint4 fb[4][2];      // token fragments of the chunk about to be multiplied, first-half feature fragments and index words
+    bf16x8 fa0[MI];
+    uint32_t ix[MI];     // of feature blocks 2i and 2i + 1; the first half of them on entry to a chunk
+#pragma unroll
+    for (int i = 0; i < MI / 2; ++i) ix[i] = pack_index(load_index(s0, i));
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) fa0[mi] = load_a(s0, mi);
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) fb[ni][h] = load_b(s0, ni, h);
+    mma_tie<0, MI / 2>(ix);
+    mma_tie<ACC_VGPR>(acc);
+    mma_operands();
+
+    // One chunk, software-pipelined across the workgroup barrier.  On entry the token fragments of chunk kc and the first
+    // half of its feature fragments are in registers.  Phase A: their 4 MI matrix instructions, with the LDS reads of the
+    // second half's features between them.  Then the one barrier of the chunk: every wave has read all it needs of chunk
+    // kc's stage, and chunk kc+1 (copied two chunks ago) has landed for everybody.  Phase B: the second half's
+    // matrix instructions, whose operands are already in registers -- so the matrix unit has work while
+    // the fragments of chunk kc+1 come in from LDS, the token fragments each into the registers of the one that has just had its
+    // last use, and the copies of chunk kc+3 begin to go out into the stage chunk kc just vacated (one at a time, see copy_slot;
+    // the others in phase A of the next chunk).  A barrier at the
+    // top of the chunk instead, with nothing in registers, exposed the LDS latency of twelve reads per wave once per chunk.
+    auto chunk = [&](unsigned char *cur, const unsigned char *nxt, unsigned char *prv, int kc) {
+        bf16x8 fa1[MI];
+        uint2 raw[MI / 2];
+        auto multiply = [&](const bf16x8 (&a)[MI], int first, int i) {   // the i-th matrix instruction of a phase
+            const int ni = i / MI, j = i % MI, b = (ni & 1) ? MI - 1 - j : j, mi = first + b;
+            if (mi & 1) Mma<T>::template sparse16<1>(a[b], as_bf16x16(fb[ni][0], fb[ni][1]), acc[mi][ni], ix[mi / 2]);
+            else Mma<T>::template sparse16<0>(a[b], as_bf16x16(fb[ni][0], fb[ni][1]), acc[mi][ni], ix[mi / 2]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+#pragma unroll
+        for (int i = 0; i < 4 * MI; ++i) {
+            multiply(fa0, 0, i);
+            if (i < MI) fa1[i] = load_a(cur, MI + i);
+            if (i >= MI && i < MI + MI / 2) raw[i - MI] = load_index(cur, MI / 2 + i - MI);
+#pragma unroll
+            for (int c = EARLY; c < NC; ++c)
+                if (copy_slot(c) - 4 * MI == i) issue(prv, c);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = 0; i < MI / 2; ++i) ix[MI / 2 + i] = pack_index(raw[i]);
+        mma_tie<MI / 2, MI / 2>(ix);   // the wait and the barrier below are the wait states
+        advance(kc + 3);
+        // all but the NC most recent copies (chunk kc+2) are complete: this lane's part of chunk kc+1 is in LDS,
+        // and its own LDS reads of chunk kc are done
+        wait_and_barrier<NC>();
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int i = 0; i < 4 * MI; ++i) {
+            multiply(fa1, MI, i);
+            if (i < MI) fa0[i] = load_a(nxt, i);
+            if (i >= MI / 2 && i < MI) raw[i - MI / 2] = load_index(nxt, i - MI / 2);
+            if (i % MI == (i + 1 < 4 * MI ? 0 : MI - 1) && i >= MI) {   // a token block is done: its successor's two reads
+                const int ni = i + 1 < 4 * MI ? i / MI - 1 : 3;
+                if (i + 1 == 4 * MI) __builtin_amdgcn_sched_barrier(0);
+                fb[ni][0] = load_b(nxt, ni, 0);
+                fb[ni][1] = load_b(nxt, ni, 1);
+            }
+#pragma unroll
+            for (int c = 0; c < EARLY; ++c)
+                if (copy_slot(c) == i) issue(cur, c);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = 0; i < MI / 2; ++i) ix[i] = pack_index(raw[i]);
+        mma_tie<0, MI / 2>(ix);
+        mma_operands();
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // past the last chunk the prefetched fragments come from a stage that holds a re-read of the last chunk (or
+    // is being refilled with one); they are never multiplied
+    int kc = 0;
+    for (; kc + 3 <= nk; kc += 3) {
+        chunk(s0, s1, s2, kc);
+        chunk(s1, s2, s0, kc + 1);
+        chunk(s2, s0, s1, kc + 2);
+    }
+    if (kc < nk) chunk(s0, s1, s2, kc);
+    if (kc + 1 < nk) chunk(s1, s2, s0, kc + 1);
+    mma_drain<ACC_VGPR>(acc);
+    // drain the copies still in flight, then reuse the ring as a staging area for the output tile
+    wait_and_barrier<0>();
+    clock_report(probe, t_start);
+    if constexpr (ACCUM) {
+        // beta = 1: add the old output in fp32 straight from the accumulators (a single rounding)
+#pragma unroll
+        for (int ni = 0; ni < 4; ++ni) {
+            const int n = n0 + 64 * wn + 16 * ni + l16;
+            if (n >= N) continue;
+#pragma unroll
+            for (int mi = 0; mi < 2 * MI; ++mi) {
+                const int m = m0 + WM * wm + 16 * mi + 4 * g;
+                if (m >= M) continue;
+                uint2 *dst = reinterpret_cast<uint2 *>(Out + (int64_t)n * M + m);
+                const uint2 old = *dst;
+                *dst = make_uint2(s24_num<T>::pack2(acc[mi][ni][0] + s24_num<T>::lo(old.x), acc[mi][ni][1] + s24_num<T>::hi(old.x)),
+                                  s24_num<T>::pack2(acc[mi][ni][2] + s24_num<T>::lo(old.y), acc[mi][ni][3] + s24_num<T>::hi(old.y)));
+            }
+        }
+        return;
+    }
+    // a wave's parking area for its output tile (64 rows of 64 MI bytes) in the drained ring
+    static_assert((WN == 4 ? 3 : 2) * (EWAVE * MI / 4) <= STAGE, "wave tiles must fit the ring stages");
+    auto region = [&](int w) {
+        if constexpr (MI == 4 && WN == 2) return (w < 2 ? s0 : s1) + (w & 1) * EWAVE;
+        else if constexpr (MI == 4) return (w < 3 ? s0 : (w < 6 ? s1 : s2)) + (w % 3) * EWAVE;
+        else return (w < 2 ? s0 : s1) + (w & 1) * (EWAVE / 2);
+    };
+    if constexpr (SWIGLU) {
+        if (bias != nullptr) add_bias<T, MI>(acc, bias + (wm ? F : 0) + m0, F - m0, lane);   // wave-uniform
+    } else if constexpr (BIAS) {
+        add_bias<T, MI>(acc, bias + m0 + WM * wm, M - (m0 + WM * wm), lane);   // launched only with a bias
+    }
+    if constexpr (GATE_BWD) {
+        unsigned char *est = region(wave);
+        stage_tile<T, 4>(acc, est, lane);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));   // the wave reads back only what it wrote itself
+        asm volatile("" ::: "memory");
+        const int n_base = n0 + 64 * wn, m_base = m0 + 128 * wm;
+        // the accumulators are dead now: all 32 loads of G and U go out before anything is computed
+        const int c = lane & 15, m = min(m_base + 8 * c, M - 8);
+        uint4 g[16], u[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int64_t o = (int64_t)min(n_base + 4 * j + (lane >> 4), N - 1) * 2 * M + m;
+            g[j] = s24_load_stream(GU + o);
+            u[j] = s24_load_stream(GU + o + M);
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int nl = 4 * j + (lane >> 4), n = n_base + nl;
+            const uint4 dh = staged_chunk(est, nl, c);
+            const uint32_t dw[4] = {dh.x, dh.y, dh.z, dh.w}, gw[4] = {g[j].x, g[j].y, g[j].z, g[j].w};
+            const uint32_t uw[4] = {u[j].x, u[j].y, u[j].z, u[j].w};
+            uint32_t dgw[4], duw[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                float dg0, du0, dg1, du1;
+                s24_glu_grad<GATE>(s24_num<T>::lo(dw[k]), s24_num<T>::lo(gw[k]), s24_num<T>::lo(uw[k]), dg0, du0);
+                s24_glu_grad<GATE>(s24_num<T>::hi(dw[k]), s24_num<T>::hi(gw[k]), s24_num<T>::hi(uw[k]), dg1, du1);
+                dgw[k] = s24_num<T>::pack2(dg0, dg1);
+                duw[k] = s24_num<T>::pack2(du0, du1);
+            }
+            if (n < N && m_base + 8 * c < M) {   // M is a multiple of 16: a chunk is all in or all out
+                const int64_t o = (int64_t)n * 2 * M + m;
+                *reinterpret_cast<uint4 *>(Out + o) = make_uint4(dgw[0], dgw[1], dgw[2], dgw[3]);
+                *reinterpret_cast<uint4 *>(Out + o + M) = make_uint4(duw[0], duw[1], duw[2], duw[3]);
+            }
+        }
+    } else if constexpr (ACT_MODE == 2) {
+        unsigned char *est = region(wave);
+        stage_tile<T, MI>(acc, est, lane);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));   // the wave reads back only what it wrote itself
+        asm volatile("" ::: "memory");
+        constexpr int LPR = 4 * MI, RPP = 64 / LPR;   // lanes per tile row (16-byte pieces), rows per pass
+        const int n_base = n0 + 64 * wn, m_base = m0 + WM * wm;
+        const int c = lane % LPR, m = min(m_base + 8 * c, M - 8);
+        uint4 z[LPR];   // the accumulators are dead: all loads of Z go out before anything is computed
+#pragma unroll
+        for (int j = 0; j < LPR; ++j)
+            z[j] = s24_load_stream(GU + (int64_t)min(n_base + RPP * j + lane / LPR, N - 1) * M + m);
+        if constexpr (TABLE) {   // under the loads of Z
+            Table::template build<128 * WN>(table, tid);
+            wait_and_barrier<63>();
+        }
+#pragma unroll
+        for (int j = 0; j < LPR; ++j) {
+            const int nl = RPP * j + lane / LPR, n = n_base + nl;
+            const uint4 dh = staged_chunk<MI>(est, nl, c);
+            const uint32_t dw[4] = {dh.x, dh.y, dh.z, dh.w}, zw[4] = {z[j].x, z[j].y, z[j].z, z[j].w};
+            uint32_t o[4];
+            float2 slope[4];
+            if constexpr (TABLE) {
+                Table::lookup(table, zw, slope);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) slope[k] = make_float2(s24_act_slope<ACT>(s24_num<T>::lo(zw[k])), s24_act_slope<ACT>(s24_num<T>::hi(zw[k])));
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[k] = s24_num<T>::pack2(s24_num<T>::lo(dw[k]) * slope[k].x, s24_num<T>::hi(dw[k]) * slope[k].y);
+            if (n < N && m_base + 8 * c < M)   // M is a multiple of 16: a chunk is all in or all out
+                *reinterpret_cast<uint4 *>(Out + (int64_t)n * M + m) = make_uint4(o[0], o[1], o[2], o[3]);
+        }
+    } else if constexpr (ACT_MODE == 1) {
+        unsigned char *est = region(wave);
+        stage_tile<T, MI>(acc, est, lane);
+        if constexpr (TABLE && !EARLY_TABLE) {
+            Table::template build<128 * WN>(table, tid);
+            wait_and_barrier<0>();
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
+        asm volatile("" ::: "memory");
+        constexpr int LPR = 4 * MI, RPP = 64 / LPR;
+        const int n_base = n0 + 64 * wn, m_base = m0 + WM * wm;
+#pragma unroll 4
+        for (int j = 0; j < LPR; ++j) {
+            const int nl = RPP * j + lane / LPR, c = lane % LPR;
+            const int n = n_base + nl, m = m_base + 8 * c;
+            if (n >= N || m >= M) continue;
+            const uint4 zc = staged_chunk<MI>(est, nl, c);
+            const uint32_t zw[4] = {zc.x, zc.y, zc.z, zc.w};
+            uint32_t h[4];
+            if constexpr (TABLE) {
+                Table::lookup(table, zw, h);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    h[k] = s24_num<T>::pack2(s24_act_value<ACT>(s24_num<T>::lo(zw[k])), s24_act_value<ACT>(s24_num<T>::hi(zw[k])));
+            }
+            s24_store_stream(Out + (int64_t)n * M + m, zc);
+            *reinterpret_cast<uint4 *>(H + (int64_t)n * M + m) = make_uint4(h[0], h[1], h[2], h[3]);
+        }
+    } else if constexpr (!SWIGLU) {
+        staged_store<T, MI>(acc, region(wave), Out, N, M, n0 + 64 * wn, m0 + WM * wm, lane);
+    } else {
+        // waves (0, wn) and (1, wn) hold the gate and the up tile of the same 64 tokens x 128 features: both park
+        // their bf16 tiles, then each takes 32 of the 64 token rows and writes G, U and H in 16-byte pieces
+        stage_tile<T, 4>(acc, region(wave), lane);
+        wait_and_barrier<0>();
+        const unsigned char *sg = region(2 * wn), *su = region(2 * wn + 1);
+#pragma unroll 2
+        for (int j = 0; j < 8; ++j) {
+            const int idx = j * 64 + lane, nl = 32 * wm + (idx >> 4), c = idx & 15;
+            const int n = n0 + 64 * wn + nl, f = m0 + 8 * c;
+            if (n >= N || f >= F) continue;   // F is a multiple of 8: a chunk is all in or all out
+            const uint4 g = staged_chunk(sg, nl, c), u = staged_chunk(su, nl, c);
+            const uint32_t gw[4] = {g.x, g.y, g.z, g.w}, uw[4] = {u.x, u.y, u.z, u.w};
+            uint32_t hw[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                hw[k] = s24_num<T>::pack2(s24_glu<GATE>(s24_num<T>::lo(gw[k]), s24_num<T>::lo(uw[k])),
+                                          s24_glu<GATE>(s24_num<T>::hi(gw[k]), s24_num<T>::hi(uw[k])));
+            s24_store_stream(Out + (int64_t)n * M + f, g);
+            s24_store_stream(Out + (int64_t)n * M + F + f, u);
+            *reinterpret_cast<uint4 *>(H + (int64_t)n * F + f) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+        }
+    }
+}
+
 template <typename T, bool ACCUM, bool SWIGLU = false, bool GATE_BWD = false, int GATE = S24_GATE_SILU, bool BIAS = false,
           int ACT_MODE = 0, int ACT = S24_ACT_RELU, int MI = 4, int WN = MI>
 __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *__restrict__ B,
@@ -320,13 +701,10 @@ __global__ __launch_bounds__(128 * WN) void spmm_nt_big_kernel(const uint16_t *_
                                                               const uint16_t *__restrict__ bias = nullptr)
 {
     constexpr int RING = spmm_stage(MI, WN);
-    // One array per ring stage: the compiler then knows which stage a direct-to-LDS
-    // copy writes and does not make reads of the other stages wait for it.
     __shared__ __attribute__((aligned(16))) unsigned char s0[RING];
     __shared__ __attribute__((aligned(16))) unsigned char s1[RING];
     __shared__ __attribute__((aligned(16))) unsigned char s2[RING];
-    const unsigned block = blockIdx.x;
-#include "s24_spmm_nt_body.inc"
+    spmm_nt_tile<T, ACCUM, SWIGLU, GATE_BWD, GATE, BIAS, ACT_MODE, ACT, MI, WN>(s0, s1, s2, blockIdx.x, B, Av, Am, Out, N, K, M, tiles_m, tiles_n, probe, H, F, GU, bias);
 }
 }  // namespace big
 
@@ -534,6 +912,326 @@ template <int WTM_, int WTN_, int BT_> struct Cfg {
 // DECAY: the masked decay term is added in the epilogue: dW[m][n] += lambda * Wt[m][n] where bit
 // 4*(m%4) + n%4 of mask[m/4][n/4] is clear, with the same single fused multiply-add the stand-alone
 // decay kernel applies to the stored gradient, so both routes give the same bits.
+// `block`, s0 .. s3 (C::STAGE bytes each): as in big::spmm_nt_tile
+template <typename ET, typename C, bool ACCUM, bool DECAY>
+__device__ __forceinline__ void dense_tn_tile(unsigned char *s0, unsigned char *s1, unsigned char *s2, unsigned char *s3, unsigned block, const DwBatch &batch,
+                                              unsigned long long *probe)
+{
+    constexpr int WTM = C::WTM, WTN = C::WTN, BM = C::BM, BN = C::BN, BT = C::BT, ROWA = C::ROWA, ROWX = C::ROWX;
+    constexpr int OPERAND = C::OPERAND, STAGE = C::STAGE, NIA = C::NIA, NIX = C::NIX, NI = C::NI;
+    constexpr int KS = BT / 32, CPS = NI / KS;   // 32-token steps per chunk, copies issued per step
+    static_assert(CPS * KS == NI, "every step issues the same number of copies");
+    constexpr int MB = 2 * WTM, NB = 2 * WTN;     // 16 x 16 accumulator blocks of a wave
+    const big::ClockStamp t_start = big::clock_now();
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave & 1, wn = wave >> 1;
+    const int slot = (int)(block >> 3);
+    int which = 0;   // wave-uniform: the problem this workgroup's tile belongs to
+#pragma unroll
+    for (int i = 1; i < kMaxBatch; ++i)
+        if (slot >= batch.first_slot[i]) which = i;
+    const DwWindow &win = batch.w[which];
+    const int per_xcd = batch.first_slot[which + 1] - batch.first_slot[which];
+    const int t = (int)(block & 7) * per_xcd + (slot - batch.first_slot[which]);
+    if (t >= win.tiles_m * win.tiles_n) return;
+    const uint16_t *__restrict__ dY = win.dY, *__restrict__ X = win.X, *__restrict__ Wt = win.Wt, *__restrict__ mask = win.mask;
+    float *__restrict__ dW = win.dW;
+    const int T = win.T, M = win.M, N = win.N, ldy = win.ldy, ldx = win.ldx, ldw = win.ldw;
+    const int tiles_m = win.tiles_m, tiles_n = win.tiles_n;
+    const float lambda = win.lambda;
+    constexpr int GROUP = 8;
+    const int group_sz = GROUP * tiles_m, grp = t / group_sz, in_grp = t - grp * group_sz;
+    const int gw = min(GROUP, tiles_n - grp * GROUP);
+    const int tm = in_grp / gw, tn = grp * GROUP + in_grp % gw;
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int nk = (T + BT - 1) / BT;
+
+    // Copies: instruction g of an operand fills the 16-byte slots 64g .. 64g+63 of its stage region, slot ->
+    // (row = slot / slots per row, chunk = the rest); the source chunk is chunk ^ tr_swizzle(row).  Columns past the
+    // matrix edge are clamped to its last 16-byte chunk.  A lane's byte offsets from the first token row of its copies
+    // are fixed for the whole kernel; only the (wave-uniform) row base moves, so a copy costs no vector
+    // arithmetic.  The tokens of a 32-token step are contiguous rows, and always 32 of them: the step that would reach past
+    // the last token starts at T - 32 and overlaps its predecessor (clear_tail drops the overlap), and so does one that would
+    // lie past it altogether; with fewer than 32 tokens in all, rows past T - 1 re-read row T - 1.  Which tokens one matrix
+    // instruction sums therefore does not depend on the tile or its BT, nor do the bits of the result.  (A stage of two steps
+    // that started at T - 64 as a whole gave other bits than two stages of one for T % 64 of 33 to 63.)
+    const int part = wave * KS / 4;   // the step of a stage whose rows this wave copies
+    static_assert(KS <= 2 && BT / 4 <= 32, "a wave copies rows of one step");
+    uint32_t voffA[NIA], voffB[NIX];
+    const int lastA = (min(M - m0, BM) >> 3) - 1, lastB = (min(N - n0, BN) >> 3) - 1;
+#pragma unroll
+    for (int j = 0; j < NIA; ++j) {
+        constexpr int CPR = ROWA / 16;
+        const int slot = (wave * NIA + j) * 64 + lane, row = min(slot / CPR - 32 * part, T - 1), c = (slot % CPR) ^ tr_swizzle<ROWA>(slot / CPR);
+        voffA[j] = (uint32_t)(row * ldy + m0 + 8 * min(c, lastA)) * 2u;
+    }
+#pragma unroll
+    for (int j = 0; j < NIX; ++j) {
+        constexpr int CPR = ROWX / 16;
+        const int slot = (wave * NIX + j) * 64 + lane, row = min(slot / CPR - 32 * part, T - 1), c = (slot % CPR) ^ tr_swizzle<ROWX>(slot / CPR);
+        voffB[j] = (uint32_t)(row * ldx + n0 + 8 * min(c, lastB)) * 2u;
+    }
+    auto first_row = [&](int kc) { return max(min(kc * BT + 32 * part, T - 32), 0); };   // of this wave's copies
+    const char *baseA = reinterpret_cast<const char *>(dY), *baseB = reinterpret_cast<const char *>(X);
+    // Copy c of a chunk's list (the dY tile's NIA, then the X tile's NIX), rowsA and rowsB its first token row.
+    // The copies are buffer loads into LDS: a descriptor (scalar registers) whose base is the first of those token
+    // rows, and the lane's fixed 32-bit offset; nothing of a copy's address is computed on the vector unit.
+    auto issue = [&](unsigned char *st, const char *rowsA, const char *rowsB, int c) {
+        if (c < NIA) big::buffer_to_lds<16>(big::buffer_of(rowsA), (lds_ptr)(st + (wave * NIA + c) * 1024), voffA[c]);
+        else big::buffer_to_lds<16>(big::buffer_of(rowsB), (lds_ptr)(st + OPERAND + (wave * NIX + c - NIA) * 1024), voffB[c - NIA]);
+    };
+    auto issue_all = [&](unsigned char *st, int kc) {
+        const char *ra = baseA + (int64_t)first_row(kc) * ldy * 2, *rb = baseB + (int64_t)first_row(kc) * ldx * 2;
+#pragma unroll
+        for (int c = 0; c < NI; ++c) issue(st, ra, rb, c);
+    };
+    f32x4 acc[MB][NB];
+#pragma unroll
+    for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NB; ++ni) acc[mi][ni] = f32x4{};
+
+    // fragment addressing of this lane: group G = lane/16 takes tokens 8G .. 8G+7 of a step, 16 columns per block
+    const int gi = lane & 15, G = lane >> 4;
+    const int frow = 8 * G + (gi >> 2), fcol = 4 * (gi & 3);
+    // Byte offsets of a lane's fragments from a stage, and the same plus two stages for the upper two, whose distance does
+    // not fit an instruction's offset field (kept in registers of their own: added on the spot, they were 16 vector
+    // instructions per chunk).
+    constexpr int FAR = 2 * STAGE;
+    int offA[2][MB], offB[2][NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i) offA[0][i] = tr_off<ROWA>(frow, 32 * WTM * wm + 16 * i + fcol);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) offB[0][i] = OPERAND + tr_off<ROWX>(frow, 32 * WTN * wn + 16 * i + fcol);
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+        offA[1][i] = offA[0][i] + FAR;
+        asm volatile("" : "+v"(offA[1][i]));
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        offB[1][i] = offB[0][i] + FAR;
+        asm volatile("" : "+v"(offB[1][i]));
+    }
+    // Half h (tokens 8G + 4h ..) of fragment i of step ks.  S: number of the stage `st`
+    auto load_a = [&](const unsigned char *st, auto S, int ks, int i, int h) {
+        return tr_half((S < 2 ? st + offA[0][i] : st - FAR + offA[1][i]) + (32 * ks + 4 * h) * ROWA);
+    };
+    auto load_b = [&](const unsigned char *st, auto S, int ks, int i, int h) {
+        return tr_half((S < 2 ? st + offB[0][i] : st - FAR + offB[1][i]) + (32 * ks + 4 * h) * ROWX);
+    };
+    // The last chunk of a token count that is not a multiple of BT holds rows that must not contribute: of each step the
+    // leading ones that its predecessor already covered, or, when there are fewer than 32 tokens in all, the trailing
+    // ones past T.  They are cleared in both tiles: in one alone, an infinity in the other would make a NaN.
+    auto clear_tail = [&](unsigned char *st, int kc) {
+        auto clear = [&](unsigned char *rows, int bytes) {
+            for (int at = 16 * tid; at < bytes; at += 16 * THREADS) *reinterpret_cast<uint4 *>(rows + at) = make_uint4(0, 0, 0, 0);
+        };
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int live = max(min(T - kc * BT - 32 * ks, 32), 0), row = 32 * ks + (T < 32 ? live : 0);
+            clear(st + row * ROWA, (32 - live) * ROWA);
+            clear(st + OPERAND + row * ROWX, (32 - live) * ROWX);
+        }
+        __syncthreads();
+    };
+    const bool partial = (T % BT) != 0;
+
+    // prologue: chunks 0..2 in flight, chunk 0 landed, its first fragments in registers
+    issue_all(s0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    issue_all(s1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    issue_all(s2, 2);
+    __builtin_amdgcn_sched_barrier(0);
+    big::wait_and_barrier<2 * NI>();
+    if (partial && nk == 1) clear_tail(s0, 0);
+    // Fragments: of X those of the current and of the next 32-token step; of dY one set, each replaced by the next step's
+    // as soon as its row of accumulators is done (the last one at the start of that step).
+    const std::integral_constant<int, 0> c0;
+    const std::integral_constant<int, 1> c1;
+    const std::integral_constant<int, 2> c2;
+    const std::integral_constant<int, 3> c3;
+    bf16x8 fa[MB], fb[2][NB];
+#pragma unroll
+    for (int ni = 0; ni < NB; ++ni) fb[0][ni] = join(load_b(s0, c0, 0, ni, 0), load_b(s0, c0, 0, ni, 1));
+#pragma unroll
+    for (int mi = 0; mi < MB - 1; ++mi) fa[mi] = join(load_a(s0, c0, 0, mi, 0), load_a(s0, c0, 0, mi, 1));
+    mma_tie<ACC_AGPR>(acc);
+    mma_operands();
+    const char *rowsA = baseA + (int64_t)first_row(3) * ldy * 2, *rowsB = baseB + (int64_t)first_row(3) * ldx * 2;   // of the next chunk to copy
+
+    // One step: rows of NB matrix instructions.  A wave is alone on its SIMD and issues an instruction every four cycles, a
+    // matrix instruction lasts sixteen: whatever else goes out between two of them beyond three instructions leaves the matrix
+    // unit idle (a wait state before each cost 6 % of the kernel).  So the rest is dealt out evenly: beside row mi the
+    // LDS reads of one dY fragment and its share of the NB X fragments', one read per matrix instruction, one copy, and a part of
+    // the address of the next chunk's rows.  The X fragment is the instruction's row operand: a lane's four accumulators
+    // are then four consecutive columns of one row of dW.  Neighbouring instructions share a fragment, at the turns
+    // of the serpentine the other one: the operand bits that toggle cost clock.
+    // `cs` / `ns`: numbers of the stages cur / nxt; `which`: the X fragment set of this step.
+    auto step = [&](const unsigned char *cur, auto cs, int ks, const unsigned char *nxt, auto ns, int ksn, unsigned char *refill, int copy0, int next_row,
+                    auto which) {
+        constexpr int P = decltype(which)::value;
+        static_assert((2 * NB + MB - 1) / MB + 2 <= NB && CPS <= MB, "one read per matrix instruction, one copy per row");
+        int64_t nextA = 0, nextB = 0;
+        v4i16 lo{}, loA{};
+#pragma unroll
+        for (int mi = 0; mi < MB; ++mi) {
+            const int x0 = 2 * NB * mi / MB, RB = 2 * NB * (mi + 1) / MB - x0, R = RB + 2;   // reads of X beside this row, all reads
+#pragma unroll
+            for (int nj = 0; nj < NB; ++nj) {
+                const int ni = (mi & 1) ? NB - 1 - nj : nj;
+                Mma<ET>::dense16(fb[P][ni], fa[mi], acc[mi][ni]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    if (r * NB / R != nj) continue;
+                    if (r < RB) {
+                        const int i = x0 + r;
+                        if (i % 2 == 0) lo = load_b(nxt, ns, ksn, i / 2, 0);
+                        else fb[1 - P][i / 2] = join(lo, load_b(nxt, ns, ksn, i / 2, 1));
+                    } else if (mi == 0) {
+                        if (r == RB) loA = load_a(cur, cs, ks, MB - 1, 0);
+                        else fa[MB - 1] = join(loA, load_a(cur, cs, ks, MB - 1, 1));
+                    } else {
+                        if (r == RB) loA = load_a(nxt, ns, ksn, mi - 1, 0);
+                        else fa[mi - 1] = join(loA, load_a(nxt, ns, ksn, mi - 1, 1));
+                    }
+                }
+                if (nj == NB - 1 && mi < CPS) issue(refill, rowsA, rowsB, copy0 + mi);
+                if (next_row >= 0 && nj == 1) {   // the address of the next chunk's rows, a product or a sum at a time
+                    if (mi == MB - 4) { nextA = (int64_t)next_row * ldy * 2; asm volatile("" : "+s"(nextA)); }
+                    if (mi == MB - 3) { nextB = (int64_t)next_row * ldx * 2; asm volatile("" : "+s"(nextB)); }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (next_row >= 0) { rowsA = baseA + nextA; rowsB = baseB + nextB; }
+    };
+    // Iteration kc: all but the NI most recent copies (chunk kc+2) are complete, so chunk kc+1 is in LDS for
+    // every wave after the barrier, and nobody reads the stage of chunk kc-1 any more: it takes chunk kc+3.  (The last read
+    // of that stage fed the last row of iteration kc-1; the reads still in flight here are of chunk kc and need no wait.)
+    // Past the last chunk the fragments fetched ahead come from a stage nobody uses and are dropped.
+    auto chunk = [&](const unsigned char *cur, auto cs, unsigned char *nxt, auto ns, unsigned char *refill, int kc, bool tail) {
+        big::wait_and_barrier<NI, false>();
+        if (tail && partial && kc + 2 == nk) clear_tail(nxt, kc + 1);
+        const int next_row = first_row(kc + 4);
+        if constexpr (KS == 1) {
+            step(cur, cs, 0, nxt, ns, 0, refill, 0, next_row, std::integral_constant<int, decltype(cs)::value & 1>());
+        } else {
+            step(cur, cs, 0, cur, cs, 1, refill, 0, -1, c0);
+            step(cur, cs, 1, nxt, ns, 0, refill, CPS, next_row, c1);
+        }
+    };
+    int kc = 0;
+    for (; kc + 6 <= nk; kc += 4) {   // the chunk that needs its overlap cleared is never `nxt` in here
+        chunk(s0, c0, s1, c1, s3, kc, false);
+        chunk(s1, c1, s2, c2, s0, kc + 1, false);
+        chunk(s2, c2, s3, c3, s1, kc + 2, false);
+        chunk(s3, c3, s0, c0, s2, kc + 3, false);
+    }
+    for (; kc < nk; kc += 4) {
+        chunk(s0, c0, s1, c1, s3, kc, true);
+        if (kc + 1 >= nk) break;
+        chunk(s1, c1, s2, c2, s0, kc + 1, true);
+        if (kc + 2 >= nk) break;
+        chunk(s2, c2, s3, c3, s1, kc + 2, true);
+        if (kc + 3 >= nk) break;
+        chunk(s3, c3, s0, c0, s2, kc + 3, true);
+    }
+    // Epilogue through LDS, so that global memory sees 16-byte accesses along rows: each wave parks a slice of its tile
+    // at a time (32*RB rows x 64 columns of fp32, 256-byte rows) in its own ring stage, then lane l of pass j
+    // owns row (64j + l) / 16, columns 4 * (l % 16) .. +3: one LDS read, one 16-byte store, and for the
+    // optional terms one 16-byte load of the old gradient, one 8-byte load of W and one mask word.
+    // The W and mask loads of a whole slice are issued in one go, well before they are needed: those of
+    // the first slice ahead of the wait that drains the ring, those of the second before it is parked in LDS.
+    // Loaded pass by pass where they are used, their latency was exposed eight times per tile with only four
+    // waves on the compute unit to hide it (c5: 0.45 ms per step).
+    // They are buffer loads: pass j reads four rows further down than pass j - 1, which is a wave-uniform step (a
+    // scalar register), so the 64 loads of a slice share two address registers.  M is a multiple of 16 and a wave's
+    // rows start at a multiple of 32: the four rows of a pass are all inside the matrix or all outside, and passes
+    // past the edge re-read the last pass inside (a wave with no row inside re-reads the tile's first rows).
+    constexpr int RB = WTM * 8192 <= STAGE ? WTM : WTM / 2, NR = WTM / RB;   // row blocks per slice, slices down a wave's tile
+    static_assert(RB * 8192 <= STAGE && RB * NR == WTM, "a wave's slice fits one stage");
+    constexpr int NP = 8 * RB;   // passes per slice
+    uint2 wv[DECAY ? NP : 1];
+    uint32_t keep[DECAY ? NP : 1];
+    const int wave_rows = min(M - m0 - 32 * WTM * wm, 32 * WTM);   // rows of this wave's sub-tile inside the matrix
+    const int wave_row0 = wave_rows > 0 ? 32 * WTM * wm : 0, last_pass = wave_rows > 0 ? (wave_rows >> 2) - 1 : 0;
+    auto decay_loads = [&](int h2, int r2) {
+        if constexpr (DECAY) {
+            const int nc = min(n0 + 32 * WTN * wn + 64 * h2 + 4 * (lane & 15), N - 4);
+            const big::rsrc_t wbuf = big::buffer_of(Wt + (int64_t)(m0 + wave_row0) * ldw);
+            const big::rsrc_t mbuf = big::buffer_of(mask + (int64_t)((m0 + wave_row0) >> 2) * (ldw >> 2));
+            const uint32_t voff_w = ((uint32_t)(lane >> 4) * (uint32_t)ldw + (uint32_t)nc) * 2u, voff_m = (uint32_t)(nc >> 2) * 2u;
+            const uint32_t shift = 4 * (lane >> 4);   // row of the 4 x 4 block: the tile starts at a multiple of four
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                const uint32_t jc = (uint32_t)min(NP * r2 + j, last_pass);
+                wv[j] = big::buffer_load_8(wbuf, voff_w, jc * 8u * (uint32_t)ldw);
+                keep[j] = big::buffer_load_2(mbuf, voff_m, jc * 2u * (uint32_t)(ldw >> 2)) >> shift;
+            }
+        }
+    };
+    mma_drain<ACC_AGPR>(acc);
+    decay_loads(0, 0);
+    big::wait_and_barrier<0>();   // last (redundant) copies drained, nobody reads the ring any more: reuse it
+    big::clock_report(probe, t_start);
+    unsigned char *est = wave == 0 ? s0 : (wave == 1 ? s1 : (wave == 2 ? s2 : s3));
+#pragma unroll
+    for (int slice = 0; slice < NR * (WTN / 2); ++slice) {
+        const int h2 = slice / NR, r2 = slice % NR;
+        if (slice > 0) decay_loads(h2, r2);
+#pragma unroll
+        for (int nj = 0; nj < 4; ++nj)
+#pragma unroll
+            for (int mi = 0; mi < 2 * RB; ++mi) {   // 16-byte piece c of row r sits at slot c ^ (r & 15)
+                const int row = 16 * mi + (lane & 15), c4 = 4 * nj + (lane >> 4);
+                *reinterpret_cast<f32x4 *>(est + row * 256 + ((c4 ^ (row & 15)) << 4)) = acc[2 * RB * r2 + mi][4 * h2 + nj];
+            }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(big::wait_vm_lgkm0(63));   // LDS only: the wave reads back only what it wrote itself
+        asm volatile("" ::: "memory");
+        const int ms = m0 + 32 * WTM * wm + 32 * RB * r2, ns = n0 + 32 * WTN * wn + 64 * h2;   // the slice's first row and column
+        constexpr int BATCH = 8;
+#pragma unroll
+        for (int j0 = 0; j0 < NP; j0 += BATCH) {
+            float4 v[BATCH], old[BATCH];
+            bool live[BATCH];
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) {
+                const int idx = (j0 + b) * 64 + lane, row = idx >> 4, c4 = idx & 15;
+                const int m = ms + row, n = ns + 4 * c4;
+                live[b] = m < M && n < N;   // N is a multiple of 16: the four columns are all in or all out
+                const int mc = min(m, M - 1), nc = min(n, N - 4);
+                v[b] = *reinterpret_cast<const float4 *>(est + row * 256 + ((c4 ^ (row & 15)) << 4));
+                if (ACCUM) old[b] = *reinterpret_cast<const float4 *>(dW + (int64_t)mc * ldw + nc);
+            }
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) {
+                const int idx = (j0 + b) * 64 + lane, row = idx >> 4, c4 = idx & 15;
+                const int m = ms + row, n = ns + 4 * c4;
+                float4 o = v[b];
+                if (ACCUM) { o.x = old[b].x + o.x; o.y = old[b].y + o.y; o.z = old[b].z + o.z; o.w = old[b].w + o.w; }
+                if constexpr (DECAY) {
+                    const uint2 w2 = wv[j0 + b];
+                    const uint32_t kp = keep[j0 + b];
+                    if (!(kp & 1u)) o.x = fmaf(lambda, s24_num<ET>::lo(w2.x), o.x);
+                    if (!(kp & 2u)) o.y = fmaf(lambda, s24_num<ET>::hi(w2.x), o.y);
+                    if (!(kp & 4u)) o.z = fmaf(lambda, s24_num<ET>::lo(w2.y), o.z);
+                    if (!(kp & 8u)) o.w = fmaf(lambda, s24_num<ET>::hi(w2.y), o.w);
+                }
+                if (live[b]) s24_store_stream(dW + (int64_t)m * ldw + n, o);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // one batch at a time: hoisting the next batches' reads costs registers
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(big::wait_vm_lgkm0(63));   // LDS reads done before the other half overwrites
+        asm volatile("" ::: "memory");
+    }
+}
+
 template <typename ET, typename C, bool ACCUM, bool DECAY>
 __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch batch, unsigned long long *probe)
 {
@@ -541,8 +1239,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
     __shared__ __attribute__((aligned(16))) unsigned char s1[C::STAGE];
     __shared__ __attribute__((aligned(16))) unsigned char s2[C::STAGE];
     __shared__ __attribute__((aligned(16))) unsigned char s3[C::STAGE];
-    const unsigned block = blockIdx.x;
-#include "s24_dense_tn_body.inc"
+    dense_tn_tile<ET, C, ACCUM, DECAY>(s0, s1, s2, s3, blockIdx.x, batch, probe);
 }
 }  // namespace dmatn
 
@@ -556,7 +1253,7 @@ __global__ __launch_bounds__(THREADS) void dense_tn_dma_kernel(const DwBatch bat
 template <typename ET, bool DECAY, typename C>
 __global__ __launch_bounds__(256) void dw_dx_kernel(const uint16_t *__restrict__ B, const uint16_t *__restrict__ Av, const uint16_t *__restrict__ Am,
                                                     uint16_t *__restrict__ Out, int N, int K, int M, int dw_blocks, int tiles_m, int tiles_n,
-                                                    const dmatn::DwBatch batch, unsigned long long *probe_)
+                                                    const dmatn::DwBatch batch, unsigned long long *probe)
 {
     constexpr int DX = big::spmm_stage(4, 2), RING = DX > C::STAGE ? DX : C::STAGE;
     static_assert(3 * RING + C::STAGE <= 160 * 1024 && dmatn::THREADS == 256, "one ring for either");
@@ -564,24 +1261,11 @@ __global__ __launch_bounds__(256) void dw_dx_kernel(const uint16_t *__restrict__
     __shared__ __attribute__((aligned(16))) unsigned char s1[RING];
     __shared__ __attribute__((aligned(16))) unsigned char s2[RING];
     __shared__ __attribute__((aligned(16))) unsigned char s3[C::STAGE];
-    if ((int)blockIdx.x < dw_blocks) {   // a multiple of eight
-        using namespace dmatn;
-        constexpr bool ACCUM = false;
-        const unsigned block = blockIdx.x;
-        unsigned long long *const probe = probe_;
-#include "s24_dense_tn_body.inc"
-    } else {
-        using namespace big;
-        typedef ET T;
-        constexpr bool ACCUM = false, SWIGLU = false, GATE_BWD = false, BIAS = false;
-        constexpr int GATE = S24_GATE_SILU, ACT = S24_ACT_RELU, MI = 4, WN = 2, F = 0;
-        constexpr int ACT_MODE = std::is_void_v<ET>;   // 0, by way of a template parameter: what a branch for another mode says is then not looked at
-        const unsigned block = blockIdx.x - (unsigned)dw_blocks;
-        unsigned long long *const probe = nullptr;
-        uint16_t *const H = nullptr;
-        const uint16_t *const GU = nullptr, *const bias = nullptr;
-#include "s24_spmm_nt_body.inc"
-    }
+    if ((int)blockIdx.x < dw_blocks)   // a multiple of eight
+        dmatn::dense_tn_tile<ET, C, false, DECAY>(s0, s1, s2, s3, blockIdx.x, batch, probe);
+    else
+        big::spmm_nt_tile<ET, false, false, false, S24_GATE_SILU, false, 0, S24_ACT_RELU, 4, 2>(s0, s1, s2, blockIdx.x - (unsigned)dw_blocks, B, Av, Am, Out, N, K, M, tiles_m,
+                                                                                              tiles_n, nullptr, nullptr, 0, nullptr, nullptr);
 }
 
 // ------------------------------------------------------------------ sparse TN (weight gradient from a pruned dY)
@@ -949,7 +1633,8 @@ inline NtTile nt_tile_or_slab(int64_t M, int64_t N, int64_t K)
 }
 // The dense product: us per 64 of k, large 1.45 and 0.94 (full, few), medium 0.85 and 0.54, small 1.04 with two workgroups per
 // compute unit, 0.44 with one.  8192 x 1024, K = 4096: large 75, medium 65, small 76 us; 500 x 4096, K = 16384: 240, 178, 119;
-// 2048 x 3072, K = 768: 20, 16, 17.  0.5 % above the best tile at the mean of 128 products.
+// 2048 x 3072, K = 768: 20, 16, 17.  0.5 % above the best tile at the mean of 128 products.  (On one set of operands, launched on end.  Out of
+// the caches they add their way in: the first product in medium tiles 64 us so, 76 on eight sets in turn, 79 in a dense step.)
 inline NtTile dense_tile(int64_t M, int64_t N) { return cheapest_tile(M, N, {0.53, 0.30, 0.62, 0.40, 0.20, 0.70, 0.26, 0.08}); }
 // The sparse weight gradient: us per 64 tokens, large 0.83 and 0.53 (full, few), medium 0.46 and 0.35, small 0.63 with two
 // workgroups per compute unit and 0.30 with one.  8192 tokens, 768 x 3072: large 77, medium 54, small 45 us; 2048, 512 x 2048: 24,
@@ -1491,7 +2176,8 @@ int find_strip(const DwProblem *prs, int count, int64_t total, int &cols, int &r
     }
     return -1;
 }
-// The tile for several problems on one whole grid, if they have one, and what s24_dense_dw_batch takes for them (a strip: a third of a round)
+// The tile for several problems on one whole grid, if they have one, and what s24_dense_dw_batch takes for them (a strip: a third of a round).  It
+// has to say what s24_dense_dw_batch does: the tests compare the tile of a joint launch with the one that the gradients take by themselves.
 bool dw_whole_grid(const s24_dw_problem *problems, const DwProblem *prs, int count, DwTile &tile, double &us)
 {
     const int64_t cus = s24_cu_count();
@@ -1687,8 +2373,9 @@ extern "C" int s24_spmm_bwd_dx_dw(const void *dY, const void *valsT, const uint1
     if (together && dt != S24_F32 && !slices && launch_dw_dx(static_cast<const uint16_t *>(dY), static_cast<const uint16_t *>(valsT), metaT,
                                                              static_cast<uint16_t *>(dX), p, q, r, problems, count, dt, st))
         return s24_launch_status();
-    // 16-bit: where the input gradient runs in slices, one token block to a tile, and the weight gradients in the small tile by eight waves or by
-    // four at no more tokens than make these equal
+    // 16-bit, few tokens: the input gradient in slices of one token block to a tile beside the weight gradients in the small tile by eight waves.  Up to
+    // 1024 tokens: beyond, that tile is slower than the one of four waves by more than a launch (in turn and together, 1024 tokens: 64 x 256
+    // 12.4 and 11.4 us, 256 x 1024 14.3 and 12.8; 1536: 14.7 and 14.8, 17.9 and 18.6; 3072: 21.9 and 25.0, 29.4 and 29.4).
     for (int i = 0; i < count; ++i) together = together && dw_is_small(problems[i]) && problems[i].p <= 1024;
     const S24SlicePlan narrow = together && slices ? s24_slice_plan(p, r, q, 1) : S24SlicePlan{};
     if (narrow && narrow.us <= 1.3 * slices.us) {
