@@ -229,9 +229,10 @@ typedef struct {
 int s24_dense_dw_batch(const s24_dw_problem *problems, int count, float beta, s24_dtype dt, void *stream);
 
 /* The last input gradient of a layer and its weight gradients: the same result, bit for bit, as s24_spmm_bwd_dx(dY, valsT, metaT, dX,
- * p, q, r, 0, ...) followed by s24_dense_dw_batch(problems, count, 0, ...), neither of which needs the other's.  Small ones
- * that leave the chip mostly idle run in one launch, unless one of them writes what another one reads or writes; all others
- * in turn.  Everything is validated before the first launch. */
+ * p, q, r, 0, ...) followed by s24_dense_dw_batch(problems, count, 0, ...), neither of which needs the other's.  They run in one
+ * launch where that is the faster: small ones that leave the chip mostly idle, and 16-bit ones of many tokens whose last rounds do.  In
+ * turn, in this order, run all others, and those of which one writes what another one reads or writes.  Everything is
+ * validated before the first launch. */
 int s24_spmm_bwd_dx_dw(const void *dY, const void *valsT, const uint16_t *metaT, void *dX, int64_t p, int64_t q, int64_t r,
                        const s24_dw_problem *problems, int count, s24_dtype dt, void *stream);
 

@@ -367,7 +367,8 @@ def dense_dw_batch(problems, beta=0.0):
 
 
 def spmm_bwd_dx_dw(dY, valsT, metaT, dX, problems):
-    """spmm_bwd_dx(dY, valsT, metaT, dX) and dense_dw_batch(problems), which do not depend on each other: one launch where both are small."""
+    """spmm_bwd_dx(dY, valsT, metaT, dX) and dense_dw_batch(problems), which do not depend on each other: in one launch where that is the
+    faster (see include/s24.h)."""
     _dense("s24_spmm_bwd_dx_dw", "dY valsT metaT dX", dY, valsT, metaT, dX)
     p, r = dY.shape
     arr = _dw_problems("s24_spmm_bwd_dx_dw", problems, dY.dtype)

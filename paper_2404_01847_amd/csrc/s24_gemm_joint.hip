@@ -10,7 +10,7 @@ using namespace s24_lds;
 using namespace s24_dw;
 
 // A 128 x 128 tile of a weight gradient of few tokens, by eight waves of 32 (rows of dW) x 64: same tokens to an instruction and same order
-// of the sums as above, so the same bits.  With 256 tokens the products are a third of the time and the rest is the way in and out, which more waves with less
+// of the sums as in dense_tn_tile (s24_gemm.hip), so the same bits.  With 256 tokens the products are a third of the time and the rest is the way in and out, which more waves with less
 // to do each get over sooner; W and the mask are requested before anything else.  s0 .. s3: SHORT_STAGE bytes of LDS each.
 constexpr int SHORT_STAGE = 2 * 32 * 256, SHORT_THREADS = 512;
 __device__ __forceinline__ f32x4 mfma16(uint16_t, bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
