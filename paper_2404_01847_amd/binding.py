@@ -352,7 +352,7 @@ def _dw_problems(where, problems, dtype):
     for dY, X, dW, W, mask, lam in problems:
         p, r = dY.shape
         _dense(where, "dY X dW W mask", dY, X, dW, W, mask)
-        if dY.dtype != dtype or X.dtype != dtype or (W is not None and W.dtype != dtype):
+        if dY.dtype is not dtype or X.dtype is not dtype or (W is not None and W.dtype is not dtype):
             raise ValueError(f"{where}: the operands and weights of all problems must share one dtype")
         packed.append(_pack_dw(_ptr(dY), _ptr(X), _ptr(dW) or 0, _ptr(W) or 0, _ptr(mask) or 0, p, X.shape[1], r, _f32(lam).value))
     return b"".join(packed)

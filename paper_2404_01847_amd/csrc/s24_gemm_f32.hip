@@ -386,12 +386,15 @@ __global__ __launch_bounds__(64 * KS) void f32_tn_kernel(const TnArgs args)
 // An input gradient in eight slices and weight gradients that do not depend on it in one launch: neither fills the chip, and each is a
 // launch and a few trips to memory that the other one can hide.  The input gradient's tiles walk the longer sums and go first.
 // 512 tokens, 256 x 1024 (10.2 and 12.5 us under the tracer): 54.6 -> 47.2 us a step.
+// first: B, Av; second: Am, tiles of the input gradient, N; third: K, M, its tiles of features, nothing
 template <int D>
-__global__ __launch_bounds__(512) void f32_nt_tn_kernel(const float *B, const float *Av, const uint16_t *Am, int nt_tiles, int N, int K, int M, int tiles_m,
-                                                        float *Out, const TnArgs args)
+__global__ __launch_bounds__(512) void f32_nt_tn_kernel(const s24_words first, const s24_words second, const s24_words third, float *Out, const TnArgs args)
 {
     __shared__ __attribute__((aligned(16))) float s_red[lds_floats(1, 8)];
-    if ((int)blockIdx.x < nt_tiles) f32_nt_tile<true, false, S24_F32_PLAIN, 0, 1, 8>(s_red, (int)blockIdx.x, B, Av, Am, N, K, M, M, tiles_m, Out, nullptr, nullptr);
+    const int nt_tiles = s24_low(second.y), M = s24_high(third.x);
+    if ((int)blockIdx.x < nt_tiles)
+        f32_nt_tile<true, false, S24_F32_PLAIN, 0, 1, 8>(s_red, (int)blockIdx.x, s24_global<const float>(first.x), s24_global<const float>(first.y), s24_global<const uint16_t>(second.x),
+                                                         s24_high(second.y), s24_low(third.x), M, M, s24_low(third.y), Out, nullptr, nullptr);
     else f32_tn_tile<false, false, 1, 8, D>(s_red, (int)blockIdx.x - nt_tiles, args);
 }
 
@@ -513,8 +516,8 @@ bool s24_f32_nt_tn(const S24F32Nt &g, const S24F32TnProblem *pr, int count, hipS
     if (p.whole || p.T != 1 || p.tiles >= 1ll << 30) return false;
     const int64_t tiles_m = ceil_div(g.M, 32), tiles = tiles_m * ceil_div(g.N, 32);
     auto launch = [&](auto d) {
-        hipLaunchKernelGGL((f32_nt_tn_kernel<decltype(d)::value>), dim3((unsigned)(tiles + p.tiles)), dim3(512), 0, st, g.B, g.Av, g.Am, (int)tiles, (int)g.N, (int)g.K,
-                           (int)g.M, (int)tiles_m, g.Out, p.a);
+        hipLaunchKernelGGL((f32_nt_tn_kernel<decltype(d)::value>), dim3((unsigned)(tiles + p.tiles)), dim3(512), 0, st, s24_pack(g.B, g.Av), s24_pack(g.Am, (int)tiles, (int)g.N),
+                           s24_pack((int)g.K, (int)g.M, (int)tiles_m, 0), g.Out, p.a);
     };
     if (p.D == 1) launch(std::integral_constant<int, 1>());
     else if (p.D == 2) launch(std::integral_constant<int, 2>());

@@ -153,9 +153,9 @@ __device__ __forceinline__ void short_tn_tile(lds_byte *s0, lds_byte *s1, lds_by
 // An input gradient in slices (s24_slice_tile.h) and weight gradients of few tokens that do not depend on it in one launch: neither fills the chip,
 // and two workgroups share a compute unit, so that one is on its way to memory while the other one multiplies.  The input gradient's
 // workgroups (`dx_blocks`, a multiple of eight) walk the longer sums and go first.  256 tokens x 768 x 3072 (7.8 and 12.2 us under the tracer): 42.6 -> 36.9 us a step.
+// first: B, Av; second: Am, dx_blocks, N; third: K, M, tiles of tokens, all tiles of the input gradient
 template <typename T, bool DECAY, int TM>
-__global__ __launch_bounds__(512, 4) void dx_dw_kernel(const uint16_t *__restrict__ B, const uint16_t *__restrict__ Av, const uint16_t *__restrict__ Am, int dx_blocks,
-                                                       int N, int K, int M, int tiles_n, int tiles, uint16_t *Out, const DwBatch batch)
+__global__ __launch_bounds__(512, 4) void dx_dw_kernel(const s24_words first, const s24_words second, const s24_words third, uint16_t *Out, const DwBatch batch)
 {
     static_assert(s24_slice::stage_bytes(1) == SHORT_STAGE && 64 * s24_slice::KS == SHORT_THREADS, "one ring for either");
     __shared__ __attribute__((aligned(16))) unsigned char s0[SHORT_STAGE];
@@ -163,9 +163,11 @@ __global__ __launch_bounds__(512, 4) void dx_dw_kernel(const uint16_t *__restric
     __shared__ __attribute__((aligned(16))) unsigned char s2[SHORT_STAGE];
     __shared__ __attribute__((aligned(16))) unsigned char s3[SHORT_STAGE];
     lds_byte *const l0 = (lds_byte *)s0, *const l1 = (lds_byte *)s1, *const l2 = (lds_byte *)s2, *const l3 = (lds_byte *)s3;
+    const int dx_blocks = s24_low(second.y), M = s24_high(third.x);
     if ((int)blockIdx.x < dx_blocks)
-        s24_slice::slice_tile<T, false, S24_SLICE_PLAIN, 0, TM, 1, false>(l0, l1, l2, l3, (int)blockIdx.x, B, Av, Am, N, K, M, M, tiles_n, tiles, Out, nullptr, nullptr,
-                                                                          nullptr);
+        s24_slice::slice_tile<T, false, S24_SLICE_PLAIN, 0, TM, 1, false>(l0, l1, l2, l3, (int)blockIdx.x, s24_global<const uint16_t>(first.x), s24_global<const uint16_t>(first.y),
+                                                                          s24_global<const uint16_t>(second.x), s24_high(second.y), s24_low(third.x), M, M, s24_low(third.y),
+                                                                          s24_high(third.y), Out, nullptr, nullptr, nullptr);
     else short_tn_tile<T, DECAY>(l0, l1, l2, l3, (int)blockIdx.x - dx_blocks, batch);
 }
 
@@ -176,8 +178,8 @@ void s24_dx_dw(const S24SliceNt &g, int tm, const DwBatch &batch, bool decay, in
     const int tiles_n = (int)((g.N + 15) / 16), tiles = (int)((g.M + 16 * tm - 1) / (16 * tm)) * tiles_n, dx_blocks = (tiles + 7) / 8 * 8;
     const dim3 grid(dx_blocks + 8 * batch.first_slot[kMaxBatch]), block(SHORT_THREADS);
     auto launch = [&](auto t, auto dec, auto blocks) {
-        hipLaunchKernelGGL((dx_dw_kernel<decltype(t), decltype(dec)::value, decltype(blocks)::value>), grid, block, 0, st, g.B, g.Av, g.Am, dx_blocks, (int)g.N,
-                           (int)g.K, (int)g.M, tiles_n, tiles, g.Out, batch);
+        hipLaunchKernelGGL((dx_dw_kernel<decltype(t), decltype(dec)::value, decltype(blocks)::value>), grid, block, 0, st, s24_pack(g.B, g.Av), s24_pack(g.Am, dx_blocks, (int)g.N),
+                           s24_pack((int)g.K, (int)g.M, tiles_n, tiles), g.Out, batch);
     };
     auto with = [&](auto t, auto dec) {
         if (tm == 1) launch(t, dec, std::integral_constant<int, 1>());

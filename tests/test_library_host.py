@@ -539,7 +539,7 @@ def test_short_kernels_take_few_arguments(lib, tmp_path):
     if not os.path.exists(readelf):
         assert not os.path.exists("/opt/rocm/bin/hipcc"), "a compiler without its readelf: the arguments go uncounted"
         pytest.skip("no llvm-readelf")
-    counted = {"spmm_slice_kernel": 0, "f32_nt_kernel": 0}
+    counted = {"spmm_slice_kernel": 0, "f32_nt_kernel": 0, "dx_dw_kernel": 0, "f32_nt_tn_kernel": 0}
     for k, code in enumerate(_device_code(s24.lib_path())):
         obj = tmp_path / f"{k}.co"
         obj.write_bytes(code)
@@ -549,5 +549,5 @@ def test_short_kernels_take_few_arguments(lib, tmp_path):
             for short in counted:
                 if name and short in name[1]:
                     counted[short] += 1
-                    assert len(re.findall(r"\.value_kind: +(?!hidden)", kernel)) <= 4, name[1]
+                    assert len(re.findall(r"\.value_kind: +(?!hidden)", kernel)) <= 5, name[1]
     assert all(counted.values()), counted
