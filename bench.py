@@ -668,6 +668,14 @@ def timed_steps(torch, wl, ffn, X, dY, steps, warmup):
     return ms_per_step, kernels
 
 
+def kernels_note(ffn):
+    """What the kernel table's steps do otherwise than a step without events."""
+    if not ffn.batch_dw or ffn.mvue:
+        return None
+    return ("with per-kernel events a step computes its last input gradient and its weight gradients in calls of their own "
+            "(spmm_bwd_dx, dense_dw); without, in one (s24_spmm_bwd_dx_dw), which runs them in one launch where that is faster")
+
+
 def workload_label(wl):
     return (f"{wl.name}: FFN d_model={wl.d_model} d_ff={wl.d_ff} tokens={wl.p} act={wl.act} "
             f"{wl.dtype}, {len(wl.weight_names)} weights, mask+compress every step")
@@ -777,6 +785,7 @@ def main():
               "weight_gradients_in_one_pass": bool(ffn.batch_dw and not ffn.mvue),
               "weight_gradient": "sparse GEMM on the MVUE-pruned output gradient" if ffn.mvue else "dense GEMM",
               "gemm_flops_per_step": wl.gemm_flops}
+    note = kernels_note(ffn)
     cpu = None if args.no_cpu_baseline else cpu_baseline(wl, host)
 
     # the other workloads' steps, after the headline's buffers are gone
@@ -800,7 +809,8 @@ def main():
                             "pct_of_sparse_mfma_peak_whole_step": round(100 * w2.gemm_flops / ms2 / 1e9 / PEAK_SPARSE_BF16, 2),
                             "ms_per_step_with_kernel_events": round(ms_i, 4),
                             "kernels": {k: {f: v[f] for f in ("launches_per_step", "ms_per_step", "achieved", "unit", "frac")}
-                                        for k, v in k2.items()}}
+                                        for k, v in k2.items()},
+                            "kernels_note": kernels_note(f2)}
             if not f2.mvue:   # the same step replayed from one HIP graph: what it costs without launch gaps
                 graph = f2.capture(d2["X"], d2["dY"])
                 ms_g = _time_ms(torch, graph.replay, 20)
@@ -824,6 +834,7 @@ def main():
         "pct_of_sparse_mfma_peak_whole_step": round(100 * value / PEAK_SPARSE_BF16, 2),
         "roofline": roofline,
         "kernels": kernels,
+        "kernels_note": note,
         "extras": extras,
     }
     if cpu is not None:
