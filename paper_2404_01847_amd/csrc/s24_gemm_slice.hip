@@ -44,13 +44,13 @@ void launch(const S24SliceNt &g, hipStream_t st)
 #define S24_LAUNCH_SLICE(STREAM)                                                                                                            \
     hipLaunchKernelGGL((spmm_slice_kernel<T, ACCUM, EPI, ACT, TM, TN, STREAM>), grid, block, 0, st, s24_pack(g.B, g.Av), s24_pack(g.Am, (int)g.N, (int)g.K), \
                        s24_pack((int)g.M, (int)F, tiles_n, tiles), (SliceEnds{g.Out, g.H, g.Z, g.bias}))
-    // Weights that nobody else reads (one token tile) go past the caches from 64 MB on.  A layer's smaller ones stay in the 256 MB Infinity Cache from
-    // one pass to the next, or would for a few such layers: one token, 2048 x 8192 (19 MB each) 12.8 us a forward pass past the caches and
-    // 11.1 through them; 16 tokens, the 51 MB of 11008 -> 4096 11.8 and 10.0, and where they were pushed out 13.2 and 13.3.  Larger ones mostly
-    // do not: 16 tokens, 101 MB of 4096 -> 22016 that were pushed out 19.9 and 21.0, a layer of 8192 x 28672 136 and 150.  The lowest tile
-    // has too few bytes in flight for the longer way: one token, 101 MB of 22016 -> 4096 18.5 and 15.7, pushed out 19.6 and 19.7.
+    // Weights that nobody else reads (one token tile) go past the caches from 48 MB on.  Smaller ones of a layer stay in the 256 MB Infinity Cache from
+    // one pass to the next: one token through 2048 x 8192 (19 MB each), three layers in turn, 12.8 us past the caches and 11.1 through them;
+    // 3584 x 9600 (39) 19.3 and 15.8.  Larger ones mostly do not (16 tokens, 4544 x 12288, 63 MB each, 30.9 and 32.1; one layer of 8192 x 28672
+    // 136 and 150), and a first pass over them has to push others out: 3072 x 16384 (57) 40 and 47.  Both are equal at 54 MB.  The lowest tile
+    // has too few bytes in flight for the longer way: one token, 101 MB of 22016 -> 4096 18.5 and 15.7, where they were pushed out 19.6 and 19.7.
     if constexpr (TN == 1 && TM > 1) {
-        if (tiles_n == 1 && g.M * g.K >= 57ll << 20) {   // values and index words are 9/8 byte per place
+        if (tiles_n == 1 && g.M * g.K / 8 * 9 >= 48ll << 20) {   // values and index words are 9/8 byte per place
             S24_LAUNCH_SLICE(true);
             return;
         }

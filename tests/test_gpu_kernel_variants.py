@@ -510,8 +510,8 @@ def test_few_tokens_of_many_features_on_either_kernel(s24, q):
     few_tokens(s24, 13, q, 49152)
 
 
-# below 64 MB of values and index words, from there on, and 101 MB in the lowest tile
-@pytest.mark.parametrize("q, r, variant", [(4096, 14528, (4, 1, False)), (4096, 14592, (4, 1, True)), (22016, 4096, (1, 1, False))])
+# below 48 MB of values and index words, from there on, and 101 MB in the lowest tile
+@pytest.mark.parametrize("q, r, variant", [(4096, 10880, (4, 1, False)), (4096, 10944, (4, 1, True)), (22016, 4096, (1, 1, False))])
 def test_weights_of_few_tokens_past_the_caches_and_through_them(s24, q, r, variant):
     assert few_tokens(s24, 13, q, r) == [variant]
 
